@@ -230,30 +230,28 @@ nna_status nna_out_shape(const nna_plan* plan, long long B, long long L, long lo
 
 /* out_dev[B, F, T] = STFT of x_dev[B, L] in the plan's output format; F = n_fft/2+1 for a
  * plan from nna_plan_stft, freq_bins for one from nna_plan_stft_scaled.
- * A plan from nna_plan_stft (magnitude, power or log output, not made trainable) whose hop divides n_fft an
- * even number of times >= 4 and is a multiple of 32 is computed from the folded frame: the windows of Sec.
+ * A plan from nna_plan_stft (float32, not made trainable) whose n_fft / 2 has no prime factor above 7, n_fft 64 to about
+ * 13,000, takes eq. (DFT2)'s sums in stages -- a fast Fourier transform of every windowed frame, the same result to
+ * rounding; any hop.  The other sizes are contractions with the kernel bank: with magnitude, power or log output and a hop that
+ * divides n_fft an even number of times >= 4 and is a multiple of 32, from the folded frame (the windows of Sec.
  * III-A satisfy w[n] = w[N-n], so eq. (DFT2)'s real kernels meet x[n] + x[N-n] and its imaginary kernels
- * x[n] - x[N-n] over n < N/2 only -- half the multiply-adds, the same result to rounding.  Where n_fft is also a
- * multiple of 256 the folded taps are summed by parity, E over even n and O over odd n: cos(2 pi (N/2 - k) n / N) =
- * (-1)^n cos(2 pi k n / N) (and -(-1)^n for the sine), so bin k is E + O and bin N/2 - k is E - O and only the kernels of
- * the bins below N/4 are multiplied -- a quarter of the direct form's multiply-adds.  Every other plan runs eq. (DFT2)
- * as it stands. */
+ * x[n] - x[N-n] over n < N/2 only); where n_fft is also a multiple of 256 the folded taps are summed by parity, E over
+ * even n and O over odd n, so that bins k and N/2 - k are E + O and E - O and share their kernels.  Every other plan
+ * (trainable, re-spaced axes) runs eq. (DFT2) as it stands. */
 nna_status nna_stft(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                     void* hip_stream);
 
 /* out_dev[B, n_mels, T] = Mel spectrogram of x_dev[B, L]; plan from nna_plan_mel.
- * The STFT itself is never written to memory.  Folded frames, split by tap parity where n_fft is a multiple of 128, as
- * for nna_stft, unless the plan was made trainable (a plan that is folded but not split also runs the direct form when
- * a filter has weight on bin n_fft/2). */
+ * The STFT itself is never written to memory.  The forms of nna_stft: a fast Fourier transform where n_fft allows it, else
+ * folded frames, split by tap parity where n_fft is a multiple of 128, else (and on trainable plans) the direct form. */
 nna_status nna_mel(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                    void* hip_stream);
 
 /* nna_mel that also hands out the spectrogram its filterbank is applied to (Fig. 3: the STFT layer's
  * output feeding the Mel layer), from the one contraction: mel_dev[B, n_mels, T] as nna_mel writes it and
  * spec_dev[B, n_fft/2+1, T] = |X|^power (power 2: the power spectrogram; power 1: the magnitude).  For a
- * caller that wants both, this is one kernel launch of nna_mel's cost plus the spectrogram's stores (the first pass
- * of a plan with more than 128 filters then sweeps every bin; a plan that does not run split by tap parity takes the
- * direct contraction for this call).
+ * caller that wants both, this is one kernel launch of nna_mel's cost plus the spectrogram's stores (a plan that runs
+ * neither the fast Fourier transform nor split by tap parity takes the direct contraction for this call).
  * Plan from nna_plan_mel (float32); errors as nna_mel, NNA_ERR_INVALID_ARG for a NULL spec_dev. */
 nna_status nna_mel_with_stft(const nna_plan* plan, const float* x_dev, long long B, long long L,
                              float* mel_dev, float* spec_dev, void* hip_stream);
@@ -496,8 +494,9 @@ nna_status nna_plan_spectral_kernels(const nna_plan* plan, double* host_out, siz
  * taps they do not skip included) and algorithmic flops per frame (non-zero taps only:
  * 2*K*rows_nonzero for the DFT bank, 4*sum_k N_k for the CQT, plus 2*nnz(W) for Mel;
  * nna_plan_cqt1992: the DFT plus 8 per (constant-Q bin, kept DFT bin)).  The algorithmic figure of an
- * STFT or Mel plan is that of eq. (DFT2) taken directly, 2 K^2; a plan that runs folded frames (see
- * nna_stft) executes about half of it, K^2 + 2K.
+ * STFT or Mel plan is that of eq. (DFT2) taken directly, 2 K^2; the executed figure is that of the contraction the plan's
+ * kernel bank stands for (folded: K^2 + 2K, split by tap parity: K^2 / 2 + 4K), also where the call takes the sums by a
+ * fast Fourier transform instead, about 2.5 K log2 K operations.
  */
 nna_status nna_plan_info(const nna_plan* plan, int* kind, long long* bank_rows, long long* taps,
                          long long* out_bins, double* executed_flops_per_frame,

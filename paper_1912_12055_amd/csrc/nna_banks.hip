@@ -101,6 +101,7 @@ void build_stft_bank_fold(nna_plan* p) {
     // below N/4, two fragments per group (Re, Im kernels of the tile's bins).
     p->fold_split = true;
     p->n_rt_split = N / 128;
+    if (p->fft) return;
     p->bankf_floats = (size_t)(G * p->n_rt_split + ST_NKG) * 2 * 64 * 4;
     p->h_bankf.assign(p->bankf_floats, 0.0f);
     DftTable tab(N, p->window);
@@ -131,6 +132,16 @@ void build_stft_bank_fold(nna_plan* p) {
     p->wmid = (float)tab.w[N / 2];
     return;
   }
+  // per frame: N/2 folded taps x all rows of the row tiles, and the N multiply-adds of bin N/2
+  p->exec_flops_fold = 2.0 * ((double)p->n_chunks * nj2 * ST_KC) * (double)p->n_rt * ST_ROWS + 2.0 * N;
+  // One more halving for the plain STFT (see nna_kernels_fold.hip): row tiles of the bins below N/4 only -- N/4 must be
+  // a whole number of 64-bin row tiles -- and taps whose parity is that of their position in a fragment (even hop).
+  p->fold_split = p->kind == NNA_KIND_STFT && N % 256 == 0 && p->hop % 2 == 0;
+  if (p->fold_split) {
+    p->n_rt_split = p->n_rt / 2;
+    p->exec_flops_split = 2.0 * ((double)p->n_chunks * nj2 * ST_KC) * (double)(p->n_rt / 2) * ST_ROWS + 4.0 * N;
+  }
+  if (p->fft) return;
   p->bankf_floats = (size_t)(G * p->n_rt + ST_NKG) * ST_RB * 64 * 4;
   p->h_bankf.assign(p->bankf_floats, 0.0f);
   DftTable tab(N, p->window);
@@ -155,13 +166,7 @@ void build_stft_bank_fold(nna_plan* p) {
   p->h_wn.assign((size_t)(J + 3) / 4 * 4 * p->hop, 0.0f);
   for (int n = 0; n < N; ++n) p->h_wn[n] = (float)((n & 1) ? -tab.w[n] : tab.w[n]);
   p->wmid = (float)tab.w[N / 2];
-  // per frame: N/2 folded taps x all rows of the row tiles, and the N multiply-adds of bin N/2
-  p->exec_flops_fold = 2.0 * ((double)p->n_chunks * nj2 * ST_KC) * (double)p->n_rt * ST_ROWS + 2.0 * N;
-  // One more halving for the plain STFT (see nna_kernels_fold.hip): row tiles of the bins below N/4 only -- N/4 must be
-  // a whole number of 64-bin row tiles -- and taps whose parity is that of their position in a fragment (even hop).
-  p->fold_split = p->kind == NNA_KIND_STFT && N % 256 == 0 && p->hop % 2 == 0;
   if (p->fold_split) {
-    p->n_rt_split = p->n_rt / 2;
     // bin N/4: cos(pi n / 2) = 1, 0, -1, 0, ...; -sin(pi n / 2) = 0, -1, 0, 1, ...
     const size_t tbl = (size_t)(J + 3) / 4 * 4 * p->hop;
     p->h_wq.assign(2 * tbl, 0.0f);
@@ -170,7 +175,42 @@ void build_stft_bank_fold(nna_plan* p) {
       p->h_wq[n] = (float)((n & 1) ? 0.0 : (n & 2) ? -w : w);
       p->h_wq[tbl + n] = (float)((n & 1) ? ((n & 2) ? w : -w) : 0.0);
     }
-    p->exec_flops_split = 2.0 * ((double)p->n_chunks * nj2 * ST_KC) * (double)(p->n_rt / 2) * ST_ROWS + 4.0 * N;
+  }
+}
+
+// Tables of the fast Fourier transform: half the window (the bins are sums and differences of two values of the
+// half-length transform, divided by two), the roots of unity, and the radices of the general kernel.
+void build_fft_tables(nna_plan* p) {
+  const int N = p->K;
+  if (p->freq_scale || p->precision != 0 || !nna::fft_radices(N, p->fft_radix, p->fft_n_radix)) return;
+  p->fft = true;
+  p->h_fft_win.resize(N);
+  p->h_fft_tw.resize(2 * (size_t)N);
+  DftTable tab(N, p->window);
+  for (int k = 0; k < N; ++k) {
+    p->h_fft_win[k] = (float)(0.5 * tab.w[k]);
+    p->h_fft_tw[2 * k] = (float)tab.c[k];
+    p->h_fft_tw[2 * k + 1] = (float)tab.s[k];
+  }
+  std::vector<int> lane;
+  nna::fft_lane_twiddles(N / 2, lane);
+  for (const int k : lane)
+    for (const float v : {p->h_fft_tw[2 * k], p->h_fft_tw[2 * k + 1]}) p->h_fft_lane.push_back(v);
+}
+
+// The Mel filters as the transform's kernel reads them: per filter the bins from its first to its last weight, in quads.
+void build_fft_mel(nna_plan* p) {
+  if (!p->fft) return;
+  const int F = p->n_half + 1;
+  for (int m = 0; m < p->n_mels; ++m) {
+    const float* W = &p->h_melW[(size_t)m * F];
+    int lo = 0, hi = F;
+    while (lo < F && W[lo] == 0.0f) ++lo;
+    while (hi > lo && W[hi - 1] == 0.0f) --hi;
+    if (lo >= hi) lo = hi = 0;
+    const int quads = (hi - lo + 3) / 4;
+    for (const int v : {lo, quads, (int)(p->h_fft_melw.size() / 4), 0}) p->h_fft_mel.push_back(v);
+    for (int i = 0; i < 4 * quads; ++i) p->h_fft_melw.push_back(lo + i < hi ? W[lo + i] : 0.0f);
   }
 }
 

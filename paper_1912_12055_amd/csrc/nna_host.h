@@ -90,7 +90,24 @@ struct nna_plan {
 
   double exec_flops = 0, alg_flops = 0;
 
-  // Folded-frame contraction (nna_kernels_fold.hip): plain DFT bank, hop dividing n_fft an even number of
+  // Fast Fourier transform of each frame (nna_kernels_fft.hip): plain DFT bins with fixed float32 kernels, N/2 free of
+  // prime factors above 7.  The direct bank stays (inspection, trainable plans).
+  bool fft = false;
+  int fft_radix[16] = {}, fft_n_radix = 0;
+  std::vector<float> h_fft_win;          // [N] half the window
+  std::vector<float> h_fft_tw;           // [N][2] cos, sin of 2 pi k / N
+  std::vector<float> h_fft_lane;         // the same roots in the order the lanes of the kernel for this N take them
+  std::vector<int> h_fft_mel;            // Mel: [n_mels][4] first bin, quads of bins, first quad of weights, 0
+  std::vector<float> h_fft_melw;         // Mel: the filters' weights between their first and last bin, quads
+  float* d_fft_win = nullptr;
+  float* d_fft_tw = nullptr;
+  float* d_fft_lane = nullptr;
+  int* d_fft_mel = nullptr;
+  float* d_fft_melw = nullptr;
+  bool runs_fft() const { return fft && !d_wrm && precision == 0; }
+
+  // Folded-frame contraction (nna_kernels_fold.hip), for the sizes the transform above does not take (for the others only
+  // the facts nna_plan_info reports about the contraction are kept): plain DFT bank, hop dividing n_fft an even number of
   // times >= 4.  The direct bank stays (inspection, trainable plans, complex / phase output).
   bool fold = false;
   double exec_flops_fold = 0;
@@ -101,7 +118,8 @@ struct nna_plan {
   float* d_wn = nullptr;
   float* d_melwf = nullptr;            // Mel weights as the folded kernel's second MFMA reads them
   unsigned char* d_mel_maskf = nullptr;
-  bool runs_folded() const { return fold && !d_wrm && precision == 0; }
+  bool folded_form() const { return fold && !d_wrm && precision == 0; }
+  bool runs_folded() const { return folded_form() && !fft; }
   // STFT plans whose n_fft is a multiple of 256 and whose hop is even: the folded contraction split once more by tap
   // parity (bins below N/4 only; their partners N/2 - k from the same sums).  h_wq / d_wq: the two weight tables of
   // bin N/4, [2][J rounded up to 4][hop]
@@ -112,7 +130,8 @@ struct nna_plan {
   double exec_flops_split = 0;
   std::vector<float> h_wq;
   float* d_wq = nullptr;
-  bool runs_split() const { return runs_folded() && fold_split; }
+  bool split_form() const { return folded_form() && fold_split; }
+  bool runs_split() const { return split_form() && !fft; }
   // Mel plans that run split: the split kernel's own pass table, the filters' weights on bin N/4 (all zero: mel_q_any = 0)
   int* d_mel_pass_rtf = nullptr;
   int* d_mel_pass_rtf_spec = nullptr;  // the same with the first pass sweeping every tile (nna_mel_with_stft)
@@ -337,6 +356,8 @@ void for_each_cqt_fragment(const nna_plan* p, Fn fn) {
 
 void build_stft_bank(nna_plan* p);
 void build_stft_bank_fold(nna_plan* p);
+void build_fft_tables(nna_plan* p);      // sets p->fft if the plan qualifies
+void build_fft_mel(nna_plan* p);
 bool build_stft_bank_f16(nna_plan* p);
 void build_mel_weights(nna_plan* p, double fmin, double fmax, int scale, int norm_area);
 MelDeviceLayout layout_mel(nna_plan* p);

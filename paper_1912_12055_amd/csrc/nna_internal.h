@@ -121,6 +121,33 @@ struct StftParams {
   int row_offset;             // the plan's first output row is row row_offset of each waveform's output
 };
 
+// ---- STFT / Mel by fast Fourier transform (nna_kernels_fft.hip) -------------------------------
+constexpr int FFT_MODE_POWER = 0;  // magnitude, power or log
+constexpr int FFT_MODE_CPLX = 1;   // (Re, Im) rows or the phase
+constexpr int FFT_MODE_MEL = 2;    // Mel bands, the spectrogram beside them if `spec` is set
+
+struct FftParams {
+  FrameGeom g;
+  const float* win;    // [N] half the window
+  const float2* tw;    // [N] (cos, sin)(2 pi k / N)
+  const float4* tw_lane;  // sizes with a kernel of their own: roots of unity in the order fft_lane_twiddles lists
+  float* out;
+  float* spec;         // Mel: optional |X|^power output [B][M + 1][T]
+  const int4* mel;     // [n_mels]: first bin, quads of bins, first quad of weights
+  const float4* melw;
+  int n_mels, mel_power;
+  int M;               // N / 2
+  int fmt;
+  int radix[16], n_radix;  // passes of the general kernel
+  int pitch, lg_tf;    // set by the launcher: LDS words per frame, log2 of the frames per tile
+  long long n_tiles;
+};
+// the radices the general kernel takes N/2 apart with; false: N has a prime factor above 7, or does not fit in LDS
+bool fft_radices(int n_fft, int (&radix)[16], int& n_radix);
+void fft_lane_twiddles(int M, std::vector<int>& index);  // indices k of e^{-2 pi i k / N}; empty: no kernel of its own
+hipError_t launch_stft_fft(FftParams& p, int mode, hipStream_t stream);
+hipError_t fft_kernels_init();  // per-process function attributes of nna_kernels_fft.hip
+
 struct Stft16Params {
   FrameGeom g;
   const _Float16* bank;  // [row tile][chunk][hop-shift][H_ROWS][H_KC] float16

@@ -46,7 +46,16 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
       s = upload(&p->d_bank16, p->h_bank16.data(), p->bank16_halves * sizeof(_Float16), "float16 kernel bank");
     if (s == NNA_OK && p->precision == NNA_PREC_F16 && p->bank16s_halves)
       s = upload(&p->d_bank16s, p->h_bank16s.data(), p->bank16s_halves * sizeof(_Float16), "float16 kernel bank (streaming order)");
-    if (s == NNA_OK && p->fold) {
+    if (s == NNA_OK && p->fft) {
+      s = upload(&p->d_fft_win, p->h_fft_win.data(), p->h_fft_win.size() * sizeof(float), "window");
+      if (s == NNA_OK) s = upload(&p->d_fft_tw, p->h_fft_tw.data(), p->h_fft_tw.size() * sizeof(float), "twiddles");
+      if (s == NNA_OK) s = upload(&p->d_fft_lane, p->h_fft_lane.data(), p->h_fft_lane.size() * sizeof(float), "twiddles (lane order)");
+      if (s == NNA_OK && p->kind == NNA_KIND_MEL) {
+        s = upload(&p->d_fft_mel, p->h_fft_mel.data(), p->h_fft_mel.size() * sizeof(int), "mel filter table");
+        if (s == NNA_OK) s = upload(&p->d_fft_melw, p->h_fft_melw.data(), p->h_fft_melw.size() * sizeof(float), "mel filter weights");
+      }
+    }
+    if (s == NNA_OK && p->fold && !p->fft) {
       s = upload(&p->d_bankf, p->h_bankf.data(), p->bankf_floats * sizeof(float), "folded kernel bank");
       if (s == NNA_OK) s = upload(&p->d_wn, p->h_wn.data(), p->h_wn.size() * sizeof(float), "alternating window");
       if (s == NNA_OK && p->fold_split) s = upload(&p->d_wq, p->h_wq.data(), p->h_wq.size() * sizeof(float), "weights of bin N/4");
@@ -246,6 +255,7 @@ nna_status nna_plan_stft(nna_plan** plan, int sr, int n_fft, int hop, nna_window
     p->K = n_fft;
     p->pad = center ? n_fft / 2 : 0;
     build_stft_bank(p);
+    build_fft_tables(p);
     if (fmt == NNA_OUT_MAGNITUDE || fmt == NNA_OUT_POWER || fmt == NNA_OUT_LOG) build_stft_bank_fold(p);
   } catch (const std::bad_alloc&) {
     delete p;
@@ -360,8 +370,10 @@ nna_status nna_plan_mel(nna_plan** plan, int sr, int n_fft, int hop, nna_window 
     p->n_mels = n_mels;
     p->mel_power = power == 1.0 ? 1 : 2;
     build_stft_bank(p);
+    build_fft_tables(p);
     build_stft_bank_fold(p);
     build_mel_weights(p, fmin, fmax, scale, norm_area);
+    build_fft_mel(p);
     mel = layout_mel(p);
   } catch (const std::bad_alloc&) {
     delete p;
@@ -758,8 +770,8 @@ nna_status nna_plan_info(const nna_plan* plan, int* kind, long long* bank_rows, 
   if (taps) *taps = plan->K;
   if (out_bins) *out_bins = plan->out_rows();
   if (executed_flops_per_frame)
-    *executed_flops_per_frame = plan->runs_split()    ? plan->exec_flops_split
-                                : plan->runs_folded() ? plan->exec_flops_fold
+    *executed_flops_per_frame = plan->split_form()    ? plan->exec_flops_split
+                                : plan->folded_form() ? plan->exec_flops_fold
                                 : plan->runs_cqfold() ? plan->exec_flops_cqf
                                                       : plan->exec_flops;
   if (algorithmic_flops_per_frame) *algorithmic_flops_per_frame = plan->alg_flops;
@@ -802,6 +814,11 @@ void nna_plan_destroy(nna_plan* plan) {
         if (ev) (void)hipEventDestroy(ev);
       (void)hipFree(plan->d_bank);
       (void)hipFree(plan->d_bank16);
+      (void)hipFree(plan->d_fft_win);
+      (void)hipFree(plan->d_fft_tw);
+      (void)hipFree(plan->d_fft_lane);
+      (void)hipFree(plan->d_fft_mel);
+      (void)hipFree(plan->d_fft_melw);
       (void)hipFree(plan->d_bankf);
       (void)hipFree(plan->d_fir_he);
       (void)hipFree(plan->d_fir_ho);

@@ -25,6 +25,7 @@ hipError_t ensure_kernels_init(int device) {
   if (!g_init_done[device]) {
     hipError_t e = nna::kernels_init();
     if (e == hipSuccess) e = nna::cqf_kernels_init();
+    if (e == hipSuccess) e = nna::fft_kernels_init();
     if (e != hipSuccess) return e;
     void* ptr = nullptr;
     e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
@@ -120,6 +121,34 @@ nna_status run_stft_core(const nna_plan* plan, int kind, const float* x, long lo
     hipError_t e = guard.enter(plan->device);
     if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
     e = nna::launch_stft16(P, reinterpret_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return fail_hip(e, "kernel launch");
+    return NNA_OK;
+  }
+  if (plan->runs_fft() && (kind == NNA_KIND_STFT || kind == NNA_KIND_MEL)) {
+    nna::FftParams P;
+    std::memset(&P, 0, sizeof(P));
+    P.g = make_geom(plan, x, B, L, T);
+    P.win = plan->d_fft_win;
+    P.tw = reinterpret_cast<const float2*>(plan->d_fft_tw);
+    P.tw_lane = reinterpret_cast<const float4*>(plan->d_fft_lane);
+    P.out = out;
+    P.spec = spec_out;
+    P.M = plan->K / 2;
+    P.fmt = plan->fmt;
+    P.n_radix = plan->fft_n_radix;
+    std::copy(plan->fft_radix, plan->fft_radix + 16, P.radix);
+    int mode = plan->fmt == NNA_OUT_COMPLEX || plan->fmt == NNA_OUT_PHASE ? nna::FFT_MODE_CPLX : nna::FFT_MODE_POWER;
+    if (kind == NNA_KIND_MEL) {
+      mode = nna::FFT_MODE_MEL;
+      P.mel = reinterpret_cast<const int4*>(plan->d_fft_mel);
+      P.melw = reinterpret_cast<const float4*>(plan->d_fft_melw);
+      P.n_mels = plan->n_mels;
+      P.mel_power = plan->mel_power;
+    }
+    DeviceGuard guard;
+    hipError_t e = guard.enter(plan->device);
+    if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
+    e = nna::launch_stft_fft(P, mode, reinterpret_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return NNA_OK;
   }
