@@ -193,7 +193,7 @@ nna_status nna_plan_cqt2010v2(nna_plan** plan, int sr, int hop, double fmin, int
 
 /*
  * Constant-Q plan with frequency-domain kernels (Sec. III-C "CQT using neural networks",
- * eqs. (Parseval), (CQT1992), Fig. 5; the paper's CQT1992 layer).  Two stages, run in one kernel:
+ * eqs. (Parseval), (CQT1992), Fig. 5; the paper's CQT1992 layer).  Two stages:
  *   1. the un-windowed STFT X_t[k], k = 0..n_fft/2, of the waveform (the DFT bank of nna_plan_stft
  *      with a rectangular window; the constant-Q window lives in the kernels);
  *   2. X_cq[q, t] = (1/n_fft) sum_{k=0}^{n_fft/2} X_t[k] Y[q, k], followed by the output format.
@@ -202,8 +202,9 @@ nna_status nna_plan_cqt2010v2(nna_plan** plan, int sr, int hop, double fmin, int
  * two sides agree when k runs over all n_fft bins.  Only the half k <= n_fft/2 is kept, as in the
  * paper, so the result approximates nna_cqt's (to about 1e-4 of the peak for 12 bins per octave well
  * below the Nyquist frequency, a few 1e-3 for 6 bins per octave reaching 0.8 of it); no
- * sparsity threshold is applied to Y.  Cost per frame is that of an STFT with n_fft taps, for every
- * 64 constant-Q bins: the paper itself calls this form inefficient and offers it for research.
+ * sparsity threshold is applied to Y.  While the kernels are fixed the two stages run as one contraction with the composed
+ * kernels c_q[n] = (1/n_fft) sum_{k <= n_fft/2} Y[q, k] exp(-2 pi i k n / n_fft), 4 n_bins n_fft flops per frame; a plan made
+ * trainable runs both stages, at the cost of an STFT with n_fft taps for every 64 constant-Q bins.
  *   n_fft  0 = the smallest power of two >= the longest kernel; else a power of two >= it, <= 65536
  * Output bins = n_bins; frames as for nna_plan_cqt with n_taps = n_fft.
  */

@@ -250,6 +250,14 @@ nna_status nna_plan_trainable(nna_plan* plan) {
       if ((s = nna_plan_trainable(sub)) != NNA_OK) return s;
     return NNA_OK;
   }
+  if (plan->bank_idle() && !plan->d_bank) {
+    try {
+      const std::vector<float> bank = stft_bank_values(plan);
+      if ((s = upload(&plan->d_bank, bank.data(), plan->bank_floats * sizeof(float), "kernel bank")) != NNA_OK) return s;
+    } catch (const std::bad_alloc&) {
+      return fail(NNA_ERR_ALLOC, "out of host memory while building the DFT bank");
+    }
+  }
   plan->rows_pad = plan->n_rt * ST_ROWS;
   plan->kp = (plan->K + nna::BW_NT - 1) / nna::BW_NT * nna::BW_NT;
   const size_t bytes = (size_t)plan->rows_pad * plan->kp * sizeof(float);

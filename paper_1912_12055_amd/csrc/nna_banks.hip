@@ -53,7 +53,17 @@ void build_stft_bank(nna_plan* p) {
   const long long G = (long long)p->n_chunks * p->nj * ST_NKG;  // fragment groups per row tile
   p->bank_groups = G * p->n_rt;
   p->bank_floats = (size_t)(p->bank_groups + ST_NKG) * ST_RB * 64 * 4;  // + prefetch overrun
-  p->h_bank.assign(p->bank_floats, 0.0f);
+  const double k_exec = (double)p->n_chunks * p->nj * ST_KC;
+  p->exec_flops = 2.0 * k_exec * (double)p->n_rt * ST_ROWS;
+  // plain DFT: N non-zero rows (cos 0..N/2, sin 1..N/2-1) x N taps; re-spaced: 2 rows per bin
+  p->alg_flops = p->freq_scale ? 2.0 * (double)N * 2.0 * (double)p->n_half : 2.0 * (double)N * (double)N;
+}
+
+// The bank's values in the layout build_stft_bank chose.
+std::vector<float> stft_bank_values(const nna_plan* p) {
+  const int N = p->K;
+  const long long G = (long long)p->n_chunks * p->nj * ST_NKG;
+  std::vector<float> bank(p->bank_floats, 0.0f);
   DftTable tab(N, p->window);
   for (int rt = 0; rt < p->n_rt; ++rt)
     for (int c = 0; c < p->n_chunks; ++c)
@@ -64,16 +74,13 @@ void build_stft_bank(nna_plan* p) {
             for (int lane = 0; lane < 64; ++lane) {
               const int h = lane >> 5, r = lane & 31;
               const int pr = rt * ST_ROWS + rb * 32 + r;
-              float* dst = &p->h_bank[((((size_t)rt * G + g) * ST_RB + rb) * 64 + lane) * 4];
+              float* dst = &bank[((((size_t)rt * G + g) * ST_RB + rb) * 64 + lane) * 4];
               for (int e = 0; e < 4; ++e)
                 dst[e] = (float)(p->freq_scale ? scaled_value(p, pr, stft_tap(p, c, j, kg, h, e))
                                                : stft_packed_value(tab, p->n_half, pr, stft_tap(p, c, j, kg, h, e)));
             }
         }
-  const double k_exec = (double)p->n_chunks * p->nj * ST_KC;
-  p->exec_flops = 2.0 * k_exec * (double)p->n_rt * ST_ROWS;
-  // plain DFT: N non-zero rows (cos 0..N/2, sin 1..N/2-1) x N taps; re-spaced: 2 rows per bin
-  p->alg_flops = p->freq_scale ? 2.0 * (double)N * 2.0 * (double)p->n_half : 2.0 * (double)N * (double)N;
+  return bank;
 }
 
 // The bank of the folded-frame kernel: Re and Im kernels of eq. (DFT2) over the taps n < N/2 only (they
@@ -485,20 +492,25 @@ void fft_pow2(std::vector<std::complex<double>>& a) {
 // and eq. (CQT1992) keeps k = 0..K/2.  Y[q, k] = conj(B_q[k]).  In real arithmetic, per bin k:
 //   Re X_cq += (Xr Yr - Xi Yi)/K,   Im X_cq += (Xr Yi + Xi Yr)/K.
 // Packed STFT rows: 2s = Re X[s], 2s+1 = Im X[s]; slot 0 holds the two purely real bins 0 and K/2.
+// a = B_q, K values
+static void cqt1992_spectrum(const nna_plan* p, int q, std::vector<std::complex<double>>& a) {
+  std::fill(a.begin(), a.end(), std::complex<double>(0.0, 0.0));
+  double wsum = 0;
+  for (long long n = 0; n < p->Nk[q]; ++n) wsum += window_value(p->cq_window, n, p->Nk[q]);
+  for (long long n = 0; n < p->Nk[q]; ++n) {
+    const double w = window_value(p->cq_window, n, p->Nk[q]) / wsum;
+    a[p->sk[q] + n] = std::polar(w, 2.0 * kPi * p->Q * (double)n / (double)p->Nk[q]);  // conj(kappa)
+  }
+  fft_pow2(a);
+}
+
 void build_cqt1992_matrix(nna_plan* p) {
   const int K = p->K, n_half = p->n_half, R = 2 * p->n_bins, C = 2 * n_half;
   p->h_linW.assign((size_t)R * C, 0.0f);
   std::vector<std::complex<double>> a(K);
   const double inv = 1.0 / (double)K;
   for (int q = 0; q < p->n_bins; ++q) {
-    std::fill(a.begin(), a.end(), std::complex<double>(0.0, 0.0));
-    double wsum = 0;
-    for (long long n = 0; n < p->Nk[q]; ++n) wsum += window_value(p->cq_window, n, p->Nk[q]);
-    for (long long n = 0; n < p->Nk[q]; ++n) {
-      const double w = window_value(p->cq_window, n, p->Nk[q]) / wsum;
-      a[p->sk[q] + n] = std::polar(w, 2.0 * kPi * p->Q * (double)n / (double)p->Nk[q]);  // conj(kappa)
-    }
-    fft_pow2(a);
+    cqt1992_spectrum(p, q, a);
     float* re_row = &p->h_linW[(size_t)(2 * q) * C];
     float* im_row = &p->h_linW[(size_t)(2 * q + 1) * C];
     for (int s = 0; s <= n_half; ++s) {
@@ -704,6 +716,28 @@ void build_conv_bank(nna_plan* p, ValueFn value) {
     }
   });
   p->exec_flops = 2.0 * (double)exec_groups * CQ_KC * CQ_ROWS;
+}
+
+// Both stages of eq. (CQT1992) as one: X_cq[q] = sum_n x[n] c_q[n] with c_q[n] = (1/K) sum_{k <= K/2} Y[q, k] e^{-2 pi i k n / K},
+// the kernel of eq. (CQT) less its negative frequencies.  Dense in n, so a bank of 2 n_bins rows x K taps: for plans whose
+// kernels are fixed 2 n_bins / K of the two-stage form's multiply-adds.  `c` is a plan of kind CQT with p's geometry.
+void build_cqt1992_composed(const nna_plan* p, nna_plan* c) {
+  const int K = p->K;
+  std::vector<double> rows((size_t)2 * p->n_bins * K);
+  std::vector<std::complex<double>> a(K);
+  for (int q = 0; q < p->n_bins; ++q) {
+    cqt1992_spectrum(p, q, a);
+    for (int k = 0; k < K; ++k) a[k] = k <= K / 2 ? std::conj(a[k]) : 0.0;
+    fft_pow2(a);
+    for (int n = 0; n < K; ++n) {
+      rows[(size_t)(2 * q) * K + n] = a[n].real() / K;
+      rows[(size_t)(2 * q + 1) * K + n] = a[n].imag() / K;
+    }
+  }
+  c->conv_rows = 2 * p->n_bins;
+  c->row_s.assign(c->conv_rows, 0);
+  c->row_e.assign(c->conv_rows, K);
+  build_conv_bank(c, [&](int row, long long tap) { return row < c->conv_rows && tap < K ? rows[(size_t)row * K + tap] : 0.0; });
 }
 
 void build_cqt_bank(nna_plan* p) {

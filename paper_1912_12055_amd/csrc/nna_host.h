@@ -62,6 +62,10 @@ struct nna_plan {
   size_t lin_frag_floats = 0;
   int lin_blocks = 4;  // 32-row output blocks per pass of the second contraction (4 or 6)
 
+  // ... and both stages as one bank, for as long as the kernels are fixed: a plan of kind CQT that this one owns
+  nna_plan* composed = nullptr;
+  bool runs_composed() const { return composed && !d_wrm; }
+
   // CQT
   int n_bins = 0, bpo = 0, n_rb = 0;
   int k_first = 0;  // bin k sits at fmin 2^((k_first + k) / bpo): non-zero for the octaves of a downsampling plan
@@ -139,7 +143,9 @@ struct nna_plan {
   int mel_q_any = 0;
   int n_rt_split = 0;  // row tiles of the split launch (STFT: 64 bins each, Mel: 32)
 
-  // host copy of the packed bank (host-only plans keep it; device plans drop it after upload)
+  // Packed bank: host-only plans keep the host copy, device plans drop it after upload.  A plan that does not run its bank (fast
+  // Fourier transform, composed kernels) holds neither: nna_plan_bank computes the values, nna_plan_trainable uploads them.
+  bool bank_idle() const { return fft || kind == NNA_KIND_CQT1992; }
   std::vector<float> h_bank;
   size_t bank_floats = 0;
 
@@ -354,7 +360,8 @@ void for_each_cqt_fragment(const nna_plan* p, Fn fn) {
   }
 }
 
-void build_stft_bank(nna_plan* p);
+void build_stft_bank(nna_plan* p);       // geometry and flop counts; the values come from stft_bank_values
+std::vector<float> stft_bank_values(const nna_plan* p);
 void build_stft_bank_fold(nna_plan* p);
 void build_fft_tables(nna_plan* p);      // sets p->fft if the plan qualifies
 void build_fft_mel(nna_plan* p);
@@ -363,6 +370,7 @@ void build_mel_weights(nna_plan* p, double fmin, double fmax, int scale, int nor
 MelDeviceLayout layout_mel(nna_plan* p);
 void build_cqt1992_matrix(nna_plan* p);
 MelDeviceLayout layout_cqt1992(nna_plan* p);
+void build_cqt1992_composed(const nna_plan* p, nna_plan* c);
 void build_cqt_bank(nna_plan* p);
 void build_cqt_bank_fold(nna_plan* p);  // sets p->cq_fold if the plan qualifies
 // the decimation filter of `fir_taps` taps: its taps, their split by parity for the decimation kernel, and the

@@ -41,7 +41,7 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
       delete p;
       return fail_hip(e, "kernel attribute setup");
     }
-    nna_status s = upload(&p->d_bank, p->h_bank.data(), p->bank_floats * sizeof(float), "kernel bank");
+    nna_status s = p->bank_idle() ? NNA_OK : upload(&p->d_bank, p->h_bank.data(), p->bank_floats * sizeof(float), "kernel bank");
     if (s == NNA_OK && p->precision == NNA_PREC_F16)
       s = upload(&p->d_bank16, p->h_bank16.data(), p->bank16_halves * sizeof(_Float16), "float16 kernel bank");
     if (s == NNA_OK && p->precision == NNA_PREC_F16 && p->bank16s_halves)
@@ -256,6 +256,7 @@ nna_status nna_plan_stft(nna_plan** plan, int sr, int n_fft, int hop, nna_window
     p->pad = center ? n_fft / 2 : 0;
     build_stft_bank(p);
     build_fft_tables(p);
+    if (!p->bank_idle()) p->h_bank = stft_bank_values(p);
     if (fmt == NNA_OUT_MAGNITUDE || fmt == NNA_OUT_POWER || fmt == NNA_OUT_LOG) build_stft_bank_fold(p);
   } catch (const std::bad_alloc&) {
     delete p;
@@ -289,6 +290,7 @@ nna_status nna_plan_stft_prec(nna_plan** plan, int sr, int n_fft, int hop, nna_w
     p->pad = center ? n_fft / 2 : 0;
     p->precision = NNA_PREC_F16;
     build_stft_bank(p);
+    p->h_bank = stft_bank_values(p);
     if (!build_stft_bank_f16(p)) {
       delete p;
       return fail(NNA_ERR_UNSUPPORTED,
@@ -337,6 +339,7 @@ nna_status nna_plan_stft_scaled(nna_plan** plan, int sr, int n_fft, int hop, nna
       p->sigma[k] = freq_scale == NNA_FREQ_LINEAR ? (fmax - fmin) * N / (mu * sr) * k + fmin * N / sr
                                                   : fmin * N / sr * std::pow(fmax / fmin, k / mu);
     build_stft_bank(p);
+    p->h_bank = stft_bank_values(p);
   } catch (const std::bad_alloc&) {
     delete p;
     return fail(NNA_ERR_ALLOC, "out of host memory while building the DFT bank");
@@ -371,6 +374,7 @@ nna_status nna_plan_mel(nna_plan** plan, int sr, int n_fft, int hop, nna_window 
     p->mel_power = power == 1.0 ? 1 : 2;
     build_stft_bank(p);
     build_fft_tables(p);
+    if (!p->bank_idle()) p->h_bank = stft_bank_values(p);
     build_stft_bank_fold(p);
     build_mel_weights(p, fmin, fmax, scale, norm_area);
     build_fft_mel(p);
@@ -396,6 +400,7 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
   nna_plan* p = new (std::nothrow) nna_plan;
   if (!p) return fail(NNA_ERR_ALLOC, "out of host memory");
   MelDeviceLayout lin;
+  nna_plan* c = nullptr;  // the composed kernels
   try {
     p->kind = NNA_KIND_CQT1992;
     p->device = device;
@@ -439,9 +444,28 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
     build_stft_bank(p);
     build_cqt1992_matrix(p);
     lin = layout_cqt1992(p);
+    c = new nna_plan;
+    c->kind = NNA_KIND_CQT;
+    c->device = device;
+    c->sr = sr;
+    c->hop = hop;
+    c->center = center;
+    c->window = win;
+    c->fmt = fmt;
+    c->n_bins = n_bins;
+    c->bpo = bins_per_octave;
+    c->K = p->K;
+    c->pad = p->pad;
+    build_cqt1992_composed(p, c);
   } catch (const std::bad_alloc&) {
+    delete c;
     delete p;
-    return fail(NNA_ERR_ALLOC, "out of host memory while building the DFT bank and the spectral kernels");
+    return fail(NNA_ERR_ALLOC, "out of host memory while building the spectral kernels");
+  }
+  nna_status s = finish_plan(c, &p->composed, nullptr);
+  if (s != NNA_OK) {
+    delete p;
+    return s;
   }
   return finish_plan(p, plan, &lin);
 }
@@ -662,7 +686,10 @@ nna_status nna_plan_bank(const nna_plan* plan, double* host_out, size_t cap) {
   std::vector<float> tmp;
   const float* src = nullptr;
   try {
-    if (plan->device >= 0) {
+    if (plan->bank_idle() && !plan->d_bank) {
+      tmp = stft_bank_values(plan);
+      src = tmp.data();
+    } else if (plan->device >= 0) {
       tmp.resize(plan->bank_floats);
       DeviceGuard guard;
       hipError_t e = guard.enter(plan->device);
@@ -799,6 +826,7 @@ void nna_plan_destroy(nna_plan* plan) {
   if (!plan) return;
   for (nna_plan* sub : plan->octave) nna_plan_destroy(sub);
   nna_plan_destroy(plan->fir);
+  nna_plan_destroy(plan->composed);
   if (plan->device >= 0) {
     DeviceGuard guard;
     if (guard.enter(plan->device) == hipSuccess) {

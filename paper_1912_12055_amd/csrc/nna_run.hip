@@ -349,6 +349,19 @@ nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long 
   return NNA_OK;
 }
 
+// A plan with frequency-domain kernels: both stages as one bank while the kernels are fixed -- 4 n_bins K flops per frame where
+// the two stages take 2 K^2 for every 64 or 96 bins (16 x 220,500 samples, 84 bins, K = 32,768: 120 ms -> 566 us) -- and the
+// two-stage kernel once they are trainable, each stage then being a weight of its own.
+nna_status run_cqt1992(const nna_plan* plan, const float* x, long long B, long long L, long long T, float* out,
+                       long long out_wave_stride, int row_offset, void* hip_stream) {
+  if (!plan->runs_composed())
+    return run_stft_core(plan, NNA_KIND_CQT1992, x, B, L, T, out, out_wave_stride, row_offset, hip_stream);
+  DeviceGuard guard;
+  hipError_t e = guard.enter(plan->device);
+  if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
+  return run_conv(plan->composed, x, B, L, T, out, out_wave_stride, row_offset, hip_stream);
+}
+
 // one decimation step: y[B, Ln] from x[B, L], Ln = ceil(L / 2) (arguments checked by the caller)
 nna_status run_fir(const nna_plan* fir, const float* x, long long B, long long L, float* y, long long Ln, void* hip_stream) {
   nna::FirParams P;
@@ -402,7 +415,10 @@ using namespace nna::host;
 extern "C" {
 
 nna_status nna_cqt1992(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev, void* hip_stream) {
-  return run_stft_like(plan, NNA_KIND_CQT1992, x_dev, B, L, out_dev, hip_stream);
+  long long T = 0;
+  nna_status s = check_call(plan, NNA_KIND_CQT1992, x_dev, B, L, out_dev, &T);
+  if (s != NNA_OK) return s;
+  return run_cqt1992(plan, x_dev, B, L, T, out_dev, (long long)plan->out_rows() * T, 0, hip_stream);
 }
 
 nna_status nna_cqt2010v2_workspace(const nna_plan* plan, long long B, long long L, size_t* bytes) {
@@ -438,9 +454,9 @@ static nna_status run_octaves(const nna_plan* plan, int kind, const float* x_dev
   const int n_oct = (int)plan->octave.size();
   // every launch of the call must fit before the first one is enqueued
   for (int a = 0; a < n_oct; ++a) {
-    const nna_plan* sub = plan->octave[a];
+    const nna_plan* sub = plan->octave[a]->runs_composed() ? plan->octave[a]->composed : plan->octave[a];
     const int lds_rows = sub->kind == NNA_KIND_CQT1992 && sub->lin_blocks == 6 ? nna::ST_LDS_ROWS_WIDE : ST_LDS_ROWS;
-    const int M = kind == NNA_KIND_CQT2010V2 ? pick_tile_frames(CQ_FRAMES, T, (sub->max_jspan - 1) * sub->row_step, CQ_LDS_ROWS_MAX)
+    const int M = sub->kind == NNA_KIND_CQT ? pick_tile_frames(CQ_FRAMES, T, (sub->max_jspan - 1) * sub->row_step, CQ_LDS_ROWS_MAX)
                                              : pick_tile_frames(ST_FRAMES, T, sub->nj - 1, lds_rows);
     if (M < 1) return fail(NNA_ERR_UNSUPPORTED, "frame tile does not fit in LDS");
   }
@@ -487,7 +503,7 @@ static nna_status run_octaves(const nna_plan* plan, int kind, const float* x_dev
     if (kind == NNA_KIND_CQT2010V2)
       s = run_conv(plan->octave[a], cur, B, La[a], T, out_dev, (long long)plan->out_rows() * T, row0, st);
     else
-      s = run_stft_core(plan->octave[a], NNA_KIND_CQT1992, cur, B, La[a], T, out_dev, (long long)plan->out_rows() * T, row0, st);
+      s = run_cqt1992(plan->octave[a], cur, B, La[a], T, out_dev, (long long)plan->out_rows() * T, row0, st);
     if (forked) {
       e = hipEventRecord(plan->ev_oct[a], st);
       if (e == hipSuccess) launched = a + 1;
