@@ -162,8 +162,10 @@ nna_status nna_plan_mel(nna_plan** plan, int sr, int n_fft, int hop, nna_window 
  * the kernels are symmetric about their centres up to the common phase exp(-i pi Q), and where
  * that pays (a seventh or more of the multiply-adds saved: 12 or more bins per octave, kernels of
  * eight hops or more, hop a multiple of 16 dividing n_taps / 2, a window that vanishes at n = 0) they are
- * applied to the frame folded about that centre.  nna_plan_info reports the flops of the form
- * that runs; nna_plan_bank always returns the kernels as defined above.
+ * applied to the frame folded about that centre.  With a hop that is a multiple of 32 and divides n_taps (at most 2^18) they are
+ * cut at the hops' boundaries and applied as combinations of the few functions per hop that hold them to 6e-8 of each kernel's
+ * norm (half a unit in the last place of a float32 tap), wherever that takes fewer multiply-adds.  nna_plan_info reports the flops
+ * of the direct or folded form; nna_plan_bank always returns the kernels as defined above.
  */
 nna_status nna_plan_cqt(nna_plan** plan, int sr, int hop, double fmin, int n_bins, int bins_per_octave,
                         nna_window win, int center, int n_taps, nna_output fmt, int device);

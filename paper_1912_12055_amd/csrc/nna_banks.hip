@@ -720,8 +720,8 @@ void build_conv_bank(nna_plan* p, ValueFn value) {
 
 // Both stages of eq. (CQT1992) as one: X_cq[q] = sum_n x[n] c_q[n] with c_q[n] = (1/K) sum_{k <= K/2} Y[q, k] e^{-2 pi i k n / K},
 // the kernel of eq. (CQT) less its negative frequencies.  Dense in n, so a bank of 2 n_bins rows x K taps: for plans whose
-// kernels are fixed 2 n_bins / K of the two-stage form's multiply-adds.  `c` is a plan of kind CQT with p's geometry.
-void build_cqt1992_composed(const nna_plan* p, nna_plan* c) {
+// kernels are fixed 2 n_bins / K of the two-stage form's multiply-adds.
+std::vector<double> cqt1992_composed_rows(const nna_plan* p) {
   const int K = p->K;
   std::vector<double> rows((size_t)2 * p->n_bins * K);
   std::vector<std::complex<double>> a(K);
@@ -734,10 +734,17 @@ void build_cqt1992_composed(const nna_plan* p, nna_plan* c) {
       rows[(size_t)(2 * q + 1) * K + n] = a[n].imag() / K;
     }
   }
-  c->conv_rows = 2 * p->n_bins;
-  c->row_s.assign(c->conv_rows, 0);
-  c->row_e.assign(c->conv_rows, K);
-  build_conv_bank(c, [&](int row, long long tap) { return row < c->conv_rows && tap < K ? rows[(size_t)row * K + tap] : 0.0; });
+  return rows;
+}
+
+// c's bank from a dense [2 n_bins][K] array
+void build_cqt_bank_rows(nna_plan* c, const std::vector<double>& rows) {
+  const long long K = c->K;
+  const int n_rows = 2 * c->n_bins;
+  c->conv_rows = n_rows;
+  c->row_s.assign(n_rows, 0);
+  c->row_e.assign(n_rows, K);
+  build_conv_bank(c, [&](int row, long long tap) { return row < n_rows && tap < K ? rows[(size_t)row * K + tap] : 0.0; });
 }
 
 void build_cqt_bank(nna_plan* p) {
@@ -753,6 +760,306 @@ void build_cqt_bank(nna_plan* p) {
   CqtKernelGen gen(p);
   build_conv_bank(p, [&](int row, long long tap) { return gen.value(row, tap); });
   p->alg_flops = 4.0 * sumN;
+}
+
+// ---- CQT kernels in two stages over hop-blocks (nna_kernels_cql.hip) ---------------------------
+// A kernel cut at the hops' boundaries is a stack of rows of `hop` taps, and the rows of neighbouring long kernels are smooth
+// functions of little bandwidth: the 2,144 rows of the 16 lowest bins of 24 per octave at 44.1 kHz, hop 512, lie within 6e-8 of
+// a space of 12 dimensions.  So U[i][c] (i < r) is an orthonormal basis of that space and A the rows' coordinates in it:
+//     y[b][i] = sum_c U[i][c] x[b hop + c],   C_k[t] = sum_j sum_i A_k[j][i] y[t + j][i].
+// The basis is grown by Gram-Schmidt, the row furthest from the space next, until what is left of every kernel is below a
+// quarter of kTol of its norm; the coordinates are then turned to their principal axes and as many of these dropped as kTol allows.
+namespace {
+constexpr double kLowrankTol = 6e-8;  // half a unit in the last place of float32: the weights' own rounding
+
+// (eight partial sums: one chain of additions would cost four cycles a term)
+double dot(const double* a, const double* b, int n) {
+  double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  int i = 0;
+  for (; i + 8 <= n; i += 8)
+    for (int e = 0; e < 8; ++e) s[e] += a[i + e] * b[i + e];
+  for (; i < n; ++i) s[0] += a[i] * b[i];
+  return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+}
+// eigenvectors (columns of V, largest eigenvalue first) of a symmetric n x n matrix by cyclic Jacobi rotations
+void principal_axes(std::vector<double>& G, int n, std::vector<double>& V, std::vector<int>& order) {
+  V.assign((size_t)n * n, 0.0);
+  for (int i = 0; i < n; ++i) V[(size_t)i * n + i] = 1.0;
+  double trace = 0;
+  for (int i = 0; i < n; ++i) trace += G[(size_t)i * n + i];
+  for (int sweep = 0; sweep < 30; ++sweep) {
+    double off = 0;
+    for (int i = 0; i < n; ++i)
+      for (int j = 0; j < i; ++j) off = std::max(off, std::fabs(G[(size_t)i * n + j]));
+    if (off <= 1e-18 * trace) break;
+    for (int p = 0; p < n; ++p)
+      for (int q = p + 1; q < n; ++q) {
+        const double g = G[(size_t)p * n + q];
+        if (std::fabs(g) <= 1e-19 * trace) continue;
+        const double th = (G[(size_t)q * n + q] - G[(size_t)p * n + p]) / (2.0 * g);
+        const double t = (th >= 0 ? 1.0 : -1.0) / (std::fabs(th) + std::sqrt(th * th + 1.0));
+        const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
+        for (int i = 0; i < n; ++i) {  // rows p, q, then columns p, q
+          const double a = G[(size_t)p * n + i], b = G[(size_t)q * n + i];
+          G[(size_t)p * n + i] = c * a - s * b;
+          G[(size_t)q * n + i] = s * a + c * b;
+        }
+        for (int i = 0; i < n; ++i) {
+          const double a = G[(size_t)i * n + p], b = G[(size_t)i * n + q];
+          G[(size_t)i * n + p] = c * a - s * b;
+          G[(size_t)i * n + q] = s * a + c * b;
+          const double u = V[(size_t)i * n + p], v = V[(size_t)i * n + q];
+          V[(size_t)i * n + p] = c * u - s * v;
+          V[(size_t)i * n + q] = s * u + c * v;
+        }
+      }
+  }
+  order.resize(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return G[(size_t)a * n + a] > G[(size_t)b * n + b]; });
+}
+}  // namespace
+
+void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long long)>& value) {
+  p->lowrank = false;
+  const long long K = p->K;
+  const int hop = p->hop;
+  // whole 32-column chunks, frames and kernels on one grid of hops, and a plan that is built in a second
+  if (hop % 32 != 0 || hop > 4096 || K % hop != 0 || K / hop < 4 || K > CQL_MAX_TAPS) return;
+  constexpr int G = 16;
+  bool any = false;
+  // row block b of the bins from k0 on: its taps
+  auto taps_of = [&](int k0, int nb, int b, long long& lo, long long& hi) {
+    lo = K;
+    hi = 0;
+    for (int k = k0 + 8 * b; k < std::min(k0 + nb, k0 + 8 * b + 8); ++k) {
+      lo = std::min(lo, p->row_s[2 * k]);
+      hi = std::max(hi, p->row_e[2 * k]);
+    }
+  };
+  // the kernels as they stand: up to 32 bins, per 32 columns of the hop the steps of 16 taps that hold taps
+  auto add_direct = [&](int k0, int nb) {
+    nna::CqlItem item{};
+    item.bin0 = k0;
+    item.n_bins = nb;
+    const int n_rb = (nb + 7) / 8;
+    long long lo[4], hi[4];
+    for (int b = 0; b < n_rb; ++b) taps_of(k0, nb, b, lo[b], hi[b]);
+    for (int b = n_rb - 1; b > 0; --b) {  // (longer kernels come first, so a block's taps lie among those of the one before)
+      lo[b - 1] = std::min(lo[b - 1], lo[b]);
+      hi[b - 1] = std::max(hi[b - 1], hi[b]);
+    }
+    item.j0 = (int)(lo[0] / hop);
+    item.jspan = (int)ceil_div(hi[0], hop) - item.j0;
+    item.u0 = (long long)p->h_lu.size() / 4;
+    while (p->h_lsteps.size() % 4 != (4 - (hop / 32 + 1) % 4) % 4) p->h_lsteps.push_back(0);  // the steps are read four at a time
+    item.step0 = (long long)p->h_lsteps.size();
+    std::vector<int> first, steps;
+    for (int c = 0; c < hop; c += 32) {
+      first.push_back((int)steps.size());
+      for (int j = 0; j < item.jspan; ++j)
+        for (int half = 0; half < 2; ++half) {
+          const long long t0 = (long long)(item.j0 + j) * hop + c + 16 * half;
+          int a = 0;
+          while (a < n_rb && t0 + 16 > lo[a] && t0 < hi[a]) ++a;
+          if (!a) continue;
+          steps.push_back(a | (c / 16 + half) << 3 | j << 12);
+          for (int b = 0; b < 4; ++b)
+            for (int lane = 0; lane < 64; ++lane)
+              for (int e = 0; e < 4; ++e) {
+                const int row = 16 * b + (lane & 15), k = k0 + row / 2;
+                const long long tap = t0 + 4 * (lane >> 4) + e;
+                const bool there = b < a && row < 2 * nb && tap >= p->row_s[2 * k] && tap < p->row_e[2 * k];
+                p->h_lu.push_back(there ? (float)value(2 * k0 + row, tap) : 0.0f);
+              }
+        }
+      while (steps.size() % 4) {  // empty steps: the kernel goes through them by fours
+        steps.push_back(0);
+        p->h_lu.insert(p->h_lu.end(), 4 * 64 * 4, 0.0f);
+      }
+    }
+    first.push_back((int)steps.size());
+    item.n_step = (int)steps.size();
+    p->h_lsteps.insert(p->h_lsteps.end(), first.begin(), first.end());
+    p->h_lsteps.insert(p->h_lsteps.end(), steps.begin(), steps.end());
+    p->h_litems.push_back(item);
+  };
+  std::vector<int> as_is;  // first bins of the groups whose kernels stay
+  for (int k0 = 0; k0 < p->n_bins; k0 += G) {
+    const int nb = std::min(G, p->n_bins - k0);
+    // hop-blocks of the two row blocks
+    int jl[2] = {INT_MAX, INT_MAX}, jh[2] = {0, 0};
+    double direct = 0;  // multiply-adds per frame of the form that would run otherwise
+    for (int k = k0; k < k0 + nb; ++k) {
+      const int b = (k - k0) / 8;
+      jl[b] = std::min(jl[b], (int)(p->row_s[2 * k] / hop));
+      jh[b] = std::max(jh[b], (int)ceil_div(p->row_e[2 * k], hop));
+      direct += 2.0 * (double)(p->row_e[2 * k] - p->row_s[2 * k]);
+    }
+    if (nb <= 8) jl[1] = jh[1] = jl[0];
+    double as_is_cost = 0;
+    for (int b = 0; b < 2; ++b) {
+      long long lo, hi;
+      taps_of(k0, nb, b, lo, hi);
+      if (lo < hi) as_is_cost += 16.0 * (double)(hi - lo + 16);
+    }
+    if (jh[0] - jl[0] < 3) {  // a basis of `hop` columns for one or two hop-blocks saves nothing
+      as_is.push_back(k0);
+      continue;
+    }
+    const int j0 = std::min(jl[0], jl[1]), J = std::max(jh[0], jh[1]) - j0;
+    const int m = 2 * nb * J;
+    std::vector<double> R((size_t)m * hop), n2(m), norm2(nb, 0.0);
+    for (int k = 0; k < nb; ++k)
+      for (int ri = 0; ri < 2; ++ri)
+        for (int j = 0; j < J; ++j) {
+          double* row = &R[((size_t)(2 * k + ri) * J + j) * hop];
+          const long long t0 = (long long)(j0 + j) * hop;
+          if (t0 + hop <= p->row_s[2 * (k0 + k)] || t0 >= p->row_e[2 * (k0 + k)]) continue;
+          double s = 0;
+          for (int c = 0; c < hop; ++c) {
+            row[c] = value(2 * (k0 + k) + ri, t0 + c);
+            s += row[c] * row[c];
+          }
+          norm2[k] += s;
+        }
+    for (int k = 0; k < nb; ++k) {
+      if (!(norm2[k] > 0)) norm2[k] = 1.0;
+      const double f = 1.0 / std::sqrt(norm2[k]);
+      for (size_t i = (size_t)2 * k * J * hop; i < (size_t)2 * (k + 1) * J * hop; ++i) R[i] *= f;
+    }
+    // Gram-Schmidt; C[m][.] collects the coordinates
+    const int cap = std::min(hop, 16 * CQL_MAX_BASIS);
+    std::vector<double> U, C((size_t)m * cap, 0.0);
+    int r0 = 0;
+    bool fits = false;
+    for (;;) {
+      int best = 0;
+      std::vector<double> left(nb, 0.0);
+      for (int i = 0; i < m; ++i) {
+        const double* row = &R[(size_t)i * hop];
+        const double s = dot(row, row, hop);
+        n2[i] = s;
+        left[i / (2 * J)] += s;
+        if (s > n2[best]) best = i;
+      }
+      if (std::sqrt(*std::max_element(left.begin(), left.end())) <= 0.25 * kLowrankTol) {
+        fits = true;
+        break;
+      }
+      if (r0 == cap) break;
+      std::vector<double> u(&R[(size_t)best * hop], &R[(size_t)best * hop] + hop);
+      for (int pass = 0; pass < 2; ++pass) {
+        for (int i = 0; i < r0; ++i) {
+          const double* v = &U[(size_t)i * hop];
+          const double d = dot(u.data(), v, hop);
+          for (int c = 0; c < hop; ++c) u[c] -= d * v[c];
+        }
+        const double s = 1.0 / std::sqrt(dot(u.data(), u.data(), hop));
+        for (int c = 0; c < hop; ++c) u[c] *= s;
+      }
+      U.insert(U.end(), u.begin(), u.end());
+      for (int i = 0; i < m; ++i) {
+        double* row = &R[(size_t)i * hop];
+        const double d = dot(row, u.data(), hop);
+        for (int c = 0; c < hop; ++c) row[c] -= d * u[c];
+        C[(size_t)i * cap + r0] += d;
+      }
+      ++r0;
+    }
+    if (!fits) {
+      as_is.push_back(k0);
+      continue;
+    }
+    // principal axes of the coordinates
+    std::vector<double> Gm((size_t)r0 * r0, 0.0), V;
+    std::vector<int> order;
+    for (int i = 0; i < m; ++i) {
+      const double* c = &C[(size_t)i * cap];
+      for (int a = 0; a < r0; ++a) {
+        if (c[a] == 0.0) continue;
+        for (int b = 0; b <= a; ++b) Gm[(size_t)a * r0 + b] += c[a] * c[b];
+      }
+    }
+    for (int a = 0; a < r0; ++a)
+      for (int b = 0; b < a; ++b) Gm[(size_t)b * r0 + a] = Gm[(size_t)a * r0 + b];
+    principal_axes(Gm, r0, V, order);
+    std::vector<double> D((size_t)m * r0), W((size_t)r0 * hop, 0.0), Vt((size_t)r0 * r0);  // coordinates on the axes, the axes
+    for (int a = 0; a < r0; ++a) {
+      const int ax = order[a];
+      for (int b = 0; b < r0; ++b) {
+        const double v = V[(size_t)b * r0 + ax];
+        for (int c = 0; c < hop; ++c) W[(size_t)a * hop + c] += v * U[(size_t)b * hop + c];
+        Vt[(size_t)a * r0 + b] = v;
+      }
+    }
+    for (int i = 0; i < m; ++i)
+      for (int a = 0; a < r0; ++a) D[(size_t)i * r0 + a] = dot(&C[(size_t)i * cap], &Vt[(size_t)a * r0], r0);
+    // what every kernel loses with the axes from `keep` on
+    std::vector<double> lost(nb, 0.0);
+    int keep = r0;
+    while (keep > 1) {
+      std::vector<double> next = lost;
+      for (int i = 0; i < m; ++i) next[i / (2 * J)] += D[(size_t)i * r0 + keep - 1] * D[(size_t)i * r0 + keep - 1];
+      if (std::sqrt(*std::max_element(next.begin(), next.end())) > kLowrankTol) break;
+      lost = next;
+      --keep;
+    }
+    nna::CqlItem item{};
+    item.r = (keep + 3) / 8 * 8 + 4;  // 4 modulo 8: the rows of 16 frames then lie on different LDS banks
+    item.n_ib = (item.r + 15) / 16;
+    item.j0 = j0;
+    item.jspan = J;
+    item.n_step = (int)ceil_div((long long)J * item.r, 16);
+    item.s_lo = (int)((long long)(jl[1] - j0) * item.r / 16);
+    item.s_hi = nb > 8 ? (int)ceil_div((long long)(jh[1] - j0) * item.r, 16) : item.s_lo;
+    item.bin0 = k0;
+    item.n_bins = nb;
+    // multiply-adds per frame, a quarter more hop-blocks than frames in the first stage, against those of the kernels as they stand
+    const double cost = 1.25 * 16.0 * item.n_ib * hop + 256.0 * (item.n_step + item.s_hi - item.s_lo);
+    if (item.n_ib > CQL_MAX_BASIS || cost > as_is_cost) {
+      as_is.push_back(k0);
+      continue;
+    }
+    any = true;
+    // ... of the kernel that runs otherwise: 0.55 of the taps where they fold (dense kernels do not)
+    p->lr_limit += (p->row_e[2 * k0] - p->row_s[2 * k0] == K ? 1.0 : 0.55) * direct;
+    // basis fragments [chunk][block][half][lane]: lane (q, i) holds U[16 block + i][32 chunk + 16 half + 4 q + e]
+    item.u0 = (long long)p->h_lu.size() / 4;
+    for (int c = 0; c < hop; c += 32)
+      for (int ib = 0; ib < item.n_ib; ++ib)
+        for (int half = 0; half < 2; ++half)
+          for (int lane = 0; lane < 64; ++lane)
+            for (int e = 0; e < 4; ++e) {
+              const int i = 16 * ib + (lane & 15), col = c + 16 * half + 4 * (lane >> 4) + e;
+              p->h_lu.push_back(i < std::min(item.r, r0) ? (float)W[(size_t)i * hop + col] : 0.0f);
+            }
+    // coefficient fragments [step][lane]: lane (q, row) holds A[row][16 step + 4 q + e], the coordinates of the row's
+    // hop-blocks one after the other
+    for (int b = 0; b < 2; ++b) {
+      item.a0[b] = (long long)p->h_la.size() / 4;
+      for (int s = b ? item.s_lo : 0; s < (b ? item.s_hi : item.n_step); ++s)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int e = 0; e < 4; ++e) {
+            const int row = 16 * b + (lane & 15), f = 16 * s + 4 * (lane >> 4) + e, j = f / item.r, i = f - j * item.r;
+            const bool there = row < 2 * nb && j < J && i < r0;
+            p->h_la.push_back(there ? (float)(D[((size_t)row * J + j) * r0 + i] * std::sqrt(norm2[row / 2])) : 0.0f);
+          }
+    }
+    p->h_litems.push_back(item);
+  }
+  if (!any) return;
+  for (size_t i = 0; i < as_is.size(); ++i) {
+    const bool two = i + 1 < as_is.size() && as_is[i + 1] == as_is[i] + G;
+    add_direct(as_is[i], std::min(two ? 2 * G : G, p->n_bins - as_is[i]));
+    if (two) ++i;
+  }
+  // those with a basis first, the heaviest first: the light ones fill their launch's tail
+  auto weight = [&](const nna::CqlItem& it) {
+    return it.r ? 1e12 + 16.0 * it.n_ib * hop + 256.0 * (it.n_step + it.s_hi - it.s_lo) : (double)it.n_step;
+  };
+  std::stable_sort(p->h_litems.begin(), p->h_litems.end(), [&](const nna::CqlItem& a, const nna::CqlItem& b) { return weight(a) > weight(b); });
+  p->lowrank = true;
 }
 
 // ---- CQT bank folded about the kernels' centres (nna_kernels_cqf.hip) --------------------------

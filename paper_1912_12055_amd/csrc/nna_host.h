@@ -14,6 +14,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <new>
 
@@ -198,6 +199,17 @@ struct nna_plan {
   nna::CqfChunk* d_qchunks = nullptr;
   int* d_qbins = nullptr;
   bool runs_cqfold() const { return cq_fold && !d_wrm; }
+  // The long kernels as combinations of a few functions per hop-block (nna_kernels_cql.hip)
+  bool lowrank = false;
+  std::vector<nna::CqlItem> h_litems;
+  std::vector<float> h_lu, h_la;
+  std::vector<int> h_lsteps;
+  int* d_lsteps = nullptr;
+  double lr_limit = 0;  // multiply-adds per frame of the other form, at the rate of this one
+  float* d_lu = nullptr;
+  float* d_la = nullptr;
+  nna::CqlItem* d_litems = nullptr;
+  bool runs_lowrank() const { return lowrank && !d_wrm; }
   // trainable CQT plans: index map caller's tensor -> streaming order, each row's tap support, and the
   // tables that let the backward contractions skip what lies outside every support
   int* d_cq_map = nullptr;
@@ -370,8 +382,11 @@ void build_mel_weights(nna_plan* p, double fmin, double fmax, int scale, int nor
 MelDeviceLayout layout_mel(nna_plan* p);
 void build_cqt1992_matrix(nna_plan* p);
 MelDeviceLayout layout_cqt1992(nna_plan* p);
-void build_cqt1992_composed(const nna_plan* p, nna_plan* c);
+std::vector<double> cqt1992_composed_rows(const nna_plan* p);
 void build_cqt_bank(nna_plan* p);
+// Rows 2k, 2k + 1 of `value` (bin k's kernel, p->K taps) in the form of nna_kernels_cql.hip; sets p->lowrank if it saves anything
+void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long long)>& value);
+void build_cqt_bank_rows(nna_plan* c, const std::vector<double>& rows);
 void build_cqt_bank_fold(nna_plan* p);  // sets p->cq_fold if the plan qualifies
 // the decimation filter of `fir_taps` taps: its taps, their split by parity for the decimation kernel, and the
 // 64-row bank form kept for inspection

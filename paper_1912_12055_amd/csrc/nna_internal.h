@@ -253,6 +253,56 @@ struct CqfParams {
   long long n_ft;
 };
 
+// ---- constant-Q kernels in two stages over hop-blocks (nna_kernels_cql.hip) -------------------
+constexpr int CQL_MAX_BASIS = 8;   // 16-row blocks of an item's basis
+constexpr long long CQL_MAX_TAPS = 1 << 18;  // of a kernel: the plan holds 32 of them in double precision
+
+constexpr int CQL_LDS_TWO = 80 * 1024;   // two workgroups per CU
+constexpr int CQL_LDS_ONE = 156 * 1024;  // one
+
+// direct items: columns of a hop per LDS tile and loader passes per tile, by 16-frame blocks per wave; rows a tile can hold
+constexpr int CQL_COLS(int fb) { return fb == 1 ? 64 : 32; }
+constexpr int CQL_PASSES(int fb) { return fb == 1 ? 6 : 5; }
+constexpr int CQL_ROWS(int fb) { return CQL_PASSES(fb) * 1024 / CQL_COLS(fb); }
+
+// A work item: 16 consecutive bins (two 16-row blocks), the basis their kernels' hop-blocks are combinations of and the
+// combinations; or (r = 0) up to 32 bins and their kernels as they stand.
+struct CqlItem {
+  long long u0;      // first float4 of the basis: [32-column chunk][16-row block][half][64 lanes]; r = 0: of the kernels,
+                     // [step][4 row blocks][64 lanes]
+  long long a0[2];   // first float4 of row block b's coefficients: [16-tap step][64 lanes]
+  long long step0;   // r = 0: first entry of the item's step table
+  int r;             // basis functions, 4 modulo 8: the pitch of a hop-block's coefficients in LDS
+  int n_ib;          // 16-row blocks of the basis
+  int j0, jspan;     // the item's hop-blocks of a frame: j0 .. j0 + jspan - 1
+  int s_lo, s_hi;    // steps of 16 coefficients in which the second row block is not zero; the first has all n_step
+  int n_step;
+  int bin0, n_bins;  // first bin, bins (1 .. 16; r = 0: 1 .. 32)
+  int pad0;
+};
+
+struct CqlPart {
+  const CqlItem* items;
+  int n_items;
+  int fb;            // 16-frame blocks per wave: a tile holds up to 64 fb frames
+  int tile_frames;
+  long long n_ft;
+};
+
+struct CqlParams {
+  FrameGeom g;
+  const float4* u;
+  const float4* a;
+  const int* steps;
+  float* out;
+  long long out_wave_stride;
+  CqlPart basis, direct;  // the items with a basis; those whose kernels stay as they are
+  int fmt;
+  int lds_floats;
+};
+hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream);
+hipError_t cql_kernels_init();  // per-process function attributes of nna_kernels_cql.hip
+
 // ---- backward pass of the STFT layer (trainable kernel banks) --------------------------------
 constexpr int BW_MT = 128;   // output tile rows per workgroup
 constexpr int BW_NT = 128;   // output tile columns per workgroup

@@ -1,0 +1,518 @@
+// Constant-Q transform with time-domain kernels (Sec. III-C, eq. (CQT)), the kernels as combinations of a few functions per hop.
+//
+// A kernel of N_k taps spans J hops, and cut at the hops' boundaries the kernels of 16 neighbouring bins are J x 32 rows of `hop`
+// taps.  Far fewer dimensions hold them all (to 6e-8 of each kernel, the rounding of its float32 taps; nna_banks.hip), because
+// within one hop a low bin's kernel is a smooth function.  With U an orthonormal basis of that space and A the coordinates,
+//     y[b][i] = sum_c U[i][c] x[b hop + c]          i < r, every hop-block b of the padded waveform
+//     C_k[t]  = sum_j sum_i A_k[j][i] y[t + j][i].
+// Bins of 24 per octave at 44.1 kHz, hop 512: 0.8 million multiply-adds per frame against 1.6 million of the kernels folded about
+// their centres (nna_kernels_cqf.hip) and 3.2 million of the kernels as they stand.
+//
+// Short kernels, where the first stage alone would cost more than their taps, stay as they are: direct items of up to 32 bins.
+//
+// A workgroup takes one item (16 bins) and one tile of 64 FB frames.  Stage 1 (v_mfma_f32_16x16x4_f32, basis rows x hop-blocks)
+// reads its hop-blocks from the waveform straight into registers in operand order -- sixteen hops per load, 64 bytes of each --
+// and writes y to LDS, a hop's r coordinates in a row.  Stage 2 then is the convolution of the direct kernel with a hop of r
+// samples: the taps of a frame are r J consecutive words of LDS, so r needs no padding to the sixteen taps of a step, only to 4
+// modulo 8, which keeps the rows of sixteen frames on different banks.
+//
+// Bound by the float32 matrix pipe (two thirds busy at the batch below); a short batch by latency, a workgroup or two per CU.
+// 1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms folded about the centres -> 7.2 ms; 16 x 220,500, 84 bins
+// of 12 per octave: 300 -> 63 us; the dense composed kernels of the frequency-domain layer (16 x 220,500, 32,768 taps): 566 -> 158 us.
+#include <type_traits>
+
+#include "nna_device.h"
+
+namespace nna {
+namespace {
+
+typedef f32x4 f32x4_u __attribute__((aligned(4)));
+using std::integral_constant;
+using True = integral_constant<bool, true>;
+using False = integral_constant<bool, false>;
+
+// lane (q, n), registers 0 .. 3 of row block b: (Re, Im) of bins 8 b + 2 q and + 1, frame n of the wave's frame block
+template <int FB, int RB>
+__device__ __forceinline__ void store_bins(const CqlParams& P, const CqlItem& item, const f32x4 (&acc)[FB][RB], const bool (&valid)[FB],
+                                           long long f0, int wave, int q, int n) {
+  const FrameGeom& g = P.g;
+  const int fmt = P.fmt;
+#pragma unroll
+  for (int fb = 0; fb < FB; ++fb) {
+    if (!valid[fb]) continue;
+    const long long f = f0 + wave * (16 * FB) + fb * 16 + n, b = f / g.T;
+    float* __restrict__ op = P.out + b * P.out_wave_stride + (f - b * g.T);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int k = 8 * rb + 2 * q + u;
+        if (k >= item.n_bins) continue;
+        const long long bin = item.bin0 + k;
+        const float re = acc[fb][rb][2 * u], im = acc[fb][rb][2 * u + 1], pw = re * re + im * im;
+        if (fmt == NNA_OUT_COMPLEX) {
+          op[2 * bin * g.T] = re;
+          op[(2 * bin + 1) * g.T] = im;
+        } else if (fmt == NNA_OUT_PHASE) {
+          op[bin * g.T] = atan2f(im, re);
+        } else {
+          op[bin * g.T] = fmt == NNA_OUT_MAGNITUDE ? format_power<NNA_OUT_MAGNITUDE>(pw)
+                          : fmt == NNA_OUT_POWER   ? pw
+                                                   : format_power<NNA_OUT_LOG>(pw);
+        }
+      }
+  }
+}
+
+// Short kernels, tap by tap.
+template <int FB>
+__device__ __forceinline__ void direct_item(const CqlParams& P, const CqlPart& part, const CqlItem& item, long long ft, float* Y) {
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int q = lane >> 4, n = lane & 15;
+  const FrameGeom& g = P.g;
+  const long long f0 = ft * part.tile_frames;
+  const int m_valid = (int)((g.n_frames - f0) < part.tile_frames ? (g.n_frames - f0) : part.tile_frames);
+  TileMap tm;
+  tm.T = g.T;
+  tm.b0 = f0 / g.T;
+  tm.t0 = (int)(f0 - tm.b0 * g.T);
+  tm.n0 = (g.T - tm.t0) < m_valid ? (g.T - tm.t0) : m_valid;
+  tm.extra = item.jspan - 1;
+  const int rows_used = tm.frame_row(m_valid - 1) + tm.extra + 1;
+  const int hop = g.hop;
+  constexpr int RB = 4;  // row blocks
+  // this wave's frames
+  bool valid[FB];
+#pragma unroll
+  for (int fb = 0; fb < FB; ++fb) valid[fb] = wave * (16 * FB) + fb * 16 + n < m_valid;
+  f32x4 acc[FB][RB];
+  auto clear = [&] {
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int b = 0; b < RB; ++b) acc[fb][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  };
+    // KC columns of the tile's hops at a time in LDS (row t + j serves frame t at hop-block j, as in the direct kernel), two
+  // buffers; per chunk the steps of 16 taps that hold taps, each of them for the first `a` row blocks (the kernels shrink from
+  // row block to row block).  The code is kept short: a workgroup runs most of it a few times only, and instructions that miss
+  // their cache cost more than the work (unrolled over four chunk switches, 16 x 220,500 samples took 89 us instead of 67).
+  constexpr int KC = CQL_COLS(FB), NP = CQL_PASSES(FB), PITCH = KC + 4, V = KC / 4, RPP = 256 / V;
+  const int L = (int)g.L;
+  const int rows_buf = (rows_used + 31) & ~31;
+  const int* __restrict__ chunk0 = P.steps + item.step0;       // first step of every 32 columns, [hop / 32 + 1], multiples of four
+  const int* __restrict__ steps = chunk0 + hop / 32 + 1;       // a | 16-column block << 3 | hop-block << 12
+  const float4* __restrict__ up = P.u + item.u0 + lane;        // [step][4 row blocks][64 lanes]
+  const int cv = tid % V, r0 = tid / V;
+  const float* xb[NP];  // this thread's rows: their waveform, the first of its four samples in column 0
+  int pos[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int row = p * RPP + r0;
+    long long b;
+    int sigma;
+    tm.decode(row < rows_used ? row : rows_used - 1, b, sigma);
+    xb[p] = g.x + b * g.L;
+    pos[p] = (sigma + item.j0) * hop - g.pad + 4 * cv;
+  }
+  // four samples on one side of either end are a stored run, read backwards behind an end; a run that straddles an end (only when
+  // L, the hop or the padding are not multiples of 4) is read again, sample by sample, when the tile is written
+  f32x4 R[NP];
+  unsigned rev = 0;
+  bool gen = false;
+  auto request = [&](int c) {
+    rev = 0;
+    gen = false;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int s = pos[p] + c;
+      const int src = s < 0 ? -s - 3 : s > L - 4 ? 2 * (L - 1) - s - 3 : s;
+      rev |= (src != s ? 1u : 0u) << p;
+      gen |= (unsigned)src > (unsigned)(L - 4);
+      R[p] = *reinterpret_cast<const f32x4_u*>(xb[p] + (src < 0 ? 0 : src > L - 4 ? L - 4 : src));
+    }
+  };
+  auto store = [&](int c, float* dst) {
+    dst += r0 * PITCH + 4 * cv;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const f32x4 v = R[p];
+      const bool r = (rev >> p) & 1u;
+      if (p * RPP + r0 < rows_buf)
+        *reinterpret_cast<f32x4*>(dst + p * RPP * PITCH) = (f32x4){r ? v.w : v.x, r ? v.z : v.y, r ? v.y : v.z, r ? v.x : v.w};
+    }
+    if (__builtin_amdgcn_ballot_w64(gen) == 0) return;
+#pragma unroll 1
+    for (int row = r0; row < rows_used; row += RPP) {
+      long long b;
+      int sigma;
+      tm.decode(row, b, sigma);
+      const float* __restrict__ x = g.x + b * g.L;
+      const int s = (sigma + item.j0) * hop - g.pad + 4 * cv + c;
+      const int src = s < 0 ? -s - 3 : s > L - 4 ? 2 * (L - 1) - s - 3 : s;
+      if ((unsigned)src > (unsigned)(L - 4))
+        for (int e = 0; e < 4; ++e) dst[(row - r0) * PITCH + e] = x[reflect_clamped(s + e, L)];
+    }
+  };
+  int f_off[FB];
+#pragma unroll
+  for (int fb = 0; fb < FB; ++fb) f_off[fb] = (valid[fb] ? tm.frame_row(wave * (16 * FB) + fb * 16 + n) : 0) * PITCH + 4 * q;
+  auto multiply = [&](int a, const f32x4 (&w)[4], const f32x4 (&x)[FB]) {
+    // row block by row block: a kernel that has ended costs a branch
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < a) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int fb = 0; fb < FB; ++fb)
+            acc[fb][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][k], x[fb][k], acc[fb][i], 0, 0, 0);
+      }
+  };
+  // The weights are requested three steps ahead, across chunks; the frames are read from LDS one step ahead, within a chunk.
+  const int n_step = item.n_step;
+  f32x4 w[4][4], x[2][FB];
+  auto fetch_w = [&](int s, f32x4 (&v)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const f32x4*>(up + ((long long)s * 4 + i) * 64);
+  };
+  clear();
+  request(0);
+#pragma unroll
+  for (int u = 0; u < 3; ++u) fetch_w(u, w[u]);
+  for (int c = 0; c < hop; c += KC) {
+    float* tile = Y + ((c / KC) & 1) * rows_buf * PITCH;
+    store(c, tile);
+    __syncthreads();  // also: the buffer of the chunk before last has been read by every wave
+    if (c + KC < hop) request(c + KC);
+    const int next = (c + KC) / 32, s1 = chunk0[next < hop / 32 ? next : hop / 32];
+    auto fetch_x = [&](int d, f32x4 (&v)[FB]) {
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb)
+        v[fb] = *reinterpret_cast<const f32x4*>(tile + f_off[fb] + (d >> 12) * PITCH + ((d << 1) & (KC - 16)));
+    };
+    int s = chunk0[c / 32];
+    int4 d = s < s1 ? *reinterpret_cast<const int4*>(steps + s) : make_int4(0, 0, 0, 0);
+    fetch_x(d.x, x[0]);
+    for (; s < s1; s += 4) {
+      const int4 dn = *reinterpret_cast<const int4*>(steps + (s + 4 < n_step ? s + 4 : s));
+      const int du[5] = {d.x, d.y, d.z, d.w, dn.x};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        fetch_w(s + u + 3 < n_step ? s + u + 3 : n_step - 1, w[(u + 3) & 3]);
+        // (behind the chunk's last step: a step of the next chunk, its offsets within the tile all the same; read and dropped)
+        fetch_x(du[u + 1], x[(u + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(du[u] & 7, w[u], x[u & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      d = dn;
+    }
+  }
+  store_bins<FB, RB>(P, item, acc, valid, f0, wave, q, n);
+}
+
+// Kernels as combinations of the item's basis.
+template <int FB>
+__device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& part, const CqlItem& item, long long ft, float* Y) {
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int q = lane >> 4, n = lane & 15;
+  const FrameGeom& g = P.g;
+  const long long f0 = ft * part.tile_frames;
+  const int m_valid = (int)((g.n_frames - f0) < part.tile_frames ? (g.n_frames - f0) : part.tile_frames);
+  TileMap tm;
+  tm.T = g.T;
+  tm.b0 = f0 / g.T;
+  tm.t0 = (int)(f0 - tm.b0 * g.T);
+  tm.n0 = (g.T - tm.t0) < m_valid ? (g.T - tm.t0) : m_valid;
+  tm.extra = item.jspan - 1;
+  const int rows_used = tm.frame_row(m_valid - 1) + tm.extra + 1;
+  const int r = item.r;
+  constexpr int RB = 2;  // row blocks
+  const int L = (int)g.L, hop = g.hop;
+  // acc[p][i] += 16 rows of weights (i) x 16 runs of samples (p) over columns [c_begin, c_end), 32 at a time.  A lane's run starts
+  // at sample pos[p] of its waveform, xb[p] points there (EDGE: at the waveform; some run of the wave touches a mirrored end).
+  // `u`: [chunk][u_blocks][half][64 lanes], of which the first IB blocks are used.
+  auto contract = [&](auto edge_tag, auto ib_tag, auto& acc, const auto& xb, const auto& pos, const float4* u, int u_blocks,
+                      int c_begin, int c_end) {
+    constexpr bool EDGE = decltype(edge_tag)::value;
+    constexpr int IB = decltype(ib_tag)::value, NB = sizeof(acc) / sizeof(acc[0]);
+    const float4* up = u + lane;
+    auto fetch = [&](int c, f32x4 (&x)[NB][2], f32x4 (&w)[IB][2], unsigned& rev) {
+      const float4* uc = up + (long long)((c - c_begin) >> 5) * u_blocks * 128;
+#pragma unroll
+      for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) w[i][h] = *reinterpret_cast<const f32x4*>(uc + (2 * i + h) * 64);
+      if constexpr (!EDGE) {
+#pragma unroll
+        for (int p = 0; p < NB; ++p) {
+          x[p][0] = *reinterpret_cast<const f32x4_u*>(xb[p] + c);
+          x[p][1] = *reinterpret_cast<const f32x4_u*>(xb[p] + c + 16);
+        }
+      } else {
+        // four samples on one side of either end are a stored run, read backwards behind an end (turned round when they are used:
+        // a request is not waited for here)
+        rev = 0;
+        bool gen = false;
+#pragma unroll
+        for (int p = 0; p < NB; ++p)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int s = pos[p] + c + 16 * h;
+            const int src = s < 0 ? -s - 3 : s > L - 4 ? 2 * (L - 1) - s - 3 : s;
+            rev |= (src != s ? 1u : 0u) << (2 * p + h);
+            gen |= (unsigned)src > (unsigned)(L - 4);
+            const int at = src < 0 ? 0 : src > L - 4 ? L - 4 : src;
+            x[p][h] = *reinterpret_cast<const f32x4_u*>(xb[p] + at);
+          }
+        // runs that straddle an end (only when L, the hop or the padding are not multiples of 4): sample by sample
+        if (__builtin_amdgcn_ballot_w64(gen) != 0) {
+#pragma unroll
+          for (int p = 0; p < NB; ++p)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const int s = pos[p] + c + 16 * h;
+              const int src = s < 0 ? -s - 3 : s > L - 4 ? 2 * (L - 1) - s - 3 : s;
+              if ((unsigned)src > (unsigned)(L - 4)) {
+                rev &= ~(1u << (2 * p + h));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[p][h][e] = xb[p][reflect_clamped(s + e, L)];
+              }
+            }
+        }
+      }
+    };
+    auto multiply = [&](f32x4 (&x)[NB][2], const f32x4 (&w)[IB][2], unsigned rev) {
+      if constexpr (EDGE) {
+#pragma unroll
+        for (int p = 0; p < NB; ++p)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const f32x4 v = x[p][h];
+            const bool r = (rev >> (2 * p + h)) & 1u;
+            x[p][h] = (f32x4){r ? v.w : v.x, r ? v.z : v.y, r ? v.y : v.z, r ? v.x : v.w};
+          }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int p = 0; p < NB; ++p)
+#pragma unroll
+          for (int i = 0; i < IB; ++i)
+            acc[p][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][e >> 2][e & 3], x[p][e >> 2][e & 3], acc[p][i], 0, 0, 0);
+    };
+    if (c_begin >= c_end) return;
+    // two register sets: the next 32 columns are requested ahead of this chunk's matrix instructions
+    f32x4 x0[NB][2], w0[IB][2], x1[NB][2], w1[IB][2];
+    unsigned r0 = 0, r1 = 0;
+    fetch(c_begin, x0, w0, r0);
+    for (int c = c_begin; c < c_end; c += 64) {
+      fetch(c + 32 < c_end ? c + 32 : c, x1, w1, r1);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(x0, w0, r0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (c + 32 >= c_end) break;
+      fetch(c + 64 < c_end ? c + 64 : c, x0, w0, r0);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(x1, w1, r1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // this wave's frames
+  bool valid[FB];
+#pragma unroll
+  for (int fb = 0; fb < FB; ++fb) valid[fb] = wave * (16 * FB) + fb * 16 + n < m_valid;
+  f32x4 acc[FB][RB];
+  auto clear = [&] {
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int b = 0; b < RB; ++b) acc[fb][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  };
+  // ---- stage 1: the hop-blocks' coordinates -------------------------------------------
+  // NB x IB tiles of 16 hop-blocks x 16 basis functions
+  auto sweep = [&](auto edge_tag, auto nb_tag, auto ib_tag, int blk0, int ib0) {
+    constexpr bool EDGE = decltype(edge_tag)::value;
+    constexpr int NB = decltype(nb_tag)::value, IB = decltype(ib_tag)::value;
+    const float* xb[NB];
+    int pos[NB];
+    f32x4 y[NB][IB];
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+      const int row = (blk0 + p) * 16 + n;
+      long long b;
+      int sigma;
+      tm.decode(row < rows_used ? row : rows_used - 1, b, sigma);  // rows nobody reads: the last one's samples
+      pos[p] = (sigma + item.j0) * hop - g.pad + 4 * q;
+      xb[p] = EDGE ? g.x + b * g.L : g.x + b * g.L + pos[p];
+#pragma unroll
+      for (int i = 0; i < IB; ++i) y[p][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    contract(edge_tag, ib_tag, y, xb, pos, P.u + item.u0 + (long long)ib0 * 128, item.n_ib, 0, hop);
+    // lane (q, n), register e: basis function 16 block + 4 q + e of hop-block n
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+      const int row = (blk0 + p) * 16 + n;
+      if (row < rows_used) {
+#pragma unroll
+        for (int i = 0; i < IB; ++i) {
+          const int f = (ib0 + i) * 16 + 4 * q;
+          if (f < r) *reinterpret_cast<f32x4*>(Y + row * r + f) = y[p][i];
+        }
+      }
+    }
+  };
+  {
+    // The waves share the (passes over the basis) x (blocks of 16 hop-blocks) evenly, a wave's share in runs of one pass.
+    const int nblk = (rows_used + 15) >> 4, n_pass = (item.n_ib + 2) / 3, units = nblk * n_pass;
+    const int first = units * wave >> 2, last = units * (wave + 1) >> 2;
+    for (int u = first; u < last;) {
+      const int pass = u / nblk, blk = u - pass * nblk, todo = (last < (pass + 1) * nblk ? last : (pass + 1) * nblk) - u;
+      const int nb = todo <= 4 ? todo : todo <= 6 ? 3 : 4;  // 5 = 3 + 2, 6 = 3 + 3, 7 = 4 + 3
+      const int ib = item.n_ib * pass / n_pass, ni = item.n_ib * (pass + 1) / n_pass - ib;  // 1 .. 3 basis blocks
+      // does any of these hop-blocks leave its waveform?  lane: one of their (up to 64) rows
+      const int row = blk * 16 + lane;
+      bool edge = false;
+      if (lane < 16 * nb && row < rows_used) {
+        long long b;
+        int sigma;
+        tm.decode(row, b, sigma);
+        const int s = (sigma + item.j0) * hop - g.pad;
+        edge = s < 0 || s + hop > L;
+      }
+      auto with_ib = [&](auto edge_tag, auto nb_tag) {
+        if (ni == 3) sweep(edge_tag, nb_tag, integral_constant<int, 3>{}, blk, ib);
+        else if (ni == 2) sweep(edge_tag, nb_tag, integral_constant<int, 2>{}, blk, ib);
+        else sweep(edge_tag, nb_tag, integral_constant<int, 1>{}, blk, ib);
+      };
+      auto with_nb = [&](auto edge_tag) {
+        if (nb == 4) with_ib(edge_tag, integral_constant<int, 4>{});
+        else if (nb == 3) with_ib(edge_tag, integral_constant<int, 3>{});
+        else if (nb == 2) with_ib(edge_tag, integral_constant<int, 2>{});
+        else with_ib(edge_tag, integral_constant<int, 1>{});
+      };
+      if (__builtin_amdgcn_ballot_w64(edge) != 0) with_nb(True{});
+      else with_nb(False{});
+      u += nb;
+    }
+    // the last step of the last frame reads up to fifteen words (times zero) past its hop-blocks
+    if (tid < 16) Y[rows_used * r + tid] = 0.f;
+  }
+  __syncthreads();
+
+  // ---- stage 2: the frames' combinations ----------------------------------------------
+  clear();
+  int y_off[FB];
+#pragma unroll
+  for (int fb = 0; fb < FB; ++fb) y_off[fb] = (valid[fb] ? tm.frame_row(wave * (16 * FB) + fb * 16 + n) : 0) * r + 4 * q;
+  const float4* a0p = P.a + item.a0[0] + lane;
+  const float4* a1p = P.a + item.a0[1] - (long long)item.s_lo * 64 + lane;
+  // steps [s, e): both row blocks, or the first alone
+  auto steps = [&](auto both_tag, int s, int e) {
+    constexpr bool BOTH = decltype(both_tag)::value;
+    if (s >= e) return;
+    auto fetch = [&](int i, f32x4& c0, f32x4& c1, f32x4 (&y)[FB]) {
+      c0 = *reinterpret_cast<const f32x4*>(a0p + (long long)i * 64);
+      if constexpr (BOTH) c1 = *reinterpret_cast<const f32x4*>(a1p + (long long)i * 64);
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb) y[fb] = *reinterpret_cast<const f32x4*>(Y + y_off[fb] + 16 * i);
+    };
+    auto multiply = [&](const f32x4& c0, const f32x4& c1, const f32x4 (&y)[FB]) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) {
+          acc[fb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(c0[k], y[fb][k], acc[fb][0], 0, 0, 0);
+          if constexpr (BOTH) acc[fb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(c1[k], y[fb][k], acc[fb][1], 0, 0, 0);
+        }
+    };
+    // four register sets of coefficients and frames, requested three steps ahead
+    f32x4 c0[4], c1[4], y[4][FB];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) fetch(s + u < e ? s + u : e - 1, c0[u], c1[u], y[u]);
+    for (int i = s; i < e; i += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int ahead = i + u + 3;
+        fetch(ahead < e ? ahead : e - 1, c0[(u + 3) & 3], c1[(u + 3) & 3], y[(u + 3) & 3]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + u < e) multiply(c0[u], c1[u], y[u]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  if (item.s_lo < item.s_hi) {
+    steps(False{}, 0, item.s_lo);
+    steps(True{}, item.s_lo, item.s_hi);
+    steps(False{}, item.s_hi, item.n_step);
+  } else {
+    steps(False{}, 0, item.n_step);
+  }
+  store_bins<FB, RB>(P, item, acc, valid, f0, wave, q, n);
+}
+
+// FB, FD: 16-frame blocks per wave of the items with a basis and of the direct ones.  The direct ones come first, the item the slow
+// index.  The others: workgroup ids are dealt round-robin to the 8 XCDs, and the items of one tile are neighbours on one XCD,
+// where they meet the tile's samples in its L2 (28 million L2 misses instead of 263 million, 7.1 -> 6.5 ms at 1,770 x 176,400);
+// rotated by one from tile to tile, because items differ in length and the CUs are dealt out in a fixed order too.
+template <int FB, int FD>
+__global__ __launch_bounds__(256, 2) void cqt_lowrank_kernel(const CqlParams P) {
+  extern __shared__ __attribute__((aligned(16))) float Y[];
+  long long bid = blockIdx.x;
+  const long long n_direct = P.direct.n_ft * P.direct.n_items;
+  if (bid < n_direct) {
+    const int id = (int)(bid / P.direct.n_ft);
+    const CqlItem item = P.direct.items[id];
+    direct_item<FD>(P, P.direct, item, bid - (long long)id * P.direct.n_ft, Y);
+  } else {
+    bid -= n_direct;
+    const int n_items = P.basis.n_items;
+    const long long local = bid >> 3, per_xcd = (P.basis.n_ft + 7) >> 3, tile = local / n_items;
+    const long long ft = (bid & 7) * per_xcd + tile;
+    if (ft >= P.basis.n_ft) return;
+    const CqlItem item = P.basis.items[(local + tile) % n_items];
+    lowrank_item<FB>(P, P.basis, item, ft, Y);
+  }
+}
+
+template <int FB, int FD>
+hipError_t allow_lds() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(cqt_lowrank_kernel<FB, FD>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             CQL_LDS_ONE);
+}
+
+template <int FB, int FD>
+void launch(const CqlParams& p, unsigned blocks, hipStream_t stream) {
+  hipLaunchKernelGGL((cqt_lowrank_kernel<FB, FD>), dim3(blocks), dim3(256), (size_t)p.lds_floats * 4, stream, p);
+}
+
+}  // namespace
+
+hipError_t cql_kernels_init() {
+  hipError_t e = allow_lds<1, 1>();
+  if (e == hipSuccess) e = allow_lds<2, 1>();
+  if (e == hipSuccess) e = allow_lds<4, 1>();
+  if (e == hipSuccess) e = allow_lds<1, 2>();
+  if (e == hipSuccess) e = allow_lds<2, 2>();
+  if (e == hipSuccess) e = allow_lds<4, 2>();
+  return e;
+}
+
+hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream) {
+  clear_stale_error();
+  const long long blocks = (p.basis.n_ft + 7) / 8 * 8 * p.basis.n_items + p.direct.n_ft * p.direct.n_items;
+  if (blocks <= 0 || blocks > 0x7fffffffLL || p.g.hop % 32) return hipErrorInvalidValue;
+  if (p.basis.tile_frames < 1 || p.basis.tile_frames > 64 * p.basis.fb || p.direct.tile_frames > 64 * p.direct.fb) return hipErrorInvalidValue;
+  if (p.lds_floats < 1 || (size_t)p.lds_floats * 4 > (size_t)CQL_LDS_ONE) return hipErrorInvalidValue;
+  const int fb = p.basis.fb, fd = p.direct.fb;
+  if ((fb != 1 && fb != 2 && fb != 4) || (fd != 1 && fd != 2)) return hipErrorInvalidValue;
+  if (fd == 1)
+    fb == 1 ? launch<1, 1>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 1>(p, (unsigned)blocks, stream) : launch<4, 1>(p, (unsigned)blocks, stream);
+  else
+    fb == 1 ? launch<1, 2>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 2>(p, (unsigned)blocks, stream) : launch<4, 2>(p, (unsigned)blocks, stream);
+  return hipGetLastError();
+}
+
+}  // namespace nna

@@ -33,12 +33,12 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
     DeviceGuard guard;
     hipError_t e = guard.enter(p->device);
     if (e != hipSuccess) {
-      delete p;
+      nna_plan_destroy(p);
       return fail_hip(e, "hipSetDevice");
     }
     e = ensure_kernels_init(p->device);
     if (e != hipSuccess) {
-      delete p;
+      nna_plan_destroy(p);
       return fail_hip(e, "kernel attribute setup");
     }
     nna_status s = p->bank_idle() ? NNA_OK : upload(&p->d_bank, p->h_bank.data(), p->bank_floats * sizeof(float), "kernel bank");
@@ -93,6 +93,12 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
         if (s == NNA_OK) s = upload(&p->d_qchunks, p->h_qchunks.data(), p->h_qchunks.size() * sizeof(nna::CqfChunk), "folded cqt chunk table");
         if (s == NNA_OK) s = upload(&p->d_qbins, p->h_qbins.data(), p->h_qbins.size() * sizeof(int), "folded cqt bin table");
       }
+      if (s == NNA_OK && p->lowrank) {
+        s = upload(&p->d_lu, p->h_lu.data(), p->h_lu.size() * sizeof(float), "hop-block basis");
+        if (s == NNA_OK) s = upload(&p->d_la, p->h_la.data(), p->h_la.size() * sizeof(float), "hop-block coefficients");
+        if (s == NNA_OK) s = upload(&p->d_lsteps, p->h_lsteps.data(), p->h_lsteps.size() * sizeof(int), "step table");
+        if (s == NNA_OK) s = upload(&p->d_litems, p->h_litems.data(), p->h_litems.size() * sizeof(nna::CqlItem), "hop-block item table");
+      }
     }
     if (s != NNA_OK) {
       const std::string keep = g_err;
@@ -103,6 +109,8 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
     std::vector<float>().swap(p->h_bank);  // the device copy is the bank from here on
     std::vector<float>().swap(p->h_bankf);
     std::vector<float>().swap(p->h_bankq);
+    std::vector<float>().swap(p->h_lu);
+    std::vector<float>().swap(p->h_la);
     std::vector<_Float16>().swap(p->h_bank16);
     std::vector<_Float16>().swap(p->h_bank16s);
   }
@@ -150,7 +158,7 @@ nna_status check_cqt_args(double fmin, int n_bins, int bins_per_octave, int n_ta
 
 // CQT plan whose bin k sits at fmin 2^((k_first + k) / bins_per_octave); arguments already checked
 nna_status make_cqt_plan(nna_plan** plan, int sr, int hop, double fmin, int k_first, int n_bins, int bins_per_octave,
-                         int win, int center, int n_taps, int fmt, int device) {
+                         int win, int center, int n_taps, int fmt, int device, bool lowrank = false) {
   nna_plan* p = new (std::nothrow) nna_plan;
   if (!p) return fail(NNA_ERR_ALLOC, "out of host memory");
   try {
@@ -196,6 +204,10 @@ nna_status make_cqt_plan(nna_plan** plan, int sr, int hop, double fmin, int k_fi
     p->pad = center ? (int)(taps / 2) : 0;
     for (int k = 0; k < n_bins; ++k) p->sk[k] = (taps - p->Nk[k]) / 2;
     build_cqt_bank(p);
+    if (lowrank && device >= 0) {
+      CqtKernelGen gen(p);
+      build_cqt_bank_lowrank(p, [&](int row, long long tap) { return gen.value(row, tap); });
+    }
     build_cqt_bank_fold(p);
   } catch (const std::bad_alloc&) {
     delete p;
@@ -391,12 +403,12 @@ nna_status nna_plan_cqt(nna_plan** plan, int sr, int hop, double fmin, int n_bin
   nna_status s = check_common(plan, sr, hop, win, center, device);
   if (s != NNA_OK) return s;
   if ((s = check_cqt_args(fmin, n_bins, bins_per_octave, n_taps, fmt, sr, true)) != NNA_OK) return s;
-  return make_cqt_plan(plan, sr, hop, fmin, 0, n_bins, bins_per_octave, win, center, n_taps, fmt, device);
+  return make_cqt_plan(plan, sr, hop, fmin, 0, n_bins, bins_per_octave, win, center, n_taps, fmt, device, true);
 }
 
 // two-stage CQT plan whose bin k sits at fmin 2^((k_first + k) / bins_per_octave); arguments already checked
 static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmin, int k_first, int n_bins,
-                                    int bins_per_octave, int win, int center, int n_fft, int fmt, int device) {
+                                    int bins_per_octave, int win, int center, int n_fft, int fmt, int device, bool lowrank = false) {
   nna_plan* p = new (std::nothrow) nna_plan;
   if (!p) return fail(NNA_ERR_ALLOC, "out of host memory");
   MelDeviceLayout lin;
@@ -444,6 +456,7 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
     build_stft_bank(p);
     build_cqt1992_matrix(p);
     lin = layout_cqt1992(p);
+    const std::vector<double> rows = cqt1992_composed_rows(p);
     c = new nna_plan;
     c->kind = NNA_KIND_CQT;
     c->device = device;
@@ -456,7 +469,8 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
     c->bpo = bins_per_octave;
     c->K = p->K;
     c->pad = p->pad;
-    build_cqt1992_composed(p, c);
+    build_cqt_bank_rows(c, rows);
+    if (lowrank && device >= 0) build_cqt_bank_lowrank(c, [&](int row, long long tap) { return rows[(size_t)row * p->K + tap]; });
   } catch (const std::bad_alloc&) {
     delete c;
     delete p;
@@ -475,7 +489,7 @@ nna_status nna_plan_cqt1992(nna_plan** plan, int sr, int hop, double fmin, int n
   nna_status s = check_common(plan, sr, hop, win, center, device);
   if (s != NNA_OK) return s;
   if ((s = check_cqt_args(fmin, n_bins, bins_per_octave, n_fft, fmt, sr, true)) != NNA_OK) return s;
-  return make_cqt1992_plan(plan, sr, hop, fmin, 0, n_bins, bins_per_octave, win, center, n_fft, fmt, device);
+  return make_cqt1992_plan(plan, sr, hop, fmin, 0, n_bins, bins_per_octave, win, center, n_fft, fmt, device, true);
 }
 
 // Both downsampling plans: one sub-plan per octave (time-domain kernels: a plan as from nna_plan_cqt;
@@ -873,6 +887,10 @@ void nna_plan_destroy(nna_plan* plan) {
       (void)hipFree(plan->d_qitems);
       (void)hipFree(plan->d_qchunks);
       (void)hipFree(plan->d_qbins);
+      (void)hipFree(plan->d_lu);
+      (void)hipFree(plan->d_la);
+      (void)hipFree(plan->d_litems);
+      (void)hipFree(plan->d_lsteps);
       (void)hipFree(plan->d_cq_map);
       (void)hipFree(plan->d_row_lo);
       (void)hipFree(plan->d_row_hi);

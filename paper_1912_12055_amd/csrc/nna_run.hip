@@ -25,6 +25,7 @@ hipError_t ensure_kernels_init(int device) {
   if (!g_init_done[device]) {
     hipError_t e = nna::kernels_init();
     if (e == hipSuccess) e = nna::cqf_kernels_init();
+    if (e == hipSuccess) e = nna::cql_kernels_init();
     if (e == hipSuccess) e = nna::fft_kernels_init();
     if (e != hipSuccess) return e;
     void* ptr = nullptr;
@@ -313,9 +314,75 @@ nna_status run_conv_fold(const nna_plan* sub, const float* x, long long B, long 
   return NNA_OK;
 }
 
+// The kernels by hop-blocks (nna_kernels_cql.hip).  A tile is 64 frames per 16-frame block of a wave (the registers of a direct
+// item hold two such blocks); smaller tiles spread a short batch over the chip.  Two workgroups per CU want 80 KB of LDS each; a
+// tile cut below three quarters for that takes one workgroup's 156 KB instead.  False: not a launch for this kernel (waveforms of
+// so few frames that the first stage, which runs over their hop-blocks, costs more than it saves).
+bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::CqlParams& P) {
+  double cost = 0;
+  int n_basis = 0;
+  const int n_items = (int)sub->h_litems.size();
+  for (const nna::CqlItem& it : sub->h_litems)
+    if (it.r) {
+      ++n_basis;
+      cost += 16.0 * it.n_ib * sub->hop * (double)(T + it.jspan - 1) / (double)T + 256.0 * (it.n_step + it.s_hi - it.s_lo);
+    }
+  if (cost > sub->lr_limit) return false;
+  P.lds_floats = 0;
+  for (int direct = 0; direct < 2; ++direct) {
+    const int i0 = direct ? n_basis : 0, i1 = direct ? n_items : n_basis;
+    nna::CqlPart& part = direct ? P.direct : P.basis;
+    part.items = sub->d_litems + i0;
+    part.n_items = i1 - i0;
+    part.fb = 1;
+    if (i0 == i1) continue;
+    auto fits = [&](int cap, size_t lds) {
+      int M = cap;
+      for (int i = i0; i < i1; ++i) {
+        const int rows = direct ? nna::CQL_ROWS(cap / 64) : (int)((lds / 4 - 16) / sub->h_litems[i].r);
+        M = std::min(M, pick_tile_frames(M, T, sub->h_litems[i].jspan - 1, rows));
+      }
+      return M;
+    };
+    int cap = direct ? CQ_FRAMES / 2 : CQ_FRAMES;
+    while (cap > 64 && (n_frames + cap - 1) / cap * n_items < 512) cap /= 2;
+    int M = fits(cap, nna::CQL_LDS_TWO);
+    if (4 * M < 3 * cap) M = fits(cap, nna::CQL_LDS_ONE);
+    if (M < 16) return false;
+    part.fb = cap / 64;
+    part.tile_frames = M;
+    part.n_ft = (n_frames + M - 1) / M;
+    const long long nseg = 1 + (M - 1 + T - 1) / T;
+    for (int i = i0; i < i1; ++i) {
+      const int rows = (int)(M + nseg * (sub->h_litems[i].jspan - 1));
+      P.lds_floats = std::max(P.lds_floats, direct ? (rows + 31) / 32 * 32 * 2 * (nna::CQL_COLS(part.fb) + 4) : rows * sub->h_litems[i].r + 16);
+    }
+  }
+  return true;
+}
+
+nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
+                            long long out_wave_stride, int row_offset, nna::CqlParams& P, void* hip_stream) {
+  P.g = make_geom(sub, x, B, L, T);
+  P.u = reinterpret_cast<const float4*>(sub->d_lu);
+  P.a = reinterpret_cast<const float4*>(sub->d_la);
+  P.steps = sub->d_lsteps;
+  P.out = out + (long long)row_offset * T;
+  P.out_wave_stride = out_wave_stride;
+  P.fmt = sub->fmt;
+  const hipError_t e = nna::launch_cqt_lowrank(P, reinterpret_cast<hipStream_t>(hip_stream));
+  if (e != hipSuccess) return fail_hip(e, "kernel launch");
+  return NNA_OK;
+}
+
 // one launch of the CQT kernel: `sub`'s bank over T frames of each of the B waveforms in x
 nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
                     long long out_wave_stride, int row_offset, void* hip_stream, bool may_fold = false) {
+  if (sub->runs_lowrank()) {
+    nna::CqlParams Q;
+    std::memset(&Q, 0, sizeof(Q));
+    if (shape_lowrank(sub, B * T, T, Q)) return run_conv_lowrank(sub, x, B, L, T, out, out_wave_stride, row_offset, Q, hip_stream);
+  }
   const int extra = (sub->max_jspan - 1) * sub->row_step;
   const int M = pick_tile_frames(CQ_FRAMES, T, extra, CQ_LDS_ROWS_MAX);
   if (may_fold && sub->runs_cqfold()) {

@@ -1,0 +1,61 @@
+"""Constant-Q kernels as combinations of a few functions per hop-block against the oracle and against the direct kernel (the same
+plan made trainable): edges of tiles and items, lengths whose ends fall inside a run of four samples, the shortest waveform the
+padding allows, frames without padding, batches that reach every tile size."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+# the kernels' float32 taps and sums of up to 16,384 terms: 1e-6 .. 4e-6 of a bin's own norm measured between the two forms
+TOL = 5e-5
+
+
+@pytest.fixture(scope="module")
+def nb():
+    from paper_1912_12055_amd import binding
+    binding.lib()
+    return binding
+
+
+CASES = [
+    # n_bins, bpo, sr, hop, fmin, n_taps, B, L, center
+    (1, 12, 8000, 32, 40.0, 0, 1, 4001, True),          # one bin, one row block
+    (17, 12, 8000, 64, 40.0, 0, 3, 2050, True),         # 16 + 1 bins; two samples past the shortest waveform
+    (33, 24, 16000, 128, 60.0, 0, 2, 16391, True),      # 24 per octave, odd length
+    (60, 12, 16000, 96, 50.0, 6144, 5, 9001, True),     # a hop that is no power of two
+    (40, 12, 22050, 512, 60.0, 0, 1, 30000, False),     # no padding
+    (84, 12, 22050, 512, 32.7, 0, 40, 44101, True),     # tiles of 128 frames across waveforms
+    (48, 24, 22050, 256, 65.4, 0, 90, 40002, True),     # ... of 256
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}x{c[3]}")
+@pytest.mark.parametrize("fmt", ["MAGNITUDE", "COMPLEX"])
+def test_hop_blocks(nb, case, fmt):
+    import torch
+    n_bins, bpo, sr, hop, fmin, n_taps, B, L, center = case
+    print(f"[case] hop-blocks {case} {fmt}", file=sys.stderr, flush=True)
+    cfg = dict(sr=sr, hop=hop, fmin=fmin, n_bins=n_bins, bins_per_octave=bpo, n_taps=n_taps)
+    rng = np.random.default_rng([29, n_bins, hop])
+    x = (0.3 * rng.standard_normal((B, L))).astype(np.float32)
+    x[0, L // 3:L // 2] = 0.0
+    xd = torch.from_numpy(x).to("cuda:0")
+    plan = nb.nna_plan_cqt(center=center, fmt=getattr(nb, "NNA_OUT_" + fmt), device=0, **cfg)
+    assert plan.info()["executed_flops_per_frame"] > 0
+    out = torch.full(plan_shape(nb, plan, B, L), float("nan"), device="cuda:0")
+    got = nb.nna_cqt(plan, xd, out=out).cpu().numpy().astype(np.float64)
+    direct = nb.nna_cqt(nb.nna_plan_trainable(plan), xd).cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    assert np.abs(got - direct).max() < TOL * np.abs(direct).max()
+    if fmt == "MAGNITUDE":
+        some = sorted({0, B // 2, B - 1})
+        ref = oracle.cqt(x[some], center=center, **cfg)
+        assert np.abs(got[some] - ref).max() < TOL * np.abs(ref).max()
+
+
+def plan_shape(nb, plan, B, L):
+    rows, frames = nb.nna_out_shape(plan, B, L)
+    return B, rows, frames
