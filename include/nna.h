@@ -240,7 +240,8 @@ nna_status nna_out_shape(const nna_plan* plan, long long B, long long L, long lo
  * III-A satisfy w[n] = w[N-n], so eq. (DFT2)'s real kernels meet x[n] + x[N-n] and its imaginary kernels
  * x[n] - x[N-n] over n < N/2 only); where n_fft is also a multiple of 256 the folded taps are summed by parity, E over
  * even n and O over odd n, so that bins k and N/2 - k are E + O and E - O and share their kernels.  Every other plan
- * (trainable, re-spaced axes) runs eq. (DFT2) as it stands. */
+ * (trainable, re-spaced axes) runs eq. (DFT2) as it stands; trainable plans on the bfloat16 matrix pipe, every float32 as the
+ * exact sum of three bfloat16 (a sample that is not finite makes its frames NaN). */
 nna_status nna_stft(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                     void* hip_stream);
 

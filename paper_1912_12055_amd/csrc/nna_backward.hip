@@ -285,7 +285,13 @@ nna_status nna_plan_trainable(nna_plan* plan) {
     std::vector<float> rm((size_t)plan->mels_pad * plan->fp, 0.0f);
     for (int m = 0; m < plan->n_mels; ++m)
       for (int k = 0; k < F; ++k) rm[(size_t)m * plan->fp + k] = plan->h_melW[(size_t)m * F + k];
+    plan->melt_rows = (F + nna::BW_KC - 1) / nna::BW_KC * nna::BW_KC;
+    plan->melt_pitch = (plan->n_mels + nna::BW_MT - 1) / nna::BW_MT * nna::BW_MT;
+    std::vector<float> tr((size_t)plan->melt_rows * plan->melt_pitch, 0.0f);
+    for (int m = 0; m < plan->n_mels; ++m)
+      for (int k = 0; k < F; ++k) tr[(size_t)k * plan->melt_pitch + m] = plan->h_melW[(size_t)m * F + k];
     s = upload(&plan->d_melw_rm, rm.data(), rm.size() * sizeof(float), "row-major filterbank");
+    if (s == NNA_OK) s = upload(&plan->d_melw_t, tr.data(), tr.size() * sizeof(float), "transposed filterbank");
     if (s == NNA_OK) {
       e = hipMemcpy(plan->d_mel_mask, mask.data(), mask.size(), hipMemcpyHostToDevice);
       if (e == hipSuccess) e = hipMemcpy(plan->d_mel_pass_rt, pass_rt.data(), pass_rt.size() * sizeof(int), hipMemcpyHostToDevice);
@@ -294,7 +300,8 @@ nna_status nna_plan_trainable(nna_plan* plan) {
     if (s != NNA_OK) {
       (void)hipFree(plan->d_wrm);
       (void)hipFree(plan->d_melw_rm);
-      plan->d_wrm = plan->d_melw_rm = nullptr;
+      (void)hipFree(plan->d_melw_t);
+      plan->d_wrm = plan->d_melw_rm = plan->d_melw_t = nullptr;
       return s;
     }
     plan->mel_nyq_any = 1;
@@ -420,7 +427,9 @@ static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, l
   // (a complex-format output is C itself: its gradient is G, and nothing needs to be recomputed)
   if (fmt == NNA_OUT_COMPLEX && !pout)
     e = nna::launch_g_from_complex(gbuf, gout_dev, n_frames, (int)T, out_bins, plan->rows_pad, plan->n_half, packed, stream);
-  else
+  else if (fmt == NNA_OUT_POWER)
+    e = nna::launch_split_forward(P, nna::ST_MODE_GRAD, plan->d_wrm, plan->kp, plan->K, stream);
+  else  // (these derivatives divide by |C|: near zeros of the transform they turn the order of its sums into results)
     e = nna::launch_stft(P, nna::ST_MODE_GRAD, stream);
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
   // 2. the two contractions with G
@@ -1091,7 +1100,7 @@ nna_status nna_plan_set_mel_weights(nna_plan* plan, const float* w_dev, void* hi
   DeviceGuard guard;
   hipError_t e = guard.enter(plan->device);
   if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
-  e = nna::launch_mel_from_logical(w_dev, plan->d_melw, plan->d_mel_wnyq, plan->d_melw_rm, plan->n_mels, plan->n_half,
+  e = nna::launch_mel_from_logical(w_dev, plan->d_melw, plan->d_mel_wnyq, plan->d_melw_rm, plan->d_melw_t, plan->melt_pitch, plan->n_mels, plan->n_half,
                                    plan->n_rt, plan->n_pass, plan->fp, reinterpret_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
   return NNA_OK;

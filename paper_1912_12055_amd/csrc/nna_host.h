@@ -170,6 +170,9 @@ struct nna_plan {
   // trainable Mel plans: the filterbank row-major [mels_pad][fp], zero padded
   float* d_melw_rm = nullptr;
   int fp = 0, mels_pad = 0;
+  // ... and transposed, [melt_rows][melt_pitch] (bins, mels), zero padded
+  float* d_melw_t = nullptr;
+  int melt_rows = 0, melt_pitch = 0;
   // trainable plans with frequency-domain constant-Q kernels: the spectral kernels as the caller's tensor
   // Ysk[2 n_bins][n_half + 1] (row 2q = Re, 2q+1 = Im, 1/n_fft included), and the real matrix they form on the
   // (Re, Im) rows of a spectrum, row-major both ways round, zero padded: Ylin[lin_mp][lin_rp], YlinT[lin_rp][lin_mp]

@@ -91,6 +91,7 @@ struct StftParams {
   int pair;
   float* out;
   int n_rt;             // row tiles
+  int rt_per_wg;        // consecutive row tiles one workgroup handles (set by launch_stft)
   int n_chunks;         // LDS chunks per row tile
   int nj;               // hop-shifts per chunk (n_fft/hop when the frames overlap in LDS, else 1)
   int n_half;           // number of (Re,Im) slots that exist (n_fft / 2 for the plain DFT)
@@ -417,11 +418,11 @@ hipError_t launch_lin_fold_gradient(const float* gylin, float* gysk, int n_bins,
 // launcher first clears whatever is pending: the status it returns is then its own launch's.
 inline void clear_stale_error() { (void)hipGetLastError(); }
 
-hipError_t launch_stft(const StftParams& p, int mode, hipStream_t stream);
+hipError_t launch_stft(StftParams p, int mode, hipStream_t stream);
 hipError_t launch_stft_fold(const StftParams& p, int mode, hipStream_t stream);  // ST_MODE_STFT or ST_MODE_MEL
 hipError_t launch_mel_bw_spec(const MelBwParams& p, hipStream_t stream);    // gP
 hipError_t launch_mel_bw_weights(const MelBwParams& p, hipStream_t stream); // gW
-hipError_t launch_mel_from_logical(const float* w, float* frag, float* wnyq, float* wrm, int n_mels, int n_half, int n_rt,
+hipError_t launch_mel_from_logical(const float* w, float* frag, float* wnyq, float* wrm, float* wt, int wt_pitch, int n_mels, int n_half, int n_rt,
                                    int n_pass, int fp, hipStream_t stream);
 hipError_t launch_fill_zero(float* p, long long n, hipStream_t stream);
 hipError_t launch_fill_zero_frames(float* gbuf, long long rows_pad, long long f0, long long f1, hipStream_t stream);
@@ -431,6 +432,10 @@ hipError_t launch_g_from_complex(float* gbuf, const float* gout, long long n_fra
 hipError_t launch_bank_from_logical(const BankPermuteParams& p, hipStream_t stream);  // logical -> bank, wrm
 hipError_t launch_bank_to_rowmajor(const BankPermuteParams& p, hipStream_t stream);   // bank -> wrm
 hipError_t launch_bank_to_logical(const BankPermuteParams& p, hipStream_t stream);    // wrm -> logical
+// the trainable layers' contractions (nna_kernels_split.hip); `mode` ST_MODE_STFT, _CPLX or _GRAD, wrm as in BwParams
+hipError_t launch_split_forward(StftParams p, int mode, const float* wrm, int kp, int K, hipStream_t stream);
+hipError_t launch_split_bank(const BwParams& p, hipStream_t stream);
+hipError_t launch_split_wave(const BwParams& p, hipStream_t stream);
 hipError_t launch_bw_bank(const BwParams& p, hipStream_t stream);      // gw += G x frames
 hipError_t launch_bw_wave(const BwParams& p, hipStream_t stream);      // gx += transposed convolution
 // decimation by two on the vector ALUs (fir_decimate_kernel)

@@ -874,6 +874,7 @@ void nna_plan_destroy(nna_plan* plan) {
       (void)hipFree(plan->d_bank16s);
       (void)hipFree(plan->d_wrm);
       (void)hipFree(plan->d_melw_rm);
+      (void)hipFree(plan->d_melw_t);
       (void)hipFree(plan->d_ysk);
       (void)hipFree(plan->d_ylin);
       (void)hipFree(plan->d_ylinT);

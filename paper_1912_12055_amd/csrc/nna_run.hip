@@ -271,7 +271,29 @@ nna_status run_stft_core(const nna_plan* plan, int kind, const float* x, long lo
                    : kind == NNA_KIND_CQT1992 ? nna::ST_MODE_LIN
                    : (plan->fmt == NNA_OUT_COMPLEX || plan->fmt == NNA_OUT_PHASE) ? nna::ST_MODE_CPLX
                                                                                   : nna::ST_MODE_STFT;
-  e = nna::launch_stft(P, mode, reinterpret_cast<hipStream_t>(stream));
+  if (plan->d_wrm && kind == NNA_KIND_MEL && spec_out) {
+    // trained filters are dense: the spectrogram by the split contraction, then filterbank x spectrogram as a product of its own
+    P.out = spec_out;
+    P.out_bins = plan->n_half + 1;
+    P.fmt = plan->mel_power == 1 ? NNA_OUT_MAGNITUDE : NNA_OUT_POWER;
+    e = nna::launch_split_forward(P, nna::ST_MODE_STFT, plan->d_wrm, plan->kp, plan->K, reinterpret_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return fail_hip(e, "kernel launch");
+    nna::MelBwParams Q;
+    std::memset(&Q, 0, sizeof(Q));
+    Q.g = spec_out;
+    Q.wrm = plan->d_melw_t;
+    Q.gP = out;
+    Q.B = B;
+    Q.T = (int)T;
+    Q.F = plan->n_mels;
+    Q.n_mels = plan->n_half + 1;
+    Q.fp = plan->melt_pitch;
+    Q.mels_pad = plan->melt_rows;
+    e = nna::launch_mel_bw_spec(Q, reinterpret_cast<hipStream_t>(stream));
+  } else if (plan->d_wrm && kind == NNA_KIND_STFT)
+    e = nna::launch_split_forward(P, mode, plan->d_wrm, plan->kp, plan->K, reinterpret_cast<hipStream_t>(stream));
+  else
+    e = nna::launch_stft(P, mode, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
   return NNA_OK;
 }

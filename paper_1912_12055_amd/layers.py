@@ -83,7 +83,7 @@ class _MelFn(torch.autograd.Function):
     def forward(ctx, x, W, Wmel, layer):
         ctx.layer = layer
         ctx.save_for_backward(x)
-        return nb.nna_mel(layer.plan, x)
+        return nb.nna_mel_with_stft(layer.plan, x)[0]  # dense filters: through the spectrogram
 
     @staticmethod
     def backward(ctx, gout):

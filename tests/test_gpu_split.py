@@ -1,0 +1,37 @@
+"""The trainable STFT layer's three contractions (each float32 as three bfloat16) against the same sums in 64 bits: frame counts
+around a tile, taps that are no multiple of a chunk, odd hops and lengths, samples and kernels of very different magnitudes."""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+# six of the nine partial products: 2^-26 of each product dropped, float32 accumulation over n <= 2,048 terms; as the float32
+# instruction, below 2e-6 of the result's norm
+TOL = 4e-6
+
+
+@pytest.mark.parametrize("n_fft,hop,B,L", [(64, 16, 1, 2032), (64, 16, 1, 2048), (400, 163, 3, 7001), (1024, 100, 2, 1999),
+                                           (2048, 512, 5, 22050), (256, 256, 1, 129)])
+@pytest.mark.parametrize("scale", [1.0, 1e-12])
+def test_trainable_stft_power(n_fft, hop, B, L, scale):
+    import torch
+    from paper_1912_12055_amd import layers
+    print(f"[case] split stft n_fft={n_fft} hop={hop} B={B} L={L} scale={scale}", file=sys.stderr, flush=True)
+    gen = torch.Generator().manual_seed(n_fft + hop)
+    x = torch.randn(B, L, generator=gen) * scale
+    x[:, : L // 2] *= 1e-3
+    layer = layers.STFT(n_fft=n_fft, hop_length=hop, sr=16000, output_format="Power", trainable=True)
+    xd = x.cuda().requires_grad_(True)
+    out = layer(xd)
+    gout = torch.randn(out.shape, generator=gen)
+    gw, gx = torch.autograd.grad(out, [layer.wsin_wcos, xd], gout.cuda())
+    x64 = x.double().requires_grad_(True)
+    w64 = layer.wsin_wcos.detach().cpu().double().requires_grad_(True)
+    frames = torch.nn.functional.pad(x64[:, None], (n_fft // 2, n_fft // 2), mode="reflect")[:, 0].unfold(1, n_fft, hop)
+    c = frames @ w64.t()
+    ref = (c[..., 0::2] ** 2 + c[..., 1::2] ** 2).transpose(1, 2)
+    rw, rx = torch.autograd.grad(ref, [w64, x64], gout.double())
+    for name, got, want in (("out", out, ref), ("gw", gw, rw), ("gx", gx, rx)):
+        got, want = got.detach().cpu().double().numpy(), want.detach().numpy()
+        assert np.linalg.norm(got - want) < TOL * np.linalg.norm(want), name
