@@ -455,7 +455,9 @@ static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, l
     // unit, twice over), each with at least 64 chunks to amortise its start-up
     const long long tiles = (long long)(plan->rows_pad / nna::BW_MT) * (plan->kp / nna::BW_NT);
     const long long chunks = gpitch / nna::BW_KC;
+    // (a short batch: pieces of 16 chunks, if that is what it takes to have two workgroups per compute unit)
     long long split = std::max(1LL, std::min((1024 + tiles - 1) / tiles, chunks / 64));
+    if (split * tiles < 512) split = std::max(split, std::min((512 + tiles - 1) / tiles, chunks / 16));
     Q.chunks_per_split = (chunks + split - 1) / split;
     Q.n_split = (int)((chunks + Q.chunks_per_split - 1) / Q.chunks_per_split);
     e = nna::launch_bw_bank(Q, stream);
@@ -536,7 +538,7 @@ static nna_status cqt_backward_core(const nna_plan* plan, const float* x_dev, lo
   P.gout_wave_stride = gout_wave_stride;
   P.gbuf = gbuf;
   P.rows_pad = plan->rows_pad;
-  e = nna::launch_cqt(P, stream);
+  e = launch_conv(plan, P, stream);
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
   // 2. the two contractions with G, restricted to the tiles that hold taps
   nna::BwParams Q;
@@ -569,7 +571,9 @@ static nna_status cqt_backward_core(const nna_plan* plan, const float* x_dev, lo
     const long long chunks = gpitch / nna::BW_KC;
     // the tile count is whatever the supports give: aim at eight rounds of the 512 resident workgroups, so
     // that a partly filled last round costs little
+    // (a short batch: pieces of 16 chunks, if that is what it takes to have two workgroups per compute unit)
     long long split = std::max(1LL, std::min((4096 + (long long)Q.n_tiles - 1) / Q.n_tiles, chunks / 64));
+    if (split * Q.n_tiles < 512) split = std::max(split, std::min((512 + (long long)Q.n_tiles - 1) / Q.n_tiles, chunks / 16));
     Q.chunks_per_split = (chunks + split - 1) / split;
     Q.n_split = (int)((chunks + Q.chunks_per_split - 1) / Q.chunks_per_split);
     e = nna::launch_bw_bank(Q, stream);

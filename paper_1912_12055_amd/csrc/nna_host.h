@@ -412,6 +412,8 @@ inline void octave_bins(int n_bins, int bpo, int a, int& lo, int& hi) {
   hi = n_bins - a * bpo;
   lo = std::max(0, hi - bpo);
 }
+// cqt_kernel's launch, or on a trainable plan the one for batches that would leave most CUs without a workgroup
+hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t stream);
 bool cqt2010_lengths(const nna_plan* plan, long long L, long long (&La)[MAX_OCTAVES]);
 // one decimation step: y[B, Ln] from x[B, L], Ln = ceil(L / 2) (arguments checked by the caller)
 nna_status run_fir(const nna_plan* fir, const float* x, long long B, long long L, float* y, long long Ln, void* hip_stream);

@@ -455,6 +455,8 @@ struct FirParams {
 };
 hipError_t launch_fir_decimate(const FirParams& p, hipStream_t stream);
 hipError_t launch_cqt(const CqtParams& p, hipStream_t stream);
+// ... for batches of few workgroups; rows [row_lo, row_hi) hold taps
+hipError_t launch_cqt_few(const CqtParams& p, const int* row_lo, const int* row_hi, hipStream_t stream);
 hipError_t launch_cqt_fold(const CqfParams& p, hipStream_t stream);
 hipError_t cqf_kernels_init();  // per-process function attributes of nna_kernels_cqf.hip
 size_t cqt_launch_lds_bytes(int n_chunks, int lds_rows);  // dynamic LDS launch_cqt asks for (limit: 160 KB)

@@ -436,6 +436,60 @@ __device__ __forceinline__ void for_each_index(F&& fn, std::integer_sequence<int
   (fn(std::integral_constant<int, S>{}), ...);
 }
 
+// One lane's four accumulator registers of a row block: (Re, Im) of bins bin0 and bin0 + 1.  Backward pass: dLoss/dC of frame `fr`
+// into G[frame / 32][row][frame % 32], row = 2 bin (Re), 2 bin + 1 (Im).
+__device__ __forceinline__ void cqt_grad_bins(const CqtParams& P, const f32x4& acc, int bin0, long long fr) {
+  const long long T = P.g.T, b = fr / T;
+  const float* __restrict__ gp = P.gout + b * P.gout_wave_stride + (fr - b * T);
+  float* __restrict__ Gp = P.gbuf + (fr >> 5) * ((long long)P.rows_pad * 32) + (fr & 31);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const long long bin = bin0 + u;
+    if (bin >= P.n_bins) continue;
+    const float re = acc[2 * u], im = acc[2 * u + 1];
+    const float pw = re * re + im * im;
+    float gr, gi;
+    if (P.fmt == NNA_OUT_COMPLEX) {
+      gr = gp[2 * bin * T];
+      gi = gp[(2 * bin + 1) * T];
+    } else if (P.fmt == NNA_OUT_PHASE) {  // d atan2(Im, Re) = (Re dIm - Im dRe) / P
+      const float s = pw > 0.f ? gp[bin * T] / pw : 0.f;
+      gr = -s * im;
+      gi = s * re;
+    } else {
+      const float go = gp[bin * T];
+      const float s = P.fmt == NNA_OUT_MAGNITUDE ? grad_scale<NNA_OUT_MAGNITUDE>(go, pw)
+                      : P.fmt == NNA_OUT_POWER   ? grad_scale<NNA_OUT_POWER>(go, pw)
+                                                 : grad_scale<NNA_OUT_LOG>(go, pw);
+      gr = s * re;
+      gi = s * im;
+    }
+    Gp[2 * bin * 32] = gr;
+    Gp[(2 * bin + 1) * 32] = gi;
+  }
+}
+// ... forward: the output format; `op` points at (waveform, first row, frame)
+__device__ __forceinline__ void cqt_store_bins(const CqtParams& P, const f32x4& acc, int bin0, float* __restrict__ op) {
+  const long long T = P.g.T;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const long long bin = bin0 + u;
+    if (bin >= P.n_bins) continue;
+    const float re = acc[2 * u], im = acc[2 * u + 1];
+    const float pw = re * re + im * im;
+    if (P.fmt == NNA_OUT_COMPLEX) {  // rows 2k = Re, 2k+1 = Im of bin k
+      op[2 * bin * T] = re;
+      op[(2 * bin + 1) * T] = im;
+    } else if (P.fmt == NNA_OUT_PHASE) {
+      op[bin * T] = atan2f(im, re);
+    } else {
+      op[bin * T] = P.fmt == NNA_OUT_MAGNITUDE ? format_power<NNA_OUT_MAGNITUDE>(pw)
+                    : P.fmt == NNA_OUT_POWER   ? pw
+                                               : format_power<NNA_OUT_LOG>(pw);
+    }
+  }
+}
+
 // GRAD: instead of the spectrogram the kernel writes G = dLoss/dC, the derivative of the output format
 // applied to the upstream gradient, in the blocked layout the backward contractions read.
 template <bool GRAD>
@@ -654,46 +708,15 @@ __global__ __launch_bounds__(256, 2) void cqt_kernel(const CqtParams P) {
 #pragma unroll
   for (int i = 0; i < CQ_PREFETCH; ++i) wait_vm<0>(bq[i]);
 
-  const int f = P.fmt;
   if constexpr (GRAD) {
     // lane (q, n), registers 0..3 of row block rb: (Re, Im) of bins 8 rb + 2 q and + 1, frame n of the
     // wave's frame block fb.  G[frame / 32][row][frame % 32], row = 2 bin (Re), 2 bin + 1 (Im).
 #pragma unroll
     for (int fb = 0; fb < 4; ++fb) {
       if (!valid[fb]) continue;
-      const long long fr = f0 + wave * 64 + fb * 16 + n;
-      const long long b = fr / g.T;
-      const float* __restrict__ gp = P.gout + b * P.gout_wave_stride + (fr - b * g.T);
-      float* __restrict__ Gp = P.gbuf + (fr >> 5) * ((long long)P.rows_pad * 32) + (fr & 31);
 #pragma unroll
-      for (int r = 0; r < CQ_ITEM_RB; ++r) {
-        if (r >= n_rb) continue;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int bin = (item.rb_first + r) * (CQ_ROWS / 2) + 2 * q + u;
-          if (bin >= P.n_bins) continue;
-          const float re = acc[r][fb][2 * u], im = acc[r][fb][2 * u + 1];
-          const float pw = re * re + im * im;
-          float gr, gi;
-          if (f == NNA_OUT_COMPLEX) {
-            gr = gp[(2LL * bin) * g.T];
-            gi = gp[(2LL * bin + 1) * g.T];
-          } else if (f == NNA_OUT_PHASE) {  // d atan2(Im, Re) = (Re dIm - Im dRe) / P
-            const float s = pw > 0.f ? gp[(long long)bin * g.T] / pw : 0.f;
-            gr = -s * im;
-            gi = s * re;
-          } else {
-            const float go = gp[(long long)bin * g.T];
-            const float s = f == NNA_OUT_MAGNITUDE ? grad_scale<NNA_OUT_MAGNITUDE>(go, pw)
-                            : f == NNA_OUT_POWER   ? grad_scale<NNA_OUT_POWER>(go, pw)
-                                                   : grad_scale<NNA_OUT_LOG>(go, pw);
-            gr = s * re;
-            gi = s * im;
-          }
-          Gp[(2LL * bin) * 32] = gr;
-          Gp[(2LL * bin + 1) * 32] = gi;
-        }
-      }
+      for (int r = 0; r < CQ_ITEM_RB; ++r)
+        if (r < n_rb) cqt_grad_bins(P, acc[r][fb], (item.rb_first + r) * (CQ_ROWS / 2) + 2 * q, f0 + wave * 64 + fb * 16 + n);
     }
     return;
   }
@@ -704,35 +727,120 @@ __global__ __launch_bounds__(256, 2) void cqt_kernel(const CqtParams P) {
 #pragma unroll
     for (int fb = 0; fb < 4; ++fb) {
       if (!valid[fb]) continue;
-      float* __restrict__ op = P.out + o_off[fb];
-      if (f == NNA_OUT_COMPLEX) {  // rows 2k = Re, 2k+1 = Im of bin k
-        if (bin0 < P.n_bins) {
-          op[(2LL * bin0) * g.T] = acc[r][fb][0];
-          op[(2LL * bin0 + 1) * g.T] = acc[r][fb][1];
-        }
-        if (bin0 + 1 < P.n_bins) {
-          op[(2LL * bin0 + 2) * g.T] = acc[r][fb][2];
-          op[(2LL * bin0 + 3) * g.T] = acc[r][fb][3];
-        }
-        continue;
-      }
-      if (f == NNA_OUT_PHASE) {
-        if (bin0 < P.n_bins) op[(long long)bin0 * g.T] = atan2f(acc[r][fb][1], acc[r][fb][0]);
-        if (bin0 + 1 < P.n_bins) op[(long long)(bin0 + 1) * g.T] = atan2f(acc[r][fb][3], acc[r][fb][2]);
-        continue;
-      }
-      const float p0 = acc[r][fb][0] * acc[r][fb][0] + acc[r][fb][1] * acc[r][fb][1];
-      const float p1 = acc[r][fb][2] * acc[r][fb][2] + acc[r][fb][3] * acc[r][fb][3];
-      if (bin0 < P.n_bins)
-        op[(long long)bin0 * g.T] = f == NNA_OUT_MAGNITUDE ? format_power<NNA_OUT_MAGNITUDE>(p0)
-                                    : f == NNA_OUT_POWER   ? p0
-                                                           : format_power<NNA_OUT_LOG>(p0);
-      if (bin0 + 1 < P.n_bins)
-        op[(long long)(bin0 + 1) * g.T] = f == NNA_OUT_MAGNITUDE ? format_power<NNA_OUT_MAGNITUDE>(p1)
-                                          : f == NNA_OUT_POWER   ? p1
-                                                                 : format_power<NNA_OUT_LOG>(p1);
+      cqt_store_bins(P, acc[r][fb], bin0, P.out + o_off[fb]);
     }
   }
+}
+
+// ---------------------------------------------------------------------------------------
+// The same contraction for trainable plans and batches that leave cqt_kernel's workgroups (256 frames, all taps of up to four row
+// blocks) fewer than the CUs: a wave takes 16 frames and one row block.  The sums are cqt_kernel's term by term and in its order
+// (hop columns in chunks of 16, every shift of a chunk before the next), so the results are too: in the backward pass the
+// derivatives that divide by |C| turn the order of its sums into results where C is near zero.
+// Both operands go from memory to registers in MFMA layout, eight steps of 16 taps ahead: weights as cqt_kernel streams them (from
+// the row-major bank, whose rows lie a power of two apart, sixteen requests met in one L2 channel: 210 us), the same for the
+// workgroup's four waves; samples 64 bytes of sixteen frames, all but one of them lines of
+// the step before.  Bound by the chain of dependent matrix instructions, 140 cycles a step.
+// 16 x 88,200 samples, 84 bins of up to 11,341 taps (MI355X): 33 workgroups 413 us -> 484 workgroups 172 us.
+// ---------------------------------------------------------------------------------------
+typedef f32x4 f32x4_u __attribute__((aligned(4)));
+constexpr int CQW_FRAMES = 64, CQW_AHEAD = 8;
+
+template <bool GRAD>
+__global__ __launch_bounds__(256, 2) void cqt_few_kernel(const CqtParams P, const int* __restrict__ row_lo, const int* __restrict__ row_hi) {
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q = lane >> 4, n = lane & 15;
+  const FrameGeom& g = P.g;
+  const long long n_ft = (g.n_frames + CQW_FRAMES - 1) / CQW_FRAMES;
+  const int rb = (int)(blockIdx.x / n_ft);  // longest kernels first
+  const long long fi = (blockIdx.x - rb * n_ft) * CQW_FRAMES + wave * 16 + n;
+  const int L = (int)g.L;
+  // steps of 16 taps of the block's longest (first) kernel
+  const int s_lo = row_lo[rb * CQ_ROWS] >> 4, s_hi = (row_hi[rb * CQ_ROWS] + 15) >> 4, n_step = s_hi - s_lo;
+  // the row block's place in the bank: block r of item `it`; the cursor runs through the item's chunks
+  int it = 0;
+  while (it + 1 < P.n_items && rb >= P.items[it + 1].rb_first) ++it;
+  const CqtItem item = P.items[it];
+  const int r = rb - item.rb_first;
+  const CqtChunk* __restrict__ ck = P.chunks + (long long)it * P.n_chunks;
+  long long frag = item.frag0, base = frag;  // first fragment of the chunk behind the cursor's; of the row block in the cursor's
+  int c = 0, jj = 0, n_jj = 0, tap0 = 0, last = 0;
+  auto next_step = [&](long long& fr) {  // tap and fragment of the step at the cursor; the last one again behind the end
+    while (jj >= n_jj && c < item.n_chunks) {
+      const CqtChunk k = ck[c++];
+      int before = 0, all = 0;
+#pragma unroll
+      for (int i = 0; i < CQ_ITEM_RB; ++i) {
+        if (i < r) before += k.nj[i] & 0xffff;
+        all += k.nj[i] & 0xffff;
+      }
+      const int mine = r == 0 ? k.nj[0] : r == 1 ? k.nj[1] : r == 2 ? k.nj[2] : k.nj[3];
+      const int off = r == 0 ? k.joff[0] : r == 1 ? k.joff[1] : r == 2 ? k.joff[2] : k.joff[3];
+      base = frag + before;
+      frag += all;
+      jj = 0;
+      n_jj = mine >> 16;
+      tap0 = (k.jlo + off) * P.tap_stride + k.c0;
+    }
+    if (jj < n_jj) {
+      last = tap0 + jj * P.tap_stride;
+      ++jj;
+    }
+    fr = base + jj - 1;
+    return last;
+  };
+  const float4* __restrict__ wp = P.bank + lane;
+  const long long f = fi < g.n_frames ? fi : g.n_frames - 1, b = f / g.T;
+  const float* __restrict__ xb = g.x + b * g.L;
+  const int pos = (int)(f - b * g.T) * g.hop - g.pad + 4 * q;
+  const bool edge = __builtin_amdgcn_ballot_w64(pos - 4 * q + 16 * s_lo < 0 || pos - 4 * q + 16 * s_hi > L) != 0;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto sweep = [&](auto edge_tag) {
+    constexpr bool EDGE = decltype(edge_tag)::value;
+    f32x4 w[CQW_AHEAD], x[CQW_AHEAD];
+    bool rev[CQW_AHEAD];
+    auto fetch = [&](f32x4& wv, f32x4& xv, bool& r) {
+      long long fr;
+      const int i = pos + next_step(fr);
+      wv = *reinterpret_cast<const f32x4*>(wp + fr * 64);
+      if constexpr (!EDGE) {
+        xv = *reinterpret_cast<const f32x4_u*>(xb + i);
+      } else {
+        // four samples on one side of either end are a stored run, read backwards behind an end (turned round when used)
+        const int src = i < 0 ? -i - 3 : i > L - 4 ? 2 * (L - 1) - i - 3 : i;
+        const bool gen = (unsigned)src > (unsigned)(L - 4);
+        r = src != i && !gen;
+        xv = *reinterpret_cast<const f32x4_u*>(xb + (src < 0 ? 0 : src > L - 4 ? L - 4 : src));
+        if (__builtin_amdgcn_ballot_w64(gen) != 0 && gen) {  // a run that straddles an end: sample by sample
+#pragma unroll
+          for (int e = 0; e < 4; ++e) xv[e] = xb[reflect_clamped(i + e, L)];
+        }
+      }
+    };
+#pragma unroll
+    for (int u = 0; u < CQW_AHEAD; ++u) fetch(w[u], x[u], rev[u]);
+    for (int s = 0; s < n_step; s += CQW_AHEAD) {
+#pragma unroll
+      for (int u = 0; u < CQW_AHEAD; ++u) {
+        f32x4 v = x[u];
+        if constexpr (EDGE) v = (f32x4){rev[u] ? v.w : v.x, rev[u] ? v.z : v.y, rev[u] ? v.y : v.z, rev[u] ? v.x : v.w};
+        if (s + u < n_step) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][k], v[k], acc, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(w[u], x[u], rev[u]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  if (edge) sweep(std::integral_constant<bool, true>{});
+  else sweep(std::integral_constant<bool, false>{});
+  if (fi >= g.n_frames) return;
+  const int bin0 = rb * (CQ_ROWS / 2) + 2 * q;
+  if constexpr (GRAD)
+    cqt_grad_bins(P, acc, bin0, f);
+  else
+    cqt_store_bins(P, acc, bin0, P.out + b * P.out_wave_stride + (long long)P.row_offset * g.T + (f - b * g.T));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -895,6 +1003,17 @@ hipError_t launch_fir_decimate(const FirParams& p, hipStream_t stream) {
   const size_t lds = 2ull * p.lds_stream * sizeof(float);
   if (lds > 64 * 1024) return hipErrorInvalidValue;
   hipLaunchKernelGGL(fir_decimate_kernel, dim3((unsigned)tiles, (unsigned)p.B), dim3(256), lds, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_cqt_few(const CqtParams& p, const int* row_lo, const int* row_hi, hipStream_t stream) {
+  clear_stale_error();
+  const long long blocks = (p.g.n_frames + CQW_FRAMES - 1) / CQW_FRAMES * ((2LL * p.n_bins + CQ_ROWS - 1) / CQ_ROWS);
+  if (blocks <= 0 || blocks > 0x7fffffffLL || (p.gbuf && (!p.gout || p.rows_pad < 2 * p.n_bins))) return hipErrorInvalidValue;
+  if (p.gbuf)
+    hipLaunchKernelGGL(cqt_few_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, p, row_lo, row_hi);
+  else
+    hipLaunchKernelGGL(cqt_few_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, p, row_lo, row_hi);
   return hipGetLastError();
 }
 

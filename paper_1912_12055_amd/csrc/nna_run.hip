@@ -397,6 +397,12 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
   return NNA_OK;
 }
 
+hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t stream) {
+  if (sub->d_wrm && P.n_ft * P.n_items < 256)
+    return nna::launch_cqt_few(P, sub->d_row_lo, sub->d_row_hi, stream);
+  return nna::launch_cqt(P, stream);
+}
+
 // one launch of the CQT kernel: `sub`'s bank over T frames of each of the B waveforms in x
 nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
                     long long out_wave_stride, int row_offset, void* hip_stream, bool may_fold = false) {
@@ -433,7 +439,7 @@ nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long 
   const long long nseg = 1 + (M - 1 + T - 1) / T;
   P.lds_rows = (int)((M + nseg * extra + 63) / 64 * 64);  // whole loader passes of 64 rows (<= CQ_LDS_ROWS_MAX)
   P.n_ft = (P.g.n_frames + M - 1) / M;
-  hipError_t e = nna::launch_cqt(P, reinterpret_cast<hipStream_t>(hip_stream));
+  hipError_t e = launch_conv(sub, P, reinterpret_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
   return NNA_OK;
 }
