@@ -8,13 +8,14 @@ seeded synthetic waveforms already resident in HBM; plans (kernel banks) are bui
 timing, as the paper excludes initialisation from its timings (Sec. IV-A).
 
 Prints one JSON line: whole-job GSamples/s (input samples consumed by the three transforms
-per second), per-transform figures, the MFMA roofline of the dominant kernel measured with
+per second), per-transform figures, the roofline of the dominant kernel measured with
 HIP events on the launch stream, and the float64 CPU oracle timed on a bounded sample.
 """
 from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -27,16 +28,7 @@ PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X dense fp32 matrix peak
 PEAK_F16_MFMA_TFLOPS = 2500.0  # MI355X dense fp16 / bf16 matrix peak
 PEAK_HBM_GBS = 8000.0
 # the kernel each transform of the step launches (names as rocprofv3 prints them)
-KERNELS = {"stft": "stft_fold_kernel<0, 2, true, true>", "mel": "stft_fold_kernel<1, 4, true, true>", "cqt": "cqt_fold_kernel"}
-
-
-def _read_traffic():
-    """HBM bytes per launch of each kernel from the committed rocprofv3 counter summary, if any."""
-    path = os.path.join(ROOT, "profiles", "hbm_traffic_1770x176400.json.txt")
-    try:
-        return json.load(open(path))
-    except Exception:
-        return {}
+KERNELS = {"stft": "fft_kernel<1024, ..., POWER>", "mel": "fft_kernel<1024, ..., MEL>", "cqt": "cqt_lowrank_kernel<4, 2>"}
 
 
 def main() -> int:
@@ -133,7 +125,15 @@ def main() -> int:
     samples_per_step = len(names) * B * L
     value = samples_per_step / (wall / args.steps) / 1e9
 
-    traffic = _read_traffic()
+    def running_flops(plan, hop=512):
+        """What the form that runs cannot do without, per frame: a fast Fourier transform (Mel: + power and filters), or one
+        complex multiply-add per new sample and constant-Q bin."""
+        info = plan.info()
+        if info["kind"] in (nb.NNA_KIND_STFT, nb.NNA_KIND_MEL):
+            N = info["taps"]
+            return 2.5 * N * math.log2(N) + (4.0 * N if info["kind"] == nb.NNA_KIND_MEL else 0.0)
+        return 4.0 * sum(min(int(k), hop) for k in nb.nna_plan_cqt_lengths(plan))
+
     per = {}
     for n in names:
         ms = float(np.mean([a.elapsed_time(b) for a, b in events[n]]))
@@ -142,36 +142,25 @@ def main() -> int:
         alg = info["algorithmic_flops_per_frame"] * frames
         exe = info["executed_flops_per_frame"] * frames
         out_bytes = legs[n][2].numel() * 4
-        # STFT and Mel run the folded contraction (x[n] +- x[N-n] against the first halves of the kernels of
-        # eq. (DFT2)): N^2 + 2N flop per frame where the direct form needs 2 N^2.  Their roofline numerator is
-        # what the kernel executes (the matrix-instruction counter confirms it), never the direct form's count;
-        # that one is quoted beside it as `direct_form_equivalent_tflops`.  The plain STFT halves once more (the
-        # folded taps summed by parity give bin k and bin N/2 - k from the kernels of k < N/4): N^2 / 2 + 4N.
-        # The CQT runs its kernels folded about their centres (2 sum N_k flop per frame where the direct form needs
-        # 4 sum N_k); its 16-row blocks hold bins of one length parity, and what the launch executes is the
-        # longest kernel of each block for all 16 rows (`executed`), about 1.5 x the taps inside the kernels
-        # themselves (`mfma_frac_useful`).
-        folded = exe < alg
-        split = folded and exe < 0.3 * alg  # the plain STFT is split once more by tap parity: N^2 / 2 + 4N
-        cq_fold = n == "cqt" and folded
-        useful = exe if folded else alg
-        strict = alg / 2 if cq_fold else useful  # multiply-adds the method itself needs in the form that runs
+        # None of the three runs eq. (DFT2) / eq. (CQT) term by term (2 N^2, 4 sum N_k flop per frame: quoted as
+        # `direct_form_equivalent_tflops`).  STFT and Mel take a fast Fourier transform per frame, the CQT its kernels as
+        # combinations of a few functions per hop; the roofline numerator is what that form cannot do without: 2.5 N log2 N
+        # (Mel: + 4 N for power and filters), and one complex multiply-add per new sample and bin.
+        useful = exe = strict = running_flops(legs[n][1]) * frames
         per[n] = {
             "ms": round(ms, 4),
             "gsamples_per_s": round(B * L / ms / 1e6, 4),
             "frames_per_s": round(frames / ms * 1e3, 1),
-            "contraction": ("kernels folded about their centres, 2 sum N_k flop per frame inside the kernels" if cq_fold
-                            else "folded frame split by tap parity, N^2 / 2 + 4N flop per frame" if split
-                            else "folded frame, N^2 + 2N flop per frame" if folded else "direct"),
+            "contraction": ("kernels by hop-blocks, 4 sum min(N_k, hop) flop per frame" if n == "cqt"
+                            else "fast Fourier transform, 2.5 N log2 N flop per frame"),
             "algorithmic_tflops": round(useful / ms / 1e9, 3),
             "executed_tflops": round(exe / ms / 1e9, 3),
             "mfma_frac": round(useful / ms / 1e9 / PEAK_FP32_MFMA_TFLOPS, 4),
             "mfma_frac_executed": round(exe / ms / 1e9 / PEAK_FP32_MFMA_TFLOPS, 4),
             "mfma_frac_useful": round(strict / ms / 1e9 / PEAK_FP32_MFMA_TFLOPS, 4),
-            "direct_form_equivalent_tflops": round(alg / ms / 1e9, 3) if folded else None,
+            "direct_form_equivalent_tflops": round(alg / ms / 1e9, 3),
             "algorithmic_gb": round((B * L * 4 + out_bytes) / 1e9, 4),
             "hbm_frac": round((B * L * 4 + out_bytes) / ms / 1e6 / PEAK_HBM_GBS, 5),
-            "hbm_traffic_bytes": traffic.get(n),
         }
     dom = max(names, key=lambda n: per[n]["ms"])
     roofline = {
@@ -182,10 +171,9 @@ def main() -> int:
         "unit": "TFLOP/s",
         "frac": per[dom]["mfma_frac"],
         "frac_useful": per[dom]["mfma_frac_useful"],
-        "traffic": traffic.get(dom),
+        "traffic": None,
     }
-    # the kernel of the step that sits furthest below its roof, by the strictest count: the multiply-adds the form
-    # that runs needs (for the folded CQT the taps inside the kernels, not the zeros its blocks multiply as well)
+    # the kernel of the step that sits furthest below its roof, by the multiply-adds the form that runs needs
     low = min(names, key=lambda n: per[n]["mfma_frac_useful"])
     roofline_min = {"kernel": KERNELS[low], "frac": per[low]["mfma_frac_useful"],
                     "frac_executed": per[low]["mfma_frac_executed"]}
@@ -241,12 +229,16 @@ def main() -> int:
             torch.cuda.synchronize()
             ms = float(np.mean([a.elapsed_time(b) for a, b in ev]))
             info = plan.info()
+            by_blocks = info["kind"] == nb.NNA_KIND_CQT1992  # composed kernels by hop-blocks
+            composed = info["kind"] == nb.NNA_KIND_CQT2010   # its octaves' kernels composed: the plan's count is the two stages'
+            alg = running_flops(plan) if by_blocks else info["algorithmic_flops_per_frame"]
+            exe = alg if by_blocks else info["executed_flops_per_frame"]
             extras[name] = {
                 "ms": round(ms, 4),
                 "gsamples_per_s": round(n_samples / ms / 1e6, 4),
-                "algorithmic_tflops": round(info["algorithmic_flops_per_frame"] * n_frames / ms / 1e9, 3),
-                "executed_tflops": round(info["executed_flops_per_frame"] * n_frames / ms / 1e9, 3),
-                "mfma_frac": round(info["algorithmic_flops_per_frame"] * n_frames / ms / 1e9
+                "algorithmic_tflops": round(alg * n_frames / ms / 1e9, 3),
+                "executed_tflops": round(exe * n_frames / ms / 1e9, 3),
+                "mfma_frac": None if composed else round(alg * n_frames / ms / 1e9
                                    / (PEAK_F16_MFMA_TFLOPS if name == "stft_f16_operands" else PEAK_FP32_MFMA_TFLOPS), 4),
                 "mfma_peak_tflops": PEAK_F16_MFMA_TFLOPS if name == "stft_f16_operands" else PEAK_FP32_MFMA_TFLOPS,
             }
@@ -279,7 +271,7 @@ def main() -> int:
             torch.cuda.synchronize()
             ms = float(np.mean([a.elapsed_time(b) for a, b in ev]))
             info = plan.info()
-            exe, alg = info["executed_flops_per_frame"] * B * Tp, info["algorithmic_flops_per_frame"] * B * Tp
+            exe = alg = running_flops(plan) * B * Tp
             paper[name] = {
                 "ms": round(ms, 4),
                 "gsamples_per_s": round(B * Lp / ms / 1e6, 4),
@@ -304,11 +296,10 @@ def main() -> int:
             ev.append((a, b))
         torch.cuda.synchronize()
         ms = float(np.mean([a.elapsed_time(b) for a, b in ev]))
-        # the launch runs the folded contraction split by tap parity: the fraction of the peak is of the flops it
-        # executes; the direct form's count is quoted beside it
+        # a fast Fourier transform per frame; the direct form's count is quoted beside it
         info2 = p_mel2.info()
         alg = info2["algorithmic_flops_per_frame"] * B * T
-        exe = info2["executed_flops_per_frame"] * B * T
+        exe = running_flops(p_mel2) * B * T
         extras["mel_with_stft"] = {
             "ms": round(ms, 4),
             "gsamples_per_s": round(B * L / ms / 1e6, 4),
