@@ -163,8 +163,8 @@ nna_status nna_plan_mel(nna_plan** plan, int sr, int n_fft, int hop, nna_window 
  * that pays (a seventh or more of the multiply-adds saved: 12 or more bins per octave, kernels of
  * eight hops or more, hop a multiple of 16 dividing n_taps / 2, a window that vanishes at n = 0) they are
  * applied to the frame folded about that centre.  With a hop that is a multiple of 32 and divides n_taps (at most 2^18) they are
- * cut at the hops' boundaries and applied as combinations of the few functions per hop that hold them to 6e-8 of each kernel's
- * norm (half a unit in the last place of a float32 tap), wherever that takes fewer multiply-adds.  nna_plan_info reports the flops
+ * cut at the hops' boundaries and applied as combinations of the few functions per hop that hold each kernel as closely as
+ * its taps rounded to float32 would (2.6e-8 of its norm), wherever that takes fewer multiply-adds.  nna_plan_info reports the flops
  * of the direct or folded form; nna_plan_bank always returns the kernels as defined above.
  */
 nna_status nna_plan_cqt(nna_plan** plan, int sr, int hop, double fmin, int n_bins, int bins_per_octave,
@@ -481,6 +481,18 @@ nna_status nna_plan_part(const nna_plan* plan, int index, const nna_plan** part)
  * small.  The required size is returned by nna_plan_info (rows * K).
  */
 nna_status nna_plan_bank(const nna_plan* plan, double* host_out, size_t cap);
+
+/*
+ * Plans from nna_plan_cqt and nna_plan_cqt1992 whose kernels are fixed, for inspection: host_out[2 n_bins, K], the kernels as the
+ * calls apply them to the waveform -- the float32 numbers of the form that runs multiplied out in double.  Computed on the host.
+ */
+nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size_t cap);
+/*
+ * ... and how a call on B waveforms of L samples cuts them up: frames per workgroup (frames[0], frames[1]) and 16-frame blocks per
+ * wave (blocks[0], blocks[1]: 1, 2 or 4) of the bins taken as combinations of a basis (0) and tap by tap beside them (1); zero
+ * where there are none, all zero where the call runs another kernel.
+ */
+nna_status nna_plan_applied_tiles(const nna_plan* plan, long long B, long long L, int* frames, int* blocks);
 
 /* Mel plans only: the filterbank W[n_mels, n_fft/2+1] as the GPU holds it. */
 nna_status nna_plan_mel_weights(const nna_plan* plan, double* host_out, size_t cap);

@@ -34,7 +34,7 @@ EXPORTS = [
     "nna_cqt_backward_workspace", "nna_cqt_backward", "nna_mel_with_stft", "nna_cqt2010v2_static",
     "nna_cqt2010v2_backward_workspace", "nna_cqt2010v2_backward",
     "nna_plan_get_spectral_kernels", "nna_plan_set_spectral_kernels", "nna_cqt1992_backward_workspace", "nna_cqt1992_backward",
-    "nna_cqt2010_backward_workspace", "nna_cqt2010_backward",
+    "nna_cqt2010_backward_workspace", "nna_cqt2010_backward", "nna_plan_applied_kernels", "nna_plan_applied_tiles",
     "nna_plan_destroy",
     "nna_status_str", "nna_last_error",
 ]
@@ -112,6 +112,8 @@ def lib():
         for name in ("nna_stft", "nna_mel", "nna_cqt", "nna_cqt1992", "nna_cqt2010v2_static"):
             getattr(L, name).argtypes = [_VP, _VP, _LL, _LL, _VP, _VP]
         L.nna_plan_bank.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
+        L.nna_plan_applied_kernels.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
+        L.nna_plan_applied_tiles.argtypes = [_VP, _LL, _LL, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int)]
         L.nna_plan_mel_weights.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
         L.nna_plan_info.argtypes = [_VP, _c.POINTER(_c.c_int), _c.POINTER(_LL), _c.POINTER(_LL), _c.POINTER(_LL),
                                     _c.POINTER(_c.c_double), _c.POINTER(_c.c_double)]
@@ -254,6 +256,21 @@ def nna_plan_bank(plan: Plan) -> np.ndarray:
     out = np.empty((i["bank_rows"], i["taps"]), dtype=np.float64)
     _check(lib().nna_plan_bank(plan.handle, out.ctypes.data_as(_c.POINTER(_c.c_double)), out.size))
     return out
+
+
+def nna_plan_applied_kernels(plan: Plan) -> np.ndarray:
+    """The kernels a fixed constant-Q plan applies, [2 n_bins, K], multiplied out in 64 bits."""
+    i = plan.info()
+    out = np.empty((2 * len(nna_plan_cqt_lengths(plan)), i["taps"]), dtype=np.float64)
+    _check(lib().nna_plan_applied_kernels(plan.handle, out.ctypes.data_as(_c.POINTER(_c.c_double)), out.size))
+    return out
+
+
+def nna_plan_applied_tiles(plan: Plan, B: int, L: int):
+    """((frames, 16-frame blocks per wave) of the bins with a basis, the same of those taken tap by tap)."""
+    f, b = (_c.c_int * 2)(), (_c.c_int * 2)()
+    _check(lib().nna_plan_applied_tiles(plan.handle, B, L, f, b))
+    return (f[0], b[0]), (f[1], b[1])
 
 
 def nna_plan_mel_weights(plan: Plan) -> np.ndarray:

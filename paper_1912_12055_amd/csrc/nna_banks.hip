@@ -764,13 +764,15 @@ void build_cqt_bank(nna_plan* p) {
 
 // ---- CQT kernels in two stages over hop-blocks (nna_kernels_cql.hip) ---------------------------
 // A kernel cut at the hops' boundaries is a stack of rows of `hop` taps, and the rows of neighbouring long kernels are smooth
-// functions of little bandwidth: the 2,144 rows of the 16 lowest bins of 24 per octave at 44.1 kHz, hop 512, lie within 6e-8 of
-// a space of 12 dimensions.  So U[i][c] (i < r) is an orthonormal basis of that space and A the rows' coordinates in it:
+// functions of little bandwidth: the 2,880 rows of the 16 lowest bins of 24 per octave at 44.1 kHz, hop 512, lie within 1e-8 of
+// a space of 16 dimensions.  So U[i][c] (i < r) is an orthonormal basis of that space and A the rows' coordinates in it:
 //     y[b][i] = sum_c U[i][c] x[b hop + c],   C_k[t] = sum_j sum_i A_k[j][i] y[t + j][i].
 // The basis is grown by Gram-Schmidt, the row furthest from the space next, until what is left of every kernel is below a
-// quarter of kTol of its norm; the coordinates are then turned to their principal axes and as many of these dropped as kTol allows.
+// quarter of what rounding its taps to float32 costs; the coordinates are then turned to their principal axes, the last of which are
+// dropped as far as the product A U stays as close to the kernels as float32 taps are (2.6e-8 of the norm).
 namespace {
-constexpr double kLowrankTol = 6e-8;  // half a unit in the last place of float32: the weights' own rounding
+// What rounding to float32 costs a kernel's taps, of its norm: 2.5e-8 .. 2.7e-8 for the kernels of eq. (CQT).
+constexpr double kTapRounding = 2.6e-8;
 
 // (eight partial sums: one chain of additions would cost four cycles a term)
 double dot(const double* a, const double* b, int n) {
@@ -933,9 +935,10 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
     std::vector<double> U, C((size_t)m * cap, 0.0);
     int r0 = 0;
     bool fits = false;
+    std::vector<double> left(nb);  // of every kernel's squared norm
     for (;;) {
       int best = 0;
-      std::vector<double> left(nb, 0.0);
+      std::fill(left.begin(), left.end(), 0.0);
       for (int i = 0; i < m; ++i) {
         const double* row = &R[(size_t)i * hop];
         const double s = dot(row, row, hop);
@@ -943,7 +946,7 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
         left[i / (2 * J)] += s;
         if (s > n2[best]) best = i;
       }
-      if (std::sqrt(*std::max_element(left.begin(), left.end())) <= 0.25 * kLowrankTol) {
+      if (std::sqrt(*std::max_element(left.begin(), left.end())) <= 0.25 * kTapRounding) {
         fits = true;
         break;
       }
@@ -995,19 +998,44 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
     }
     for (int i = 0; i < m; ++i)
       for (int a = 0; a < r0; ++a) D[(size_t)i * r0 + a] = dot(&C[(size_t)i * cap], &Vt[(size_t)a * r0], r0);
-    // what every kernel loses with the axes from `keep` on
-    std::vector<double> lost(nb, 0.0);
-    int keep = r0;
-    while (keep > 1) {
-      std::vector<double> next = lost;
-      for (int i = 0; i < m; ++i) next[i / (2 * J)] += D[(size_t)i * r0 + keep - 1] * D[(size_t)i * r0 + keep - 1];
-      if (std::sqrt(*std::max_element(next.begin(), next.end())) > kLowrankTol) break;
-      lost = next;
-      --keep;
-    }
+    // before[k][a]: what the axes ahead of axis a hold of kernel k (a fraction of its squared norm)
+    std::vector<double> before((size_t)nb * (r0 + 1), 0.0);
+    for (int k = 0; k < nb; ++k)
+      for (int a = 0; a < r0; ++a) {
+        double s = 0;
+        for (int i = k * 2 * J; i < (k + 1) * 2 * J; ++i) s += D[(size_t)i * r0 + a] * D[(size_t)i * r0 + a];
+        before[(size_t)k * (r0 + 1) + a + 1] = before[(size_t)k * (r0 + 1) + a] + s;
+      }
+    // The smallest basis whose product with the coefficients is as close to every kernel as its float32 taps are.  Of r functions
+    // `keep` are axes; the others repeat the first ones, for what their float32 coefficients leave.  What float32 leaves of the
+    // functions themselves is in the first stage's spare rows, for the first n_lo of them: these hold nearly all of a kernel.
     nna::CqlItem item{};
-    item.r = (keep + 3) / 8 * 8 + 4;  // 4 modulo 8: the rows of 16 frames then lie on different LDS banks
-    item.n_ib = (item.r + 15) / 16;
+    int keep = 0, twice = 0;
+    for (int r = 4; r <= 16 * CQL_MAX_BASIS && !item.r; r += 8) {  // 4 modulo 8: the rows of 16 frames then lie on different LDS banks
+      const int n_lo = r % 16 == 4 && r > 4 ? 8 : 4;
+      double least = kTapRounding * kTapRounding;
+      for (int kp = r / 2; kp <= std::min(r, r0); ++kp) {
+        double worst = 0;
+        for (int k = 0; k < nb; ++k) {
+          const double* h = &before[(size_t)k * (r0 + 1)];
+          const double rounded = 2.0 * h[kp] - h[std::min(kp, n_lo)] - h[std::min(kp, r - kp)];
+          worst = std::max(worst, left[k] + h[r0] - h[kp] + kTapRounding * kTapRounding * rounded);
+        }
+        if (worst <= least) {
+          least = worst;
+          item.r = r;
+          item.n_lo = n_lo;
+          keep = kp;
+          twice = std::min(kp, r - kp);
+        }
+      }
+    }
+    if (!item.r) {
+      as_is.push_back(k0);
+      continue;
+    }
+    auto axis = [&](int i) { return i < keep ? i : i < keep + twice ? i - keep : -1; };  // of function i
+    item.n_ib = (item.r + item.n_lo + 15) / 16;
     item.j0 = j0;
     item.jspan = J;
     item.n_step = (int)ceil_div((long long)J * item.r, 16);
@@ -1024,15 +1052,19 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
     any = true;
     // ... of the kernel that runs otherwise: 0.55 of the taps where they fold (dense kernels do not)
     p->lr_limit += (p->row_e[2 * k0] - p->row_s[2 * k0] == K ? 1.0 : 0.55) * direct;
-    // basis fragments [chunk][block][half][lane]: lane (q, i) holds U[16 block + i][32 chunk + 16 half + 4 q + e]
+    // basis fragments [chunk][block][half][lane]: lane (q, i) holds row i of the block, columns 32 chunk + 16 half + 4 q + e.  The
+    // last n_lo rows of block 0 are what float32 leaves of its first n_lo.
     item.u0 = (long long)p->h_lu.size() / 4;
     for (int c = 0; c < hop; c += 32)
       for (int ib = 0; ib < item.n_ib; ++ib)
         for (int half = 0; half < 2; ++half)
           for (int lane = 0; lane < 64; ++lane)
             for (int e = 0; e < 4; ++e) {
-              const int i = 16 * ib + (lane & 15), col = c + 16 * half + 4 * (lane >> 4) + e;
-              p->h_lu.push_back(i < std::min(item.r, r0) ? (float)W[(size_t)i * hop + col] : 0.0f);
+              const int row = lane & 15, col = c + 16 * half + 4 * (lane >> 4) + e;
+              const bool lo = ib == 0 && row >= 16 - item.n_lo;
+              const int i = ib ? 16 * ib - item.n_lo + row : lo ? row - (16 - item.n_lo) : row, a = i < item.r ? axis(i) : -1;
+              const double u = a < 0 ? 0.0 : W[(size_t)a * hop + col];
+              p->h_lu.push_back(lo ? (float)(u - (double)(float)u) : (float)u);
             }
     // coefficient fragments [step][lane]: lane (q, row) holds A[row][16 step + 4 q + e], the coordinates of the row's
     // hop-blocks one after the other
@@ -1042,8 +1074,9 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
         for (int lane = 0; lane < 64; ++lane)
           for (int e = 0; e < 4; ++e) {
             const int row = 16 * b + (lane & 15), f = 16 * s + 4 * (lane >> 4) + e, j = f / item.r, i = f - j * item.r;
-            const bool there = row < 2 * nb && j < J && i < r0;
-            p->h_la.push_back(there ? (float)(D[((size_t)row * J + j) * r0 + i] * std::sqrt(norm2[row / 2])) : 0.0f);
+            const int a = row < 2 * nb && j < J ? axis(i) : -1;
+            const double v = a < 0 ? 0.0 : D[((size_t)row * J + j) * r0 + a] * std::sqrt(norm2[row / 2]);
+            p->h_la.push_back(i < keep ? (float)v : (float)(v - (double)(float)v));
           }
     }
     p->h_litems.push_back(item);
@@ -1060,6 +1093,73 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
   };
   std::stable_sort(p->h_litems.begin(), p->h_litems.end(), [&](const nna::CqlItem& a, const nna::CqlItem& b) { return weight(a) > weight(b); });
   p->lowrank = true;
+}
+
+// A plan that holds what build_cqt_bank_lowrank made of `sub`'s kernels (a device plan keeps them on the device only); false: `sub`
+// is not a plan whose kernels are taken by hop-blocks.  `owner`: the plan with frequency-domain kernels that `sub` composes, or sub.
+bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy) {
+  if (!sub->hop_blocks) return false;
+  copy.K = sub->K;
+  copy.hop = sub->hop;
+  copy.pad = sub->pad;
+  copy.n_bins = sub->n_bins;
+  copy.row_s = sub->row_s;
+  copy.row_e = sub->row_e;
+  if (owner != sub) {
+    const std::vector<double> rows = cqt1992_composed_rows(owner);
+    build_cqt_bank_lowrank(&copy, [&](int row, long long tap) { return rows[(size_t)row * copy.K + tap]; });
+  } else {
+    CqtKernelGen gen(sub);
+    build_cqt_bank_lowrank(&copy, [&](int row, long long tap) { return gen.value(row, tap); });
+  }
+  return copy.lowrank;
+}
+
+// [2 n_bins][K]: the kernels of `p`'s items, multiplied out
+void cqt_applied_rows(const nna_plan* p, double* out) {
+  const long long K = p->K;
+  const int hop = p->hop;
+  std::fill(out, out + 2LL * p->n_bins * K, 0.0);
+  std::vector<double> U;
+  for (const nna::CqlItem& it : p->h_litems) {
+    const float* lu = p->h_lu.data() + 4 * it.u0;
+    if (!it.r) {
+      const int* chunk0 = p->h_lsteps.data() + it.step0;
+      for (int c = 0; c < hop; c += 32)
+        for (int s = chunk0[c / 32]; s < chunk0[c / 32 + 1]; ++s) {
+          const int d = (chunk0 + hop / 32 + 1)[s];
+          for (int b = 0; b < (d & 7); ++b)
+            for (int lane = 0; lane < 64; ++lane)
+              for (int e = 0; e < 4; ++e) {
+                const int row = 16 * b + (lane & 15);
+                const long long tap = (long long)(it.j0 + (d >> 12)) * hop + ((d >> 3) & 511) * 16 + 4 * (lane >> 4) + e;
+                if (row < 2 * it.n_bins && tap < K) out[(2LL * it.bin0 + row) * K + tap] = lu[(((size_t)s * 4 + b) * 64 + lane) * 4 + e];
+              }
+        }
+      continue;
+    }
+    U.assign((size_t)it.r * hop, 0.0);
+    for (int c = 0; c < hop; ++c) {
+      auto entry = [&](int blk, int row) {
+        const int lane = (c % 16) / 4 * 16 + row;
+        return (double)lu[((((size_t)(c / 32) * it.n_ib + blk) * 2 + (c % 32) / 16) * 64 + lane) * 4 + c % 4];
+      };
+      for (int i = 0; i < it.r; ++i) {
+        const int first = 16 - it.n_lo;  // functions in block 0
+        U[(size_t)i * hop + c] = i < first ? entry(0, i) : entry(1 + (i - first) / 16, (i - first) % 16);
+        if (i < it.n_lo) U[(size_t)i * hop + c] += entry(0, first + i);
+      }
+    }
+    for (int row = 0; row < 2 * it.n_bins; ++row)
+      for (int f = 0; f < it.jspan * it.r; ++f) {
+        const int b = row / 16, s = f / 16, s0 = b ? it.s_lo : 0, s1 = b ? it.s_hi : it.n_step;
+        if (s < s0 || s >= s1) continue;
+        const double a = p->h_la[(size_t)it.a0[b] * 4 + ((size_t)(s - s0) * 64 + (f % 16) / 4 * 16 + row % 16) * 4 + f % 4];
+        double* o = out + (2LL * it.bin0 + row) * K + (long long)(it.j0 + f / it.r) * hop;
+        const double* u = &U[(size_t)(f % it.r) * hop];
+        for (int c = 0; c < hop; ++c) o[c] += a * u[c];
+      }
+  }
 }
 
 // ---- CQT bank folded about the kernels' centres (nna_kernels_cqf.hip) --------------------------

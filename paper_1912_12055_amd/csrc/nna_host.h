@@ -203,6 +203,7 @@ struct nna_plan {
   int* d_qbins = nullptr;
   bool runs_cqfold() const { return cq_fold && !d_wrm; }
   // The long kernels as combinations of a few functions per hop-block (nna_kernels_cql.hip)
+  bool hop_blocks = false;  // a plan whose kernels may be taken so (a host-only plan holds no basis)
   bool lowrank = false;
   std::vector<nna::CqlItem> h_litems;
   std::vector<float> h_lu, h_la;
@@ -389,6 +390,8 @@ std::vector<double> cqt1992_composed_rows(const nna_plan* p);
 void build_cqt_bank(nna_plan* p);
 // Rows 2k, 2k + 1 of `value` (bin k's kernel, p->K taps) in the form of nna_kernels_cql.hip; sets p->lowrank if it saves anything
 void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long long)>& value);
+bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy);
+void cqt_applied_rows(const nna_plan* p, double* out);
 void build_cqt_bank_rows(nna_plan* c, const std::vector<double>& rows);
 void build_cqt_bank_fold(nna_plan* p);  // sets p->cq_fold if the plan qualifies
 // the decimation filter of `fir_taps` taps: its taps, their split by parity for the decimation kernel, and the
@@ -412,6 +415,9 @@ inline void octave_bins(int n_bins, int bpo, int a, int& lo, int& hi) {
   hi = n_bins - a * bpo;
   lo = std::max(0, hi - bpo);
 }
+// tiles of a launch of nna_kernels_cql.hip; false: not a launch for it
+bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::CqlParams& P);
+long long frames_of(const nna_plan* p, long long L);
 // cqt_kernel's launch, or on a trainable plan the one for batches that would leave most CUs without a workgroup
 hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t stream);
 bool cqt2010_lengths(const nna_plan* plan, long long L, long long (&La)[MAX_OCTAVES]);

@@ -274,12 +274,12 @@ struct CqlItem {
   long long a0[2];   // first float4 of row block b's coefficients: [16-tap step][64 lanes]
   long long step0;   // r = 0: first entry of the item's step table
   int r;             // basis functions, 4 modulo 8: the pitch of a hop-block's coefficients in LDS
-  int n_ib;          // 16-row blocks of the basis
+  int n_ib;          // 16-row blocks of the basis: block 0 holds functions 0 .. 15 - n_lo, and what float32 leaves of the first n_lo
   int j0, jspan;     // the item's hop-blocks of a frame: j0 .. j0 + jspan - 1
   int s_lo, s_hi;    // steps of 16 coefficients in which the second row block is not zero; the first has all n_step
   int n_step;
   int bin0, n_bins;  // first bin, bins (1 .. 16; r = 0: 1 .. 32)
-  int pad0;
+  int n_lo;          // 4 or 8
 };
 
 struct CqlPart {

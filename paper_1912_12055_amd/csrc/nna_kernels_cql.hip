@@ -1,8 +1,8 @@
 // Constant-Q transform with time-domain kernels (Sec. III-C, eq. (CQT)), the kernels as combinations of a few functions per hop.
 //
 // A kernel of N_k taps spans J hops, and cut at the hops' boundaries the kernels of 16 neighbouring bins are J x 32 rows of `hop`
-// taps.  Far fewer dimensions hold them all (to 6e-8 of each kernel, the rounding of its float32 taps; nna_banks.hip), because
-// within one hop a low bin's kernel is a smooth function.  With U an orthonormal basis of that space and A the coordinates,
+// taps.  Far fewer dimensions hold them all, as closely as float32 taps would (nna_banks.hip), because within one hop a low bin's
+// kernel is a smooth function.  With U an orthonormal basis of that space and A the coordinates,
 //     y[b][i] = sum_c U[i][c] x[b hop + c]          i < r, every hop-block b of the padded waveform
 //     C_k[t]  = sum_j sum_i A_k[j][i] y[t + j][i].
 // Bins of 24 per octave at 44.1 kHz, hop 512: 0.8 million multiply-adds per frame against 1.6 million of the kernels folded about
@@ -17,8 +17,8 @@
 // modulo 8, which keeps the rows of sixteen frames on different banks.
 //
 // Bound by the float32 matrix pipe (two thirds busy at the batch below); a short batch by latency, a workgroup or two per CU.
-// 1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms folded about the centres -> 7.2 ms; 16 x 220,500, 84 bins
-// of 12 per octave: 300 -> 63 us; the dense composed kernels of the frequency-domain layer (16 x 220,500, 32,768 taps): 566 -> 158 us.
+// 1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms folded about the centres -> 8.3 ms; 16 x 220,500, 84 bins
+// of 12 per octave: 300 -> 65 us; the dense composed kernels of the frequency-domain layer (16 x 220,500, 32,768 taps): 566 -> 205 us.
 #include <type_traits>
 
 #include "nna_device.h"
@@ -351,15 +351,25 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       for (int i = 0; i < IB; ++i) y[p][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     contract(edge_tag, ib_tag, y, xb, pos, P.u + item.u0 + (long long)ib0 * 128, item.n_ib, 0, hop);
-    // lane (q, n), register e: basis function 16 block + 4 q + e of hop-block n
+    // lane (q, n), register e: row 4 q + e of a basis block, hop-block n.  Block 0's last n_lo rows go to its first.
+    const int n_lo = item.n_lo;
+    if (ib0 == 0) {
+#pragma unroll
+      for (int p = 0; p < NB; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float lo = __shfl(y[p][0][e], lane + 64 - 4 * n_lo);  // (in every lane; used by those of the first n_lo rows)
+          if (4 * q < n_lo) y[p][0][e] += lo;
+        }
+    }
 #pragma unroll
     for (int p = 0; p < NB; ++p) {
       const int row = (blk0 + p) * 16 + n;
       if (row < rows_used) {
 #pragma unroll
         for (int i = 0; i < IB; ++i) {
-          const int f = (ib0 + i) * 16 + 4 * q;
-          if (f < r) *reinterpret_cast<f32x4*>(Y + row * r + f) = y[p][i];
+          const int blk = ib0 + i, f = blk ? 16 * blk - n_lo + 4 * q : 4 * q;
+          if (f < r && (blk || f < 16 - n_lo)) *reinterpret_cast<f32x4*>(Y + row * r + f) = y[p][i];
         }
       }
     }

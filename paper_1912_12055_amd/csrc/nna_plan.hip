@@ -204,6 +204,7 @@ nna_status make_cqt_plan(nna_plan** plan, int sr, int hop, double fmin, int k_fi
     p->pad = center ? (int)(taps / 2) : 0;
     for (int k = 0; k < n_bins; ++k) p->sk[k] = (taps - p->Nk[k]) / 2;
     build_cqt_bank(p);
+    p->hop_blocks = lowrank;
     if (lowrank && device >= 0) {
       CqtKernelGen gen(p);
       build_cqt_bank_lowrank(p, [&](int row, long long tap) { return gen.value(row, tap); });
@@ -470,6 +471,7 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
     c->K = p->K;
     c->pad = p->pad;
     build_cqt_bank_rows(c, rows);
+    c->hop_blocks = lowrank;
     if (lowrank && device >= 0) build_cqt_bank_lowrank(c, [&](int row, long long tap) { return rows[(size_t)row * p->K + tap]; });
   } catch (const std::bad_alloc&) {
     delete c;
@@ -749,6 +751,52 @@ nna_status nna_plan_bank(const nna_plan* plan, double* host_out, size_t cap) {
                 }
               }
           }
+  }
+  return NNA_OK;
+}
+
+// the plan of kind CQT whose kernels a fixed plan of either kind applies to the waveform; NULL: another kind, or trainable
+static const nna_plan* applied_plan(const nna_plan* plan) {
+  const nna_plan* sub = plan->kind == NNA_KIND_CQT1992 ? plan->composed : plan;
+  return sub && sub->kind == NNA_KIND_CQT && !plan->d_wrm && !sub->fir_taps ? sub : nullptr;
+}
+
+nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size_t cap) {
+  if (!plan || !host_out) return fail(NNA_ERR_INVALID_ARG, "plan / host_out is NULL");
+  const nna_plan* sub = applied_plan(plan);
+  if (!sub) return fail(NNA_ERR_INVALID_ARG, "not a plan with fixed constant-Q kernels at one rate");
+  if ((unsigned long long)cap < (unsigned long long)(sub->conv_rows * (long long)sub->K)) return fail(NNA_ERR_INVALID_ARG, "host_out is too small");
+  try {
+    nna_plan copy;
+    if (rebuild_lowrank(plan, sub, copy))
+      cqt_applied_rows(&copy, host_out);
+    else
+      return nna_plan_bank(sub, host_out, cap);
+  } catch (const std::bad_alloc&) {
+    return fail(NNA_ERR_ALLOC, "out of host memory");
+  }
+  return NNA_OK;
+}
+
+nna_status nna_plan_applied_tiles(const nna_plan* plan, long long B, long long L, int* frames, int* blocks) {
+  if (!plan || !frames || !blocks) return fail(NNA_ERR_INVALID_ARG, "plan / frames / blocks is NULL");
+  const nna_plan* sub = applied_plan(plan);
+  if (!sub) return fail(NNA_ERR_INVALID_ARG, "not a plan with fixed constant-Q kernels at one rate");
+  const long long T = B < 1 ? 0 : frames_of(sub, L);
+  if (T < 1) return fail(NNA_ERR_SHAPE, "no frames");
+  frames[0] = frames[1] = blocks[0] = blocks[1] = 0;
+  try {
+    nna_plan copy;
+    nna::CqlParams P;
+    std::memset(&P, 0, sizeof(P));
+    if (rebuild_lowrank(plan, sub, copy) && shape_lowrank(&copy, B * T, T, P))
+      for (int i = 0; i < 2; ++i) {
+        const nna::CqlPart& part = i ? P.direct : P.basis;
+        frames[i] = part.n_items ? part.tile_frames : 0;
+        blocks[i] = part.n_items ? part.fb : 0;
+      }
+  } catch (const std::bad_alloc&) {
+    return fail(NNA_ERR_ALLOC, "out of host memory");
   }
   return NNA_OK;
 }
