@@ -485,8 +485,9 @@ nna_status nna_plan_bank(const nna_plan* plan, double* host_out, size_t cap);
 /*
  * Plans from nna_plan_cqt and nna_plan_cqt1992 whose kernels are fixed, for inspection: host_out[2 n_bins, K], the kernels as the
  * calls apply them to the waveform -- the float32 numbers of the form that runs multiplied out in double.  Computed on the host.
+ * rows, if not NULL, gets 2 n_bins; a NULL host_out asks for that alone.
  */
-nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size_t cap);
+nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size_t cap, long long* rows);
 /*
  * ... and how a call on B waveforms of L samples cuts them up: frames per workgroup (frames[0], frames[1]) and 16-frame blocks per
  * wave (blocks[0], blocks[1]: 1, 2 or 4) of the bins taken as combinations of a basis (0) and tap by tap beside them (1); zero

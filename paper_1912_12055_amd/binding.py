@@ -112,7 +112,7 @@ def lib():
         for name in ("nna_stft", "nna_mel", "nna_cqt", "nna_cqt1992", "nna_cqt2010v2_static"):
             getattr(L, name).argtypes = [_VP, _VP, _LL, _LL, _VP, _VP]
         L.nna_plan_bank.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
-        L.nna_plan_applied_kernels.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
+        L.nna_plan_applied_kernels.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t, _c.POINTER(_LL)]
         L.nna_plan_applied_tiles.argtypes = [_VP, _LL, _LL, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int)]
         L.nna_plan_mel_weights.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
         L.nna_plan_info.argtypes = [_VP, _c.POINTER(_c.c_int), _c.POINTER(_LL), _c.POINTER(_LL), _c.POINTER(_LL),
@@ -260,9 +260,10 @@ def nna_plan_bank(plan: Plan) -> np.ndarray:
 
 def nna_plan_applied_kernels(plan: Plan) -> np.ndarray:
     """The kernels a fixed constant-Q plan applies, [2 n_bins, K], multiplied out in 64 bits."""
-    i = plan.info()
-    out = np.empty((2 * len(nna_plan_cqt_lengths(plan)), i["taps"]), dtype=np.float64)
-    _check(lib().nna_plan_applied_kernels(plan.handle, out.ctypes.data_as(_c.POINTER(_c.c_double)), out.size))
+    rows = _LL()
+    _check(lib().nna_plan_applied_kernels(plan.handle, None, 0, _c.byref(rows)))
+    out = np.empty((rows.value, plan.info()["taps"]), dtype=np.float64)
+    _check(lib().nna_plan_applied_kernels(plan.handle, out.ctypes.data_as(_c.POINTER(_c.c_double)), out.size, None))
     return out
 
 

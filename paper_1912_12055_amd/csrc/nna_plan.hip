@@ -761,10 +761,12 @@ static const nna_plan* applied_plan(const nna_plan* plan) {
   return sub && sub->kind == NNA_KIND_CQT && !plan->d_wrm && !sub->fir_taps ? sub : nullptr;
 }
 
-nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size_t cap) {
-  if (!plan || !host_out) return fail(NNA_ERR_INVALID_ARG, "plan / host_out is NULL");
+nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size_t cap, long long* rows) {
+  if (!plan || (!host_out && !rows)) return fail(NNA_ERR_INVALID_ARG, "plan / host_out is NULL");
   const nna_plan* sub = applied_plan(plan);
   if (!sub) return fail(NNA_ERR_INVALID_ARG, "not a plan with fixed constant-Q kernels at one rate");
+  if (rows) *rows = sub->conv_rows;
+  if (!host_out) return NNA_OK;
   if ((unsigned long long)cap < (unsigned long long)(sub->conv_rows * (long long)sub->K)) return fail(NNA_ERR_INVALID_ARG, "host_out is too small");
   try {
     nna_plan copy;
