@@ -16,9 +16,13 @@
 // samples: the taps of a frame are r J consecutive words of LDS, so r needs no padding to the sixteen taps of a step, only to 4
 // modulo 8, which keeps the rows of sixteen frames on different banks.
 //
+// Every sum is taken in blocks of 16 products (32 in stage 1), each from zero and then added to a total: a chain of a thousand
+// roundings was off by up to 9e-7 of a bin's norm, more than the folded kernel's half as many in the bins taken tap by tap; the
+// blocks are off by 3e-7 at most, and the additions hide behind the matrix instructions (within 3 % either way).
+//
 // Bound by the float32 matrix pipe (two thirds busy at the batch below); a short batch by latency, a workgroup or two per CU.
-// 1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms folded about the centres -> 8.3 ms; 16 x 220,500, 84 bins
-// of 12 per octave: 300 -> 65 us; the dense composed kernels of the frequency-domain layer (16 x 220,500, 32,768 taps): 566 -> 205 us.
+// 1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms folded about the centres -> 8.25 ms; 16 x 220,500, 84 bins
+// of 12 per octave: 300 -> 67 us; the dense composed kernels of the frequency-domain layer (16 x 220,500, 32,768 taps): 566 -> 182 us.
 #include <type_traits>
 
 #include "nna_device.h"
@@ -162,11 +166,13 @@ __device__ __forceinline__ void direct_item(const CqlParams& P, const CqlPart& p
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (i < a) {
+        f32x4 sum[FB] = {};
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-          for (int fb = 0; fb < FB; ++fb)
-            acc[fb][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][k], x[fb][k], acc[fb][i], 0, 0, 0);
+          for (int fb = 0; fb < FB; ++fb) sum[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][k], x[fb][k], sum[fb], 0, 0, 0);
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb) acc[fb][i] += sum[fb];
       }
   };
   // The weights are requested three steps ahead, across chunks; the frames are read from LDS one step ahead, within a chunk.
@@ -296,12 +302,16 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
           }
       }
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
+      for (int p = 0; p < NB; ++p) {
+        f32x4 sum[IB] = {};
 #pragma unroll
-        for (int p = 0; p < NB; ++p)
+        for (int e = 0; e < 8; ++e)
 #pragma unroll
           for (int i = 0; i < IB; ++i)
-            acc[p][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][e >> 2][e & 3], x[p][e >> 2][e & 3], acc[p][i], 0, 0, 0);
+            sum[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][e >> 2][e & 3], x[p][e >> 2][e & 3], sum[i], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < IB; ++i) acc[p][i] += sum[i];
+      }
     };
     if (c_begin >= c_end) return;
     // two register sets: the next 32 columns are requested ahead of this chunk's matrix instructions
@@ -430,13 +440,19 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       for (int fb = 0; fb < FB; ++fb) y[fb] = *reinterpret_cast<const f32x4*>(Y + y_off[fb] + 16 * i);
     };
     auto multiply = [&](const f32x4& c0, const f32x4& c1, const f32x4 (&y)[FB]) {
+      f32x4 sum[FB][2] = {};
 #pragma unroll
       for (int k = 0; k < 4; ++k)
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
-          acc[fb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(c0[k], y[fb][k], acc[fb][0], 0, 0, 0);
-          if constexpr (BOTH) acc[fb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(c1[k], y[fb][k], acc[fb][1], 0, 0, 0);
+          sum[fb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(c0[k], y[fb][k], sum[fb][0], 0, 0, 0);
+          if constexpr (BOTH) sum[fb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(c1[k], y[fb][k], sum[fb][1], 0, 0, 0);
         }
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb) {
+        acc[fb][0] += sum[fb][0];
+        if constexpr (BOTH) acc[fb][1] += sum[fb][1];
+      }
     };
     // four register sets of coefficients and frames, requested three steps ahead
     f32x4 c0[4], c1[4], y[4][FB];
