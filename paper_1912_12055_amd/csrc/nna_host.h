@@ -208,11 +208,13 @@ struct nna_plan {
   std::vector<nna::CqlItem> h_litems;
   std::vector<float> h_lu, h_la;
   std::vector<int> h_lsteps;
+  std::vector<int> h_lsupport;  // [n_bins][2] first tap, last tap + 1 of each kernel
   int* d_lsteps = nullptr;
   double lr_limit = 0;  // multiply-adds per frame of the other form, at the rate of this one
   float* d_lu = nullptr;
   float* d_la = nullptr;
   nna::CqlItem* d_litems = nullptr;
+  int2* d_lsupport = nullptr;
   bool runs_lowrank() const { return lowrank && !d_wrm; }
   // trainable CQT plans: index map caller's tensor -> streaming order, each row's tap support, and the
   // tables that let the backward contractions skip what lies outside every support

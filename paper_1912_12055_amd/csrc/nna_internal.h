@@ -295,6 +295,7 @@ struct CqlParams {
   const float4* u;
   const float4* a;
   const int* steps;
+  const int2* support;  // [bins]: first tap, last tap + 1
   float* out;
   long long out_wave_stride;
   CqlPart basis, direct;  // the items with a basis; those whose kernels stay as they are

@@ -98,6 +98,7 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
         if (s == NNA_OK) s = upload(&p->d_la, p->h_la.data(), p->h_la.size() * sizeof(float), "hop-block coefficients");
         if (s == NNA_OK) s = upload(&p->d_lsteps, p->h_lsteps.data(), p->h_lsteps.size() * sizeof(int), "step table");
         if (s == NNA_OK) s = upload(&p->d_litems, p->h_litems.data(), p->h_litems.size() * sizeof(nna::CqlItem), "hop-block item table");
+        if (s == NNA_OK) s = upload(&p->d_lsupport, p->h_lsupport.data(), p->h_lsupport.size() * sizeof(int), "kernel supports");
       }
     }
     if (s != NNA_OK) {
@@ -942,6 +943,7 @@ void nna_plan_destroy(nna_plan* plan) {
       (void)hipFree(plan->d_la);
       (void)hipFree(plan->d_litems);
       (void)hipFree(plan->d_lsteps);
+      (void)hipFree(plan->d_lsupport);
       (void)hipFree(plan->d_cq_map);
       (void)hipFree(plan->d_row_lo);
       (void)hipFree(plan->d_row_hi);

@@ -389,6 +389,7 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
   P.u = reinterpret_cast<const float4*>(sub->d_lu);
   P.a = reinterpret_cast<const float4*>(sub->d_la);
   P.steps = sub->d_lsteps;
+  P.support = sub->d_lsupport;
   P.out = out + (long long)row_offset * T;
   P.out_wave_stride = out_wave_stride;
   P.fmt = sub->fmt;
