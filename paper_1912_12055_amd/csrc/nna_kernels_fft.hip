@@ -230,6 +230,9 @@ __device__ __forceinline__ void mel_tile(const FftParams& P, const float* __rest
 // ---------------------------------------------------------------------------------------
 // N = 2 M a power of two, 64 .. 4,096: radices R1, R2 (, R3), V complex values per lane.
 // ---------------------------------------------------------------------------------------
+constexpr int kLdsTwo = 80 * 1024;   // two workgroups per CU
+constexpr int kLdsMax = 156 * 1024;  // one
+
 template <int M, int R1, int R2, int R3, int V, int NW, int MODE>
 struct FftTile {
   static constexpr int RL = R3 > 1 ? R3 : R2;           // radix of the last pass
@@ -240,7 +243,37 @@ struct FftTile {
   static constexpr int PLANE = M + 1;
   static constexpr int WORDS = MODE == FFT_MODE_CPLX ? 2 * M + 2 : (M + M / 16 > M + 4 ? M + M / 16 : M + 4);
   static constexpr int PITCH = WORDS | 1;
+  // steps of the largest tile: as many as two workgroups' LDS holds, at most 64 frames (the lanes of a store)
+  static constexpr int max_steps() {
+    int n = 1;
+    while (2 * n * FPWG <= 64 && 2 * n * FPWG * PITCH * 4 <= kLdsTwo) n *= 2;
+    return n;
+  }
+  static constexpr int LDS_BYTES = max_steps() * FPWG * PITCH * 4;
+  static_assert(FPWG <= 64 && LDS_BYTES <= kLdsTwo, "a tile is at most as wide as a wave");
 };
+
+// The sizes that have a kernel of their own, and its shape.
+template <int M_, int R1_, int R2_, int R3_, int V_, int NW_>
+struct Shape {
+  static constexpr int M = M_, R1 = R1_, R2 = R2_, R3 = R3_, V = V_, NW = NW_;
+  template <int MODE>
+  using Tile = FftTile<M, R1, R2, R3, V, NW, MODE>;
+};
+constexpr int kShapes[] = {32, 64, 128, 256, 512, 1024, 2048};
+template <typename Fn>
+bool with_shape(int M, Fn&& fn) {
+  switch (M) {
+    case 32: fn(Shape<32, 8, 4, 1, 8, 4>{}); return true;
+    case 64: fn(Shape<64, 8, 8, 1, 16, 4>{}); return true;
+    case 128: fn(Shape<128, 16, 8, 1, 16, 4>{}); return true;
+    case 256: fn(Shape<256, 8, 8, 4, 16, 4>{}); return true;
+    case 512: fn(Shape<512, 8, 8, 8, 16, 4>{}); return true;
+    case 1024: fn(Shape<1024, 16, 16, 4, 16, 4>{}); return true;
+    case 2048: fn(Shape<2048, 16, 16, 8, 16, 4>{}); return true;
+    default: return false;
+  }
+}
 
 __device__ __forceinline__ constexpr int padded(int i) { return i + (i >> 4); }  // LDS word of exchanged value i
 
@@ -554,9 +587,6 @@ __global__ __launch_bounds__(256, 2) void fft_general_kernel(FftParams P) {
   }
 }
 
-constexpr int kLdsTwo = 80 * 1024;   // two workgroups per CU
-constexpr int kLdsMax = 156 * 1024;  // one
-
 // Grid and tile of a launch: the steps per tile are halved until there are 512 tiles, two per CU, or one step is left; small
 // tiles spread a short batch over the chip, large ones write longer runs.
 void shape_launch(FftParams& P, int frames_per_step, int max_iters) {
@@ -568,33 +598,21 @@ void shape_launch(FftParams& P, int frames_per_step, int max_iters) {
   P.n_tiles = (P.g.n_frames + tf - 1) / tf;
 }
 
-template <int M, int R1, int R2, int R3, int V, int NW, int MODE>
+template <typename S, int MODE>
 hipError_t launch_fixed(FftParams& P, hipStream_t stream) {
-  using C = FftTile<M, R1, R2, R3, V, NW, MODE>;
-  // as many steps per tile as 70 KB of LDS hold, at most 64 frames (the lanes of a store)
-  int iters = 1;
-  while (2 * iters * C::FPWG <= 64 && 2 * iters * C::FPWG * C::PITCH * 4 <= kLdsTwo) iters *= 2;
-  static_assert(C::FPWG <= 64, "a tile is at most as wide as a wave");
-  shape_launch(P, C::FPWG, iters);
+  using C = typename S::template Tile<MODE>;
+  shape_launch(P, C::FPWG, C::max_steps());
   const size_t bytes = (size_t)(1 << P.lg_tf) * C::PITCH * 4;
   const long long grid = std::min<long long>(P.n_tiles, 512);
   clear_stale_error();
-  hipLaunchKernelGGL((fft_kernel<M, R1, R2, R3, V, NW, MODE>), dim3((unsigned)grid), dim3(64 * NW), bytes, stream, P);
+  hipLaunchKernelGGL((fft_kernel<S::M, S::R1, S::R2, S::R3, S::V, S::NW, MODE>), dim3((unsigned)grid), dim3(64 * S::NW), bytes, stream, P);
   return hipGetLastError();
 }
 
 template <int MODE>
 hipError_t launch_mode(FftParams& P, hipStream_t stream) {
-  switch (P.M) {
-    case 32: return launch_fixed<32, 8, 4, 1, 8, 4, MODE>(P, stream);
-    case 64: return launch_fixed<64, 8, 8, 1, 16, 4, MODE>(P, stream);
-    case 128: return launch_fixed<128, 16, 8, 1, 16, 4, MODE>(P, stream);
-    case 256: return launch_fixed<256, 8, 8, 4, 16, 4, MODE>(P, stream);
-    case 512: return launch_fixed<512, 8, 8, 8, 16, 4, MODE>(P, stream);
-    case 1024: return launch_fixed<1024, 16, 16, 4, 16, 4, MODE>(P, stream);
-    case 2048: return launch_fixed<2048, 16, 16, 8, 16, 4, MODE>(P, stream);
-    default: break;
-  }
+  hipError_t e = hipSuccess;
+  if (with_shape(P.M, [&](auto s) { e = launch_fixed<decltype(s), MODE>(P, stream); })) return e;
   const size_t row = (size_t)P.pitch * 4, work = (size_t)P.M * 16;
   int nw = 4, tf = 16;
   while (nw > 1 && nw * work + nw * row > (size_t)kLdsTwo) nw >>= 1;
@@ -606,30 +624,28 @@ hipError_t launch_mode(FftParams& P, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int M, int R1, int R2, int R3, int V, int NW, int MODE>
-hipError_t allow_lds() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(fft_kernel<M, R1, R2, R3, V, NW, MODE>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsTwo);
-}
-
+// every launch that may ask for more than 64 KB has leave to
 template <int MODE>
 hipError_t allow_lds_mode() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fft_general_kernel<MODE>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax);
-  if (e == hipSuccess) e = allow_lds<256, 8, 8, 4, 16, 4, MODE>();
-  if (e == hipSuccess) e = allow_lds<512, 8, 8, 8, 16, 4, MODE>();
-  if (e == hipSuccess) e = allow_lds<1024, 16, 16, 4, 16, 4, MODE>();
-  if (e == hipSuccess) e = allow_lds<2048, 16, 16, 8, 16, 4, MODE>();
+  for (const int M : kShapes)
+    with_shape(M, [&](auto s) {
+      using S = decltype(s);
+      if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(fft_kernel<S::M, S::R1, S::R2, S::R3, S::V, S::NW, MODE>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, S::template Tile<MODE>::LDS_BYTES);
+    });
   return e;
 }
 
 }  // namespace
 
-// The order in which the lanes of a frame take their twiddles in fft_kernel<M>: see tlane there.
-template <int M, int R1, int R2, int R3, int V, int NW>
+// The order in which the lanes of a frame take their twiddles in fft_kernel<M>: those of the last pass, then of the bins.
+template <typename S>
 void lane_twiddles(std::vector<int>& index) {
-  using C = FftTile<M, R1, R2, R3, V, NW, FFT_MODE_POWER>;
-  constexpr int RL = C::RL, H = C::H, TPF = C::TPF, NBL = C::NBL;
+  using C = typename S::template Tile<FFT_MODE_POWER>;
+  constexpr int V = S::V, RL = C::RL, H = C::H, TPF = C::TPF, NBL = C::NBL;
   static_assert(NBL * (RL - 1) % 2 == 0 && V % 4 == 0, "twiddles in pairs");
   index.resize((size_t)TPF * (NBL * (RL - 1) + V / 2));
   for (int lt = 0; lt < TPF; ++lt) {
@@ -648,16 +664,8 @@ void lane_twiddles(std::vector<int>& index) {
 }
 
 void fft_lane_twiddles(int M, std::vector<int>& index) {
-  switch (M) {
-    case 32: return lane_twiddles<32, 8, 4, 1, 8, 4>(index);
-    case 64: return lane_twiddles<64, 8, 8, 1, 16, 4>(index);
-    case 128: return lane_twiddles<128, 16, 8, 1, 16, 4>(index);
-    case 256: return lane_twiddles<256, 8, 8, 4, 16, 4>(index);
-    case 512: return lane_twiddles<512, 8, 8, 8, 16, 4>(index);
-    case 1024: return lane_twiddles<1024, 16, 16, 4, 16, 4>(index);
-    case 2048: return lane_twiddles<2048, 16, 16, 8, 16, 4>(index);
-    default: index.clear();
-  }
+  index.clear();
+  with_shape(M, [&](auto s) { lane_twiddles<decltype(s)>(index); });
 }
 
 bool fft_radices(int n_fft, int (&radix)[16], int& n_radix) {
