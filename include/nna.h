@@ -235,7 +235,7 @@ nna_status nna_out_shape(const nna_plan* plan, long long B, long long L, long lo
  * plan from nna_plan_stft, freq_bins for one from nna_plan_stft_scaled.
  * A plan from nna_plan_stft (float32, not made trainable) whose n_fft / 2 has no prime factor above 7, n_fft 64 to about
  * 13,000, takes eq. (DFT2)'s sums in stages -- a fast Fourier transform of every windowed frame, the same result to
- * rounding; any hop.  The other sizes are contractions with the kernel bank: with magnitude, power or log output and a hop that
+ * rounding; any hop.  (Below 256 samples only up to some 10,000 to 100,000 frames: a contraction then takes less time.)  The other sizes are contractions with the kernel bank: with magnitude, power or log output and a hop that
  * divides n_fft an even number of times >= 4 and is a multiple of 32, from the folded frame (the windows of Sec.
  * III-A satisfy w[n] = w[N-n], so eq. (DFT2)'s real kernels meet x[n] + x[N-n] and its imaginary kernels
  * x[n] - x[N-n] over n < N/2 only); where n_fft is also a multiple of 256 the folded taps are summed by parity, E over

@@ -108,7 +108,7 @@ void build_stft_bank_fold(nna_plan* p) {
     // below N/4, two fragments per group (Re, Im kernels of the tile's bins).
     p->fold_split = true;
     p->n_rt_split = N / 128;
-    if (p->fft) return;
+    if (p->fft_only()) return;
     p->bankf_floats = (size_t)(G * p->n_rt_split + ST_NKG) * 2 * 64 * 4;
     p->h_bankf.assign(p->bankf_floats, 0.0f);
     DftTable tab(N, p->window);
@@ -148,7 +148,7 @@ void build_stft_bank_fold(nna_plan* p) {
     p->n_rt_split = p->n_rt / 2;
     p->exec_flops_split = 2.0 * ((double)p->n_chunks * nj2 * ST_KC) * (double)(p->n_rt / 2) * ST_ROWS + 4.0 * N;
   }
-  if (p->fft) return;
+  if (p->fft_only()) return;
   p->bankf_floats = (size_t)(G * p->n_rt + ST_NKG) * ST_RB * 64 * 4;
   p->h_bankf.assign(p->bankf_floats, 0.0f);
   DftTable tab(N, p->window);
@@ -191,6 +191,12 @@ void build_fft_tables(nna_plan* p) {
   const int N = p->K;
   if (p->freq_scale || p->precision != 0 || !nna::fft_radices(N, p->fft_radix, p->fft_n_radix)) return;
   p->fft = true;
+  // Frames up to which the transform is the faster form, against the contraction (time over the contraction's, magnitudes, complex
+  // and Mel, hops N/4, N/2 and 32; MI355X).  N < 128: 0.5 .. 0.9 at 5,000 frames, 0.7 .. 1.3 at 10,000, 1.2 .. 2.2 at 20,000,
+  // 2.1 .. 3.4 at 320,000; N = 128: STFT 0.9 .. 1.2 at 10,000, 1.4 .. 1.8 at 20,000, 1.0 at 320,000, Mel 0.5 .. 1.3 throughout; 130 ..
+  // 198: 0.3 .. 0.8 at 10,000, 0.6 .. 1.4 at 20,000, 1.0 .. 1.9 at 320,000; 200 .. 254: 0.6 .. 1.0 at 80,000, 0.7 .. 1.2 at 160,000,
+  // 0.8 .. 1.5 at 320,000; from 256 on 0.1 .. 0.8 at any number, N = 64 0.5 .. 1.1.
+  p->fft_frames = N >= 256 || N == 64 || (N == 128 && p->kind == NNA_KIND_MEL) ? LLONG_MAX : N < 128 ? 8192 : N < 200 ? 16384 : 131072;
   p->h_fft_win.resize(N);
   p->h_fft_tw.resize(2 * (size_t)N);
   DftTable tab(N, p->window);

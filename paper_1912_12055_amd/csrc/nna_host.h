@@ -98,6 +98,10 @@ struct nna_plan {
   // Fast Fourier transform of each frame (nna_kernels_fft.hip): plain DFT bins with fixed float32 kernels, N/2 free of
   // prime factors above 7.  The direct bank stays (inspection, trainable plans).
   bool fft = false;
+  // ... up to this many frames a call: below 256 samples the contraction, which these plans keep beside it, overtakes it on large
+  // batches (the line: build_fft_tables)
+  long long fft_frames = 0;
+  bool fft_only() const { return fft && fft_frames == LLONG_MAX; }
   int fft_radix[16] = {}, fft_n_radix = 0;
   std::vector<float> h_fft_win;          // [N] half the window
   std::vector<float> h_fft_tw;           // [N][2] cos, sin of 2 pi k / N
@@ -124,7 +128,7 @@ struct nna_plan {
   float* d_melwf = nullptr;            // Mel weights as the folded kernel's second MFMA reads them
   unsigned char* d_mel_maskf = nullptr;
   bool folded_form() const { return fold && !d_wrm && precision == 0; }
-  bool runs_folded() const { return folded_form() && !fft; }
+  bool runs_folded() const { return folded_form() && !fft_only(); }
   // STFT plans whose n_fft is a multiple of 256 and whose hop is even: the folded contraction split once more by tap
   // parity (bins below N/4 only; their partners N/2 - k from the same sums).  h_wq / d_wq: the two weight tables of
   // bin N/4, [2][J rounded up to 4][hop]
@@ -136,7 +140,7 @@ struct nna_plan {
   std::vector<float> h_wq;
   float* d_wq = nullptr;
   bool split_form() const { return folded_form() && fold_split; }
-  bool runs_split() const { return split_form() && !fft; }
+  bool runs_split() const { return split_form() && !fft_only(); }
   // Mel plans that run split: the split kernel's own pass table, the filters' weights on bin N/4 (all zero: mel_q_any = 0)
   int* d_mel_pass_rtf = nullptr;
   int* d_mel_pass_rtf_spec = nullptr;  // the same with the first pass sweeping every tile (nna_mel_with_stft)
@@ -146,7 +150,7 @@ struct nna_plan {
 
   // Packed bank: host-only plans keep the host copy, device plans drop it after upload.  A plan that does not run its bank (fast
   // Fourier transform, composed kernels) holds neither: nna_plan_bank computes the values, nna_plan_trainable uploads them.
-  bool bank_idle() const { return fft || kind == NNA_KIND_CQT1992; }
+  bool bank_idle() const { return fft_only() || kind == NNA_KIND_CQT1992; }
   std::vector<float> h_bank;
   size_t bank_floats = 0;
 

@@ -55,7 +55,7 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
         if (s == NNA_OK) s = upload(&p->d_fft_melw, p->h_fft_melw.data(), p->h_fft_melw.size() * sizeof(float), "mel filter weights");
       }
     }
-    if (s == NNA_OK && p->fold && !p->fft) {
+    if (s == NNA_OK && p->fold && !p->fft_only()) {
       s = upload(&p->d_bankf, p->h_bankf.data(), p->bankf_floats * sizeof(float), "folded kernel bank");
       if (s == NNA_OK) s = upload(&p->d_wn, p->h_wn.data(), p->h_wn.size() * sizeof(float), "alternating window");
       if (s == NNA_OK && p->fold_split) s = upload(&p->d_wq, p->h_wq.data(), p->h_wq.size() * sizeof(float), "weights of bin N/4");

@@ -125,7 +125,7 @@ nna_status run_stft_core(const nna_plan* plan, int kind, const float* x, long lo
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return NNA_OK;
   }
-  if (plan->runs_fft() && (kind == NNA_KIND_STFT || kind == NNA_KIND_MEL)) {
+  if (plan->runs_fft() && B * T <= plan->fft_frames && (kind == NNA_KIND_STFT || kind == NNA_KIND_MEL)) {
     nna::FftParams P;
     std::memset(&P, 0, sizeof(P));
     P.g = make_geom(plan, x, B, L, T);
