@@ -76,6 +76,9 @@ class _StftFn(torch.autograd.Function):
         return gx, gw, None
 
 
+_SPECTROGRAM_FLOATS = 1 << 28  # 1 GiB: what a trainable Mel layer's forward pass holds besides its output
+
+
 class _MelFn(torch.autograd.Function):
     """nna_mel with nna_mel_backward as its derivative (filterbank, kernels and waveform)."""
 
@@ -83,7 +86,14 @@ class _MelFn(torch.autograd.Function):
     def forward(ctx, x, W, Wmel, layer):
         ctx.layer = layer
         ctx.save_for_backward(x)
-        return nb.nna_mel_with_stft(layer.plan, x)[0]  # dense filters: through the spectrogram
+        # the filters are dense: through the spectrogram, of a slice of the batch at a time
+        B, (bins, frames), F = x.shape[0], nb.nna_out_shape(layer.plan, *x.shape), layer.wsin_wcos.shape[0] // 2
+        step = max(1, _SPECTROGRAM_FLOATS // (F * frames))
+        out, spec = x.new_empty((B, bins, frames)), x.new_empty((min(step, B), F, frames))
+        for b in range(0, max(B, 1), step):
+            n = min(step, B - b)
+            nb.nna_mel_with_stft(layer.plan, x[b:b + n], out=out[b:b + n], spec=spec[:n])
+        return out
 
     @staticmethod
     def backward(ctx, gout):

@@ -32,3 +32,20 @@ def test_batches_of_short_waveforms(B, L, n_mels):
     one = x[B - 1:].clone().requires_grad_(True)
     g1, = torch.autograd.grad(layer(one), one, g[B - 1:])
     assert (gx[B - 1:] - g1).abs().max() <= 1e-5 * g1.abs().max()  # (the adds of the waveform gradient have no fixed order)
+
+
+def test_forward_holds_a_bounded_spectrogram():
+    import torch
+    from paper_1912_12055_amd import layers
+    print("[case] mel product memory", file=sys.stderr, flush=True)
+    layer = layers.MelSpectrogram(sr=22050, n_fft=2048, hop_length=512, n_mels=40, trainable_mel=True)
+    x = torch.randn((14000, 22050), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")  # 2.5 GB of spectrogram
+    with torch.no_grad():
+        layer(x[:4])
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        out = layer(x)
+        assert torch.cuda.max_memory_allocated() - before < (1 << 30) + out.numel() * 4 + (64 << 20)
+        for b in (0, 5937, 5938, 13999):
+            assert torch.equal(out[b], layer(x[b])[0])
