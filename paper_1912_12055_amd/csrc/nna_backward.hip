@@ -231,6 +231,22 @@ static nna_status make_spectral_trainable(nna_plan* plan) {
   return s;
 }
 
+// What only calls with fixed kernels run by: a trainable plan gives it back.
+static void release_fixed_forms(nna_plan* plan) {
+  (void)hipFree(plan->d_lu);
+  (void)hipFree(plan->d_la);
+  (void)hipFree(plan->d_lsteps);
+  (void)hipFree(plan->d_litems);
+  (void)hipFree(plan->d_lsupport);
+  plan->d_lu = plan->d_la = nullptr;
+  plan->d_lsteps = nullptr;
+  plan->d_litems = nullptr;
+  plan->d_lsupport = nullptr;
+  plan->lowrank = false;
+  nna_plan_destroy(plan->composed);
+  plan->composed = nullptr;
+}
+
 nna_status nna_plan_trainable(nna_plan* plan) {
   nna_status s = check_trainable_kind(plan);
   if (s != NNA_OK) return s;
@@ -238,7 +254,10 @@ nna_status nna_plan_trainable(nna_plan* plan) {
   DeviceGuard guard;
   hipError_t e = guard.enter(plan->device);
   if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
-  if (plan->kind == NNA_KIND_CQT) return make_cqt_trainable(plan);
+  if (plan->kind == NNA_KIND_CQT) {
+    if ((s = make_cqt_trainable(plan)) == NNA_OK) release_fixed_forms(plan);
+    return s;
+  }
   if (plan->kind == NNA_KIND_CQT2010V2) {
     // every octave convolves with (rows of) the one weight: each keeps its own streaming-order copy
     for (nna_plan* sub : plan->octave)
@@ -314,6 +333,7 @@ nna_status nna_plan_trainable(nna_plan* plan) {
     plan->d_wrm = nullptr;
     return s;
   }
+  release_fixed_forms(plan);
   return NNA_OK;
 }
 

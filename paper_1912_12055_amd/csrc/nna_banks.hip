@@ -4,6 +4,9 @@
 // time-domain constant-Q kernels of eqs. (Q), (N_k), (CQT), and the decimation filter of "Downsampling".
 #include "nna_host.h"
 
+#include <atomic>
+#include <thread>
+
 namespace nna {
 namespace host {
 
@@ -826,25 +829,230 @@ void principal_axes(std::vector<double>& G, int n, std::vector<double>& V, std::
   for (int i = 0; i < n; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return G[(size_t)a * n + a] > G[(size_t)b * n + b]; });
 }
+
+struct LowrankGroup {
+  bool basis = false;        // the kernels of its bins are combinations of a basis
+  nna::CqlItem item{};
+  std::vector<float> lu, la;  // (item.u0, item.a0 count from their beginning)
+  double limit = 0;          // its share of lr_limit
+};
+constexpr int kGroup = 16;
+
+// taps of row block b of the nb bins from k0 on
+void block_taps(const nna_plan* p, int k0, int nb, int b, long long& lo, long long& hi) {
+  lo = p->K;
+  hi = 0;
+  for (int k = k0 + 8 * b; k < std::min(k0 + nb, k0 + 8 * b + 8); ++k) {
+    lo = std::min(lo, p->row_s[2 * k]);
+    hi = std::max(hi, p->row_e[2 * k]);
+  }
+}
+
+LowrankGroup lowrank_group(const nna_plan* p, int k0, const CqtKernelSource& kernels) {
+  LowrankGroup g;
+  const long long K = p->K;
+  const int hop = p->hop, nb = std::min(kGroup, p->n_bins - k0);
+  // hop-blocks of the two row blocks
+  int jl[2] = {INT_MAX, INT_MAX}, jh[2] = {0, 0};
+  double direct = 0;  // multiply-adds per frame of the form that would run otherwise
+  for (int k = k0; k < k0 + nb; ++k) {
+    const int b = (k - k0) / 8;
+    jl[b] = std::min(jl[b], (int)(p->row_s[2 * k] / hop));
+    jh[b] = std::max(jh[b], (int)ceil_div(p->row_e[2 * k], hop));
+    direct += 2.0 * (double)(p->row_e[2 * k] - p->row_s[2 * k]);
+  }
+  if (nb <= 8) jl[1] = jh[1] = jl[0];
+  double as_is_cost = 0;
+  for (int b = 0; b < 2; ++b) {
+    long long lo, hi;
+    block_taps(p, k0, nb, b, lo, hi);
+    if (lo < hi) as_is_cost += 16.0 * (double)(hi - lo + 16);
+  }
+  if (jh[0] - jl[0] < 3) return g;  // a basis of `hop` columns for one or two hop-blocks saves nothing
+  const int j0 = std::min(jl[0], jl[1]), J = std::max(jh[0], jh[1]) - j0;
+  const int m = 2 * nb * J;
+  std::vector<double> R((size_t)m * hop), n2(m), norm2(nb, 0.0);
+  for (int k = 0; k < nb; ++k)
+    for (int j = 0; j < J; ++j) {
+      double* re = &R[((size_t)(2 * k) * J + j) * hop];
+      double* im = re + (size_t)J * hop;
+      const long long t0 = (long long)(j0 + j) * hop;
+      if (t0 + hop <= p->row_s[2 * (k0 + k)] || t0 >= p->row_e[2 * (k0 + k)]) continue;
+      kernels.taps(k0 + k, t0, hop, re, im);
+      norm2[k] += dot(re, re, hop) + dot(im, im, hop);
+    }
+  for (int k = 0; k < nb; ++k) {
+    if (!(norm2[k] > 0)) norm2[k] = 1.0;
+    const double f = 1.0 / std::sqrt(norm2[k]);
+    for (size_t i = (size_t)2 * k * J * hop; i < (size_t)2 * (k + 1) * J * hop; ++i) R[i] *= f;
+  }
+  // multiply-adds per frame, a quarter more hop-blocks than frames in the first stage
+  auto cost_of = [&](int r) { return 1.25 * 16.0 * ((r + 15) / 16) * hop + 256.0 * ((double)J * r / 16 + (nb > 8 ? (double)(jh[1] - jl[1]) * r / 16 : 0)); };
+  // Gram-Schmidt; C[m][.] collects the coordinates.  A row of which next to nothing is left is done with, a group that will not pay
+  // (the axes that are dropped in the end are fewer than sixteen) given up.
+  const int cap = std::min(hop, 16 * CQL_MAX_BASIS);
+  const double done = 0.01 * kTapRounding * kTapRounding / (2 * J);
+  std::vector<double> U, C((size_t)m * cap, 0.0);
+  int r0 = 0;
+  std::vector<double> left(nb);  // of every kernel's squared norm
+  for (int i = 0; i < m; ++i) n2[i] = dot(&R[(size_t)i * hop], &R[(size_t)i * hop], hop);
+  for (;;) {
+    std::fill(left.begin(), left.end(), 0.0);
+    for (int i = 0; i < m; ++i) left[i / (2 * J)] += n2[i];
+    if (std::sqrt(*std::max_element(left.begin(), left.end())) <= 0.25 * kTapRounding) break;
+    if (r0 == cap || cost_of(r0 - 16) > as_is_cost) return g;
+    const size_t best = std::max_element(n2.begin(), n2.end()) - n2.begin();
+    std::vector<double> u(&R[best * hop], &R[best * hop] + hop);
+    for (int pass = 0; pass < 2; ++pass) {
+      for (int i = 0; i < r0; ++i) {
+        const double* v = &U[(size_t)i * hop];
+        const double d = dot(u.data(), v, hop);
+        for (int c = 0; c < hop; ++c) u[c] -= d * v[c];
+      }
+      const double s = 1.0 / std::sqrt(dot(u.data(), u.data(), hop));
+      for (int c = 0; c < hop; ++c) u[c] *= s;
+    }
+    U.insert(U.end(), u.begin(), u.end());
+    for (int i = 0; i < m; ++i) {
+      if (n2[i] <= done) continue;
+      double* row = &R[(size_t)i * hop];
+      const double d = dot(row, u.data(), hop);
+      for (int c = 0; c < hop; ++c) row[c] -= d * u[c];
+      C[(size_t)i * cap + r0] = d;
+      n2[i] = dot(row, row, hop);
+    }
+    ++r0;
+  }
+  // principal axes of the coordinates
+  std::vector<double> Gm((size_t)r0 * r0, 0.0), V;
+  std::vector<int> order;
+  for (int i = 0; i < m; ++i) {
+    const double* c = &C[(size_t)i * cap];
+    for (int a = 0; a < r0; ++a) {
+      if (c[a] == 0.0) continue;
+      for (int b = 0; b <= a; ++b) Gm[(size_t)a * r0 + b] += c[a] * c[b];
+    }
+  }
+  for (int a = 0; a < r0; ++a)
+    for (int b = 0; b < a; ++b) Gm[(size_t)b * r0 + a] = Gm[(size_t)a * r0 + b];
+  principal_axes(Gm, r0, V, order);
+  std::vector<double> D((size_t)m * r0), W((size_t)r0 * hop, 0.0), Vt((size_t)r0 * r0);  // coordinates on the axes, the axes
+  for (int a = 0; a < r0; ++a) {
+    const int ax = order[a];
+    for (int b = 0; b < r0; ++b) {
+      const double v = V[(size_t)b * r0 + ax];
+      for (int c = 0; c < hop; ++c) W[(size_t)a * hop + c] += v * U[(size_t)b * hop + c];
+      Vt[(size_t)a * r0 + b] = v;
+    }
+  }
+  for (int i = 0; i < m; ++i)
+    for (int a = 0; a < r0; ++a) D[(size_t)i * r0 + a] = dot(&C[(size_t)i * cap], &Vt[(size_t)a * r0], r0);
+  // before[k][a]: what the axes ahead of axis a hold of kernel k (a fraction of its squared norm)
+  std::vector<double> before((size_t)nb * (r0 + 1), 0.0);
+  for (int k = 0; k < nb; ++k)
+    for (int a = 0; a < r0; ++a) {
+      double s = 0;
+      for (int i = k * 2 * J; i < (k + 1) * 2 * J; ++i) s += D[(size_t)i * r0 + a] * D[(size_t)i * r0 + a];
+      before[(size_t)k * (r0 + 1) + a + 1] = before[(size_t)k * (r0 + 1) + a] + s;
+    }
+  // The smallest basis whose product with the coefficients is as close to every kernel as its float32 taps are.  Of r functions
+  // `keep` are axes; the others repeat the first ones, for what their float32 coefficients leave.  What float32 leaves of the
+  // functions themselves is in the first stage's spare rows, for the first n_lo of them: these hold nearly all of a kernel.
+  nna::CqlItem& item = g.item;
+  int keep = 0, twice = 0;
+  for (int r = 4; r <= 16 * CQL_MAX_BASIS && !item.r; r += 8) {  // 4 modulo 8: the rows of 16 frames then lie on different LDS banks
+    const int n_lo = r % 16 == 4 && r > 4 ? 8 : 4;
+    double least = kTapRounding * kTapRounding;
+    for (int kp = r / 2; kp <= std::min(r, r0); ++kp) {
+      double worst = 0;
+      for (int k = 0; k < nb; ++k) {
+        const double* h = &before[(size_t)k * (r0 + 1)];
+        const double rounded = 2.0 * h[kp] - h[std::min(kp, n_lo)] - h[std::min(kp, r - kp)];
+        worst = std::max(worst, left[k] + h[r0] - h[kp] + kTapRounding * kTapRounding * rounded);
+      }
+      if (worst <= least) {
+        least = worst;
+        item.r = r;
+        item.n_lo = n_lo;
+        keep = kp;
+        twice = std::min(kp, r - kp);
+      }
+    }
+  }
+  if (!item.r) return g;
+  auto axis = [&](int i) { return i < keep ? i : i < keep + twice ? i - keep : -1; };  // of function i
+  item.n_ib = (item.r + item.n_lo + 15) / 16;
+  item.j0 = j0;
+  item.jspan = J;
+  item.n_step = (int)ceil_div((long long)J * item.r, 16);
+  item.s_lo = (int)((long long)(jl[1] - j0) * item.r / 16);
+  item.s_hi = nb > 8 ? (int)ceil_div((long long)(jh[1] - j0) * item.r, 16) : item.s_lo;
+  item.bin0 = k0;
+  item.n_bins = nb;
+  if (item.n_ib > CQL_MAX_BASIS || cost_of(item.r) > as_is_cost) return g;
+  g.basis = true;
+  // ... of the kernel that runs otherwise: 0.55 of the taps where they fold (dense kernels do not)
+  g.limit = (p->row_e[2 * k0] - p->row_s[2 * k0] == K ? 1.0 : 0.55) * direct;
+  // basis fragments [chunk][block][half][lane]: lane (q, i) holds row i of the block, columns 32 chunk + 16 half + 4 q + e.  The
+  // last n_lo rows of block 0 are what float32 leaves of its first n_lo.
+  item.u0 = (long long)g.lu.size() / 4;
+  for (int c = 0; c < hop; c += 32)
+    for (int ib = 0; ib < item.n_ib; ++ib)
+      for (int half = 0; half < 2; ++half)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int e = 0; e < 4; ++e) {
+            const int row = lane & 15, col = c + 16 * half + 4 * (lane >> 4) + e;
+            const bool lo = ib == 0 && row >= 16 - item.n_lo;
+            const int i = ib ? 16 * ib - item.n_lo + row : lo ? row - (16 - item.n_lo) : row, a = i < item.r ? axis(i) : -1;
+            const double u = a < 0 ? 0.0 : W[(size_t)a * hop + col];
+            g.lu.push_back(lo ? (float)(u - (double)(float)u) : (float)u);
+          }
+  // coefficient fragments [step][lane]: lane (q, row) holds A[row][16 step + 4 q + e], the coordinates of the row's
+  // hop-blocks one after the other
+  for (int b = 0; b < 2; ++b) {
+    item.a0[b] = (long long)g.la.size() / 4;
+    for (int s = b ? item.s_lo : 0; s < (b ? item.s_hi : item.n_step); ++s)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int e = 0; e < 4; ++e) {
+          const int row = 16 * b + (lane & 15), f = 16 * s + 4 * (lane >> 4) + e, j = f / item.r, i = f - j * item.r;
+          const int a = row < 2 * nb && j < J ? axis(i) : -1;
+          const double v = a < 0 ? 0.0 : D[((size_t)row * J + j) * r0 + a] * std::sqrt(norm2[row / 2]);
+          g.la.push_back(i < keep ? (float)v : (float)(v - (double)(float)v));
+        }
+  }
+  return g;
+}
+
+// fn(0 .. n - 1), each on whichever of a few host threads is free; throws what fn throws (bad_alloc)
+template <typename Fn>
+void for_each_parallel(int n, Fn fn) {
+  std::atomic<int> next{0};
+  std::atomic<bool> failed{false};
+  auto work = [&] {
+    try {
+      for (int i; !failed && (i = next++) < n;) fn(i);
+    } catch (const std::bad_alloc&) {
+      failed = true;
+    }
+  };
+  std::vector<std::thread> threads;
+  const int more = std::min({n, 8, (int)std::thread::hardware_concurrency()}) - 1;
+  try {
+    for (int i = 0; i < more; ++i) threads.emplace_back(work);
+  } catch (const std::exception&) {  // no more threads to be had: those that are there do
+  }
+  work();
+  for (std::thread& t : threads) t.join();
+  if (failed) throw std::bad_alloc();
+}
 }  // namespace
 
-void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long long)>& value) {
+void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels) {
   p->lowrank = false;
   const long long K = p->K;
   const int hop = p->hop;
   // whole 32-column chunks, frames and kernels on one grid of hops, and a plan that is built in a second
   if (hop % 32 != 0 || hop > 4096 || K % hop != 0 || K / hop < 4 || K > CQL_MAX_TAPS) return;
-  constexpr int G = 16;
-  bool any = false;
-  // row block b of the bins from k0 on: its taps
-  auto taps_of = [&](int k0, int nb, int b, long long& lo, long long& hi) {
-    lo = K;
-    hi = 0;
-    for (int k = k0 + 8 * b; k < std::min(k0 + nb, k0 + 8 * b + 8); ++k) {
-      lo = std::min(lo, p->row_s[2 * k]);
-      hi = std::max(hi, p->row_e[2 * k]);
-    }
-  };
   // the kernels as they stand: up to 32 bins, per 32 columns of the hop the steps of 16 taps that hold taps
   auto add_direct = [&](int k0, int nb) {
     nna::CqlItem item{};
@@ -852,7 +1060,7 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
     item.n_bins = nb;
     const int n_rb = (nb + 7) / 8;
     long long lo[4], hi[4];
-    for (int b = 0; b < n_rb; ++b) taps_of(k0, nb, b, lo[b], hi[b]);
+    for (int b = 0; b < n_rb; ++b) block_taps(p, k0, nb, b, lo[b], hi[b]);
     for (int b = n_rb - 1; b > 0; --b) {  // (longer kernels come first, so a block's taps lie among those of the one before)
       lo[b - 1] = std::min(lo[b - 1], lo[b]);
       hi[b - 1] = std::max(hi[b - 1], hi[b]);
@@ -878,7 +1086,7 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
                 const int row = 16 * b + (lane & 15), k = k0 + row / 2;
                 const long long tap = t0 + 4 * (lane >> 4) + e;
                 const bool there = b < a && row < 2 * nb && tap >= p->row_s[2 * k] && tap < p->row_e[2 * k];
-                p->h_lu.push_back(there ? (float)value(2 * k0 + row, tap) : 0.0f);
+                p->h_lu.push_back(there ? (float)kernels.value(2 * k0 + row, tap) : 0.0f);
               }
         }
       while (steps.size() % 4) {  // empty steps: the kernel goes through them by fours
@@ -893,204 +1101,35 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
     p->h_litems.push_back(item);
   };
   std::vector<int> as_is;  // first bins of the groups whose kernels stay
-  for (int k0 = 0; k0 < p->n_bins; k0 += G) {
-    const int nb = std::min(G, p->n_bins - k0);
-    // hop-blocks of the two row blocks
-    int jl[2] = {INT_MAX, INT_MAX}, jh[2] = {0, 0};
-    double direct = 0;  // multiply-adds per frame of the form that would run otherwise
-    for (int k = k0; k < k0 + nb; ++k) {
-      const int b = (k - k0) / 8;
-      jl[b] = std::min(jl[b], (int)(p->row_s[2 * k] / hop));
-      jh[b] = std::max(jh[b], (int)ceil_div(p->row_e[2 * k], hop));
-      direct += 2.0 * (double)(p->row_e[2 * k] - p->row_s[2 * k]);
-    }
-    if (nb <= 8) jl[1] = jh[1] = jl[0];
-    double as_is_cost = 0;
-    for (int b = 0; b < 2; ++b) {
-      long long lo, hi;
-      taps_of(k0, nb, b, lo, hi);
-      if (lo < hi) as_is_cost += 16.0 * (double)(hi - lo + 16);
-    }
-    if (jh[0] - jl[0] < 3) {  // a basis of `hop` columns for one or two hop-blocks saves nothing
-      as_is.push_back(k0);
+  // the groups know nothing of each other (44.1 kHz, 168 bins of 24 per octave: 155 -> 39 ms)
+  std::vector<LowrankGroup> groups((p->n_bins + kGroup - 1) / kGroup);
+  for_each_parallel((int)groups.size(), [&](int i) { groups[i] = lowrank_group(p, i * kGroup, kernels); });
+  double cost = 0;  // of a waveform of many frames
+  for (size_t i = 0; i < groups.size(); ++i) {
+    LowrankGroup& g = groups[i];
+    if (!g.basis) {
+      as_is.push_back((int)i * kGroup);
       continue;
     }
-    const int j0 = std::min(jl[0], jl[1]), J = std::max(jh[0], jh[1]) - j0;
-    const int m = 2 * nb * J;
-    std::vector<double> R((size_t)m * hop), n2(m), norm2(nb, 0.0);
-    for (int k = 0; k < nb; ++k)
-      for (int ri = 0; ri < 2; ++ri)
-        for (int j = 0; j < J; ++j) {
-          double* row = &R[((size_t)(2 * k + ri) * J + j) * hop];
-          const long long t0 = (long long)(j0 + j) * hop;
-          if (t0 + hop <= p->row_s[2 * (k0 + k)] || t0 >= p->row_e[2 * (k0 + k)]) continue;
-          double s = 0;
-          for (int c = 0; c < hop; ++c) {
-            row[c] = value(2 * (k0 + k) + ri, t0 + c);
-            s += row[c] * row[c];
-          }
-          norm2[k] += s;
-        }
-    for (int k = 0; k < nb; ++k) {
-      if (!(norm2[k] > 0)) norm2[k] = 1.0;
-      const double f = 1.0 / std::sqrt(norm2[k]);
-      for (size_t i = (size_t)2 * k * J * hop; i < (size_t)2 * (k + 1) * J * hop; ++i) R[i] *= f;
-    }
-    // Gram-Schmidt; C[m][.] collects the coordinates
-    const int cap = std::min(hop, 16 * CQL_MAX_BASIS);
-    std::vector<double> U, C((size_t)m * cap, 0.0);
-    int r0 = 0;
-    bool fits = false;
-    std::vector<double> left(nb);  // of every kernel's squared norm
-    for (;;) {
-      int best = 0;
-      std::fill(left.begin(), left.end(), 0.0);
-      for (int i = 0; i < m; ++i) {
-        const double* row = &R[(size_t)i * hop];
-        const double s = dot(row, row, hop);
-        n2[i] = s;
-        left[i / (2 * J)] += s;
-        if (s > n2[best]) best = i;
-      }
-      if (std::sqrt(*std::max_element(left.begin(), left.end())) <= 0.25 * kTapRounding) {
-        fits = true;
-        break;
-      }
-      if (r0 == cap) break;
-      std::vector<double> u(&R[(size_t)best * hop], &R[(size_t)best * hop] + hop);
-      for (int pass = 0; pass < 2; ++pass) {
-        for (int i = 0; i < r0; ++i) {
-          const double* v = &U[(size_t)i * hop];
-          const double d = dot(u.data(), v, hop);
-          for (int c = 0; c < hop; ++c) u[c] -= d * v[c];
-        }
-        const double s = 1.0 / std::sqrt(dot(u.data(), u.data(), hop));
-        for (int c = 0; c < hop; ++c) u[c] *= s;
-      }
-      U.insert(U.end(), u.begin(), u.end());
-      for (int i = 0; i < m; ++i) {
-        double* row = &R[(size_t)i * hop];
-        const double d = dot(row, u.data(), hop);
-        for (int c = 0; c < hop; ++c) row[c] -= d * u[c];
-        C[(size_t)i * cap + r0] += d;
-      }
-      ++r0;
-    }
-    if (!fits) {
-      as_is.push_back(k0);
-      continue;
-    }
-    // principal axes of the coordinates
-    std::vector<double> Gm((size_t)r0 * r0, 0.0), V;
-    std::vector<int> order;
-    for (int i = 0; i < m; ++i) {
-      const double* c = &C[(size_t)i * cap];
-      for (int a = 0; a < r0; ++a) {
-        if (c[a] == 0.0) continue;
-        for (int b = 0; b <= a; ++b) Gm[(size_t)a * r0 + b] += c[a] * c[b];
-      }
-    }
-    for (int a = 0; a < r0; ++a)
-      for (int b = 0; b < a; ++b) Gm[(size_t)b * r0 + a] = Gm[(size_t)a * r0 + b];
-    principal_axes(Gm, r0, V, order);
-    std::vector<double> D((size_t)m * r0), W((size_t)r0 * hop, 0.0), Vt((size_t)r0 * r0);  // coordinates on the axes, the axes
-    for (int a = 0; a < r0; ++a) {
-      const int ax = order[a];
-      for (int b = 0; b < r0; ++b) {
-        const double v = V[(size_t)b * r0 + ax];
-        for (int c = 0; c < hop; ++c) W[(size_t)a * hop + c] += v * U[(size_t)b * hop + c];
-        Vt[(size_t)a * r0 + b] = v;
-      }
-    }
-    for (int i = 0; i < m; ++i)
-      for (int a = 0; a < r0; ++a) D[(size_t)i * r0 + a] = dot(&C[(size_t)i * cap], &Vt[(size_t)a * r0], r0);
-    // before[k][a]: what the axes ahead of axis a hold of kernel k (a fraction of its squared norm)
-    std::vector<double> before((size_t)nb * (r0 + 1), 0.0);
-    for (int k = 0; k < nb; ++k)
-      for (int a = 0; a < r0; ++a) {
-        double s = 0;
-        for (int i = k * 2 * J; i < (k + 1) * 2 * J; ++i) s += D[(size_t)i * r0 + a] * D[(size_t)i * r0 + a];
-        before[(size_t)k * (r0 + 1) + a + 1] = before[(size_t)k * (r0 + 1) + a] + s;
-      }
-    // The smallest basis whose product with the coefficients is as close to every kernel as its float32 taps are.  Of r functions
-    // `keep` are axes; the others repeat the first ones, for what their float32 coefficients leave.  What float32 leaves of the
-    // functions themselves is in the first stage's spare rows, for the first n_lo of them: these hold nearly all of a kernel.
-    nna::CqlItem item{};
-    int keep = 0, twice = 0;
-    for (int r = 4; r <= 16 * CQL_MAX_BASIS && !item.r; r += 8) {  // 4 modulo 8: the rows of 16 frames then lie on different LDS banks
-      const int n_lo = r % 16 == 4 && r > 4 ? 8 : 4;
-      double least = kTapRounding * kTapRounding;
-      for (int kp = r / 2; kp <= std::min(r, r0); ++kp) {
-        double worst = 0;
-        for (int k = 0; k < nb; ++k) {
-          const double* h = &before[(size_t)k * (r0 + 1)];
-          const double rounded = 2.0 * h[kp] - h[std::min(kp, n_lo)] - h[std::min(kp, r - kp)];
-          worst = std::max(worst, left[k] + h[r0] - h[kp] + kTapRounding * kTapRounding * rounded);
-        }
-        if (worst <= least) {
-          least = worst;
-          item.r = r;
-          item.n_lo = n_lo;
-          keep = kp;
-          twice = std::min(kp, r - kp);
-        }
-      }
-    }
-    if (!item.r) {
-      as_is.push_back(k0);
-      continue;
-    }
-    auto axis = [&](int i) { return i < keep ? i : i < keep + twice ? i - keep : -1; };  // of function i
-    item.n_ib = (item.r + item.n_lo + 15) / 16;
-    item.j0 = j0;
-    item.jspan = J;
-    item.n_step = (int)ceil_div((long long)J * item.r, 16);
-    item.s_lo = (int)((long long)(jl[1] - j0) * item.r / 16);
-    item.s_hi = nb > 8 ? (int)ceil_div((long long)(jh[1] - j0) * item.r, 16) : item.s_lo;
-    item.bin0 = k0;
-    item.n_bins = nb;
-    // multiply-adds per frame, a quarter more hop-blocks than frames in the first stage, against those of the kernels as they stand
-    const double cost = 1.25 * 16.0 * item.n_ib * hop + 256.0 * (item.n_step + item.s_hi - item.s_lo);
-    if (item.n_ib > CQL_MAX_BASIS || cost > as_is_cost) {
-      as_is.push_back(k0);
-      continue;
-    }
-    any = true;
-    // ... of the kernel that runs otherwise: 0.55 of the taps where they fold (dense kernels do not)
-    p->lr_limit += (p->row_e[2 * k0] - p->row_s[2 * k0] == K ? 1.0 : 0.55) * direct;
-    // basis fragments [chunk][block][half][lane]: lane (q, i) holds row i of the block, columns 32 chunk + 16 half + 4 q + e.  The
-    // last n_lo rows of block 0 are what float32 leaves of its first n_lo.
-    item.u0 = (long long)p->h_lu.size() / 4;
-    for (int c = 0; c < hop; c += 32)
-      for (int ib = 0; ib < item.n_ib; ++ib)
-        for (int half = 0; half < 2; ++half)
-          for (int lane = 0; lane < 64; ++lane)
-            for (int e = 0; e < 4; ++e) {
-              const int row = lane & 15, col = c + 16 * half + 4 * (lane >> 4) + e;
-              const bool lo = ib == 0 && row >= 16 - item.n_lo;
-              const int i = ib ? 16 * ib - item.n_lo + row : lo ? row - (16 - item.n_lo) : row, a = i < item.r ? axis(i) : -1;
-              const double u = a < 0 ? 0.0 : W[(size_t)a * hop + col];
-              p->h_lu.push_back(lo ? (float)(u - (double)(float)u) : (float)u);
-            }
-    // coefficient fragments [step][lane]: lane (q, row) holds A[row][16 step + 4 q + e], the coordinates of the row's
-    // hop-blocks one after the other
-    for (int b = 0; b < 2; ++b) {
-      item.a0[b] = (long long)p->h_la.size() / 4;
-      for (int s = b ? item.s_lo : 0; s < (b ? item.s_hi : item.n_step); ++s)
-        for (int lane = 0; lane < 64; ++lane)
-          for (int e = 0; e < 4; ++e) {
-            const int row = 16 * b + (lane & 15), f = 16 * s + 4 * (lane >> 4) + e, j = f / item.r, i = f - j * item.r;
-            const int a = row < 2 * nb && j < J ? axis(i) : -1;
-            const double v = a < 0 ? 0.0 : D[((size_t)row * J + j) * r0 + a] * std::sqrt(norm2[row / 2]);
-            p->h_la.push_back(i < keep ? (float)v : (float)(v - (double)(float)v));
-          }
-    }
-    p->h_litems.push_back(item);
+    g.item.u0 += (long long)p->h_lu.size() / 4;
+    for (long long& a0 : g.item.a0) a0 += (long long)p->h_la.size() / 4;
+    p->h_lu.insert(p->h_lu.end(), g.lu.begin(), g.lu.end());
+    p->h_la.insert(p->h_la.end(), g.la.begin(), g.la.end());
+    p->h_litems.push_back(g.item);
+    p->lr_limit += g.limit;
+    cost += 16.0 * g.item.n_ib * hop + 256.0 * (g.item.n_step + g.item.s_hi - g.item.s_lo);
+    g = LowrankGroup();
   }
-  if (!any) return;
+  if (p->h_litems.empty() || cost > p->lr_limit) {  // (no call would take this form: shape_lowrank)
+    p->h_litems.clear();
+    std::vector<float>().swap(p->h_lu);
+    std::vector<float>().swap(p->h_la);
+    p->lr_limit = 0;
+    return;
+  }
   for (size_t i = 0; i < as_is.size(); ++i) {
-    const bool two = i + 1 < as_is.size() && as_is[i + 1] == as_is[i] + G;
-    add_direct(as_is[i], std::min(two ? 2 * G : G, p->n_bins - as_is[i]));
+    const bool two = i + 1 < as_is.size() && as_is[i + 1] == as_is[i] + kGroup;
+    add_direct(as_is[i], std::min(two ? 2 * kGroup : kGroup, p->n_bins - as_is[i]));
     if (two) ++i;
   }
   // those with a basis first, the heaviest first: the light ones fill their launch's tail
@@ -1103,6 +1142,20 @@ void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long lo
   p->lowrank = true;
 }
 
+CqtKernelSource cqt_kernels(const nna_plan* p) {
+  auto gen = std::make_shared<CqtKernelGen>(p);
+  return {[gen](int row, long long tap) { return gen->value(row, tap); },
+          [gen](int k, long long tap0, int n, double* re, double* im) { gen->taps(k, tap0, n, re, im); }};
+}
+CqtKernelSource dense_kernels(std::vector<double> rows, long long K) {
+  auto r = std::make_shared<const std::vector<double>>(std::move(rows));
+  return {[r, K](int row, long long tap) { return (*r)[(size_t)row * K + tap]; },
+          [r, K](int k, long long tap0, int n, double* re, double* im) {
+            std::copy_n(r->data() + (size_t)(2 * k) * K + tap0, n, re);
+            std::copy_n(r->data() + (size_t)(2 * k + 1) * K + tap0, n, im);
+          }};
+}
+
 // A plan that holds what build_cqt_bank_lowrank made of `sub`'s kernels (a device plan keeps them on the device only); false: `sub`
 // is not a plan whose kernels are taken by hop-blocks.  `owner`: the plan with frequency-domain kernels that `sub` composes, or sub.
 bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy) {
@@ -1113,13 +1166,10 @@ bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy)
   copy.n_bins = sub->n_bins;
   copy.row_s = sub->row_s;
   copy.row_e = sub->row_e;
-  if (owner != sub) {
-    const std::vector<double> rows = cqt1992_composed_rows(owner);
-    build_cqt_bank_lowrank(&copy, [&](int row, long long tap) { return rows[(size_t)row * copy.K + tap]; });
-  } else {
-    CqtKernelGen gen(sub);
-    build_cqt_bank_lowrank(&copy, [&](int row, long long tap) { return gen.value(row, tap); });
-  }
+  if (owner != sub)
+    build_cqt_bank_lowrank(&copy, dense_kernels(cqt1992_composed_rows(owner), copy.K));
+  else
+    build_cqt_bank_lowrank(&copy, cqt_kernels(sub));
   return copy.lowrank;
 }
 

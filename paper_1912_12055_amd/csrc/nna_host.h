@@ -15,6 +15,7 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <new>
 
@@ -361,6 +362,24 @@ struct CqtKernelGen {
     const double ph = 2.0 * kPi * p->Q * (double)n / (double)p->Nk[k];
     return (row & 1) ? -w * std::sin(ph) : w * std::cos(ph);
   }
+  // bin k's kernel, taps tap0 .. tap0 + n - 1
+  void taps(int k, long long tap0, int n, double* re, double* im) const {
+    for (int i = 0; i < n; ++i) {
+      const long long t = tap0 + i - p->sk[k];
+      re[i] = im[i] = 0.0;
+      if (t < 0 || t >= p->Nk[k]) continue;
+      const double w = window_value(p->window, t, p->Nk[k]) / wsum[k];
+      double s, c;
+      sincos(2.0 * kPi * p->Q * (double)t / (double)p->Nk[k], &s, &c);
+      re[i] = w * c;
+      im[i] = -w * s;
+    }
+  }
+};
+// a bank of constant-Q kernels: row 2k / 2k + 1 (Re / Im of bin k) at one tap, and a run of taps of both; called from several threads
+struct CqtKernelSource {
+  std::function<double(int row, long long tap)> value;
+  std::function<void(int k, long long tap0, int n, double* re, double* im)> taps;
 };
 
 inline long long floor_div(long long a, long long b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
@@ -394,8 +413,10 @@ void build_cqt1992_matrix(nna_plan* p);
 MelDeviceLayout layout_cqt1992(nna_plan* p);
 std::vector<double> cqt1992_composed_rows(const nna_plan* p);
 void build_cqt_bank(nna_plan* p);
-// Rows 2k, 2k + 1 of `value` (bin k's kernel, p->K taps) in the form of nna_kernels_cql.hip; sets p->lowrank if it saves anything
-void build_cqt_bank_lowrank(nna_plan* p, const std::function<double(int, long long)>& value);
+// The kernels (p->K taps) in the form of nna_kernels_cql.hip; sets p->lowrank if it saves anything
+void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels);
+CqtKernelSource cqt_kernels(const nna_plan* p);
+CqtKernelSource dense_kernels(std::vector<double> rows, long long K);  // [2 n_bins][K]
 bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy);
 void cqt_applied_rows(const nna_plan* p, double* out);
 void build_cqt_bank_rows(nna_plan* c, const std::vector<double>& rows);

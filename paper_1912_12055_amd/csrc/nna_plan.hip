@@ -206,10 +206,7 @@ nna_status make_cqt_plan(nna_plan** plan, int sr, int hop, double fmin, int k_fi
     for (int k = 0; k < n_bins; ++k) p->sk[k] = (taps - p->Nk[k]) / 2;
     build_cqt_bank(p);
     p->hop_blocks = lowrank;
-    if (lowrank && device >= 0) {
-      CqtKernelGen gen(p);
-      build_cqt_bank_lowrank(p, [&](int row, long long tap) { return gen.value(row, tap); });
-    }
+    if (lowrank && device >= 0) build_cqt_bank_lowrank(p, cqt_kernels(p));
     build_cqt_bank_fold(p);
   } catch (const std::bad_alloc&) {
     delete p;
@@ -458,7 +455,7 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
     build_stft_bank(p);
     build_cqt1992_matrix(p);
     lin = layout_cqt1992(p);
-    const std::vector<double> rows = cqt1992_composed_rows(p);
+    std::vector<double> rows = cqt1992_composed_rows(p);
     c = new nna_plan;
     c->kind = NNA_KIND_CQT;
     c->device = device;
@@ -473,7 +470,7 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
     c->pad = p->pad;
     build_cqt_bank_rows(c, rows);
     c->hop_blocks = lowrank;
-    if (lowrank && device >= 0) build_cqt_bank_lowrank(c, [&](int row, long long tap) { return rows[(size_t)row * p->K + tap]; });
+    if (lowrank && device >= 0) build_cqt_bank_lowrank(c, dense_kernels(std::move(rows), c->K));
   } catch (const std::bad_alloc&) {
     delete c;
     delete p;
