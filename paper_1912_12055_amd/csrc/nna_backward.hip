@@ -132,6 +132,17 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
   } catch (const std::bad_alloc&) {
     return fail(NNA_ERR_ALLOC, "out of host memory");
   }
+  // cqt_few_kernel's time goes by frames times all steps of 16 taps, cqt_kernel's, while its workgroups are fewer than the chip holds,
+  // by the longest workgroup's steps.  Training step over cqt_kernel's by frames x steps / longest (22.05 kHz, 60 and 120 bins, hops
+  // 256 and 512, MI355X): 0.40 .. 0.58 at 10,000, 0.73 .. 0.86 at 22,000 .. 25,000, 0.85 at 33,000, 1.05 at 37,000.
+  long long steps = 0, longest = 1;
+  for (const nna::CqtItem& item : plan->h_items) {
+    long long sum = 0;
+    for (int rb = item.rb_first; rb < item.rb_first + item.n_rb; ++rb) sum += (plan->row_e[rb * CQ_ROWS] - plan->row_s[rb * CQ_ROWS] + 15) / 16;
+    steps += sum;
+    longest = std::max(longest, sum);
+  }
+  plan->few_frames = 34000 * longest / std::max(1LL, steps);
   plan->rows_pad = rows_pad;
   plan->kp = kp;
   float* d_logical = nullptr;

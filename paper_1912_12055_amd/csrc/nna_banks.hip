@@ -834,7 +834,6 @@ struct LowrankGroup {
   bool basis = false;        // the kernels of its bins are combinations of a basis
   nna::CqlItem item{};
   std::vector<float> lu, la;  // (item.u0, item.a0 count from their beginning)
-  double limit = 0;          // its share of lr_limit
 };
 constexpr int kGroup = 16;
 
@@ -850,16 +849,13 @@ void block_taps(const nna_plan* p, int k0, int nb, int b, long long& lo, long lo
 
 LowrankGroup lowrank_group(const nna_plan* p, int k0, const CqtKernelSource& kernels) {
   LowrankGroup g;
-  const long long K = p->K;
   const int hop = p->hop, nb = std::min(kGroup, p->n_bins - k0);
   // hop-blocks of the two row blocks
   int jl[2] = {INT_MAX, INT_MAX}, jh[2] = {0, 0};
-  double direct = 0;  // multiply-adds per frame of the form that would run otherwise
   for (int k = k0; k < k0 + nb; ++k) {
     const int b = (k - k0) / 8;
     jl[b] = std::min(jl[b], (int)(p->row_s[2 * k] / hop));
     jh[b] = std::max(jh[b], (int)ceil_div(p->row_e[2 * k], hop));
-    direct += 2.0 * (double)(p->row_e[2 * k] - p->row_s[2 * k]);
   }
   if (nb <= 8) jl[1] = jh[1] = jl[0];
   double as_is_cost = 0;
@@ -991,8 +987,6 @@ LowrankGroup lowrank_group(const nna_plan* p, int k0, const CqtKernelSource& ker
   item.n_bins = nb;
   if (item.n_ib > CQL_MAX_BASIS || cost_of(item.r) > as_is_cost) return g;
   g.basis = true;
-  // ... of the kernel that runs otherwise: 0.55 of the taps where they fold (dense kernels do not)
-  g.limit = (p->row_e[2 * k0] - p->row_s[2 * k0] == K ? 1.0 : 0.55) * direct;
   // basis fragments [chunk][block][half][lane]: lane (q, i) holds row i of the block, columns 32 chunk + 16 half + 4 q + e.  The
   // last n_lo rows of block 0 are what float32 leaves of its first n_lo.
   item.u0 = (long long)g.lu.size() / 4;
@@ -1079,6 +1073,7 @@ void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels) {
           int a = 0;
           while (a < n_rb && t0 + 16 > lo[a] && t0 < hi[a]) ++a;
           if (!a) continue;
+          p->lr_direct += 256.0 * a;
           steps.push_back(a | (c / 16 + half) << 3 | j << 12);
           for (int b = 0; b < 4; ++b)
             for (int lane = 0; lane < 64; ++lane)
@@ -1104,7 +1099,6 @@ void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels) {
   // the groups know nothing of each other (44.1 kHz, 168 bins of 24 per octave: 155 -> 39 ms)
   std::vector<LowrankGroup> groups((p->n_bins + kGroup - 1) / kGroup);
   for_each_parallel((int)groups.size(), [&](int i) { groups[i] = lowrank_group(p, i * kGroup, kernels); });
-  double cost = 0;  // of a waveform of many frames
   for (size_t i = 0; i < groups.size(); ++i) {
     LowrankGroup& g = groups[i];
     if (!g.basis) {
@@ -1116,17 +1110,9 @@ void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels) {
     p->h_lu.insert(p->h_lu.end(), g.lu.begin(), g.lu.end());
     p->h_la.insert(p->h_la.end(), g.la.begin(), g.la.end());
     p->h_litems.push_back(g.item);
-    p->lr_limit += g.limit;
-    cost += 16.0 * g.item.n_ib * hop + 256.0 * (g.item.n_step + g.item.s_hi - g.item.s_lo);
     g = LowrankGroup();
   }
-  if (p->h_litems.empty() || cost > p->lr_limit) {  // (no call would take this form: shape_lowrank)
-    p->h_litems.clear();
-    std::vector<float>().swap(p->h_lu);
-    std::vector<float>().swap(p->h_la);
-    p->lr_limit = 0;
-    return;
-  }
+  if (p->h_litems.empty()) return;
   for (size_t i = 0; i < as_is.size(); ++i) {
     const bool two = i + 1 < as_is.size() && as_is[i + 1] == as_is[i] + kGroup;
     add_direct(as_is[i], std::min(two ? 2 * kGroup : kGroup, p->n_bins - as_is[i]));
@@ -1166,6 +1152,14 @@ bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy)
   copy.n_bins = sub->n_bins;
   copy.row_s = sub->row_s;
   copy.row_e = sub->row_e;
+  copy.exec_flops = sub->exec_flops;
+  copy.h_items = sub->h_items;
+  copy.max_jspan = sub->max_jspan;
+  copy.row_step = sub->row_step;
+  copy.cq_fold = sub->cq_fold;
+  copy.exec_flops_cqf = sub->exec_flops_cqf;
+  copy.h_qitems = sub->h_qitems;
+  copy.q_max_jspan = sub->q_max_jspan;
   if (owner != sub)
     build_cqt_bank_lowrank(&copy, dense_kernels(cqt1992_composed_rows(owner), copy.K));
   else

@@ -215,7 +215,7 @@ struct nna_plan {
   std::vector<int> h_lsteps;
   std::vector<int> h_lsupport;  // [n_bins][2] first tap, last tap + 1 of each kernel
   int* d_lsteps = nullptr;
-  double lr_limit = 0;  // multiply-adds per frame of the other form, at the rate of this one
+  double lr_direct = 0;  // multiply-adds per frame of the kernels that stay as they are
   float* d_lu = nullptr;
   float* d_la = nullptr;
   nna::CqlItem* d_litems = nullptr;
@@ -223,6 +223,7 @@ struct nna_plan {
   bool runs_lowrank() const { return lowrank && !d_wrm; }
   // trainable CQT plans: index map caller's tensor -> streaming order, each row's tap support, and the
   // tables that let the backward contractions skip what lies outside every support
+  long long few_frames = 0;  // frames below which launch_conv takes the kernel for batches of few workgroups
   int* d_cq_map = nullptr;
   int* d_row_lo = nullptr;
   int* d_row_hi = nullptr;

@@ -338,19 +338,15 @@ nna_status run_conv_fold(const nna_plan* sub, const float* x, long long B, long 
 
 // The kernels by hop-blocks (nna_kernels_cql.hip).  A tile is 64 frames per 16-frame block of a wave (the registers of a direct
 // item hold two such blocks); smaller tiles spread a short batch over the chip.  Two workgroups per CU want 80 KB of LDS each; a
-// tile cut below three quarters for that takes one workgroup's 156 KB instead.  False: not a launch for this kernel (waveforms of
-// so few frames that the first stage, which runs over their hop-blocks, costs more than it saves).
+// tile cut below three quarters for that takes one workgroup's 156 KB instead.  False: not a launch for this kernel.  It is one
+// where the form that runs otherwise (folded about the centres, or tap by tap) has fewer workgroups than there are CUs (its time over
+// the other's, batches of 50 to 13,000 frames, MI355X: 0.02 .. 0.9), or takes 1.43 times the multiply-adds, unfilled tiles and the
+// first stage's overlap counted (theirs over the other's 0.1 .. 0.5: time 0.04 .. 0.73, 0.51 .. 0.62: 0.53 .. 0.93, 0.63 .. 0.69: 0.7
+// .. 1.06, 0.71 .. 0.81: 0.7 .. 1.23; 13,000 to 400,000 frames).
 bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::CqlParams& P) {
-  double cost = 0;
-  int n_basis = 0;
-  const int n_items = (int)sub->h_litems.size();
-  for (const nna::CqlItem& it : sub->h_litems)
-    if (it.r) {
-      ++n_basis;
-      cost += 16.0 * it.n_ib * sub->hop * (double)(T + it.jspan - 1) / (double)T + 256.0 * (it.n_step + it.s_hi - it.s_lo);
-    }
-  if (cost > sub->lr_limit) return false;
+  const int n_items = (int)sub->h_litems.size(), n_basis = (int)std::count_if(sub->h_litems.begin(), sub->h_litems.end(), [](const nna::CqlItem& it) { return it.r != 0; });
   P.lds_floats = 0;
+  double cost = 0;  // multiply-adds per frame
   for (int direct = 0; direct < 2; ++direct) {
     const int i0 = direct ? n_basis : 0, i1 = direct ? n_items : n_basis;
     nna::CqlPart& part = direct ? P.direct : P.basis;
@@ -376,11 +372,19 @@ bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::Cq
     part.n_ft = (n_frames + M - 1) / M;
     const long long nseg = 1 + (M - 1 + T - 1) / T;
     for (int i = i0; i < i1; ++i) {
-      const int rows = (int)(M + nseg * (sub->h_litems[i].jspan - 1));
-      P.lds_floats = std::max(P.lds_floats, direct ? (rows + 31) / 32 * 32 * 2 * (nna::CQL_COLS(part.fb) + 4) : rows * sub->h_litems[i].r + 16);
+      const nna::CqlItem& it = sub->h_litems[i];
+      const int rows = (int)(M + nseg * (it.jspan - 1));
+      P.lds_floats = std::max(P.lds_floats, direct ? (rows + 31) / 32 * 32 * 2 * (nna::CQL_COLS(part.fb) + 4) : rows * it.r + 16);
+      cost += direct ? 0.0 : (16.0 * it.n_ib * sub->hop * rows + 256.0 * (it.n_step + it.s_hi - it.s_lo) * cap) / M;
     }
+    if (direct) cost += sub->lr_direct * cap / M;
   }
-  return true;
+  const int M0 = pick_tile_frames(CQ_FRAMES, T, (sub->max_jspan - 1) * sub->row_step, CQ_LDS_ROWS_MAX);
+  const int Mf = sub->runs_cqfold() ? pick_tile_frames(CQ_FRAMES, T, sub->q_max_jspan - 1, nna::CQF_LDS_ROWS) : 0;
+  const bool folds = Mf >= 1 && 2 * Mf >= M0;
+  const int M = folds ? Mf : M0;
+  if (M < 1 || (n_frames + M - 1) / M * (long long)(folds ? sub->h_qitems.size() : sub->h_items.size()) < 256) return true;
+  return cost <= 0.7 * 0.5 * (folds ? sub->exec_flops_cqf : sub->exec_flops) * CQ_FRAMES / M;
 }
 
 nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
@@ -399,8 +403,7 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
 }
 
 hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t stream) {
-  if (sub->d_wrm && P.n_ft * P.n_items < 256)
-    return nna::launch_cqt_few(P, sub->d_row_lo, sub->d_row_hi, stream);
+  if (sub->d_wrm && P.g.n_frames < sub->few_frames) return nna::launch_cqt_few(P, sub->d_row_lo, sub->d_row_hi, stream);
   return nna::launch_cqt(P, stream);
 }
 

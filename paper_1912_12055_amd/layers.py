@@ -87,10 +87,13 @@ class _MelFn(torch.autograd.Function):
         ctx.layer = layer
         ctx.save_for_backward(x)
         # the filters are dense: through the spectrogram, of a slice of the batch at a time
-        B, (bins, frames), F = x.shape[0], nb.nna_out_shape(layer.plan, *x.shape), layer.wsin_wcos.shape[0] // 2
+        B, F = x.shape[0], layer.wsin_wcos.shape[0] // 2
+        if B * F * (x.shape[1] // layer.hop_length + 2) <= _SPECTROGRAM_FLOATS:
+            return nb.nna_mel_with_stft(layer.plan, x)[0]
+        bins, frames = nb.nna_out_shape(layer.plan, *x.shape)
         step = max(1, _SPECTROGRAM_FLOATS // (F * frames))
         out, spec = x.new_empty((B, bins, frames)), x.new_empty((min(step, B), F, frames))
-        for b in range(0, max(B, 1), step):
+        for b in range(0, B, step):
             n = min(step, B - b)
             nb.nna_mel_with_stft(layer.plan, x[b:b + n], out=out[b:b + n], spec=spec[:n])
         return out
@@ -166,6 +169,7 @@ class MelSpectrogram(_Trainable):
                                     n_mels=n_mels, fmin=fmin, fmax=fmax or 0.0,
                                     scale=nb.NNA_MEL_HTK if htk else nb.NNA_MEL_SLANEY, norm_area=bool(norm),
                                     power=power, device=_device_index(device))
+        self.hop_length = hop_length
         self.trainable = bool(trainable_mel or trainable_STFT)
         if self.trainable:
             nb.nna_plan_trainable(self.plan)
