@@ -260,9 +260,7 @@ __global__ __launch_bounds__(256, LIN_NB > 4 ? 1 : 2) void stft_kernel(const Stf
           float* __restrict__ pp = P.pout ? P.pout + (b_lane * P.out_bins) * g.T + t_lane : nullptr;
           if (P.fmt == NNA_OUT_MAGNITUDE)
             stft_grad_tile<NNA_OUT_MAGNITUDE>(acc, gp, g.T, Gp, P.gpitch, slot_base, h, P.n_half, P.packed, pp);
-          else if (P.fmt == NNA_OUT_POWER)
-            stft_grad_tile<NNA_OUT_POWER>(acc, gp, g.T, Gp, P.gpitch, slot_base, h, P.n_half, P.packed, pp);
-          else if (P.fmt == NNA_OUT_LOG)
+          else if (P.fmt == NNA_OUT_LOG)  // (power: launch_split_forward)
             stft_grad_tile<NNA_OUT_LOG>(acc, gp, g.T, Gp, P.gpitch, slot_base, h, P.n_half, P.packed);
           else if (P.fmt == NNA_OUT_COMPLEX)
             stft_grad_tile<NNA_OUT_COMPLEX>(acc, gp, g.T, Gp, P.gpitch, slot_base, h, P.n_half, P.packed);
@@ -963,6 +961,7 @@ hipError_t launch_stft(StftParams p, int mode, hipStream_t stream) {
   p.rt_per_wg = ST_RG;
   while (p.rt_per_wg > 1 && p.n_ft * ((p.n_rt + p.rt_per_wg - 1) / p.rt_per_wg) < 512) p.rt_per_wg /= 2;
   const bool mel = mode == ST_MODE_MEL || mode == ST_MODE_LIN || mode == ST_MODE_MELSPEC;
+  if (mode == ST_MODE_GRAD && p.fmt == NNA_OUT_POWER) return hipErrorInvalidValue;
   if (mode == ST_MODE_MELSPEC && !p.pout) return hipErrorInvalidValue;
   if (mel) {
     blocks = p.n_ft * p.n_pass;

@@ -612,7 +612,6 @@ hipError_t cql_kernels_init() {
   hipError_t e = allow_lds<1, 1>();
   if (e == hipSuccess) e = allow_lds<2, 1>();
   if (e == hipSuccess) e = allow_lds<4, 1>();
-  if (e == hipSuccess) e = allow_lds<1, 2>();
   if (e == hipSuccess) e = allow_lds<2, 2>();
   if (e == hipSuccess) e = allow_lds<4, 2>();
   return e;
@@ -624,12 +623,13 @@ hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream) {
   if (blocks <= 0 || blocks > 0x7fffffffLL || p.g.hop % 32) return hipErrorInvalidValue;
   if (p.basis.tile_frames < 1 || p.basis.tile_frames > 64 * p.basis.fb || p.direct.tile_frames > 64 * p.direct.fb) return hipErrorInvalidValue;
   if (p.lds_floats < 1 || (size_t)p.lds_floats * 4 > (size_t)CQL_LDS_ONE) return hipErrorInvalidValue;
+  // (a batch large enough for two blocks per wave of the direct items is so for those with a basis)
   const int fb = p.basis.fb, fd = p.direct.fb;
-  if ((fb != 1 && fb != 2 && fb != 4) || (fd != 1 && fd != 2)) return hipErrorInvalidValue;
+  if ((fb != 1 && fb != 2 && fb != 4) || (fd != 1 && fd != 2) || fd > fb) return hipErrorInvalidValue;
   if (fd == 1)
     fb == 1 ? launch<1, 1>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 1>(p, (unsigned)blocks, stream) : launch<4, 1>(p, (unsigned)blocks, stream);
   else
-    fb == 1 ? launch<1, 2>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 2>(p, (unsigned)blocks, stream) : launch<4, 2>(p, (unsigned)blocks, stream);
+    fb == 2 ? launch<2, 2>(p, (unsigned)blocks, stream) : launch<4, 2>(p, (unsigned)blocks, stream);
   return hipGetLastError();
 }
 
