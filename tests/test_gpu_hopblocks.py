@@ -21,22 +21,26 @@ def nb():
 
 
 CASES = [
-    # n_bins, bpo, sr, hop, fmin, n_taps, B, L, center
-    (1, 12, 8000, 32, 40.0, 0, 1, 4001, True),          # one bin, one row block
-    (17, 12, 8000, 64, 40.0, 0, 3, 2050, True),         # 16 + 1 bins; two samples past the shortest waveform
-    (33, 24, 16000, 128, 60.0, 0, 2, 16391, True),      # 24 per octave, odd length
-    (60, 12, 16000, 96, 50.0, 6144, 5, 9001, True),     # a hop that is no power of two
-    (40, 12, 22050, 512, 60.0, 0, 1, 30000, False),     # no padding
-    (84, 12, 22050, 512, 32.7, 0, 40, 44101, True),     # tiles of 128 frames across waveforms
-    (48, 24, 22050, 256, 65.4, 0, 90, 40002, True),     # ... of 256
+    # n_bins, bpo, sr, hop, fmin, n_taps, B, L, center, (frames per tile, 16-frame blocks per wave) of the bins with a basis and tap by tap
+    (8, 12, 8000, 64, 40.0, 0, 1, 4001, True, ((64, 1), (0, 0))),          # one row block
+    (1, 12, 8000, 32, 40.0, 0, 3, 2050, True, ((64, 1), (0, 0))),          # one bin; two samples past the shortest waveform
+    (17, 24, 8000, 64, 40.0, 0, 3, 4098, True, ((64, 1), (0, 0))),         # 16 + 1 bins
+    (33, 24, 16000, 128, 60.0, 0, 2, 16391, True, ((64, 1), (0, 0))),      # odd length
+    (60, 12, 16000, 96, 50.0, 6144, 5, 9001, True, ((64, 1), (64, 1))),    # a hop that is no power of two
+    (40, 12, 22050, 512, 60.0, 0, 1, 30000, False, ((64, 1), (64, 1))),    # no padding
+    (84, 12, 22050, 512, 32.7, 0, 40, 44101, True, ((64, 1), (64, 1))),    # tiles across waveforms
+    (60, 12, 8000, 64, 80.0, 0, 170, 9001, True, ((128, 2), (128, 2))),    # tiles of 128 frames and of
+    (40, 24, 8000, 64, 40.0, 0, 170, 9001, True, ((128, 2), (0, 0))),      # ... 256, with kernels taken tap by tap beside them and without
+    (60, 12, 16000, 96, 50.0, 6144, 1000, 6001, True, ((253, 4), (127, 2))),
+    (40, 24, 8000, 64, 40.0, 0, 400, 9001, True, ((256, 4), (0, 0))),
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}x{c[3]}")
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}x{c[3]}-{c[6]}x{c[7]}")
 @pytest.mark.parametrize("fmt", ["MAGNITUDE", "COMPLEX"])
 def test_hop_blocks(nb, case, fmt):
     import torch
-    n_bins, bpo, sr, hop, fmin, n_taps, B, L, center = case
+    n_bins, bpo, sr, hop, fmin, n_taps, B, L, center, tiles = case
     print(f"[case] hop-blocks {case} {fmt}", file=sys.stderr, flush=True)
     cfg = dict(sr=sr, hop=hop, fmin=fmin, n_bins=n_bins, bins_per_octave=bpo, n_taps=n_taps)
     rng = np.random.default_rng([29, n_bins, hop])
@@ -44,7 +48,7 @@ def test_hop_blocks(nb, case, fmt):
     x[0, L // 3:L // 2] = 0.0
     xd = torch.from_numpy(x).to("cuda:0")
     plan = nb.nna_plan_cqt(center=center, fmt=getattr(nb, "NNA_OUT_" + fmt), device=0, **cfg)
-    assert plan.info()["executed_flops_per_frame"] > 0
+    assert nb.nna_plan_applied_tiles(plan, B, L) == tiles
     out = torch.full(plan_shape(nb, plan, B, L), float("nan"), device="cuda:0")
     got = nb.nna_cqt(plan, xd, out=out).cpu().numpy().astype(np.float64)
     direct = nb.nna_cqt(nb.nna_plan_trainable(plan), xd).cpu().numpy().astype(np.float64)
