@@ -243,7 +243,8 @@ nna_status nna_out_shape(const nna_plan* plan, long long B, long long L, long lo
  * x[n] - x[N-n] over n < N/2 only); where n_fft is also a multiple of 256 the folded taps are summed by parity, E over
  * even n and O over odd n, so that bins k and N/2 - k are E + O and E - O and share their kernels.  Every other plan
  * (trainable, re-spaced axes) runs eq. (DFT2) as it stands; trainable plans on the bfloat16 matrix pipe, every float32 as the
- * exact sum of three bfloat16 (a sample that is not finite makes its frames NaN). */
+ * sum of three bfloat16 (exact from 2^-110 to 3.39e38 in magnitude; below, low bits are lost).  On plans that run the transform, and on
+ * trainable ones, a sample that is not finite makes every output of its frames NaN, also where an infinity alone would give one. */
 nna_status nna_stft(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                     void* hip_stream);
 
@@ -257,7 +258,8 @@ nna_status nna_mel(const nna_plan* plan, const float* x_dev, long long B, long l
  * output feeding the Mel layer), from the one contraction: mel_dev[B, n_mels, T] as nna_mel writes it and
  * spec_dev[B, n_fft/2+1, T] = |X|^power (power 2: the power spectrogram; power 1: the magnitude).  For a
  * caller that wants both, this is one kernel launch of nna_mel's cost plus the spectrogram's stores (a plan that runs
- * neither the fast Fourier transform nor split by tap parity takes the direct contraction for this call).
+ * neither the fast Fourier transform nor split by tap parity takes the direct contraction for this call).  A plan made trainable
+ * takes two: the spectrogram, then its product with the filterbank.
  * Plan from nna_plan_mel (float32); errors as nna_mel, NNA_ERR_INVALID_ARG for a NULL spec_dev. */
 nna_status nna_mel_with_stft(const nna_plan* plan, const float* x_dev, long long B, long long L,
                              float* mel_dev, float* spec_dev, void* hip_stream);

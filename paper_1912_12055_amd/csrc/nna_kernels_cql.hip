@@ -5,7 +5,7 @@
 // kernel is a smooth function.  With U an orthonormal basis of that space and A the coordinates,
 //     y[b][i] = sum_c U[i][c] x[b hop + c]          i < r, every hop-block b of the padded waveform
 //     C_k[t]  = sum_j sum_i A_k[j][i] y[t + j][i].
-// Bins of 24 per octave at 44.1 kHz, hop 512: 0.8 million multiply-adds per frame against 1.6 million of the kernels folded about
+// 168 bins of 24 per octave at 44.1 kHz, hop 512: 0.7 million multiply-adds per frame against 1.6 million of the kernels folded about
 // their centres (nna_kernels_cqf.hip) and 3.2 million of the kernels as they stand.
 //
 // Short kernels, where the first stage alone would cost more than their taps, stay as they are: direct items of up to 32 bins.

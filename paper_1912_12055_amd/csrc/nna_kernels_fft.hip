@@ -6,8 +6,10 @@
 // X[k] = (Z[k] + conj Z[M-k]) / 2 - i e^{-2 pi i k / N} (Z[k] - conj Z[M-k]) / 2.  About 60,000 operations per frame of
 // 2,048 samples instead of 2.1 million in the contraction that used every symmetry of its kernels.
 //
-// What bounds it: the vector ALUs (about 700 instructions per 64 lanes and frame) and, behind them, writing the spectrum in
-// runs of 16 frames (64 bytes, rarely aligned: 700 of the 2,200 us below).  A wave owns whole frames up to N = 2,048, so
+// What bounds it: two waves per SIMD, each a chain of passes through LDS.  No pipe is full (1,770 x 176,400 samples, N = 2,048, and
+// the Mel call at N = 4,096 below, counters): vector ALUs busy 43 and 47 %, the LDS pipe 24 and 28 %, 2.0 and 0.8 TB/s of memory; a
+// wave waits for data 21 and 42 % of its cycles (at 4,096 two waves share a frame and meet at barriers), to issue 35 and 23 %.  A wave
+// owns whole frames up to N = 2,048, so
 // the passes exchange their values through LDS without a barrier (a wave's LDS accesses complete in order); real and
 // imaginary parts go one after the other through the same words.  The region a frame exchanges through is the row of the
 // output tile its finished bins are written to, so a tile of 16 frames costs 70 KB and two workgroups share a CU.  The tile

@@ -10,14 +10,16 @@
 //     a b = a0 b0 + (a0 b1 + a1 b0) + (a0 b2 + a1 b1 + a2 b0) + terms below 2^-26 |a b|,
 // six products whose terms are exact in float32, summed by v_mfma_f32_32x32x16_bf16 into float32 accumulators: sixteen times the
 // rate of the float32 instruction for six times the work, and fewer roundings (six per sixteen terms; the float32 instruction
-// rounds every two).  A sample or weight that is not finite makes everything it meets NaN.
+// rounds every two).  Exact holds for magnitudes from 2^-110 to the largest bfloat16, 3.39e38: a smaller one loses low bits (its third
+// part falls below the smallest bfloat16), a larger one rounds to infinity.  A sample or weight that is not finite makes everything
+// it meets NaN.
 //
 // A workgroup computes 128 rows x 128 columns, a wave all the rows x 32 columns of its own.  The rows' operand is staged through
 // LDS, split on the way in, every value once (two buffers, one barrier per 32 contraction indices); the columns' operand nobody
 // else in the workgroup reads, and it goes from memory to the wave's registers.
 //
-// What bounds it: the matrix pipe is half busy and the vector ALUs, which split the operands, a third; with two waves per SIMD the
-// two overlap in part.  64 x 110,250 samples, n_fft 2,048 (116 GFLOP each, MI355X; float32 instruction before): contraction 1,045 ->
+// What bounds it: the matrix pipe is busy 37 to 42 % and the vector ALUs, which split the operands, 30 to 46 % (16 x 44,217 samples, the
+// three kernels, counters); with two waves per SIMD the two overlap in part.  64 x 110,250 samples, n_fft 2,048 (116 GFLOP each, MI355X; float32 instruction before): contraction 1,045 ->
 // 650 us, bank gradient 1,000 -> 640 us; 16 x 44,217: bank gradient 146 -> 117 us, waveform gradient 177 -> 113 us.  Errors against
 // 64 bits there: output 6.6e-7 -> 4.7e-7, bank gradient 1.29e-6 -> 9.3e-7.
 #include "nna_device.h"

@@ -177,7 +177,8 @@ class MelSpectrogram(_Trainable):
             self.wsin_wcos = torch.nn.Parameter(nb.nna_plan_get_bank(self.plan), requires_grad=bool(trainable_STFT))
 
     def forward(self, x, return_spectrogram=False):
-        """``return_spectrogram=True`` returns (mel, |X|^power) from the one launch (not differentiable)."""
+        """``return_spectrogram=True`` returns (mel, |X|^power), of a fixed layer from the one launch (not differentiable).  A trainable
+        layer's forward pass holds up to 1 GiB of spectrogram besides its output."""
         x = _as_batch(x)
         if self.trainable:
             self._sync(self.wsin_wcos, nb.nna_plan_set_bank, "bank")
