@@ -35,3 +35,27 @@ def test_trainable_stft_power(n_fft, hop, B, L, scale):
     for name, got, want in (("out", out, ref), ("gw", gw, rw), ("gx", gx, rx)):
         got, want = got.detach().cpu().double().numpy(), want.detach().numpy()
         assert np.linalg.norm(got - want) < TOL * np.linalg.norm(want), name
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e30])
+def test_trainable_stft_range(scale):
+    """Three bfloat16 hold a float32 from 2^-110 up to where its neighbour would be infinite: no more is lost at 1e-30 or 1e30 than
+    at 1, forward and for the kernels' gradient (complex output, so that nothing is squared)."""
+    import torch
+    from paper_1912_12055_amd import layers
+    n_fft, hop, B, L = 512, 128, 3, 9001
+    print(f"[case] split stft range scale={scale}", file=sys.stderr, flush=True)
+    gen = torch.Generator().manual_seed(7)
+    x = torch.randn(B, L, generator=gen) * scale
+    layer = layers.STFT(n_fft=n_fft, hop_length=hop, sr=16000, output_format="Complex", trainable=True)
+    out = layer(x.cuda())
+    gout = torch.randn(out.shape, generator=gen)
+    (gw,) = torch.autograd.grad(out, [layer.wsin_wcos], gout.cuda())
+    w64 = layer.wsin_wcos.detach().cpu().double().requires_grad_(True)
+    frames = torch.nn.functional.pad(x.double()[:, None], (n_fft // 2, n_fft // 2), mode="reflect")[:, 0].unfold(1, n_fft, hop)
+    c = (frames @ w64.t()).transpose(1, 2)
+    (rw,) = torch.autograd.grad(c, [w64], gout.double())
+    rw[[1, n_fft + 1]] = 0.0  # the sine kernels of k = 0 and n_fft / 2 vanish: no parameters
+    for name, got, want in (("out", out, c), ("gw", gw, rw)):
+        got, want = got.detach().cpu().double().numpy().ravel(), want.detach().numpy().ravel()
+        assert np.linalg.norm(got - want) < TOL * np.linalg.norm(want), name
