@@ -137,10 +137,14 @@ struct FftParams {
   const int4* mel;     // [n_mels]: first bin, quads of bins, first quad of weights
   const float4* melw;
   int n_mels, mel_power;
+  int mel_quads;       // of weights, all bands
   int M;               // N / 2
   int fmt;
   int radix[16], n_radix;  // passes of the general kernel
   int pitch, lg_tf;    // set by the launcher: LDS words per frame, log2 of the frames per tile
+  int buf_words;       // LDS words from one tile's buffer to the next one's
+  int sync_word;       // LDS word of two counters
+  int mel_lds;         // LDS word the Mel tables are copied to; 0: they stay in memory
   long long n_tiles;
 };
 // the radices the general kernel takes N/2 apart with; false: N has a prime factor above 7, or does not fit in LDS

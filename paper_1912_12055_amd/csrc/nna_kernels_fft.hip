@@ -6,19 +6,20 @@
 // X[k] = (Z[k] + conj Z[M-k]) / 2 - i e^{-2 pi i k / N} (Z[k] - conj Z[M-k]) / 2.  About 60,000 operations per frame of
 // 2,048 samples instead of 2.1 million in the contraction that used every symmetry of its kernels.
 //
-// What bounds it: two waves per SIMD, each a chain of passes through LDS.  No pipe is full (1,770 x 176,400 samples, N = 2,048, and
-// the Mel call at N = 4,096 below, counters): vector ALUs busy 43 and 47 %, the LDS pipe 24 and 28 %, 2.0 and 0.8 TB/s of memory; a
-// wave waits for data 21 and 42 % of its cycles (at 4,096 two waves share a frame and meet at barriers), to issue 35 and 23 %.  A wave
-// owns whole frames up to N = 2,048, so
-// the passes exchange their values through LDS without a barrier (a wave's LDS accesses complete in order); real and
-// imaginary parts go one after the other through the same words.  The region a frame exchanges through is the row of the
-// output tile its finished bins are written to, so a tile of 16 frames costs 70 KB and two workgroups share a CU.  The tile
-// turns bins-per-frame into runs of consecutive frames of one bin, the order of the output.
+// A wave owns whole frames up to N = 2,048, so the passes exchange their values through LDS without a barrier (a wave's LDS
+// accesses complete in order); real and imaginary parts go one after the other through the same words.  The region a frame
+// exchanges through is the row of the output tile its finished bins are written to.  The tile turns bins-per-frame into runs
+// of consecutive frames of one bin, the order of the output; while one tile is computed, the one before it is written out.
 //
-// 1,770 x 176,400 samples, N = 2,048, hop 512 (MI355X): magnitudes 10.1 -> 2.20 ms.  Mel, 1,770 x 80,000, N = 4,096, 512
-// bands: 34.9 -> 2.01 ms; 64 x 110,250, 128 bands: 808 -> 48 us.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles
-// read from the caches for every frame with four waves per SIMD (2.85 ms: the vector memory path saturates), three
-// waves per SIMD (spills, 4.3 ms), eight waves per workgroup (2.34 ms).
+// What bounds it: two waves per SIMD (the tables a lane keeps in registers), a chain of passes through LDS each.  Without its
+// output the call below takes 0.82 ms, the vector ALUs' time; meeting once a tile and the stores' own instructions add the rest.
+//
+// 1,770 x 176,400 samples, N = 2,048, hop 512 (MI355X): magnitudes 10.1 ms contracted, 2.20 with a tile computed, then stored
+// between two barriers and neighbouring tiles 29 us apart (an output line left its L2 half written, 3.65 GB for 2.50), now 1.50;
+// N = 1,024, hop 256, complex: 4.02 -> 2.35.  Mel, 64 x 110,250, 128 bands: 808 us contracted, 48 -> 39; 1,770 x 80,000,
+// N = 4,096, 512 bands: 34.9 ms, 2.02 -> 1.80.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles read from the caches for
+// every frame with four waves per SIMD (2.85 ms: the vector memory path saturates), from LDS with four waves per SIMD (spills,
+// 1.87 ms), three waves per SIMD (spills, 4.3 ms), the tile stored by two workgroups of four waves (runs of 32 bytes, 2.04 ms).
 #include "nna_device.h"
 
 namespace nna {
@@ -166,56 +167,102 @@ __device__ __forceinline__ void frame_of(int fi, long long b0, int t0, int T, lo
 
 __device__ __forceinline__ int reflect(int i, int L) { return i < 0 ? -i : (i >= L ? 2 * (L - 1) - i : i); }
 
-template <int MODE>
-__device__ __forceinline__ float formatted(const float* __restrict__ row, int r, int plane, int fmt) {
-  if constexpr (MODE == FFT_MODE_CPLX) {
-    if (fmt == NNA_OUT_PHASE) return atan2f(row[plane + r], row[r]);
+template <int FMT>
+__device__ __forceinline__ float formatted(const float* __restrict__ row, int r, int plane) {
+  if constexpr (FMT == NNA_OUT_PHASE)
+    return atan2f(row[plane + r], row[r]);
+  else if constexpr (FMT == NNA_OUT_COMPLEX)
     return row[(r & 1) * plane + (r >> 1)];
-  } else {
-    const float v = row[r];
-    return fmt == NNA_OUT_MAGNITUDE ? __builtin_amdgcn_sqrtf(v) : fmt == NNA_OUT_POWER ? v : logf(fmaxf(v, 1e-10f));
-  }
+  else if constexpr (FMT == NNA_OUT_MAGNITUDE)
+    return __builtin_amdgcn_sqrtf(row[r]);
+  else
+    return FMT == NNA_OUT_POWER ? row[r] : logf(fmaxf(row[r], 1e-10f));
 }
 
 // The finished tile, frame after frame in LDS, to [waveform][row][frame]: a wave writes G = 64 / TF rows per instruction,
 // TF consecutive frames each.  The G rows lie TF apart, which spreads their LDS reads over all banks (the pitch is odd).
-template <int MODE>
-__device__ __forceinline__ void store_tile(const float* __restrict__ tile, int pitch, int plane, int lg_tf, int rows,
-                                           float* __restrict__ out, int fmt, long long n_left, long long b0, int t0, int T,
-                                           int wave, int n_wave, int lane) {
+// Part `part` of 2^lg_parts of this wave's share, a run of consecutive rows: constant steps in LDS, a scalar step in memory.
+template <int FMT>
+__device__ __forceinline__ void store_rows(const float* __restrict__ tile, int pitch, int plane, int lg_tf, int rows,
+                                           float* __restrict__ out, long long n_left, long long b0, int t0, int T,
+                                           int wave, int n_wave, int lane, int part, int lg_parts) {
   const int TF = 1 << lg_tf, f = lane & (TF - 1), r_lane = (lane >> lg_tf) << lg_tf;
   if (f >= n_left) return;
   long long b;
   int t;
   frame_of(f, b0, t0, T, b, t);
   float* __restrict__ op = out + (b * rows + r_lane) * (long long)T + t;
-  const float* __restrict__ row = tile + f * pitch;
-  int v = wave;
-#pragma unroll 4
-  for (; ((v >> lg_tf) << 6) + 64 <= rows; v += n_wave) {
+  // (complex: an odd r_lane only where TF is 1, and then every r below is even)
+  const float* __restrict__ row = tile + f * pitch + (FMT == NNA_OUT_COMPLEX ? (r_lane & 1) * plane + r_lane / 2 : r_lane);
+  const int full = rows >> 6 << lg_tf;  // instructions that write G rows
+  int v = full * wave / n_wave, v_end = full * (wave + 1) / n_wave;
+  const int n = v_end - v;
+  v_end = v + (n * (part + 1) >> lg_parts);
+  v += n * part >> lg_parts;
+  while (v < v_end) {
     const int r = ((v >> lg_tf) << 6) + (v & (TF - 1));
-    op[(long long)r * T] = formatted<MODE>(row, r_lane + r, plane, fmt);
+    if (v + 8 <= v_end && (v & (TF - 1)) + 8 <= TF && (FMT != NNA_OUT_COMPLEX || r % 2 == 0)) {
+      const float* __restrict__ src = row + (FMT == NNA_OUT_COMPLEX ? r / 2 : r);
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = formatted<FMT>(src, i, plane);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) op[(long long)(r + i) * T] = x[i];
+      v += 8;
+    } else {
+      op[(long long)r * T] = formatted<FMT>(row, r, plane);
+      ++v;
+    }
   }
-  for (; ((v >> lg_tf) << 6) < rows; v += n_wave) {
-    const int r = ((v >> lg_tf) << 6) + (v & (TF - 1));
-    if (r_lane + r < rows) op[(long long)r * T] = formatted<MODE>(row, r_lane + r, plane, fmt);
+  // the rows behind the last 64: TF of them per turn, the lanes past the last one idle
+  if (part + 1 == 1 << lg_parts)
+    for (int i = wave; i < TF && i < (rows & 63); i += n_wave) {
+      const int r = (rows & ~63) + i;
+      if (r + r_lane < rows) op[(long long)r * T] = formatted<FMT>(row, r, plane);
+    }
+}
+
+template <int MODE>
+__device__ __forceinline__ void store_tile(const float* __restrict__ tile, int pitch, int plane, int lg_tf, int rows,
+                                           float* __restrict__ out, int fmt, long long n_left, long long b0, int t0, int T,
+                                           int wave, int n_wave, int lane, int part, int lg_parts) {
+  if constexpr (MODE == FFT_MODE_CPLX) {
+    if (fmt == NNA_OUT_COMPLEX)
+      store_rows<NNA_OUT_COMPLEX>(tile, pitch, plane, lg_tf, rows, out, n_left, b0, t0, T, wave, n_wave, lane, part, lg_parts);
+    else
+      store_rows<NNA_OUT_PHASE>(tile, pitch, plane, lg_tf, rows, out, n_left, b0, t0, T, wave, n_wave, lane, part, lg_parts);
+  } else if constexpr (MODE == FFT_MODE_MEL) {
+    store_rows<NNA_OUT_POWER>(tile, pitch, plane, lg_tf, rows, out, n_left, b0, t0, T, wave, n_wave, lane, part, lg_parts);
+  } else {
+    if (fmt == NNA_OUT_MAGNITUDE)
+      store_rows<NNA_OUT_MAGNITUDE>(tile, pitch, plane, lg_tf, rows, out, n_left, b0, t0, T, wave, n_wave, lane, part, lg_parts);
+    else if (fmt == NNA_OUT_POWER)
+      store_rows<NNA_OUT_POWER>(tile, pitch, plane, lg_tf, rows, out, n_left, b0, t0, T, wave, n_wave, lane, part, lg_parts);
+    else
+      store_rows<NNA_OUT_LOG>(tile, pitch, plane, lg_tf, rows, out, n_left, b0, t0, T, wave, n_wave, lane, part, lg_parts);
   }
 }
 
 // Mel bands of the tile: lanes are (band, frame), so the frames of one band share its weights and a wave's LDS reads
-// are runs of TF words.  Only a band's own bins are visited, four at a time (padded with zero weights).
-__device__ __forceinline__ void mel_tile(const FftParams& P, const float* __restrict__ tile, int pitch, int lg_tf, long long n_left,
-                                         long long b0, int t0, int wave, int n_wave, int lane) {
+// are runs of TF words.  Only a band's own bins are visited, four at a time (padded with zero weights).  `mel`, `melw`: the
+// tables, in LDS where they fit beside the tile (every band's reads of its descriptor and weights are a chain that the caches
+// answer in hundreds of cycles a link).  Bands grow longer upwards: the waves take turns in alternating order.
+__device__ __forceinline__ void mel_tile(const FftParams& P, const int4* mel, const float4* melw, const float* __restrict__ tile, int pitch,
+                                         int lg_tf, long long n_left, long long b0, int t0, int wave, int n_wave, int lane, int part,
+                                         int lg_parts) {
   const int TF = 1 << lg_tf, f = lane & (TF - 1), G = 64 >> lg_tf;
   if (f >= n_left) return;
   long long b;
   int t;
   frame_of(f, b0, t0, P.g.T, b, t);
   float* __restrict__ op = P.out + (b * P.n_mels) * (long long)P.g.T + t;
-  for (int m = wave * G + (lane >> lg_tf); m < P.n_mels; m += n_wave * G) {
-    const int4 d = P.mel[m];  // first bin, quads of bins, first quad of weights
+  const int rounds = (P.n_mels + G * n_wave - 1) / (G * n_wave);
+  for (int j = rounds * part >> lg_parts; j < rounds * (part + 1) >> lg_parts; ++j) {
+    const int m = (j * n_wave + (j & 1 ? n_wave - 1 - wave : wave)) * G + (lane >> lg_tf);
+    if (m >= P.n_mels) continue;
+    const int4 d = mel[m];  // first bin, quads of bins, first quad of weights
     const float* __restrict__ p = tile + f * pitch + d.x;
-    const float4* __restrict__ w = P.melw + d.z;
+    const float4* w = melw + d.z;
     float a0 = 0.f, a1 = 0.f;
 #pragma unroll 2
     for (int i = 0; i < d.y; ++i) {
@@ -234,54 +281,58 @@ __device__ __forceinline__ void mel_tile(const FftParams& P, const float* __rest
 // ---------------------------------------------------------------------------------------
 constexpr int kLdsTwo = 80 * 1024;   // two workgroups per CU
 constexpr int kLdsMax = 156 * 1024;  // one
+constexpr int kLdsAll = 160 * 1024;  // ... to the last byte
 
-template <int M, int R1, int R2, int R3, int V, int NW, int MODE>
+template <int M, int R1, int R2, int R3, int V, int MODE>
 struct FftTile {
   static constexpr int RL = R3 > 1 ? R3 : R2;           // radix of the last pass
   static constexpr int H = M / RL;                      // its butterflies per frame
   static constexpr int TPF = M / V;                     // lanes per frame
-  static constexpr int FPWG = 64 * NW / TPF;            // frames per workgroup and step
   static constexpr int NBL = V / RL;                    // butterflies of the last pass per lane, in pairs j, H - j
   static constexpr int PLANE = M + 1;
   static constexpr int WORDS = MODE == FFT_MODE_CPLX ? 2 * M + 2 : (M + M / 16 > M + 4 ? M + M / 16 : M + 4);
   static constexpr int PITCH = WORDS | 1;
-  // steps of the largest tile: as many as two workgroups' LDS holds, at most 64 frames (the lanes of a store)
-  static constexpr int max_steps() {
+  static constexpr int frames_per_step(int n_wave) { return 64 * n_wave / TPF; }
+  // What a workgroup may take of a CU: eight waves are all that its registers hold.  In one workgroup they write longer runs of the
+  // output; in two, where the output is small (Mel), the two waves of a SIMD wait for nothing of each other's.
+  static constexpr int WAVES = MODE != FFT_MODE_MEL && TPF <= 64 && frames_per_step(8) <= 64 && 2 * frames_per_step(8) * PITCH * 4 <= kLdsAll - 16 ? 8 : 4;
+  static constexpr int LDS = WAVES == 8 ? kLdsAll : kLdsTwo;
+  // steps of the largest tile: what the LDS holds twice, at most 64 frames (the lanes of a store)
+  static constexpr int max_steps(int n_wave, int other_bytes) {
     int n = 1;
-    while (2 * n * FPWG <= 64 && 2 * n * FPWG * PITCH * 4 <= kLdsTwo) n *= 2;
+    while (2 * n * frames_per_step(n_wave) <= 64 && 4 * n * frames_per_step(n_wave) * PITCH * 4 + other_bytes <= LDS) n *= 2;
     return n;
   }
-  static constexpr int LDS_BYTES = max_steps() * FPWG * PITCH * 4;
-  static_assert(FPWG <= 64 && LDS_BYTES <= kLdsTwo, "a tile is at most as wide as a wave");
+  static_assert(frames_per_step(4) <= 64 && 2 * frames_per_step(4) * PITCH * 4 + 16 <= LDS, "a tile is at most as wide as a wave");
 };
 
 // The sizes that have a kernel of their own, and its shape.
-template <int M_, int R1_, int R2_, int R3_, int V_, int NW_>
+template <int M_, int R1_, int R2_, int R3_, int V_>
 struct Shape {
-  static constexpr int M = M_, R1 = R1_, R2 = R2_, R3 = R3_, V = V_, NW = NW_;
+  static constexpr int M = M_, R1 = R1_, R2 = R2_, R3 = R3_, V = V_;
   template <int MODE>
-  using Tile = FftTile<M, R1, R2, R3, V, NW, MODE>;
+  using Tile = FftTile<M, R1, R2, R3, V, MODE>;
 };
 constexpr int kShapes[] = {32, 64, 128, 256, 512, 1024, 2048};
 template <typename Fn>
 bool with_shape(int M, Fn&& fn) {
   switch (M) {
-    case 32: fn(Shape<32, 8, 4, 1, 8, 4>{}); return true;
-    case 64: fn(Shape<64, 8, 8, 1, 16, 4>{}); return true;
-    case 128: fn(Shape<128, 16, 8, 1, 16, 4>{}); return true;
-    case 256: fn(Shape<256, 8, 8, 4, 16, 4>{}); return true;
-    case 512: fn(Shape<512, 8, 8, 8, 16, 4>{}); return true;
-    case 1024: fn(Shape<1024, 16, 16, 4, 16, 4>{}); return true;
-    case 2048: fn(Shape<2048, 16, 16, 8, 16, 4>{}); return true;
+    case 32: fn(Shape<32, 8, 4, 1, 8>{}); return true;
+    case 64: fn(Shape<64, 8, 8, 1, 16>{}); return true;
+    case 128: fn(Shape<128, 16, 8, 1, 16>{}); return true;
+    case 256: fn(Shape<256, 8, 8, 4, 16>{}); return true;
+    case 512: fn(Shape<512, 8, 8, 8, 16>{}); return true;
+    case 1024: fn(Shape<1024, 16, 16, 4, 16>{}); return true;
+    case 2048: fn(Shape<2048, 16, 16, 8, 16>{}); return true;
     default: return false;
   }
 }
 
 __device__ __forceinline__ constexpr int padded(int i) { return i + (i >> 4); }  // LDS word of exchanged value i
 
-template <int M, int R1, int R2, int R3, int V, int NW, int MODE>
-__global__ __launch_bounds__(64 * NW, 2) void fft_kernel(FftParams P) {
-  using C = FftTile<M, R1, R2, R3, V, NW, MODE>;
+template <int M, int R1, int R2, int R3, int V, int MODE>
+__global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
+  using C = FftTile<M, R1, R2, R3, V, MODE>;
   constexpr int RL = C::RL, H = C::H, TPF = C::TPF, NBL = C::NBL;
   static_assert(R1 * R2 * R3 == M && V % R1 == 0 && V % R2 == 0 && NBL % 2 == 0 && RL % 2 == 0, "pass shape");
   static_assert(R3 == 1 || TPF % R1 == 0, "the middle pass shares one set of twiddles");
@@ -290,8 +341,9 @@ __global__ __launch_bounds__(64 * NW, 2) void fft_kernel(FftParams P) {
   // this lane's frame in a step, and its place in the frame
   const int first = TPF >= 64 ? wave / (TPF / 64 > 0 ? TPF / 64 : 1) : wave * (64 / TPF) + lane / TPF;
   const int lt = TPF >= 64 ? (wave % (TPF / 64 > 0 ? TPF / 64 : 1)) * 64 + lane : lane % TPF;
+  const int n_wave = blockDim.x >> 6, FPWG = 64 * n_wave / TPF;  // frames per step
   const int TF = 1 << P.lg_tf, L = (int)P.g.L, T = P.g.T;
-  const int iters = TF / C::FPWG;
+  const int iters = TF / FPWG;
   // a frame inside one wave needs no barrier between its passes: the wave's LDS accesses complete in order
   auto fence = [] {
     if constexpr (TPF > 64)
@@ -299,9 +351,20 @@ __global__ __launch_bounds__(64 * NW, 2) void fft_kernel(FftParams P) {
     else
       wave_fence();
   };
-  // contiguous tiles per workgroup: frames that overlap, and output lines that neighbouring tiles share, meet in one L2
-  const long long lo = P.n_tiles * blockIdx.x / gridDim.x, hi = P.n_tiles * (blockIdx.x + 1) / gridDim.x;
+  // Workgroup ids are dealt round-robin to the 8 XCDs.  An XCD's workgroups take neighbouring tiles at the same time, so that the
+  // samples their frames share, and the output lines that a tile begins and its neighbour ends, meet in one L2 while they are there.
+  const long long per_xcd = (P.n_tiles + 7) >> 3, lo = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  const long long hi = ((blockIdx.x & 7) + 1) * per_xcd < P.n_tiles ? ((blockIdx.x & 7) + 1) * per_xcd : P.n_tiles;
+  const int stride = gridDim.x >> 3;  // tiles from one of this workgroup's to its next
   if (lo >= hi) return;
+  int4* mel = reinterpret_cast<int4*>(tile + P.mel_lds);
+  float4* melw = reinterpret_cast<float4*>(mel + P.n_mels);
+  if constexpr (MODE == FFT_MODE_MEL) {
+    if (P.mel_lds) {  // (every wave is past this when it meets the others at the end of its first tile)
+      for (int i = tid; i < P.n_mels; i += blockDim.x) mel[i] = P.mel[i];
+      for (int i = tid; i < P.mel_quads; i += blockDim.x) melw[i] = P.melw[i];
+    }
+  }
   long long b0 = (unsigned long long)(lo << P.lg_tf) / (unsigned)T;  // waveform and frame of the tile's first frame
   int t0 = (int)((lo << P.lg_tf) - b0 * T);
   long long b;  // ... of this lane's next frame
@@ -338,7 +401,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fft_kernel(FftParams P) {
   }
 
   cplx z[V];  // samples of the frame that comes next
-  auto load_next = [&] {
+  auto load_next = [&](int advance) {  // `advance`: frames to the one after it
     const bool past = b >= P.g.B;  // behind the last frame: that frame again, never written
     const int i0 = (past ? T - 1 : t) * P.g.hop - P.g.pad;
     const float* __restrict__ xb = P.g.x + (past ? P.g.B - 1 : b) * P.g.L;
@@ -352,22 +415,73 @@ __global__ __launch_bounds__(64 * NW, 2) void fft_kernel(FftParams P) {
         z[i] = {xb[reflect(m, L)], xb[reflect(m + 1, L)]};
       }
     }
-    t += C::FPWG;
+    t += advance;
     if (t >= T) {
       const int q = t - T < T ? 1 : t / T;
       t -= q * T;
       b += q;
     }
   };
-  load_next();
+  const int to_next = ((stride - 1) << P.lg_tf) + FPWG;  // from a tile's last step to the next tile's first
+  load_next(iters > 1 ? FPWG : to_next);
+  // The tile before this one is written out (or taken to Mel bands) a part after every step, while the stores of the parts
+  // before are on their way: a step of its own for it, between two barriers, had all the chip's workgroups computing and then
+  // all of them storing (1,770 x 176,400 samples: 2.20 ms).
+  long long pb0 = 0, p_left = 0;
+  int pt0 = 0;
+  // Waves whose frames are their own wait for each other through two counters, of the waves' tiles computed and of their tiles
+  // written out, and only for what they are about to touch: a wave may be a step ahead of another.  Meeting at a barrier once a
+  // tile keeps them all in the same pass, on the same pipe (1,770 x 176,400 samples, without any output: 1.22 ms against 0.82).
+  int* const computed = reinterpret_cast<int*>(tile + P.sync_word);
+  int* const written = computed + 1;
+  if (tid < 2) computed[tid] = 0;
+  __syncthreads();
+  auto signal = [&](int* counter) {
+    wave_fence();
+    if (lane == 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  auto wait = [&](const int* counter, int until) {
+    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < until) __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  };
+  constexpr bool FLAGS = TPF <= 64;
+  // written out in the first steps of the next tile, so that no wave waits for another's last one
+  const int lg_parts = iters > 1 ? 30 - __builtin_clz(iters) : 0, parts = 1 << lg_parts;
+  auto emit = [&](const float* done, int part) {
+    if constexpr (MODE == FFT_MODE_MEL) {
+      if (P.mel_lds)
+        mel_tile(P, mel, melw, done, C::PITCH, P.lg_tf, p_left, pb0, pt0, wave, n_wave, lane, part, lg_parts);
+      else
+        mel_tile(P, P.mel, P.melw, done, C::PITCH, P.lg_tf, p_left, pb0, pt0, wave, n_wave, lane, part, lg_parts);
+      if (P.spec)
+        store_tile<FFT_MODE_MEL>(done, C::PITCH, 0, P.lg_tf, M + 1, P.spec, NNA_OUT_POWER, p_left, pb0, pt0, T, wave, n_wave, lane, part, lg_parts);
+    } else {
+      const int rows = MODE == FFT_MODE_CPLX && P.fmt == NNA_OUT_COMPLEX ? 2 * (M + 1) : M + 1;
+      store_tile<MODE>(done, C::PITCH, C::PLANE, P.lg_tf, rows, P.out, P.fmt, p_left, pb0, pt0, T, wave, n_wave, lane, part, lg_parts);
+    }
+  };
+  [[maybe_unused]] int step = 0;
+  int n_done = 0;  // n_wave times the tiles this wave has computed
 
-  for (long long tile_i = lo; tile_i < hi; ++tile_i) {
+  float *cur = tile, *old = tile + P.buf_words;
+  for (long long tile_i = lo; tile_i < hi; tile_i += stride) {
+    if (FLAGS && n_done > n_wave) wait(written, n_done - n_wave);  // the buffer's last tile
     for (int it = 0; it < iters; ++it) {
-      float* __restrict__ reg = tile + (it * C::FPWG + first) * C::PITCH;
+      // The two waves of a SIMD take the lead in turn.  Left to themselves the older one always has it, and waits for the other at
+      // the end of its tile (1,770 x 176,400 samples: 1.63 -> 1.50 ms).
+      if constexpr (C::WAVES == 8 || TPF > 64) {
+        if ((wave >> 2 ^ step++) & 1)
+          __builtin_amdgcn_s_setprio(1);
+        else
+          __builtin_amdgcn_s_setprio(0);
+      }
+      float* __restrict__ reg = cur + (it * FPWG + first) * C::PITCH;
       cplx a[V];
 #pragma unroll
       for (int i = 0; i < V; ++i) a[i] = {z[i].x * w[i].x, z[i].y * w[i].y};
-      load_next();
+      load_next(it + 2 == iters || iters == 1 ? to_next : FPWG);
+      __builtin_amdgcn_sched_barrier(0);  // (the requests stay in front of the passes: 1.67 -> 1.51 ms)
       // pass 1
 #pragma unroll
       for (int p = 0; p < V / R1; ++p) {
@@ -469,20 +583,31 @@ __global__ __launch_bounds__(64 * NW, 2) void fft_kernel(FftParams P) {
       if constexpr (MODE == FFT_MODE_MEL) {
         if (lt < 3) reg[M + 1 + lt] = 0.f;  // bins a band's last quad of weights may pad into
       }
+      // the next frame's samples, requested at the start of this step, are waited for here: behind the stores below the wait would
+      // be for those too
+#pragma unroll
+      for (int i = 0; i < V; ++i) asm volatile("" : "+v"(z[i].x), "+v"(z[i].y));
+      if (p_left > 0 && it < parts) {
+        if (FLAGS && it == 0) wait(computed, n_done);
+        emit(old, it);
+        if (FLAGS && it == parts - 1) signal(written);
+      }
     }
-    __syncthreads();
-    const long long n_left = P.g.n_frames - (tile_i << P.lg_tf);
-    if constexpr (MODE == FFT_MODE_MEL) {
-      mel_tile(P, tile, C::PITCH, P.lg_tf, n_left, b0, t0, wave, NW, lane);
-      if (P.spec)
-        store_tile<FFT_MODE_POWER>(tile, C::PITCH, 0, P.lg_tf, M + 1, P.spec, NNA_OUT_POWER, n_left, b0, t0, T, wave, NW, lane);
-    } else {
-      const int rows = MODE == FFT_MODE_CPLX && P.fmt == NNA_OUT_COMPLEX ? 2 * (M + 1) : M + 1;
-      store_tile<MODE>(tile, C::PITCH, C::PLANE, P.lg_tf, rows, P.out, P.fmt, n_left, b0, t0, T, wave, NW, lane);
-    }
-    __syncthreads();
-    frame_of(TF, b0, t0, T, b0, t0);
+    n_done += n_wave;
+    if (FLAGS)
+      signal(computed);
+    else
+      __syncthreads();  // this tile is complete, and the one before it written out
+    pb0 = b0;
+    pt0 = t0;
+    p_left = P.g.n_frames - (tile_i << P.lg_tf);
+    float* const swap = cur;
+    cur = old;
+    old = swap;
+    frame_of(stride << P.lg_tf, b0, t0, T, b0, t0);
   }
+  if (FLAGS) wait(computed, n_done);
+  for (int it = 0; it < parts; ++it) emit(old, it);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -578,12 +703,12 @@ __global__ __launch_bounds__(256, 2) void fft_general_kernel(FftParams P) {
     }
     __syncthreads();
     if constexpr (MODE == FFT_MODE_MEL) {
-      mel_tile(P, tile, pitch, P.lg_tf, P.g.n_frames - f0, b0, t0, wave, nw, lane);
+      mel_tile(P, P.mel, P.melw, tile, pitch, P.lg_tf, P.g.n_frames - f0, b0, t0, wave, nw, lane, 0, 0);
       if (P.spec)
-        store_tile<FFT_MODE_POWER>(tile, pitch, 0, P.lg_tf, M + 1, P.spec, NNA_OUT_POWER, P.g.n_frames - f0, b0, t0, T, wave, nw, lane);
+        store_tile<FFT_MODE_MEL>(tile, pitch, 0, P.lg_tf, M + 1, P.spec, NNA_OUT_POWER, P.g.n_frames - f0, b0, t0, T, wave, nw, lane, 0, 0);
     } else {
       const int rows = MODE == FFT_MODE_CPLX && P.fmt == NNA_OUT_COMPLEX ? 2 * (M + 1) : M + 1;
-      store_tile<MODE>(tile, pitch, M + 1, P.lg_tf, rows, P.out, P.fmt, P.g.n_frames - f0, b0, t0, T, wave, nw, lane);
+      store_tile<MODE>(tile, pitch, M + 1, P.lg_tf, rows, P.out, P.fmt, P.g.n_frames - f0, b0, t0, T, wave, nw, lane, 0, 0);
     }
     __syncthreads();
   }
@@ -603,11 +728,27 @@ void shape_launch(FftParams& P, int frames_per_step, int max_iters) {
 template <typename S, int MODE>
 hipError_t launch_fixed(FftParams& P, hipStream_t stream) {
   using C = typename S::template Tile<MODE>;
-  shape_launch(P, C::FPWG, C::max_steps());
-  const size_t bytes = (size_t)(1 << P.lg_tf) * C::PITCH * 4;
-  const long long grid = std::min<long long>(P.n_tiles, 512);
+  // a batch too short for every CU to take a step spreads over twice as many in workgroups of half the size
+  const int n_wave = P.g.n_frames > 256LL * C::frames_per_step(4) ? C::WAVES : 4, step = C::frames_per_step(n_wave);
+  const int groups = C::WAVES == 8 ? 256 : 512;
+  // Largest tile whose workgroups are done about as early as with smaller ones
+  auto longest = [&](int steps) { return (P.g.n_frames + (long long)groups * steps * step - 1) / ((long long)groups * steps * step) * steps; };
+  const int tables = MODE == FFT_MODE_MEL ? (P.n_mels + P.mel_quads) * 16 : 0;
+  P.mel_lds = tables > 0 && 2 * step * C::PITCH * 4 + 32 + tables <= C::LDS;
+  int iters = C::max_steps(n_wave, 32 + (P.mel_lds ? tables : 0));
+  while (iters > 1 && 5 * longest(iters) > (iters == 2 ? 7 : 5) * longest(iters / 2)) iters >>= 1;
+  const int tf = step * iters;
+  P.lg_tf = 0;
+  while ((1 << P.lg_tf) < tf) ++P.lg_tf;
+  P.n_tiles = (P.g.n_frames + tf - 1) / tf;
+  const long long grid = std::min<long long>((P.n_tiles + 7) / 8 * 8, groups);
+  const int words = (tf * C::PITCH + 3) & ~3;
+  P.buf_words = P.n_tiles > grid ? words : 0;
+  P.sync_word = words + P.buf_words;
+  if (P.mel_lds) P.mel_lds = P.sync_word + 4;
+  const size_t bytes = (size_t)(P.sync_word + 4) * 4 + (P.mel_lds ? tables : 0);
   clear_stale_error();
-  hipLaunchKernelGGL((fft_kernel<S::M, S::R1, S::R2, S::R3, S::V, S::NW, MODE>), dim3((unsigned)grid), dim3(64 * S::NW), bytes, stream, P);
+  hipLaunchKernelGGL((fft_kernel<S::M, S::R1, S::R2, S::R3, S::V, MODE>), dim3((unsigned)grid), dim3(64 * n_wave), bytes, stream, P);
   return hipGetLastError();
 }
 
@@ -635,8 +776,8 @@ hipError_t allow_lds_mode() {
     with_shape(M, [&](auto s) {
       using S = decltype(s);
       if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(fft_kernel<S::M, S::R1, S::R2, S::R3, S::V, S::NW, MODE>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, S::template Tile<MODE>::LDS_BYTES);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(fft_kernel<S::M, S::R1, S::R2, S::R3, S::V, MODE>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kLdsAll);
     });
   return e;
 }

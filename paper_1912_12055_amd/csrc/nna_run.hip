@@ -143,6 +143,7 @@ nna_status run_stft_core(const nna_plan* plan, int kind, const float* x, long lo
       mode = nna::FFT_MODE_MEL;
       P.mel = reinterpret_cast<const int4*>(plan->d_fft_mel);
       P.melw = reinterpret_cast<const float4*>(plan->d_fft_melw);
+      P.mel_quads = (int)(plan->h_fft_melw.size() / 4);
       P.n_mels = plan->n_mels;
       P.mel_power = plan->mel_power;
     }
