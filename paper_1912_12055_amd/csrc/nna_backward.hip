@@ -59,6 +59,8 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
   std::vector<int2> shift_rng;
   std::vector<int2> tiles;
   std::vector<float> logical;
+  std::vector<int4> few;
+  std::vector<int> few_first;
   try {
     // streaming order <- [row][tap]: the inverse of the layout build_conv_bank writes
     map.assign(plan->bank_floats, -1);
@@ -75,6 +77,43 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
     for (int r = 0; r < rows; ++r) {
       lo[r] = (int)plan->row_s[r];
       hi[r] = (int)plan->row_e[r];
+    }
+    // the steps of 16 taps that launch_cqt_few takes, by row block and 32 columns of the hop
+    const int hop = plan->hop, n_tile = hop / nna::CQW_COLS;
+    if (plan->tap_stride == hop && plan->row_step == 1 && hop % nna::CQW_COLS == 0) {
+      struct Run { int frag, j, n; };  // of one chunk of 16 columns
+      std::vector<Run> runs((size_t)plan->n_rb * 2 * n_tile, Run{0, 0, 0});
+      bool ok = true;
+      for (int rb = 0; rb < plan->n_rb; ++rb)
+        plan->few_jspan = std::max(plan->few_jspan, (hi[rb * CQ_ROWS] + hop - 1) / hop - lo[rb * CQ_ROWS] / hop);
+      for_each_cqt_fragment(plan, [&](long long f, int rb, int j, int c0, bool real) {
+        if (!real) return;
+        Run& r = runs[(size_t)rb * 2 * n_tile + c0 / 16];
+        if (r.n++ == 0) {
+          r.frag = (int)f;
+          r.j = j - lo[rb * CQ_ROWS] / hop;
+        }
+        ok = ok && f == r.frag + r.n - 1 && r.j >= 0 && r.j + r.n <= plan->few_jspan && f < INT_MAX;
+      });
+      int4 pair = make_int4(0, 0, 0, 0);
+      bool half = false;
+      auto push = [&](int frag, int word) {
+        (half ? pair.z : pair.x) = frag;
+        (half ? pair.w : pair.y) = word;
+        if (half) few.push_back(pair);
+        half = !half;
+      };
+      for (int rb = 0; rb < plan->n_rb && ok; ++rb)
+        for (int t = 0; t <= n_tile; ++t) {
+          few_first.push_back((int)few.size());
+          for (int c = 2 * t; c < 2 * t + 2 && t < n_tile; ++c) {
+            const Run& r = runs[(size_t)rb * 2 * n_tile + c];
+            for (int i = 0; i < r.n; i += 4) push(r.frag + i, ((r.j + i) * nna::CQW_PITCH + 16 * (c & 1)) << 3 | std::min(r.n - i, 4));
+          }
+          if (half) push(0, 0);
+        }
+      for (int i = 0; i < 4; ++i) push(0, 0);  // read ahead, never taken
+      if (!ok) few.clear();  // (a block's longest kernel does not span the others)
     }
     // bank gradient: output tiles (128 rows x 128 taps) that hold a parameter
     for (int mt = 0; mt < rows_pad / nna::BW_MT; ++mt) {
@@ -132,9 +171,9 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
   } catch (const std::bad_alloc&) {
     return fail(NNA_ERR_ALLOC, "out of host memory");
   }
-  // cqt_few_kernel's time goes by frames times all steps of 16 taps, cqt_kernel's, while its workgroups are fewer than the chip holds,
-  // by the longest workgroup's steps.  Training step over cqt_kernel's by frames x steps / longest (22.05 kHz, 60 and 120 bins, hops
-  // 256 and 512, MI355X): 0.40 .. 0.58 at 10,000, 0.73 .. 0.86 at 22,000 .. 25,000, 0.85 at 33,000, 1.05 at 37,000.
+  // launch_cqt_few's time goes by frames times all steps of 16 taps, cqt_kernel's, while its workgroups are fewer than the chip holds,
+  // by the longest workgroup's steps.  Training step over cqt_kernel's by frames x steps / longest (MI355X): 84 bins, hop 512: 0.71 at
+  // 28,000, 0.88 at 46,000, 1.13 at 69,000; 120 bins, hop 256: 0.98 at 97,000, 1.11 at 194,000.
   long long steps = 0, longest = 1;
   for (const nna::CqtItem& item : plan->h_items) {
     long long sum = 0;
@@ -142,7 +181,7 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
     steps += sum;
     longest = std::max(longest, sum);
   }
-  plan->few_frames = 34000 * longest / std::max(1LL, steps);
+  plan->few_frames = 50000 * longest / std::max(1LL, steps);
   plan->rows_pad = rows_pad;
   plan->kp = kp;
   float* d_logical = nullptr;
@@ -151,6 +190,8 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
   if (s == NNA_OK) s = upload(&plan->d_cq_map, map.data(), map.size() * sizeof(int), "bank index map");
   if (s == NNA_OK) s = upload(&plan->d_row_lo, lo.data(), lo.size() * sizeof(int), "row supports");
   if (s == NNA_OK) s = upload(&plan->d_row_hi, hi.data(), hi.size() * sizeof(int), "row supports");
+  if (s == NNA_OK && !few.empty()) s = upload(&plan->d_few_groups, few.data(), few.size() * sizeof(int4), "step table");
+  if (s == NNA_OK && !few.empty()) s = upload(&plan->d_few_first, few_first.data(), few_first.size() * sizeof(int), "step table");
   if (s == NNA_OK) s = upload(&plan->d_bw_tiles, tiles.data(), tiles.size() * sizeof(int2), "gradient tile list");
   if (s == NNA_OK) s = upload(&plan->d_shift_rng, shift_rng.data(), shift_rng.size() * sizeof(int2), "hop-shift table");
   if (s == NNA_OK) s = upload(&d_logical, logical.data(), logical.size() * sizeof(float), "kernel bank");
@@ -165,6 +206,10 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
     (void)hipFree(plan->d_wrm);
     (void)hipFree(plan->d_cq_map);
     (void)hipFree(plan->d_row_lo);
+    (void)hipFree(plan->d_few_groups);
+    (void)hipFree(plan->d_few_first);
+    plan->d_few_groups = nullptr;
+    plan->d_few_first = nullptr;
     (void)hipFree(plan->d_row_hi);
     (void)hipFree(plan->d_bw_tiles);
     (void)hipFree(plan->d_shift_rng);

@@ -226,6 +226,9 @@ struct nna_plan {
   long long few_frames = 0;  // frames below which launch_conv takes the kernel for batches of few workgroups
   int* d_cq_map = nullptr;
   int* d_row_lo = nullptr;
+  int4* d_few_groups = nullptr;  // launch_cqt_few's tables, or NULL
+  int* d_few_first = nullptr;
+  int few_jspan = 0;             // hop-blocks the longest row block spans
   int* d_row_hi = nullptr;
   int2* d_bw_tiles = nullptr;
   int n_bw_tiles = 0;

@@ -460,8 +460,13 @@ struct FirParams {
 };
 hipError_t launch_fir_decimate(const FirParams& p, hipStream_t stream);
 hipError_t launch_cqt(const CqtParams& p, hipStream_t stream);
-// ... for batches of few workgroups; rows [row_lo, row_hi) hold taps
-hipError_t launch_cqt_few(const CqtParams& p, const int* row_lo, const int* row_hi, hipStream_t stream);
+// ... for batches of few workgroups; rows [row_lo, row_hi) hold taps.  With `groups` (kernels and frames share a grid of hops): runs of
+// up to four steps of 16 taps on consecutive shifts, two to an int4: first bank fragment, then LDS word of its samples in frame 0's
+// row << 3 | steps.  first[row block][hop / 32 + 1]: the first pair of every 32 columns of the hop.  `lds_rows`: rows of a hop in an
+// LDS tile (0: more than fit)
+constexpr int CQW_FRAMES = 64, CQW_COLS = 32, CQW_PITCH = CQW_COLS + 4, CQW_PASSES = 9;
+constexpr int CQW_ROWS = 80 * 1024 / (2 * CQW_PITCH * 4) - 2;  // two tiles in half a CU's LDS, and what a run's missing steps read
+hipError_t launch_cqt_few(const CqtParams& p, const int* row_lo, const int* row_hi, const int4* groups, const int* first, int lds_rows, hipStream_t stream);
 hipError_t launch_cqt_fold(const CqfParams& p, hipStream_t stream);
 hipError_t cqf_kernels_init();  // per-process function attributes of nna_kernels_cqf.hip
 size_t cqt_launch_lds_bytes(int n_chunks, int lds_rows);  // dynamic LDS launch_cqt asks for (limit: 160 KB)

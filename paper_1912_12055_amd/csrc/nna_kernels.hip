@@ -738,11 +738,11 @@ __global__ __launch_bounds__(256, 2) void cqt_kernel(const CqtParams P) {
 // Both operands go from memory to registers in MFMA layout, eight steps of 16 taps ahead: weights as cqt_kernel streams them (from
 // the row-major bank, whose rows lie a power of two apart, sixteen requests met in one L2 channel: 210 us), the same for the
 // workgroup's four waves; samples 64 bytes of sixteen frames, all but one of them lines of
-// the step before.  Bound by the chain of dependent matrix instructions, 140 cycles a step.
-// 16 x 88,200 samples, 84 bins of up to 11,341 taps (MI355X): 33 workgroups 413 us -> 484 workgroups 172 us.
+// the step before.  16 x 88,200 samples, 84 bins of up to 11,341 taps (MI355X): 33 workgroups 413 us -> 484 workgroups 172 us.
+// (Where hops, frames and kernels share one grid, the kernel after this one runs.)
 // ---------------------------------------------------------------------------------------
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
-constexpr int CQW_FRAMES = 64, CQW_AHEAD = 8;
+constexpr int CQW_AHEAD = 8;
 
 template <bool GRAD>
 __global__ __launch_bounds__(256, 2) void cqt_few_kernel(const CqtParams P, const int* __restrict__ row_lo, const int* __restrict__ row_hi) {
@@ -835,6 +835,168 @@ __global__ __launch_bounds__(256, 2) void cqt_few_kernel(const CqtParams P, cons
   else sweep(std::integral_constant<bool, false>{});
   if (fi >= g.n_frames) return;
   const int bin0 = rb * (CQ_ROWS / 2) + 2 * q;
+  if constexpr (GRAD)
+    cqt_grad_bins(P, acc, bin0, f);
+  else
+    cqt_store_bins(P, acc, bin0, P.out + b * P.out_wave_stride + (long long)P.row_offset * g.T + (f - b * g.T));
+}
+
+// ---------------------------------------------------------------------------------------
+// The same where hops, frames and kernels share one grid: 32 columns of the tile's hops at a time in LDS, where row t + j serves frame
+// t at shift j.  Read straight from the waveform, sixteen hops a request, every one of them lies in the same one or two channels of the
+// L2 (hop 512: 2 KB apart), once per shift: 580 cycles a step of the longest chain.  Weights as above, eight steps ahead, from a table of
+// runs of four steps: what a step does besides its four matrix instructions is time in their chain.
+// Bound by the chain of dependent matrix instructions of the longest kernels.  16 x 88,200 samples, 84 bins (MI355X): 172 -> 90 us;
+// 1 x 31,011, 60 bins at hop 256, training step: 357 -> 181 us.
+// ---------------------------------------------------------------------------------------
+template <bool GRAD>
+__global__ __launch_bounds__(256, 2) void cqt_few_tile_kernel(const CqtParams P, const int* __restrict__ row_lo, const int* __restrict__ row_hi,
+                                                              const int4* __restrict__ groups, const int* __restrict__ first_pair, int lds_rows) {
+  extern __shared__ __attribute__((aligned(16))) float few_lds[];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q = lane >> 4, n = lane & 15;
+  const FrameGeom& g = P.g;
+  const long long n_ft = (g.n_frames + CQW_FRAMES - 1) / CQW_FRAMES;
+  const int rb = (int)(blockIdx.x / n_ft);  // longest kernels first
+  const long long f0 = (blockIdx.x - rb * n_ft) * CQW_FRAMES;
+  const int m_valid = (int)(g.n_frames - f0 < CQW_FRAMES ? g.n_frames - f0 : CQW_FRAMES);
+  const int L = (int)g.L, hop = g.hop, n_tile = hop / CQW_COLS;
+  const int j_first = row_lo[rb * CQ_ROWS] / hop;
+  TileMap tm;
+  tm.T = g.T;
+  tm.b0 = f0 / g.T;
+  tm.t0 = (int)(f0 - tm.b0 * g.T);
+  tm.n0 = g.T - tm.t0 < m_valid ? g.T - tm.t0 : m_valid;
+  tm.extra = (row_hi[rb * CQ_ROWS] + hop - 1) / hop - j_first - 1;
+  const int rows_used = tm.frame_row(m_valid - 1) + tm.extra + 1;
+  const int* __restrict__ first = first_pair + (long long)rb * (n_tile + 1);
+
+  // ---- the samples: four columns of a row per thread and pass
+  constexpr int V = CQW_COLS / 4, RPP = 256 / V;
+  const int cv = tid % V, r0 = tid / V;
+  const float* xb[CQW_PASSES];
+  int pos[CQW_PASSES];
+#pragma unroll
+  for (int p = 0; p < CQW_PASSES; ++p) {
+    const int row = p * RPP + r0;
+    long long b;
+    int sigma;
+    tm.decode(row < rows_used ? row : rows_used - 1, b, sigma);
+    xb[p] = g.x + b * g.L;
+    pos[p] = (sigma + j_first) * hop - g.pad + 4 * cv;
+  }
+  // four samples on one side of either end are a stored run, read backwards behind an end; a run that straddles an end (only when
+  // L, the hop or the padding are not multiples of 4) is read again, sample by sample, when the tile is written
+  f32x4 R[CQW_PASSES];
+  unsigned rev = 0;
+  bool gen = false;
+  auto request = [&](int c) {
+    rev = 0;
+    gen = false;
+#pragma unroll
+    for (int p = 0; p < CQW_PASSES; ++p)
+      if (p * RPP < rows_used) {
+        const int s = pos[p] + c;
+        const int src = s < 0 ? -s - 3 : s > L - 4 ? 2 * (L - 1) - s - 3 : s;
+        rev |= (src != s ? 1u : 0u) << p;
+        gen |= (unsigned)src > (unsigned)(L - 4);
+        R[p] = *reinterpret_cast<const f32x4_u*>(xb[p] + (src < 0 ? 0 : src > L - 4 ? L - 4 : src));
+      }
+  };
+  auto store = [&](int c, float* dst) {
+    dst += r0 * CQW_PITCH + 4 * cv;
+#pragma unroll
+    for (int p = 0; p < CQW_PASSES; ++p)
+      if (p * RPP + r0 < rows_used) {
+        const f32x4 v = R[p];
+        const bool r = (rev >> p) & 1u;
+        *reinterpret_cast<f32x4*>(dst + p * RPP * CQW_PITCH) = (f32x4){r ? v.w : v.x, r ? v.z : v.y, r ? v.y : v.z, r ? v.x : v.w};
+      }
+    if (__builtin_amdgcn_ballot_w64(gen) == 0) return;
+#pragma unroll 1
+    for (int row = r0; row < rows_used; row += RPP) {
+      long long b;
+      int sigma;
+      tm.decode(row, b, sigma);
+      const float* __restrict__ x = g.x + b * g.L;
+      const int s = (sigma + j_first) * hop - g.pad + 4 * cv + c;
+      const int src = s < 0 ? -s - 3 : s > L - 4 ? 2 * (L - 1) - s - 3 : s;
+      if ((unsigned)src > (unsigned)(L - 4))
+        for (int e = 0; e < 4; ++e) dst[(row - r0) * CQW_PITCH + e] = x[reflect_clamped(s + e, L)];
+    }
+  };
+
+  // ---- two groups of up to four steps a turn; the weights are requested a turn ahead, the samples a group ahead
+  const float4* __restrict__ wp = P.bank + lane;
+  auto fetch_w = [&](int frag, f32x4 (&w)[4]) {
+    const float4* __restrict__ p = wp + (long long)frag * 64;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) w[u] = *reinterpret_cast<const f32x4*>(p + u * 64);
+  };
+  auto next_tile = [&](int t) {  // the next one that holds steps, or n_tile
+    while (t < n_tile && first[t] == first[t + 1]) ++t;
+    return t;
+  };
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](int steps, const f32x4 (&w)[4], const f32x4 (&x)[4]) {
+    if (steps == 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][k], x[u][k], acc, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (u < steps) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][k], x[u][k], acc, 0, 0, 0);
+        }
+    }
+  };
+  int t = next_tile(0);
+  if (t < n_tile) {
+    const bool valid = wave * 16 + n < m_valid;
+    const int x_off = (valid ? tm.frame_row(wave * 16 + n) : 0) * CQW_PITCH + 4 * q;
+    int i = first[0], buf = 0;
+    int4 cur = groups[i], nxt = groups[i + 1];
+    f32x4 w0[4], w1[4], x0[4], x1[4];
+    request(t * CQW_COLS);
+    fetch_w(cur.x, w0);
+    fetch_w(cur.z, w1);
+    while (t < n_tile) {
+      const float* tile = few_lds + buf * lds_rows * CQW_PITCH;
+      store(t * CQW_COLS, few_lds + buf * lds_rows * CQW_PITCH);
+      buf ^= 1;
+      __syncthreads();  // also: every wave has read the tile before last
+      const int end = first[t + 1];
+      t = next_tile(t + 1);
+      if (t < n_tile) request(t * CQW_COLS);
+      auto fetch_x = [&](int word, f32x4 (&x)[4]) {  // (a group's missing steps: rows behind the tile's, in the LDS all the same)
+        const float* p = tile + x_off + (word >> 3);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const f32x4*>(p + u * CQW_PITCH);
+      };
+      fetch_x(cur.y, x0);
+      for (; i < end; ++i) {
+        const int4 after = groups[i + 2];
+        fetch_x(cur.w, x1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(cur.y & 7, w0, x0);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_w(nxt.x, w0);
+        fetch_x(nxt.y, x0);  // (behind the tile's last turn: read again from the next tile)
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(cur.w & 7, w1, x1);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_w(nxt.z, w1);
+        cur = nxt;
+        nxt = after;
+      }
+    }
+  }
+  const long long f = f0 + wave * 16 + n;
+  if (f >= g.n_frames) return;
+  const int bin0 = rb * (CQ_ROWS / 2) + 2 * q;
+  const long long b = f / g.T;
   if constexpr (GRAD)
     cqt_grad_bins(P, acc, bin0, f);
   else
@@ -945,7 +1107,8 @@ size_t cqt_launch_lds_bytes(int n_chunks, int lds_rows) {
 }
 
 hipError_t kernels_init() {
-  const void* kernels[] = {reinterpret_cast<const void*>(cqt_kernel<false>), reinterpret_cast<const void*>(cqt_kernel<true>)};
+  const void* kernels[] = {reinterpret_cast<const void*>(cqt_kernel<false>), reinterpret_cast<const void*>(cqt_kernel<true>),
+                           reinterpret_cast<const void*>(cqt_few_tile_kernel<false>), reinterpret_cast<const void*>(cqt_few_tile_kernel<true>)};
   for (const void* k : kernels) {
     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CQ_DYN_LDS_MAX);
     if (e != hipSuccess) return e;
@@ -1005,14 +1168,23 @@ hipError_t launch_fir_decimate(const FirParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_cqt_few(const CqtParams& p, const int* row_lo, const int* row_hi, hipStream_t stream) {
+hipError_t launch_cqt_few(const CqtParams& p, const int* row_lo, const int* row_hi, const int4* groups, const int* first, int lds_rows,
+                          hipStream_t stream) {
   clear_stale_error();
   const long long blocks = (p.g.n_frames + CQW_FRAMES - 1) / CQW_FRAMES * ((2LL * p.n_bins + CQ_ROWS - 1) / CQ_ROWS);
   if (blocks <= 0 || blocks > 0x7fffffffLL || (p.gbuf && (!p.gout || p.rows_pad < 2 * p.n_bins))) return hipErrorInvalidValue;
-  if (p.gbuf)
+  if (groups && first && lds_rows > 0) {
+    if (lds_rows > CQW_ROWS || lds_rows > CQW_PASSES * 32 || p.tap_stride != p.g.hop || p.row_step != 1 || p.g.hop % CQW_COLS) return hipErrorInvalidValue;
+    const size_t lds = (2ull * lds_rows + 4) * CQW_PITCH * sizeof(float);
+    if (p.gbuf)
+      hipLaunchKernelGGL(cqt_few_tile_kernel<true>, dim3((unsigned)blocks), dim3(256), lds, stream, p, row_lo, row_hi, groups, first, lds_rows);
+    else
+      hipLaunchKernelGGL(cqt_few_tile_kernel<false>, dim3((unsigned)blocks), dim3(256), lds, stream, p, row_lo, row_hi, groups, first, lds_rows);
+  } else if (p.gbuf) {
     hipLaunchKernelGGL(cqt_few_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, p, row_lo, row_hi);
-  else
+  } else {
     hipLaunchKernelGGL(cqt_few_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, p, row_lo, row_hi);
+  }
   return hipGetLastError();
 }
 

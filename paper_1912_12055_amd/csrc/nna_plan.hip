@@ -943,6 +943,8 @@ void nna_plan_destroy(nna_plan* plan) {
       (void)hipFree(plan->d_lsupport);
       (void)hipFree(plan->d_cq_map);
       (void)hipFree(plan->d_row_lo);
+      (void)hipFree(plan->d_few_groups);
+      (void)hipFree(plan->d_few_first);
       (void)hipFree(plan->d_row_hi);
       (void)hipFree(plan->d_bw_tiles);
       (void)hipFree(plan->d_shift_rng);

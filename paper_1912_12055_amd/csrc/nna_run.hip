@@ -404,7 +404,10 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
 }
 
 hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t stream) {
-  if (sub->d_wrm && P.g.n_frames < sub->few_frames) return nna::launch_cqt_few(P, sub->d_row_lo, sub->d_row_hi, stream);
+  if (sub->d_wrm && P.g.n_frames < sub->few_frames) {
+    const long long T = P.g.T, rows = nna::CQW_FRAMES + (1 + (nna::CQW_FRAMES - 1 + T - 1) / T) * (sub->few_jspan - 1);
+    return nna::launch_cqt_few(P, sub->d_row_lo, sub->d_row_hi, sub->d_few_groups, sub->d_few_first, rows <= nna::CQW_ROWS ? (int)rows : 0, stream);
+  }
   return nna::launch_cqt(P, stream);
 }
 
