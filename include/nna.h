@@ -379,6 +379,23 @@ nna_status nna_cqt_backward(const nna_plan* plan, const float* x_dev, long long 
                             size_t workspace_bytes, void* hip_stream);
 
 /*
+ * A training step whose backward pass need not compute C = W x again: the forward pass writes it to kept_dev beside its output.
+ * For plans from nna_plan_stft (power format), nna_plan_mel (power 2) and nna_plan_cqt (every format but NNA_OUT_COMPLEX) made
+ * trainable; results are those of nna_stft / nna_mel_with_stft / nna_cqt and their backward calls.
+ *   nna_kept_bytes     size of kept_dev (bank rows padded to 128 x padded frames x 4); 0: this plan's calls keep nothing.
+ *   nna_forward_keep   as nna_stft, nna_cqt or (spec_dev not NULL, Mel plans only) nna_mel_with_stft, and kept_dev (256-byte aligned).
+ *   nna_backward_kept  as the plan's backward call with the same workspace; kept_dev from the forward pass of the same x_dev and
+ *                      bank, unchanged by the call.  gmelw_dev: Mel plans only.
+ * Errors as for those calls; NNA_ERR_UNSUPPORTED where nna_kept_bytes is 0.
+ */
+nna_status nna_kept_bytes(const nna_plan* plan, long long B, long long L, size_t* bytes);
+nna_status nna_forward_keep(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev, float* spec_dev,
+                            void* kept_dev, size_t kept_bytes, void* hip_stream);
+nna_status nna_backward_kept(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
+                             const void* kept_dev, size_t kept_bytes, float* gmelw_dev, float* gw_dev, float* gx_dev,
+                             void* workspace_dev, size_t workspace_bytes, void* hip_stream);
+
+/*
  * Trainable kernels of the downsampling CQT with time-domain kernels (Sec. IV-C; the `trainable` argument of the
  * paper's CQT2010v2 layer, Sec. III-C "Downsampling"): nna_plan_trainable also accepts plans from
  * nna_plan_cqt2010v2.  The layer has ONE weight, the top octave's kernels W[2 n_top, n_taps] (n_top =

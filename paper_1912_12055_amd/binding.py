@@ -34,7 +34,7 @@ EXPORTS = [
     "nna_cqt_backward_workspace", "nna_cqt_backward", "nna_mel_with_stft", "nna_cqt2010v2_static",
     "nna_cqt2010v2_backward_workspace", "nna_cqt2010v2_backward",
     "nna_plan_get_spectral_kernels", "nna_plan_set_spectral_kernels", "nna_cqt1992_backward_workspace", "nna_cqt1992_backward",
-    "nna_cqt2010_backward_workspace", "nna_cqt2010_backward", "nna_plan_applied_kernels", "nna_plan_applied_tiles",
+    "nna_cqt2010_backward_workspace", "nna_cqt2010_backward", "nna_kept_bytes", "nna_forward_keep", "nna_backward_kept", "nna_plan_applied_kernels", "nna_plan_applied_tiles",
     "nna_plan_destroy",
     "nna_status_str", "nna_last_error",
 ]
@@ -100,6 +100,9 @@ def lib():
         L.nna_stft_backward.argtypes = [_VP, _VP, _LL, _LL, _VP, _VP, _VP, _VP, _c.c_size_t, _VP]
         L.nna_cqt_backward_workspace.argtypes = [_VP, _LL, _LL, _c.POINTER(_c.c_size_t)]
         L.nna_cqt_backward.argtypes = [_VP, _VP, _LL, _LL, _VP, _VP, _VP, _VP, _c.c_size_t, _VP]
+        L.nna_kept_bytes.argtypes = [_VP, _LL, _LL, _c.POINTER(_c.c_size_t)]
+        L.nna_forward_keep.argtypes = [_VP, _VP, _LL, _LL, _VP, _VP, _VP, _c.c_size_t, _VP]
+        L.nna_backward_kept.argtypes = [_VP, _VP, _LL, _LL, _VP, _VP, _c.c_size_t, _VP, _VP, _VP, _VP, _c.c_size_t, _VP]
         L.nna_cqt2010v2_backward_workspace.argtypes = [_VP, _LL, _LL, _c.POINTER(_c.c_size_t)]
         L.nna_cqt2010v2_backward.argtypes = [_VP, _VP, _LL, _LL, _VP, _VP, _VP, _VP, _c.c_size_t, _VP]
         L.nna_plan_get_spectral_kernels.argtypes = [_VP, _VP, _VP]
@@ -655,4 +658,50 @@ def nna_mel_backward(plan: Plan, x, gout, want_gmelw=True, want_gw=True, want_gx
                                   gm.data_ptr() if want_gmelw else None, gw.data_ptr() if want_gw else None,
                                   gx.data_ptr() if want_gx else None, workspace.data_ptr(), ws_bytes,
                                   _stream_of(x, stream)))
+    return gm, gw, gx
+
+
+def nna_kept_bytes(plan: Plan, B: int, L: int) -> int:
+    n = _c.c_size_t()
+    _check(lib().nna_kept_bytes(plan.handle, B, L, _c.byref(n)))
+    return n.value
+
+
+def nna_forward_keep(plan: Plan, x, stream=None):
+    """(out, kept): nna_stft, nna_mel or nna_cqt of a trainable plan, and what nna_backward_kept takes instead of computing it again."""
+    import torch
+
+    kept = torch.empty(nna_kept_bytes(plan, *x.shape), dtype=torch.uint8, device=x.device)
+    info, spec = plan.info(), None
+    if info["kind"] == NNA_KIND_MEL:
+        spec = torch.empty((x.shape[0], info["bank_rows"] // 2, nna_out_shape(plan, *x.shape)[1]), dtype=torch.float32, device=x.device)
+
+    def fn(handle, xp, B, L, op, st):
+        return lib().nna_forward_keep(handle, xp, B, L, op, None if spec is None else spec.data_ptr(), kept.data_ptr(), kept.numel(), st)
+
+    return _run(fn, plan, x, None, stream), kept
+
+
+def nna_backward_kept(plan: Plan, x, gout, kept, want_gmelw=False, want_gw=True, want_gx=True, stream=None):
+    """(gWmel or None, gW or None, gx or None), as the plan's backward call, with C from nna_forward_keep(plan, x)."""
+    import torch
+
+    for name, t in (("x", x), ("gout", gout)):
+        if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
+            raise TypeError(f"{name} must be a contiguous float32 CUDA tensor")
+    if x.dim() != 2 or not (kept.is_cuda and kept.is_contiguous() and gout.device == x.device == kept.device):
+        raise TypeError("x must be [B, L], gout and kept contiguous on its device")
+    B, L = x.shape
+    bins, frames = nna_out_shape(plan, B, L)
+    if tuple(gout.shape) != (B, bins, frames):
+        raise TypeError(f"gout must be of shape {(B, bins, frames)}")
+    size = {NNA_KIND_MEL: nna_mel_backward_workspace, NNA_KIND_CQT: nna_cqt_backward_workspace}
+    need = size.get(plan.info()["kind"], nna_stft_backward_workspace)(plan, B, L)
+    workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+    gm = torch.empty(_mel_shape(plan), dtype=torch.float32, device=x.device) if want_gmelw else None
+    gw = torch.empty(_bank_shape(plan), dtype=torch.float32, device=x.device) if want_gw else None
+    gx = torch.empty_like(x) if want_gx else None
+    _check(lib().nna_backward_kept(plan.handle, x.data_ptr(), B, L, gout.data_ptr(), kept.data_ptr(), kept.numel() * kept.element_size(),
+                                   gm.data_ptr() if want_gmelw else None, gw.data_ptr() if want_gw else None,
+                                   gx.data_ptr() if want_gx else None, workspace.data_ptr(), need, _stream_of(x, stream)))
     return gm, gw, gx

@@ -467,10 +467,11 @@ nna_status nna_stft_backward_workspace(const nna_plan* plan, long long B, long l
 // The backward pass of the STFT stage: gout[B, out_bins, T] is the gradient with respect to the stage's
 // output in format `fmt`; gbuf holds G (rows_pad x padded frames floats).  Arguments already checked.
 // pout (optional, magnitude / power formats): the stage's own output is written there on the way.
-// With gw_dev and gx_dev both NULL only G (and pout) are produced.
+// With gw_dev and gx_dev both NULL only G (and pout) are produced.  kept (optional): C from the forward pass, in G's order.
 static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, long long B, long long L, long long T,
                                      const float* gout_dev, int fmt, int out_bins, float* gw_dev, float* gx_dev,
-                                     float* gbuf, void* hip_stream, float* pout = nullptr, bool zero_gw = true) {
+                                     float* gbuf, void* hip_stream, float* pout = nullptr, bool zero_gw = true,
+                                     const float* kept = nullptr) {
   const int M = pick_tile_frames(ST_FRAMES, T, plan->nj - 1, ST_LDS_ROWS);
   if (M < 1) return fail(NNA_ERR_UNSUPPORTED, "frame tile does not fit in LDS");
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
@@ -481,8 +482,7 @@ static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, l
   const long long n_frames = B * T, gpitch = bw_gpitch(n_frames);
   const int packed = plan->freq_scale ? 0 : 1;
   // 1. G = dLoss/dC: the forward contraction again, its epilogue turned into the output format's derivative
-  e = nna::launch_fill_zero_frames(gbuf, plan->rows_pad, n_frames, gpitch, stream);
-  if (e != hipSuccess) return fail_hip(e, "kernel launch");
+  if (!kept && (e = nna::launch_fill_zero_frames(gbuf, plan->rows_pad, n_frames, gpitch, stream)) != hipSuccess) return fail_hip(e, "kernel launch");
   nna::StftParams P;
   std::memset(&P, 0, sizeof(P));
   P.g = make_geom(plan, x_dev, B, L, T);
@@ -501,7 +501,9 @@ static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, l
   P.gbuf = gbuf;
   P.gpitch = 32;  // G is stored in blocks of 32 frames: [frame / 32][packed row][frame % 32]
   // (a complex-format output is C itself: its gradient is G, and nothing needs to be recomputed)
-  if (fmt == NNA_OUT_COMPLEX && !pout)
+  if (kept)
+    e = nna::launch_g_from_kept({kept, gout_dev, gbuf, pout, n_frames, gpitch, (int)T, out_bins, plan->rows_pad, plan->n_half, packed, fmt}, stream);
+  else if (fmt == NNA_OUT_COMPLEX && !pout)
     e = nna::launch_g_from_complex(gbuf, gout_dev, n_frames, (int)T, out_bins, plan->rows_pad, plan->n_half, packed, stream);
   else if (fmt == NNA_OUT_POWER)
     e = nna::launch_split_forward(P, nna::ST_MODE_GRAD, plan->d_wrm, plan->kp, plan->K, stream);
@@ -548,8 +550,8 @@ static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, l
   return NNA_OK;
 }
 
-nna_status nna_stft_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
-                             float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
+static nna_status stft_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
+                             float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes, void* hip_stream, const float* kept) {
   nna_status s = check_trainable(plan);
   if (s != NNA_OK) return s;
   if (plan->kind != NNA_KIND_STFT) return fail(NNA_ERR_INVALID_ARG, "plan was built for a different transform");
@@ -563,7 +565,12 @@ nna_status nna_stft_backward(const nna_plan* plan, const float* x_dev, long long
   if (!workspace_dev || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace_dev) & 255))
     return fail(NNA_ERR_INVALID_ARG, "workspace_dev is NULL, not 256-byte aligned or smaller than nna_stft_backward_workspace asks for");
   return stft_backward_core(plan, x_dev, B, L, T, gout_dev, plan->fmt, plan->out_rows(), gw_dev, gx_dev,
-                            static_cast<float*>(workspace_dev), hip_stream);
+                            static_cast<float*>(workspace_dev), hip_stream, nullptr, true, kept);
+}
+
+nna_status nna_stft_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
+                             float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
+  return stft_backward(plan, x_dev, B, L, gout_dev, gw_dev, gx_dev, workspace_dev, workspace_bytes, hip_stream, nullptr);
 }
 
 // ---- trainable constant-Q kernels (time-domain kernels at one rate) ------------------------------
@@ -582,18 +589,19 @@ nna_status nna_cqt_backward_workspace(const nna_plan* plan, long long B, long lo
 // The backward pass of one constant-Q convolution: plan's bank over T frames of each of the B waveforms in x_dev.
 // gout points at the plan's first output row of waveform 0 (consecutive waveforms gout_wave_stride floats apart);
 // gw (may be NULL) receives atomic adds -- zeroed here if zero_gw, else accumulated onto; gx (may be NULL) is
-// overwritten.  gbuf: rows_pad x padded frames floats.  Arguments already checked, device current.
+// overwritten.  gbuf: rows_pad x padded frames floats.  kept (optional, gout of the whole plan): C from the forward pass, in G's order.
+// Arguments already checked, device current.
 static nna_status cqt_backward_core(const nna_plan* plan, const float* x_dev, long long B, long long L, long long T,
                                     const float* gout, long long gout_wave_stride, float* gw_dev, bool zero_gw,
-                                    float* gx_dev, float* gbuf, hipStream_t stream) {
+                                    float* gx_dev, float* gbuf, hipStream_t stream, const float* kept = nullptr) {
   const int extra = (plan->max_jspan - 1) * plan->row_step;
   const int M = pick_tile_frames(CQ_FRAMES, T, extra, CQ_LDS_ROWS_MAX);
   if (M < 1) return fail(NNA_ERR_UNSUPPORTED, "frame tile does not fit in LDS");
   const long long n_frames = B * T, gpitch = bw_gpitch(n_frames);
   // 1. G = dLoss/dC: the forward contraction again with the derivative of the output format as its
   //    epilogue.  The kernel writes the rows of existing bins and frames; the padding stays zero.
-  hipError_t e = nna::launch_fill_zero(gbuf, (long long)plan->rows_pad * gpitch, stream);
-  if (e != hipSuccess) return fail_hip(e, "kernel launch");
+  hipError_t e = hipSuccess;
+  if (!kept && (e = nna::launch_fill_zero(gbuf, (long long)plan->rows_pad * gpitch, stream)) != hipSuccess) return fail_hip(e, "kernel launch");
   nna::CqtParams P;
   std::memset(&P, 0, sizeof(P));
   P.g = make_geom(plan, x_dev, B, L, T);
@@ -614,7 +622,8 @@ static nna_status cqt_backward_core(const nna_plan* plan, const float* x_dev, lo
   P.gout_wave_stride = gout_wave_stride;
   P.gbuf = gbuf;
   P.rows_pad = plan->rows_pad;
-  e = launch_conv(plan, P, stream);
+  e = kept ? nna::launch_g_from_kept({kept, gout, gbuf, nullptr, n_frames, gpitch, (int)T, plan->out_rows(), plan->rows_pad, plan->n_bins, 0, plan->fmt}, stream)
+           : launch_conv(plan, P, stream);
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
   // 2. the two contractions with G, restricted to the tiles that hold taps
   nna::BwParams Q;
@@ -671,8 +680,8 @@ static nna_status cqt_backward_core(const nna_plan* plan, const float* x_dev, lo
   return NNA_OK;
 }
 
-nna_status nna_cqt_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
-                            float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
+static nna_status cqt_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
+                            float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes, void* hip_stream, const float* kept) {
   nna_status s = check_trainable(plan);
   if (s != NNA_OK) return s;
   if (plan->kind != NNA_KIND_CQT) return fail(NNA_ERR_INVALID_ARG, "plan was built for a different transform");
@@ -688,7 +697,12 @@ nna_status nna_cqt_backward(const nna_plan* plan, const float* x_dev, long long 
   hipError_t e = guard.enter(plan->device);
   if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
   return cqt_backward_core(plan, x_dev, B, L, T, gout_dev, (long long)plan->out_rows() * T, gw_dev, true, gx_dev,
-                           static_cast<float*>(workspace_dev), reinterpret_cast<hipStream_t>(hip_stream));
+                           static_cast<float*>(workspace_dev), reinterpret_cast<hipStream_t>(hip_stream), kept);
+}
+
+nna_status nna_cqt_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
+                            float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
+  return cqt_backward(plan, x_dev, B, L, gout_dev, gw_dev, gx_dev, workspace_dev, workspace_bytes, hip_stream, nullptr);
 }
 
 // ---- trainable kernels of the downsampling CQT (time-domain kernels; the paper's CQT2010v2 layer) -----------------
@@ -1200,9 +1214,9 @@ nna_status nna_mel_backward_workspace(const nna_plan* plan, long long B, long lo
   return NNA_OK;
 }
 
-nna_status nna_mel_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
-                            float* gmelw_dev, float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes,
-                            void* hip_stream) {
+static nna_status mel_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
+                               float* gmelw_dev, float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes,
+                               void* hip_stream, const float* kept) {
   nna_status s = check_trainable_mel(plan);
   if (s != NNA_OK) return s;
   if (!gout_dev) return fail(NNA_ERR_INVALID_ARG, "gout_dev is NULL");
@@ -1243,7 +1257,7 @@ nna_status nna_mel_backward(const nna_plan* plan, const float* x_dev, long long 
   e = nna::launch_mel_bw_spec(Q, stream);
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
   if ((s = stft_backward_core(plan, x_dev, B, L, T, gpbuf, fmt, F, gw_dev, gx_dev, gbuf, hip_stream,
-                              gmelw_dev ? pbuf : nullptr)) != NNA_OK)
+                              gmelw_dev ? pbuf : nullptr, true, kept)) != NNA_OK)
     return s;
   if (gmelw_dev) {
     e = nna::launch_fill_zero(gmelw_dev, (long long)plan->n_mels * F, stream);
@@ -1256,5 +1270,72 @@ nna_status nna_mel_backward(const nna_plan* plan, const float* x_dev, long long 
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
   }
   return NNA_OK;
+}
+
+nna_status nna_mel_backward(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev,
+                            float* gmelw_dev, float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes,
+                            void* hip_stream) {
+  return mel_backward(plan, x_dev, B, L, gout_dev, gmelw_dev, gw_dev, gx_dev, workspace_dev, workspace_bytes, hip_stream, nullptr);
+}
+
+// ---- forward passes that keep C for the backward pass ---------------------------------------------
+// Worth it where the backward pass would compute C again as the forward pass does: STFT stages in the power format (the other
+// formats' derivatives take the float32 contraction's C, which the forward pass does not compute), the constant-Q kernels in all
+// formats but the complex one (whose derivative needs no C).
+static bool keeps_c(const nna_plan* plan) {
+  if (plan->kind == NNA_KIND_STFT) return plan->fmt == NNA_OUT_POWER;
+  if (plan->kind == NNA_KIND_MEL) return plan->mel_power == 2;
+  return plan->kind == NNA_KIND_CQT && plan->fmt != NNA_OUT_COMPLEX;
+}
+
+nna_status nna_kept_bytes(const nna_plan* plan, long long B, long long L, size_t* bytes) {
+  nna_status s = check_trainable(plan);
+  if (s != NNA_OK) return s;
+  if (!bytes) return fail(NNA_ERR_INVALID_ARG, "bytes is NULL");
+  if (B < 1) return fail(NNA_ERR_SHAPE, "B must be >= 1");
+  const long long T = frames_of(plan, L);
+  if (T < 1) return fail(NNA_ERR_SHAPE, plan->center ? "L must exceed the reflection padding (K/2)" : "L is shorter than one window");
+  *bytes = keeps_c(plan) ? (size_t)plan->rows_pad * (size_t)bw_gpitch(B * T) * sizeof(float) : 0;
+  return NNA_OK;
+}
+
+static nna_status check_kept(const nna_plan* plan, long long B, long long L, const void* kept, size_t kept_bytes) {
+  size_t need = 0;
+  const nna_status s = nna_kept_bytes(plan, B, L, &need);
+  if (s != NNA_OK) return s;
+  if (need == 0) return fail(NNA_ERR_UNSUPPORTED, "this plan's forward pass keeps nothing (nna_kept_bytes is 0)");
+  if (!kept || kept_bytes < need || (reinterpret_cast<uintptr_t>(kept) & 255))
+    return fail(NNA_ERR_INVALID_ARG, "kept_dev is NULL, not 256-byte aligned or smaller than nna_kept_bytes asks for");
+  return NNA_OK;
+}
+
+nna_status nna_forward_keep(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev, float* spec_dev,
+                            void* kept_dev, size_t kept_bytes, void* hip_stream) {
+  nna_status s = check_trainable(plan);
+  if (s != NNA_OK) return s;
+  long long T = 0;
+  if ((s = check_call(plan, plan->kind, x_dev, B, L, out_dev, &T)) != NNA_OK) return s;
+  if ((s = check_kept(plan, B, L, kept_dev, kept_bytes)) != NNA_OK) return s;
+  if ((plan->kind == NNA_KIND_MEL) != (spec_dev != nullptr)) return fail(NNA_ERR_INVALID_ARG, "spec_dev: for Mel plans, and only for them");
+  float* kept = static_cast<float*>(kept_dev);
+  if (plan->kind != NNA_KIND_CQT) return run_stft_core(plan, plan->kind, x_dev, B, L, T, out_dev, 0, 0, hip_stream, spec_dev, kept);
+  DeviceGuard guard;
+  const hipError_t e = guard.enter(plan->device);
+  if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
+  return run_conv(plan, x_dev, B, L, T, out_dev, (long long)plan->out_rows() * T, 0, hip_stream, true, kept);
+}
+
+nna_status nna_backward_kept(const nna_plan* plan, const float* x_dev, long long B, long long L, const float* gout_dev, const void* kept_dev,
+                             size_t kept_bytes, float* gmelw_dev, float* gw_dev, float* gx_dev, void* workspace_dev, size_t workspace_bytes,
+                             void* hip_stream) {
+  nna_status s = check_trainable(plan);
+  if (s != NNA_OK) return s;
+  if ((s = check_kept(plan, B, L, kept_dev, kept_bytes)) != NNA_OK) return s;
+  const float* kept = static_cast<const float*>(kept_dev);
+  if (plan->kind == NNA_KIND_MEL)
+    return mel_backward(plan, x_dev, B, L, gout_dev, gmelw_dev, gw_dev, gx_dev, workspace_dev, workspace_bytes, hip_stream, kept);
+  if (gmelw_dev) return fail(NNA_ERR_INVALID_ARG, "gmelw_dev: for Mel plans only");
+  if (plan->kind == NNA_KIND_STFT) return stft_backward(plan, x_dev, B, L, gout_dev, gw_dev, gx_dev, workspace_dev, workspace_bytes, hip_stream, kept);
+  return cqt_backward(plan, x_dev, B, L, gout_dev, gw_dev, gx_dev, workspace_dev, workspace_bytes, hip_stream, kept);
 }
 }  // extern "C"

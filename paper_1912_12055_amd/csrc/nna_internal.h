@@ -115,6 +115,7 @@ struct StftParams {
   // from the upstream gradient gout[B, out_bins, T] (fmt selects the derivative of the output format)
   const float* gout;
   float* pout;                // optional (magnitude / power formats): the stage's output [B, out_bins, T] as well
+  float* keep;                // forward pass of the split contraction, optional: C as well, in the order of gbuf
   float* gbuf;                // [frame / 32][n_rt * ST_ROWS packed rows][frame % 32]
   long long gpitch;           // elements between consecutive rows of gbuf (32)
   // ST_MODE_LIN only: where this plan's bins go in `out`
@@ -211,6 +212,7 @@ struct CqtParams {
   const float* gout;       // upstream gradient [B][out rows][T]
   long long gout_wave_stride;
   float* gbuf;             // G in blocks of 32 frames, [frames / 32][rows_pad][32]
+  float* keep;             // forward pass, optional: C as well, in the order of gbuf
   int rows_pad;
 };
 
@@ -432,6 +434,17 @@ hipError_t launch_mel_from_logical(const float* w, float* frag, float* wnyq, flo
 hipError_t launch_fill_zero(float* p, long long n, hipStream_t stream);
 hipError_t launch_fill_zero_frames(float* gbuf, long long rows_pad, long long f0, long long f1, hipStream_t stream);
 // G <- the upstream gradient of a complex-format output, re-laid out (see g_from_complex_kernel)
+// G = dLoss/dC of every row and padded frame from the C a forward pass kept, and the upstream gradient; pout (optional): the format of
+// C, [B, out_rows, T].  (kept may be NULL for the complex format, whose derivative needs no C.)
+struct KeptParams {
+  const float* kept;   // [frame / 32][rows_pad][frame % 32]
+  const float* gout;   // [B][out_rows][T]
+  float* gbuf;         // as kept
+  float* pout;
+  long long n_frames, gpitch;
+  int T, out_rows, rows_pad, n_slots, packed, fmt;
+};
+hipError_t launch_g_from_kept(const KeptParams& p, hipStream_t stream);
 hipError_t launch_g_from_complex(float* gbuf, const float* gout, long long n_frames, int T, int out_rows, int rows_pad,
                                  int n_half, int packed, hipStream_t stream);
 hipError_t launch_bank_from_logical(const BankPermuteParams& p, hipStream_t stream);  // logical -> bank, wrm

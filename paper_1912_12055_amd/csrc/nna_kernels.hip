@@ -466,6 +466,13 @@ __device__ __forceinline__ void cqt_grad_bins(const CqtParams& P, const f32x4& a
     Gp[(2 * bin + 1) * 32] = gi;
   }
 }
+// ... forward: C as it stands, for the backward pass
+__device__ __forceinline__ void cqt_keep_bins(const CqtParams& P, const f32x4& acc, int bin0, long long fr) {
+  float* __restrict__ Kp = P.keep + (fr >> 5) * ((long long)P.rows_pad * 32) + (fr & 31);
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (bin0 + u / 2 < P.n_bins) Kp[(2 * bin0 + u) * 32] = acc[u];
+}
 // ... forward: the output format; `op` points at (waveform, first row, frame)
 __device__ __forceinline__ void cqt_store_bins(const CqtParams& P, const f32x4& acc, int bin0, float* __restrict__ op) {
   const long long T = P.g.T;
@@ -726,6 +733,7 @@ __global__ __launch_bounds__(256, 2) void cqt_kernel(const CqtParams P) {
     for (int fb = 0; fb < 4; ++fb) {
       if (!valid[fb]) continue;
       cqt_store_bins(P, acc[r][fb], bin0, P.out + o_off[fb]);
+      if (P.keep) cqt_keep_bins(P, acc[r][fb], bin0, f0 + wave * 64 + fb * 16 + n);
     }
   }
 }
@@ -835,10 +843,12 @@ __global__ __launch_bounds__(256, 2) void cqt_few_kernel(const CqtParams P, cons
   else sweep(std::integral_constant<bool, false>{});
   if (fi >= g.n_frames) return;
   const int bin0 = rb * (CQ_ROWS / 2) + 2 * q;
-  if constexpr (GRAD)
+  if constexpr (GRAD) {
     cqt_grad_bins(P, acc, bin0, f);
-  else
+  } else {
     cqt_store_bins(P, acc, bin0, P.out + b * P.out_wave_stride + (long long)P.row_offset * g.T + (f - b * g.T));
+    if (P.keep) cqt_keep_bins(P, acc, bin0, f);
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -997,10 +1007,12 @@ __global__ __launch_bounds__(256, 2) void cqt_few_tile_kernel(const CqtParams P,
   if (f >= g.n_frames) return;
   const int bin0 = rb * (CQ_ROWS / 2) + 2 * q;
   const long long b = f / g.T;
-  if constexpr (GRAD)
+  if constexpr (GRAD) {
     cqt_grad_bins(P, acc, bin0, f);
-  else
+  } else {
     cqt_store_bins(P, acc, bin0, P.out + b * P.out_wave_stride + (long long)P.row_offset * g.T + (f - b * g.T));
+    if (P.keep) cqt_keep_bins(P, acc, bin0, f);
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1173,6 +1185,7 @@ hipError_t launch_cqt_few(const CqtParams& p, const int* row_lo, const int* row_
   clear_stale_error();
   const long long blocks = (p.g.n_frames + CQW_FRAMES - 1) / CQW_FRAMES * ((2LL * p.n_bins + CQ_ROWS - 1) / CQ_ROWS);
   if (blocks <= 0 || blocks > 0x7fffffffLL || (p.gbuf && (!p.gout || p.rows_pad < 2 * p.n_bins))) return hipErrorInvalidValue;
+  if (p.keep && p.rows_pad < 2 * p.n_bins) return hipErrorInvalidValue;
   if (groups && first && lds_rows > 0) {
     if (lds_rows > CQW_ROWS || lds_rows > CQW_PASSES * 32 || p.tap_stride != p.g.hop || p.row_step != 1 || p.g.hop % CQW_COLS) return hipErrorInvalidValue;
     const size_t lds = (2ull * lds_rows + 4) * CQW_PITCH * sizeof(float);
@@ -1193,6 +1206,7 @@ hipError_t launch_cqt(const CqtParams& p, hipStream_t stream) {
   const long long blocks = p.n_ft * p.n_items;
   if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (p.lds_rows > CQ_LDS_ROWS_MAX || p.row_step < 1) return hipErrorInvalidValue;
+  if (p.keep && p.rows_pad < 2 * p.n_bins) return hipErrorInvalidValue;
   const size_t lds = cqt_launch_lds_bytes(p.n_chunks, p.lds_rows);
   if (lds > CQ_DYN_LDS_MAX) return hipErrorInvalidValue;
   if (p.gbuf) {

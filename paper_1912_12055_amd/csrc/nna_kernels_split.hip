@@ -229,6 +229,13 @@ __global__ __launch_bounds__(256, 2) void split_forward_kernel(const StftParams 
     stft_grad_tile<NNA_OUT_POWER>(acc, gp, g.T, Gp, 32, slot_base, h, P.n_half, P.packed, pp);
   } else {
     float* __restrict__ op = P.out + (b_lane * P.out_bins) * g.T + t_lane;
+    if (MODE == ST_MODE_STFT && P.keep) {
+      float* __restrict__ Kp = P.keep + (f >> 5) * ((long long)P.n_rt * ST_ROWS * 32) + (f & 31);
+#pragma unroll
+      for (int rb = 0; rb < ST_RB; ++rb)
+#pragma unroll
+        for (int u = 0; u < 16; ++u) Kp[(2 * (slot_base + 2 * h + rb * 16 + 4 * (u >> 2) + ((u >> 1) & 1)) + (u & 1)) * 32] = acc[rb][u];
+    }
     if constexpr (MODE == ST_MODE_CPLX) {
       if (P.fmt == NNA_OUT_COMPLEX)
         stft_store_tile_complex<NNA_OUT_COMPLEX>(acc, op, g.T, slot_base, h, P.n_half, P.packed);

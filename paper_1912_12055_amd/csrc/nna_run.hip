@@ -98,7 +98,7 @@ nna::FrameGeom make_geom(const nna_plan* p, const float* x, long long B, long lo
 // caller).  out_wave_stride / row_offset place a two-stage CQT plan's rows inside a larger output
 // (octave of a downsampling plan); 0 / 0 = the plan's own [B, bins, T].
 nna_status run_stft_core(const nna_plan* plan, int kind, const float* x, long long B, long long L, long long T,
-                         float* out, long long out_wave_stride, int row_offset, void* stream, float* spec_out = nullptr) {
+                         float* out, long long out_wave_stride, int row_offset, void* stream, float* spec_out, float* keep) {
   if (plan->precision == NNA_PREC_F16) {
     const int M = pick_tile_frames(nna::H_FRAMES, T, plan->nj - 1, nna::H_LB_ROWS);
     if (M < 1) return fail(NNA_ERR_UNSUPPORTED, "frame tile does not fit in LDS");
@@ -268,6 +268,7 @@ nna_status run_stft_core(const nna_plan* plan, int kind, const float* x, long lo
   hipError_t e = guard.enter(plan->device);
   if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
   P.pout = spec_out;
+  P.keep = keep;
   const int mode = kind == NNA_KIND_MEL       ? (spec_out ? nna::ST_MODE_MELSPEC : nna::ST_MODE_MEL)
                    : kind == NNA_KIND_CQT1992 ? nna::ST_MODE_LIN
                    : (plan->fmt == NNA_OUT_COMPLEX || plan->fmt == NNA_OUT_PHASE) ? nna::ST_MODE_CPLX
@@ -413,7 +414,7 @@ hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t
 
 // one launch of the CQT kernel: `sub`'s bank over T frames of each of the B waveforms in x
 nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
-                    long long out_wave_stride, int row_offset, void* hip_stream, bool may_fold = false) {
+                    long long out_wave_stride, int row_offset, void* hip_stream, bool may_fold, float* keep) {
   if (sub->runs_lowrank()) {
     nna::CqlParams Q;
     std::memset(&Q, 0, sizeof(Q));
@@ -443,6 +444,8 @@ nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long 
   P.n_chunks = sub->n_chunks;
   P.n_bins = sub->n_bins;
   P.fmt = sub->fmt;
+  P.keep = keep;
+  P.rows_pad = sub->rows_pad;
   P.tile_frames = M;
   const long long nseg = 1 + (M - 1 + T - 1) / T;
   P.lds_rows = (int)((M + nseg * extra + 63) / 64 * 64);  // whole loader passes of 64 rows (<= CQ_LDS_ROWS_MAX)

@@ -156,6 +156,52 @@ __global__ __launch_bounds__(256) void g_from_complex_kernel(float* __restrict__
   }
 }
 
+// G from the C a forward pass kept.  A workgroup takes a block of 32 frames and 64 (Re, Im) slots of it: 128-byte runs of C, of G and,
+// where T allows, of the upstream gradient.  Bound by memory.
+__global__ __launch_bounds__(256) void g_from_kept_kernel(const KeptParams P) {
+  const long long f = (long long)blockIdx.x * 32 + (threadIdx.x & 31), T = P.T, b = f / T;
+  const long long at = (long long)blockIdx.x * P.rows_pad * 32 + (threadIdx.x & 31);
+  const float* __restrict__ gp = P.gout + b * P.out_rows * T + (f - b * T);
+  float* __restrict__ pp = P.pout ? P.pout + b * P.out_rows * T + (f - b * T) : nullptr;
+  for (int slot = 64 * blockIdx.y + (threadIdx.x >> 5); slot < 64 * (int)blockIdx.y + 64 && 2 * slot < P.rows_pad; slot += 8) {
+    float gr = 0.f, gi = 0.f;
+    if (f < P.n_frames && slot < P.n_slots) {
+      const float re = P.kept ? P.kept[at + 64LL * slot] : 0.f, im = P.kept ? P.kept[at + 64LL * slot + 32] : 0.f;
+      const float pw = re * re + im * im;
+      if (P.fmt == NNA_OUT_COMPLEX) {
+        gr = gp[2 * slot * T];
+        gi = gp[(2 * slot + 1) * T];
+      } else if (P.fmt == NNA_OUT_PHASE) {  // d atan2(Im, Re) = (Re dIm - Im dRe) / P
+        const float s = pw > 0.f ? gp[slot * T] / pw : 0.f;
+        gr = -s * im;
+        gi = s * re;
+      } else {
+        auto scale = [&](float g, float p) {
+          return P.fmt == NNA_OUT_MAGNITUDE ? grad_scale<NNA_OUT_MAGNITUDE>(g, p)
+                 : P.fmt == NNA_OUT_POWER   ? grad_scale<NNA_OUT_POWER>(g, p)
+                                            : grad_scale<NNA_OUT_LOG>(g, p);
+        };
+        auto format = [&](float p) { return P.fmt == NNA_OUT_MAGNITUDE ? __builtin_amdgcn_sqrtf(p) : p; };  // (pout: these two only)
+        if (slot == 0 && P.packed) {  // the two real bins 0 and n_slots
+          gr = scale(gp[0], re * re) * re;
+          gi = scale(gp[P.n_slots * T], im * im) * im;
+          if (pp) {
+            pp[0] = format(re * re);
+            pp[P.n_slots * T] = format(im * im);
+          }
+        } else {
+          const float s = scale(gp[slot * T], pw);
+          gr = s * re;
+          gi = s * im;
+          if (pp) pp[slot * T] = format(pw);
+        }
+      }
+    }
+    P.gbuf[at + 64LL * slot] = gr;
+    P.gbuf[at + 64LL * slot + 32] = gi;
+  }
+}
+
 // frames [f0, f1) of every row of the blocked G buffer [frame / 32][rows_pad][frame % 32]
 __global__ void fill_zero_frames_kernel(float* __restrict__ p, long long rows_pad, long long f0, long long f1) {
   const long long w = f1 - f0, n = rows_pad * w;
@@ -826,6 +872,17 @@ hipError_t launch_g_from_complex(float* gbuf, const float* gout, long long n_fra
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL(g_from_complex_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, gbuf, gout, n_frames, T, out_rows,
                      rows_pad, n_half, packed);
+  return hipGetLastError();
+}
+
+hipError_t launch_g_from_kept(const KeptParams& p, hipStream_t stream) {
+  clear_stale_error();
+  const long long blocks = p.gpitch / 32;
+  if (blocks < 1 || blocks > 0x7fffffffLL || p.gpitch % 32 || p.n_frames < 1 || p.n_frames > p.gpitch || p.T < 1 || p.rows_pad < 2 || p.rows_pad % 2 ||
+      2 * p.n_slots > p.rows_pad || (p.fmt == NNA_OUT_COMPLEX ? 2 * p.n_slots : p.packed ? p.n_slots + 1 : p.n_slots) > p.out_rows ||
+      (p.fmt == NNA_OUT_COMPLEX && p.packed) || (!p.kept && p.fmt != NNA_OUT_COMPLEX))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(g_from_kept_kernel, dim3((unsigned)blocks, (unsigned)((p.rows_pad + 127) / 128)), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 

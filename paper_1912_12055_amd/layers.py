@@ -59,21 +59,41 @@ def _no_grad_input(x):
     return _as_batch(x)
 
 
+_KEPT_BYTES = 1 << 30  # what a forward pass holds for its backward pass, at most; a larger batch's computes it again
+
+
+def _forward(ctx, plan, x, keep, run):
+    """run(plan, x), or what is worth keeping for the backward pass with it (`keep`: there will be one)."""
+    if keep and x.is_cuda and x.dim() == 2 and x.shape[1] >= 4 and 0 < nb.nna_kept_bytes(plan, *x.shape) <= _KEPT_BYTES:
+        out, kept = nb.nna_forward_keep(plan, x)
+        ctx.save_for_backward(x, kept)
+        return out
+    ctx.save_for_backward(x)
+    return run(plan, x)
+
+
+def _recorded(*tensors):
+    """Whether autograd records a call on these."""
+    return torch.is_grad_enabled() and any(t.requires_grad for t in tensors)
+
+
 class _StftFn(torch.autograd.Function):
     """nna_stft with nna_stft_backward as its derivative (kernels W and waveform x)."""
 
     @staticmethod
-    def forward(ctx, x, W, layer):
+    def forward(ctx, x, W, layer, keep):
         ctx.layer = layer
-        ctx.save_for_backward(x)
-        return nb.nna_stft(layer.plan, x)
+        return _forward(ctx, layer.plan, x, keep, nb.nna_stft)
 
     @staticmethod
     def backward(ctx, gout):
-        (x,) = ctx.saved_tensors
+        x, *kept = ctx.saved_tensors
         need_x, need_w = ctx.needs_input_grad[0], ctx.needs_input_grad[1]
-        gw, gx = nb.nna_stft_backward(ctx.layer.plan, x, gout.contiguous(), want_gw=need_w, want_gx=need_x)
-        return gx, gw, None
+        if kept:
+            _, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept[0], want_gw=need_w, want_gx=need_x)
+        else:
+            gw, gx = nb.nna_stft_backward(ctx.layer.plan, x, gout.contiguous(), want_gw=need_w, want_gx=need_x)
+        return gx, gw, None, None
 
 
 _SPECTROGRAM_FLOATS = 1 << 28  # 1 GiB: what a trainable Mel layer's forward pass holds besides its output
@@ -83,13 +103,13 @@ class _MelFn(torch.autograd.Function):
     """nna_mel with nna_mel_backward as its derivative (filterbank, kernels and waveform)."""
 
     @staticmethod
-    def forward(ctx, x, W, Wmel, layer):
+    def forward(ctx, x, W, Wmel, layer, keep):
         ctx.layer = layer
-        ctx.save_for_backward(x)
         # the filters are dense: through the spectrogram, of a slice of the batch at a time
         B, F = x.shape[0], layer.wsin_wcos.shape[0] // 2
         if B * F * (x.shape[1] // layer.hop_length + 2) <= _SPECTROGRAM_FLOATS:
-            return nb.nna_mel_with_stft(layer.plan, x)[0]
+            return _forward(ctx, layer.plan, x, keep, lambda plan, x: nb.nna_mel_with_stft(plan, x)[0])
+        ctx.save_for_backward(x)
         bins, frames = nb.nna_out_shape(layer.plan, *x.shape)
         step = max(1, _SPECTROGRAM_FLOATS // (F * frames))
         out, spec = x.new_empty((B, bins, frames)), x.new_empty((min(step, B), F, frames))
@@ -100,11 +120,14 @@ class _MelFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, gout):
-        (x,) = ctx.saved_tensors
+        x, *kept = ctx.saved_tensors
         need_x, need_w, need_m = ctx.needs_input_grad[:3]
-        gm, gw, gx = nb.nna_mel_backward(ctx.layer.plan, x, gout.contiguous(), want_gmelw=need_m, want_gw=need_w,
-                                         want_gx=need_x)
-        return gx, gw, gm, None
+        want = dict(want_gmelw=need_m, want_gw=need_w, want_gx=need_x)
+        if kept:
+            gm, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept[0], **want)
+        else:
+            gm, gw, gx = nb.nna_mel_backward(ctx.layer.plan, x, gout.contiguous(), **want)
+        return gx, gw, gm, None, None
 
 
 class _Trainable(torch.nn.Module):
@@ -152,7 +175,7 @@ class STFT(_Trainable):
             return nb.nna_stft(self.plan, _no_grad_input(x))
         x = _as_batch(x)
         self._sync(self.wsin_wcos, nb.nna_plan_set_bank, "bank")
-        return _StftFn.apply(x, self.wsin_wcos, self)
+        return _StftFn.apply(x, self.wsin_wcos, self, _recorded(x, self.wsin_wcos))
 
 
 class MelSpectrogram(_Trainable):
@@ -189,7 +212,7 @@ class MelSpectrogram(_Trainable):
             return nb.nna_mel(self.plan, _no_grad_input(x))
         self._sync(self.wsin_wcos, nb.nna_plan_set_bank, "bank")
         self._sync(self.mel_basis, nb.nna_plan_set_mel_weights, "mel")
-        return _MelFn.apply(x, self.wsin_wcos, self.mel_basis, self)
+        return _MelFn.apply(x, self.wsin_wcos, self.mel_basis, self, _recorded(x, self.wsin_wcos, self.mel_basis))
 
 
 def _cqt_bins(sr, fmin, fmax, n_bins, bins_per_octave):
@@ -203,17 +226,19 @@ class _CqtFn(torch.autograd.Function):
     """nna_cqt with nna_cqt_backward as its derivative (kernels W and waveform x)."""
 
     @staticmethod
-    def forward(ctx, x, W, layer):
+    def forward(ctx, x, W, layer, keep):
         ctx.layer = layer
-        ctx.save_for_backward(x)
-        return nb.nna_cqt(layer.plan, x)
+        return _forward(ctx, layer.plan, x, keep, nb.nna_cqt)
 
     @staticmethod
     def backward(ctx, gout):
-        (x,) = ctx.saved_tensors
+        x, *kept = ctx.saved_tensors
         need_x, need_w = ctx.needs_input_grad[0], ctx.needs_input_grad[1]
-        gw, gx = nb.nna_cqt_backward(ctx.layer.plan, x, gout.contiguous(), want_gw=need_w, want_gx=need_x)
-        return gx, gw, None
+        if kept:
+            _, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept[0], want_gw=need_w, want_gx=need_x)
+        else:
+            gw, gx = nb.nna_cqt_backward(ctx.layer.plan, x, gout.contiguous(), want_gw=need_w, want_gx=need_x)
+        return gx, gw, None, None
 
 
 class _Cqt(_Trainable):
@@ -249,7 +274,7 @@ class CQT1992v2(_Cqt):
             return nb.nna_cqt(self.plan, _no_grad_input(x))
         x = _as_batch(x)
         self._sync(self.cqt_kernels, nb.nna_plan_set_bank, "bank")
-        return _CqtFn.apply(x, self.cqt_kernels, self)
+        return _CqtFn.apply(x, self.cqt_kernels, self, _recorded(x, self.cqt_kernels))
 
 
 class CQT1992(_Cqt):

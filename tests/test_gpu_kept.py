@@ -1,0 +1,76 @@
+"""Training steps whose forward pass keeps C: the same output bit for bit and the same gradients as the calls that compute C again."""
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+# partial sums meet in memory by atomic adds, in any order: float32 rounding of a few of them
+TOL = 2e-6
+
+
+def _close(got, want):
+    assert (got is None) == (want is None)
+    assert got is None or (got - want).norm() <= TOL * want.norm()
+
+
+PLANS = [("stft", "POWER"), ("mel", "POWER"), ("cqt", "MAGNITUDE"), ("cqt", "POWER"), ("cqt", "LOG"), ("cqt", "PHASE")]
+
+
+# frames short of, at and past a block of 32; waveforms that end inside a run of four samples; many frames (the kernel for large batches)
+@pytest.mark.parametrize("B,L", [(1, 2100), (3, 4097), (2, 7003), (60, 9001)])
+@pytest.mark.parametrize("kind,fmt", PLANS)
+def test_same_as_recomputed(kind, fmt, B, L):
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] kept {kind} {fmt} {B}x{L}", file=sys.stderr, flush=True)
+    made = {"stft": lambda: nb.nna_plan_stft(n_fft=400, hop=100, fmt=getattr(nb, "NNA_OUT_" + fmt), device=0),
+            "mel": lambda: nb.nna_plan_mel(sr=16000, n_fft=512, hop=128, n_mels=40, device=0),
+            "cqt": lambda: nb.nna_plan_cqt(sr=8000, hop=32, fmin=80.0, n_bins=31, bins_per_octave=12, fmt=getattr(nb, "NNA_OUT_" + fmt), device=0)}
+    plan = nb.nna_plan_trainable(made[kind]())
+    gen = torch.Generator().manual_seed(B * L)
+    x = torch.randn((B, L), generator=gen).cuda()
+    run = {"stft": nb.nna_stft, "mel": lambda p, x: nb.nna_mel_with_stft(p, x)[0], "cqt": nb.nna_cqt}[kind]
+    out, kept = nb.nna_forward_keep(plan, x)
+    assert torch.equal(out, run(plan, x))
+    gout = torch.randn(out.shape, generator=gen).cuda()
+    gm, gw, gx = nb.nna_backward_kept(plan, x, gout, kept, want_gmelw=kind == "mel")
+    want = {"stft": nb.nna_stft_backward, "mel": nb.nna_mel_backward, "cqt": nb.nna_cqt_backward}[kind](plan, x, gout)
+    for got, ref in zip((gm, gw, gx), want if kind == "mel" else (None, *want)):
+        _close(got, ref)
+    with pytest.raises(nb.NnaError):
+        nb.nna_backward_kept(plan, x, gout, kept[:-256])
+
+
+def test_plans_that_keep_nothing():
+    from paper_1912_12055_amd import binding as nb
+    for plan in (nb.nna_plan_stft(fmt=nb.NNA_OUT_MAGNITUDE, device=0), nb.nna_plan_stft(fmt=nb.NNA_OUT_COMPLEX, device=0),
+                 nb.nna_plan_mel(power=1.0, device=0), nb.nna_plan_cqt(fmin=220.0, n_bins=24, fmt=nb.NNA_OUT_COMPLEX, device=0)):
+        assert nb.nna_kept_bytes(nb.nna_plan_trainable(plan), 2, 30000) == 0
+    with pytest.raises(nb.NnaError):
+        nb.nna_kept_bytes(nb.nna_plan_stft(device=0), 2, 30000)  # not trainable
+
+
+@pytest.mark.parametrize("kind", ["stft", "mel", "cqt"])
+def test_layers(kind, monkeypatch):
+    import torch
+    from paper_1912_12055_amd import layers
+    made = {"stft": lambda: layers.STFT(n_fft=512, hop_length=128, output_format="Power", trainable=True),
+            "mel": lambda: layers.MelSpectrogram(n_fft=512, hop_length=128, n_mels=40, trainable_mel=True, trainable_STFT=True),
+            "cqt": lambda: layers.CQT1992v2(sr=8000, hop_length=32, fmin=80.0, n_bins=20, trainable=True)}
+    layer = made[kind]()
+    x = torch.randn((2, 5001), generator=torch.Generator().manual_seed(3)).cuda().requires_grad_()
+    wanted = list(layer.parameters()) + [x]
+    out = layer(x)
+    gout = torch.randn(out.shape, generator=torch.Generator().manual_seed(4)).cuda()
+    first = torch.autograd.grad(out, wanted, gout, retain_graph=True)
+    again = torch.autograd.grad(out, wanted, gout)
+    monkeypatch.setattr(layers, "_KEPT_BYTES", 0)  # every batch is too large
+    out2 = layer(x)
+    assert torch.equal(out, out2)
+    for a, b, c in zip(first, again, torch.autograd.grad(out2, wanted, gout)):
+        _close(a, c)
+        _close(b, c)
+    monkeypatch.undo()
+    monkeypatch.setattr(layers.nb, "nna_forward_keep", None)  # without a backward pass to come nothing is kept
+    with torch.no_grad():
+        assert torch.equal(layer(x), out)
