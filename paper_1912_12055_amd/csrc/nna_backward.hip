@@ -290,11 +290,14 @@ static nna_status make_spectral_trainable(nna_plan* plan) {
 // What only calls with fixed kernels run by: a trainable plan gives it back.
 static void release_fixed_forms(nna_plan* plan) {
   (void)hipFree(plan->d_lu);
+  (void)hipFree(plan->d_lub);
+  (void)hipFree(plan->d_lab);
   (void)hipFree(plan->d_la);
   (void)hipFree(plan->d_lsteps);
   (void)hipFree(plan->d_litems);
   (void)hipFree(plan->d_lsupport);
   plan->d_lu = plan->d_la = nullptr;
+  plan->d_lub = plan->d_lab = nullptr;
   plan->d_lsteps = nullptr;
   plan->d_litems = nullptr;
   plan->d_lsupport = nullptr;

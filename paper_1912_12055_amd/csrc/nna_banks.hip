@@ -984,9 +984,10 @@ LowrankGroup lowrank_group(const nna_plan* p, int k0, const CqtKernelSource& ker
   item.n_ib = (item.r + item.n_lo + 15) / 16;
   item.j0 = j0;
   item.jspan = J;
-  item.n_step = (int)ceil_div((long long)J * item.r, 16);
-  item.s_lo = (int)((long long)(jl[1] - j0) * item.r / 16);
-  item.s_hi = nb > 8 ? (int)ceil_div((long long)(jh[1] - j0) * item.r, 16) : item.s_lo;
+  // (the kernel takes steps of 16 in pairs)
+  item.n_step = 2 * (int)ceil_div((long long)J * item.r, 32);
+  item.s_lo = 2 * (int)((long long)(jl[1] - j0) * item.r / 32);
+  item.s_hi = nb > 8 ? 2 * (int)ceil_div((long long)(jh[1] - j0) * item.r, 32) : item.s_lo;
   item.bin0 = k0;
   item.n_bins = nb;
   if (item.n_ib > CQL_MAX_BASIS || cost_of(item.r) > as_is_cost) return g;
@@ -1073,9 +1074,9 @@ void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels) {
       first.push_back((int)steps.size());
       for (int j = 0; j < item.jspan; ++j)
         for (int half = 0; half < 2; ++half) {
-          const long long t0 = (long long)(item.j0 + j) * hop + c + 16 * half;
-          int a = 0;
-          while (a < n_rb && t0 + 16 > lo[a] && t0 < hi[a]) ++a;
+          const long long t1 = (long long)(item.j0 + j) * hop + c, t0 = t1 + 16 * half;
+          int a = 0;  // (the kernel takes steps of 16 in pairs)
+          while (a < n_rb && t1 + 32 > lo[a] && t1 < hi[a]) ++a;
           if (!a) continue;
           p->lr_direct += 256.0 * a;
           steps.push_back(a | (c / 16 + half) << 3 | j << 12);
@@ -1171,6 +1172,46 @@ bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy)
   else
     build_cqt_bank_lowrank(&copy, cqt_kernels(sub));
   return copy.lowrank;
+}
+
+// The items' weights as the matrix pipe takes them: every two fragments of 16 taps as one of 32, [.. one fragment ..][3 planes][64 lanes],
+// a lane's eight values in an octet of bfloat16, so fragment pair i of h_lu and h_la starts at 192 i octets.
+void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<unsigned>& a) {
+  auto round = [](float v) {  // to the nearest bfloat16, ties to even; finite values
+    unsigned b;
+    std::memcpy(&b, &v, 4);
+    b += 0x7fff + ((b >> 16) & 1);
+    return b & 0xffff0000u;
+  };
+  // first: the pair's first fragment; gap: floats from it to the second
+  auto octets = [&](const float* first, size_t gap, unsigned* out) {
+    for (int lane = 0; lane < 64; ++lane)
+      for (int e = 0; e < 8; ++e) {
+        float v = first[(e / 4) * gap + 4 * lane + e % 4];
+        for (int l = 0; l < 3; ++l) {
+          const unsigned b = round(v);
+          float part;
+          std::memcpy(&part, &b, 4);
+          v -= part;
+          out[(l * 64 + lane) * 4 + e / 2] |= e % 2 ? b : b >> 16;
+        }
+      }
+  };
+  u.assign(p->h_lu.size() / 2 * 3, 0u);
+  a.assign(p->h_la.size() / 2 * 3, 0u);
+  for (const nna::CqlItem& it : p->h_litems) {
+    const size_t u0 = (size_t)it.u0 * 4;
+    if (it.r) {
+      for (int i = 0; i < p->hop / 32 * it.n_ib; ++i) octets(&p->h_lu[u0 + (size_t)i * 512], 256, &u[u0 / 2 * 3 + (size_t)i * 768]);
+      for (int b = 0; b < 2; ++b)
+        for (int i = 0; i < (b ? it.s_hi - it.s_lo : it.n_step) / 2; ++i)
+          octets(&p->h_la[(size_t)it.a0[b] * 4 + (size_t)i * 512], 256, &a[(size_t)it.a0[b] * 6 + (size_t)i * 768]);
+    } else {
+      for (int i = 0; i < it.n_step / 2; ++i)
+        for (int b = 0; b < 4; ++b)
+          octets(&p->h_lu[u0 + (size_t)i * 2048 + b * 256], 1024, &u[u0 / 2 * 3 + ((size_t)i * 4 + b) * 768]);
+    }
+  }
 }
 
 // [2 n_bins][K]: the kernels of `p`'s items, multiplied out

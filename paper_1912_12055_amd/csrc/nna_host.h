@@ -217,6 +217,7 @@ struct nna_plan {
   int* d_lsteps = nullptr;
   double lr_direct = 0;  // multiply-adds per frame of the kernels that stay as they are
   float* d_lu = nullptr;
+  unsigned *d_lub = nullptr, *d_lab = nullptr;  // lowrank_planes
   float* d_la = nullptr;
   nna::CqlItem* d_litems = nullptr;
   int2* d_lsupport = nullptr;
@@ -419,6 +420,7 @@ std::vector<double> cqt1992_composed_rows(const nna_plan* p);
 void build_cqt_bank(nna_plan* p);
 // The kernels (p->K taps) in the form of nna_kernels_cql.hip; sets p->lowrank if it saves anything
 void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels);
+void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<unsigned>& a);
 CqtKernelSource cqt_kernels(const nna_plan* p);
 CqtKernelSource dense_kernels(std::vector<double> rows, long long K);  // [2 n_bins][K]
 bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy);

@@ -282,7 +282,7 @@ struct CqlItem {
   int r;             // basis functions, 4 modulo 8: the pitch of a hop-block's coefficients in LDS
   int n_ib;          // 16-row blocks of the basis: block 0 holds functions 0 .. 15 - n_lo, and what float32 leaves of the first n_lo
   int j0, jspan;     // the item's hop-blocks of a frame: j0 .. j0 + jspan - 1
-  int s_lo, s_hi;    // steps of 16 coefficients in which the second row block is not zero; the first has all n_step
+  int s_lo, s_hi;    // steps of 16 coefficients in which the second row block is not zero; the first has all n_step (all even)
   int n_step;
   int bin0, n_bins;  // first bin, bins (1 .. 16; r = 0: 1 .. 32)
   int n_lo;          // 4 or 8
@@ -300,6 +300,7 @@ struct CqlParams {
   FrameGeom g;
   const float4* u;
   const float4* a;
+  const uint4 *ub, *ab;  // the same as three bfloat16 each, two fragments of 16 taps to one of 32 (lowrank_planes)
   const int* steps;
   const int2* support;  // [bins]: first tap, last tap + 1
   float* out;

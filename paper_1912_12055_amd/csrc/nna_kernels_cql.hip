@@ -78,6 +78,15 @@ __device__ __forceinline__ unsigned store_bins(const CqlParams& P, const CqlItem
   return odd;
 }
 
+// sum + the 32 products of two octets a lane, small terms first
+__device__ __forceinline__ f32x4 multiply_octets(const u32x4 (&w)[3], const Planes& x, f32x4 sum) {
+  constexpr int lw[6] = {2, 1, 0, 1, 0, 0}, lx[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+  for (int m = 0; m < 6; ++m)
+    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[lw[m]]), __builtin_bit_cast(bf16x8, x.p[lx[m]]), sum, 0, 0, 0);
+  return sum;
+}
+
 // Short kernels, tap by tap.
 template <int FB>
 __device__ __forceinline__ void direct_item(const CqlParams& P, const CqlPart& part, const CqlItem& item, long long ft, float* Y) {
@@ -116,7 +125,7 @@ __device__ __forceinline__ void direct_item(const CqlParams& P, const CqlPart& p
   const int rows_buf = (rows_used + 31) & ~31;
   const int* __restrict__ chunk0 = P.steps + item.step0;       // first step of every 32 columns, [hop / 32 + 1], multiples of four
   const int* __restrict__ steps = chunk0 + hop / 32 + 1;       // a | 16-column block << 3 | hop-block << 12
-  const float4* __restrict__ up = P.u + item.u0 + lane;        // [step][4 row blocks][64 lanes]
+  const uint4* __restrict__ up = P.ub + item.u0 / 2 * 3 + lane;  // [pair of steps][4 row blocks][3 planes][64 lanes]
   const int cv = tid % V, r0 = tid / V;
   const float* xb[NP];  // this thread's rows: their waveform, the first of its four samples in column 0
   int pos[NP];
@@ -171,55 +180,59 @@ __device__ __forceinline__ void direct_item(const CqlParams& P, const CqlPart& p
   int f_off[FB];
 #pragma unroll
   for (int fb = 0; fb < FB; ++fb) f_off[fb] = (valid[fb] ? tm.frame_row(wave * (16 * FB) + fb * 16 + n) : 0) * PITCH + 4 * q;
-  auto multiply = [&](int a, const f32x4 (&w)[4], const f32x4 (&x)[FB]) {
+  // A step: 32 columns of one hop-block, for the first `a` row blocks
+  auto multiply = [&](int a, const u32x4 (&w)[4][3], const f32x4 (&x)[FB][2]) {
+    if (!a) return;
+    Planes b[FB];
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb) b[fb] = split8(x[fb]);
     // row block by row block: a kernel that has ended costs a branch
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (i < a) {
-        f32x4 sum[FB] = {};
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-          for (int fb = 0; fb < FB; ++fb) sum[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][k], x[fb][k], sum[fb], 0, 0, 0);
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb) acc[fb][i] += sum[fb];
+        for (int fb = 0; fb < FB; ++fb) acc[fb][i] += multiply_octets(w[i], b[fb], (f32x4){0.f, 0.f, 0.f, 0.f});
       }
   };
-  // The weights are requested three steps ahead, across chunks; the frames are read from LDS one step ahead, within a chunk.
-  const int n_step = item.n_step;
-  f32x4 w[4][4], x[2][FB];
-  auto fetch_w = [&](int s, f32x4 (&v)[4]) {
+  // The weights are requested a step ahead, across chunks, and so are the frames, from LDS, within a chunk.
+  const int n_pair = item.n_step / 2;
+  u32x4 w[2][4][3];
+  f32x4 x[2][FB][2];
+  auto fetch_w = [&](int s, u32x4 (&v)[4][3]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const f32x4*>(up + ((long long)s * 4 + i) * 64);
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int l = 0; l < 3; ++l) v[i][l] = *reinterpret_cast<const u32x4*>(up + (((long long)s * 4 + i) * 3 + l) * 64);
   };
   clear();
   request(0);
-#pragma unroll
-  for (int u = 0; u < 3; ++u) fetch_w(u, w[u]);
+  fetch_w(0, w[0]);
   for (int c = 0; c < hop; c += KC) {
     float* tile = Y + ((c / KC) & 1) * rows_buf * PITCH;
     store(c, tile);
     __syncthreads();  // also: the buffer of the chunk before last has been read by every wave
     if (c + KC < hop) request(c + KC);
-    const int next = (c + KC) / 32, s1 = chunk0[next < hop / 32 ? next : hop / 32];
-    auto fetch_x = [&](int d, f32x4 (&v)[FB]) {
+    const int next = (c + KC) / 32, s1 = chunk0[next < hop / 32 ? next : hop / 32] / 2;
+    auto fetch_x = [&](int d, f32x4 (&v)[FB][2]) {
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb)
-        v[fb] = *reinterpret_cast<const f32x4*>(tile + f_off[fb] + (d >> 12) * PITCH + ((d << 1) & (KC - 16)));
-    };
-    int s = chunk0[c / 32];
-    int4 d = s < s1 ? *reinterpret_cast<const int4*>(steps + s) : make_int4(0, 0, 0, 0);
-    fetch_x(d.x, x[0]);
-    for (; s < s1; s += 4) {
-      const int4 dn = *reinterpret_cast<const int4*>(steps + (s + 4 < n_step ? s + 4 : s));
-      const int du[5] = {d.x, d.y, d.z, d.w, dn.x};
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        fetch_w(s + u + 3 < n_step ? s + u + 3 : n_step - 1, w[(u + 3) & 3]);
+        for (int h = 0; h < 2; ++h)
+          v[fb][h] = *reinterpret_cast<const f32x4*>(tile + f_off[fb] + (d >> 12) * PITCH + ((d << 1) & (KC - 32)) + 16 * h);
+    };
+    int s = chunk0[c / 32] / 2;
+    int4 d = s < s1 ? *reinterpret_cast<const int4*>(steps + 2 * s) : make_int4(0, 0, 0, 0);
+    fetch_x(d.x, x[0]);
+    for (; s < s1; s += 2) {
+      const int4 dn = *reinterpret_cast<const int4*>(steps + 2 * (s + 2 < n_pair ? s + 2 : s));
+      const int du[3] = {d.x, d.z, dn.x};
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        fetch_w(s + u + 1 < n_pair ? s + u + 1 : n_pair - 1, w[u ^ 1]);
         // (behind the chunk's last step: a step of the next chunk, its offsets within the tile all the same; read and dropped)
-        fetch_x(du[u + 1], x[(u + 1) & 1]);
+        fetch_x(du[u + 1], x[u ^ 1]);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(du[u] & 7, w[u], x[u & 1]);
+        multiply(du[u] & 7, w[u], x[u]);
         __builtin_amdgcn_sched_barrier(0);
       }
       d = dn;
@@ -249,18 +262,18 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
   const int L = (int)g.L, hop = g.hop;
   // acc[p][i] += 16 rows of weights (i) x 16 runs of samples (p) over columns [c_begin, c_end), 32 at a time.  A lane's run starts
   // at sample pos[p] of its waveform, xb[p] points there (EDGE: at the waveform; some run of the wave touches a mirrored end).
-  // `u`: [chunk][u_blocks][half][64 lanes], of which the first IB blocks are used.
-  auto contract = [&](auto edge_tag, auto ib_tag, auto& acc, const auto& xb, const auto& pos, const float4* u, int u_blocks,
+  // `u`: [chunk][u_blocks][3 planes][64 lanes], of which the first IB blocks are used.
+  auto contract = [&](auto edge_tag, auto ib_tag, auto& acc, const auto& xb, const auto& pos, const uint4* u, int u_blocks,
                       int c_begin, int c_end) {
     constexpr bool EDGE = decltype(edge_tag)::value;
     constexpr int IB = decltype(ib_tag)::value, NB = sizeof(acc) / sizeof(acc[0]);
-    const float4* up = u + lane;
-    auto fetch = [&](int c, f32x4 (&x)[NB][2], f32x4 (&w)[IB][2], unsigned& rev) {
-      const float4* uc = up + (long long)((c - c_begin) >> 5) * u_blocks * 128;
+    const uint4* up = u + lane;
+    auto fetch = [&](int c, f32x4 (&x)[NB][2], u32x4 (&w)[IB][3], unsigned& rev) {
+      const uint4* uc = up + (long long)((c - c_begin) >> 5) * u_blocks * 192;
 #pragma unroll
       for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) w[i][h] = *reinterpret_cast<const f32x4*>(uc + (2 * i + h) * 64);
+        for (int l = 0; l < 3; ++l) w[i][l] = *reinterpret_cast<const u32x4*>(uc + (3 * i + l) * 64);
       if constexpr (!EDGE) {
 #pragma unroll
         for (int p = 0; p < NB; ++p) {
@@ -300,7 +313,7 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
         }
       }
     };
-    auto multiply = [&](f32x4 (&x)[NB][2], const f32x4 (&w)[IB][2], unsigned rev) {
+    auto multiply = [&](f32x4 (&x)[NB][2], const u32x4 (&w)[IB][3], unsigned rev) {
       if constexpr (EDGE) {
 #pragma unroll
         for (int p = 0; p < NB; ++p)
@@ -313,19 +326,15 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       }
 #pragma unroll
       for (int p = 0; p < NB; ++p) {
-        f32x4 sum[IB] = {};
+        const Planes b = split8(x[p]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-          for (int i = 0; i < IB; ++i)
-            sum[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][e >> 2][e & 3], x[p][e >> 2][e & 3], sum[i], 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < IB; ++i) acc[p][i] += sum[i];
+        for (int i = 0; i < IB; ++i) acc[p][i] += multiply_octets(w[i], b, (f32x4){0.f, 0.f, 0.f, 0.f});
       }
     };
     if (c_begin >= c_end) return;
     // two register sets: the next 32 columns are requested ahead of this chunk's matrix instructions
-    f32x4 x0[NB][2], w0[IB][2], x1[NB][2], w1[IB][2];
+    f32x4 x0[NB][2], x1[NB][2];
+    u32x4 w0[IB][3], w1[IB][3];
     unsigned r0 = 0, r1 = 0;
     fetch(c_begin, x0, w0, r0);
     for (int c = c_begin; c < c_end; c += 64) {
@@ -370,7 +379,7 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
 #pragma unroll
       for (int i = 0; i < IB; ++i) y[p][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
-    contract(edge_tag, ib_tag, y, xb, pos, P.u + item.u0 + (long long)ib0 * 128, item.n_ib, 0, hop);
+    contract(edge_tag, ib_tag, y, xb, pos, P.ub + item.u0 / 2 * 3 + (long long)ib0 * 192, item.n_ib, 0, hop);
     // lane (q, n), register e: row 4 q + e of a basis block, hop-block n.  Block 0's last n_lo rows go to its first.
     const int n_lo = item.n_lo;
     if (ib0 == 0) {
@@ -427,8 +436,8 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       else with_nb(False{});
       u += nb;
     }
-    // the last step of the last frame reads up to fifteen words (times zero) past its hop-blocks
-    if (tid < 16) Y[rows_used * r + tid] = 0.f;
+    // the last step of the last frame reads up to 31 words (times zero) past its hop-blocks
+    if (tid < 32) Y[rows_used * r + tid] = 0.f;
   }
   __syncthreads();
 
@@ -437,42 +446,42 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
   int y_off[FB];
 #pragma unroll
   for (int fb = 0; fb < FB; ++fb) y_off[fb] = (valid[fb] ? tm.frame_row(wave * (16 * FB) + fb * 16 + n) : 0) * r + 4 * q;
-  const float4* a0p = P.a + item.a0[0] + lane;
-  const float4* a1p = P.a + item.a0[1] - (long long)item.s_lo * 64 + lane;
-  // steps [s, e): both row blocks, or the first alone
+  const uint4* a0p = P.ab + item.a0[0] / 2 * 3 + lane;
+  const uint4* a1p = P.ab + item.a0[1] / 2 * 3 - (long long)(item.s_lo / 2) * 192 + lane;
+  // steps [s, e) of 32: both row blocks, or the first alone
   auto steps = [&](auto both_tag, int s, int e) {
     constexpr bool BOTH = decltype(both_tag)::value;
     if (s >= e) return;
-    auto fetch = [&](int i, f32x4& c0, f32x4& c1, f32x4 (&y)[FB]) {
-      c0 = *reinterpret_cast<const f32x4*>(a0p + (long long)i * 64);
-      if constexpr (BOTH) c1 = *reinterpret_cast<const f32x4*>(a1p + (long long)i * 64);
+    auto fetch = [&](int i, u32x4 (&c0)[3], u32x4 (&c1)[3], f32x4 (&y)[FB][2]) {
 #pragma unroll
-      for (int fb = 0; fb < FB; ++fb) y[fb] = *reinterpret_cast<const f32x4*>(Y + y_off[fb] + 16 * i);
+      for (int l = 0; l < 3; ++l) {
+        c0[l] = *reinterpret_cast<const u32x4*>(a0p + ((long long)i * 3 + l) * 64);
+        if constexpr (BOTH) c1[l] = *reinterpret_cast<const u32x4*>(a1p + ((long long)i * 3 + l) * 64);
+      }
+#pragma unroll
+      for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) y[fb][h] = *reinterpret_cast<const f32x4*>(Y + y_off[fb] + 32 * i + 16 * h);
     };
-    auto multiply = [&](const f32x4& c0, const f32x4& c1, const f32x4 (&y)[FB]) {
-      f32x4 sum[FB][2] = {};
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb) {
-          sum[fb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(c0[k], y[fb][k], sum[fb][0], 0, 0, 0);
-          if constexpr (BOTH) sum[fb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(c1[k], y[fb][k], sum[fb][1], 0, 0, 0);
-        }
+    auto multiply = [&](const u32x4 (&c0)[3], const u32x4 (&c1)[3], const f32x4 (&y)[FB][2]) {
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb) {
-        acc[fb][0] += sum[fb][0];
-        if constexpr (BOTH) acc[fb][1] += sum[fb][1];
+        const Planes b = split8(y[fb]);
+        acc[fb][0] += multiply_octets(c0, b, (f32x4){0.f, 0.f, 0.f, 0.f});
+        if constexpr (BOTH) acc[fb][1] += multiply_octets(c1, b, (f32x4){0.f, 0.f, 0.f, 0.f});
       }
     };
-    // four register sets of coefficients and frames, requested three steps ahead
-    f32x4 c0[4], c1[4], y[4][FB];
+    // register sets of coefficients and frames, requested up to three steps ahead
+    constexpr int SETS = FB == 1 ? 4 : 2;
+    u32x4 c0[SETS][3], c1[SETS][3];
+    f32x4 y[SETS][FB][2];
 #pragma unroll
-    for (int u = 0; u < 3; ++u) fetch(s + u < e ? s + u : e - 1, c0[u], c1[u], y[u]);
-    for (int i = s; i < e; i += 4) {
+    for (int u = 0; u < SETS - 1; ++u) fetch(s + u < e ? s + u : e - 1, c0[u], c1[u], y[u]);
+    for (int i = s; i < e; i += SETS) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int ahead = i + u + 3;
-        fetch(ahead < e ? ahead : e - 1, c0[(u + 3) & 3], c1[(u + 3) & 3], y[(u + 3) & 3]);
+      for (int u = 0; u < SETS; ++u) {
+        const int ahead = i + u + SETS - 1, at = (u + SETS - 1) % SETS;
+        fetch(ahead < e ? ahead : e - 1, c0[at], c1[at], y[at]);
         __builtin_amdgcn_sched_barrier(0);
         if (i + u < e) multiply(c0[u], c1[u], y[u]);
         __builtin_amdgcn_sched_barrier(0);
@@ -480,11 +489,11 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
     }
   };
   if (item.s_lo < item.s_hi) {
-    steps(False{}, 0, item.s_lo);
-    steps(True{}, item.s_lo, item.s_hi);
-    steps(False{}, item.s_hi, item.n_step);
+    steps(False{}, 0, item.s_lo / 2);
+    steps(True{}, item.s_lo / 2, item.s_hi / 2);
+    steps(False{}, item.s_hi / 2, item.n_step / 2);
   } else {
-    steps(False{}, 0, item.n_step);
+    steps(False{}, 0, item.n_step / 2);
   }
   // A sample that is not finite reaches, through its hop-block's coordinates, bins and frames whose own taps it lies outside of, and
   // turns infinities into NaN.  So a sum that is not finite is taken again over the bin's own taps: those samples alone if there

@@ -31,37 +31,11 @@ namespace nna {
 namespace {
 
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SP_T = 128;      // rows and columns of a tile
 constexpr int SP_KC = 32;      // contraction indices per chunk
 constexpr int SP_PITCH = 20;   // words per row of a staged plane: 32 bfloat16 and a pad (conflict-free 16-byte reads)
 constexpr int SP_PLANE = SP_T * SP_PITCH;
-
-struct Planes {
-  u32x4 p[3];  // eight values: their first, second and third bfloat16
-};
-
-__device__ __forceinline__ Planes split8(const f32x4 (&v)[2]) {
-  Planes o;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f32x2 a = {v[i >> 1][2 * (i & 1)], v[i >> 1][2 * (i & 1) + 1]};
-#pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(a, bf16x2));
-      o.p[l][i] = u;
-      if (l < 2) {
-        a.x -= __builtin_bit_cast(float, u << 16);
-        a.y -= __builtin_bit_cast(float, u & 0xffff0000u);
-      }
-    }
-  }
-  return o;
-}
 
 // acc[s] += the products of ROWS 32-row blocks of the staged chunk with this wave's columns
 template <int ROWS>

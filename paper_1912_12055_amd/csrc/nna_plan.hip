@@ -96,6 +96,12 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
       if (s == NNA_OK && p->lowrank) {
         s = upload(&p->d_lu, p->h_lu.data(), p->h_lu.size() * sizeof(float), "hop-block basis");
         if (s == NNA_OK) s = upload(&p->d_la, p->h_la.data(), p->h_la.size() * sizeof(float), "hop-block coefficients");
+        if (s == NNA_OK) {
+          std::vector<unsigned> u, a;
+          lowrank_planes(p, u, a);
+          s = upload(&p->d_lub, u.data(), u.size() * sizeof(unsigned), "hop-block basis");
+          if (s == NNA_OK) s = upload(&p->d_lab, a.data(), a.size() * sizeof(unsigned), "hop-block coefficients");
+        }
         if (s == NNA_OK) s = upload(&p->d_lsteps, p->h_lsteps.data(), p->h_lsteps.size() * sizeof(int), "step table");
         if (s == NNA_OK) s = upload(&p->d_litems, p->h_litems.data(), p->h_litems.size() * sizeof(nna::CqlItem), "hop-block item table");
         if (s == NNA_OK) s = upload(&p->d_lsupport, p->h_lsupport.data(), p->h_lsupport.size() * sizeof(int), "kernel supports");
@@ -937,6 +943,8 @@ void nna_plan_destroy(nna_plan* plan) {
       (void)hipFree(plan->d_qchunks);
       (void)hipFree(plan->d_qbins);
       (void)hipFree(plan->d_lu);
+      (void)hipFree(plan->d_lub);
+      (void)hipFree(plan->d_lab);
       (void)hipFree(plan->d_la);
       (void)hipFree(plan->d_litems);
       (void)hipFree(plan->d_lsteps);

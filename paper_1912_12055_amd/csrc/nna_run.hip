@@ -359,7 +359,7 @@ bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::Cq
     auto fits = [&](int cap, size_t lds) {
       int M = cap;
       for (int i = i0; i < i1; ++i) {
-        const int rows = direct ? nna::CQL_ROWS(cap / 64) : (int)((lds / 4 - 16) / sub->h_litems[i].r);
+        const int rows = direct ? nna::CQL_ROWS(cap / 64) : (int)((lds / 4 - 32) / sub->h_litems[i].r);
         M = std::min(M, pick_tile_frames(M, T, sub->h_litems[i].jspan - 1, rows));
       }
       return M;
@@ -376,7 +376,7 @@ bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::Cq
     for (int i = i0; i < i1; ++i) {
       const nna::CqlItem& it = sub->h_litems[i];
       const int rows = (int)(M + nseg * (it.jspan - 1));
-      P.lds_floats = std::max(P.lds_floats, direct ? (rows + 31) / 32 * 32 * 2 * (nna::CQL_COLS(part.fb) + 4) : rows * it.r + 16);
+      P.lds_floats = std::max(P.lds_floats, direct ? (rows + 31) / 32 * 32 * 2 * (nna::CQL_COLS(part.fb) + 4) : rows * it.r + 32);
       cost += direct ? 0.0 : (16.0 * it.n_ib * sub->hop * rows + 256.0 * (it.n_step + it.s_hi - it.s_lo) * cap) / M;
     }
     if (direct) cost += sub->lr_direct * cap / M;
@@ -394,6 +394,8 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
   P.g = make_geom(sub, x, B, L, T);
   P.u = reinterpret_cast<const float4*>(sub->d_lu);
   P.a = reinterpret_cast<const float4*>(sub->d_la);
+  P.ub = reinterpret_cast<const uint4*>(sub->d_lub);
+  P.ab = reinterpret_cast<const uint4*>(sub->d_lab);
   P.steps = sub->d_lsteps;
   P.support = sub->d_lsupport;
   P.out = out + (long long)row_offset * T;
