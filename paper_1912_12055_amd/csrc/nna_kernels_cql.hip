@@ -259,6 +259,11 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
   const int rows_used = tm.frame_row(m_valid - 1) + tm.extra + 1;
   const int r = item.r;
   constexpr int RB = 2;  // row blocks
+  // Where the LDS has room for six bytes a coordinate they are kept as the three bfloat16 stage 2 multiplies, split once instead of
+  // once per hop-block that reads them; planes of p_words values.
+  const int p_words = rows_used * r + 32;
+  const bool split = 6 * p_words <= 4 * P.lds_floats;
+  unsigned short* const Yb = reinterpret_cast<unsigned short*>(Y);
   const int L = (int)g.L, hop = g.hop;
   // acc[p][i] += 16 rows of weights (i) x 16 runs of samples (p) over columns [c_begin, c_end), 32 at a time.  A lane's run starts
   // at sample pos[p] of its waveform, xb[p] points there (EDGE: at the waveform; some run of the wave touches a mirrored end).
@@ -398,7 +403,16 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
 #pragma unroll
         for (int i = 0; i < IB; ++i) {
           const int blk = ib0 + i, f = blk ? 16 * blk - n_lo + 4 * q : 4 * q;
-          if (f < r && (blk || f < 16 - n_lo)) *reinterpret_cast<f32x4*>(Y + row * r + f) = y[p][i];
+          if (f < r && (blk || f < 16 - n_lo)) {
+            if (!split) {
+              *reinterpret_cast<f32x4*>(Y + row * r + f) = y[p][i];
+            } else {
+              const f32x4 both[2] = {y[p][i], y[p][i]};
+              const Planes b = split8(both);
+#pragma unroll
+              for (int l = 0; l < 3; ++l) *reinterpret_cast<uint2*>(Yb + l * p_words + row * r + f) = make_uint2(b.p[l][0], b.p[l][1]);
+            }
+          }
         }
       }
     }
@@ -437,7 +451,11 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       u += nb;
     }
     // the last step of the last frame reads up to 31 words (times zero) past its hop-blocks
-    if (tid < 32) Y[rows_used * r + tid] = 0.f;
+    if (tid < 32) {
+      if (!split) Y[rows_used * r + tid] = 0.f;
+      else
+        for (int l = 0; l < 3; ++l) Yb[l * p_words + rows_used * r + tid] = 0;
+    }
   }
   __syncthreads();
 
@@ -449,10 +467,11 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
   const uint4* a0p = P.ab + item.a0[0] / 2 * 3 + lane;
   const uint4* a1p = P.ab + item.a0[1] / 2 * 3 - (long long)(item.s_lo / 2) * 192 + lane;
   // steps [s, e) of 32: both row blocks, or the first alone
-  auto steps = [&](auto both_tag, int s, int e) {
-    constexpr bool BOTH = decltype(both_tag)::value;
+  auto steps = [&](auto both_tag, auto split_tag, int s, int e) {
+    constexpr bool BOTH = decltype(both_tag)::value, SPLIT = decltype(split_tag)::value;
+    constexpr int YV = SPLIT ? 3 : 2;  // 16-byte words a step of a frame block takes from LDS
     if (s >= e) return;
-    auto fetch = [&](int i, u32x4 (&c0)[3], u32x4 (&c1)[3], f32x4 (&y)[FB][2]) {
+    auto fetch = [&](int i, u32x4 (&c0)[3], u32x4 (&c1)[3], u32x4 (&y)[FB][YV]) {
 #pragma unroll
       for (int l = 0; l < 3; ++l) {
         c0[l] = *reinterpret_cast<const u32x4*>(a0p + ((long long)i * 3 + l) * 64);
@@ -461,12 +480,27 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) y[fb][h] = *reinterpret_cast<const f32x4*>(Y + y_off[fb] + 32 * i + 16 * h);
+        for (int h = 0; h < YV; ++h) {
+          if constexpr (SPLIT) {
+            const unsigned short* p = Yb + h * p_words + y_off[fb] + 32 * i;
+            const uint2 lo = *reinterpret_cast<const uint2*>(p), hi = *reinterpret_cast<const uint2*>(p + 16);
+            y[fb][h] = (u32x4){lo.x, lo.y, hi.x, hi.y};
+          } else {
+            y[fb][h] = *reinterpret_cast<const u32x4*>(Y + y_off[fb] + 32 * i + 16 * h);
+          }
+        }
     };
-    auto multiply = [&](const u32x4 (&c0)[3], const u32x4 (&c1)[3], const f32x4 (&y)[FB][2]) {
+    auto multiply = [&](const u32x4 (&c0)[3], const u32x4 (&c1)[3], const u32x4 (&y)[FB][YV]) {
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb) {
-        const Planes b = split8(y[fb]);
+        Planes b;
+        if constexpr (SPLIT) {
+#pragma unroll
+          for (int l = 0; l < 3; ++l) b.p[l] = y[fb][l];
+        } else {
+          const f32x4 v[2] = {__builtin_bit_cast(f32x4, y[fb][0]), __builtin_bit_cast(f32x4, y[fb][1])};
+          b = split8(v);
+        }
         acc[fb][0] += multiply_octets(c0, b, (f32x4){0.f, 0.f, 0.f, 0.f});
         if constexpr (BOTH) acc[fb][1] += multiply_octets(c1, b, (f32x4){0.f, 0.f, 0.f, 0.f});
       }
@@ -474,7 +508,7 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
     // register sets of coefficients and frames, requested up to three steps ahead
     constexpr int SETS = FB == 1 ? 4 : 2;
     u32x4 c0[SETS][3], c1[SETS][3];
-    f32x4 y[SETS][FB][2];
+    u32x4 y[SETS][FB][YV];
 #pragma unroll
     for (int u = 0; u < SETS - 1; ++u) fetch(s + u < e ? s + u : e - 1, c0[u], c1[u], y[u]);
     for (int i = s; i < e; i += SETS) {
@@ -488,13 +522,15 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       }
     }
   };
-  if (item.s_lo < item.s_hi) {
-    steps(False{}, 0, item.s_lo / 2);
-    steps(True{}, item.s_lo / 2, item.s_hi / 2);
-    steps(False{}, item.s_hi / 2, item.n_step / 2);
-  } else {
-    steps(False{}, 0, item.n_step / 2);
-  }
+  auto all_steps = [&](auto split_tag) {
+    const bool two = item.s_lo < item.s_hi;
+    steps(False{}, split_tag, 0, (two ? item.s_lo : item.n_step) / 2);
+    if (!two) return;
+    steps(True{}, split_tag, item.s_lo / 2, item.s_hi / 2);
+    steps(False{}, split_tag, item.s_hi / 2, item.n_step / 2);
+  };
+  if (split) all_steps(True{});
+  else all_steps(False{});
   // A sample that is not finite reaches, through its hop-block's coordinates, bins and frames whose own taps it lies outside of, and
   // turns infinities into NaN.  So a sum that is not finite is taken again over the bin's own taps: those samples alone if there
   // are any, else hop-block by hop-block, the ones whose coordinates are not finite sample by sample.  (1,770 x 176,400 samples, a
@@ -510,7 +546,13 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
     const float* __restrict__ a = reinterpret_cast<const float*>(P.a + (rb ? item.a0[1] : item.a0[0]) + (2 * k & 15));  // (Im: the next row)
     const float* __restrict__ u = reinterpret_cast<const float*>(P.u + item.u0);
     const float* __restrict__ xb = g.x + b * g.L;
-    const float* __restrict__ y0 = Y + tm.frame_row(fi) * r;
+    const int y0 = tm.frame_row(fi) * r;
+    auto coordinate = [&](int i) {
+      if (!split) return Y[y0 + i];
+      float v = 0.f;
+      for (int l = 2; l >= 0; --l) v += __builtin_bit_cast(float, (unsigned)Yb[l * p_words + y0 + i] << 16);
+      return v;
+    };
     const int first = own.x / hop - item.j0, last = (own.y - 1) / hop - item.j0;  // hop-blocks of the bin's own taps
     // of hop-block j: its own columns, coefficients of function i, sample and weight of column c
     auto begin = [&](int j) { const int c = own.x - (item.j0 + j) * hop; return c > 0 ? c : 0; };
@@ -538,7 +580,7 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
     bool met = false;
 #pragma unroll 1
     for (int j = first; j <= last; ++j) {
-      if (finite(y0[j * r])) continue;
+      if (finite(coordinate(j * r))) continue;
 #pragma unroll 1
       for (int c = begin(j); c < end(j) && !(re != re && im != im); ++c) {
         const float x = sample(j, c);
@@ -556,7 +598,7 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       float yr = 0.f, yi = 0.f;
 #pragma unroll 1
       for (int i = 0; i < r; ++i) {
-        const float y = y0[j * r + i];
+        const float y = coordinate(j * r + i);
         float ar, ai;
         coefficients(j, i, ar, ai);
         fine = fine && finite(y);

@@ -342,9 +342,8 @@ nna_status run_conv_fold(const nna_plan* sub, const float* x, long long B, long 
 // item hold two such blocks); smaller tiles spread a short batch over the chip.  Two workgroups per CU want 80 KB of LDS each; a
 // tile cut below three quarters for that takes one workgroup's 156 KB instead.  False: not a launch for this kernel.  It is one
 // where the form that runs otherwise (folded about the centres, or tap by tap) has fewer workgroups than there are CUs (its time over
-// the other's, batches of 50 to 13,000 frames, MI355X: 0.02 .. 0.9), or takes 1.43 times the multiply-adds, unfilled tiles and the
-// first stage's overlap counted (theirs over the other's 0.1 .. 0.5: time 0.04 .. 0.73, 0.51 .. 0.62: 0.53 .. 0.93, 0.63 .. 0.69: 0.7
-// .. 1.06, 0.71 .. 0.81: 0.7 .. 1.23; 13,000 to 400,000 frames).
+// the other's, batches of 50 to 13,000 frames, MI355X: 0.02 .. 0.9), or takes 1.25 times the multiply-adds, unfilled tiles and the
+// first stage's overlap counted (theirs over the other's 0.22 .. 0.55, 86,000 frames and more: time 0.16 .. 0.46; 0.76: 0.82).
 bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::CqlParams& P) {
   const int n_items = (int)sub->h_litems.size(), n_basis = (int)std::count_if(sub->h_litems.begin(), sub->h_litems.end(), [](const nna::CqlItem& it) { return it.r != 0; });
   P.lds_floats = 0;
@@ -386,7 +385,7 @@ bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::Cq
   const bool folds = Mf >= 1 && 2 * Mf >= M0;
   const int M = folds ? Mf : M0;
   if (M < 1 || (n_frames + M - 1) / M * (long long)(folds ? sub->h_qitems.size() : sub->h_items.size()) < 256) return true;
-  return cost <= 0.7 * 0.5 * (folds ? sub->exec_flops_cqf : sub->exec_flops) * CQ_FRAMES / M;
+  return cost <= 0.8 * 0.5 * (folds ? sub->exec_flops_cqf : sub->exec_flops) * CQ_FRAMES / M;
 }
 
 nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
