@@ -1174,28 +1174,27 @@ bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy)
   return copy.lowrank;
 }
 
-// The items' weights as the matrix pipe takes them: every two fragments of 16 taps as one of 32, [.. one fragment ..][3 planes][64 lanes],
-// a lane's eight values in an octet of bfloat16, so fragment pair i of h_lu and h_la starts at 192 i octets.
-void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<unsigned>& a) {
-  auto round = [](float v) {  // to the nearest bfloat16, ties to even; finite values
+// The three bfloat16 of a float32 (each to nearest, ties to even; finite values) into half `e` of a word of every plane
+static void put_parts(float v, unsigned* word, size_t plane, int e) {
+  for (int l = 0; l < 3; ++l) {
     unsigned b;
     std::memcpy(&b, &v, 4);
     b += 0x7fff + ((b >> 16) & 1);
-    return b & 0xffff0000u;
-  };
+    b &= 0xffff0000u;
+    float part;
+    std::memcpy(&part, &b, 4);
+    v -= part;
+    word[l * plane] |= e ? b : b >> 16;
+  }
+}
+
+// The items' weights as the matrix pipe takes them: every two fragments of 16 taps as one of 32, [.. one fragment ..][3 planes][64 lanes],
+// a lane's eight values in an octet of bfloat16, so fragment pair i of h_lu and h_la starts at 192 i octets.
+void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<unsigned>& a) {
   // first: the pair's first fragment; gap: floats from it to the second
   auto octets = [&](const float* first, size_t gap, unsigned* out) {
     for (int lane = 0; lane < 64; ++lane)
-      for (int e = 0; e < 8; ++e) {
-        float v = first[(e / 4) * gap + 4 * lane + e % 4];
-        for (int l = 0; l < 3; ++l) {
-          const unsigned b = round(v);
-          float part;
-          std::memcpy(&part, &b, 4);
-          v -= part;
-          out[(l * 64 + lane) * 4 + e / 2] |= e % 2 ? b : b >> 16;
-        }
-      }
+      for (int e = 0; e < 8; ++e) put_parts(first[(e / 4) * gap + 4 * lane + e % 4], out + lane * 4 + e / 2, 256, e % 2);
   };
   u.assign(p->h_lu.size() / 2 * 3, 0u);
   a.assign(p->h_la.size() / 2 * 3, 0u);
@@ -1488,6 +1487,19 @@ void build_fir_bank(nna_plan* p, int fir_taps) {
   for (int v = ve_lo; v <= ve_hi; ++v) p->h_fir_he[v - ve_lo] = (float)p->h_fir[half + 2 * v];
   for (int v = vo_lo; v <= vo_hi; ++v) p->h_fir_ho[v - vo_lo] = (float)p->h_fir[half + 2 * v + 1];
   p->fir_mode = half_band ? 1 : 0;
+  // fir_split_kernel's matrix, lane (q, r), element e of step s: tap 32 s + 8 q + e of output r.  Its five steps cost the same for every
+  // filter, the other kernel's time is its taps' (1,770 x 88,200 samples, 168 bins, the other -> this one, us: 131 taps 2,321 -> 2,193,
+  // 161 2,145 -> 2,003, 193 2,428 -> 2,190, 257 2,386 -> 2,001, 289 2,658 -> 2,197; 127 taps with the other 2,060).
+  const int no = (int)p->h_fir_ho.size();
+  if (half_band && no > 64 && no + 15 <= 32 * nna::FIRM_STEPS) {
+    p->h_fir_planes.assign(nna::FIRM_STEPS * 3 * 64 * 4, 0u);
+    for (int s = 0; s < nna::FIRM_STEPS; ++s)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int e = 0; e < 8; ++e) {
+          const int k = 32 * s + 8 * (lane >> 4) + e - (lane & 15);
+          if (k >= 0 && k < no) put_parts(p->h_fir_ho[k], &p->h_fir_planes[(s * 192 + lane) * 4 + e / 2], 256, e % 2);
+        }
+  }
   // flops per frame of FIR_ROWS output samples: the taps kept
   p->alg_flops = 2.0 * ((ve_hi - ve_lo + 1) + (vo_hi - vo_lo + 1)) * FIR_ROWS;
   p->exec_flops = 2.0 * (double)(p->h_fir_he.size() + p->h_fir_ho.size()) * FIR_ROWS;

@@ -37,6 +37,15 @@ __device__ __forceinline__ Planes split8(const f32x4 (&v)[2]) {
   return o;
 }
 
+// sum + the 32 products of two octets a lane, small terms first
+__device__ __forceinline__ f32x4 multiply_octets(const u32x4 (&w)[3], const Planes& x, f32x4 sum) {
+  constexpr int lw[6] = {2, 1, 0, 1, 0, 0}, lx[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+  for (int m = 0; m < 6; ++m)
+    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[lw[m]]), __builtin_bit_cast(bf16x8, x.p[lx[m]]), sum, 0, 0, 0);
+  return sum;
+}
+
 // ---------------------------------------------------------------------------------------
 // Frame tile <-> LDS row mapping.  A tile of consecutive global frames f0.. may span several
 // waveforms ("segments"); each segment owns (its frames + extra) consecutive LDS rows.

@@ -36,6 +36,7 @@ struct nna_plan {
   // the decimation kernel's taps: he[k] = h[half + 2 (fir_ve0 + k)] on the even samples, ho[k] = h[half + 2 (fir_vo0 + k) + 1]
   // on the odd ones, each zero padded to a multiple of eight
   std::vector<float> h_fir_he, h_fir_ho;
+  std::vector<unsigned> h_fir_planes;  // FirParams::hp
   int fir_ve0 = 0, fir_vo0 = 0;
   float* d_fir_he = nullptr;
   float* d_fir_ho = nullptr;
@@ -217,6 +218,7 @@ struct nna_plan {
   int* d_lsteps = nullptr;
   double lr_direct = 0;  // multiply-adds per frame of the kernels that stay as they are
   float* d_lu = nullptr;
+  unsigned* d_fir_planes = nullptr;
   unsigned *d_lub = nullptr, *d_lab = nullptr;  // lowrank_planes
   float* d_la = nullptr;
   nna::CqlItem* d_litems = nullptr;

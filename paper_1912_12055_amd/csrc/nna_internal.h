@@ -460,12 +460,14 @@ hipError_t launch_bw_wave(const BwParams& p, hipStream_t stream);      // gx += 
 // decimation by two on the vector ALUs (fir_decimate_kernel)
 constexpr int FIR_T = 8;                // outputs per thread
 constexpr int FIR_TILE = 256 * FIR_T;   // outputs per workgroup
+constexpr int FIRM_STEPS = 5;           // of 32 odd samples, fir_split_kernel
 struct FirParams {
   const float* x;        // [B, L]
   float* y;              // [B, Ln], Ln = ceil(L / 2)
   long long B, L, Ln;
   const float* he;       // taps on the even samples, he[k] = h[half + 2 (ve0 + k)], zero padded to a multiple of 8
   const float* ho;       // taps on the odd samples, ho[k] = h[half + 2 (vo0 + k) + 1], likewise
+  const unsigned* hp;    // fir_split_kernel: [FIRM_STEPS][3 planes][64 lanes][4 words], the Toeplitz matrix of ho; NULL: the other kernel
   int ne, no;            // padded tap counts
   int ve0, vo0;          // first v of each tap list (<= 0)
   int lds_stream;        // floats of LDS per stream: (FIR_TILE + (span of v) + 8) * 9 / 8, rounded up

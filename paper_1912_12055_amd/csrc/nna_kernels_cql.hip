@@ -10,19 +10,25 @@
 //
 // Short kernels, where the first stage alone would cost more than their taps, stay as they are: direct items of up to 32 bins.
 //
-// A workgroup takes one item (16 bins) and one tile of 64 FB frames.  Stage 1 (v_mfma_f32_16x16x4_f32, basis rows x hop-blocks)
-// reads its hop-blocks from the waveform straight into registers in operand order -- sixteen hops per load, 64 bytes of each --
-// and writes y to LDS, a hop's r coordinates in a row.  Stage 2 then is the convolution of the direct kernel with a hop of r
-// samples: the taps of a frame are r J consecutive words of LDS, so r needs no padding to the sixteen taps of a step, only to 4
-// modulo 8, which keeps the rows of sixteen frames on different banks.
+// A workgroup takes one item (16 bins) and one tile of 64 FB frames.  Stage 1 (basis rows x hop-blocks) reads its hop-blocks from
+// the waveform straight into registers in operand order -- sixteen hops per load, 64 bytes of each -- and writes y to LDS, a hop's r
+// coordinates in a row.  Stage 2 then is the convolution of the direct kernel with a hop of r samples: the taps of a frame are r J
+// consecutive words of LDS, so r needs no padding to the taps of a step, only to 4 modulo 8, which keeps the rows of sixteen frames on
+// different banks.
 //
-// Every sum is taken in blocks of 16 products (32 in stage 1), each from zero and then added to a total: a chain of a thousand
+// Both run on v_mfma_f32_16x16x32_bf16, every float32 exact as three bfloat16 and the six products that matter of nine: 32 taps in 96
+// cycles of a SIMD's pipe against 256 as eight v_mfma_f32_16x16x4_f32.  The weights are split with the plan, the samples on the way
+// into the instruction, the coordinates once, on the way into LDS, where six bytes a coordinate fit.
+//
+// Every sum is taken in blocks of 32 products (six instructions), each from zero and then added to a total: a chain of a thousand
 // roundings was off by up to 9e-7 of a bin's norm, more than the folded kernel's half as many in the bins taken tap by tap; the
-// blocks are off by 3e-7 at most, and the additions hide behind the matrix instructions (within 3 % either way).
+// blocks are off by 3e-7 at most.  Against 64 bits the bfloat16 form's errors are 0.55 .. 0.85 of the float32 instruction's.
 //
-// Bound by the float32 matrix pipe (two thirds busy at the batch below); a short batch by latency, a workgroup or two per CU.
-// 1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms folded about the centres -> 8.25 ms; 16 x 220,500, 84 bins
-// of 12 per octave: 300 -> 67 us; the dense composed kernels of the frequency-domain layer (16 x 220,500, 32,768 taps): 566 -> 182 us.
+// Bound by no one pipe at the batch below: matrix instructions, the samples' splits on the vector ALUs and the weights' loads take
+// turns; a short batch by latency, a workgroup or two per CU.  1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms
+// folded about the centres, 8.25 here in float32, 6.59 in bfloat16 with every coordinate split by each frame that reads it, now 5.74;
+// 16 x 220,500, 84 bins of 12 per octave: 300 -> 67.8 -> 53.8 us; the dense composed kernels of the frequency-domain layer (16 x
+// 220,500, 32,768 taps): 566 -> 183 -> 138 us.
 #include <type_traits>
 
 #include "nna_device.h"
@@ -76,15 +82,6 @@ __device__ __forceinline__ unsigned store_bins(const CqlParams& P, const CqlItem
       }
   }
   return odd;
-}
-
-// sum + the 32 products of two octets a lane, small terms first
-__device__ __forceinline__ f32x4 multiply_octets(const u32x4 (&w)[3], const Planes& x, f32x4 sum) {
-  constexpr int lw[6] = {2, 1, 0, 1, 0, 0}, lx[6] = {0, 1, 2, 0, 1, 0};
-#pragma unroll
-  for (int m = 0; m < 6; ++m)
-    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[lw[m]]), __builtin_bit_cast(bf16x8, x.p[lx[m]]), sum, 0, 0, 0);
-  return sum;
 }
 
 // Short kernels, tap by tap.

@@ -83,6 +83,8 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
     if (s == NNA_OK && !p->h_fir_he.empty()) {
       s = upload(&p->d_fir_he, p->h_fir_he.data(), p->h_fir_he.size() * sizeof(float), "decimation taps");
       if (s == NNA_OK) s = upload(&p->d_fir_ho, p->h_fir_ho.data(), p->h_fir_ho.size() * sizeof(float), "decimation taps");
+      if (s == NNA_OK && !p->h_fir_planes.empty())
+        s = upload(&p->d_fir_planes, p->h_fir_planes.data(), p->h_fir_planes.size() * sizeof(unsigned), "decimation taps");
     }
     if (s == NNA_OK && p->kind == NNA_KIND_CQT) {
       s = upload(&p->d_items, p->h_items.data(), p->h_items.size() * sizeof(nna::CqtItem), "cqt item table");
@@ -917,6 +919,7 @@ void nna_plan_destroy(nna_plan* plan) {
       (void)hipFree(plan->d_fft_melw);
       (void)hipFree(plan->d_bankf);
       (void)hipFree(plan->d_fir_he);
+      (void)hipFree(plan->d_fir_planes);
       (void)hipFree(plan->d_fir_ho);
       (void)hipFree(plan->d_wn);
       (void)hipFree(plan->d_wq);

@@ -477,6 +477,7 @@ nna_status run_fir(const nna_plan* fir, const float* x, long long B, long long L
   P.Ln = Ln;
   P.he = fir->d_fir_he;
   P.ho = fir->d_fir_ho;
+  P.hp = fir->d_fir_planes;
   P.ne = (int)fir->h_fir_he.size();
   P.no = (int)fir->h_fir_ho.size();
   P.ve0 = fir->fir_ve0;

@@ -1,0 +1,48 @@
+"""The decimation filter of the downsampling constant-Q layers on the bfloat16 matrix pipe: lengths at the edges of its tiles (2,048 outputs,
+256 a wave, 16 a column, rows that are not aligned), the longest and shortest filters that run there, samples that are not finite."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+KW = dict(sr=22050, hop=64, fmin=2000.0, n_bins=24, bins_per_octave=12)  # the lower octave reads the filter's output
+
+
+@pytest.mark.parametrize("fir", [0, 131, 289])
+@pytest.mark.parametrize("B,L", [(3, 513), (2, 767), (2, 4064), (1, 4095), (5, 4097), (2, 8192), (3, 8706), (700, 4100)])
+def test_lengths(B, L, fir):
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] fir {fir} {B}x{L}", file=sys.stderr, flush=True)
+    x = np.random.default_rng([7, L, fir]).standard_normal((B, L)).astype(np.float32)
+    plan = nb.nna_plan_cqt2010v2(fir_taps=fir, fmt=nb.NNA_OUT_COMPLEX, device=0, **KW)
+    got = nb.nna_cqt2010v2(plan, torch.from_numpy(x).cuda()).cpu().numpy()[-3:]
+    ref = oracle.cqt2010v2(x[-3:], fir_taps=fir or oracle.FIR_TAPS, fmt=oracle.COMPLEX, **KW)
+    low = slice(0, 24)
+    # 130 products and 128 taps in float32, each sum off by less than sqrt(130) / 2 roundings of 6e-8: 1e-6 of the norm
+    assert np.linalg.norm(got[:, low] - ref[:, low]) <= 1e-6 * np.linalg.norm(ref[:, low])
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 3.4e38])
+def test_reach_of_one_sample(bad):
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] fir nonfinite {bad}", file=sys.stderr, flush=True)
+    B, L, at, b = 3, 9001, 4097, 1
+    x = np.random.default_rng(8).standard_normal((B, L)).astype(np.float32)
+    x[b, at] = 0.0
+    plan = nb.nna_plan_cqt2010v2(fmt=nb.NNA_OUT_COMPLEX, device=0, **KW)
+    clean = nb.nna_cqt2010v2(plan, torch.from_numpy(x).cuda()).cpu().numpy()
+    x[b, at] = bad
+    got = nb.nna_cqt2010v2(plan, torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.array_equal(np.delete(got, b, 0), np.delete(clean, b, 0))
+    # a frame of the lower octave is 128 taps of every second sample about 64 t, each 128 samples either side through the filter
+    t = 64 * np.arange(got.shape[2])
+    clear = np.abs(t - at) > 2 * 64 + 128 + 2
+    assert np.abs(got[b][:24, clear] - clean[b][:24, clear]).max() <= 1e-5 * np.abs(clean[b][:24]).max()
+    if not np.isfinite(bad):
+        assert not np.isfinite(got[b][:24, np.abs(t - at) < 64]).any()
