@@ -1198,7 +1198,8 @@ void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<uns
   };
   u.assign(p->h_lu.size() / 2 * 3, 0u);
   a.assign(p->h_la.size() / 2 * 3, 0u);
-  for (const nna::CqlItem& it : p->h_litems) {
+  for_each_parallel((int)p->h_litems.size(), [&](int k) {
+    const nna::CqlItem& it = p->h_litems[k];
     const size_t u0 = (size_t)it.u0 * 4;
     if (it.r) {
       for (int i = 0; i < p->hop / 32 * it.n_ib; ++i) octets(&p->h_lu[u0 + (size_t)i * 512], 256, &u[u0 / 2 * 3 + (size_t)i * 768]);
@@ -1210,7 +1211,7 @@ void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<uns
         for (int b = 0; b < 4; ++b)
           octets(&p->h_lu[u0 + (size_t)i * 2048 + b * 256], 1024, &u[u0 / 2 * 3 + ((size_t)i * 4 + b) * 768]);
     }
-  }
+  });
 }
 
 // [2 n_bins][K]: the kernels of `p`'s items, multiplied out

@@ -100,8 +100,12 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
         if (s == NNA_OK) s = upload(&p->d_la, p->h_la.data(), p->h_la.size() * sizeof(float), "hop-block coefficients");
         if (s == NNA_OK) {
           std::vector<unsigned> u, a;
-          lowrank_planes(p, u, a);
-          s = upload(&p->d_lub, u.data(), u.size() * sizeof(unsigned), "hop-block basis");
+          try {
+            lowrank_planes(p, u, a);
+          } catch (const std::bad_alloc&) {
+            s = fail(NNA_ERR_ALLOC, "out of host memory while building the hop-block basis");
+          }
+          if (s == NNA_OK) s = upload(&p->d_lub, u.data(), u.size() * sizeof(unsigned), "hop-block basis");
           if (s == NNA_OK) s = upload(&p->d_lab, a.data(), a.size() * sizeof(unsigned), "hop-block coefficients");
         }
         if (s == NNA_OK) s = upload(&p->d_lsteps, p->h_lsteps.data(), p->h_lsteps.size() * sizeof(int), "step table");
