@@ -24,8 +24,8 @@
 // roundings was off by up to 9e-7 of a bin's norm, more than the folded kernel's half as many in the bins taken tap by tap; the
 // blocks are off by 3e-7 at most.  Against 64 bits the bfloat16 form's errors are 0.55 .. 0.85 of the float32 instruction's.
 //
-// Bound by no one pipe at the batch below: matrix instructions, the samples' splits on the vector ALUs and the weights' loads take
-// turns; a short batch by latency, a workgroup or two per CU.  1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms
+// Bound by no one pipe at the batch below: the samples' splits keep the vector ALUs 52 % busy, the matrix pipe is at 39 %; a short batch
+// by latency, a workgroup or two per CU.  1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms
 // folded about the centres, 8.25 here in float32, 6.59 in bfloat16 with every coordinate split by each frame that reads it, now 5.74;
 // 16 x 220,500, 84 bins of 12 per octave: 300 -> 67.8 -> 53.8 us; the dense composed kernels of the frequency-domain layer (16 x
 // 220,500, 32,768 taps): 566 -> 183 -> 138 us.

@@ -15,7 +15,7 @@
 // output the call below takes 0.82 ms, the vector ALUs' time; meeting once a tile and the stores' own instructions add the rest.
 //
 // 1,770 x 176,400 samples, N = 2,048, hop 512 (MI355X): magnitudes 10.1 ms contracted, 2.20 with a tile computed, then stored
-// between two barriers and neighbouring tiles 29 us apart (an output line left its L2 half written, 3.65 GB for 2.50), now 1.50;
+// between two barriers and neighbouring tiles 29 us apart, now 1.51 (either way 3.66 GB are written for 2.50: runs of half a line);
 // N = 1,024, hop 256, complex: 4.02 -> 2.35.  Mel, 64 x 110,250, 128 bands: 808 us contracted, 48 -> 39; 1,770 x 80,000,
 // N = 4,096, 512 bands: 34.9 ms, 2.02 -> 1.80.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles read from the caches for
 // every frame with four waves per SIMD (2.85 ms: the vector memory path saturates), from LDS with four waves per SIMD (spills,
