@@ -265,8 +265,8 @@ nna_status nna_mel_with_stft(const nna_plan* plan, const float* x_dev, long long
                              float* mel_dev, float* spec_dev, void* hip_stream);
 
 /* out_dev[B, n_bins, T] = constant-Q spectrogram of x_dev[B, L]; plan from nna_plan_cqt.  A sample that is not finite makes
- * the outputs whose kernels reach it not finite: of a short kernel, the sixteen-tap steps it shares with seven neighbours (the
- * forms are at nna_plan_cqt), else the kernel's own taps. */
+ * the outputs whose kernels reach it not finite: with kernels cut at the hops' boundaries, by the kernel's own taps, else by the
+ * sixteen-tap steps it shares with seven neighbours (the forms are at nna_plan_cqt). */
 nna_status nna_cqt(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                    void* hip_stream);
 

@@ -235,7 +235,46 @@ __device__ __forceinline__ void direct_item(const CqlParams& P, const CqlPart& p
       d = dn;
     }
   }
-  store_bins<FB, RB>(P, item, acc, valid, f0, wave, q, n);
+  // A sample that is not finite, or so large that its first bfloat16 is not, makes every sum that holds its step of 32 taps NaN.  Such a
+  // sum is taken again over the bin's own taps in float32: the samples that are not finite alone if there are any, else all of them.
+  // (66 x 481,793 samples, 168 bins, every thousandth NaN: 16 -> 25 ms; none: 0.71 either way.)
+  unsigned odd = store_bins<FB, RB>(P, item, acc, valid, f0, wave, q, n);
+#pragma unroll 1
+  while (odd) {
+    const int bit = __builtin_ctz(odd), rb = (bit >> 1) % RB, k = 8 * rb + 2 * q + (bit & 1), fi = (wave * FB + (bit >> 1) / RB) * 16 + n;
+    odd &= odd - 1;
+    const long long f = f0 + fi, b = f / g.T;
+    const int t = (int)(f - b * g.T);
+    const int2 own = P.support[item.bin0 + k];
+    const float* __restrict__ xw = g.x + b * g.L;
+    const float* __restrict__ u = reinterpret_cast<const float*>(P.u + item.u0 + rb * 64 + (2 * k & 15));  // (Im: the next row)
+    float re = 0.f, im = 0.f;
+    bool met = false;
+#pragma unroll 1
+    for (int all = 0; all < 2 && !met; ++all)
+#pragma unroll 1
+      for (int tap0 = own.x; tap0 < own.y && !(re != re && im != im); tap0 += 8) {
+        float v[8];
+        bool any = all;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          v[i] = xw[reflect_clamped(t * hop - g.pad + (tap0 + i < own.y ? tap0 + i : tap0), L)];
+          any = any || !finite(v[i]);
+        }
+        if (!any) continue;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          if (tap0 + i >= own.y || (!all && finite(v[i]))) continue;
+          // the tap's step of 16: those of 32 columns follow each other by hop-block and half
+          const int at = tap0 + i - item.j0 * hop, j = at / hop, c = at - j * hop, first = chunk0[c / 32];
+          const float* w = u + ((first + 2 * (j - (steps[first] >> 12)) + ((c >> 4) & 1)) * RB * 64 + ((c >> 2) & 3) * 16) * 4 + (c & 3);
+          re += w[0] * v[i];
+          im += w[4] * v[i];
+          met = true;
+        }
+      }
+    store_bin(P, P.out + b * P.out_wave_stride + t, item.bin0 + k, re, im);
+  }
 }
 
 // Kernels as combinations of the item's basis.

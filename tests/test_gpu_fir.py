@@ -46,3 +46,29 @@ def test_reach_of_one_sample(bad):
     assert np.abs(got[b][:24, clear] - clean[b][:24, clear]).max() <= 1e-5 * np.abs(clean[b][:24]).max()
     if not np.isfinite(bad):
         assert not np.isfinite(got[b][:24, np.abs(t - at) < 64]).any()
+
+
+@pytest.mark.parametrize("fir", [131, 255, 257])
+def test_reach_is_the_filters_own_taps(fir):
+    """Outputs of the filter that none of its taps reach a NaN from: seen through the lower octave's kernels, whose steps of sixteen taps
+    begin at every 32nd output, for a NaN on each of 32 consecutive odd samples."""
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] fir reach {fir}", file=sys.stderr, flush=True)
+    plan = nb.nna_plan_cqt2010v2(fir_taps=fir, fmt=nb.NNA_OUT_COMPLEX, device=0, **KW)
+    top = nb.nna_plan_part(plan, 0)
+    lengths, half = nb.nna_plan_cqt_lengths(top), top.info()["taps"] // 2
+    B, L = 32, 9001
+    x = np.tile(np.random.default_rng(9).standard_normal(L).astype(np.float32), (B, 1))
+    at = 4097 + 2 * np.arange(B)
+    x[np.arange(B), at] = np.nan
+    got = np.isfinite(nb.nna_cqt2010v2(plan, torch.from_numpy(x).cuda()).cpu().numpy())[:, :24].reshape(B, 12, 2, -1)
+    y = np.arange(L // 2 + 1)
+    reached = np.abs(2 * y[None] - at[:, None]) <= fir // 2  # (an odd offset: never a tap that is zero)
+    for block in (slice(0, 8), slice(8, 12)):  # bins whose kernels share their steps
+        n = int(lengths[block].max())
+        lo, hi = (half - (n + 1) // 2) // 16 * 16, (half + n // 2 + 15) // 16 * 16
+        for t in range(got.shape[3]):
+            window = slice(max(0, 32 * t - half + lo), max(0, 32 * t - half + hi))
+            clear = ~reached[:, window].any(1)
+            assert got[clear, block, :, t].all(), (fir, t, at[clear][~got[clear, block, :, t].all((1, 2))])
