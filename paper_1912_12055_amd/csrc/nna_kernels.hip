@@ -1191,7 +1191,7 @@ __global__ __launch_bounds__(256, 3) void fir_split_kernel(const FirParams P, un
         const float* __restrict__ xb = P.x + b * P.L;
         float sum = centre * sample(xb, 2 * (m + e));
 #pragma unroll 1
-        for (int k = 0; k < P.no; ++k) sum += P.ho[k] * sample(xb, 2 * (m + e + P.vo0 + k) + 1);
+        for (int k = 0; k < -2 * P.vo0; ++k) sum += P.ho[k] * sample(xb, 2 * (m + e + P.vo0 + k) + 1);  // (P.no counts padding, too)
         acc[e] = sum;
       }
       float* __restrict__ op = P.y + b * P.Ln + m;
