@@ -38,7 +38,6 @@ namespace {
 
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
 using std::integral_constant;
-__device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) < __builtin_inff(); }
 using True = integral_constant<bool, true>;
 using False = integral_constant<bool, false>;
 

@@ -72,3 +72,29 @@ def test_reach_is_the_filters_own_taps(fir):
             window = slice(max(0, 32 * t - half + lo), max(0, 32 * t - half + hi))
             clear = ~reached[:, window].any(1)
             assert got[clear, block, :, t].all(), (fir, t, at[clear][~got[clear, block, :, t].all((1, 2))])
+
+
+def test_cost_of_samples_that_are_not_finite():
+    """A recording full of them, or with one in every frame, keeps to a small multiple of the time of one without."""
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print("[case] fir nonfinite cost", file=sys.stderr, flush=True)
+    plan = nb.nna_plan_cqt2010v2(fmt=nb.NNA_OUT_COMPLEX, device=0, **KW)
+    clean = torch.randn((400, 100000), generator=torch.Generator().manual_seed(1)).cuda()
+    some = clean.clone()
+    some[:, 137::1000] = float("nan")
+
+    def milliseconds(x):
+        best = float("inf")
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            nb.nna_cqt2010v2(plan, x)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    base = milliseconds(clean)  # (tap by tap from memory: 28 and 15 times as long)
+    assert milliseconds(torch.full_like(clean, float("nan"))) < 7 * base
+    assert milliseconds(some) < 7 * base
