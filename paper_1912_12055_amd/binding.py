@@ -154,6 +154,7 @@ class Plan:
         self.handle = handle
         self.device = device
         self.owner = owner  # a part of another plan: that plan owns the handle (and is kept alive here)
+        self.bank_sets = 0  # calls of nna_plan_set_bank
 
     def __del__(self):
         h, self.handle = getattr(self, "handle", None), None
@@ -438,6 +439,7 @@ def nna_plan_set_bank(plan: Plan, W, stream=None):
     if not (W.is_cuda and W.dtype.is_floating_point and W.element_size() == 4 and W.is_contiguous()
             and tuple(W.shape) == shape and W.device.index == plan.device):
         raise TypeError(f"W must be a contiguous float32 CUDA tensor of shape {shape} on the plan's device")
+    plan.bank_sets += 1
     _check(lib().nna_plan_set_bank(plan.handle, W.data_ptr(), _stream_of(W, stream)))
 
 

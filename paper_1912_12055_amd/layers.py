@@ -67,9 +67,16 @@ def _forward(ctx, plan, x, keep, run):
     if keep and x.is_cuda and x.dim() == 2 and x.shape[1] >= 4 and 0 < nb.nna_kept_bytes(plan, *x.shape) <= _KEPT_BYTES:
         out, kept = nb.nna_forward_keep(plan, x)
         ctx.save_for_backward(x, kept)
+        ctx.bank_sets = plan.bank_sets
         return out
     ctx.save_for_backward(x)
     return run(plan, x)
+
+
+def _saved(ctx):
+    """(x, what was kept or None): a bank set since the forward pass is the one the gradients are taken with, so C is computed again."""
+    x, *kept = ctx.saved_tensors
+    return x, kept[0] if kept and ctx.bank_sets == ctx.layer.plan.bank_sets else None
 
 
 def _recorded(*tensors):
@@ -87,10 +94,10 @@ class _StftFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, gout):
-        x, *kept = ctx.saved_tensors
+        x, kept = _saved(ctx)
         need_x, need_w = ctx.needs_input_grad[0], ctx.needs_input_grad[1]
-        if kept:
-            _, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept[0], want_gw=need_w, want_gx=need_x)
+        if kept is not None:
+            _, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept, want_gw=need_w, want_gx=need_x)
         else:
             gw, gx = nb.nna_stft_backward(ctx.layer.plan, x, gout.contiguous(), want_gw=need_w, want_gx=need_x)
         return gx, gw, None, None
@@ -120,11 +127,11 @@ class _MelFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, gout):
-        x, *kept = ctx.saved_tensors
+        x, kept = _saved(ctx)
         need_x, need_w, need_m = ctx.needs_input_grad[:3]
         want = dict(want_gmelw=need_m, want_gw=need_w, want_gx=need_x)
-        if kept:
-            gm, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept[0], **want)
+        if kept is not None:
+            gm, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept, **want)
         else:
             gm, gw, gx = nb.nna_mel_backward(ctx.layer.plan, x, gout.contiguous(), **want)
         return gx, gw, gm, None, None
@@ -232,10 +239,10 @@ class _CqtFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, gout):
-        x, *kept = ctx.saved_tensors
+        x, kept = _saved(ctx)
         need_x, need_w = ctx.needs_input_grad[0], ctx.needs_input_grad[1]
-        if kept:
-            _, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept[0], want_gw=need_w, want_gx=need_x)
+        if kept is not None:
+            _, gw, gx = nb.nna_backward_kept(ctx.layer.plan, x, gout.contiguous(), kept, want_gw=need_w, want_gx=need_x)
         else:
             gw, gx = nb.nna_cqt_backward(ctx.layer.plan, x, gout.contiguous(), want_gw=need_w, want_gx=need_x)
         return gx, gw, None, None

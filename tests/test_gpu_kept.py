@@ -74,3 +74,27 @@ def test_layers(kind, monkeypatch):
     monkeypatch.setattr(layers.nb, "nna_forward_keep", None)  # without a backward pass to come nothing is kept
     with torch.no_grad():
         assert torch.equal(layer(x), out)
+
+
+@pytest.mark.parametrize("kind", ["stft", "mel", "cqt"])
+def test_bank_set_between_the_passes(kind):
+    """A forward pass, new kernels, another forward pass, then the first one's backward pass: gradients with the new kernels throughout."""
+    import torch
+    from paper_1912_12055_amd import binding as nb, layers
+    print(f"[case] kept bank {kind}", file=sys.stderr, flush=True)
+    made = {"stft": lambda: layers.STFT(n_fft=512, hop_length=128, output_format="Power", trainable=True),
+            "mel": lambda: layers.MelSpectrogram(n_fft=512, hop_length=128, n_mels=40, trainable_mel=True, trainable_STFT=True),
+            "cqt": lambda: layers.CQT1992v2(sr=8000, hop_length=32, fmin=80.0, n_bins=20, trainable=True)}
+    layer = made[kind]()
+    bank = layer.cqt_kernels if kind == "cqt" else layer.wsin_wcos
+    gen = torch.Generator().manual_seed(5)
+    x = torch.randn((2, 5001), generator=gen).cuda().requires_grad_()
+    out = layer(x)
+    gout = torch.randn(out.shape, generator=gen).cuda()
+    with torch.no_grad():
+        bank.mul_(1.0 + 0.1 * torch.randn(bank.shape, generator=gen).cuda())
+    layer(x[:1].detach())
+    got = torch.autograd.grad(out, [bank, x], gout)
+    backward = {"stft": nb.nna_stft_backward, "mel": nb.nna_mel_backward, "cqt": nb.nna_cqt_backward}[kind]
+    for g, want in zip(got, backward(layer.plan, x.detach(), gout)[-2:]):
+        _close(g, want)
