@@ -171,9 +171,13 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
   } catch (const std::bad_alloc&) {
     return fail(NNA_ERR_ALLOC, "out of host memory");
   }
-  // launch_cqt_few's time goes by frames times all steps of 16 taps, cqt_kernel's, while its workgroups are fewer than the chip holds,
-  // by the longest workgroup's steps.  Training step over cqt_kernel's by frames x steps / longest (MI355X): 84 bins, hop 512: 0.71 at
-  // 28,000, 0.88 at 46,000, 1.13 at 69,000; 120 bins, hop 256: 0.98 at 97,000, 1.11 at 194,000.
+  // cqt_few_tile_kernel's time goes by frames times all steps of 16 taps, cqt_kernel's, while its workgroups are fewer than the chip holds,
+  // by the longest workgroup's steps.  Its time over cqt_kernel's by frames x steps / longest (MI355X, nna_cqt): 84 bins, hop 512: 0.75 at
+  // 36,000, 0.86 at 48,000, 0.98 at 55,000, 1.23 at 70,000; 120 bins, hop 256: 0.74, 0.93, 0.95, 1.17.
+  // cqt_few_kernel reads the samples of every shift from memory, which costs the more the more shifts cqt_kernel serves from one tile: even
+  // at 52,000 (24 shifts), 43,000 (48), 30,000 (60), 25,000 (88), 14,000 (132), 13,500 (180); past that line 1.2 at 25,000 and 1.9 at 50,000
+  // (136 shifts).  Where cqt_kernel takes one shift a tile (hop 441: 0.24 at 15,000, 0.58 at 48,000, 0.84 at 70,000) or its tiles hold fewer
+  // than 128 frames (214 shifts, 82 frames: 0.84 at 5,000, 1.0 at 12,000, 0.69 at 50,000) it has the other kernel's line.
   long long steps = 0, longest = 1;
   for (const nna::CqtItem& item : plan->h_items) {
     long long sum = 0;
@@ -182,6 +186,7 @@ static nna_status make_cqt_trainable(nna_plan* plan) {
     longest = std::max(longest, sum);
   }
   plan->few_frames = 50000 * longest / std::max(1LL, steps);
+  plan->few_frames_untiled = std::min(50000, 2000000 / plan->max_jspan) * longest / std::max(1LL, steps);
   plan->rows_pad = rows_pad;
   plan->kp = kp;
   float* d_logical = nullptr;

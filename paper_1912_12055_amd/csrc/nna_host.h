@@ -226,7 +226,9 @@ struct nna_plan {
   bool runs_lowrank() const { return lowrank && !d_wrm; }
   // trainable CQT plans: index map caller's tensor -> streaming order, each row's tap support, and the
   // tables that let the backward contractions skip what lies outside every support
-  long long few_frames = 0;  // frames below which launch_conv takes the kernel for batches of few workgroups
+  // frames below which launch_conv takes the kernels for batches of few workgroups: with samples through LDS, or straight from memory
+  // beside a cqt_kernel that shares them
+  long long few_frames = 0, few_frames_untiled = 0;
   int* d_cq_map = nullptr;
   int* d_row_lo = nullptr;
   int4* d_few_groups = nullptr;  // launch_cqt_few's tables, or NULL

@@ -406,9 +406,11 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
 }
 
 hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t stream) {
-  if (sub->d_wrm && P.g.n_frames < sub->few_frames) {
+  if (sub->d_wrm) {
     const long long T = P.g.T, rows = nna::CQW_FRAMES + (1 + (nna::CQW_FRAMES - 1 + T - 1) / T) * (sub->few_jspan - 1);
-    return nna::launch_cqt_few(P, sub->d_row_lo, sub->d_row_hi, sub->d_few_groups, sub->d_few_first, rows <= nna::CQW_ROWS ? (int)rows : 0, stream);
+    const bool tiled = sub->d_few_groups && rows <= nna::CQW_ROWS;
+    if (P.g.n_frames < (tiled || !sub->sliding || P.tile_frames < 128 ? sub->few_frames : sub->few_frames_untiled))
+      return nna::launch_cqt_few(P, sub->d_row_lo, sub->d_row_hi, sub->d_few_groups, sub->d_few_first, tiled ? (int)rows : 0, stream);
   }
   return nna::launch_cqt(P, stream);
 }
