@@ -16,7 +16,7 @@ def _close(got, want):
 PLANS = [("stft", "POWER"), ("mel", "POWER"), ("cqt", "MAGNITUDE"), ("cqt", "POWER"), ("cqt", "LOG"), ("cqt", "PHASE")]
 
 
-# frames short of, at and past a block of 32; waveforms that end inside a run of four samples; many frames (the kernel for large batches)
+# frames short of, at and past a block of 32; waveforms that end inside a run of four samples; many frames
 @pytest.mark.parametrize("B,L", [(1, 2100), (3, 4097), (2, 7003), (60, 9001)])
 @pytest.mark.parametrize("kind,fmt", PLANS)
 def test_same_as_recomputed(kind, fmt, B, L):
@@ -39,6 +39,34 @@ def test_same_as_recomputed(kind, fmt, B, L):
         _close(got, ref)
     with pytest.raises(nb.NnaError):
         nb.nna_backward_kept(plan, x, gout, kept[:-256])
+
+
+@pytest.mark.parametrize("kind,hop,n_bins,B,L", [
+    ("large", 32, 31, 200, 9001),     # 56,400 frames, above every line: cqt_kernel
+    ("large", 96, 41, 260, 20003),    # ... its tiles across waveforms, a row block of one bin
+    ("straight", 48, 31, 3, 5001),    # a hop that is no multiple of 32: the kernel that reads samples from memory
+    ("straight", 8, 9, 5, 2051),
+    ("respaced", 100, 131, 3, 7003), ("respaced", 100, 1, 1, 2100), ("respaced", 128, 200, 40, 9001)])
+def test_other_kernels(kind, hop, n_bins, B, L):
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] kept {kind} {hop} {n_bins} {B}x{L}", file=sys.stderr, flush=True)
+    if kind == "respaced":
+        plan = nb.nna_plan_stft_scaled(sr=16000, n_fft=400, hop=hop, freq_scale=nb.NNA_FREQ_LOG, fmin=60.0, fmax=6000.0, freq_bins=n_bins,
+                                       fmt=nb.NNA_OUT_POWER, device=0)
+        run, backward = nb.nna_stft, nb.nna_stft_backward
+    else:
+        plan = nb.nna_plan_cqt(sr=8000, hop=hop, fmin=80.0 if hop > 8 else 400.0, n_bins=n_bins, bins_per_octave=12, fmt=nb.NNA_OUT_LOG, device=0)
+        run, backward = nb.nna_cqt, nb.nna_cqt_backward
+    plan = nb.nna_plan_trainable(plan)
+    gen = torch.Generator().manual_seed(B * L)
+    x = torch.randn((B, L), generator=gen).cuda()
+    out, kept = nb.nna_forward_keep(plan, x)
+    assert torch.equal(out, run(plan, x))
+    gout = torch.randn(out.shape, generator=gen).cuda()
+    _, gw, gx = nb.nna_backward_kept(plan, x, gout, kept)
+    for got, ref in zip((gw, gx), backward(plan, x, gout)):
+        _close(got, ref)
 
 
 def test_plans_that_keep_nothing():
