@@ -434,9 +434,8 @@ hipError_t launch_mel_from_logical(const float* w, float* frag, float* wnyq, flo
                                    int n_pass, int fp, hipStream_t stream);
 hipError_t launch_fill_zero(float* p, long long n, hipStream_t stream);
 hipError_t launch_fill_zero_frames(float* gbuf, long long rows_pad, long long f0, long long f1, hipStream_t stream);
-// G <- the upstream gradient of a complex-format output, re-laid out (see g_from_complex_kernel)
-// G = dLoss/dC of every row and padded frame from the C a forward pass kept, and the upstream gradient; pout (optional): the format of
-// C, [B, out_rows, T].  (kept may be NULL for the complex format, whose derivative needs no C.)
+// G = dLoss/dC of every row and padded frame from the C a forward pass kept, and the upstream gradient; pout (optional, power format):
+// |C|^2, [B, out_rows, T].  Every format but the complex one, whose derivative needs no C; packed: the power format
 struct KeptParams {
   const float* kept;   // [frame / 32][rows_pad][frame % 32]
   const float* gout;   // [B][out_rows][T]
@@ -446,6 +445,7 @@ struct KeptParams {
   int T, out_rows, rows_pad, n_slots, packed, fmt;
 };
 hipError_t launch_g_from_kept(const KeptParams& p, hipStream_t stream);
+// G <- the upstream gradient of a complex-format output, re-laid out (see g_from_complex_kernel)
 hipError_t launch_g_from_complex(float* gbuf, const float* gout, long long n_frames, int T, int out_rows, int rows_pad,
                                  int n_half, int packed, hipStream_t stream);
 hipError_t launch_bank_from_logical(const BankPermuteParams& p, hipStream_t stream);  // logical -> bank, wrm

@@ -166,35 +166,26 @@ __global__ __launch_bounds__(256) void g_from_kept_kernel(const KeptParams P) {
   for (int slot = 64 * blockIdx.y + (threadIdx.x >> 5); slot < 64 * (int)blockIdx.y + 64 && 2 * slot < P.rows_pad; slot += 8) {
     float gr = 0.f, gi = 0.f;
     if (f < P.n_frames && slot < P.n_slots) {
-      const float re = P.kept ? P.kept[at + 64LL * slot] : 0.f, im = P.kept ? P.kept[at + 64LL * slot + 32] : 0.f;
-      const float pw = re * re + im * im;
-      if (P.fmt == NNA_OUT_COMPLEX) {
-        gr = gp[2 * slot * T];
-        gi = gp[(2 * slot + 1) * T];
-      } else if (P.fmt == NNA_OUT_PHASE) {  // d atan2(Im, Re) = (Re dIm - Im dRe) / P
+      const float re = P.kept[at + 64LL * slot], im = P.kept[at + 64LL * slot + 32], pw = re * re + im * im;
+      if (P.fmt == NNA_OUT_PHASE) {  // d atan2(Im, Re) = (Re dIm - Im dRe) / P
         const float s = pw > 0.f ? gp[slot * T] / pw : 0.f;
         gr = -s * im;
         gi = s * re;
-      } else {
-        auto scale = [&](float g, float p) {
-          return P.fmt == NNA_OUT_MAGNITUDE ? grad_scale<NNA_OUT_MAGNITUDE>(g, p)
-                 : P.fmt == NNA_OUT_POWER   ? grad_scale<NNA_OUT_POWER>(g, p)
-                                            : grad_scale<NNA_OUT_LOG>(g, p);
-        };
-        auto format = [&](float p) { return P.fmt == NNA_OUT_MAGNITUDE ? __builtin_amdgcn_sqrtf(p) : p; };  // (pout: these two only)
-        if (slot == 0 && P.packed) {  // the two real bins 0 and n_slots
-          gr = scale(gp[0], re * re) * re;
-          gi = scale(gp[P.n_slots * T], im * im) * im;
-          if (pp) {
-            pp[0] = format(re * re);
-            pp[P.n_slots * T] = format(im * im);
-          }
-        } else {
-          const float s = scale(gp[slot * T], pw);
-          gr = s * re;
-          gi = s * im;
-          if (pp) pp[slot * T] = format(pw);
+      } else if (slot == 0 && P.packed) {  // the two real bins 0 and n_slots of a power spectrogram
+        gr = grad_scale<NNA_OUT_POWER>(gp[0], re * re) * re;
+        gi = grad_scale<NNA_OUT_POWER>(gp[P.n_slots * T], im * im) * im;
+        if (pp) {
+          pp[0] = re * re;
+          pp[P.n_slots * T] = im * im;
         }
+      } else {
+        const float g = gp[slot * T];
+        const float s = P.fmt == NNA_OUT_MAGNITUDE ? grad_scale<NNA_OUT_MAGNITUDE>(g, pw)
+                        : P.fmt == NNA_OUT_POWER   ? grad_scale<NNA_OUT_POWER>(g, pw)
+                                                   : grad_scale<NNA_OUT_LOG>(g, pw);
+        gr = s * re;
+        gi = s * im;
+        if (pp) pp[slot * T] = pw;
       }
     }
     P.gbuf[at + 64LL * slot] = gr;
@@ -879,8 +870,8 @@ hipError_t launch_g_from_kept(const KeptParams& p, hipStream_t stream) {
   clear_stale_error();
   const long long blocks = p.gpitch / 32;
   if (blocks < 1 || blocks > 0x7fffffffLL || p.gpitch % 32 || p.n_frames < 1 || p.n_frames > p.gpitch || p.T < 1 || p.rows_pad < 2 || p.rows_pad % 2 ||
-      2 * p.n_slots > p.rows_pad || (p.fmt == NNA_OUT_COMPLEX ? 2 * p.n_slots : p.packed ? p.n_slots + 1 : p.n_slots) > p.out_rows ||
-      (p.fmt == NNA_OUT_COMPLEX && p.packed) || (!p.kept && p.fmt != NNA_OUT_COMPLEX))
+      2 * p.n_slots > p.rows_pad || (p.packed ? p.n_slots + 1 : p.n_slots) > p.out_rows || !p.kept || p.fmt == NNA_OUT_COMPLEX ||
+      ((p.packed || p.pout) && p.fmt != NNA_OUT_POWER))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(g_from_kept_kernel, dim3((unsigned)blocks, (unsigned)((p.rows_pad + 127) / 128)), dim3(256), 0, stream, p);
   return hipGetLastError();
