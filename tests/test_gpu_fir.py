@@ -27,6 +27,19 @@ def test_lengths(B, L, fir):
     assert np.linalg.norm(got[:, low] - ref[:, low]) <= 1e-6 * np.linalg.norm(ref[:, low])
 
 
+@pytest.mark.parametrize("scale", [2.0 ** -100, 2.0 ** 100])
+def test_range(scale):
+    """Samples as three bfloat16: nothing is lost from 2^-110 up (measured: 1.7e-7 from 1e-33 to 3e37, 2.6e-7 at 1e-34, 1.9e-5 at 1e-36)."""
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] fir range {scale}", file=sys.stderr, flush=True)
+    x = np.random.default_rng(7).standard_normal((2, 8706)).astype(np.float32)
+    plan = nb.nna_plan_cqt2010v2(fmt=nb.NNA_OUT_COMPLEX, device=0, **KW)
+    got = nb.nna_cqt2010v2(plan, torch.from_numpy(x * np.float32(scale)).cuda()).cpu().numpy()[:, :24].astype(np.float64) / scale
+    ref = oracle.cqt2010v2(x, fmt=oracle.COMPLEX, **KW)[:, :24]
+    assert np.linalg.norm(got - ref) <= 1e-6 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), 3.4e38])
 def test_reach_of_one_sample(bad):
     import torch
