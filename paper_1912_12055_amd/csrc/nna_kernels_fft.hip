@@ -209,6 +209,14 @@ __device__ __forceinline__ void store_rows(const float* __restrict__ tile, int p
 #pragma unroll
       for (int i = 0; i < 8; ++i) op[(long long)(r + i) * T] = x[i];
       v += 8;
+    } else if (v + 4 <= v_end) {
+      // (tiles of fewer frames: one row after the other, each waiting for its own word, 4 x 22,050 samples, complex: 12.0 us instead of 10.4)
+      float x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = formatted<FMT>(row, ((v + i) >> lg_tf << 6) + ((v + i) & (TF - 1)), plane);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) op[(long long)(((v + i) >> lg_tf << 6) + ((v + i) & (TF - 1))) * T] = x[i];
+      v += 4;
     } else {
       op[(long long)r * T] = formatted<FMT>(row, r, plane);
       ++v;
