@@ -145,6 +145,7 @@ struct FftParams {
   int pitch, lg_tf;    // set by the launcher: LDS words per frame, log2 of the frames per tile
   int buf_words;       // LDS words from one tile's buffer to the next one's
   int sync_word;       // LDS word of two counters
+  int at_once;         // kernels whose frames span waves: a tile is written out before the next one is begun, from one buffer
   int mel_lds;         // LDS word the Mel tables are copied to; 0: they stay in memory
   long long n_tiles;
 };

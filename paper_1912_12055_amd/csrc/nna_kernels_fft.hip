@@ -455,7 +455,7 @@ __global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
   };
   constexpr bool FLAGS = TPF <= 64;
   // written out in the first steps of the next tile, so that no wave waits for another's last one
-  const int lg_parts = iters > 1 ? 30 - __builtin_clz(iters) : 0, parts = 1 << lg_parts;
+  const int lg_parts = iters > 1 && !P.at_once ? 30 - __builtin_clz(iters) : 0, parts = 1 << lg_parts;
   auto emit = [&](const float* done, int part) {
     if constexpr (MODE == FFT_MODE_MEL) {
       if (P.mel_lds)
@@ -609,6 +609,11 @@ __global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
     pb0 = b0;
     pt0 = t0;
     p_left = P.g.n_frames - (tile_i << P.lg_tf);
+    if (!FLAGS && P.at_once) {
+      emit(cur, 0);
+      __syncthreads();
+      p_left = 0;
+    }
     float* const swap = cur;
     cur = old;
     old = swap;
@@ -744,14 +749,31 @@ hipError_t launch_fixed(FftParams& P, hipStream_t stream) {
   const int tables = MODE == FFT_MODE_MEL ? (P.n_mels + P.mel_quads) * 16 : 0;
   P.mel_lds = tables > 0 && 2 * step * C::PITCH * 4 + 32 + tables <= C::LDS;
   int iters = C::max_steps(n_wave, 32 + (P.mel_lds ? tables : 0));
-  while (iters > 1 && 5 * longest(iters) > (iters == 2 ? 7 : 5) * longest(iters / 2)) iters >>= 1;
+  // Frames of two waves (N = 4,096) whose LDS holds two buffers of one step, two frames, only: one buffer of two steps, where a workgroup
+  // takes several tiles.  Rows of four frames are written in half the requests and the bands' lanes are filled: 140,000 frames, complex,
+  // 2.83 ms (four frames, stored between two barriers) -> 3.14 (two buffers) -> 2.41; Mel, 40 bands 1.00 -> 1.45 -> 1.02, 128: 0.90 -> 1.00
+  // -> 0.77, 512: 1.06 -> 0.93 -> 0.90.  Four steps leave the Mel tables in memory (1.07 to 1.1 times the time), for bands that fill the
+  // lanes better by more than that: 80 bands 0.92 -> 1.12 -> 1.00 in two steps, 0.91 in four.
+  if (C::TPF > 64 && iters == 1 && P.g.n_frames > (long long)groups * step) {
+    auto rounds = [&](int steps) { return (P.n_mels * step * steps + 64 * n_wave - 1) / (64 * n_wave); };  // of a tile's bands
+    P.at_once = 1;
+    iters = MODE == FFT_MODE_MEL && 4 * step * C::PITCH * 4 + 16 <= C::LDS && 11 * rounds(4) < 20 * rounds(2) ? 4 : 2;
+  }
+  // Twice the steps where the longest workgroup takes no more than these times what it would take without.  Two steps for one: at 4 / 3
+  // between 9 % more and 20 % less time (n_fft 512 to 4,096, 6,000 to 20,000 frames), at twice as many 20 to 45 % more; from one buffer at
+  // 1.2 11 % less time for 40 bands and 10 % more for 512, at 1.11 between 19 % less and 2 % more.  Four for two, 80 bands: at 1.01 9 % less,
+  // at 1.11 1 %, at 1.2 4 % more.
+  auto limit = [&] { return iters == 2 ? (P.at_once && MODE == FFT_MODE_MEL ? 1.15 : 1.4) : P.at_once ? 1.1 : 1.0; };
+  while (iters > 1 && longest(iters) > limit() * longest(iters / 2)) iters >>= 1;
+  if (iters == 1) P.at_once = 0;
+  if (P.at_once && iters == 4) P.mel_lds = 0;
   const int tf = step * iters;
   P.lg_tf = 0;
   while ((1 << P.lg_tf) < tf) ++P.lg_tf;
   P.n_tiles = (P.g.n_frames + tf - 1) / tf;
   const long long grid = std::min<long long>((P.n_tiles + 7) / 8 * 8, groups);
   const int words = (tf * C::PITCH + 3) & ~3;
-  P.buf_words = P.n_tiles > grid ? words : 0;
+  P.buf_words = P.n_tiles > grid && !P.at_once ? words : 0;
   P.sync_word = words + P.buf_words;
   if (P.mel_lds) P.mel_lds = P.sync_word + 4;
   const size_t bytes = (size_t)(P.sync_word + 4) * 4 + (P.mel_lds ? tables : 0);

@@ -38,3 +38,23 @@ def test_mel(n_fft, hop, n_mels, frames):
     B = -(-frames // alone.shape[2])
     out = nb.nna_mel(plan, base.repeat(-(-B // 3), 1)[:B].contiguous())
     assert torch.equal(out, alone.repeat(-(-B // 3), 1, 1)[:B])
+
+
+# frames of two waves: one buffer of two steps or four (80 bands, tables in memory) where two buffers hold one step, one tile a workgroup
+# and several, a last tile of any size
+@pytest.mark.parametrize("kind,n_mels", [("COMPLEX", 0), ("PHASE", 0), ("MAGNITUDE", 0), ("mel", 40), ("mel", 80), ("mel", 512)])
+@pytest.mark.parametrize("frames", [1021, 1027, 2051, 4100, 9003])
+def test_frames_of_two_waves(kind, n_mels, frames):
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] fft buffers 4096 {kind}{n_mels} frames={frames}", file=sys.stderr, flush=True)
+    n_fft, hop = 4096, 512
+    base = torch.randn((3, 16 * hop + 5), generator=torch.Generator().manual_seed(frames)).cuda()
+    if kind == "mel":
+        plan, run = nb.nna_plan_mel(n_fft=n_fft, hop=hop, n_mels=n_mels, device=0), nb.nna_mel
+    else:
+        plan, run = nb.nna_plan_stft(n_fft=n_fft, hop=hop, fmt=getattr(nb, "NNA_OUT_" + kind), device=0), nb.nna_stft
+    alone = run(plan, base)
+    B = -(-frames // alone.shape[2])
+    out = run(plan, base.repeat(-(-B // 3), 1)[:B].contiguous())
+    assert torch.equal(out, alone.repeat(-(-B // 3), 1, 1)[:B])
