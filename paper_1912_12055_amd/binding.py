@@ -155,6 +155,7 @@ class Plan:
         self.device = device
         self.owner = owner  # a part of another plan: that plan owns the handle (and is kept alive here)
         self.bank_sets = 0  # calls of nna_plan_set_bank
+        self._constants = None
 
     def __del__(self):
         h, self.handle = getattr(self, "handle", None), None
@@ -168,6 +169,14 @@ class Plan:
         _check(lib().nna_plan_info(self.handle, kind, rows, taps, bins, ex, alg))
         return dict(kind=kind.value, bank_rows=rows.value, taps=taps.value, out_bins=bins.value,
                     executed_flops_per_frame=ex.value, algorithmic_flops_per_frame=alg.value)
+
+
+    def constants(self):
+        """(kind, bank rows, taps): asked for once, a plan never changes them."""
+        if self._constants is None:
+            i = self.info()
+            self._constants = (i["kind"], i["bank_rows"], i["taps"])
+        return self._constants
 
 
 def _new_plan(fn, args, device):
@@ -375,7 +384,7 @@ def nna_mel_with_stft(plan: Plan, x, out=None, spec=None, stream=None):
     spectrogram its filterbank is applied to."""
     import torch
 
-    F = plan.info()["bank_rows"] // 2
+    F = plan.constants()[1] // 2
     cfn = lib().nna_mel_with_stft
     holder = {}
 
@@ -411,8 +420,7 @@ def nna_plan_trainable(plan: Plan) -> Plan:
 
 
 def _bank_shape(plan: Plan):
-    i = plan.info()
-    return (i["bank_rows"], i["taps"])
+    return plan.constants()[1:]
 
 
 def _stream_of(t, stream):
@@ -669,17 +677,20 @@ def nna_kept_bytes(plan: Plan, B: int, L: int) -> int:
     return n.value
 
 
-def nna_forward_keep(plan: Plan, x, stream=None):
-    """(out, kept): nna_stft, nna_mel or nna_cqt of a trainable plan, and what nna_backward_kept takes instead of computing it again."""
+def nna_forward_keep(plan: Plan, x, stream=None, size=None):
+    """(out, kept): nna_stft, nna_mel or nna_cqt of a trainable plan, and what nna_backward_kept takes instead of computing it again.
+    `size`: nna_kept_bytes of the call, where the caller has asked for it."""
     import torch
 
-    kept = torch.empty(nna_kept_bytes(plan, *x.shape), dtype=torch.uint8, device=x.device)
-    info, spec = plan.info(), None
-    if info["kind"] == NNA_KIND_MEL:
-        spec = torch.empty((x.shape[0], info["bank_rows"] // 2, nna_out_shape(plan, *x.shape)[1]), dtype=torch.float32, device=x.device)
+    if size is None:
+        size = nna_kept_bytes(plan, *x.shape)
+    kept, spec = torch.empty(size, dtype=torch.uint8, device=x.device), None
+    kind, rows, _ = plan.constants()
+    if kind == NNA_KIND_MEL:
+        spec = torch.empty((x.shape[0], rows // 2, nna_out_shape(plan, *x.shape)[1]), dtype=torch.float32, device=x.device)
 
     def fn(handle, xp, B, L, op, st):
-        return lib().nna_forward_keep(handle, xp, B, L, op, None if spec is None else spec.data_ptr(), kept.data_ptr(), kept.numel(), st)
+        return lib().nna_forward_keep(handle, xp, B, L, op, None if spec is None else spec.data_ptr(), kept.data_ptr(), size, st)
 
     return _run(fn, plan, x, None, stream), kept
 
@@ -697,8 +708,9 @@ def nna_backward_kept(plan: Plan, x, gout, kept, want_gmelw=False, want_gw=True,
     bins, frames = nna_out_shape(plan, B, L)
     if tuple(gout.shape) != (B, bins, frames):
         raise TypeError(f"gout must be of shape {(B, bins, frames)}")
-    size = {NNA_KIND_MEL: nna_mel_backward_workspace, NNA_KIND_CQT: nna_cqt_backward_workspace}
-    need = size.get(plan.info()["kind"], nna_stft_backward_workspace)(plan, B, L)
+    kind = plan.constants()[0]
+    size = nna_mel_backward_workspace if kind == NNA_KIND_MEL else nna_cqt_backward_workspace if kind == NNA_KIND_CQT else nna_stft_backward_workspace
+    need = size(plan, B, L)
     workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
     gm = torch.empty(_mel_shape(plan), dtype=torch.float32, device=x.device) if want_gmelw else None
     gw = torch.empty(_bank_shape(plan), dtype=torch.float32, device=x.device) if want_gw else None

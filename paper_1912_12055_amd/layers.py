@@ -64,11 +64,13 @@ _KEPT_BYTES = 1 << 30  # what a forward pass holds for its backward pass, at mos
 
 def _forward(ctx, plan, x, keep, run):
     """run(plan, x), or what is worth keeping for the backward pass with it (`keep`: there will be one)."""
-    if keep and x.is_cuda and x.dim() == 2 and x.shape[1] >= 4 and 0 < nb.nna_kept_bytes(plan, *x.shape) <= _KEPT_BYTES:
-        out, kept = nb.nna_forward_keep(plan, x)
-        ctx.save_for_backward(x, kept)
-        ctx.bank_sets = plan.bank_sets
-        return out
+    if keep and x.is_cuda and x.dim() == 2 and x.shape[1] >= 4:
+        size = nb.nna_kept_bytes(plan, *x.shape)
+        if 0 < size <= _KEPT_BYTES:
+            out, kept = nb.nna_forward_keep(plan, x, size=size)
+            ctx.save_for_backward(x, kept)
+            ctx.bank_sets = plan.bank_sets
+            return out
     ctx.save_for_backward(x)
     return run(plan, x)
 
@@ -77,11 +79,6 @@ def _saved(ctx):
     """(x, what was kept or None): a bank set since the forward pass is the one the gradients are taken with, so C is computed again."""
     x, *kept = ctx.saved_tensors
     return x, kept[0] if kept and ctx.bank_sets == ctx.layer.plan.bank_sets else None
-
-
-def _recorded(*tensors):
-    """Whether autograd records a call on these."""
-    return torch.is_grad_enabled() and any(t.requires_grad for t in tensors)
 
 
 class _StftFn(torch.autograd.Function):
@@ -140,6 +137,15 @@ class _MelFn(torch.autograd.Function):
 class _Trainable(torch.nn.Module):
     """Keeps the library's copy of a parameter in step with the ``nn.Parameter`` an optimiser updates."""
 
+    def _make_trainable(self):
+        nb.nna_plan_trainable(self.plan)
+        # (a property of the transform and its output format, the same for every batch)
+        self._keeps = nb.nna_kept_bytes(self.plan, 1, 2 * self.plan.constants()[2] + 4) > 0
+
+    def _keep(self, *tensors):
+        """Whether a call on these has a backward pass to come that takes what the forward pass keeps."""
+        return self._keeps and torch.is_grad_enabled() and any(t.requires_grad for t in tensors)
+
     def _sync(self, param, setter, tag):
         # Tensor._version counts in-place updates (optimiser steps, load_state_dict, manual edits)
         # alone misses `param.data = ...` and a replaced Parameter object: the storage and the object count too
@@ -174,7 +180,7 @@ class STFT(_Trainable):
             raise ValueError("freq_scale: 'no', 'linear' or 'log'")
         self.trainable = bool(trainable)
         if self.trainable:
-            nb.nna_plan_trainable(self.plan)
+            self._make_trainable()
             self.wsin_wcos = torch.nn.Parameter(nb.nna_plan_get_bank(self.plan))
 
     def forward(self, x):
@@ -182,7 +188,7 @@ class STFT(_Trainable):
             return nb.nna_stft(self.plan, _no_grad_input(x))
         x = _as_batch(x)
         self._sync(self.wsin_wcos, nb.nna_plan_set_bank, "bank")
-        return _StftFn.apply(x, self.wsin_wcos, self, _recorded(x, self.wsin_wcos))
+        return _StftFn.apply(x, self.wsin_wcos, self, self._keep(x, self.wsin_wcos))
 
 
 class MelSpectrogram(_Trainable):
@@ -202,7 +208,7 @@ class MelSpectrogram(_Trainable):
         self.hop_length = hop_length
         self.trainable = bool(trainable_mel or trainable_STFT)
         if self.trainable:
-            nb.nna_plan_trainable(self.plan)
+            self._make_trainable()
             self.mel_basis = torch.nn.Parameter(nb.nna_plan_get_mel_weights(self.plan), requires_grad=bool(trainable_mel))
             self.wsin_wcos = torch.nn.Parameter(nb.nna_plan_get_bank(self.plan), requires_grad=bool(trainable_STFT))
 
@@ -219,7 +225,7 @@ class MelSpectrogram(_Trainable):
             return nb.nna_mel(self.plan, _no_grad_input(x))
         self._sync(self.wsin_wcos, nb.nna_plan_set_bank, "bank")
         self._sync(self.mel_basis, nb.nna_plan_set_mel_weights, "mel")
-        return _MelFn.apply(x, self.wsin_wcos, self.mel_basis, self, _recorded(x, self.wsin_wcos, self.mel_basis))
+        return _MelFn.apply(x, self.wsin_wcos, self.mel_basis, self, self._keep(x, self.wsin_wcos, self.mel_basis))
 
 
 def _cqt_bins(sr, fmin, fmax, n_bins, bins_per_octave):
@@ -273,7 +279,7 @@ class CQT1992v2(_Cqt):
                                     fmt=_format(output_format), device=_device_index(device))
         self.trainable = bool(trainable)
         if self.trainable:
-            nb.nna_plan_trainable(self.plan)
+            self._make_trainable()
             self.cqt_kernels = torch.nn.Parameter(nb.nna_plan_get_bank(self.plan))
 
     def forward(self, x):
@@ -281,7 +287,7 @@ class CQT1992v2(_Cqt):
             return nb.nna_cqt(self.plan, _no_grad_input(x))
         x = _as_batch(x)
         self._sync(self.cqt_kernels, nb.nna_plan_set_bank, "bank")
-        return _CqtFn.apply(x, self.cqt_kernels, self, _recorded(x, self.cqt_kernels))
+        return _CqtFn.apply(x, self.cqt_kernels, self, self._keep(x, self.cqt_kernels))
 
 
 class CQT1992(_Cqt):
