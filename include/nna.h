@@ -266,12 +266,13 @@ nna_status nna_mel_with_stft(const nna_plan* plan, const float* x_dev, long long
 
 /* out_dev[B, n_bins, T] = constant-Q spectrogram of x_dev[B, L]; plan from nna_plan_cqt.  A sample that is not finite makes
  * the outputs whose kernels reach it not finite: with kernels cut at the hops' boundaries, by the kernel's own taps, else by the
- * sixteen-tap steps it shares with seven neighbours (the forms are at nna_plan_cqt). */
+ * sixteen-tap steps it shares with seven neighbours (the forms are at nna_plan_cqt).  Kernels cut at the hops' boundaries run on the
+ * bfloat16 matrix pipe, every float32 as the sum of three bfloat16: exact from 2^-110 in magnitude up; below, low bits are lost. */
 nna_status nna_cqt(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                    void* hip_stream);
 
 /* out_dev[B, n_bins, T] = constant-Q spectrogram of x_dev[B, L]; plan from nna_plan_cqt1992.
- * The STFT itself is never written to memory. */
+ * The STFT itself is never written to memory.  Fixed kernels run as nna_cqt's, with the same range. */
 nna_status nna_cqt1992(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                        void* hip_stream);
 
@@ -290,7 +291,7 @@ nna_status nna_cqt2010v2_workspace(const nna_plan* plan, long long B, long long 
  * under stream capture those streams join the capture and leave it again.  Calls on one plan from several host threads
  * enqueue one after the other (a lock in the plan).  NNA_ERR_SHAPE if some octave's waveform is not longer
  * than the kernels' half length n_taps/2 or shorter than the filter's frame (fir_taps + 126
- * samples, rounded up to a multiple of 128). */
+ * samples, rounded up to a multiple of 128).  Filters of 131 to 289 taps hold samples as nna_cqt does (low bits lost below 2^-110). */
 nna_status nna_cqt2010v2(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                          void* workspace_dev, size_t workspace_bytes, void* hip_stream);
 
@@ -385,7 +386,7 @@ nna_status nna_cqt_backward(const nna_plan* plan, const float* x_dev, long long 
  *   nna_kept_bytes     size of kept_dev (bank rows padded to 128 x padded frames x 4); 0: this plan's calls keep nothing.
  *   nna_forward_keep   as nna_stft, nna_cqt or (spec_dev not NULL, Mel plans only) nna_mel_with_stft, and kept_dev (256-byte aligned).
  *   nna_backward_kept  as the plan's backward call with the same workspace; kept_dev from the forward pass of the same x_dev and
- *                      bank, unchanged by the call.  gmelw_dev: Mel plans only.
+ *                      bank (a bank set since makes the kernels' and the waveform's gradient a mixture of both), unchanged by the call.  gmelw_dev: Mel plans only.
  * Errors as for those calls; NNA_ERR_UNSUPPORTED where nna_kept_bytes is 0.
  */
 nna_status nna_kept_bytes(const nna_plan* plan, long long B, long long L, size_t* bytes);
@@ -490,9 +491,10 @@ nna_status nna_mel_backward(const nna_plan* plan, const float* x_dev, long long 
  * nna_plan_cqt -- from nna_plan_cqt1992 for a plan made by nna_plan_cqt2010 -- for nna_plan_bank /
  * nna_plan_info / nna_plan_cqt_lengths / nna_plan_spectral_kernels), or with index -1 the
  * decimation filter, for inspection, as a bank of 64 rows: row r = the taps h shifted right by 2 r
- * (64 consecutive output samples per frame of 128 input samples).  The decimation itself runs on the
- * vector ALUs from the same taps split by the parity of their offset from the centre (a half-band design
- * is zero on the even offsets but for the centre: those are not multiplied).  The parts belong to `plan`. */
+ * (64 consecutive output samples per frame of 128 input samples).  The decimation itself runs
+ * from the same taps split by the parity of their offset from the centre (a half-band design
+ * is zero on the even offsets but for the centre: those are not multiplied): half-band filters of 131 to 289 taps on the
+ * bfloat16 matrix pipe, every float32 as three bfloat16, the others on the vector ALUs.  The parts belong to `plan`. */
 nna_status nna_plan_part(const nna_plan* plan, int index, const nna_plan** part);
 
 /*

@@ -1467,7 +1467,7 @@ void build_fir_bank(nna_plan* p, int fir_taps) {
     return i >= 0 && i < fir_taps ? p->h_fir[i] : 0.0;
   });
   p->alg_flops = 2.0 * fir_taps * FIR_ROWS;  // per frame of FIR_ROWS output samples
-  // The decimation itself runs on the vector ALUs from the taps split by the parity of their offset u = i - half
+  // The decimation itself runs from the taps split by the parity of their offset u = i - half
   // from the centre: y[m] = sum_v h[half + 2v] x~[2 (m + v)] + sum_v h[half + 2v + 1] x~[2 (m + v) + 1].  A half-band
   // design is zero on every even offset but 0 (sin(pi u / 2) = 0; in double the taps come out as ~1e-17):
   // those taps are dropped, which leaves the centre tap on the even samples.

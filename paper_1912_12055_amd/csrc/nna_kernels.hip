@@ -1113,7 +1113,8 @@ __global__ __launch_bounds__(256) void fir_decimate_kernel(const FirParams P) {
 // this one's products.  The centre tap, the only one on an even sample, is added on the vector ALUs.
 //
 // Bound by the matrix pipe it shares with the octaves' kernels: three workgroups of a CU leave room for those, which run at the same
-// time.  The downsampling layer, 1,770 x 176,400 samples, 168 bins (MI355X): 4.40 ms with fir_decimate_kernel, whose vector ALUs ran
+// time.  (Alone, 1,770 x 176,400 samples to half as many: 0.41 ms, matrix pipe 34 % and vector ALUs 37 % busy, 1.3 GB; what is left are
+// waits at its two barriers a tile.)  The downsampling layer, 168 bins (MI355X): 4.40 ms with fir_decimate_kernel, whose vector ALUs ran
 // as long as the octaves' matrix instructions, now 3.53; 16 x 459,811 samples and other rows of odd length read unaligned.
 constexpr int FIRM_SPAN = FIR_TILE + 32 * FIRM_STEPS;  // odd samples of a tile
 

@@ -16,19 +16,23 @@
 // consecutive words of LDS, so r needs no padding to the taps of a step, only to 4 modulo 8, which keeps the rows of sixteen frames on
 // different banks.
 //
-// Both run on v_mfma_f32_16x16x32_bf16, every float32 exact as three bfloat16 and the six products that matter of nine: 32 taps in 96
-// cycles of a SIMD's pipe against 256 as eight v_mfma_f32_16x16x4_f32.  The weights are split with the plan, the samples on the way
-// into the instruction, the coordinates once, on the way into LDS, where six bytes a coordinate fit.
+// Both run on v_mfma_f32_16x16x32_bf16, every float32 as three bfloat16 (exact from 2^-110 up to 3.396e38; below, low bits are lost, above
+// the first part is infinite and the sum is taken again in float32) and the six products that matter of nine: 32 taps in 96 cycles of a
+// SIMD's pipe against 256 as eight v_mfma_f32_16x16x4_f32.  The weights are split with the plan, the samples on the way into the
+// instruction.  Coordinates are split once, on the way into LDS, by the items that need six bytes for each in no more LDS than the
+// launch's largest item takes at four: small bases; the others' are split by every frame that reads them (two of the six items with a
+// basis of the first and the last call below).
 //
 // Every sum is taken in blocks of 32 products (six instructions), each from zero and then added to a total: a chain of a thousand
 // roundings was off by up to 9e-7 of a bin's norm, more than the folded kernel's half as many in the bins taken tap by tap; the
-// blocks are off by 3e-7 at most.  Against 64 bits the bfloat16 form's errors are 0.55 .. 0.85 of the float32 instruction's.
+// blocks are off by 3e-7 at most.  Against 64 bits the bfloat16 form's errors are 0.5 .. 0.9 of the float32 instruction's, eight
+// configurations, six signals each.
 //
 // Bound by no one pipe at the batch below: the samples' splits keep the vector ALUs 52 % busy, the matrix pipe is at 39 %; a short batch
 // by latency, a workgroup or two per CU.  1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms
 // folded about the centres, 8.25 here in float32, 6.59 in bfloat16 with every coordinate split by each frame that reads it, now 5.74;
 // 16 x 220,500, 84 bins of 12 per octave: 300 -> 67.8 -> 53.8 us; the dense composed kernels of the frequency-domain layer (16 x
-// 220,500, 32,768 taps): 566 -> 183 -> 138 us.
+// 220,500, 16,384 taps): 566 -> 183 -> 138 us.
 #include <type_traits>
 
 #include "nna_device.h"
@@ -294,8 +298,8 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
   const int rows_used = tm.frame_row(m_valid - 1) + tm.extra + 1;
   const int r = item.r;
   constexpr int RB = 2;  // row blocks
-  // Where the LDS has room for six bytes a coordinate they are kept as the three bfloat16 stage 2 multiplies, split once instead of
-  // once per hop-block that reads them; planes of p_words values.
+  // Where the launch's LDS, sized for its largest item at four bytes a coordinate, has room for six, they are kept as the three bfloat16
+  // stage 2 multiplies, split once instead of once per hop-block that reads them; planes of p_words values.
   const int p_words = rows_used * r + 32;
   const bool split = 6 * p_words <= 4 * P.lds_floats;
   unsigned short* const Yb = reinterpret_cast<unsigned short*>(Y);

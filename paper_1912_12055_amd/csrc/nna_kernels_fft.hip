@@ -9,7 +9,8 @@
 // A wave owns whole frames up to N = 2,048, so the passes exchange their values through LDS without a barrier (a wave's LDS
 // accesses complete in order); real and imaginary parts go one after the other through the same words.  The region a frame
 // exchanges through is the row of the output tile its finished bins are written to.  The tile turns bins-per-frame into runs
-// of consecutive frames of one bin, the order of the output; while one tile is computed, the one before it is written out.
+// of consecutive frames of one bin, the order of the output; while one tile is computed, the one before it is written out (where LDS
+// holds two tiles of more than two frames: launch_fixed).
 //
 // What bounds it: two waves per SIMD (the tables a lane keeps in registers), a chain of passes through LDS each.  Without its
 // output the call below takes 0.82 ms, the vector ALUs' time; meeting once a tile and the stores' own instructions add the rest.
@@ -17,7 +18,7 @@
 // 1,770 x 176,400 samples, N = 2,048, hop 512 (MI355X): magnitudes 10.1 ms contracted, 2.20 with a tile computed, then stored
 // between two barriers and neighbouring tiles 29 us apart, now 1.51 (either way 3.66 GB are written for 2.50: runs of half a line);
 // N = 1,024, hop 256, complex: 4.02 -> 2.35.  Mel, 64 x 110,250, 128 bands: 808 us contracted, 48 -> 39; 1,770 x 80,000,
-// N = 4,096, 512 bands: 34.9 ms, 2.02 -> 1.80.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles read from the caches for
+// N = 4,096, 512 bands: 34.9 ms, 2.02 -> 1.74.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles read from the caches for
 // every frame with four waves per SIMD (2.85 ms: the vector memory path saturates), from LDS with four waves per SIMD (spills,
 // 1.87 ms), three waves per SIMD (spills, 4.3 ms), the tile stored by two workgroups of four waves (runs of 32 bytes, 2.04 ms).
 #include "nna_device.h"
@@ -360,7 +361,8 @@ __global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
       wave_fence();
   };
   // Workgroup ids are dealt round-robin to the 8 XCDs.  An XCD's workgroups take neighbouring tiles at the same time, so that the
-  // samples their frames share, and the output lines that a tile begins and its neighbour ends, meet in one L2 while they are there.
+  // samples their frames share meet in one L2 while they are there.  (Output lines that a tile begins and its neighbour ends do not: as
+  // many bytes are written as with neighbouring tiles one after the other.)
   const long long per_xcd = (P.n_tiles + 7) >> 3, lo = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   const long long hi = ((blockIdx.x & 7) + 1) * per_xcd < P.n_tiles ? ((blockIdx.x & 7) + 1) * per_xcd : P.n_tiles;
   const int stride = gridDim.x >> 3;  // tiles from one of this workgroup's to its next

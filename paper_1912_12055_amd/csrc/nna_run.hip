@@ -343,7 +343,8 @@ nna_status run_conv_fold(const nna_plan* sub, const float* x, long long B, long 
 // tile cut below three quarters for that takes one workgroup's 156 KB instead.  False: not a launch for this kernel.  It is one
 // where the form that runs otherwise (folded about the centres, or tap by tap) has fewer workgroups than there are CUs (its time over
 // the other's, batches of 50 to 13,000 frames, MI355X: 0.02 .. 0.9), or takes 1.25 times the multiply-adds, unfilled tiles and the
-// first stage's overlap counted (theirs over the other's 0.22 .. 0.55, 86,000 frames and more: time 0.16 .. 0.46; 0.76: 0.82).
+// first stage's overlap counted (13,000 to 300,000 frames, theirs over the other's 0.22 .. 0.55: time 0.16 .. 0.46; 0.63 .. 0.67: 0.45
+// .. 0.85; 0.73 .. 0.81: 0.38 .. 0.87).  (Beyond the line, 0.84 .. 1.13, the time would still be 0.41 .. 0.74.)
 bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::CqlParams& P) {
   const int n_items = (int)sub->h_litems.size(), n_basis = (int)std::count_if(sub->h_litems.begin(), sub->h_litems.end(), [](const nna::CqlItem& it) { return it.r != 0; });
   P.lds_floats = 0;
@@ -459,7 +460,7 @@ nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long 
 }
 
 // A plan with frequency-domain kernels: both stages as one bank while the kernels are fixed -- 4 n_bins K flops per frame where
-// the two stages take 2 K^2 for every 64 or 96 bins (16 x 220,500 samples, 84 bins, K = 32,768: 120 ms -> 566 us) -- and the
+// the two stages take 2 K^2 for every 64 or 96 bins (16 x 220,500 samples, 84 bins, K = 16,384: 120 ms -> 566 us) -- and the
 // two-stage kernel once they are trainable, each stage then being a weight of its own.
 nna_status run_cqt1992(const nna_plan* plan, const float* x, long long B, long long L, long long T, float* out,
                        long long out_wave_stride, int row_offset, void* hip_stream) {
@@ -577,7 +578,7 @@ static nna_status run_octaves(const nna_plan* plan, int kind, const float* x_dev
   if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
   // The filter chain x_0 -> x_1 -> ... runs on the caller's stream; octave a's kernels need x_a only and go to one of the
   // plan's two streams (even / odd octaves), so they run beside the next filter steps and beside each other: the
-  // filter is bound by the vector ALUs, the octaves' kernels by the matrix pipe, and the deep octaves' launches are too
+  // filter alone keeps the matrix pipe a third busy and waits for more than half of its time, and the deep octaves' launches are too
   // small to fill the chip alone.  Every stream is back on the caller's before the call returns, so the call still
   // is one piece of work on that stream (under stream capture: a fork and a join).
   hipStream_t main_stream = static_cast<hipStream_t>(hip_stream);

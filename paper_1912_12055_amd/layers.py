@@ -6,6 +6,10 @@ trainable layers of Sec. IV-C, every gradient -- is computed by the HIP library;
 tensors, the parameter objects and the autograd graph the calls are hooked into.
 
 Input ``x``: float32 CUDA tensor ``[B, L]`` (or ``[L]``); output ``[B, bins, T]``.
+
+Memory: a call of a trainable ``MelSpectrogram`` (power 2), ``STFT`` (``output_format='Power'``) or ``CQT1992v2`` (every format but
+``'Complex'``) that autograd records holds, until its backward pass, the kernels' products with the waveform besides ``x``: bank rows
+rounded up to 128 times frames times 4 bytes, at most 1 GiB a call.  Larger batches hold ``x`` alone and compute the products again.
 """
 from __future__ import annotations
 
@@ -214,7 +218,7 @@ class MelSpectrogram(_Trainable):
 
     def forward(self, x, return_spectrogram=False):
         """``return_spectrogram=True`` returns (mel, |X|^power), of a fixed layer from the one launch (not differentiable).  A trainable
-        layer's forward pass holds up to 1 GiB of spectrogram besides its output."""
+        layer's forward pass holds up to 1 GiB of spectrogram while it runs, besides its output and what the backward pass takes."""
         x = _as_batch(x)
         if self.trainable:
             self._sync(self.wsin_wcos, nb.nna_plan_set_bank, "bank")
