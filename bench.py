@@ -27,6 +27,7 @@ if ROOT not in sys.path:
 PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X dense fp32 matrix peak
 PEAK_FP32_VALU_TFLOPS = 157.3  # ... and of its vector ALUs
 PEAK_F16_MFMA_TFLOPS = 2500.0  # MI355X dense fp16 / bf16 matrix peak
+PEAK_SPLIT_TFLOPS = PEAK_F16_MFMA_TFLOPS / 6  # ... of float32 products as six of bfloat16
 PEAK_HBM_GBS = 8000.0
 # the kernel each transform of the step launches (names as rocprofv3 prints them)
 KERNELS = {"stft": "fft_kernel<1024, ..., POWER>", "mel": "fft_kernel<1024, ..., MEL>", "cqt": "cqt_lowrank_kernel<4, 2>"}
@@ -144,11 +145,11 @@ def main() -> int:
         out_bytes = legs[n][2].numel() * 4
         # None of the three runs eq. (DFT2) / eq. (CQT) term by term (2 N^2, 4 sum N_k flop per frame: quoted as
         # `direct_form_equivalent_tflops`).  STFT and Mel take a fast Fourier transform per frame on the vector ALUs, the CQT its
-        # kernels as combinations of a few functions per hop on the matrix pipe.  `needed_tflops` and the fractions count what
-        # that form cannot do without: 2.5 N log2 N (Mel: + 4 N for power and filters), and one complex multiply-add per new
-        # sample and bin; what a launch executes beyond it no plan counts (null).
+        # kernels as combinations of a few functions per hop on the bfloat16 matrix pipe, six products for a float32 one.
+        # `needed_tflops` and the fractions count what that form cannot do without: 2.5 N log2 N (Mel: + 4 N for power and filters),
+        # and one complex multiply-add per new sample and bin; what a launch executes beyond it no plan counts (null).
         needed = running_flops(legs[n][1]) * frames
-        frac = round(needed / ms / 1e9 / PEAK_FP32_MFMA_TFLOPS, 4)
+        frac = round(needed / ms / 1e9 / PEAK_SPLIT_TFLOPS, 4)
         per[n] = {
             "ms": round(ms, 4),
             "gsamples_per_s": round(B * L / ms / 1e6, 4),
@@ -175,7 +176,7 @@ def main() -> int:
         "kernel": KERNELS[dom],
         "bound": bound(dom),
         "achieved": per[dom]["needed_tflops"],
-        "peak": PEAK_FP32_MFMA_TFLOPS if bound(dom) == "mfma" else PEAK_FP32_VALU_TFLOPS,
+        "peak": round(PEAK_SPLIT_TFLOPS, 1) if bound(dom) == "mfma" else PEAK_FP32_VALU_TFLOPS,
         "unit": "TFLOP/s",
         "frac": share(dom),
         "frac_useful": share(dom),
@@ -240,14 +241,14 @@ def main() -> int:
             composed = info["kind"] == nb.NNA_KIND_CQT2010   # its octaves' kernels composed: the plan's count is the two stages'
             alg = running_flops(plan) if by_blocks else info["algorithmic_flops_per_frame"]
             exe = None if by_blocks or composed else info["executed_flops_per_frame"]
+            peak = PEAK_F16_MFMA_TFLOPS if name == "stft_f16_operands" else PEAK_SPLIT_TFLOPS if by_blocks else PEAK_FP32_MFMA_TFLOPS
             extras[name] = {
                 "ms": round(ms, 4),
                 "gsamples_per_s": round(n_samples / ms / 1e6, 4),
                 "algorithmic_tflops": round(alg * n_frames / ms / 1e9, 3),
                 "executed_tflops": None if exe is None else round(exe * n_frames / ms / 1e9, 3),
-                "mfma_frac": None if composed else round(alg * n_frames / ms / 1e9
-                                   / (PEAK_F16_MFMA_TFLOPS if name == "stft_f16_operands" else PEAK_FP32_MFMA_TFLOPS), 4),
-                "mfma_peak_tflops": PEAK_F16_MFMA_TFLOPS if name == "stft_f16_operands" else PEAK_FP32_MFMA_TFLOPS,
+                "mfma_frac": None if composed else round(alg * n_frames / ms / 1e9 / peak, 4),
+                "mfma_peak_tflops": round(peak, 1),
             }
         # The paper's own timing parameters (Sec. IV-A): n_fft 4096 / hop 512 STFT, 512 Mel filters on it, and the
         # 24-bins-per-octave CQT, on 1,770 clips of 80,000 samples at 44.1 kHz -- the shape of its MAPS excerpts
@@ -283,7 +284,7 @@ def main() -> int:
                 "ms": round(ms, 4),
                 "gsamples_per_s": round(B * Lp / ms / 1e6, 4),
                 "needed_tflops": round(needed / ms / 1e9, 3),
-                "mfma_frac": None if by_fft else round(needed / ms / 1e9 / PEAK_FP32_MFMA_TFLOPS, 4),
+                "mfma_frac": None if by_fft else round(needed / ms / 1e9 / PEAK_SPLIT_TFLOPS, 4),
                 "valu_frac": round(needed / ms / 1e9 / PEAK_FP32_VALU_TFLOPS, 4) if by_fft else None,
                 "sample": (out_t, xin, cfg),
             }
