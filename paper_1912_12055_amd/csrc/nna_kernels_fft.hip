@@ -200,6 +200,19 @@ __device__ __forceinline__ void store_rows(const float* __restrict__ tile, int p
   const int n = v_end - v;
   v_end = v + (n * (part + 1) >> lg_parts);
   v += n * part >> lg_parts;
+  // (tiles of fewer than eight frames.  One row after the other, each waiting for its own word: 4 x 22,050 samples, complex, 12.0 us instead
+  // of 10.4.  Two frames: four rows at a time take 24.5 us for 865 frames of 4,096, complex, two 22.8, one 21.6; 173 logarithms 11.5, 11.9
+  // and 12.6, 865 of them 19.1, 18.5 and 18.3; 173 phases 12.5, 13.3 and 14.2)
+  auto some_rows = [&](auto n_tag, int& v) {
+    constexpr int N = decltype(n_tag)::value;
+    float x[N];
+    auto row_of = [&](int i) { return ((v + i) >> lg_tf << 6) + ((v + i) & (TF - 1)); };
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = formatted<FMT>(row, row_of(i), plane);
+#pragma unroll
+    for (int i = 0; i < N; ++i) op[(long long)row_of(i) * T] = x[i];
+    v += N;
+  };
   while (v < v_end) {
     const int r = ((v >> lg_tf) << 6) + (v & (TF - 1));
     if (v + 8 <= v_end && (v & (TF - 1)) + 8 <= TF && (FMT != NNA_OUT_COMPLEX || r % 2 == 0)) {
@@ -210,14 +223,10 @@ __device__ __forceinline__ void store_rows(const float* __restrict__ tile, int p
 #pragma unroll
       for (int i = 0; i < 8; ++i) op[(long long)(r + i) * T] = x[i];
       v += 8;
-    } else if (v + 4 <= v_end) {
-      // (tiles of fewer frames: one row after the other, each waiting for its own word, 4 x 22,050 samples, complex: 12.0 us instead of 10.4)
-      float x[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = formatted<FMT>(row, ((v + i) >> lg_tf << 6) + ((v + i) & (TF - 1)), plane);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) op[(long long)(((v + i) >> lg_tf << 6) + ((v + i) & (TF - 1))) * T] = x[i];
-      v += 4;
+    } else if (v + 4 <= v_end && (lg_tf != 1 || FMT == NNA_OUT_PHASE)) {
+      some_rows(std::integral_constant<int, 4>{}, v);
+    } else if (v + 2 <= v_end && lg_tf == 1 && FMT != NNA_OUT_PHASE) {
+      some_rows(std::integral_constant<int, 2>{}, v);
     } else {
       op[(long long)r * T] = formatted<FMT>(row, r, plane);
       ++v;
@@ -754,9 +763,11 @@ hipError_t launch_fixed(FftParams& P, hipStream_t stream) {
   // Frames of two waves (N = 4,096) whose LDS holds two buffers of one step, two frames, only: one buffer of two steps, where a workgroup
   // takes several tiles.  Rows of four frames are written in half the requests and the bands' lanes are filled: 140,000 frames, complex,
   // 2.83 ms (four frames, stored between two barriers) -> 3.14 (two buffers) -> 2.41; Mel, 40 bands 1.00 -> 1.45 -> 1.02, 128: 0.90 -> 1.00
-  // -> 0.77, 512: 1.06 -> 0.93 -> 0.90.  Four steps leave the Mel tables in memory (1.07 to 1.1 times the time), for bands that fill the
-  // lanes better by more than that: 80 bands 0.92 -> 1.12 -> 1.00 in two steps, 0.91 in four.
-  if (C::TPF > 64 && iters == 1 && P.g.n_frames > (long long)groups * step) {
+  // -> 0.77, 512: 1.06 -> 0.93 -> 0.90.  Several: of two steps for bands and phases, which are computed on the way out (1,384 frames: 23.4
+  // us -> 27.0, 80 bands 21.0 -> 25.1), of one for complex rows (30.6 -> 28.4).  Four steps leave the Mel tables in memory (1.07 to 1.1
+  // times the time), for bands that fill the lanes better by more than that: 80 bands 0.92 -> 1.12 -> 1.00 ms in two steps, 0.91 in four.
+  const bool computed_out = MODE == FFT_MODE_MEL || (MODE == FFT_MODE_CPLX && P.fmt == NNA_OUT_PHASE);
+  if (C::TPF > 64 && iters == 1 && P.g.n_frames > (long long)groups * step * (computed_out ? 2 : 1)) {
     auto rounds = [&](int steps) { return (P.n_mels * step * steps + 64 * n_wave - 1) / (64 * n_wave); };  // of a tile's bands
     P.at_once = 1;
     iters = MODE == FFT_MODE_MEL && 4 * step * C::PITCH * 4 + 16 <= C::LDS && 11 * rounds(4) < 20 * rounds(2) ? 4 : 2;
@@ -765,8 +776,8 @@ hipError_t launch_fixed(FftParams& P, hipStream_t stream) {
   // between 9 % more and 20 % less time (n_fft 512 to 4,096, 6,000 to 20,000 frames), at twice as many 20 to 45 % more; from one buffer at
   // 1.2 11 % less time for 40 bands and 10 % more for 512, at 1.11 between 19 % less and 2 % more.  Four for two, 80 bands: at 1.01 9 % less,
   // at 1.11 1 %, at 1.2 4 % more.
-  auto limit = [&] { return iters == 2 ? (P.at_once && MODE == FFT_MODE_MEL ? 1.15 : 1.4) : P.at_once ? 1.1 : 1.0; };
-  while (iters > 1 && longest(iters) > limit() * longest(iters / 2)) iters >>= 1;
+  auto limit = [&] { return iters == 2 ? (P.at_once && computed_out ? 1.15 : 1.4) : P.at_once ? 1.1 : 1.0; };
+  while (iters > 1 && (longest(iters) > limit() * longest(iters / 2) || (P.at_once && iters == 4 && longest(4) > 1.15 * longest(1)))) iters >>= 1;
   if (iters == 1) P.at_once = 0;
   if (P.at_once && iters == 4) P.mel_lds = 0;
   const int tf = step * iters;
