@@ -200,19 +200,19 @@ __device__ __forceinline__ void store_rows(const float* __restrict__ tile, int p
   const int n = v_end - v;
   v_end = v + (n * (part + 1) >> lg_parts);
   v += n * part >> lg_parts;
-  // (tiles of fewer than eight frames.  One row after the other, each waiting for its own word: 4 x 22,050 samples, complex, 12.0 us instead
-  // of 10.4.  Two frames: four rows at a time take 24.5 us for 865 frames of 4,096, complex, two 22.8, one 21.6; 173 logarithms 11.5, 11.9
-  // and 12.6, 865 of them 19.1, 18.5 and 18.3; 173 phases 12.5, 13.3 and 14.2)
-  auto some_rows = [&](auto n_tag, int& v) {
-    constexpr int N = decltype(n_tag)::value;
-    float x[N];
-    auto row_of = [&](int i) { return ((v + i) >> lg_tf << 6) + ((v + i) & (TF - 1)); };
+  // Fewer than eight frames: four rows at a time.  One after the other, each waiting for its own word, 4 x 22,050 samples, complex, take
+  // 12.0 us instead of 10.4.  Rows of two frames do better one by one where the chip is full (865 frames of 4,096, complex: 23.6 us, 24.6 by
+  // fours), but for phases (173 frames: 13.6, 12.5).
+  if (TF < 8 && (TF != 2 || FMT == NNA_OUT_PHASE))
+#pragma unroll 1
+    for (; v + 4 <= v_end; v += 4) {
+      float x[4];
+      auto row_of = [&](int i) { return ((v + i) >> lg_tf << 6) + ((v + i) & (TF - 1)); };
 #pragma unroll
-    for (int i = 0; i < N; ++i) x[i] = formatted<FMT>(row, row_of(i), plane);
+      for (int i = 0; i < 4; ++i) x[i] = formatted<FMT>(row, row_of(i), plane);
 #pragma unroll
-    for (int i = 0; i < N; ++i) op[(long long)row_of(i) * T] = x[i];
-    v += N;
-  };
+      for (int i = 0; i < 4; ++i) op[(long long)row_of(i) * T] = x[i];
+    }
   while (v < v_end) {
     const int r = ((v >> lg_tf) << 6) + (v & (TF - 1));
     if (v + 8 <= v_end && (v & (TF - 1)) + 8 <= TF && (FMT != NNA_OUT_COMPLEX || r % 2 == 0)) {
@@ -223,10 +223,6 @@ __device__ __forceinline__ void store_rows(const float* __restrict__ tile, int p
 #pragma unroll
       for (int i = 0; i < 8; ++i) op[(long long)(r + i) * T] = x[i];
       v += 8;
-    } else if (v + 4 <= v_end && (lg_tf != 1 || FMT == NNA_OUT_PHASE)) {
-      some_rows(std::integral_constant<int, 4>{}, v);
-    } else if (v + 2 <= v_end && lg_tf == 1 && FMT != NNA_OUT_PHASE) {
-      some_rows(std::integral_constant<int, 2>{}, v);
     } else {
       op[(long long)r * T] = formatted<FMT>(row, r, plane);
       ++v;
