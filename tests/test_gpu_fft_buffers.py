@@ -41,9 +41,9 @@ def test_mel(n_fft, hop, n_mels, frames):
 
 
 # frames of two waves: one buffer of two steps or four (80 bands, tables in memory) where two buffers hold one step, one tile a workgroup
-# and several, a last tile of any size
+# and several, a last tile of any size (four steps: 12,203 frames)
 @pytest.mark.parametrize("kind,n_mels", [("COMPLEX", 0), ("PHASE", 0), ("MAGNITUDE", 0), ("mel", 40), ("mel", 80), ("mel", 512)])
-@pytest.mark.parametrize("frames", [1021, 1027, 2051, 4100, 9003])
+@pytest.mark.parametrize("frames", [1021, 1027, 2051, 4100, 9003, 12203])
 def test_frames_of_two_waves(kind, n_mels, frames):
     import torch
     from paper_1912_12055_amd import binding as nb
