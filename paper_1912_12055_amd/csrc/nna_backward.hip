@@ -307,6 +307,18 @@ static void release_fixed_forms(nna_plan* plan) {
   plan->d_litems = nullptr;
   plan->d_lsupport = nullptr;
   plan->lowrank = false;
+  (void)hipFree(plan->d_sitems);
+  (void)hipFree(plan->d_sw);
+  (void)hipFree(plan->d_staps);
+  (void)hipFree(plan->d_ssteps);
+  (void)hipFree(plan->d_scolumns);
+  (void)hipFree(plan->d_ssupport);
+  plan->d_sitems = nullptr;
+  plan->d_sw = nullptr;
+  plan->d_staps = nullptr;
+  plan->d_ssteps = plan->d_scolumns = nullptr;
+  plan->d_ssupport = nullptr;
+  plan->short_taps = false;
   nna_plan_destroy(plan->composed);
   plan->composed = nullptr;
 }

@@ -1214,6 +1214,76 @@ void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<uns
   });
 }
 
+// The kernels tap by tap (nna_kernels_short.hip): items of up to 24 bins, their taps in steps of 32.
+void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels) {
+  p->short_taps = false;
+  const int hop = p->hop;
+  if (hop % 4 != 0 || p->K > 1 << 16) return;
+  std::vector<long long> first(p->n_bins + 1, 0);  // of a kernel's own taps
+  for (int k = 0; k < p->n_bins; ++k) first[k + 1] = first[k] + p->row_e[2 * k] - p->row_s[2 * k];
+  if (first[p->n_bins] > 1 << 28) return;
+  p->h_staps.resize(2 * first[p->n_bins]);
+  for_each_parallel(p->n_bins, [&](int k) {
+    const int n = (int)(first[k + 1] - first[k]);
+    std::vector<double> re(n), im(n);
+    kernels.taps(k, p->row_s[2 * k], n, re.data(), im.data());
+    for (int i = 0; i < n; ++i) {
+      p->h_staps[2 * (first[k] + i)] = (float)re[i];
+      p->h_staps[2 * (first[k] + i) + 1] = (float)im[i];
+    }
+  });
+  for (int k = 0; k < p->n_bins; ++k)
+    for (const long long v : {p->row_s[2 * k], p->row_e[2 * k], first[k], 0LL}) p->h_ssupport.push_back((int)v);
+  constexpr int per_item = 8 * nna::SHORT_RB;
+  for (int k0 = 0; k0 < p->n_bins; k0 += per_item) {
+    nna::ShortItem item{};
+    item.bin0 = k0;
+    item.n_bins = std::min(per_item, p->n_bins - k0);
+    const int n_rb = (item.n_bins + 7) / 8;
+    long long lo[nna::SHORT_RB], hi[nna::SHORT_RB];
+    for (int b = 0; b < n_rb; ++b) block_taps(p, k0, item.n_bins, b, lo[b], hi[b]);
+    for (int b = n_rb - 1; b > 0; --b) {  // (longer kernels come first, so a block's taps lie among those of the one before)
+      lo[b - 1] = std::min(lo[b - 1], lo[b]);
+      hi[b - 1] = std::max(hi[b - 1], hi[b]);
+    }
+    item.j0 = (int)(lo[0] / hop);
+    item.jspan = (int)ceil_div(hi[0], hop) - item.j0;
+    item.w0 = (long long)p->h_sw.size() / 4;
+    item.step0 = (int)p->h_ssteps.size();
+    const long long base = (long long)item.j0 * hop;
+    item.n_step = (int)ceil_div(hi[0] - base, 32);
+    p->h_sw.resize(p->h_sw.size() + (size_t)item.n_step * nna::SHORT_RB * 3 * 256, 0u);
+    for (int s = 0; s < item.n_step; ++s) {
+      int a = 0;
+      while (a < n_rb && base + 32 * s + 32 > lo[a] && base + 32 * s < hi[a]) ++a;
+      p->h_ssteps.push_back(a);
+    }
+    for (int k = k0; k < k0 + item.n_bins; ++k)
+      for (long long tap = p->row_s[2 * k]; tap < p->row_e[2 * k]; ++tap)
+        for (int part = 0; part < 2; ++part) {
+          // [step][row block][3 planes][64 lanes] of an octet: lane (q, row) holds taps 8 q .. 8 q + 7 of the step
+          const int row = 2 * (k - k0) + part, at = (int)(tap - base), e = at % 8, lane = at / 8 % 4 * 16 + row % 16;
+          unsigned* block = &p->h_sw[(size_t)item.w0 * 4 + ((size_t)(at / 32) * nna::SHORT_RB + row / 16) * 768];
+          put_parts(p->h_staps[2 * (first[k] + tap - p->row_s[2 * k]) + part], block + lane * 4 + e / 2, 256, e % 2);
+        }
+    if (hop % 32 == 0) {
+      item.columns = (int)p->h_scolumns.size();
+      std::vector<int> order;
+      for (int c = 0; c < hop; c += 32) {
+        p->h_scolumns.push_back((int)order.size());
+        for (int j = 0; j < item.jspan; ++j) {
+          const int s = j * (hop / 32) + c / 32, a = s < item.n_step ? p->h_ssteps[item.step0 + s] : 0;
+          if (a) order.push_back(a | j << 2 | s << 12);
+        }
+      }
+      p->h_scolumns.push_back((int)order.size());
+      p->h_scolumns.insert(p->h_scolumns.end(), order.begin(), order.end());
+    }
+    p->h_sitems.push_back(item);
+  }
+  p->short_taps = true;
+}
+
 // [2 n_bins][K]: the kernels of `p`'s items, multiplied out
 void cqt_applied_rows(const nna_plan* p, double* out) {
   const long long K = p->K;

@@ -224,6 +224,18 @@ struct nna_plan {
   nna::CqlItem* d_litems = nullptr;
   int2* d_lsupport = nullptr;
   bool runs_lowrank() const { return lowrank && !d_wrm; }
+  // The kernels tap by tap on the bfloat16 matrix pipe (nna_kernels_short.hip): octaves of the downsampling plans
+  bool short_taps = false;
+  std::vector<nna::ShortItem> h_sitems;
+  std::vector<unsigned> h_sw;    // weights as three bfloat16, in operand order
+  std::vector<float> h_staps;    // (Re, Im) of every kernel's own taps
+  std::vector<int> h_ssteps, h_scolumns, h_ssupport;
+  nna::ShortItem* d_sitems = nullptr;
+  unsigned* d_sw = nullptr;
+  float* d_staps = nullptr;
+  int *d_ssteps = nullptr, *d_scolumns = nullptr;
+  int4* d_ssupport = nullptr;
+  bool runs_short() const { return short_taps && !d_wrm; }
   // trainable CQT plans: index map caller's tensor -> streaming order, each row's tap support, and the
   // tables that let the backward contractions skip what lies outside every support
   // frames below which launch_conv takes the kernels for batches of few workgroups: with samples through LDS, or straight from memory
@@ -429,6 +441,7 @@ CqtKernelSource cqt_kernels(const nna_plan* p);
 CqtKernelSource dense_kernels(std::vector<double> rows, long long K);  // [2 n_bins][K]
 bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy);
 void cqt_applied_rows(const nna_plan* p, double* out);
+void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels);  // sets p->short_taps if the plan qualifies
 void build_cqt_bank_rows(nna_plan* c, const std::vector<double>& rows);
 void build_cqt_bank_fold(nna_plan* p);  // sets p->cq_fold if the plan qualifies
 // the decimation filter of `fir_taps` taps: its taps, their split by parity for the decimation kernel, and the

@@ -112,6 +112,14 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
         if (s == NNA_OK) s = upload(&p->d_litems, p->h_litems.data(), p->h_litems.size() * sizeof(nna::CqlItem), "hop-block item table");
         if (s == NNA_OK) s = upload(&p->d_lsupport, p->h_lsupport.data(), p->h_lsupport.size() * sizeof(int), "kernel supports");
       }
+      if (s == NNA_OK && p->short_taps) {
+        s = upload(&p->d_sw, p->h_sw.data(), p->h_sw.size() * sizeof(unsigned), "kernels");
+        if (s == NNA_OK) s = upload(&p->d_staps, p->h_staps.data(), p->h_staps.size() * sizeof(float), "kernels' own taps");
+        if (s == NNA_OK) s = upload(&p->d_ssteps, p->h_ssteps.data(), p->h_ssteps.size() * sizeof(int), "step table");
+        if (s == NNA_OK && !p->h_scolumns.empty()) s = upload(&p->d_scolumns, p->h_scolumns.data(), p->h_scolumns.size() * sizeof(int), "step table by columns");
+        if (s == NNA_OK) s = upload(&p->d_sitems, p->h_sitems.data(), p->h_sitems.size() * sizeof(nna::ShortItem), "item table");
+        if (s == NNA_OK) s = upload(&p->d_ssupport, p->h_ssupport.data(), p->h_ssupport.size() * sizeof(int), "kernel supports");
+      }
     }
     if (s != NNA_OK) {
       const std::string keep = g_err;
@@ -124,6 +132,8 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
     std::vector<float>().swap(p->h_bankq);
     std::vector<float>().swap(p->h_lu);
     std::vector<float>().swap(p->h_la);
+    std::vector<unsigned>().swap(p->h_sw);
+    std::vector<float>().swap(p->h_staps);
     std::vector<_Float16>().swap(p->h_bank16);
     std::vector<_Float16>().swap(p->h_bank16s);
   }
@@ -171,7 +181,7 @@ nna_status check_cqt_args(double fmin, int n_bins, int bins_per_octave, int n_ta
 
 // CQT plan whose bin k sits at fmin 2^((k_first + k) / bins_per_octave); arguments already checked
 nna_status make_cqt_plan(nna_plan** plan, int sr, int hop, double fmin, int k_first, int n_bins, int bins_per_octave,
-                         int win, int center, int n_taps, int fmt, int device, bool lowrank = false) {
+                         int win, int center, int n_taps, int fmt, int device, bool octave) {
   nna_plan* p = new (std::nothrow) nna_plan;
   if (!p) return fail(NNA_ERR_ALLOC, "out of host memory");
   try {
@@ -217,8 +227,8 @@ nna_status make_cqt_plan(nna_plan** plan, int sr, int hop, double fmin, int k_fi
     p->pad = center ? (int)(taps / 2) : 0;
     for (int k = 0; k < n_bins; ++k) p->sk[k] = (taps - p->Nk[k]) / 2;
     build_cqt_bank(p);
-    p->hop_blocks = lowrank;
-    if (lowrank && device >= 0) build_cqt_bank_lowrank(p, cqt_kernels(p));
+    p->hop_blocks = !octave;
+    if (device >= 0) octave ? build_cqt_bank_short(p, cqt_kernels(p)) : build_cqt_bank_lowrank(p, cqt_kernels(p));
     build_cqt_bank_fold(p);
   } catch (const std::bad_alloc&) {
     delete p;
@@ -414,12 +424,12 @@ nna_status nna_plan_cqt(nna_plan** plan, int sr, int hop, double fmin, int n_bin
   nna_status s = check_common(plan, sr, hop, win, center, device);
   if (s != NNA_OK) return s;
   if ((s = check_cqt_args(fmin, n_bins, bins_per_octave, n_taps, fmt, sr, true)) != NNA_OK) return s;
-  return make_cqt_plan(plan, sr, hop, fmin, 0, n_bins, bins_per_octave, win, center, n_taps, fmt, device, true);
+  return make_cqt_plan(plan, sr, hop, fmin, 0, n_bins, bins_per_octave, win, center, n_taps, fmt, device, false);
 }
 
 // two-stage CQT plan whose bin k sits at fmin 2^((k_first + k) / bins_per_octave); arguments already checked
 static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmin, int k_first, int n_bins,
-                                    int bins_per_octave, int win, int center, int n_fft, int fmt, int device, bool lowrank = false) {
+                                    int bins_per_octave, int win, int center, int n_fft, int fmt, int device, bool octave) {
   nna_plan* p = new (std::nothrow) nna_plan;
   if (!p) return fail(NNA_ERR_ALLOC, "out of host memory");
   MelDeviceLayout lin;
@@ -481,8 +491,11 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
     c->K = p->K;
     c->pad = p->pad;
     build_cqt_bank_rows(c, rows);
-    c->hop_blocks = lowrank;
-    if (lowrank && device >= 0) build_cqt_bank_lowrank(c, dense_kernels(std::move(rows), c->K));
+    c->hop_blocks = !octave;
+    if (device >= 0) {
+      const CqtKernelSource kernels = dense_kernels(std::move(rows), c->K);
+      octave ? build_cqt_bank_short(c, kernels) : build_cqt_bank_lowrank(c, kernels);
+    }
   } catch (const std::bad_alloc&) {
     delete c;
     delete p;
@@ -501,7 +514,7 @@ nna_status nna_plan_cqt1992(nna_plan** plan, int sr, int hop, double fmin, int n
   nna_status s = check_common(plan, sr, hop, win, center, device);
   if (s != NNA_OK) return s;
   if ((s = check_cqt_args(fmin, n_bins, bins_per_octave, n_fft, fmt, sr, true)) != NNA_OK) return s;
-  return make_cqt1992_plan(plan, sr, hop, fmin, 0, n_bins, bins_per_octave, win, center, n_fft, fmt, device, true);
+  return make_cqt1992_plan(plan, sr, hop, fmin, 0, n_bins, bins_per_octave, win, center, n_fft, fmt, device, false);
 }
 
 // Both downsampling plans: one sub-plan per octave (time-domain kernels: a plan as from nna_plan_cqt;
@@ -552,10 +565,10 @@ static nna_status make_downsampling_plan(int kind, nna_plan** plan, int sr, int 
     nna_plan* sub = nullptr;
     if (kind == NNA_KIND_CQT2010V2)
       s = make_cqt_plan(&sub, sr, hop >> a, fmin, lo + a * bins_per_octave, hi - lo, bins_per_octave, win, 1, n_taps,
-                        fmt, device);
+                        fmt, device, true);
     else
       s = make_cqt1992_plan(&sub, sr, hop >> a, fmin, lo + a * bins_per_octave, hi - lo, bins_per_octave, win, 1,
-                            n_taps, fmt, device);
+                            n_taps, fmt, device, true);
     if (s == NNA_OK) p->octave.push_back(sub);
   }
   if (s == NNA_OK && n_oct > 1) s = make_fir_plan(&p->fir, fir_taps, device);
@@ -956,6 +969,12 @@ void nna_plan_destroy(nna_plan* plan) {
       (void)hipFree(plan->d_litems);
       (void)hipFree(plan->d_lsteps);
       (void)hipFree(plan->d_lsupport);
+      (void)hipFree(plan->d_sitems);
+      (void)hipFree(plan->d_sw);
+      (void)hipFree(plan->d_staps);
+      (void)hipFree(plan->d_ssteps);
+      (void)hipFree(plan->d_scolumns);
+      (void)hipFree(plan->d_ssupport);
       (void)hipFree(plan->d_cq_map);
       (void)hipFree(plan->d_row_lo);
       (void)hipFree(plan->d_few_groups);

@@ -26,6 +26,7 @@ hipError_t ensure_kernels_init(int device) {
     hipError_t e = nna::kernels_init();
     if (e == hipSuccess) e = nna::cqf_kernels_init();
     if (e == hipSuccess) e = nna::cql_kernels_init();
+    if (e == hipSuccess) e = nna::short_kernels_init();
     if (e == hipSuccess) e = nna::fft_kernels_init();
     if (e != hipSuccess) return e;
     void* ptr = nullptr;
@@ -406,6 +407,54 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
   return NNA_OK;
 }
 
+// The kernels tap by tap (nna_kernels_short.hip).  Tiles of 64 frames where 80 KB, half a CU's LDS, hold their samples and there are two
+// of them per CU; else tiles of 128 frames by columns where there are as many of these; else 32 or 16 frames, which fill the chip
+// sooner.  12 bins, hop 512: 16 frames 7.9, 18.6, 30.2, 53.5 us for 5,500, 17,250, 34,500, 69,000 frames, columns 20.5, 25.2, 29.9, 38.6;
+// 24 bins, hop 128: 64 frames 12.1, 15.2, 23.0, 36.4, columns 19.9, 20.3, 25.2, 36.0, 32 frames 9.4, 13.0, 19.6, 31.8; hop 64, 138,000 frames:
+// 47 with 64, 54 with 32, 60 by columns.  A tile that holds less than three quarters of its frames (half, by columns, where long
+// kernels take the rows) is left to the next one.  False: not a launch for this kernel.
+bool shape_short(const nna_plan* sub, long long n_frames, long long T, nna::ShortParams& P) {
+  P.n_items = (int)sub->h_sitems.size();
+  // the tile of a form, its samples in up to `lds` bytes; false: it holds less than three quarters of its frames
+  auto fit = [&](int form, size_t lds) {
+    P.form = form;
+    const bool columns = form == nna::SHORT_COLUMNS;
+    const int rows = columns ? nna::SHORT_ROWS : (int)(((long long)(lds - 16) / 6 - 24) * 8 / 9 - 32) / sub->hop;
+    int M = nna::SHORT_FRAMES[form];
+    for (const nna::ShortItem& it : sub->h_sitems) M = std::min(M, pick_tile_frames(M, T, it.jspan - 1, rows));
+    if (4 * M < (columns ? 2 : 3) * nna::SHORT_FRAMES[form] || (columns && sub->hop % 32 != 0)) return false;
+    const long long nseg = 1 + (M - 1 + T - 1) / T;
+    P.plane = nna::SHORT_PLANE_MIN[form];
+    for (const nna::ShortItem& it : sub->h_sitems)
+      if (!columns) P.plane = std::max(P.plane, nna::SHORT_PLANE((M + nseg * (it.jspan - 1)) * sub->hop));
+    P.tile_frames = M;
+    P.n_ft = (n_frames + M - 1) / M;
+    return true;
+  };
+  auto many = [&](long long tiles) { return P.n_ft * P.n_items >= tiles; };
+  if (fit(nna::SHORT_64, 80 * 1024) && many(512)) return true;
+  if (fit(nna::SHORT_COLUMNS, 0) && many(512)) return true;
+  if (fit(nna::SHORT_32, 80 * 1024) && many(256)) return true;
+  return fit(nna::SHORT_16, 80 * 1024) || fit(nna::SHORT_16, nna::SHORT_LDS) || fit(nna::SHORT_COLUMNS, 0);
+}
+
+nna_status run_conv_short(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
+                          long long out_wave_stride, int row_offset, nna::ShortParams& P, void* hip_stream) {
+  P.g = make_geom(sub, x, B, L, T);
+  P.w = reinterpret_cast<const uint4*>(sub->d_sw);
+  P.taps = reinterpret_cast<const float2*>(sub->d_staps);
+  P.support = sub->d_ssupport;
+  P.steps = sub->d_ssteps;
+  P.columns = sub->d_scolumns;
+  P.items = sub->d_sitems;
+  P.out = out + (long long)row_offset * T;
+  P.out_wave_stride = out_wave_stride;
+  P.fmt = sub->fmt;
+  const hipError_t e = nna::launch_cqt_short(P, reinterpret_cast<hipStream_t>(hip_stream));
+  if (e != hipSuccess) return fail_hip(e, "kernel launch");
+  return NNA_OK;
+}
+
 hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t stream) {
   if (sub->d_wrm) {
     const long long T = P.g.T, rows = nna::CQW_FRAMES + (1 + (nna::CQW_FRAMES - 1 + T - 1) / T) * (sub->few_jspan - 1);
@@ -423,6 +472,11 @@ nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long 
     nna::CqlParams Q;
     std::memset(&Q, 0, sizeof(Q));
     if (shape_lowrank(sub, B * T, T, Q)) return run_conv_lowrank(sub, x, B, L, T, out, out_wave_stride, row_offset, Q, hip_stream);
+  }
+  if (sub->runs_short()) {
+    nna::ShortParams Q;
+    std::memset(&Q, 0, sizeof(Q));
+    if (shape_short(sub, B * T, T, Q)) return run_conv_short(sub, x, B, L, T, out, out_wave_stride, row_offset, Q, hip_stream);
   }
   const int extra = (sub->max_jspan - 1) * sub->row_step;
   const int M = pick_tile_frames(CQ_FRAMES, T, extra, CQ_LDS_ROWS_MAX);
