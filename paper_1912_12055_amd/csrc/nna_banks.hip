@@ -1125,6 +1125,13 @@ void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels) {
     add_direct(as_is[i], std::min(two ? 2 * kGroup : kGroup, p->n_bins - as_is[i]));
     if (two) ++i;
   }
+  std::vector<std::pair<int, int>> runs;
+  for (const int k0 : as_is) {
+    const int k1 = std::min(k0 + kGroup, p->n_bins);
+    if (!runs.empty() && runs.back().second == k0) runs.back().second = k1;
+    else runs.push_back({k0, k1});
+  }
+  build_cqt_bank_short(p, kernels, runs);
   // those with a basis first, the heaviest first: the light ones fill their launch's tail
   auto weight = [&](const nna::CqlItem& it) {
     return it.r ? 1e12 + 16.0 * it.n_ib * hop + 256.0 * (it.n_step + it.s_hi - it.s_lo) : (double)it.n_step;
@@ -1215,12 +1222,16 @@ void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<uns
 }
 
 // The kernels tap by tap (nna_kernels_short.hip): items of up to 24 bins, their taps in steps of 32.
-void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels) {
+void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std::vector<std::pair<int, int>>& runs) {
   p->short_taps = false;
   const int hop = p->hop;
   if (hop % 4 != 0 || p->K > 1 << 16) return;
+  int n_bins = 0;
+  std::vector<char> in_run(p->n_bins, 0);
+  for (const auto& [lo, hi] : runs)
+    for (int k = lo; k < hi; ++k) n_bins += !in_run[k], in_run[k] = 1;
   std::vector<long long> first(p->n_bins + 1, 0);  // of a kernel's own taps
-  for (int k = 0; k < p->n_bins; ++k) first[k + 1] = first[k] + p->row_e[2 * k] - p->row_s[2 * k];
+  for (int k = 0; k < p->n_bins; ++k) first[k + 1] = first[k] + (in_run[k] ? p->row_e[2 * k] - p->row_s[2 * k] : 0);
   if (first[p->n_bins] > 1 << 28) return;
   p->h_staps.resize(2 * first[p->n_bins]);
   for_each_parallel(p->n_bins, [&](int k) {
@@ -1235,10 +1246,13 @@ void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels) {
   for (int k = 0; k < p->n_bins; ++k)
     for (const long long v : {p->row_s[2 * k], p->row_e[2 * k], first[k], 0LL}) p->h_ssupport.push_back((int)v);
   constexpr int per_item = 8 * nna::SHORT_RB;
-  for (int k0 = 0; k0 < p->n_bins; k0 += per_item) {
+  std::vector<std::pair<int, int>> items;
+  for (const auto& [lo, hi] : runs)
+    for (int k0 = lo; k0 < hi; k0 += per_item) items.push_back({k0, std::min(per_item, hi - k0)});
+  for (const auto& [k0, nb] : items) {
     nna::ShortItem item{};
     item.bin0 = k0;
-    item.n_bins = std::min(per_item, p->n_bins - k0);
+    item.n_bins = nb;
     const int n_rb = (item.n_bins + 7) / 8;
     long long lo[nna::SHORT_RB], hi[nna::SHORT_RB];
     for (int b = 0; b < n_rb; ++b) block_taps(p, k0, item.n_bins, b, lo[b], hi[b]);
@@ -1270,18 +1284,21 @@ void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels) {
       item.columns = (int)p->h_scolumns.size();
       std::vector<int> order;
       for (int c = 0; c < hop; c += 32) {
-        p->h_scolumns.push_back((int)order.size());
+        p->h_scolumns.push_back((int)order.size() / 2);
         for (int j = 0; j < item.jspan; ++j) {
           const int s = j * (hop / 32) + c / 32, a = s < item.n_step ? p->h_ssteps[item.step0 + s] : 0;
-          if (a) order.push_back(a | j << 2 | s << 12);
+          if (!a) continue;
+          order.push_back(a | j << 2 | c / 32 << 12);
+          order.push_back(s);
         }
       }
-      p->h_scolumns.push_back((int)order.size());
+      p->h_scolumns.push_back((int)order.size() / 2);
+      if (p->h_scolumns.size() % 2) p->h_scolumns.push_back(0);
       p->h_scolumns.insert(p->h_scolumns.end(), order.begin(), order.end());
     }
     p->h_sitems.push_back(item);
   }
-  p->short_taps = true;
+  p->short_taps = n_bins == p->n_bins;
 }
 
 // [2 n_bins][K]: the kernels of `p`'s items, multiplied out

@@ -441,4 +441,19 @@ __device__ __forceinline__ void stft_grad_tile(const f32x16 (&acc)[ST_RB], const
     }
 }
 
+// (Re, Im) of constant-Q bin `bin` in the output format; op: (waveform, first bin, frame)
+__device__ __forceinline__ void store_bin(int fmt, long long T, float* __restrict__ op, long long bin, float re, float im) {
+  const float pw = re * re + im * im;
+  if (fmt == NNA_OUT_COMPLEX) {
+    op[2 * bin * T] = re;
+    op[(2 * bin + 1) * T] = im;
+  } else if (fmt == NNA_OUT_PHASE) {
+    op[bin * T] = atan2f(im, re);
+  } else {
+    op[bin * T] = fmt == NNA_OUT_MAGNITUDE ? format_power<NNA_OUT_MAGNITUDE>(pw)
+                  : fmt == NNA_OUT_POWER   ? pw
+                                           : format_power<NNA_OUT_LOG>(pw);
+  }
+}
+
 }  // namespace nna

@@ -441,7 +441,8 @@ CqtKernelSource cqt_kernels(const nna_plan* p);
 CqtKernelSource dense_kernels(std::vector<double> rows, long long K);  // [2 n_bins][K]
 bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy);
 void cqt_applied_rows(const nna_plan* p, double* out);
-void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels);  // sets p->short_taps if the plan qualifies
+// Bins [first, last) of every run, tap by tap (nna_kernels_short.hip); sets p->short_taps if the plan qualifies and they are all of its bins
+void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std::vector<std::pair<int, int>>& runs);
 void build_cqt_bank_rows(nna_plan* c, const std::vector<double>& rows);
 void build_cqt_bank_fold(nna_plan* p);  // sets p->cq_fold if the plan qualifies
 // the decimation filter of `fir_taps` taps: its taps, their split by parity for the decimation kernel, and the

@@ -261,6 +261,49 @@ struct CqfParams {
   long long n_ft;
 };
 
+// ---- constant-Q kernels tap by tap (nna_kernels_short.hip) ------------------------------------
+constexpr int SHORT_RB = 3;              // 16-row blocks of an item
+constexpr int SHORT_LDS = 156 * 1024;
+// forms: tiles of 64, 32 or 16 frames, each wave a quarter of their steps; of 128, each wave a quarter of them, 32 columns at a time; of 64,
+// each wave a quarter of their steps, 32, 64 or 128 columns at a time
+enum { SHORT_64, SHORT_32, SHORT_16, SHORT_COLUMNS, SHORT_COLUMNS_64, SHORT_FORMS };
+constexpr int SHORT_FRAMES[SHORT_FORMS] = {64, 32, 16, 128, 64};
+constexpr int SHORT_ROWS = 128;          // SHORT_COLUMNS: hops of a tile
+constexpr int SHORT_PASSES = 5;          // SHORT_COLUMNS_64: hops times columns at once, as many times 2,048 values
+// values per plane that the waves' sums, or the rows, take
+constexpr int SHORT_PLANE_MIN[SHORT_FORMS] = {8192, 4096, 2048, SHORT_ROWS * 40, 8192};
+constexpr int SHORT_PLANE(long long samples) { return (int)((samples + 32) * 9 / 8 + 16) / 8 * 8; }  // one octet in nine left free
+
+// A work item: up to 24 neighbouring bins (row block b: Re and Im of bins 8 b .. 8 b + 7), longest kernels first
+struct ShortItem {
+  long long w0;      // first uint4 of the weights: [step of 32 taps][row block][3 planes][64 lanes]
+  int step0;         // first entry of the item's table: how many row blocks every step has taps of
+  int n_step;
+  int columns;       // hops of whole 32 columns: first entry of its table of steps by columns
+  int j0, jspan;     // the item's hop-blocks of a frame: j0 .. j0 + jspan - 1
+  int bin0, n_bins;
+};
+
+struct ShortParams {
+  FrameGeom g;
+  const uint4* w;
+  const float2* taps;    // (Re, Im) of every kernel's own taps
+  const int4* support;   // [bins]: first tap, last tap + 1, where its taps begin
+  const int *steps, *columns;
+  const ShortItem* items;
+  float* out;
+  long long out_wave_stride;
+  long long n_ft;
+  int n_items;
+  int form;
+  int tile_frames;
+  int plane;             // values per plane in LDS
+  int columns_at_once;
+  int fmt;
+};
+hipError_t launch_cqt_short(const ShortParams& p, hipStream_t stream);
+hipError_t short_kernels_init();  // per-process function attributes
+
 // ---- constant-Q kernels in two stages over hop-blocks (nna_kernels_cql.hip) -------------------
 constexpr int CQL_MAX_BASIS = 8;   // 16-row blocks of an item's basis
 constexpr long long CQL_MAX_TAPS = 1 << 18;  // of a kernel: the plan holds 32 of them in double precision
@@ -307,52 +350,12 @@ struct CqlParams {
   float* out;
   long long out_wave_stride;
   CqlPart basis, direct;  // the items with a basis; those whose kernels stay as they are
+  ShortParams shorts;     // ... or, of waveforms of many frames, tiles of nna_short.h in their place
   int fmt;
   int lds_floats;
 };
 hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream);
 hipError_t cql_kernels_init();  // per-process function attributes of nna_kernels_cql.hip
-
-// ---- constant-Q kernels tap by tap (nna_kernels_short.hip) ------------------------------------
-constexpr int SHORT_RB = 3;              // 16-row blocks of an item
-constexpr int SHORT_LDS = 156 * 1024;
-constexpr int SHORT_PITCH = 40;          // COLUMNS: values of a row of 32, so that rows of 16 frames lie on different banks
-constexpr int SHORT_ROWS = 128;          // ... and rows
-// forms: tiles of 64, 32 or 16 frames, each wave a quarter of their steps; of 128, each wave a quarter of them, 32 columns at a time
-enum { SHORT_64, SHORT_32, SHORT_16, SHORT_COLUMNS, SHORT_FORMS };
-constexpr int SHORT_FRAMES[SHORT_FORMS] = {64, 32, 16, 128};
-// values per plane that the waves' sums, or the rows, take
-constexpr int SHORT_PLANE_MIN[SHORT_FORMS] = {8192, 4096, 2048, SHORT_ROWS * SHORT_PITCH};
-constexpr int SHORT_PLANE(long long samples) { return (int)((samples + 32) * 9 / 8 + 16) / 8 * 8; }  // one octet in nine left free
-
-// A work item: up to 24 neighbouring bins (row block b: Re and Im of bins 8 b .. 8 b + 7), longest kernels first
-struct ShortItem {
-  long long w0;      // first uint4 of the weights: [step of 32 taps][row block][3 planes][64 lanes]
-  int step0;         // first entry of the item's table: how many row blocks every step has taps of
-  int n_step;
-  int columns;       // hops of whole 32 columns: first entry of its table of steps by columns
-  int j0, jspan;     // the item's hop-blocks of a frame: j0 .. j0 + jspan - 1
-  int bin0, n_bins;
-};
-
-struct ShortParams {
-  FrameGeom g;
-  const uint4* w;
-  const float2* taps;    // (Re, Im) of every kernel's own taps
-  const int4* support;   // [bins]: first tap, last tap + 1, where its taps begin
-  const int *steps, *columns;
-  const ShortItem* items;
-  float* out;
-  long long out_wave_stride;
-  long long n_ft;
-  int n_items;
-  int form;
-  int tile_frames;
-  int plane;             // values per plane in LDS
-  int fmt;
-};
-hipError_t launch_cqt_short(const ShortParams& p, hipStream_t stream);
-hipError_t short_kernels_init();  // per-process function attributes
 
 // ---- backward pass of the STFT layer (trainable kernel banks) --------------------------------
 constexpr int BW_MT = 128;   // output tile rows per workgroup

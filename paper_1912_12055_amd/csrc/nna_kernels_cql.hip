@@ -32,34 +32,18 @@
 // by latency, a workgroup or two per CU.  1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms
 // folded about the centres, 8.25 here in float32, 6.59 in bfloat16 with every coordinate split by each frame that reads it, now 5.74;
 // 16 x 220,500, 84 bins of 12 per octave: 300 -> 67.8 -> 53.8 us; the dense composed kernels of the frequency-domain layer (16 x
-// 220,500, 16,384 taps): 566 -> 183 -> 138 us.
+// 220,500, 16,384 taps): 566 -> 183 -> 138 us.  With the short kernels by tiles of nna_short.h (the direct items read four row blocks' weights for
+// every 16 frames, and the loads' issue bound them): 5.81 -> 5.12 ms, 58 -> 46 us.
 #include <type_traits>
 
-#include "nna_device.h"
+#include "nna_short.h"
 
 namespace nna {
 namespace {
 
-typedef f32x4 f32x4_u __attribute__((aligned(4)));
 using std::integral_constant;
 using True = integral_constant<bool, true>;
 using False = integral_constant<bool, false>;
-
-// (Re, Im) of bin `bin` in the output format; op: (waveform, first bin, frame)
-__device__ __forceinline__ void store_bin(const CqlParams& P, float* __restrict__ op, long long bin, float re, float im) {
-  const long long T = P.g.T;
-  const float pw = re * re + im * im;
-  if (P.fmt == NNA_OUT_COMPLEX) {
-    op[2 * bin * T] = re;
-    op[(2 * bin + 1) * T] = im;
-  } else if (P.fmt == NNA_OUT_PHASE) {
-    op[bin * T] = atan2f(im, re);
-  } else {
-    op[bin * T] = P.fmt == NNA_OUT_MAGNITUDE ? format_power<NNA_OUT_MAGNITUDE>(pw)
-                  : P.fmt == NNA_OUT_POWER   ? pw
-                                             : format_power<NNA_OUT_LOG>(pw);
-  }
-}
 
 // lane (q, n), registers 0 .. 3 of row block b: (Re, Im) of bins 8 b + 2 q and + 1, frame n of the wave's frame block.  Returns the
 // bins that are not finite, bit 2 (RB fb + rb) + u.
@@ -80,7 +64,7 @@ __device__ __forceinline__ unsigned store_bins(const CqlParams& P, const CqlItem
         const int k = 8 * rb + 2 * q + u;
         if (k >= item.n_bins) continue;
         const float re = acc[fb][rb][2 * u], im = acc[fb][rb][2 * u + 1];
-        store_bin(P, op, item.bin0 + k, re, im);
+        store_bin(P.fmt, P.g.T, op, item.bin0 + k, re, im);
         odd |= (finite(re) && finite(im) ? 0u : 1u) << (2 * (RB * fb + rb) + u);
       }
   }
@@ -276,7 +260,7 @@ __device__ __forceinline__ void direct_item(const CqlParams& P, const CqlPart& p
           met = true;
         }
       }
-    store_bin(P, P.out + b * P.out_wave_stride + t, item.bin0 + k, re, im);
+    store_bin(P.fmt, g.T, P.out + b * P.out_wave_stride + t, item.bin0 + k, re, im);
   }
 }
 
@@ -657,25 +641,34 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       re += yr;
       im += yi;
     }
-    store_bin(P, P.out + b * P.out_wave_stride + t, item.bin0 + k, re, im);
+    store_bin(P.fmt, g.T, P.out + b * P.out_wave_stride + t, item.bin0 + k, re, im);
   }
 }
 
 // FB, FD: 16-frame blocks per wave of the items with a basis and of the direct ones.  The direct ones come first, the item the slow
-// index.  The others: workgroup ids are dealt round-robin to the 8 XCDs, and the items of one tile are neighbours on one XCD,
+// index; tiles of nna_short.h in their place (SHORT) last, their items neighbours too: they are many and short, those with a basis
+// few and long in a short batch (tiles first: 65 us for 46 at 16 x 220,500).  The others: workgroup ids are dealt round-robin to the 8 XCDs, and the items of one tile are neighbours on one XCD,
 // where they meet the tile's samples in its L2 (28 million L2 misses instead of 263 million, 7.1 -> 6.5 ms at 1,770 x 176,400);
 // rotated by one from tile to tile, because items differ in length and the CUs are dealt out in a fixed order too.
-template <int FB, int FD>
+template <int FB, int FD, bool SHORT>
 __global__ __launch_bounds__(256, 2) void cqt_lowrank_kernel(const CqlParams P) {
   extern __shared__ __attribute__((aligned(16))) float Y[];
   long long bid = blockIdx.x;
-  const long long n_direct = P.direct.n_ft * P.direct.n_items;
-  if (bid < n_direct) {
-    const int id = (int)(bid / P.direct.n_ft);
-    const CqlItem item = P.direct.items[id];
-    direct_item<FD>(P, P.direct, item, bid - (long long)id * P.direct.n_ft, Y);
+  const long long n_basis = (P.basis.n_ft + 7) / 8 * 8 * P.basis.n_items, n_direct = P.direct.n_ft * P.direct.n_items;
+  if (SHORT ? bid >= n_basis : bid < n_direct) {
+    if constexpr (SHORT) {
+      bid -= n_basis;
+      const long long local = bid >> 3, tile = local / P.shorts.n_items, ft = (bid & 7) * ((P.shorts.n_ft + 7) >> 3) + tile;
+      if (ft >= P.shorts.n_ft) return;
+      const ShortItem item = P.shorts.items[local - tile * P.shorts.n_items];
+      short_tile<FD, 4, COLUMNS>(P.shorts, item, ft, reinterpret_cast<unsigned short*>(Y));
+    } else {
+      const int id = (int)(bid / P.direct.n_ft);
+      const CqlItem item = P.direct.items[id];
+      direct_item<FD>(P, P.direct, item, bid - (long long)id * P.direct.n_ft, Y);
+    }
   } else {
-    bid -= n_direct;
+    if (!SHORT) bid -= n_direct;
     const int n_items = P.basis.n_items;
     const long long local = bid >> 3, per_xcd = (P.basis.n_ft + 7) >> 3, tile = local / n_items;
     const long long ft = (bid & 7) * per_xcd + tile;
@@ -685,15 +678,15 @@ __global__ __launch_bounds__(256, 2) void cqt_lowrank_kernel(const CqlParams P) 
   }
 }
 
-template <int FB, int FD>
+template <int FB, int FD, bool SHORT = false>
 hipError_t allow_lds() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(cqt_lowrank_kernel<FB, FD>), hipFuncAttributeMaxDynamicSharedMemorySize,
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(cqt_lowrank_kernel<FB, FD, SHORT>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              CQL_LDS_ONE);
 }
 
-template <int FB, int FD>
+template <int FB, int FD, bool SHORT = false>
 void launch(const CqlParams& p, unsigned blocks, hipStream_t stream) {
-  hipLaunchKernelGGL((cqt_lowrank_kernel<FB, FD>), dim3(blocks), dim3(256), (size_t)p.lds_floats * 4, stream, p);
+  hipLaunchKernelGGL((cqt_lowrank_kernel<FB, FD, SHORT>), dim3(blocks), dim3(256), (size_t)p.lds_floats * 4, stream, p);
 }
 
 }  // namespace
@@ -704,19 +697,31 @@ hipError_t cql_kernels_init() {
   if (e == hipSuccess) e = allow_lds<4, 1>();
   if (e == hipSuccess) e = allow_lds<2, 2>();
   if (e == hipSuccess) e = allow_lds<4, 2>();
+  if (e == hipSuccess) e = allow_lds<1, 4, true>();
+  if (e == hipSuccess) e = allow_lds<2, 4, true>();
+  if (e == hipSuccess) e = allow_lds<4, 4, true>();
   return e;
 }
 
 hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream) {
   clear_stale_error();
-  const long long blocks = (p.basis.n_ft + 7) / 8 * 8 * p.basis.n_items + p.direct.n_ft * p.direct.n_items;
+  const bool shorts = p.shorts.n_items > 0;
+  const long long blocks = (p.basis.n_ft + 7) / 8 * 8 * p.basis.n_items +
+                           (shorts ? (p.shorts.n_ft + 7) / 8 * 8 * p.shorts.n_items : p.direct.n_ft * p.direct.n_items);
   if (blocks <= 0 || blocks > 0x7fffffffLL || p.g.hop % 32) return hipErrorInvalidValue;
   if (p.basis.tile_frames < 1 || p.basis.tile_frames > 64 * p.basis.fb || p.direct.tile_frames > 64 * p.direct.fb) return hipErrorInvalidValue;
   if (p.lds_floats < 1 || (size_t)p.lds_floats * 4 > (size_t)CQL_LDS_ONE) return hipErrorInvalidValue;
   // (a batch large enough for two blocks per wave of the direct items is so for those with a basis)
   const int fb = p.basis.fb, fd = p.direct.fb;
   if ((fb != 1 && fb != 2 && fb != 4) || (fd != 1 && fd != 2) || fd > fb) return hipErrorInvalidValue;
-  if (fd == 1)
+  if (shorts) {
+    const ShortParams& s = p.shorts;
+    constexpr int form = SHORT_COLUMNS_64;
+    if (s.form != form || s.tile_frames < 1 || s.tile_frames > SHORT_FRAMES[form] || s.plane % 8 != 0 || s.plane < SHORT_PLANE_MIN[form] ||
+        s.plane * 6 + 16 > p.lds_floats * 4 || s.columns_at_once < 32 || s.g.hop % s.columns_at_once != 0 || s.g.L < 4)
+      return hipErrorInvalidValue;
+    fb == 1 ? launch<1, 4, true>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 4, true>(p, (unsigned)blocks, stream) : launch<4, 4, true>(p, (unsigned)blocks, stream);
+  } else if (fd == 1)
     fb == 1 ? launch<1, 1>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 1>(p, (unsigned)blocks, stream) : launch<4, 1>(p, (unsigned)blocks, stream);
   else
     fb == 2 ? launch<2, 2>(p, (unsigned)blocks, stream) : launch<4, 2>(p, (unsigned)blocks, stream);

@@ -1,59 +1,11 @@
-// Constant-Q transform with time-domain kernels (Sec. III-C, eq. (CQT)), tap by tap: the octaves of the downsampling layers, whose
-// kernels are short and whose hops are small.
-//
-//     C_k[t] = sum_n w_k[n] x[t hop + n]
-//
-// On v_mfma_f32_16x16x32_bf16, every float32 as three bfloat16 and six products of nine (see nna_kernels_cql.hip, which takes its sums
-// the same way: 32 products from zero, then added to a total).  A workgroup takes one item -- up to 24 neighbouring bins, three blocks of
-// 16 rows -- and one tile of frames.  Neighbouring frames share most of their samples, so samples are split once, on the way into LDS,
-// and every step of 32 taps finds its operand there as it goes into the instruction.  Kernels shrink from row block to row block: a step
-// knows how many of them it has taps of.
-//   Tiles of 64, 32 or 16 frames: all their samples at once, one behind the other; each wave takes every fourth step of all frames, so
-//   that a workgroup reads the weights once, and the waves' sums are added through LDS.
-//   Tiles of 128 frames, where 64 frames' samples do not fit: 32 columns of all their hops at a time, a row for each hop, the next 32
-//   requested while the last step of these is multiplied (loads return in order: requested earlier, they would be waited for with the
-//   next step's weights).
-//
-// Bound by the matrix pipe and the splits in turn while hops are short (hop 64: pipe 58 % busy, vector ALUs 62 %, three workgroups per CU),
-// by latency where a tile is read column by column (hop 512: 29 %, 51 %).  1,770 x 345 frames, 24 bins of up to 742 taps
-// (MI355X), hop 512 down to 8, against cqt_kernel's float32 instruction:
-//   683, 494, 484, 359, 312, 292, 325 us -> 398, 306, 267, 196, 193, 183, 177;
-// 16 x 431 frames, 12 bins: 30, 29, 23, 17, 15, 14, 14 -> 10, 9, 10, 8, 9, 9, 9.  (hop 512 and 256 with the samples read straight into
-// registers by every wave: 527, 459 us; with tiles of 256 frames by columns, two workgroups per CU: 512, 375; hop 64 by columns: 233.)
-// Errors against 64 bits, 2-norm: 5e-8 .. 1.8e-7 of an octave where cqt_kernel's chains are off by 2.5e-7 .. 8e-7.
-#include "nna_device.h"
+// Constant-Q kernels tap by tap: the launches of nna_short.h.
+#include "nna_short.h"
 
 namespace nna {
 namespace {
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-typedef f32x4 f32x4_u __attribute__((aligned(4)));
-
-__device__ __forceinline__ void store_bin(const ShortParams& P, float* __restrict__ op, long long bin, float re, float im) {
-  const long long T = P.g.T;
-  const float pw = re * re + im * im;
-  if (P.fmt == NNA_OUT_COMPLEX) {
-    op[2 * bin * T] = re;
-    op[(2 * bin + 1) * T] = im;
-  } else if (P.fmt == NNA_OUT_PHASE) {
-    op[bin * T] = atan2f(im, re);
-  } else {
-    op[bin * T] = P.fmt == NNA_OUT_MAGNITUDE ? format_power<NNA_OUT_MAGNITUDE>(pw)
-                  : P.fmt == NNA_OUT_POWER   ? pw
-                                             : format_power<NNA_OUT_LOG>(pw);
-  }
-}
-
-// its first bfloat16 is finite
-__device__ __forceinline__ bool tame(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7fffffffu) < 0x7f7f8000u; }
-
-// where a tile's samples lie in LDS: one behind the other, in words of eight or (hops that are no multiple of 8) of four; or 32 columns of
-// all its hops at a time, a row for each hop
-enum { OCTETS_OF, QUADS_OF, COLUMNS };
-
-// WK = 4: the four waves share the steps of 16 FB frames; 1: each has 16 FB frames of its own.
 template <int FB, int WK, int LAYOUT>
-__global__ __launch_bounds__(256, LAYOUT == COLUMNS ? 4 : 3) void short_kernel(const ShortParams P) {
+__global__ __launch_bounds__(256, LAYOUT != COLUMNS ? 3 : WK == 1 ? 4 : 2) void short_kernel(const ShortParams P) {
   extern __shared__ __attribute__((aligned(16))) unsigned short S[];
   // the items of one tile are neighbours on one XCD
   const int n_items = P.n_items;
@@ -61,400 +13,7 @@ __global__ __launch_bounds__(256, LAYOUT == COLUMNS ? 4 : 3) void short_kernel(c
   const long long ft = (blockIdx.x & 7) * per_xcd + tile;
   if (tile >= per_xcd || ft >= P.n_ft) return;
   const ShortItem item = P.items[local - tile * n_items];
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int q = lane >> 4, n = lane & 15;
-  const FrameGeom& g = P.g;
-  const long long f0 = ft * P.tile_frames;
-  const int m_valid = (int)((g.n_frames - f0) < P.tile_frames ? (g.n_frames - f0) : P.tile_frames);
-  TileMap tm;
-  tm.T = g.T;
-  tm.b0 = f0 / g.T;
-  tm.t0 = (int)(f0 - tm.b0 * g.T);
-  tm.n0 = (g.T - tm.t0) < m_valid ? (g.T - tm.t0) : m_valid;
-  tm.extra = item.jspan - 1;
-  const int rows_used = tm.frame_row(m_valid - 1) + tm.extra + 1;
-  const int hop = g.hop, L = (int)g.L;
-  constexpr int RB = SHORT_RB, THREADS = 256;
-  constexpr bool OCTETS = LAYOUT == OCTETS_OF;
-  const int plane = P.plane;  // values per plane
-  const int n_step = item.n_step;
-  const int* __restrict__ steps = P.steps + item.step0;  // row blocks with taps
-  const uint4* __restrict__ wp = P.w + item.w0 + lane;   // [step][row block][3 planes][64 lanes]
-  auto fetch_w = [&](int s, u32x4 (&v)[RB][3]) {
-    const int at = s < n_step ? s : n_step - 1;  // (what is behind the last is read and dropped)
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int l = 0; l < 3; ++l) v[i][l] = *reinterpret_cast<const u32x4*>(wp + ((at * RB + i) * 3 + l) * 64);
-  };
-  const int wf = wave / WK, wk = wave % WK;
-  u32x4 w[RB][3];
-
-  // ---- samples: split once, on the way into LDS ----------------------------------------------
-  // A sample that is not finite, or so large that its first bfloat16 is not, would make every sum that holds its step of 32 taps NaN.  It
-  // counts as zero here, and its products are added to the bins whose own taps meet it at the end.
-  int* const flag = reinterpret_cast<int*>(S + 3 * plane);
-  if (tid == 0) *flag = 0;
-  __syncthreads();
-  auto reflect_run = [&](int s) { return s < 0 ? -s - 3 : s > L - 4 ? 2 * (L - 1) - s - 3 : s; };
-  // four samples from `s` of waveform xb on: a stored run, read backwards behind an end; one that straddles an end sample by sample
-  auto four = [&](const float* __restrict__ xb, int s) {
-    f32x4 v;
-    const int src = reflect_run(s);
-    if ((unsigned)src <= (unsigned)(L - 4)) {
-      v = *reinterpret_cast<const f32x4_u*>(xb + src);
-      if (src != s) v = (f32x4){v.w, v.z, v.y, v.x};
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = xb[reflect_clamped(s + e, L)];
-    }
-    return v;
-  };
-  // a unit's parts; `v` may change
-  auto planes = [&](f32x4 (&v)[2]) {
-    Planes b = split8(v);
-    u16x2 top = {0, 0};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, b.p[0][i] & 0x7fff7fffu));
-    if (__builtin_elementwise_max(top.x, top.y) >= 0x7f80) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[h][e] = tame(v[h][e]) ? v[h][e] : 0.f;
-      b = split8(v);
-      *flag = 1;
-    }
-    return b;
-  };
-  constexpr int EB = WK == 1 ? FB : 1;  // frame blocks a wave ends up with
-  f32x4 acc[EB][RB], sum[FB][RB];
-  int x_off[FB];
-#pragma unroll
-  for (int fb = 0; fb < FB; ++fb) {
-    const int i = wf * (16 * FB) + fb * 16 + n;
-    x_off[fb] = (i < m_valid ? tm.frame_row(i) : 0) * (LAYOUT == COLUMNS ? SHORT_PITCH : hop) + 8 * q;
-#pragma unroll
-    for (int b = 0; b < RB; ++b) sum[fb][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  }
-  // one octet of every nine is left free, so that frames a hop of 16 .. 512 apart lie on different banks
-  auto place = [](int i) { return OCTETS ? i + (i >> 6 << 3) : i; };
-  // a step whose first value is `offset` from the frame's row, for its first `a` row blocks; each block's weights make room for step `next`'s
-  auto step = [&](int a, int offset, int next) {
-    u32x4 x[FB][3];
-#pragma unroll
-    for (int fb = 0; fb < FB; ++fb) {
-      const unsigned short* p = S + place(x_off[fb] + offset);
-#pragma unroll
-      for (int l = 0; l < 3; ++l) {
-        if constexpr (LAYOUT != QUADS_OF) {
-          x[fb][l] = *reinterpret_cast<const u32x4*>(p + l * plane);
-        } else {
-          const uint2 lo = *reinterpret_cast<const uint2*>(p + l * plane), hi = *reinterpret_cast<const uint2*>(p + l * plane + 4);
-          x[fb][l] = (u32x4){lo.x, lo.y, hi.x, hi.y};
-        }
-      }
-    }
-    constexpr int lw[6] = {2, 1, 0, 1, 0, 0}, lx[6] = {0, 1, 2, 0, 1, 0};  // (small terms first)
-#pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      if (i < a) {
-        f32x4 t[FB];
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb) t[fb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int m = 0; m < 6; ++m)
-#pragma unroll
-          for (int fb = 0; fb < FB; ++fb)
-            t[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[i][lw[m]]), __builtin_bit_cast(bf16x8, x[fb][lx[m]]), t[fb], 0, 0, 0);
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb) sum[fb][i] += t[fb];
-      }
-#pragma unroll
-      for (int l = 0; l < 3; ++l) w[i][l] = *reinterpret_cast<const u32x4*>(wp + ((next * RB + i) * 3 + l) * 64);
-    }
-  };
-  if constexpr (LAYOUT == COLUMNS) {
-    static_assert(FB == 2 && WK == 1);
-    constexpr int PITCH = SHORT_PITCH, NP = SHORT_ROWS / 64;
-    // this thread's eight columns of every 64th row
-    const int cv = tid & 3, r0 = tid >> 2;
-    const float* xb[NP];
-    int pos[NP];
-    bool edge[NP];  // does a row of the wave leave its waveform?
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const int row = p * 64 + r0;
-      long long b;
-      int sigma;
-      tm.decode(row < rows_used ? row : rows_used - 1, b, sigma);
-      xb[p] = g.x + b * g.L;
-      pos[p] = (sigma + item.j0) * hop - g.pad + 8 * cv;
-      edge[p] = __builtin_amdgcn_ballot_w64(pos[p] < 0 || pos[p] > L - hop) != 0;
-      if (!edge[p]) xb[p] += pos[p];
-    }
-    f32x4 R[NP][2];
-    auto request = [&](int c) {
-#pragma unroll
-      for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (!edge[p]) {
-            R[p][h] = *reinterpret_cast<const f32x4_u*>(xb[p] + c + 4 * h);
-          } else {
-            const int src = reflect_run(pos[p] + c + 4 * h);
-            R[p][h] = *reinterpret_cast<const f32x4_u*>(xb[p] + (src < 0 ? 0 : src > L - 4 ? L - 4 : src));
-          }
-        }
-    };
-    // first step of every 32 columns, [hop / 32 + 1], then the steps in that order: row blocks | hop-block << 2 | step << 12
-    const int* __restrict__ chunk0 = P.columns + item.columns;
-    const int* __restrict__ order = chunk0 + hop / 32 + 1;
-    const int n_order = chunk0[hop / 32];
-    int d = order[0];
-    fetch_w(d >> 12, w);
-    request(0);
-    for (int c = 0; c < hop; c += 32) {
-      __syncthreads();  // the columns before have been read by every wave
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        if (p * 64 + r0 >= rows_used) continue;
-        f32x4 v[2] = {R[p][0], R[p][1]};
-#pragma unroll
-        for (int h = 0; h < 2 && edge[p]; ++h) {
-          const int s = pos[p] + c + 4 * h, src = reflect_run(s);
-          if (src != s) v[h] = (f32x4){v[h].w, v[h].z, v[h].y, v[h].x};
-          if ((unsigned)src > (unsigned)(L - 4)) v[h] = four(xb[p], s);
-        }
-        const Planes b = planes(v);
-#pragma unroll
-        for (int l = 0; l < 3; ++l) *reinterpret_cast<u32x4*>(S + l * plane + (p * 64 + r0) * PITCH + 8 * cv) = b.p[l];
-      }
-      __syncthreads();
-      // (loads return in order: the next columns are requested behind the weights of these columns' last step)
-      const int s1 = chunk0[c / 32 + 1], ahead = c + 32 < hop ? c + 32 : c;
-      int s = chunk0[c / 32];
-      if (s == s1) request(ahead);
-      for (; s < s1; ++s) {
-        if (s + 1 == s1) request(ahead);
-        const int dn = order[s + 1 < n_order ? s + 1 : s];
-        step(d & 3, (d >> 2 & 1023) * PITCH, dn >> 12);
-        d = dn;
-      }
-    }
-  } else {
-    fetch_w(wk, w);
-    constexpr int N = OCTETS ? 8 : 4, U = 4;  // samples of a unit, units a thread requests at a time
-    const int per_row = hop / N, units = rows_used * per_row, first = tm.n0 + tm.extra, seg = g.T + tm.extra;
-    const float inv_row = 1.f / (float)per_row, inv_seg = 1.f / (float)seg;
-    const int base = item.j0 * hop - g.pad;
-    const float* __restrict__ x0 = g.x + tm.b0 * g.L;
-    for (int u0 = tid; u0 < units + 32 / N; u0 += THREADS * U) {
-      f32x4 v[U][2];
-#pragma unroll
-      for (int k = 0; k < U; ++k) {
-        const int u = u0 + THREADS * k;
-        v[k][0] = v[k][1] = (f32x4){0.f, 0.f, 0.f, 0.f};  // (the last step of the last frame reads up to 31 values, times zero, past its samples)
-        if (u >= units) continue;
-        // (quotients below 2^20 of whole numbers: half a unit away from the next one, rounding does not matter)
-        const int row = (int)(((float)u + 0.5f) * inv_row), col = N * (u - row * per_row);
-        const int later = row >= first ? 1 + (int)(((float)(row - first) + 0.5f) * inv_seg) : 0;
-        const int sigma = row >= first ? row - first - (later - 1) * seg : tm.t0 + row;
-        const int s = sigma * hop + base + col;
-        const float* __restrict__ xb = x0 + (long long)later * g.L;
-        if (s >= 0 && s <= L - N) {
-          v[k][0] = *reinterpret_cast<const f32x4_u*>(xb + s);
-          if constexpr (OCTETS) v[k][1] = *reinterpret_cast<const f32x4_u*>(xb + s + 4);
-        } else {
-          v[k][0] = four(xb, s);
-          if constexpr (OCTETS) v[k][1] = four(xb, s + 4);
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < U; ++k) {
-        const int u = u0 + THREADS * k;
-        if (u >= units + 32 / N) continue;
-        const Planes b = planes(v[k]);
-#pragma unroll
-        for (int l = 0; l < 3; ++l) {
-          unsigned short* to = S + l * plane + place(N * u);
-          if constexpr (OCTETS) *reinterpret_cast<u32x4*>(to) = b.p[l];
-          else *reinterpret_cast<uint2*>(to) = make_uint2(b.p[l][0], b.p[l][1]);
-        }
-      }
-    }
-    __syncthreads();
-    for (int s = wk; s < n_step; s += WK) step(steps[s], 32 * s, s + WK < n_step ? s + WK : s);
-  }
-  {
-    if constexpr (WK == 1) {
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-        for (int b = 0; b < RB; ++b) acc[fb][b] = sum[fb][b];
-    } else {
-      // the waves' sums, through LDS: wave k takes frame block k
-      f32x4* const part = reinterpret_cast<f32x4*>(S) + lane;  // [wave][frame block][row block][64 lanes]
-      __syncthreads();
-#pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-        for (int b = 0; b < RB; ++b) part[((wave * FB + fb) * RB + b) * 64] = sum[fb][b];
-      __syncthreads();
-#pragma unroll
-      for (int b = 0; b < RB; ++b) {
-        acc[0][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        if (wave < FB)
-          for (int k = 0; k < WK; ++k) acc[0][b] += part[((k * FB + wave) * RB + b) * 64];
-      }
-    }
-  }
-  bool valid[EB];  // this wave's frames
-#pragma unroll
-  for (int fb = 0; fb < EB; ++fb) valid[fb] = wave * (16 * EB) + fb * 16 + n < m_valid && (WK == 1 || wave < FB);
-  auto finite_sums = [&](int fb, int rb, int u) { return finite(acc[fb][rb][2 * u]) && finite(acc[fb][rb][2 * u + 1]); };
-  // `taken`: a bin whose taps meet such samples, bit 2 (RB fb + rb) + u
-  unsigned taken = 0;
-  if (*flag) {
-    // the tile's samples in units of four, hop by hop
-    const int per_row = hop / 4, units = rows_used * per_row;
-    auto unit = [&](int u) {
-      const int row = u / per_row, col = 4 * (u - row * per_row);
-      long long b;
-      int sigma;
-      tm.decode(row, b, sigma);
-      return four(g.x + b * g.L, (sigma + item.j0) * hop - g.pad + col);
-    };
-    int* const count = reinterpret_cast<int*>(S);
-    int2* const list = reinterpret_cast<int2*>(S) + 1;  // place in the tile, value
-    __syncthreads();
-    if (tid < 2) count[tid] = 0;
-    __syncthreads();
-    int mine = 0;
-#pragma unroll 1
-    for (int u = tid; u < units; u += THREADS) {
-      const f32x4 v = unit(u);
-      for (int e = 0; e < 4; ++e) mine += tame(v[e]) ? 0 : 1;
-    }
-    atomicAdd(count + 1, mine);
-    __syncthreads();
-    const bool dense = count[1] > units / 16;
-    auto add = [&](int fb, int rb, int u, int tap, const int4& own, float v) {
-      const float2 wt = P.taps[own.z + tap - own.x];
-      acc[fb][rb][2 * u] += wt.x * v;
-      acc[fb][rb][2 * u + 1] += wt.y * v;
-      taken |= 1u << (2 * (RB * fb + rb) + u);
-    };
-    // few of them: listed a thousand samples at a time, each for the frames it meets
-#pragma unroll 1
-    for (int u0 = 0; u0 < units && !dense; u0 += THREADS) {
-      __syncthreads();
-      if (tid == 0) *count = 0;
-      __syncthreads();
-      if (u0 + tid < units) {
-        const f32x4 v = unit(u0 + tid);
-        for (int e = 0; e < 4; ++e) {
-          const float value = v[e];
-          if (!tame(value)) list[atomicAdd(count, 1)] = make_int2(4 * (u0 + tid) + e, __builtin_bit_cast(int, value));
-        }
-      }
-      __syncthreads();
-      const int m = *count;
-#pragma unroll 1
-      for (int i = 0; i < m; ++i) {
-        const int2 bad = list[i];
-#pragma unroll
-        for (int fb = 0; fb < EB; ++fb) {
-          const int fi = wave * (16 * EB) + fb * 16 + n, at = bad.x - (valid[fb] ? tm.frame_row(fi) : 0) * hop, tap = at + item.j0 * hop;
-          if (!valid[fb] || at < 0 || at >= item.jspan * hop) continue;
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-              const int k = 8 * rb + 2 * q + u;
-              const int4 own = P.support[item.bin0 + (k < item.n_bins ? k : 0)];
-              if (k < item.n_bins && tap >= own.x && tap < own.y) add(fb, rb, u, tap, own, __builtin_bit_cast(float, bad.y));
-            }
-        }
-      }
-    }
-    // one in 64 or more: every bin looks for them, until it is NaN
-#pragma unroll 1
-    for (int bit = 0; bit < 2 * RB * EB && dense; ++bit) {
-      const int k = 8 * ((bit >> 1) % RB) + 2 * q + (bit & 1), fi = (wave * EB + (bit >> 1) / RB) * 16 + n;
-      if (fi >= m_valid || k >= item.n_bins || (WK > 1 && wave >= FB)) continue;
-      const long long f = f0 + fi, b = f / g.T;
-      const float* __restrict__ xw = g.x + b * g.L;
-      const int s0 = (int)(f - b * g.T) * hop - g.pad;
-      const int4 own = P.support[item.bin0 + k];
-      float re = 0.f, im = 0.f;
-      bool met = false;
-#pragma unroll 1
-      for (int tap = own.x; tap < own.y && !(re != re && im != im); tap += 16) {
-        f32x4 v[4];
-        bool any = false;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          if (e % 4 == 0) v[e / 4] = four(xw, s0 + tap + e);
-          any = any || !tame(v[e / 4][e % 4]);
-        }
-        if (!any) continue;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          if (tap + e >= own.y || tame(v[e / 4][e % 4])) continue;
-          const float2 wt = P.taps[own.z + tap + e - own.x];
-          re += wt.x * v[e / 4][e % 4];
-          im += wt.y * v[e / 4][e % 4];
-          met = true;
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 2 * RB * EB; ++i) {
-        if (i != bit || !met) continue;
-        acc[(i >> 1) / RB][(i >> 1) % RB][2 * (i & 1)] += re;
-        acc[(i >> 1) / RB][(i >> 1) % RB][2 * (i & 1) + 1] += im;
-        taken |= 1u << i;
-      }
-    }
-  }
-
-  // lane (q, n), registers 0 .. 3 of row block b: (Re, Im) of bins 8 b + 2 q and + 1, frame n of the wave's frame block
-  unsigned odd = 0;
-#pragma unroll
-  for (int fb = 0; fb < EB; ++fb) {
-    if (!valid[fb]) continue;
-    const long long f = f0 + wave * (16 * EB) + fb * 16 + n, b = f / g.T;
-    float* __restrict__ op = P.out + b * P.out_wave_stride + (f - b * g.T);
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int k = 8 * rb + 2 * q + u;
-        if (k >= item.n_bins) continue;
-        store_bin(P, op, item.bin0 + k, acc[fb][rb][2 * u], acc[fb][rb][2 * u + 1]);
-        odd |= (finite_sums(fb, rb, u) ? 0u : 1u) << (2 * (RB * fb + rb) + u);
-      }
-  }
-  // Sums that are not finite though all their samples are: the bfloat16 of samples next to the largest float32 overflow together.  Tap by tap.
-  odd &= ~taken;
-#pragma unroll 1
-  while (odd) {
-    const int bit = __builtin_ctz(odd), k = 8 * ((bit >> 1) % RB) + 2 * q + (bit & 1), fi = (wave * EB + (bit >> 1) / RB) * 16 + n;
-    odd &= odd - 1;
-    const long long f = f0 + fi, b = f / g.T;
-    const int t = (int)(f - b * g.T);
-    const int4 own = P.support[item.bin0 + k];  // first tap, last tap + 1, where its taps are
-    const float* __restrict__ xw = g.x + b * g.L;
-    float re = 0.f, im = 0.f;
-#pragma unroll 1
-    for (int tap = own.x; tap < own.y; ++tap) {
-      const float v = xw[reflect_clamped(t * hop - g.pad + tap, L)];
-      const float2 wt = P.taps[own.z + tap - own.x];
-      re += wt.x * v;
-      im += wt.y * v;
-    }
-    store_bin(P, P.out + b * P.out_wave_stride + t, item.bin0 + k, re, im);
-  }
+  short_tile<FB, WK, LAYOUT>(P, item, ft, S);
 }
 
 template <int FB, int WK, int LAYOUT>
@@ -473,7 +32,8 @@ void with_form(int form, bool octets, Fn fn) {
   if (form == SHORT_64) octets ? fn(Form<4, 4, OCTETS_OF>{}) : fn(Form<4, 4, QUADS_OF>{});
   else if (form == SHORT_32) octets ? fn(Form<2, 4, OCTETS_OF>{}) : fn(Form<2, 4, QUADS_OF>{});
   else if (form == SHORT_16) octets ? fn(Form<1, 4, OCTETS_OF>{}) : fn(Form<1, 4, QUADS_OF>{});
-  else fn(Form<2, 1, COLUMNS>{});
+  else if (form == SHORT_COLUMNS) fn(Form<2, 1, COLUMNS>{});
+  else fn(Form<4, 4, COLUMNS>{});
 }
 
 }  // namespace
@@ -489,7 +49,7 @@ hipError_t short_kernels_init() {
 hipError_t launch_cqt_short(const ShortParams& p, hipStream_t stream) {
   clear_stale_error();
   const long long blocks = (p.n_ft + 7) / 8 * 8 * p.n_items;
-  if (blocks <= 0 || blocks > 0x7fffffffLL || p.g.L < 4 || p.g.hop % (p.form == SHORT_COLUMNS ? 32 : 4) != 0) return hipErrorInvalidValue;
+  if (blocks <= 0 || blocks > 0x7fffffffLL || p.g.L < 4 || p.g.hop % (p.form >= SHORT_COLUMNS ? 32 : 4) != 0) return hipErrorInvalidValue;
   if (p.form < 0 || p.form >= SHORT_FORMS || p.tile_frames < 1 || p.tile_frames > SHORT_FRAMES[p.form]) return hipErrorInvalidValue;
   if (p.plane % 8 != 0 || p.plane < SHORT_PLANE_MIN[p.form] || (size_t)p.plane * 6 + 16 > (size_t)SHORT_LDS) return hipErrorInvalidValue;
   with_form(p.form, p.g.hop % 8 == 0, [&](auto f) { f.launch(p, (unsigned)blocks, stream); });

@@ -112,7 +112,7 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
         if (s == NNA_OK) s = upload(&p->d_litems, p->h_litems.data(), p->h_litems.size() * sizeof(nna::CqlItem), "hop-block item table");
         if (s == NNA_OK) s = upload(&p->d_lsupport, p->h_lsupport.data(), p->h_lsupport.size() * sizeof(int), "kernel supports");
       }
-      if (s == NNA_OK && p->short_taps) {
+      if (s == NNA_OK && !p->h_sitems.empty()) {
         s = upload(&p->d_sw, p->h_sw.data(), p->h_sw.size() * sizeof(unsigned), "kernels");
         if (s == NNA_OK) s = upload(&p->d_staps, p->h_staps.data(), p->h_staps.size() * sizeof(float), "kernels' own taps");
         if (s == NNA_OK) s = upload(&p->d_ssteps, p->h_ssteps.data(), p->h_ssteps.size() * sizeof(int), "step table");
@@ -228,7 +228,7 @@ nna_status make_cqt_plan(nna_plan** plan, int sr, int hop, double fmin, int k_fi
     for (int k = 0; k < n_bins; ++k) p->sk[k] = (taps - p->Nk[k]) / 2;
     build_cqt_bank(p);
     p->hop_blocks = !octave;
-    if (device >= 0) octave ? build_cqt_bank_short(p, cqt_kernels(p)) : build_cqt_bank_lowrank(p, cqt_kernels(p));
+    if (device >= 0) octave ? build_cqt_bank_short(p, cqt_kernels(p), {{0, n_bins}}) : build_cqt_bank_lowrank(p, cqt_kernels(p));
     build_cqt_bank_fold(p);
   } catch (const std::bad_alloc&) {
     delete p;
@@ -494,7 +494,7 @@ static nna_status make_cqt1992_plan(nna_plan** plan, int sr, int hop, double fmi
     c->hop_blocks = !octave;
     if (device >= 0) {
       const CqtKernelSource kernels = dense_kernels(std::move(rows), c->K);
-      octave ? build_cqt_bank_short(c, kernels) : build_cqt_bank_lowrank(c, kernels);
+      octave ? build_cqt_bank_short(c, kernels, {{0, n_bins}}) : build_cqt_bank_lowrank(c, kernels);
     }
   } catch (const std::bad_alloc&) {
     delete c;
@@ -814,12 +814,17 @@ nna_status nna_plan_applied_tiles(const nna_plan* plan, long long B, long long L
     nna_plan copy;
     nna::CqlParams P;
     std::memset(&P, 0, sizeof(P));
-    if (rebuild_lowrank(plan, sub, copy) && shape_lowrank(&copy, B * T, T, P))
+    if (rebuild_lowrank(plan, sub, copy) && shape_lowrank(&copy, B * T, T, P)) {
       for (int i = 0; i < 2; ++i) {
         const nna::CqlPart& part = i ? P.direct : P.basis;
         frames[i] = part.n_items ? part.tile_frames : 0;
         blocks[i] = part.n_items ? part.fb : 0;
       }
+      if (P.shorts.n_items) {
+        frames[1] = P.shorts.tile_frames;
+        blocks[1] = 1;
+      }
+    }
   } catch (const std::bad_alloc&) {
     return fail(NNA_ERR_ALLOC, "out of host memory");
   }

@@ -339,6 +339,50 @@ nna_status run_conv_fold(const nna_plan* sub, const float* x, long long B, long 
   return NNA_OK;
 }
 
+// The tile of a form of the short kernels, its samples in up to `lds` bytes; false: it holds too few of its frames
+bool fit_short(const nna_plan* sub, long long n_frames, long long T, int form, size_t lds, nna::ShortParams& P) {
+  P.n_items = (int)sub->h_sitems.size();
+  P.form = form;
+  int M = nna::SHORT_FRAMES[form], rows = 0;
+  const bool columns = form >= nna::SHORT_COLUMNS;
+  if (columns && sub->hop % 32 != 0) return false;
+  // by columns: as many at a time as the tile's rows leave room for
+  auto tile = [&](int kc) {
+    rows = !columns ? (int)(((long long)(lds - 16) / 6 - 24) * 8 / 9 - 32) / sub->hop
+           : form == nna::SHORT_COLUMNS ? nna::SHORT_ROWS
+                                        : std::min(nna::SHORT_PASSES * 2048 / kc, (int)((lds - 16) / 6 / (kc + 8)));
+    int m = nna::SHORT_FRAMES[form];
+    for (const nna::ShortItem& it : sub->h_sitems) m = std::min(m, pick_tile_frames(m, T, it.jspan - 1, rows));
+    P.columns_at_once = kc;
+    return m;
+  };
+  if (form <= nna::SHORT_COLUMNS) {
+    M = tile(32);
+  } else {
+    for (int kc = 128; kc >= 32; kc /= 2)
+      if (sub->hop % kc == 0 && ((M = tile(kc)) == nna::SHORT_FRAMES[form] || kc == 32)) break;
+  }
+  if (4 * M < 3 * nna::SHORT_FRAMES[form]) return false;
+  const long long nseg = 1 + (M - 1 + T - 1) / T;
+  P.plane = nna::SHORT_PLANE_MIN[form];
+  for (const nna::ShortItem& it : sub->h_sitems) {
+    const long long r = M + nseg * (it.jspan - 1);
+    P.plane = std::max(P.plane, columns ? (int)(r * (P.columns_at_once + 8)) : nna::SHORT_PLANE(r * sub->hop));
+  }
+  P.tile_frames = M;
+  P.n_ft = (n_frames + M - 1) / M;
+  return true;
+}
+
+void set_short(const nna_plan* sub, nna::ShortParams& P) {
+  P.w = reinterpret_cast<const uint4*>(sub->d_sw);
+  P.taps = reinterpret_cast<const float2*>(sub->d_staps);
+  P.support = sub->d_ssupport;
+  P.steps = sub->d_ssteps;
+  P.columns = sub->d_scolumns;
+  P.items = sub->d_sitems;
+}
+
 // The kernels by hop-blocks (nna_kernels_cql.hip).  A tile is 64 frames per 16-frame block of a wave (the registers of a direct
 // item hold two such blocks); smaller tiles spread a short batch over the chip.  Two workgroups per CU want 80 KB of LDS each; a
 // tile cut below three quarters for that takes one workgroup's 156 KB instead.  False: not a launch for this kernel.  It is one
@@ -374,8 +418,18 @@ bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::Cq
     part.tile_frames = M;
     part.n_ft = (n_frames + M - 1) / M;
     const long long nseg = 1 + (M - 1 + T - 1) / T;
+    // The kernels that stay as they are: by tiles whose waves share their steps (nna_short.h), each reading a quarter of the weights for 64
+    // frames, where 128 columns go into LDS at a time or the tiles would hold 64 frames anyway.  22,050 Hz, 84 bins, hop 512, 6,900
+    // frames: 58 -> 46 us, 87,000: 438 -> 373; 44.1 kHz, 168 bins, 610,650 frames: 5.81 -> 5.12 ms.  (60 bins of a large batch, tiles of 128
+    // frames against these: hop 64 216, 206 us, hop 96 157, 166, hop 160 229, 239.)
+    if (direct && (sub->hop % 128 == 0 || part.fb == 1) && !sub->h_sitems.empty() &&
+        fit_short(sub, n_frames, T, nna::SHORT_COLUMNS_64, 80 * 1024, P.shorts))
+      P.lds_floats = std::max(P.lds_floats, (P.shorts.plane * 6 + 16 + 3) / 4);
+    else
+      P.shorts.n_items = 0;
     for (int i = i0; i < i1; ++i) {
       const nna::CqlItem& it = sub->h_litems[i];
+      if (direct && P.shorts.n_items) break;
       const int rows = (int)(M + nseg * (it.jspan - 1));
       P.lds_floats = std::max(P.lds_floats, direct ? (rows + 31) / 32 * 32 * 2 * (nna::CQL_COLS(part.fb) + 4) : rows * it.r + 32);
       cost += direct ? 0.0 : (16.0 * it.n_ib * sub->hop * rows + 256.0 * (it.n_step + it.s_hi - it.s_lo) * cap) / M;
@@ -402,51 +456,42 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
   P.out = out + (long long)row_offset * T;
   P.out_wave_stride = out_wave_stride;
   P.fmt = sub->fmt;
+  if (P.shorts.n_items) {
+    nna::ShortParams& s = P.shorts;
+    s.g = P.g;
+    set_short(sub, s);
+    s.out = P.out;
+    s.out_wave_stride = out_wave_stride;
+    s.fmt = sub->fmt;
+    P.direct = nna::CqlPart{};
+    P.direct.fb = 1;
+  }
   const hipError_t e = nna::launch_cqt_lowrank(P, reinterpret_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
   return NNA_OK;
 }
 
 // The kernels tap by tap (nna_kernels_short.hip).  Tiles of 64 frames where 80 KB, half a CU's LDS, hold their samples and there are two
-// of them per CU; else tiles of 128 frames by columns where there are as many of these; else 32 or 16 frames, which fill the chip
-// sooner.  12 bins, hop 512: 16 frames 7.9, 18.6, 30.2, 53.5 us for 5,500, 17,250, 34,500, 69,000 frames, columns 20.5, 25.2, 29.9, 38.6;
-// 24 bins, hop 128: 64 frames 12.1, 15.2, 23.0, 36.4, columns 19.9, 20.3, 25.2, 36.0, 32 frames 9.4, 13.0, 19.6, 31.8; hop 64, 138,000 frames:
-// 47 with 64, 54 with 32, 60 by columns.  A tile that holds less than three quarters of its frames (half, by columns, where long
-// kernels take the rows) is left to the next one.  False: not a launch for this kernel.
+// of them per CU; else tiles of 128 frames by columns where there are as many of these, or, where long kernels take the rows, of 64; else
+// 32 or 16 frames, which fill the chip sooner.  12 bins, hop 512: 16 frames 7.9, 18.6, 30.2, 53.5 us for 5,500, 17,250, 34,500, 69,000
+// frames, columns 20.5, 25.2, 29.9, 38.6; 24 bins, hop 128: 64 frames 12.1, 15.2, 23.0, 36.4, columns 19.9, 20.3, 25.2, 36.0, 32 frames 9.4, 13.0,
+// 19.6, 31.8; hop 64, 138,000 frames: 47 with 64, 54 with 32, 60 by columns; 117,200 frames, kernels of 4,336 taps, hop 256 and 128: 64 by
+// columns 401, 358, 128 with half of their frames 478, 472.  A tile that holds less than three quarters of its frames is left to
+// the next one.  False: not a launch for this kernel.
 bool shape_short(const nna_plan* sub, long long n_frames, long long T, nna::ShortParams& P) {
-  P.n_items = (int)sub->h_sitems.size();
-  // the tile of a form, its samples in up to `lds` bytes; false: it holds less than three quarters of its frames
-  auto fit = [&](int form, size_t lds) {
-    P.form = form;
-    const bool columns = form == nna::SHORT_COLUMNS;
-    const int rows = columns ? nna::SHORT_ROWS : (int)(((long long)(lds - 16) / 6 - 24) * 8 / 9 - 32) / sub->hop;
-    int M = nna::SHORT_FRAMES[form];
-    for (const nna::ShortItem& it : sub->h_sitems) M = std::min(M, pick_tile_frames(M, T, it.jspan - 1, rows));
-    if (4 * M < (columns ? 2 : 3) * nna::SHORT_FRAMES[form] || (columns && sub->hop % 32 != 0)) return false;
-    const long long nseg = 1 + (M - 1 + T - 1) / T;
-    P.plane = nna::SHORT_PLANE_MIN[form];
-    for (const nna::ShortItem& it : sub->h_sitems)
-      if (!columns) P.plane = std::max(P.plane, nna::SHORT_PLANE((M + nseg * (it.jspan - 1)) * sub->hop));
-    P.tile_frames = M;
-    P.n_ft = (n_frames + M - 1) / M;
-    return true;
-  };
+  auto fit = [&](int form, size_t lds) { return fit_short(sub, n_frames, T, form, lds, P); };
   auto many = [&](long long tiles) { return P.n_ft * P.n_items >= tiles; };
   if (fit(nna::SHORT_64, 80 * 1024) && many(512)) return true;
   if (fit(nna::SHORT_COLUMNS, 0) && many(512)) return true;
+  if (fit(nna::SHORT_COLUMNS_64, 80 * 1024) && many(512)) return true;
   if (fit(nna::SHORT_32, 80 * 1024) && many(256)) return true;
-  return fit(nna::SHORT_16, 80 * 1024) || fit(nna::SHORT_16, nna::SHORT_LDS) || fit(nna::SHORT_COLUMNS, 0);
+  return fit(nna::SHORT_16, 80 * 1024) || fit(nna::SHORT_16, nna::SHORT_LDS) || fit(nna::SHORT_COLUMNS_64, 80 * 1024);
 }
 
 nna_status run_conv_short(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
                           long long out_wave_stride, int row_offset, nna::ShortParams& P, void* hip_stream) {
   P.g = make_geom(sub, x, B, L, T);
-  P.w = reinterpret_cast<const uint4*>(sub->d_sw);
-  P.taps = reinterpret_cast<const float2*>(sub->d_staps);
-  P.support = sub->d_ssupport;
-  P.steps = sub->d_ssteps;
-  P.columns = sub->d_scolumns;
-  P.items = sub->d_sitems;
+  set_short(sub, P);
   P.out = out + (long long)row_offset * T;
   P.out_wave_stride = out_wave_stride;
   P.fmt = sub->fmt;

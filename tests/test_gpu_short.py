@@ -95,3 +95,31 @@ def test_samples_that_are_not_finite(case, step, bad):
                 assert (np.abs(got[k][:, t] - w) <= 2e-5 * size + 2.0 * np.abs(clean).max()).all(), (k, t)
             elif (np.abs(re[k][s + hit]) > 1e-4 * np.abs(re[k]).max()).any():
                 assert not np.isfinite(got[k][0, t]), (k, t)
+
+
+@pytest.mark.parametrize("sr,hop,n_bins,bpo,B,L,blocks", [
+    (22050, 512, 84, 12, 2, 100001, 1),      # beside hop-block items of 64, 128 and 256 frames
+    (22050, 512, 83, 12, 200, 60003, 2),      # a last item of eleven bins
+    (44100, 512, 120, 24, 260, 100000, 4),
+    (16000, 96, 60, 12, 3, 9003, 1),         # 32 columns at a time
+    (8000, 64, 60, 12, 4, 9002, 1),          # 64
+])
+def test_beside_hop_blocks(sr, hop, n_bins, bpo, B, L, blocks):
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] short kernels beside hop-blocks sr={sr} hop={hop} n_bins={n_bins} {B}x{L}", file=sys.stderr, flush=True)
+    cfg = dict(sr=sr, hop=hop, fmin=50.0 if hop == 96 else 80.0 if hop == 64 else 65.4, n_bins=n_bins, bins_per_octave=bpo,
+               n_taps=6144 if hop == 96 else 0)
+    plan = nb.nna_plan_cqt(fmt=nb.NNA_OUT_COMPLEX, device=0, **cfg)
+    tiles = nb.nna_plan_applied_tiles(plan, B, L)
+    assert tiles[0][1] == blocks and tiles[1] == (64, 1)
+    x = (0.3 * np.random.default_rng([61, B, L]).standard_normal((B, L))).astype(np.float32)
+    rows, T = nb.nna_out_shape(plan, B, L)
+    out = torch.full((B, rows, T), float("nan"), device="cuda")
+    got = nb.nna_cqt(plan, torch.from_numpy(x).cuda(), out=out)
+    assert bool(torch.isfinite(got).all())
+    some = sorted({0, B // 2, B - 1})
+    got = got[some].cpu().numpy().astype(np.float64)
+    want = oracle.interleave(*oracle.cqt_complex(x[some], **cfg))
+    for b in range(len(some)):
+        assert np.abs(got[b] - want[b]).max() < TOL * np.abs(want[b]).max(), some[b]
