@@ -314,14 +314,14 @@ __device__ __forceinline__ float format_power(float pw) {
 // Output of one finished STFT row tile: 64 (Re, Im) slots x this wave's 32 frames.  `op` points
 // at (waveform, bin 0, frame) of this lane; consecutive lanes hold consecutive frames, so every
 // store instruction writes two 128-byte runs.
-template <int FMT>
-__device__ __forceinline__ void stft_store_tile(const f32x16 (&acc)[ST_RB], float* __restrict__ op, long long T,
+template <int FMT, int N>
+__device__ __forceinline__ void stft_store_tile(const f32x16 (&acc)[N], float* __restrict__ op, long long T,
                                                 int slot_base, int h, int n_half, int packed) {
   float* __restrict__ p = op + (slot_base + 2 * h) * T;
-  if (slot_base > 0 && slot_base + ST_ROWS / 2 <= n_half) {
-    // interior tile: all 64 slots exist and none is the packed DC/Nyquist slot
+  if (slot_base > 0 && slot_base + 16 * N <= n_half) {
+    // interior tile: all its slots exist and none is the packed DC/Nyquist slot
 #pragma unroll
-    for (int rb = 0; rb < ST_RB; ++rb)
+    for (int rb = 0; rb < N; ++rb)
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const float re = acc[rb][2 * u], im = acc[rb][2 * u + 1];
@@ -329,7 +329,7 @@ __device__ __forceinline__ void stft_store_tile(const f32x16 (&acc)[ST_RB], floa
       }
   } else {
 #pragma unroll
-    for (int rb = 0; rb < ST_RB; ++rb)
+    for (int rb = 0; rb < N; ++rb)
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const float re = acc[rb][2 * u], im = acc[rb][2 * u + 1];
@@ -347,11 +347,11 @@ __device__ __forceinline__ void stft_store_tile(const f32x16 (&acc)[ST_RB], floa
 
 // Output of one finished row tile before the magnitude is taken: NNA_OUT_COMPLEX writes rows 2k = Re,
 // 2k+1 = Im of bin k (`op` points at (waveform, row 0, frame)); NNA_OUT_PHASE writes atan2(Im, Re).
-template <int FMT>
-__device__ __forceinline__ void stft_store_tile_complex(const f32x16 (&acc)[ST_RB], float* __restrict__ op, long long T,
+template <int FMT, int N>
+__device__ __forceinline__ void stft_store_tile_complex(const f32x16 (&acc)[N], float* __restrict__ op, long long T,
                                                         int slot_base, int h, int n_half, int packed) {
 #pragma unroll
-  for (int rb = 0; rb < ST_RB; ++rb)
+  for (int rb = 0; rb < N; ++rb)
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const float re = acc[rb][2 * u], im = acc[rb][2 * u + 1];

@@ -499,7 +499,7 @@ hipError_t launch_bank_to_logical(const BankPermuteParams& p, hipStream_t stream
 // the trainable layers' contractions (nna_kernels_split.hip); `mode` ST_MODE_STFT, _CPLX or _GRAD, wrm as in BwParams
 hipError_t launch_split_forward(StftParams p, int mode, const float* wrm, int kp, int K, hipStream_t stream);
 hipError_t launch_split_bank(const BwParams& p, hipStream_t stream);
-hipError_t launch_split_wave(const BwParams& p, hipStream_t stream);
+hipError_t launch_split_wave(BwParams p, hipStream_t stream);
 hipError_t launch_bw_bank(const BwParams& p, hipStream_t stream);      // gw += G x frames
 hipError_t launch_bw_wave(const BwParams& p, hipStream_t stream);      // gx += transposed convolution
 // decimation by two on the vector ALUs (fir_decimate_kernel)

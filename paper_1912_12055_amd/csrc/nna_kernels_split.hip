@@ -38,8 +38,8 @@ constexpr int SP_PITCH = 20;   // words per row of a staged plane: 32 bfloat16 a
 constexpr int SP_PLANE = SP_T * SP_PITCH;
 
 // acc[s] += the products of ROWS 32-row blocks of the staged chunk with this wave's columns
-template <int ROWS>
-__device__ __forceinline__ void multiply(f32x16 (&acc)[4], const unsigned* __restrict__ lds, const Planes (&b)[2], int h, int r32) {
+template <int ROWS, int N>
+__device__ __forceinline__ void multiply(f32x16 (&acc)[N], const unsigned* __restrict__ lds, const Planes (&b)[2], int h, int r32) {
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -67,24 +67,24 @@ __device__ __forceinline__ void multiply(f32x16 (&acc)[4], const unsigned* __res
 // The pipeline all three share.  fetch_rows(c, i, v): the eight values of this thread's i-th octet (i = 0, 1) of the rows' operand
 // in chunk c; fetch_cols(c, v): this lane's sixteen values of the columns' operand, v[ks] its indices 16 ks + 8 h + 0 .. 7;
 // fix_cols(v): what is left to do to them once they are there.  row_word(i): LDS word of octet i.
-// PAIRED: two chunks per turn of the loop, no copies of the columns' planes (more registers).
-template <int ROWS, bool PAIRED, typename FR, typename FC, typename FX, typename RW>
-__device__ __forceinline__ void contract(f32x16 (&acc)[4], unsigned* __restrict__ lds, long long c_begin, long long c_end, int h, int r32,
+// PAIRED: two chunks per turn of the loop, no copies of the columns' planes (more registers).  OCTETS of rows a thread (half for 64 rows).
+template <int ROWS, bool PAIRED, int OCTETS = 2, int N, typename FR, typename FC, typename FX, typename RW>
+__device__ __forceinline__ void contract(f32x16 (&acc)[N], unsigned* __restrict__ lds, long long c_begin, long long c_end, int h, int r32,
                                          FR fetch_rows, FC fetch_cols, FX fix_cols, RW row_word) {
 #pragma unroll
-  for (int s = 0; s < 4; ++s)
+  for (int s = 0; s < N; ++s)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[s][r] = 0.f;
-  f32x4 ra[2][2], rb[2][2];
+  f32x4 ra[OCTETS][2], rb[2][2];
   auto request = [&](long long c) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) fetch_rows(c, i, ra[i]);
+    for (int i = 0; i < OCTETS; ++i) fetch_rows(c, i, ra[i]);
     fetch_cols(c, rb);
   };
   auto stage = [&](int buf, Planes (&b)[2]) {
     fix_cols(rb);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < OCTETS; ++i) {
       const Planes o = split8(ra[i]);
 #pragma unroll
       for (int l = 0; l < 3; ++l) *reinterpret_cast<u32x4*>(lds + (buf * 3 + l) * SP_PLANE + row_word(i)) = o.p[l];
@@ -126,14 +126,16 @@ __device__ __forceinline__ void contract(f32x16 (&acc)[4], unsigned* __restrict_
 // ---- forward ------------------------------------------------------------------------------------
 // MODE: ST_MODE_STFT, ST_MODE_CPLX or ST_MODE_GRAD (power format), as in the float32 kernel, whose accumulator layout and epilogues
 // these are.
-template <int MODE>
+// ROWS: 32-row blocks of a tile, four or (short batches) two.
+template <int MODE, int ROWS>
 __global__ __launch_bounds__(256, 2) void split_forward_kernel(const StftParams P, const float* __restrict__ wrm, int kp, int K) {
   __shared__ __attribute__((aligned(16))) unsigned lds[2 * 3 * SP_PLANE];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, h = lane >> 5, r32 = lane & 31;
   const FrameGeom& g = P.g;
   // the row tiles of a frame tile are neighbours on one XCD: they share its samples in the L2
-  const long long local = blockIdx.x >> 3, ft = (blockIdx.x & 7) * ((P.n_ft + 7) >> 3) + local / P.n_rt;
-  const int rt = (int)(local % P.n_rt);
+  const int n_rt = P.n_rt * (4 / ROWS);
+  const long long local = blockIdx.x >> 3, ft = (blockIdx.x & 7) * ((P.n_ft + 7) >> 3) + local / n_rt;
+  const int rt = (int)(local % n_rt);
   if (ft >= P.n_ft) return;
   const long long f_lane = ft * SP_T + wave * 32 + r32;
   const bool valid = f_lane < g.n_frames;
@@ -144,9 +146,9 @@ __global__ __launch_bounds__(256, 2) void split_forward_kernel(const StftParams 
   const int k_end = (K + SP_KC - 1) / SP_KC * SP_KC;
   const bool edge = __builtin_amdgcn_ballot_w64(pos < 0 || pos + k_end > L) != 0;
   unsigned rev = 0;
-  const float* __restrict__ wp = wrm + ((long long)rt * SP_T + (tid >> 2)) * kp + 8 * (tid & 3);
-  f32x16 acc[4];
-  contract<4, true>(
+  const float* __restrict__ wp = wrm + ((long long)rt * (32 * ROWS) + (tid >> 2)) * kp + 8 * (tid & 3);
+  f32x16 acc[ROWS];
+  contract<ROWS, true, ROWS / 2>(
       acc, lds, 0, k_end / SP_KC, h, r32,
       [&](long long c, int i, f32x4 (&v)[2]) {
         const float* p = wp + (long long)(64 * i) * kp + c * SP_KC;
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(256, 2) void split_forward_kernel(const StftParams 
       },
       [&](int i) { return ((tid >> 2) + 64 * i) * SP_PITCH + 4 * (tid & 3); });
   if (!valid) return;
-  const int slot_base = rt * (ST_ROWS / 2);
+  const int slot_base = rt * (16 * ROWS);
   if constexpr (MODE == ST_MODE_GRAD) {
     const float* __restrict__ gp = P.gout + (b_lane * P.out_bins) * g.T + t_lane;
     float* __restrict__ Gp = P.gbuf + (f >> 5) * ((long long)P.n_rt * ST_ROWS * 32) + (f & 31);
@@ -206,7 +208,7 @@ __global__ __launch_bounds__(256, 2) void split_forward_kernel(const StftParams 
     if (MODE == ST_MODE_STFT && P.keep) {
       float* __restrict__ Kp = P.keep + (f >> 5) * ((long long)P.n_rt * ST_ROWS * 32) + (f & 31);
 #pragma unroll
-      for (int rb = 0; rb < ST_RB; ++rb)
+      for (int rb = 0; rb < ROWS; ++rb)
 #pragma unroll
         for (int u = 0; u < 16; ++u) Kp[(2 * (slot_base + 2 * h + rb * 16 + 4 * (u >> 2) + ((u >> 1) & 1)) + (u & 1)) * 32] = acc[rb][u];
     }
@@ -343,10 +345,12 @@ __global__ __launch_bounds__(256, 2) void split_wave_kernel(const BwParams P) {
   const FrameGeom& g = P.g;
   // the tap tiles of one frame tile are neighbours: they share its G columns in the L2
   const int n_nt = P.kp / BW_NT;
-  const long long m0 = (long long)(blockIdx.x / n_nt) * BW_MT;
-  const int n0 = (int)(blockIdx.x % n_nt) * BW_NT;
-  const long long c_end = (2 * P.n_half + SP_KC - 1) / SP_KC;  // (the padding rows of G and W are zero)
-  if (c_end < 1) return;
+  const long long tiles = P.gpitch / BW_MT * n_nt, split = blockIdx.x / tiles, tile = blockIdx.x - split * tiles;
+  const long long m0 = tile / n_nt * BW_MT;
+  const int n0 = (int)(tile % n_nt) * BW_NT;
+  const long long c_all = (2 * P.n_half + SP_KC - 1) / SP_KC;  // (the padding rows of G and W are zero)
+  const long long c_begin = split * P.chunks_per_split, c_end = c_begin + P.chunks_per_split < c_all ? c_begin + P.chunks_per_split : c_all;
+  if (c_begin >= c_end) return;
   // octet i of this thread: frame m0 + tid % 128, bank rows 8 (tid / 128 + 2 i) + 0 .. 7 of the chunk
   const int fr = tid & 127, o0 = tid >> 7;
   const float* __restrict__ ap = P.gbuf + ((m0 + fr) >> 5) * ((long long)P.rows_pad * 32) + (fr & 31) + 8 * o0 * 32;
@@ -354,7 +358,7 @@ __global__ __launch_bounds__(256, 2) void split_wave_kernel(const BwParams P) {
   const unsigned w_lane = 8 * h * P.kp + tap;
   f32x16 acc[4];
   contract<4, true>(
-      acc, lds, 0, c_end, h, r32,
+      acc, lds, c_begin, c_end, h, r32,
       [&](long long c, int i, f32x4 (&v)[2]) {
         const float* p = ap + (c * SP_KC + 16 * i) * 32;
 #pragma unroll
@@ -399,14 +403,15 @@ hipError_t launch_split_forward(StftParams P, int mode, const float* wrm, int kp
   clear_stale_error();
   P.n_ft = (P.g.n_frames + SP_T - 1) / SP_T;
   const long long blocks = (P.n_ft + 7) / 8 * 8 * P.n_rt;
-  if (blocks <= 0 || blocks > 0x7fffffffLL || kp < (K + SP_KC - 1) / SP_KC * SP_KC) return hipErrorInvalidValue;
+  if (blocks <= 0 || 2 * blocks > 0x7fffffffLL || kp < (K + SP_KC - 1) / SP_KC * SP_KC) return hipErrorInvalidValue;
   if (mode == ST_MODE_GRAD && P.fmt != NNA_OUT_POWER) return hipErrorInvalidValue;
-  if (mode == ST_MODE_GRAD)
-    hipLaunchKernelGGL((split_forward_kernel<ST_MODE_GRAD>), dim3((unsigned)blocks), dim3(256), 0, stream, P, wrm, kp, K);
-  else if (mode == ST_MODE_CPLX)
-    hipLaunchKernelGGL((split_forward_kernel<ST_MODE_CPLX>), dim3((unsigned)blocks), dim3(256), 0, stream, P, wrm, kp, K);
-  else
-    hipLaunchKernelGGL((split_forward_kernel<ST_MODE_STFT>), dim3((unsigned)blocks), dim3(256), 0, stream, P, wrm, kp, K);
+  auto run = [&](auto kernel, long long n) { hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(256), 0, stream, P, wrm, kp, K); };
+  // Few tiles: half the rows each.  A whole step, n_fft 2,048, 48 tiles: 340 -> 311 us; n_fft 400, 96: 146 -> 137; Mel, n_fft 1,024, 120: 282 ->
+  // 267; n_fft 4,096, 128: 811 -> 796; n_fft 2,048, 176: 345 -> 354, 496: 830 -> 857.
+  const bool half = P.n_ft * P.n_rt < 160;
+  if (mode == ST_MODE_GRAD) run(split_forward_kernel<ST_MODE_GRAD, 4>, blocks);
+  else if (mode == ST_MODE_CPLX) half ? run(split_forward_kernel<ST_MODE_CPLX, 2>, 2 * blocks) : run(split_forward_kernel<ST_MODE_CPLX, 4>, blocks);
+  else half ? run(split_forward_kernel<ST_MODE_STFT, 2>, 2 * blocks) : run(split_forward_kernel<ST_MODE_STFT, 4>, blocks);
   return hipGetLastError();
 }
 
@@ -422,9 +427,15 @@ hipError_t launch_split_bank(const BwParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_split_wave(const BwParams& p, hipStream_t stream) {
+hipError_t launch_split_wave(BwParams p, hipStream_t stream) {
   clear_stale_error();
-  const long long blocks = p.gpitch / BW_MT * (p.kp / BW_NT);
+  // A short batch's contraction over the bank's rows is halved, or cut into pieces of sixteen chunks until there is a workgroup per compute
+  // unit.  A whole step, n_fft 2,048, 176 tiles: 449 us whole, 427 halved, 456 in three (every piece adds onto the waveform by
+  // itself); 48 tiles 311, 298, 290, 287 in four; 352 tiles the same either way; 496 tiles 830, 840; n_fft 512, sixteen chunks, 376 tiles: 249, 270.
+  const long long tiles = p.gpitch / BW_MT * (p.kp / BW_NT), chunks = (2 * p.n_half + SP_KC - 1) / SP_KC;
+  const long long split = tiles > 0 && tiles < 256 && chunks >= 32 ? std::max(2LL, std::min((256 + tiles - 1) / tiles, chunks / 16)) : 1;
+  p.chunks_per_split = std::max(1LL, (chunks + split - 1) / split);
+  const long long blocks = tiles * ((chunks + p.chunks_per_split - 1) / p.chunks_per_split);
   if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL(split_wave_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p);
   return hipGetLastError();

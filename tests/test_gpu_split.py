@@ -59,3 +59,23 @@ def test_trainable_stft_range(scale):
     for name, got, want in (("out", out, c), ("gw", gw, rw)):
         got, want = got.detach().cpu().double().numpy().ravel(), want.detach().numpy().ravel()
         assert np.linalg.norm(got - want) < TOL * np.linalg.norm(want), name
+
+
+@pytest.mark.parametrize("fmt", ["MAGNITUDE", "COMPLEX"])
+def test_short_and_large_batches_agree(fmt):
+    """A short batch's workgroups take half the rows of a large one's, and its waveform gradient is summed in pieces: the same sums in the
+    same order forwards, the same sums backwards."""
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] split short and large {fmt}", file=sys.stderr, flush=True)
+    plan = nb.nna_plan_trainable(nb.nna_plan_stft(n_fft=1024, hop=256, fmt=getattr(nb, "NNA_OUT_" + fmt), device=0))
+    gen = torch.Generator().manual_seed(67)
+    x = torch.randn((40, 60001), generator=gen).cuda()  # 74 x 8 tiles of 128 x 128; five of them: 10 x 8
+    out = nb.nna_stft(plan, x)
+    few = nb.nna_stft(plan, x[:5].contiguous())
+    assert torch.equal(out[:5], few)
+    gout = torch.randn(out.shape, generator=gen).cuda()
+    _, gx = nb.nna_stft_backward(plan, x, gout)
+    _, gx_few = nb.nna_stft_backward(plan, x[:5].contiguous(), gout[:5].contiguous())
+    # sums of up to four frames, each in up to two pieces: float32 rounding of a few of them
+    assert (gx[:5] - gx_few).norm() <= 2e-6 * gx_few.norm()
