@@ -20,7 +20,7 @@
 //
 // What bounds it: the matrix pipe is busy 37 to 42 % and the vector ALUs, which split the operands, 30 to 46 % (16 x 44,217 samples, the
 // three kernels, counters); with two waves per SIMD the two overlap in part.  64 x 110,250 samples, n_fft 2,048 (116 GFLOP each, MI355X; float32 instruction before): contraction 1,045 ->
-// 650 us, bank gradient 1,000 -> 640 us; 16 x 44,217: bank gradient 146 -> 117 us, waveform gradient 177 -> 113 us.  Errors against
+// 650 us, bank gradient 1,000 -> 640 us; 16 x 44,217: bank gradient 146 -> 117 us, waveform gradient 177 -> 95 us.  Errors against
 // 64 bits there: output 6.6e-7 -> 4.7e-7, bank gradient 1.29e-6 -> 9.3e-7.
 #include "nna_device.h"
 
