@@ -519,6 +519,13 @@ nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size
  * where there are none, all zero where the call runs another kernel.
  */
 nna_status nna_plan_applied_tiles(const nna_plan* plan, long long B, long long L, int* frames, int* blocks);
+/*
+ * The same of the kernels taken tap by tap from samples split once per tile: the octaves of downsampling plans (nna_plan_part), and those
+ * beside a basis.  form: tiles of 64 (0), 32 (1) or 16 frames (2), all their samples at once; of 128 (3) or 64 frames (4), `columns` of
+ * them at a time; -1 where the call runs another kernel.  frames: per tile; width: samples of every hop that are read, the most of any
+ * item of neighbouring bins.
+ */
+nna_status nna_plan_short_tiles(const nna_plan* plan, long long B, long long L, int* form, int* frames, int* columns, int* width);
 
 /* Mel plans only: the filterbank W[n_mels, n_fft/2+1] as the GPU holds it. */
 nna_status nna_plan_mel_weights(const nna_plan* plan, double* host_out, size_t cap);

@@ -117,6 +117,7 @@ def lib():
         L.nna_plan_bank.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
         L.nna_plan_applied_kernels.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t, _c.POINTER(_LL)]
         L.nna_plan_applied_tiles.argtypes = [_VP, _LL, _LL, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int)]
+        L.nna_plan_short_tiles.argtypes = [_VP, _LL, _LL] + 4 * [_c.POINTER(_c.c_int)]
         L.nna_plan_mel_weights.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
         L.nna_plan_info.argtypes = [_VP, _c.POINTER(_c.c_int), _c.POINTER(_LL), _c.POINTER(_LL), _c.POINTER(_LL),
                                     _c.POINTER(_c.c_double), _c.POINTER(_c.c_double)]
@@ -285,6 +286,13 @@ def nna_plan_applied_tiles(plan: Plan, B: int, L: int):
     f, b = (_c.c_int * 2)(), (_c.c_int * 2)()
     _check(lib().nna_plan_applied_tiles(plan.handle, B, L, f, b))
     return (f[0], b[0]), (f[1], b[1])
+
+
+def nna_plan_short_tiles(plan: Plan, B: int, L: int):
+    """(form, frames per tile, columns at a time, samples of a hop) of the kernels taken tap by tap; form -1: by another kernel."""
+    v = [_c.c_int() for _ in range(4)]
+    _check(lib().nna_plan_short_tiles(plan.handle, B, L, *(_c.byref(i) for i in v)))
+    return tuple(i.value for i in v)
 
 
 def nna_plan_mel_weights(plan: Plan) -> np.ndarray:

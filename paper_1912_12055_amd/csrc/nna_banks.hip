@@ -1156,10 +1156,9 @@ CqtKernelSource dense_kernels(std::vector<double> rows, long long K) {
           }};
 }
 
-// A plan that holds what build_cqt_bank_lowrank made of `sub`'s kernels (a device plan keeps them on the device only); false: `sub`
-// is not a plan whose kernels are taken by hop-blocks.  `owner`: the plan with frequency-domain kernels that `sub` composes, or sub.
-bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy) {
-  if (!sub->hop_blocks) return false;
+// A plan that holds what build_cqt_bank_lowrank or build_cqt_bank_short made of `sub`'s kernels (a device plan keeps them on the device
+// only); whether they are taken by hop-blocks.  `owner`: the plan with frequency-domain kernels that `sub` composes, or sub.
+bool rebuild_applied(const nna_plan* owner, const nna_plan* sub, nna_plan& copy) {
   copy.K = sub->K;
   copy.hop = sub->hop;
   copy.pad = sub->pad;
@@ -1174,10 +1173,11 @@ bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy)
   copy.exec_flops_cqf = sub->exec_flops_cqf;
   copy.h_qitems = sub->h_qitems;
   copy.q_max_jspan = sub->q_max_jspan;
-  if (owner != sub)
-    build_cqt_bank_lowrank(&copy, dense_kernels(cqt1992_composed_rows(owner), copy.K));
+  const CqtKernelSource kernels = owner != sub ? dense_kernels(cqt1992_composed_rows(owner), copy.K) : cqt_kernels(sub);
+  if (sub->hop_blocks)
+    build_cqt_bank_lowrank(&copy, kernels);
   else
-    build_cqt_bank_lowrank(&copy, cqt_kernels(sub));
+    build_cqt_bank_short(&copy, kernels, {{0, copy.n_bins}});
   return copy.lowrank;
 }
 
@@ -1249,6 +1249,24 @@ void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std
   std::vector<std::pair<int, int>> items;
   for (const auto& [lo, hi] : runs)
     for (int k0 = lo; k0 < hi; k0 += per_item) items.push_back({k0, std::min(per_item, hi - k0)});
+  // A tile's rows: whole hops, which neighbouring frames share, or every frame's own taps, where these are fewer (or, hops that are no
+  // multiple of 32 and so cannot be read by columns, up to a quarter more).  Items that read less are out of step with each other, which
+  // costs them their common samples in the L2: several of them want a quarter less (36 bins, 480 and 320 of 512 samples: 163 us by whole
+  // hops, 173).  59,858 frames of 12 bins, 120 taps, hop 512, 1,024,
+  // 2,048, 4,096: 34, 54, 131, 232 us by whole hops, 13.5 by own taps (cqt_kernel 26); 299,982 frames of 1,050 taps, hop 1,000: 800, 368 (593).
+  const bool lines = hop % 32 == 0;
+  auto own = [&](long long lo) { return lines ? std::max(0LL, floor_div(lo - p->pad, 32) * 32 + p->pad) : lo / 8 * 8; };
+  bool apart = true;
+  long long columns = 0;
+  for (const auto& [k0, nb] : items) {
+    long long lo, hi, l, h;
+    block_taps(p, k0, nb, 0, lo, hi);
+    for (int b = 1; 8 * b < nb; ++b) block_taps(p, k0, nb, b, l, h), lo = std::min(lo, l), hi = std::max(hi, h);
+    const long long width = ceil_div(hi - own(lo), 32) * 32;
+    apart = apart && (lines ? width <= hop : 4 * (hi - lo) <= (hop >= 192 ? 5LL : 4LL) * hop);
+    columns += width;
+  }
+  apart = apart && (items.size() == 1 || !lines || 4 * columns <= 3LL * hop * (long long)items.size());
   for (const auto& [k0, nb] : items) {
     nna::ShortItem item{};
     item.bin0 = k0;
@@ -1260,11 +1278,12 @@ void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std
       lo[b - 1] = std::min(lo[b - 1], lo[b]);
       hi[b - 1] = std::max(hi[b - 1], hi[b]);
     }
-    item.j0 = (int)(lo[0] / hop);
-    item.jspan = (int)ceil_div(hi[0], hop) - item.j0;
+    const long long j0 = lo[0] / hop, base = apart ? own(lo[0]) : j0 * hop;
+    item.base = (int)base;
+    item.width = apart ? (int)(ceil_div(hi[0] - base, 32) * 32) : hop;
+    item.jspan = apart ? 1 : (int)(ceil_div(hi[0], hop) - j0);
     item.w0 = (long long)p->h_sw.size() / 4;
     item.step0 = (int)p->h_ssteps.size();
-    const long long base = (long long)item.j0 * hop;
     item.n_step = (int)ceil_div(hi[0] - base, 32);
     p->h_sw.resize(p->h_sw.size() + (size_t)item.n_step * nna::SHORT_RB * 3 * 256, 0u);
     for (int s = 0; s < item.n_step; ++s) {
@@ -1280,13 +1299,13 @@ void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std
           unsigned* block = &p->h_sw[(size_t)item.w0 * 4 + ((size_t)(at / 32) * nna::SHORT_RB + row / 16) * 768];
           put_parts(p->h_staps[2 * (first[k] + tap - p->row_s[2 * k]) + part], block + lane * 4 + e / 2, 256, e % 2);
         }
-    if (hop % 32 == 0) {
+    if (item.width % 32 == 0) {
       item.columns = (int)p->h_scolumns.size();
       std::vector<int> order;
-      for (int c = 0; c < hop; c += 32) {
+      for (int c = 0; c < item.width; c += 32) {
         p->h_scolumns.push_back((int)order.size() / 2);
         for (int j = 0; j < item.jspan; ++j) {
-          const int s = j * (hop / 32) + c / 32, a = s < item.n_step ? p->h_ssteps[item.step0 + s] : 0;
+          const int s = j * (item.width / 32) + c / 32, a = s < item.n_step ? p->h_ssteps[item.step0 + s] : 0;
           if (!a) continue;
           order.push_back(a | j << 2 | c / 32 << 12);
           order.push_back(s);

@@ -439,7 +439,7 @@ void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels);
 void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<unsigned>& a);
 CqtKernelSource cqt_kernels(const nna_plan* p);
 CqtKernelSource dense_kernels(std::vector<double> rows, long long K);  // [2 n_bins][K]
-bool rebuild_lowrank(const nna_plan* owner, const nna_plan* sub, nna_plan& copy);
+bool rebuild_applied(const nna_plan* owner, const nna_plan* sub, nna_plan& copy);
 void cqt_applied_rows(const nna_plan* p, double* out);
 // Bins [first, last) of every run, tap by tap (nna_kernels_short.hip); sets p->short_taps if the plan qualifies and they are all of its bins
 void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std::vector<std::pair<int, int>>& runs);
@@ -473,6 +473,7 @@ nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long 
                     int row_offset, void* hip_stream, bool may_fold = false, float* keep = nullptr);
 // tiles of a launch of nna_kernels_cql.hip; false: not a launch for it
 bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::CqlParams& P);
+bool shape_short(const nna_plan* sub, long long n_frames, long long T, nna::ShortParams& P);
 long long frames_of(const nna_plan* p, long long L);
 // cqt_kernel's launch, or on a trainable plan the one for batches that would leave most CUs without a workgroup
 hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t stream);

@@ -268,8 +268,8 @@ constexpr int SHORT_LDS = 156 * 1024;
 // each wave a quarter of their steps, 32, 64 or 128 columns at a time
 enum { SHORT_64, SHORT_32, SHORT_16, SHORT_COLUMNS, SHORT_COLUMNS_64, SHORT_FORMS };
 constexpr int SHORT_FRAMES[SHORT_FORMS] = {64, 32, 16, 128, 64};
-constexpr int SHORT_ROWS = 128;          // SHORT_COLUMNS: hops of a tile
-constexpr int SHORT_PASSES = 5;          // SHORT_COLUMNS_64: hops times columns at once, as many times 2,048 values
+constexpr int SHORT_ROWS = 128;          // SHORT_COLUMNS: rows of a tile
+constexpr int SHORT_PASSES = 5;          // SHORT_COLUMNS_64: rows times columns at once, as many times 2,048 values
 // values per plane that the waves' sums, or the rows, take
 constexpr int SHORT_PLANE_MIN[SHORT_FORMS] = {8192, 4096, 2048, SHORT_ROWS * 40, 8192};
 constexpr int SHORT_PLANE(long long samples) { return (int)((samples + 32) * 9 / 8 + 16) / 8 * 8; }  // one octet in nine left free
@@ -279,8 +279,9 @@ struct ShortItem {
   long long w0;      // first uint4 of the weights: [step of 32 taps][row block][3 planes][64 lanes]
   int step0;         // first entry of the item's table: how many row blocks every step has taps of
   int n_step;
-  int columns;       // hops of whole 32 columns: first entry of its table of steps by columns
-  int j0, jspan;     // the item's hop-blocks of a frame: j0 .. j0 + jspan - 1
+  int columns;       // widths of whole 32 columns: first entry of its table of steps by columns
+  int base, width;   // a hop's row: the `width` samples from tap `base` on; a hop, or (kernels shorter than that) whole steps of their taps
+  int jspan;         // a frame's taps lie in this many rows (1 where a row is less than a hop)
   int bin0, n_bins;
 };
 
@@ -299,6 +300,7 @@ struct ShortParams {
   int tile_frames;
   int plane;             // values per plane in LDS
   int columns_at_once;
+  int octets;            // rows of whole octets
   int fmt;
 };
 hipError_t launch_cqt_short(const ShortParams& p, hipStream_t stream);

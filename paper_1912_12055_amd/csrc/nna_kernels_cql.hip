@@ -718,7 +718,7 @@ hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream) {
     const ShortParams& s = p.shorts;
     constexpr int form = SHORT_COLUMNS_64;
     if (s.form != form || s.tile_frames < 1 || s.tile_frames > SHORT_FRAMES[form] || s.plane % 8 != 0 || s.plane < SHORT_PLANE_MIN[form] ||
-        s.plane * 6 + 16 > p.lds_floats * 4 || s.columns_at_once < 32 || s.g.hop % s.columns_at_once != 0 || s.g.L < 4)
+        s.plane * 6 + 16 > p.lds_floats * 4 || (s.columns_at_once != 32 && s.columns_at_once != 64 && s.columns_at_once != 128) || s.g.L < 4)
       return hipErrorInvalidValue;
     fb == 1 ? launch<1, 4, true>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 4, true>(p, (unsigned)blocks, stream) : launch<4, 4, true>(p, (unsigned)blocks, stream);
   } else if (fd == 1)

@@ -49,10 +49,11 @@ hipError_t short_kernels_init() {
 hipError_t launch_cqt_short(const ShortParams& p, hipStream_t stream) {
   clear_stale_error();
   const long long blocks = (p.n_ft + 7) / 8 * 8 * p.n_items;
-  if (blocks <= 0 || blocks > 0x7fffffffLL || p.g.L < 4 || p.g.hop % (p.form >= SHORT_COLUMNS ? 32 : 4) != 0) return hipErrorInvalidValue;
+  if (blocks <= 0 || blocks > 0x7fffffffLL || p.g.L < 4 || p.g.hop % 4 != 0) return hipErrorInvalidValue;
   if (p.form < 0 || p.form >= SHORT_FORMS || p.tile_frames < 1 || p.tile_frames > SHORT_FRAMES[p.form]) return hipErrorInvalidValue;
+  if (p.form == SHORT_COLUMNS_64 && p.columns_at_once != 32 && p.columns_at_once != 64 && p.columns_at_once != 128) return hipErrorInvalidValue;
   if (p.plane % 8 != 0 || p.plane < SHORT_PLANE_MIN[p.form] || (size_t)p.plane * 6 + 16 > (size_t)SHORT_LDS) return hipErrorInvalidValue;
-  with_form(p.form, p.g.hop % 8 == 0, [&](auto f) { f.launch(p, (unsigned)blocks, stream); });
+  with_form(p.form, p.octets != 0, [&](auto f) { f.launch(p, (unsigned)blocks, stream); });
   return hipGetLastError();
 }
 

@@ -793,7 +793,7 @@ nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size
   if ((unsigned long long)cap < (unsigned long long)(sub->conv_rows * (long long)sub->K)) return fail(NNA_ERR_INVALID_ARG, "host_out is too small");
   try {
     nna_plan copy;
-    if (rebuild_lowrank(plan, sub, copy))
+    if (sub->hop_blocks && rebuild_applied(plan, sub, copy))
       cqt_applied_rows(&copy, host_out);
     else
       return nna_plan_bank(sub, host_out, cap);
@@ -814,7 +814,7 @@ nna_status nna_plan_applied_tiles(const nna_plan* plan, long long B, long long L
     nna_plan copy;
     nna::CqlParams P;
     std::memset(&P, 0, sizeof(P));
-    if (rebuild_lowrank(plan, sub, copy) && shape_lowrank(&copy, B * T, T, P)) {
+    if (sub->hop_blocks && rebuild_applied(plan, sub, copy) && shape_lowrank(&copy, B * T, T, P)) {
       for (int i = 0; i < 2; ++i) {
         const nna::CqlPart& part = i ? P.direct : P.basis;
         frames[i] = part.n_items ? part.tile_frames : 0;
@@ -825,6 +825,30 @@ nna_status nna_plan_applied_tiles(const nna_plan* plan, long long B, long long L
         blocks[1] = 1;
       }
     }
+  } catch (const std::bad_alloc&) {
+    return fail(NNA_ERR_ALLOC, "out of host memory");
+  }
+  return NNA_OK;
+}
+
+nna_status nna_plan_short_tiles(const nna_plan* plan, long long B, long long L, int* form, int* frames, int* columns, int* width) {
+  if (!plan || !form || !frames || !columns || !width) return fail(NNA_ERR_INVALID_ARG, "plan / form / frames / columns / width is NULL");
+  const nna_plan* sub = applied_plan(plan);
+  if (!sub) return fail(NNA_ERR_INVALID_ARG, "not a plan with fixed constant-Q kernels at one rate");
+  const long long T = B < 1 ? 0 : frames_of(sub, L);
+  if (T < 1) return fail(NNA_ERR_SHAPE, "no frames");
+  *form = -1;
+  *frames = *columns = *width = 0;
+  try {
+    nna_plan copy;
+    nna::CqlParams P;
+    std::memset(&P, 0, sizeof(P));
+    const bool by_blocks = rebuild_applied(plan, sub, copy) && shape_lowrank(&copy, B * T, T, P);
+    if (by_blocks ? P.shorts.n_items == 0 : !copy.runs_short() || !shape_short(&copy, B * T, T, P.shorts)) return NNA_OK;
+    *form = P.shorts.form;
+    *frames = P.shorts.tile_frames;
+    *columns = P.shorts.form >= nna::SHORT_COLUMNS ? P.shorts.columns_at_once : 0;
+    for (const nna::ShortItem& it : copy.h_sitems) *width = std::max(*width, it.width);
   } catch (const std::bad_alloc&) {
     return fail(NNA_ERR_ALLOC, "out of host memory");
   }

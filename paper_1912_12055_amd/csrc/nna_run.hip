@@ -343,31 +343,40 @@ nna_status run_conv_fold(const nna_plan* sub, const float* x, long long B, long 
 bool fit_short(const nna_plan* sub, long long n_frames, long long T, int form, size_t lds, nna::ShortParams& P) {
   P.n_items = (int)sub->h_sitems.size();
   P.form = form;
-  int M = nna::SHORT_FRAMES[form], rows = 0;
+  int M = 0;
   const bool columns = form >= nna::SHORT_COLUMNS;
-  if (columns && sub->hop % 32 != 0) return false;
+  int widths = 0;
+  for (const nna::ShortItem& it : sub->h_sitems) widths |= it.width;
+  if (columns && widths % 32 != 0) return false;
+  P.octets = widths % 8 == 0;
   // by columns: as many at a time as the tile's rows leave room for
   auto tile = [&](int kc) {
-    rows = !columns ? (int)(((long long)(lds - 16) / 6 - 24) * 8 / 9 - 32) / sub->hop
-           : form == nna::SHORT_COLUMNS ? nna::SHORT_ROWS
-                                        : std::min(nna::SHORT_PASSES * 2048 / kc, (int)((lds - 16) / 6 / (kc + 8)));
     int m = nna::SHORT_FRAMES[form];
-    for (const nna::ShortItem& it : sub->h_sitems) m = std::min(m, pick_tile_frames(m, T, it.jspan - 1, rows));
+    for (const nna::ShortItem& it : sub->h_sitems) {
+      const int rows = !columns ? (int)(((long long)(lds - 16) / 6 - 24) * 8 / 9 - 32) / it.width
+                       : form == nna::SHORT_COLUMNS ? nna::SHORT_ROWS
+                                                    : std::min(nna::SHORT_PASSES * 2048 / kc, (int)((lds - 16) / 6 / (kc + 8)));
+      m = std::min(m, pick_tile_frames(m, T, it.jspan - 1, rows));
+    }
     P.columns_at_once = kc;
     return m;
+  };
+  // (the columns past a row's last are read too, and are no more than the hop's)
+  auto whole = [&](int kc) {
+    return std::all_of(sub->h_sitems.begin(), sub->h_sitems.end(), [&](const nna::ShortItem& it) { return ceil_div(it.width, kc) * kc <= std::max(it.width, sub->hop); });
   };
   if (form <= nna::SHORT_COLUMNS) {
     M = tile(32);
   } else {
     for (int kc = 128; kc >= 32; kc /= 2)
-      if (sub->hop % kc == 0 && ((M = tile(kc)) == nna::SHORT_FRAMES[form] || kc == 32)) break;
+      if (whole(kc) && ((M = tile(kc)) == nna::SHORT_FRAMES[form] || kc == 32)) break;
   }
   if (4 * M < 3 * nna::SHORT_FRAMES[form]) return false;
   const long long nseg = 1 + (M - 1 + T - 1) / T;
   P.plane = nna::SHORT_PLANE_MIN[form];
   for (const nna::ShortItem& it : sub->h_sitems) {
     const long long r = M + nseg * (it.jspan - 1);
-    P.plane = std::max(P.plane, columns ? (int)(r * (P.columns_at_once + 8)) : nna::SHORT_PLANE(r * sub->hop));
+    P.plane = std::max(P.plane, columns ? (int)(r * (P.columns_at_once + 8)) : nna::SHORT_PLANE(r * it.width));
   }
   P.tile_frames = M;
   P.n_ft = (n_frames + M - 1) / M;
@@ -471,21 +480,37 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
   return NNA_OK;
 }
 
-// The kernels tap by tap (nna_kernels_short.hip).  Tiles of 64 frames where 80 KB, half a CU's LDS, hold their samples and there are two
-// of them per CU; else tiles of 128 frames by columns where there are as many of these, or, where long kernels take the rows, of 64; else
-// 32 or 16 frames, which fill the chip sooner.  12 bins, hop 512: 16 frames 7.9, 18.6, 30.2, 53.5 us for 5,500, 17,250, 34,500, 69,000
-// frames, columns 20.5, 25.2, 29.9, 38.6; 24 bins, hop 128: 64 frames 12.1, 15.2, 23.0, 36.4, columns 19.9, 20.3, 25.2, 36.0, 32 frames 9.4, 13.0,
-// 19.6, 31.8; hop 64, 138,000 frames: 47 with 64, 54 with 32, 60 by columns; 117,200 frames, kernels of 4,336 taps, hop 256 and 128: 64 by
-// columns 401, 358, 128 with half of their frames 478, 472.  A tile that holds less than three quarters of its frames is left to
-// the next one.  False: not a launch for this kernel.
+// The kernels tap by tap (nna_kernels_short.hip).
+// Rows of whole hops: tiles of 64 frames where 80 KB, half a CU's LDS, hold their samples and there are two of them per CU; else tiles of
+// 128 frames by columns where there are as many of these, or, where long kernels take the rows, of 64; else 32 or 16 frames, which fill the
+// chip sooner.  12 bins, hop 512: 16 frames 7.9, 18.6, 30.2, 53.5 us for 5,500, 17,250, 34,500, 69,000 frames, columns 20.5, 25.2, 29.9, 38.6;
+// 24 bins, hop 128: 64 frames 12.1, 15.2, 23.0, 36.4, columns 19.9, 20.3, 25.2, 36.0, 32 frames 9.4, 13.0, 19.6, 31.8; hop 64, 138,000 frames: 47
+// with 64, 54 with 32, 60 by columns; 117,200 frames, kernels of 4,336 taps, hop 256 and 128: 64 by columns 401, 358, 128 with half of their
+// frames 478, 472.
+// Rows of own taps share nothing that a longer run of frames would keep: by columns from 300 tiles of 128 on (12 bins, 128 samples a frame,
+// 20,000, 60,000, 120,000 frames: columns 10.1, 12.7, 18.6, 64 frames 8.8, 16.1, 30.3, 32 frames 8.1, 14.3, 24.1; 256 samples: columns 16.5, 21.9,
+// 31.1, 64 by columns 14.0, 27.6, 47.7; 960: 45,000 frames 57.3, 53.2).
+// 16 frames that take more than 80 KB leave a CU one workgroup: up to 1,024 tiles, or where columns cannot be (25,000 frames of 1,024 samples: 67 us,
+// 64 by columns 53; 11,800 of two items of 800: 33, 53).  Against cqt_kernel they take, hops 1,000 to 1,500, 60,000 frames and more: kernels of 1.05
+// hops 0.9 .. 1.6 of its time, 1.6 hops 0.95 .. 1.1, 2.5 hops 0.8; two items 1.6 hops 1.1 .. 1.3, 2 hops 1.06, 2.5 hops 1.02, 3.5 hops 0.83.
+// A tile that holds less than three quarters of its frames is left to the next one.  False: not a launch for this kernel.
 bool shape_short(const nna_plan* sub, long long n_frames, long long T, nna::ShortParams& P) {
   auto fit = [&](int form, size_t lds) { return fit_short(sub, n_frames, T, form, lds, P); };
   auto many = [&](long long tiles) { return P.n_ft * P.n_items >= tiles; };
-  if (fit(nna::SHORT_64, 80 * 1024) && many(512)) return true;
-  if (fit(nna::SHORT_COLUMNS, 0) && many(512)) return true;
+  const bool apart = sub->h_sitems[0].jspan == 1;
+  int most = 0;
+  long long longest = 0;
+  for (const nna::ShortItem& it : sub->h_sitems) most = std::max(most, it.width);
+  for (int k = 0; k < sub->n_bins; ++k) longest = std::max(longest, sub->row_e[2 * k] - sub->row_s[2 * k]);
+  if (!apart && fit(nna::SHORT_64, 80 * 1024) && many(512)) return true;
+  if (fit(nna::SHORT_COLUMNS, 0) && many(apart && most <= 512 ? 300 : 512)) return true;
   if (fit(nna::SHORT_COLUMNS_64, 80 * 1024) && many(512)) return true;
   if (fit(nna::SHORT_32, 80 * 1024) && many(256)) return true;
-  return fit(nna::SHORT_16, 80 * 1024) || fit(nna::SHORT_16, nna::SHORT_LDS) || fit(nna::SHORT_COLUMNS_64, 80 * 1024);
+  if (fit(nna::SHORT_16, 80 * 1024)) return true;
+  const bool one = fit(nna::SHORT_16, nna::SHORT_LDS);
+  if (one && !many(1024)) return true;
+  if (fit(nna::SHORT_COLUMNS_64, 80 * 1024)) return true;
+  return one && fit(nna::SHORT_16, nna::SHORT_LDS) && (!many(6144) || 10 * longest > (P.n_items == 1 ? 15LL : 21LL) * sub->hop);
 }
 
 nna_status run_conv_short(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,

@@ -10,7 +10,8 @@
 // knows how many of them it has taps of.
 //   Tiles of 64, 32 or 16 frames: all their samples at once, one behind the other; each wave takes every fourth step of all frames, so
 //   that a workgroup reads the weights once, and the waves' sums are added through LDS.
-//   Tiles of 128 frames, where 64 frames' samples do not fit: 32 columns of all their hops at a time, a row for each hop, the next 32
+// A tile's rows are whole hops, which neighbouring frames share, or every frame's own taps, where these are fewer than a hop's.
+//   Tiles of 128 frames, where 64 frames' samples do not fit: 32 columns of all their rows at a time, the next 32
 //   requested while the last step of these is multiplied (loads return in order: requested earlier, they would be waited for with the
 //   next step's weights).
 //   Tiles of 64 frames by columns: up to 128 at a time, the steps shared as above; kernels of many hops, and those beside the items with a
@@ -36,8 +37,8 @@ typedef f32x4 f32x4_u __attribute__((aligned(4)));
 // its first bfloat16 is finite
 __device__ __forceinline__ bool tame(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7fffffffu) < 0x7f7f8000u; }
 
-// where a tile's samples lie in LDS: one behind the other, in words of eight or (hops that are no multiple of 8) of four; or some columns of
-// all its hops at a time, a row for each hop
+// where a tile's samples lie in LDS: one behind the other, in words of eight or (rows that are no multiple of 8) of four; or some columns of
+// all its rows at a time
 enum { OCTETS_OF, QUADS_OF, COLUMNS };
 
 // WK = 4: the four waves share the steps of 16 FB frames; 1: each has 16 FB frames of its own.
@@ -56,7 +57,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
   tm.n0 = (g.T - tm.t0) < m_valid ? (g.T - tm.t0) : m_valid;
   tm.extra = item.jspan - 1;
   const int rows_used = tm.frame_row(m_valid - 1) + tm.extra + 1;
-  const int hop = g.hop, L = (int)g.L;
+  const int hop = g.hop, width = item.width, L = (int)g.L;
   constexpr int RB = SHORT_RB, THREADS = 256;
   constexpr bool OCTETS = LAYOUT == OCTETS_OF;
   const int plane = P.plane;  // values per plane
@@ -115,11 +116,11 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
 #pragma unroll
   for (int fb = 0; fb < FB; ++fb) {
     const int i = wf * (16 * FB) + fb * 16 + n;
-    x_off[fb] = (i < m_valid ? tm.frame_row(i) : 0) * (LAYOUT == COLUMNS ? (WK == 1 ? 32 : P.columns_at_once) + 8 : hop) + 8 * q;
+    x_off[fb] = (i < m_valid ? tm.frame_row(i) : 0) * (LAYOUT == COLUMNS ? (WK == 1 ? 32 : P.columns_at_once) + 8 : width) + 8 * q;
 #pragma unroll
     for (int b = 0; b < RB; ++b) sum[fb][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
-  // one octet of every nine is left free, so that frames a hop of 16 .. 512 apart lie on different banks
+  // one octet of every nine is left free, so that frames whose rows are 16 .. 512 apart lie on different banks
   auto place = [](int i) { return OCTETS ? i + (i >> 6 << 3) : i; };
   // a step whose first value is `offset` from the frame's row, for its first `a` row blocks; each block's weights make room for step `next`'s
   auto step = [&](int a, int offset, int next) {
@@ -171,8 +172,8 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
       int sigma;
       tm.decode(row < rows_used ? row : rows_used - 1, b, sigma);
       xb[p] = g.x + b * g.L;
-      pos[p] = (sigma + item.j0) * hop - g.pad + 8 * cv;
-      edge[p] = __builtin_amdgcn_ballot_w64(pos[p] < 0 || pos[p] > L - hop) != 0;
+      pos[p] = sigma * hop + item.base - g.pad + 8 * cv;
+      edge[p] = __builtin_amdgcn_ballot_w64(pos[p] < 0 || pos[p] > L - ((width + kc - 1) & -kc)) != 0;
       if (!edge[p]) xb[p] += pos[p];
     }
     f32x4 R[NP][2];
@@ -191,16 +192,16 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
         }
       }
     };
-    // how many steps lie ahead of every 32 columns, [hop / 32 + 1], then the steps in that order: row blocks | hop-block << 2 | which 32
+    // how many steps lie ahead of every 32 columns, [width / 32 + 1], then the steps in that order: row blocks | row << 2 | which 32
     // columns << 12; step
     const int* __restrict__ ahead_of = P.columns + item.columns;
-    const int2* __restrict__ order = reinterpret_cast<const int2*>(ahead_of + (hop / 32 + 2) / 2 * 2);
-    const int n_order = ahead_of[hop / 32];
+    const int2* __restrict__ order = reinterpret_cast<const int2*>(ahead_of + (width / 32 + 2) / 2 * 2);
+    const int n_order = ahead_of[width / 32];
     int at = wk;
     int2 d = order[at < n_order ? at : 0];
     fetch_w(d.y, w);
     request(0);
-    for (int c = 0; c < hop; c += kc) {
+    for (int c = 0; c < width; c += kc) {
       __syncthreads();  // the columns before have been read by every wave
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
@@ -219,7 +220,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
       }
       __syncthreads();
       // (loads return in order: the next columns are requested behind the weights of these columns' last step)
-      const int end = ahead_of[(c + kc) / 32], next_c = c + kc < hop ? c + kc : c;
+      const int end = ahead_of[(c + kc < width ? c + kc : width) / 32], next_c = c + kc < width ? c + kc : c;
       if (at >= end) request(next_c);
       for (; at < end; at += WK) {
         if (at + WK >= end) request(next_c);
@@ -231,9 +232,9 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
   } else {
     fetch_w(wk, w);
     constexpr int N = OCTETS ? 8 : 4, U = 4;  // samples of a unit, units a thread requests at a time
-    const int per_row = hop / N, units = rows_used * per_row, first = tm.n0 + tm.extra, seg = g.T + tm.extra;
+    const int per_row = width / N, units = rows_used * per_row, first = tm.n0 + tm.extra, seg = g.T + tm.extra;
     const float inv_row = 1.f / (float)per_row, inv_seg = 1.f / (float)seg;
-    const int base = item.j0 * hop - g.pad;
+    const int base = item.base - g.pad;
     const float* __restrict__ x0 = g.x + tm.b0 * g.L;
     for (int u0 = tid; u0 < units + 32 / N; u0 += THREADS * U) {
       f32x4 v[U][2];
@@ -302,14 +303,14 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
   // `taken`: a bin whose taps meet such samples, bit 2 (RB fb + rb) + u
   unsigned taken = 0;
   if (*flag) {
-    // the tile's samples in units of four, hop by hop
-    const int per_row = hop / 4, units = rows_used * per_row;
+    // the tile's samples in units of four, row by row
+    const int per_row = width / 4, units = rows_used * per_row;
     auto unit = [&](int u) {
       const int row = u / per_row, col = 4 * (u - row * per_row);
       long long b;
       int sigma;
       tm.decode(row, b, sigma);
-      return four(g.x + b * g.L, (sigma + item.j0) * hop - g.pad + col);
+      return four(g.x + b * g.L, sigma * hop + item.base - g.pad + col);
     };
     int* const count = reinterpret_cast<int*>(S);
     int2* const list = reinterpret_cast<int2*>(S) + 1;  // place in the tile, value
@@ -351,8 +352,8 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
         const int2 bad = list[i];
 #pragma unroll
         for (int fb = 0; fb < EB; ++fb) {
-          const int fi = wave * (16 * EB) + fb * 16 + n, at = bad.x - (valid[fb] ? tm.frame_row(fi) : 0) * hop, tap = at + item.j0 * hop;
-          if (!valid[fb] || at < 0 || at >= item.jspan * hop) continue;
+          const int fi = wave * (16 * EB) + fb * 16 + n, at = bad.x - (valid[fb] ? tm.frame_row(fi) : 0) * width, tap = at + item.base;
+          if (!valid[fb] || at < 0 || at >= item.jspan * width) continue;
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
