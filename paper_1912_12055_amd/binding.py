@@ -34,7 +34,7 @@ EXPORTS = [
     "nna_cqt_backward_workspace", "nna_cqt_backward", "nna_mel_with_stft", "nna_cqt2010v2_static",
     "nna_cqt2010v2_backward_workspace", "nna_cqt2010v2_backward",
     "nna_plan_get_spectral_kernels", "nna_plan_set_spectral_kernels", "nna_cqt1992_backward_workspace", "nna_cqt1992_backward",
-    "nna_cqt2010_backward_workspace", "nna_cqt2010_backward", "nna_kept_bytes", "nna_forward_keep", "nna_backward_kept", "nna_plan_applied_kernels", "nna_plan_applied_tiles",
+    "nna_cqt2010_backward_workspace", "nna_cqt2010_backward", "nna_kept_bytes", "nna_forward_keep", "nna_backward_kept", "nna_plan_applied_kernels", "nna_plan_applied_tiles", "nna_plan_short_tiles",
     "nna_plan_destroy",
     "nna_status_str", "nna_last_error",
 ]
