@@ -300,7 +300,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
 #pragma unroll
   for (int fb = 0; fb < EB; ++fb) valid[fb] = wave * (16 * EB) + fb * 16 + n < m_valid && (WK == 1 || wave < FB);
   auto finite_sums = [&](int fb, int rb, int u) { return finite(acc[fb][rb][2 * u]) && finite(acc[fb][rb][2 * u + 1]); };
-  // `taken`: a bin whose taps meet such samples, bit 2 (RB fb + rb) + u
+  // `taken`: a bin whose taps meet a sample that is not finite, bit 2 (RB fb + rb) + u
   unsigned taken = 0;
   if (*flag) {
     // the tile's samples in units of four, row by row
@@ -314,6 +314,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
     };
     int* const count = reinterpret_cast<int*>(S);
     int2* const list = reinterpret_cast<int2*>(S) + 1;  // place in the tile, value
+    unsigned short* const order = S + 4 + 4 * 4 * THREADS;
     __syncthreads();
     if (tid < 2) count[tid] = 0;
     __syncthreads();
@@ -330,7 +331,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
       const float2 wt = P.taps[own.z + tap - own.x];
       acc[fb][rb][2 * u] += wt.x * v;
       acc[fb][rb][2 * u + 1] += wt.y * v;
-      taken |= 1u << (2 * (RB * fb + rb) + u);
+      taken |= (finite(v) ? 0u : 1u) << (2 * (RB * fb + rb) + u);
     };
     // few of them: listed a thousand samples at a time, each for the frames it meets
 #pragma unroll 1
@@ -347,9 +348,18 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
       }
       __syncthreads();
       const int m = *count;
+      // (the order of the entries is the waves' chance: by their places, so that every call adds the products in the same order)
+#pragma unroll 1
+      for (int i = tid; i < m; i += THREADS) {
+        int before = 0;
+#pragma unroll 1
+        for (int j = 0; j < m; ++j) before += list[j].x < list[i].x ? 1 : 0;
+        order[before] = (unsigned short)i;
+      }
+      __syncthreads();
 #pragma unroll 1
       for (int i = 0; i < m; ++i) {
-        const int2 bad = list[i];
+        const int2 bad = list[order[i]];
 #pragma unroll
         for (int fb = 0; fb < EB; ++fb) {
           const int fi = wave * (16 * EB) + fb * 16 + n, at = bad.x - (valid[fb] ? tm.frame_row(fi) : 0) * width, tap = at + item.base;
@@ -375,7 +385,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
       const int s0 = (int)(f - b * g.T) * hop - g.pad;
       const int4 own = P.support[item.bin0 + k];
       float re = 0.f, im = 0.f;
-      bool met = false;
+      bool met = false, wild = false;
 #pragma unroll 1
       for (int tap = own.x; tap < own.y && !(re != re && im != im); tap += 16) {
         f32x4 v[4];
@@ -393,6 +403,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
           re += wt.x * v[e / 4][e % 4];
           im += wt.y * v[e / 4][e % 4];
           met = true;
+          wild = wild || !finite(v[e / 4][e % 4]);
         }
       }
 #pragma unroll
@@ -400,7 +411,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
         if (i != bit || !met) continue;
         acc[(i >> 1) / RB][(i >> 1) % RB][2 * (i & 1)] += re;
         acc[(i >> 1) / RB][(i >> 1) % RB][2 * (i & 1) + 1] += im;
-        taken |= 1u << i;
+        taken |= (wild ? 1u : 0u) << i;
       }
     }
   }
