@@ -34,8 +34,14 @@ namespace {
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
 
-// its first bfloat16 is finite
-__device__ __forceinline__ bool tame(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7fffffffu) < 0x7f7f8000u; }
+// Samples are multiplied by 2^10 before they are split: the third bfloat16 of those below 2^-110 would lose bits to the exponent's end.  An
+// octave's error, 2-norm of its worst bin, samples of 1e-34, 1e-36, 1e-38: 3.8e-7 .. 1.2e-6, 6e-7 .. 9e-6, 6e-5 .. 9e-4 with
+// cqt_kernel's float32 instruction, 1.1e-6, 1.0e-4, 1.1e-2 as they are, 0.9e-7 .. 1.8e-7, 1.4e-7 .. 2.6e-7, 1.0e-5 .. 1.8e-5.  (By 2^24, 3e-6 ..
+// 1.5e-5 at 1e-38, but samples above 2e31 would be none that bfloat16 holds.)
+constexpr int SHORT_SCALE = 10;
+// the first bfloat16 of v, of v 2^SHORT_SCALE is finite
+__device__ __forceinline__ bool holds(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7fffffffu) < 0x7f7f8000u; }
+__device__ __forceinline__ bool tame(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7fffffffu) < 0x7f7f8000u - (SHORT_SCALE << 23); }
 
 // where a tile's samples lie in LDS: one behind the other, in words of eight or (rows that are no multiple of 8) of four; or some columns of
 // all its rows at a time
@@ -96,6 +102,8 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
   };
   // a unit's parts; `v` may change
   auto planes = [&](f32x4 (&v)[2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) v[h] *= (float)(1 << SHORT_SCALE);
     Planes b = split8(v);
     u16x2 top = {0, 0};
 #pragma unroll
@@ -104,7 +112,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[h][e] = tame(v[h][e]) ? v[h][e] : 0.f;
+        for (int e = 0; e < 4; ++e) v[h][e] = holds(v[h][e]) ? v[h][e] : 0.f;
       b = split8(v);
       *flag = 1;
     }
@@ -278,7 +286,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
 #pragma unroll
       for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
-        for (int b = 0; b < RB; ++b) acc[fb][b] = sum[fb][b];
+        for (int b = 0; b < RB; ++b) acc[fb][b] = sum[fb][b] * (1.f / (1 << SHORT_SCALE));
     } else {
       // the waves' sums, through LDS: wave k takes frame block k
       f32x4* const part = reinterpret_cast<f32x4*>(S) + lane;  // [wave][frame block][row block][64 lanes]
@@ -293,6 +301,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
         acc[0][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
         if (wave < FB)
           for (int k = 0; k < WK; ++k) acc[0][b] += part[((k * FB + wave) * RB + b) * 64];
+        acc[0][b] *= 1.f / (1 << SHORT_SCALE);
       }
     }
   }
@@ -384,10 +393,15 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
       const float* __restrict__ xw = g.x + b * g.L;
       const int s0 = (int)(f - b * g.T) * hop - g.pad;
       const int4 own = P.support[item.bin0 + k];
-      float re = 0.f, im = 0.f;
+      float re = 0.f, im = 0.f, part_re = 0.f, part_im = 0.f;  // (sums of 16 products, of 256, of all)
       bool met = false, wild = false;
 #pragma unroll 1
-      for (int tap = own.x; tap < own.y && !(re != re && im != im); tap += 16) {
+      for (int tap = own.x; tap < own.y && !(part_re != part_re && part_im != part_im); tap += 16) {
+        if ((tap - own.x) % 256 == 0) {
+          re += part_re;
+          im += part_im;
+          part_re = part_im = 0.f;
+        }
         f32x4 v[4];
         bool any = false;
 #pragma unroll
@@ -396,16 +410,21 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
           any = any || !tame(v[e / 4][e % 4]);
         }
         if (!any) continue;
+        float sum_re = 0.f, sum_im = 0.f;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           if (tap + e >= own.y || tame(v[e / 4][e % 4])) continue;
           const float2 wt = P.taps[own.z + tap + e - own.x];
-          re += wt.x * v[e / 4][e % 4];
-          im += wt.y * v[e / 4][e % 4];
+          sum_re += wt.x * v[e / 4][e % 4];
+          sum_im += wt.y * v[e / 4][e % 4];
           met = true;
           wild = wild || !finite(v[e / 4][e % 4]);
         }
+        part_re += sum_re;
+        part_im += sum_im;
       }
+      re += part_re;
+      im += part_im;
 #pragma unroll
       for (int i = 0; i < 2 * RB * EB; ++i) {
         if (i != bit || !met) continue;
