@@ -307,12 +307,7 @@ static void release_fixed_forms(nna_plan* plan) {
   plan->d_litems = nullptr;
   plan->d_lsupport = nullptr;
   plan->lowrank = false;
-  (void)hipFree(plan->d_sitems);
-  (void)hipFree(plan->d_sw);
-  (void)hipFree(plan->d_staps);
-  (void)hipFree(plan->d_ssteps);
-  (void)hipFree(plan->d_scolumns);
-  (void)hipFree(plan->d_ssupport);
+  (void)hipFree(plan->d_sw);  // and all that was uploaded with it
   plan->d_sitems = nullptr;
   plan->d_sw = nullptr;
   plan->d_staps = nullptr;

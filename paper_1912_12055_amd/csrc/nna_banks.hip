@@ -727,14 +727,39 @@ void build_conv_bank(nna_plan* p, ValueFn value) {
   p->exec_flops = 2.0 * (double)exec_groups * CQ_KC * CQ_ROWS;
 }
 
+namespace {
+// fn(0 .. n - 1), each on whichever of a few host threads is free; throws what fn throws (bad_alloc)
+template <typename Fn>
+void for_each_parallel(int n, Fn fn, bool worth_threads = true) {
+  std::atomic<int> next{0};
+  std::atomic<bool> failed{false};
+  auto work = [&] {
+    try {
+      for (int i; !failed && (i = next++) < n;) fn(i);
+    } catch (const std::bad_alloc&) {
+      failed = true;
+    }
+  };
+  std::vector<std::thread> threads;
+  const int more = worth_threads ? std::min({n, 8, (int)std::thread::hardware_concurrency()}) - 1 : 0;
+  try {
+    for (int i = 0; i < more; ++i) threads.emplace_back(work);
+  } catch (const std::exception&) {  // no more threads to be had: those that are there do
+  }
+  work();
+  for (std::thread& t : threads) t.join();
+  if (failed) throw std::bad_alloc();
+}
+}  // namespace
+
 // Both stages of eq. (CQT1992) as one: X_cq[q] = sum_n x[n] c_q[n] with c_q[n] = (1/K) sum_{k <= K/2} Y[q, k] e^{-2 pi i k n / K},
 // the kernel of eq. (CQT) less its negative frequencies.  Dense in n, so a bank of 2 n_bins rows x K taps: for plans whose
 // kernels are fixed 2 n_bins / K of the two-stage form's multiply-adds.
 std::vector<double> cqt1992_composed_rows(const nna_plan* p) {
   const int K = p->K;
   std::vector<double> rows((size_t)2 * p->n_bins * K);
-  std::vector<std::complex<double>> a(K);
-  for (int q = 0; q < p->n_bins; ++q) {
+  for_each_parallel(p->n_bins, [&](int q) {
+    std::vector<std::complex<double>> a(K);
     cqt1992_spectrum(p, q, a);
     for (int k = 0; k < K; ++k) a[k] = k <= K / 2 ? std::conj(a[k]) : 0.0;
     fft_pow2(a);
@@ -742,7 +767,7 @@ std::vector<double> cqt1992_composed_rows(const nna_plan* p) {
       rows[(size_t)(2 * q) * K + n] = a[n].real() / K;
       rows[(size_t)(2 * q + 1) * K + n] = a[n].imag() / K;
     }
-  }
+  }, (long long)p->n_bins * K > 1 << 13);
   return rows;
 }
 
@@ -756,7 +781,7 @@ void build_cqt_bank_rows(nna_plan* c, const std::vector<double>& rows) {
   build_conv_bank(c, [&](int row, long long tap) { return row < n_rows && tap < K ? rows[(size_t)row * K + tap] : 0.0; });
 }
 
-void build_cqt_bank(nna_plan* p) {
+void build_cqt_bank(nna_plan* p, const CqtKernelSource& kernels) {
   p->conv_rows = 2 * p->n_bins;
   p->row_s.resize(p->conv_rows);
   p->row_e.resize(p->conv_rows);
@@ -766,8 +791,7 @@ void build_cqt_bank(nna_plan* p) {
     p->row_e[2 * k] = p->row_e[2 * k + 1] = p->sk[k] + p->Nk[k];
     sumN += (double)p->Nk[k];
   }
-  CqtKernelGen gen(p);
-  build_conv_bank(p, [&](int row, long long tap) { return gen.value(row, tap); });
+  build_conv_bank(p, kernels.value);
   p->alg_flops = 4.0 * sumN;
 }
 
@@ -1022,28 +1046,6 @@ LowrankGroup lowrank_group(const nna_plan* p, int k0, const CqtKernelSource& ker
   return g;
 }
 
-// fn(0 .. n - 1), each on whichever of a few host threads is free; throws what fn throws (bad_alloc)
-template <typename Fn>
-void for_each_parallel(int n, Fn fn) {
-  std::atomic<int> next{0};
-  std::atomic<bool> failed{false};
-  auto work = [&] {
-    try {
-      for (int i; !failed && (i = next++) < n;) fn(i);
-    } catch (const std::bad_alloc&) {
-      failed = true;
-    }
-  };
-  std::vector<std::thread> threads;
-  const int more = std::min({n, 8, (int)std::thread::hardware_concurrency()}) - 1;
-  try {
-    for (int i = 0; i < more; ++i) threads.emplace_back(work);
-  } catch (const std::exception&) {  // no more threads to be had: those that are there do
-  }
-  work();
-  for (std::thread& t : threads) t.join();
-  if (failed) throw std::bad_alloc();
-}
 }  // namespace
 
 void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels) {
@@ -1147,6 +1149,45 @@ CqtKernelSource cqt_kernels(const nna_plan* p) {
   return {[gen](int row, long long tap) { return gen->value(row, tap); },
           [gen](int k, long long tap0, int n, double* re, double* im) { gen->taps(k, tap0, n, re, im); }};
 }
+constexpr long long kTapsWorthThreads = 1 << 13;  // some 0.3 ms of one thread's time; eight threads come up in 0.1 .. 0.2
+// ... every tap evaluated once, for plans whose kernels go into several forms (up to 64 MB of them)
+CqtKernelSource evaluated_kernels(const nna_plan* p) {
+  struct Taps {
+    std::vector<long long> s, first;
+    std::vector<std::complex<double>> v;
+  };
+  auto all = std::make_shared<Taps>();
+  all->s = p->sk;
+  all->first.assign(p->n_bins + 1, 0);
+  for (int k = 0; k < p->n_bins; ++k) all->first[k + 1] = all->first[k] + p->Nk[k];
+  if (all->first[p->n_bins] > 1 << 22) return cqt_kernels(p);
+  all->v.resize(all->first[p->n_bins]);
+  for_each_parallel(p->n_bins, [&](int k) {
+    std::complex<double>* v = &all->v[all->first[k]];
+    const long long N = p->Nk[k];
+    double sum = 0;
+    for (long long n = 0; n < N; ++n) sum += (v[n] = window_value(p->window, n, N)).real();
+    for (long long n = 0; n < N; ++n) {
+      const double w = v[n].real() / sum;
+      double s, c;
+      sincos(2.0 * kPi * p->Q * (double)n / (double)N, &s, &c);
+      v[n] = {w * c, -w * s};
+    }
+  }, all->first[p->n_bins] > kTapsWorthThreads);
+  auto at = [all](int k, long long tap) {
+    const long long n = tap - all->s[k];
+    return n < 0 || n >= all->first[k + 1] - all->first[k] ? std::complex<double>(0.0) : all->v[all->first[k] + n];
+  };
+  const int rows = 2 * p->n_bins;
+  return {[at, rows](int row, long long tap) { return row >= rows ? 0.0 : row & 1 ? at(row >> 1, tap).imag() : at(row >> 1, tap).real(); },
+          [at](int k, long long tap0, int n, double* re, double* im) {
+            for (int i = 0; i < n; ++i) {
+              const std::complex<double> v = at(k, tap0 + i);
+              re[i] = v.real();
+              im[i] = v.imag();
+            }
+          }};
+}
 CqtKernelSource dense_kernels(std::vector<double> rows, long long K) {
   auto r = std::make_shared<const std::vector<double>>(std::move(rows));
   return {[r, K](int row, long long tap) { return (*r)[(size_t)row * K + tap]; },
@@ -1233,27 +1274,19 @@ void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std
   std::vector<long long> first(p->n_bins + 1, 0);  // of a kernel's own taps
   for (int k = 0; k < p->n_bins; ++k) first[k + 1] = first[k] + (in_run[k] ? p->row_e[2 * k] - p->row_s[2 * k] : 0);
   if (first[p->n_bins] > 1 << 28) return;
-  p->h_staps.resize(2 * first[p->n_bins]);
-  for_each_parallel(p->n_bins, [&](int k) {
-    const int n = (int)(first[k + 1] - first[k]);
-    std::vector<double> re(n), im(n);
-    kernels.taps(k, p->row_s[2 * k], n, re.data(), im.data());
-    for (int i = 0; i < n; ++i) {
-      p->h_staps[2 * (first[k] + i)] = (float)re[i];
-      p->h_staps[2 * (first[k] + i) + 1] = (float)im[i];
-    }
-  });
   for (int k = 0; k < p->n_bins; ++k)
     for (const long long v : {p->row_s[2 * k], p->row_e[2 * k], first[k], 0LL}) p->h_ssupport.push_back((int)v);
   constexpr int per_item = 8 * nna::SHORT_RB;
+  long long words = 0;
+  std::vector<int> item_of(p->n_bins, 0);
   std::vector<std::pair<int, int>> items;
   for (const auto& [lo, hi] : runs)
     for (int k0 = lo; k0 < hi; k0 += per_item) items.push_back({k0, std::min(per_item, hi - k0)});
   // A tile's rows: whole hops, which neighbouring frames share, or every frame's own taps, where these are fewer (or, hops that are no
   // multiple of 32 and so cannot be read by columns, up to a quarter more).  Items that read less are out of step with each other, which
   // costs them their common samples in the L2: several of them want a quarter less (36 bins, 480 and 320 of 512 samples: 163 us by whole
-  // hops, 173).  59,858 frames of 12 bins, 120 taps, hop 512, 1,024,
-  // 2,048, 4,096: 34, 54, 131, 232 us by whole hops, 13.5 by own taps (cqt_kernel 26); 299,982 frames of 1,050 taps, hop 1,000: 800, 368 (593).
+  // hops, 173).  59,858 frames of 12 bins, 120 taps, hop 512, 1,024, 2,048, 4,096: 34, 54, 131, 232 us by whole hops, 13.5 by own taps
+  // (cqt_kernel 26); 299,982 frames of 1,050 taps, hop 1,000: 800, 368 (593).
   const bool lines = hop % 32 == 0;
   auto own = [&](long long lo) { return lines ? std::max(0LL, floor_div(lo - p->pad, 32) * 32 + p->pad) : lo / 8 * 8; };
   bool apart = true;
@@ -1282,23 +1315,15 @@ void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std
     item.base = (int)base;
     item.width = apart ? (int)(ceil_div(hi[0] - base, 32) * 32) : hop;
     item.jspan = apart ? 1 : (int)(ceil_div(hi[0], hop) - j0);
-    item.w0 = (long long)p->h_sw.size() / 4;
+    item.w0 = words / 4;
     item.step0 = (int)p->h_ssteps.size();
     item.n_step = (int)ceil_div(hi[0] - base, 32);
-    p->h_sw.resize(p->h_sw.size() + (size_t)item.n_step * nna::SHORT_RB * 3 * 256, 0u);
+    words += (long long)item.n_step * nna::SHORT_RB * 3 * 256;
     for (int s = 0; s < item.n_step; ++s) {
       int a = 0;
       while (a < n_rb && base + 32 * s + 32 > lo[a] && base + 32 * s < hi[a]) ++a;
       p->h_ssteps.push_back(a);
     }
-    for (int k = k0; k < k0 + item.n_bins; ++k)
-      for (long long tap = p->row_s[2 * k]; tap < p->row_e[2 * k]; ++tap)
-        for (int part = 0; part < 2; ++part) {
-          // [step][row block][3 planes][64 lanes] of an octet: lane (q, row) holds taps 8 q .. 8 q + 7 of the step
-          const int row = 2 * (k - k0) + part, at = (int)(tap - base), e = at % 8, lane = at / 8 % 4 * 16 + row % 16;
-          unsigned* block = &p->h_sw[(size_t)item.w0 * 4 + ((size_t)(at / 32) * nna::SHORT_RB + row / 16) * 768];
-          put_parts(p->h_staps[2 * (first[k] + tap - p->row_s[2 * k]) + part], block + lane * 4 + e / 2, 256, e % 2);
-        }
     if (item.width % 32 == 0) {
       item.columns = (int)p->h_scolumns.size();
       std::vector<int> order;
@@ -1315,8 +1340,26 @@ void build_cqt_bank_short(nna_plan* p, const CqtKernelSource& kernels, const std
       if (p->h_scolumns.size() % 2) p->h_scolumns.push_back(0);
       p->h_scolumns.insert(p->h_scolumns.end(), order.begin(), order.end());
     }
+    for (int k = k0; k < k0 + nb; ++k) item_of[k] = (int)p->h_sitems.size();
     p->h_sitems.push_back(item);
   }
+  p->h_staps.resize(2 * first[p->n_bins]);
+  p->h_sw.assign(words, 0u);
+  for_each_parallel(p->n_bins, [&](int k) {
+    const int n = (int)(first[k + 1] - first[k]);
+    if (n == 0) return;
+    const nna::ShortItem& item = p->h_sitems[item_of[k]];
+    std::vector<double> taps[2] = {std::vector<double>(n), std::vector<double>(n)};
+    kernels.taps(k, p->row_s[2 * k], n, taps[0].data(), taps[1].data());
+    for (int i = 0; i < n; ++i)
+      for (int part = 0; part < 2; ++part) {
+        const float v = p->h_staps[2 * (first[k] + i) + part] = (float)taps[part][i];
+        // [step][row block][3 planes][64 lanes] of an octet: lane (q, row) holds taps 8 q .. 8 q + 7 of the step
+        const int row = 2 * (k - item.bin0) + part, at = (int)(p->row_s[2 * k] + i - item.base), e = at % 8, lane = at / 8 % 4 * 16 + row % 16;
+        unsigned* block = &p->h_sw[(size_t)item.w0 * 4 + ((size_t)(at / 32) * nna::SHORT_RB + row / 16) * 768];
+        put_parts(v, block + lane * 4 + e / 2, 256, e % 2);
+      }
+  }, first[p->n_bins] > kTapsWorthThreads);
   p->short_taps = n_bins == p->n_bins;
 }
 

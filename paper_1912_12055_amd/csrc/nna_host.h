@@ -224,7 +224,8 @@ struct nna_plan {
   nna::CqlItem* d_litems = nullptr;
   int2* d_lsupport = nullptr;
   bool runs_lowrank() const { return lowrank && !d_wrm; }
-  // The kernels tap by tap on the bfloat16 matrix pipe (nna_kernels_short.hip): octaves of the downsampling plans
+  // The kernels tap by tap on the bfloat16 matrix pipe (nna_short.h): all of an octave of the downsampling plans (short_taps), or those
+  // beside the items with a basis.  One allocation, at d_sw.
   bool short_taps = false;
   std::vector<nna::ShortItem> h_sitems;
   std::vector<unsigned> h_sw;    // weights as three bfloat16, in operand order
@@ -433,11 +434,12 @@ MelDeviceLayout layout_mel(nna_plan* p);
 void build_cqt1992_matrix(nna_plan* p);
 MelDeviceLayout layout_cqt1992(nna_plan* p);
 std::vector<double> cqt1992_composed_rows(const nna_plan* p);
-void build_cqt_bank(nna_plan* p);
 // The kernels (p->K taps) in the form of nna_kernels_cql.hip; sets p->lowrank if it saves anything
 void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels);
 void lowrank_planes(const nna_plan* p, std::vector<unsigned>& u, std::vector<unsigned>& a);
 CqtKernelSource cqt_kernels(const nna_plan* p);
+CqtKernelSource evaluated_kernels(const nna_plan* p);
+void build_cqt_bank(nna_plan* p, const CqtKernelSource& kernels);
 CqtKernelSource dense_kernels(std::vector<double> rows, long long K);  // [2 n_bins][K]
 bool rebuild_applied(const nna_plan* owner, const nna_plan* sub, nna_plan& copy);
 void cqt_applied_rows(const nna_plan* p, double* out);

@@ -113,12 +113,30 @@ nna_status finish_plan(nna_plan* p, nna_plan** out, const MelDeviceLayout* mel) 
         if (s == NNA_OK) s = upload(&p->d_lsupport, p->h_lsupport.data(), p->h_lsupport.size() * sizeof(int), "kernel supports");
       }
       if (s == NNA_OK && !p->h_sitems.empty()) {
-        s = upload(&p->d_sw, p->h_sw.data(), p->h_sw.size() * sizeof(unsigned), "kernels");
-        if (s == NNA_OK) s = upload(&p->d_staps, p->h_staps.data(), p->h_staps.size() * sizeof(float), "kernels' own taps");
-        if (s == NNA_OK) s = upload(&p->d_ssteps, p->h_ssteps.data(), p->h_ssteps.size() * sizeof(int), "step table");
-        if (s == NNA_OK && !p->h_scolumns.empty()) s = upload(&p->d_scolumns, p->h_scolumns.data(), p->h_scolumns.size() * sizeof(int), "step table by columns");
-        if (s == NNA_OK) s = upload(&p->d_sitems, p->h_sitems.data(), p->h_sitems.size() * sizeof(nna::ShortItem), "item table");
-        if (s == NNA_OK) s = upload(&p->d_ssupport, p->h_ssupport.data(), p->h_ssupport.size() * sizeof(int), "kernel supports");
+        // one allocation and one copy for all of them: octaves are many and short (an allocation and its copy take some 30 us)
+        std::vector<unsigned char> all;
+        auto add = [&](const auto& v) {
+          const size_t at = (all.size() + 255) / 256 * 256, bytes = v.size() * sizeof(v[0]);
+          all.resize(at + bytes);
+          if (bytes) std::memcpy(all.data() + at, v.data(), bytes);
+          return at;
+        };
+        try {
+          all.reserve(p->h_sw.size() * sizeof(unsigned) + p->h_staps.size() * sizeof(float) + (1 << 16));
+          add(p->h_sw);
+          const size_t at[] = {add(p->h_staps), add(p->h_ssteps), add(p->h_scolumns), add(p->h_sitems), add(p->h_ssupport)};
+          s = upload(&p->d_sw, all.data(), all.size(), "kernels");
+          if (s == NNA_OK) {
+            char* const base = reinterpret_cast<char*>(p->d_sw);
+            p->d_staps = reinterpret_cast<float*>(base + at[0]);
+            p->d_ssteps = reinterpret_cast<int*>(base + at[1]);
+            p->d_scolumns = reinterpret_cast<int*>(base + at[2]);
+            p->d_sitems = reinterpret_cast<nna::ShortItem*>(base + at[3]);
+            p->d_ssupport = reinterpret_cast<int4*>(base + at[4]);
+          }
+        } catch (const std::bad_alloc&) {
+          s = fail(NNA_ERR_ALLOC, "out of host memory while building the octave's kernels");
+        }
       }
     }
     if (s != NNA_OK) {
@@ -226,10 +244,11 @@ nna_status make_cqt_plan(nna_plan** plan, int sr, int hop, double fmin, int k_fi
     p->K = (int)taps;
     p->pad = center ? (int)(taps / 2) : 0;
     for (int k = 0; k < n_bins; ++k) p->sk[k] = (taps - p->Nk[k]) / 2;
-    build_cqt_bank(p);
+    const CqtKernelSource kernels = evaluated_kernels(p);
+    build_cqt_bank(p, kernels);
     p->hop_blocks = !octave;
-    if (device >= 0) octave ? build_cqt_bank_short(p, cqt_kernels(p), {{0, n_bins}}) : build_cqt_bank_lowrank(p, cqt_kernels(p));
-    build_cqt_bank_fold(p);
+    if (device >= 0) octave ? build_cqt_bank_short(p, kernels, {{0, n_bins}}) : build_cqt_bank_lowrank(p, kernels);
+    if (!octave || taps > 1 << 16) build_cqt_bank_fold(p);  // (octaves whose hops it takes run the short kernels up to there)
   } catch (const std::bad_alloc&) {
     delete p;
     return fail(NNA_ERR_ALLOC, "out of host memory while building the CQT bank");
@@ -998,12 +1017,7 @@ void nna_plan_destroy(nna_plan* plan) {
       (void)hipFree(plan->d_litems);
       (void)hipFree(plan->d_lsteps);
       (void)hipFree(plan->d_lsupport);
-      (void)hipFree(plan->d_sitems);
-      (void)hipFree(plan->d_sw);
-      (void)hipFree(plan->d_staps);
-      (void)hipFree(plan->d_ssteps);
-      (void)hipFree(plan->d_scolumns);
-      (void)hipFree(plan->d_ssupport);
+      (void)hipFree(plan->d_sw);  // and all that was uploaded with it
       (void)hipFree(plan->d_cq_map);
       (void)hipFree(plan->d_row_lo);
       (void)hipFree(plan->d_few_groups);
