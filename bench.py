@@ -30,7 +30,7 @@ PEAK_F16_MFMA_TFLOPS = 2500.0  # MI355X dense fp16 / bf16 matrix peak
 PEAK_SPLIT_TFLOPS = PEAK_F16_MFMA_TFLOPS / 6  # ... of float32 products as six of bfloat16
 PEAK_HBM_GBS = 8000.0
 # the kernel each transform of the step launches (names as rocprofv3 prints them)
-KERNELS = {"stft": "fft_kernel<1024, ..., POWER>", "mel": "fft_kernel<1024, ..., MEL>", "cqt": "cqt_lowrank_kernel<4, 2>"}
+KERNELS = {"stft": "fft_kernel<1024, ..., POWER>", "mel": "fft_kernel<1024, ..., MEL>", "cqt": "cqt_lowrank_kernel<4, 4, true>"}
 
 
 def main() -> int:
@@ -239,9 +239,10 @@ def main() -> int:
             info = plan.info()
             by_blocks = info["kind"] == nb.NNA_KIND_CQT1992  # composed kernels by hop-blocks
             composed = info["kind"] == nb.NNA_KIND_CQT2010   # its octaves' kernels composed: the plan's count is the two stages'
+            octaves = composed or info["kind"] == nb.NNA_KIND_CQT2010V2  # tap by tap on the bfloat16 pipe: six products for a float32 one
             alg = running_flops(plan) if by_blocks else info["algorithmic_flops_per_frame"]
-            exe = None if by_blocks or composed else info["executed_flops_per_frame"]
-            peak = PEAK_F16_MFMA_TFLOPS if name == "stft_f16_operands" else PEAK_SPLIT_TFLOPS if by_blocks else PEAK_FP32_MFMA_TFLOPS
+            exe = None if by_blocks or octaves else info["executed_flops_per_frame"]  # (what those launches execute no plan counts)
+            peak = PEAK_F16_MFMA_TFLOPS if name == "stft_f16_operands" else PEAK_SPLIT_TFLOPS if by_blocks or octaves else PEAK_FP32_MFMA_TFLOPS
             extras[name] = {
                 "ms": round(ms, 4),
                 "gsamples_per_s": round(n_samples / ms / 1e6, 4),

@@ -545,7 +545,8 @@ nna_status nna_plan_spectral_kernels(const nna_plan* plan, double* host_out, siz
  * nna_plan_cqt1992: the DFT plus 8 per (constant-Q bin, kept DFT bin)).  The algorithmic figure of an
  * STFT or Mel plan is that of eq. (DFT2) taken directly, 2 K^2; the executed figure is that of the contraction the plan's
  * kernel bank stands for (folded: K^2 + 2K, split by tap parity: K^2 / 2 + 4K), also where the call takes the sums by a
- * fast Fourier transform instead, about 2.5 K log2 K operations.
+ * fast Fourier transform instead, about 2.5 K log2 K operations; that of a constant-Q plan, the contraction with its streaming
+ * bank or the folded one, also where the call takes the kernels by hop-blocks or tap by tap on the bfloat16 matrix pipe instead.
  */
 nna_status nna_plan_info(const nna_plan* plan, int* kind, long long* bank_rows, long long* taps,
                          long long* out_bins, double* executed_flops_per_frame,
