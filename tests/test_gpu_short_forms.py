@@ -96,3 +96,34 @@ def test_samples_that_are_not_finite(case, step, bad):
                 assert (np.abs(got[k][:, t] - w) <= 2e-5 * size + 2.0 * np.abs(clean).max()).all(), (k, t)
             elif (np.abs(re[k][s + hit]) > 1e-4 * np.abs(re[k]).max()).any():
                 assert not np.isfinite(got[k][0, t]), (k, t)
+
+
+BESIDE = [
+    # sr, hop, fmin, n_bins, bins per octave, taps, B, L, frames and blocks of the kernels beside a basis, form of their tiles
+    (22050, 512, 65.4, 84, 12, 0, 2, 100001, (64, 1), (4, 64, 128, 512)),
+    (44100, 512, 65.4, 120, 24, 0, 260, 100000, (64, 1), (4, 64, 128, 512)),
+    (16000, 96, 50.0, 60, 12, 6144, 3, 9003, (64, 1), (4, 64, 32, 96)),
+    (22050, 512, 65.4, 84, 12, 131072, 1, 70001, (64, 1), (-1, 0, 0, 0)),   # kernels of more than 65,536 taps with their padding: none of these
+    (8000, 64, 80.0, 60, 12, 0, 170, 9001, (128, 2), (-1, 0, 0, 0)),        # 128 frames, hop 64: items of two blocks a wave
+]
+
+
+@pytest.mark.parametrize("case", BESIDE, ids=lambda c: f"{c[1]}-{c[3]}-{c[5]}-{c[6]}x{c[7]}")
+def test_beside_a_basis(case):
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] short forms beside a basis {case}", file=sys.stderr, flush=True)
+    sr, hop, fmin, n_bins, bpo, taps, B, L, direct, tiles = case
+    cfg = dict(sr=sr, hop=hop, fmin=fmin, n_bins=n_bins, bins_per_octave=bpo, n_taps=taps)
+    plan = nb.nna_plan_cqt(fmt=nb.NNA_OUT_COMPLEX, device=0, **cfg)
+    assert nb.nna_plan_applied_tiles(plan, B, L)[1] == direct and nb.nna_plan_short_tiles(plan, B, L) == tiles
+    x = (0.3 * np.random.default_rng([89, B, L]).standard_normal((B, L))).astype(np.float32)
+    rows, T = nb.nna_out_shape(plan, B, L)
+    out = torch.full((B, rows, T), float("nan"), device="cuda")
+    got = nb.nna_cqt(plan, torch.from_numpy(x).cuda(), out=out)
+    assert bool(torch.isfinite(got).all())
+    some = sorted({0, B // 2, B - 1})
+    want = oracle.interleave(*oracle.cqt_complex(x[some], **cfg))
+    got = got[some].cpu().numpy().astype(np.float64)
+    for b in range(len(some)):
+        assert np.abs(got[b] - want[b]).max() < TOL * np.abs(want[b]).max(), some[b]
