@@ -407,8 +407,9 @@ hipError_t launch_split_forward(StftParams P, int mode, const float* wrm, int kp
   if (mode == ST_MODE_GRAD && P.fmt != NNA_OUT_POWER) return hipErrorInvalidValue;
   auto run = [&](auto kernel, long long n) { hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(256), 0, stream, P, wrm, kp, K); };
   // Few tiles: half the rows each.  A whole step, n_fft 2,048, 48 tiles: 340 -> 311 us; n_fft 400, 96: 146 -> 137; Mel, n_fft 1,024, 120: 282 ->
-  // 267; n_fft 4,096, 128: 811 -> 796; n_fft 2,048, 176: 345 -> 354, 496: 830 -> 857.
-  const bool half = P.n_ft * P.n_rt < 160;
+  // 267; n_fft 4,096, 128: 811 -> 796; n_fft 2,048, 176: 345 -> 354, 496: 830 -> 857.  The row tiles of a frame tile share an XCD, which holds 64
+  // workgroups: no more than that of them (n_fft 8,192, one and two frame tiles: 914 -> 1,046, 1,142 -> 1,266).
+  const bool half = P.n_ft * P.n_rt < 160 && 2 * ((P.n_ft + 7) / 8) * P.n_rt <= 64;
   if (mode == ST_MODE_GRAD) run(split_forward_kernel<ST_MODE_GRAD, 4>, blocks);
   else if (mode == ST_MODE_CPLX) half ? run(split_forward_kernel<ST_MODE_CPLX, 2>, 2 * blocks) : run(split_forward_kernel<ST_MODE_CPLX, 4>, blocks);
   else half ? run(split_forward_kernel<ST_MODE_STFT, 2>, 2 * blocks) : run(split_forward_kernel<ST_MODE_STFT, 4>, blocks);
@@ -433,7 +434,7 @@ hipError_t launch_split_wave(BwParams p, hipStream_t stream) {
   // unit.  A whole step, n_fft 2,048, 176 tiles: 449 us whole, 427 halved, 456 in three (every piece adds onto the waveform by
   // itself); 48 tiles 311, 298, 290, 287 in four; 352 tiles the same either way; 496 tiles 830, 840; n_fft 512, sixteen chunks, 376 tiles: 249, 270.
   const long long tiles = p.gpitch / BW_MT * (p.kp / BW_NT), chunks = (2 * p.n_half + SP_KC - 1) / SP_KC;
-  const long long split = tiles > 0 && tiles < 256 && chunks >= 32 ? std::max(2LL, std::min((256 + tiles - 1) / tiles, chunks / 16)) : 1;
+  const long long split = tiles > 0 && tiles < 256 && chunks >= 32 ? std::min((256 + tiles - 1) / tiles, chunks / 16) : 1;
   p.chunks_per_split = std::max(1LL, (chunks + split - 1) / split);
   const long long blocks = tiles * ((chunks + p.chunks_per_split - 1) / p.chunks_per_split);
   if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
