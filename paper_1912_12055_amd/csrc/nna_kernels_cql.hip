@@ -661,7 +661,7 @@ __global__ __launch_bounds__(256, 2) void cqt_lowrank_kernel(const CqlParams P) 
       const long long local = bid >> 3, tile = local / P.shorts.n_items, ft = (bid & 7) * ((P.shorts.n_ft + 7) >> 3) + tile;
       if (ft >= P.shorts.n_ft) return;
       const ShortItem item = P.shorts.items[local - tile * P.shorts.n_items];
-      short_tile<FD, 4, COLUMNS>(P.shorts, item, ft, reinterpret_cast<unsigned short*>(Y));
+      short_tile<FD, 4, COLUMNS, 0>(P.shorts, item, ft, reinterpret_cast<unsigned short*>(Y));
     } else {
       const int id = (int)(bid / P.direct.n_ft);
       const CqlItem item = P.direct.items[id];

@@ -13,7 +13,7 @@ __global__ __launch_bounds__(256, LAYOUT != COLUMNS ? 3 : WK == 1 ? 4 : 2) void 
   const long long ft = (blockIdx.x & 7) * per_xcd + tile;
   if (tile >= per_xcd || ft >= P.n_ft) return;
   const ShortItem item = P.items[local - tile * n_items];
-  short_tile<FB, WK, LAYOUT>(P, item, ft, S);
+  short_tile<FB, WK, LAYOUT, SHORT_SCALE>(P, item, ft, S);
 }
 
 template <int FB, int WK, int LAYOUT>
