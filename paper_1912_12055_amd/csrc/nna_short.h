@@ -18,7 +18,7 @@
 //   basis of nna_kernels_cql.hip.
 //
 // Bound by the matrix pipe and the splits in turn while hops are short (hop 64: pipe 58 % busy, vector ALUs 62 %, three workgroups per CU),
-// by latency where a tile is read column by column (hop 512: 29 %, 51 %).  1,770 x 345 frames, 24 bins of up to 742 taps
+// by latency where a tile is read column by column (hop 512: 26 %, 48 %).  1,770 x 345 frames, 24 bins of up to 742 taps
 // (MI355X), hop 512 down to 8, against cqt_kernel's float32 instruction:
 //   683, 494, 484, 359, 312, 292, 325 us -> 398, 306, 267, 196, 193, 183, 177;
 // 16 x 431 frames, 12 bins: 30, 29, 23, 17, 15, 14, 14 -> 10, 9, 10, 8, 9, 9, 9.  (hop 512 and 256 with the samples read straight into
@@ -103,8 +103,9 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
   };
   // a unit's parts; `v` may change
   auto planes = [&](f32x4 (&v)[2]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) v[h] *= (float)(1 << SCALE);
+    v[0] *= (float)(1 << SCALE);
+    if constexpr (LAYOUT != QUADS_OF) v[1] *= (float)(1 << SCALE);
+    else v[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
     Planes b = split8(v);
     u16x2 top = {0, 0};
 #pragma unroll
