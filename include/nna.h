@@ -515,8 +515,9 @@ nna_status nna_plan_bank(const nna_plan* plan, double* host_out, size_t cap);
 nna_status nna_plan_applied_kernels(const nna_plan* plan, double* host_out, size_t cap, long long* rows);
 /*
  * ... and how a call on B waveforms of L samples cuts them up: frames per workgroup (frames[0], frames[1]) and 16-frame blocks per
- * wave (blocks[0], blocks[1]: 1, 2 or 4) of the bins taken as combinations of a basis (0) and tap by tap beside them (1); zero
- * where there are none, all zero where the call runs another kernel.
+ * wave (blocks[0], blocks[1]: 1, 2 or 4) of the bins taken as combinations of a basis (0) and tap by tap beside them (1; 64 frames and one
+ * block also where the tiles are those that nna_plan_short_tiles names); zero where there are none, all zero where the call runs another
+ * kernel.
  */
 nna_status nna_plan_applied_tiles(const nna_plan* plan, long long B, long long L, int* frames, int* blocks);
 /*

@@ -352,7 +352,7 @@ struct CqlParams {
   float* out;
   long long out_wave_stride;
   CqlPart basis, direct;  // the items with a basis; those whose kernels stay as they are
-  ShortParams shorts;     // ... or, of waveforms of many frames, tiles of nna_short.h in their place
+  ShortParams shorts;     // ... or, hops of whole 128 columns and batches whose tiles hold 64 frames, tiles of nna_short.h in their place
   int fmt;
   int lds_floats;
 };

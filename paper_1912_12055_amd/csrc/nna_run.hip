@@ -493,6 +493,7 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
 // 16 frames that take more than 80 KB leave a CU one workgroup: up to 1,024 tiles, or where columns cannot be (25,000 frames of 1,024 samples: 67 us,
 // 64 by columns 53; 11,800 of two items of 800: 33, 53).  Against cqt_kernel they take, hops 1,000 to 1,500, 60,000 frames and more: kernels of 1.05
 // hops 0.9 .. 1.6 of its time, 1.6 hops 0.95 .. 1.1, 2.5 hops 0.8; two items 1.6 hops 1.1 .. 1.3, 2 hops 1.06, 2.5 hops 1.02, 3.5 hops 0.83.
+// Hops that are no multiple of 32, 60,000 frames of 36 bins of up to 4,360 taps: hop 80, 32 frames 228 us, hop 240, 16 frames 423, cqt_kernel 757, 799.
 // A tile that holds less than three quarters of its frames is left to the next one.  False: not a launch for this kernel.
 bool shape_short(const nna_plan* sub, long long n_frames, long long T, nna::ShortParams& P) {
   auto fit = [&](int form, size_t lds) { return fit_short(sub, n_frames, T, form, lds, P); };

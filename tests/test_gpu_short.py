@@ -1,6 +1,6 @@
 """Constant-Q kernels tap by tap on the bfloat16 matrix pipe: the octaves of the downsampling plans, one by one against the oracle.  Hops
-of 4 (words of four samples in LDS), of 8 and more, of whole 32 columns; batches that reach tiles of 16, 32, 64 and 128 frames; tiles
-that span waveforms, one and several items, ends inside a run of four samples; samples that are not finite, few and many."""
+of 4 (words of four samples in LDS), of 8 and more, of whole 32 columns; batches that reach tiles of 16, 32, 64 and 128 frames
+(tests/test_gpu_short_forms.py names the tiles of its cases); tiles that span waveforms, one and several items, ends inside a run of four samples; samples that are not finite, few and many."""
 import sys
 
 import numpy as np
@@ -15,14 +15,14 @@ TOL = 1e-6
 CASES = [
     # sr, hop of octave 0, fmin, n_bins, bins per octave, octave, B, L
     (8000, 8, 400.0, 24, 12, 1, 3, 2001),         # hop 4, 16 frames a tile
-    (8000, 8, 400.0, 24, 12, 1, 60, 1203),        # ... of 64, across waveforms
+    (8000, 8, 400.0, 24, 12, 1, 60, 1203),        # ... of 32, across waveforms
     (8000, 8, 400.0, 24, 12, 0, 9, 8005),         # hop 8, 32 frames
     (8000, 24, 400.0, 60, 30, 1, 7, 4003),        # hop 12, two items of a plan, the second of six bins
     (16000, 96, 500.0, 20, 12, 0, 40, 9001),      # a hop that is no power of two
     (22050, 64, 1000.0, 24, 24, 0, 300, 9002),    # hop 64, 64 frames
     (22050, 512, 1000.0, 12, 12, 0, 2, 30001),    # hop 512, 16 frames
     (22050, 256, 1500.0, 24, 24, 0, 1900, 9003),  # columns
-    (22050, 512, 700.0, 20, 12, 0, 900, 37001),   # columns, kernels of up to four hops in frames of two waveforms
+    (22050, 512, 700.0, 20, 12, 0, 900, 37001),   # columns, kernels of less than a hop
 ]
 
 
