@@ -38,7 +38,7 @@ typedef f32x4 f32x4_u __attribute__((aligned(4)));
 // octave's error, 2-norm of its worst bin, samples of 1e-34, 1e-36, 1e-38: 3.8e-7 .. 1.2e-6, 6e-7 .. 9e-6, 6e-5 .. 9e-4 with
 // cqt_kernel's float32 instruction, 1.1e-6, 1.0e-4, 1.1e-2 as they are, 0.9e-7 .. 1.8e-7, 1.4e-7 .. 2.6e-7, 1.0e-5 .. 1.8e-5.  (By 2^24, 3e-6 ..
 // 1.5e-5 at 1e-38, but samples above 2e31 would be none that bfloat16 holds.)  Octaves only: kernels beside a basis are as exact as those with
-// one either way, and 16 x 220,500 samples, 84 bins, take 41.0 us for 41.7.
+// one either way, and 16 x 220,500 samples, 84 bins, took 41.0 us for 41.7.
 constexpr int SHORT_SCALE = 10;
 // the first bfloat16 of 2^SCALE v is finite
 template <int SCALE>
@@ -110,7 +110,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
     u16x2 top = {0, 0};
 #pragma unroll
     for (int i = 0; i < 4; ++i) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, b.p[0][i] & 0x7fff7fffu));
-    if (__builtin_elementwise_max(top.x, top.y) >= 0x7f80) {
+    if (__builtin_expect(__builtin_elementwise_max(top.x, top.y) >= 0x7f80, 0)) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -313,7 +313,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
   auto finite_sums = [&](int fb, int rb, int u) { return finite(acc[fb][rb][2 * u]) && finite(acc[fb][rb][2 * u + 1]); };
   // `taken`: a bin whose taps meet a sample that is not finite, bit 2 (RB fb + rb) + u
   unsigned taken = 0;
-  if (*flag) {
+  if (__builtin_expect(*flag, 0)) {  // (out of the way of the others' instructions: 41.05 -> 40.55 us of 16 x 220,500 samples, 84 bins)
     // the tile's samples in units of four, row by row
     const int per_row = width / 4, units = rows_used * per_row;
     auto unit = [&](int u) {
@@ -457,7 +457,7 @@ __device__ __forceinline__ void short_tile(const ShortParams& P, const ShortItem
   // Sums that are not finite though all their samples are: the bfloat16 of samples next to the largest float32 overflow together.  Tap by tap.
   odd &= ~taken;
 #pragma unroll 1
-  while (odd) {
+  while (__builtin_expect(odd, 0)) {
     const int bit = __builtin_ctz(odd), k = 8 * ((bit >> 1) % RB) + 2 * q + (bit & 1), fi = (wave * EB + (bit >> 1) / RB) * 16 + n;
     odd &= odd - 1;
     const long long f = f0 + fi, b = f / g.T;
