@@ -16,15 +16,20 @@
 // output the call below takes 0.82 ms, the vector ALUs' time; meeting once a tile and the stores' own instructions add the rest.
 //
 // 1,770 x 176,400 samples, N = 2,048, hop 512 (MI355X): magnitudes 10.1 ms contracted, 2.20 with a tile computed, then stored
-// between two barriers and neighbouring tiles 29 us apart, now 1.51 (either way 3.66 GB are written for 2.50: runs of half a line);
-// N = 1,024, hop 256, complex: 4.02 -> 2.35.  Mel, 64 x 110,250, 128 bands: 808 us contracted, 48 -> 39; 1,770 x 80,000,
-// N = 4,096, 512 bands: 34.9 ms, 2.02 -> 1.74.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles read from the caches for
+// between two barriers and neighbouring tiles 29 us apart, 1.51 with samples requested word by word, now 1.35 (either way 3.66 GB are written for
+// 2.50: runs of half a line; writing them so, with nothing computed, takes 1.38 by itself, in runs that begin at 64 bytes 0.83);
+// N = 1,024, hop 256, complex: 4.02 -> 2.35.  Mel, 64 x 110,250, 128 bands: 808 us contracted, 48 -> 39 -> 38; 1,770 x 80,000,
+// N = 4,096, 512 bands: 34.9 ms, 2.02 -> 1.72 -> 1.58.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles read from the caches for
 // every frame with four waves per SIMD (2.85 ms: the vector memory path saturates), from LDS with four waves per SIMD (spills,
-// 1.87 ms), three waves per SIMD (spills, 4.3 ms), the tile stored by two workgroups of four waves (runs of 32 bytes, 2.04 ms).
+// 1.87 ms), three waves per SIMD (spills, 4.3 ms), the tile stored by two workgroups of four waves (runs of 32 bytes, 2.04 ms),
+// frames in a ring from which every row is written in segments that begin at 64 bytes (2.7 GB written, but waves that meet every step: 1.47 ms).
 #include "nna_device.h"
 
 namespace nna {
 namespace {
+
+// two samples at any word
+typedef float f32x2_u __attribute__((ext_vector_type(2), aligned(4)));
 
 __device__ __forceinline__ void wave_fence() {
   // orders the LDS accesses of one wave for the compiler; the hardware keeps them in order by itself
@@ -415,19 +420,21 @@ __global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
     for (int r = 1; r < R2; ++r) tm[r] = tw[(lt % R1) * r * (2 * M / (R1 * R2))];
   }
 
-  cplx z[V];  // samples of the frame that comes next
+  f32x2_u z[V];  // samples of the frame that comes next
   auto load_next = [&](int advance) {  // `advance`: frames to the one after it
     const bool past = b >= P.g.B;  // behind the last frame: that frame again, never written
     const int i0 = (past ? T - 1 : t) * P.g.hop - P.g.pad;
     const float* __restrict__ xb = P.g.x + (past ? P.g.B - 1 : b) * P.g.L;
-    if (__all(i0 >= 0 && i0 + 2 * M <= L)) {
+    // Pairs as vectors: as two floats each, the compiler joined both ways of this branch to 32 words requested one by one at 32 addresses
+    // computed ahead (1,770 x 176,400 samples 1.51 -> 1.35 ms, N = 1,024 complex 300 x 176,400 428 -> 369 us, N = 4,096 Mel 1.72 -> 1.58 ms).
+    if (__builtin_amdgcn_ballot_w64(i0 < 0 || i0 + 2 * M > L) == 0) {
 #pragma unroll
-      for (int i = 0; i < V; ++i) __builtin_memcpy(&z[i], xb + i0 + 2 * (lt + TPF * (i / R1) + (M / R1) * (i % R1)), 8);
+      for (int i = 0; i < V; ++i) z[i] = *reinterpret_cast<const f32x2_u*>(xb + i0 + 2 * (lt + TPF * (i / R1) + (M / R1) * (i % R1)));
     } else {
 #pragma unroll
       for (int i = 0; i < V; ++i) {
         const int m = i0 + 2 * (lt + TPF * (i / R1) + (M / R1) * (i % R1));
-        z[i] = {xb[reflect(m, L)], xb[reflect(m + 1, L)]};
+        z[i] = (f32x2_u){xb[reflect(m, L)], xb[reflect(m + 1, L)]};
       }
     }
     t += advance;
@@ -601,7 +608,7 @@ __global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
       // the next frame's samples, requested at the start of this step, are waited for here: behind the stores below the wait would
       // be for those too
 #pragma unroll
-      for (int i = 0; i < V; ++i) asm volatile("" : "+v"(z[i].x), "+v"(z[i].y));
+      for (int i = 0; i < V; ++i) asm volatile("" : "+v"(z[i]));
       if (p_left > 0 && it < parts) {
         if (FLAGS && it == 0) wait(computed, n_done);
         emit(old, it);
