@@ -271,6 +271,13 @@ nna_status nna_mel_with_stft(const nna_plan* plan, const float* x_dev, long long
 nna_status nna_cqt(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,
                    void* hip_stream);
 
+/* nna_cqt or nna_cqt1992, by the plan's kind, with device memory of the caller's in which the hop-blocks' coordinates are kept from a first
+ * launch to a second: the same outputs, sooner.  nna_cqt_workspace: the bytes a call can use (at most 256 MiB; 0: it does as well without).
+ * Less is used as far as it goes; a workspace that is NULL or not aligned to 16 bytes is not.  A workspace serves one call at a time. */
+nna_status nna_cqt_workspace(const nna_plan* plan, long long B, long long L, size_t* bytes);
+nna_status nna_cqt_in_workspace(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev, void* workspace_dev,
+                                size_t workspace_bytes, void* hip_stream);
+
 /* out_dev[B, n_bins, T] = constant-Q spectrogram of x_dev[B, L]; plan from nna_plan_cqt1992.
  * The STFT itself is never written to memory.  Fixed kernels run as nna_cqt's, with the same range. */
 nna_status nna_cqt1992(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev,

@@ -37,6 +37,7 @@ EXPORTS = [
     "nna_cqt2010_backward_workspace", "nna_cqt2010_backward", "nna_kept_bytes", "nna_forward_keep", "nna_backward_kept", "nna_plan_applied_kernels", "nna_plan_applied_tiles", "nna_plan_short_tiles",
     "nna_plan_destroy",
     "nna_status_str", "nna_last_error",
+    "nna_cqt_workspace", "nna_cqt_in_workspace",
 ]
 
 _c = ctypes
@@ -84,6 +85,8 @@ def lib():
                                        _c.c_int, _c.c_int, _c.c_int]
         L.nna_plan_spectral_kernels.argtypes = [_VP, _c.POINTER(_c.c_double), _c.c_size_t]
         L.nna_cqt2010v2_workspace.argtypes = [_VP, _LL, _LL, _c.POINTER(_c.c_size_t)]
+        L.nna_cqt_workspace.argtypes = [_VP, _LL, _LL, _c.POINTER(_c.c_size_t)]
+        L.nna_cqt_in_workspace.argtypes = [_VP, _VP, _LL, _LL, _VP, _VP, _c.c_size_t, _VP]
         L.nna_cqt2010v2.argtypes = [_VP, _VP, _LL, _LL, _VP, _VP, _c.c_size_t, _VP]
         L.nna_cqt2010.argtypes = [_VP, _VP, _LL, _LL, _VP, _VP, _c.c_size_t, _VP]
         L.nna_plan_cqt2010.argtypes = [PP, _c.c_int, _c.c_int, _c.c_double, _c.c_int, _c.c_int, _c.c_int, _c.c_int,
@@ -411,14 +414,54 @@ def nna_mel_with_stft(plan: Plan, x, out=None, spec=None, stream=None):
     return mel, holder["spec"]
 
 
+def nna_cqt_workspace(plan: Plan, B: int, L: int) -> int:
+    n = _c.c_size_t()
+    _check(lib().nna_cqt_workspace(plan.handle, B, L, _c.byref(n)))
+    return n.value
+
+
+def nna_cqt_in_workspace(plan: Plan, x, workspace, out=None, stream=None):
+    """nna_cqt or nna_cqt1992, by the plan's kind, in a CUDA tensor of the caller's."""
+    if not (workspace.is_cuda and workspace.is_contiguous() and workspace.device == x.device):
+        raise TypeError("workspace must be a contiguous CUDA tensor on x's device")
+    ws_bytes = workspace.numel() * workspace.element_size()
+
+    def fn(handle, xp, B, L, op, st):
+        return lib().nna_cqt_in_workspace(handle, xp, B, L, op, workspace.data_ptr(), ws_bytes, st)
+
+    return _run(fn, plan, x, out, stream)
+
+
+def _run_one_rate(cfn, plan, x, out, stream):
+    """`cfn`, in a workspace where that is the faster way: memory of the stream the call runs on, back with its allocator
+    when the call returns."""
+    import torch
+
+    def fn(handle, xp, B, L, op, st):
+        need = nna_cqt_workspace(plan, B, L)
+        if not need:
+            return cfn(handle, xp, B, L, op, st)
+        try:
+            if stream is None:
+                workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+            else:
+                with torch.cuda.stream(torch.cuda.ExternalStream(st, device=x.device)):
+                    workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+        except torch.OutOfMemoryError:
+            return cfn(handle, xp, B, L, op, st)
+        return lib().nna_cqt_in_workspace(handle, xp, B, L, op, workspace.data_ptr(), need, st)
+
+    return _run(fn, plan, x, out, stream)
+
+
 def nna_cqt1992(plan: Plan, x, out=None, stream=None):
     """out[B, n_bins, T] = constant-Q spectrogram of x[B, L] with frequency-domain kernels."""
-    return _run(lib().nna_cqt1992, plan, x, out, stream)
+    return _run_one_rate(lib().nna_cqt1992, plan, x, out, stream)
 
 
 def nna_cqt(plan: Plan, x, out=None, stream=None):
     """out[B, n_bins, T] = constant-Q spectrogram of x[B, L]."""
-    return _run(lib().nna_cqt, plan, x, out, stream)
+    return _run_one_rate(lib().nna_cqt, plan, x, out, stream)
 
 
 # ---- trainable Fourier kernels -------------------------------------------------------------------

@@ -1139,6 +1139,13 @@ void build_cqt_bank_lowrank(nna_plan* p, const CqtKernelSource& kernels) {
     return it.r ? 1e12 + 16.0 * it.n_ib * hop + 256.0 * (it.n_step + it.s_hi - it.s_lo) : (double)it.n_step;
   };
   std::stable_sort(p->h_litems.begin(), p->h_litems.end(), [&](const nna::CqlItem& a, const nna::CqlItem& b) { return weight(a) > weight(b); });
+  int y_r = 0, y_rj = 0;
+  for (nna::CqlItem& it : p->h_litems) {
+    it.y_r = y_r;
+    it.y_rj = y_rj;
+    y_r += it.r;
+    y_rj += it.r * (it.jspan - 1);
+  }
   for (int k = 0; k < p->n_bins; ++k)
     for (const long long tap : {p->row_s[2 * k], p->row_e[2 * k]}) p->h_lsupport.push_back((int)tap);
   p->lowrank = true;

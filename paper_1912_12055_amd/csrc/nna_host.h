@@ -472,7 +472,8 @@ inline void octave_bins(int n_bins, int bpo, int a, int& lo, int& hi) {
 nna_status run_stft_core(const nna_plan* plan, int kind, const float* x, long long B, long long L, long long T, float* out,
                          long long out_wave_stride, int row_offset, void* stream, float* spec_out = nullptr, float* keep = nullptr);
 nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out, long long out_wave_stride,
-                    int row_offset, void* hip_stream, bool may_fold = false, float* keep = nullptr);
+                    int row_offset, void* hip_stream, bool may_fold = false, float* keep = nullptr, void* workspace = nullptr,
+                    size_t workspace_bytes = 0);
 // tiles of a launch of nna_kernels_cql.hip; false: not a launch for it
 bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::CqlParams& P);
 bool shape_short(const nna_plan* sub, long long n_frames, long long T, nna::ShortParams& P);

@@ -332,6 +332,7 @@ struct CqlItem {
   int n_step;
   int bin0, n_bins;  // first bin, bins (1 .. 16; r = 0: 1 .. 32)
   int n_lo;          // 4 or 8
+  int y_r, y_rj;     // sums of r and of r (jspan - 1) over the items with a basis before this one
 };
 
 struct CqlPart {
@@ -355,7 +356,15 @@ struct CqlParams {
   ShortParams shorts;     // ... or, hops of whole 128 columns and batches whose tiles hold 64 frames, tiles of nna_short.h in their place
   int fmt;
   int lds_floats;
+  // The coordinates in memory, or NULL: of every waveform, item by item, the hop-blocks its frames reach, r floats each
+  float* y;
+  long long y_wave;      // floats of a waveform
+  int y_j0, y_rows;      // the first hop-block some item reaches, and how many of them a waveform has
+  int y_nb, y_groups;    // 16-hop-block parts of a tile, and parts the row blocks of all bases are dealt to
+  int y_blocks;          // those row blocks
+  int shared;            // tiles of 64 frames whose waves share the steps of stage 2: LDS word of their sums (24 KB), else 0
 };
+hipError_t launch_cqt_project(const CqlParams& p, hipStream_t stream);
 hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream);
 hipError_t cql_kernels_init();  // per-process function attributes of nna_kernels_cql.hip
 

@@ -264,8 +264,10 @@ __device__ __forceinline__ void direct_item(const CqlParams& P, const CqlPart& p
   }
 }
 
-// Kernels as combinations of the item's basis.
-template <int FB>
+// Kernels as combinations of the item's basis.  READY: the coordinates are in memory.  SHARED (tiles of 64 frames): the waves share the steps
+// of stage 2, each of them for all frames, and their sums are added through LDS at P.shared: every wave reading all weights for 16 frames
+// waits for them (16 x 220,500 samples, 84 dense kernels: stage 2 67 -> 50 us).
+template <int FB, bool READY, bool SHARED>
 __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& part, const CqlItem& item, long long ft, float* Y) {
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -285,7 +287,7 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
   // Where the launch's LDS, sized for its largest item at four bytes a coordinate, has room for six, they are kept as the three bfloat16
   // stage 2 multiplies, split once instead of once per hop-block that reads them; planes of p_words values.
   const int p_words = rows_used * r + 32;
-  const bool split = 6 * p_words <= 4 * P.lds_floats;
+  const bool split = 6 * p_words <= 4 * (SHARED ? P.shared : P.lds_floats);
   unsigned short* const Yb = reinterpret_cast<unsigned short*>(Y);
   const int L = (int)g.L, hop = g.hop;
   // acc[p][i] += 16 rows of weights (i) x 16 runs of samples (p) over columns [c_begin, c_end), 32 at a time.  A lane's run starts
@@ -382,12 +384,6 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
 #pragma unroll
   for (int fb = 0; fb < FB; ++fb) valid[fb] = wave * (16 * FB) + fb * 16 + n < m_valid;
   f32x4 acc[FB][RB];
-  auto clear = [&] {
-#pragma unroll
-    for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-      for (int b = 0; b < RB; ++b) acc[fb][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  };
   // ---- stage 1: the hop-blocks' coordinates -------------------------------------------
   // NB x IB tiles of 16 hop-blocks x 16 basis functions
   auto sweep = [&](auto edge_tag, auto nb_tag, auto ib_tag, int blk0, int ib0) {
@@ -440,7 +436,37 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       }
     }
   };
-  {
+  if constexpr (READY) {
+    // waveform by waveform, the tile's hop-blocks one behind the other as they lie in LDS
+    const int quads = r / 4;
+    for (int row0 = 0; row0 < rows_used;) {
+      long long b;
+      int sigma;
+      tm.decode(row0, b, sigma);
+      const int rows = row0 == 0 ? tm.n0 + tm.extra : tm.T + tm.extra, n_quad = (rows < rows_used - row0 ? rows : rows_used - row0) * quads;
+      const f32x4* __restrict__ src = reinterpret_cast<const f32x4*>(P.y + b * P.y_wave + (long long)item.y_r * g.T + item.y_rj) + (long long)sigma * quads;
+      constexpr int U = 8;
+      for (int i0 = tid; i0 < n_quad; i0 += 256 * U) {
+        f32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = src[i0 + 256 * u < n_quad ? i0 + 256 * u : n_quad - 1];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (i0 + 256 * u >= n_quad) break;
+          const int at = row0 * r + 4 * (i0 + 256 * u);
+          if (!split) {
+            *reinterpret_cast<f32x4*>(Y + at) = v[u];
+          } else {
+            const f32x4 both[2] = {v[u], v[u]};
+            const Planes q3 = split8(both);
+#pragma unroll
+            for (int l = 0; l < 3; ++l) *reinterpret_cast<uint2*>(Yb + l * p_words + at) = make_uint2(q3.p[l][0], q3.p[l][1]);
+          }
+        }
+      }
+      row0 += rows;
+    }
+  } else {
     // The waves share the (passes over the basis) x (blocks of 16 hop-blocks) evenly, a wave's share in runs of one pass.
     const int nblk = (rows_used + 15) >> 4, n_pass = (item.n_ib + 2) / 3, units = nblk * n_pass;
     const int first = units * wave >> 2, last = units * (wave + 1) >> 2;
@@ -473,35 +499,44 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
       else with_nb(False{});
       u += nb;
     }
-    // the last step of the last frame reads up to 31 words (times zero) past its hop-blocks
-    if (tid < 32) {
-      if (!split) Y[rows_used * r + tid] = 0.f;
-      else
-        for (int l = 0; l < 3; ++l) Yb[l * p_words + rows_used * r + tid] = 0;
-    }
+  }
+  // the last step of the last frame reads up to 31 words (times zero) past its hop-blocks
+  if (tid < 32) {
+    if (!split) Y[rows_used * r + tid] = 0.f;
+    else
+      for (int l = 0; l < 3; ++l) Yb[l * p_words + rows_used * r + tid] = 0;
   }
   __syncthreads();
 
   // ---- stage 2: the frames' combinations ----------------------------------------------
-  clear();
-  int y_off[FB];
+  static_assert(!SHARED || FB == 1, "a wave ends up with a block of sixteen frames");
+  constexpr int MB = SHARED ? 4 : FB;  // frame blocks a wave multiplies
+  f32x4 sum[MB][RB];
+  int y_off[MB];
 #pragma unroll
-  for (int fb = 0; fb < FB; ++fb) y_off[fb] = (valid[fb] ? tm.frame_row(wave * (16 * FB) + fb * 16 + n) : 0) * r + 4 * q;
+  for (int fb = 0; fb < MB; ++fb) {
+    const int fi = SHARED ? fb * 16 + n : wave * (16 * FB) + fb * 16 + n;
+    y_off[fb] = (fi < m_valid ? tm.frame_row(fi) : 0) * r + 4 * q;
+#pragma unroll
+    for (int b = 0; b < RB; ++b) sum[fb][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
   const uint4* a0p = P.ab + item.a0[0] / 2 * 3 + lane;
   const uint4* a1p = P.ab + item.a0[1] / 2 * 3 - (long long)(item.s_lo / 2) * 192 + lane;
   // steps [s, e) of 32: both row blocks, or the first alone
   auto steps = [&](auto both_tag, auto split_tag, int s, int e) {
     constexpr bool BOTH = decltype(both_tag)::value, SPLIT = decltype(split_tag)::value;
     constexpr int YV = SPLIT ? 3 : 2;  // 16-byte words a step of a frame block takes from LDS
+    if constexpr (SHARED) s += wave;
     if (s >= e) return;
-    auto fetch = [&](int i, u32x4 (&c0)[3], u32x4 (&c1)[3], u32x4 (&y)[FB][YV]) {
+    constexpr int BY = SHARED ? 4 : 1;
+    auto fetch = [&](int i, u32x4 (&c0)[3], u32x4 (&c1)[3], u32x4 (&y)[MB][YV]) {
 #pragma unroll
       for (int l = 0; l < 3; ++l) {
         c0[l] = *reinterpret_cast<const u32x4*>(a0p + ((long long)i * 3 + l) * 64);
         if constexpr (BOTH) c1[l] = *reinterpret_cast<const u32x4*>(a1p + ((long long)i * 3 + l) * 64);
       }
 #pragma unroll
-      for (int fb = 0; fb < FB; ++fb)
+      for (int fb = 0; fb < MB; ++fb)
 #pragma unroll
         for (int h = 0; h < YV; ++h) {
           if constexpr (SPLIT) {
@@ -513,9 +548,9 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
           }
         }
     };
-    auto multiply = [&](const u32x4 (&c0)[3], const u32x4 (&c1)[3], const u32x4 (&y)[FB][YV]) {
+    auto multiply = [&](const u32x4 (&c0)[3], const u32x4 (&c1)[3], const u32x4 (&y)[MB][YV]) {
 #pragma unroll
-      for (int fb = 0; fb < FB; ++fb) {
+      for (int fb = 0; fb < MB; ++fb) {
         Planes b;
         if constexpr (SPLIT) {
 #pragma unroll
@@ -524,23 +559,23 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
           const f32x4 v[2] = {__builtin_bit_cast(f32x4, y[fb][0]), __builtin_bit_cast(f32x4, y[fb][1])};
           b = split8(v);
         }
-        acc[fb][0] += multiply_octets(c0, b, (f32x4){0.f, 0.f, 0.f, 0.f});
-        if constexpr (BOTH) acc[fb][1] += multiply_octets(c1, b, (f32x4){0.f, 0.f, 0.f, 0.f});
+        sum[fb][0] += multiply_octets(c0, b, (f32x4){0.f, 0.f, 0.f, 0.f});
+        if constexpr (BOTH) sum[fb][1] += multiply_octets(c1, b, (f32x4){0.f, 0.f, 0.f, 0.f});
       }
     };
     // register sets of coefficients and frames, requested up to three steps ahead
-    constexpr int SETS = FB == 1 ? 4 : 2;
+    constexpr int SETS = MB == 1 ? 4 : 2;
     u32x4 c0[SETS][3], c1[SETS][3];
-    u32x4 y[SETS][FB][YV];
+    u32x4 y[SETS][MB][YV];
 #pragma unroll
-    for (int u = 0; u < SETS - 1; ++u) fetch(s + u < e ? s + u : e - 1, c0[u], c1[u], y[u]);
-    for (int i = s; i < e; i += SETS) {
+    for (int u = 0; u < SETS - 1; ++u) fetch(s + BY * u < e ? s + BY * u : s, c0[u], c1[u], y[u]);
+    for (int i = s; i < e; i += BY * SETS) {
 #pragma unroll
       for (int u = 0; u < SETS; ++u) {
-        const int ahead = i + u + SETS - 1, at = (u + SETS - 1) % SETS;
-        fetch(ahead < e ? ahead : e - 1, c0[at], c1[at], y[at]);
+        const int ahead = i + BY * (u + SETS - 1), at = (u + SETS - 1) % SETS;
+        fetch(ahead < e ? ahead : s, c0[at], c1[at], y[at]);
         __builtin_amdgcn_sched_barrier(0);
-        if (i + u < e) multiply(c0[u], c1[u], y[u]);
+        if (i + BY * u < e) multiply(c0[u], c1[u], y[u]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -554,6 +589,31 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
   };
   if (split) all_steps(True{});
   else all_steps(False{});
+  if constexpr (SHARED) {
+    // wave k takes frame block k: the other waves' sums in their order, then its own
+    f32x4* const part = reinterpret_cast<f32x4*>(Y + P.shared) + lane;  // [frame block][three waves][row block][64 lanes]
+#pragma unroll
+    for (int fb = 0; fb < MB; ++fb) {
+      if (fb == wave) continue;
+#pragma unroll
+      for (int b = 0; b < RB; ++b) part[((fb * 3 + (wave < fb ? wave : wave - 1)) * RB + b) * 64] = sum[fb][b];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+      acc[0][b] = part[(wave * 3 * RB + b) * 64];
+      acc[0][b] += part[((wave * 3 + 1) * RB + b) * 64];
+      acc[0][b] += part[((wave * 3 + 2) * RB + b) * 64];
+#pragma unroll
+      for (int fb = 0; fb < MB; ++fb)
+        if (fb == wave) acc[0][b] += sum[fb][b];
+    }
+  } else {
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+      for (int b = 0; b < RB; ++b) acc[fb][b] = sum[fb][b];
+  }
   // A sample that is not finite reaches, through its hop-block's coordinates, bins and frames whose own taps it lies outside of, and
   // turns infinities into NaN.  So a sum that is not finite is taken again over the bin's own taps: those samples alone if there
   // are any, else hop-block by hop-block, the ones whose coordinates are not finite sample by sample.  (1,770 x 176,400 samples, a
@@ -645,23 +705,28 @@ __device__ __forceinline__ void lowrank_item(const CqlParams& P, const CqlPart& 
   }
 }
 
+// tile `bid` of the short kernels
+template <int FD>
+__device__ __forceinline__ void short_work(const CqlParams& P, long long bid, float* Y) {
+  const long long local = bid >> 3, tile = local / P.shorts.n_items, ft = (bid & 7) * ((P.shorts.n_ft + 7) >> 3) + tile;
+  if (ft >= P.shorts.n_ft) return;
+  const ShortItem item = P.shorts.items[local - tile * P.shorts.n_items];
+  short_tile<FD, 4, COLUMNS, 0>(P.shorts, item, ft, reinterpret_cast<unsigned short*>(Y));
+}
+
 // FB, FD: 16-frame blocks per wave of the items with a basis and of the direct ones.  The direct ones come first, the item the slow
 // index; tiles of nna_short.h in their place (SHORT) last, their items neighbours too: they are many and short, those with a basis
 // few and long in a short batch (tiles first: 65 us for 46 at 16 x 220,500).  The others: workgroup ids are dealt round-robin to the 8 XCDs, and the items of one tile are neighbours on one XCD,
 // where they meet the tile's samples in its L2 (28 million L2 misses instead of 263 million, 7.1 -> 6.5 ms at 1,770 x 176,400);
 // rotated by one from tile to tile, because items differ in length and the CUs are dealt out in a fixed order too.
-template <int FB, int FD, bool SHORT>
+template <int FB, int FD, bool SHORT, bool READY, bool SHARED>
 __global__ __launch_bounds__(256, 2) void cqt_lowrank_kernel(const CqlParams P) {
   extern __shared__ __attribute__((aligned(16))) float Y[];
   long long bid = blockIdx.x;
   const long long n_basis = (P.basis.n_ft + 7) / 8 * 8 * P.basis.n_items, n_direct = P.direct.n_ft * P.direct.n_items;
   if (SHORT ? bid >= n_basis : bid < n_direct) {
     if constexpr (SHORT) {
-      bid -= n_basis;
-      const long long local = bid >> 3, tile = local / P.shorts.n_items, ft = (bid & 7) * ((P.shorts.n_ft + 7) >> 3) + tile;
-      if (ft >= P.shorts.n_ft) return;
-      const ShortItem item = P.shorts.items[local - tile * P.shorts.n_items];
-      short_tile<FD, 4, COLUMNS, 0>(P.shorts, item, ft, reinterpret_cast<unsigned short*>(Y));
+      short_work<FD>(P, bid - n_basis, Y);
     } else {
       const int id = (int)(bid / P.direct.n_ft);
       const CqlItem item = P.direct.items[id];
@@ -674,38 +739,270 @@ __global__ __launch_bounds__(256, 2) void cqt_lowrank_kernel(const CqlParams P) 
     const long long ft = (bid & 7) * per_xcd + tile;
     if (ft >= P.basis.n_ft) return;
     const CqlItem item = P.basis.items[(local + tile) % n_items];
-    lowrank_item<FB>(P, P.basis, item, ft, Y);
+    lowrank_item<FB, READY, SHARED>(P, P.basis, item, ft, Y);
   }
 }
 
-template <int FB, int FD, bool SHORT = false>
+__device__ __host__ inline long long g_rows(const CqlParams& P) { return P.g.B * P.y_rows; }
+
+// Stage 1 by itself: every hop-block's coordinates of all items, once.  A workgroup takes 16 NB hop-blocks and a part of the bases' row
+// blocks; the samples are split once, on the way into LDS, 64 columns at a time, and each wave multiplies every fourth row block with all
+// of them, so that a workgroup reads its weights once.  The sums are those of lowrank_item, in the same order.  lowrank_item itself reads and
+// splits every sample for each 16 bins, and for every tile whose frames reach it: 2.2 ms of 5.5 at 1,770 x 176,400 samples, 168 bins; here 1.5 ms
+// (41 % of the matrix pipe's peak; weights from the L2s at 31 bytes a cycle and CU), the call 5.5 -> 4.87.  16 x 220,500, 84 dense kernels of
+// 16,384 taps: 137 -> 86 us, of which 33 here.
+constexpr int PJ_COLS = 64, PJ_PITCH = PJ_COLS + 8;  // (rows of 36 words: sixteen of them on different banks, four words each)
+constexpr int PJ_LDS(int nb) { return 2 * 3 * 16 * nb * PJ_PITCH * 2; }
+
+template <int NB, int IB, bool SHORT>
+__global__ __launch_bounds__(256, 2) void cqt_project_kernel(const CqlParams P) {
+  extern __shared__ __attribute__((aligned(16))) float Y[];
+  if constexpr (SHORT) {
+    const long long n_project = ((g_rows(P) + 16 * NB - 1) / (16 * NB) + 7) / 8 * 8 * P.y_groups;
+    if (blockIdx.x >= n_project) {
+      short_work<4>(P, blockIdx.x - n_project, Y);
+      return;
+    }
+  }
+  unsigned short* const S = reinterpret_cast<unsigned short*>(Y);
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int q = lane >> 4, n = lane & 15;
+  const FrameGeom& g = P.g;
+  const int L = (int)g.L, hop = g.hop;
+  constexpr int ROWS = 16 * NB, PLANE = ROWS * PJ_PITCH, UNITS = NB / 2;
+  // neighbouring tiles, and the parts of one, on one XCD, whose L2 they share
+  const long long n_rows = g_rows(P), n_tiles = (n_rows + ROWS - 1) / ROWS, per_xcd = (n_tiles + 7) >> 3;
+  const long long local = blockIdx.x >> 3, in_xcd = local / P.y_groups, tile = (blockIdx.x & 7) * per_xcd + in_xcd;
+  const int group = (int)(local - in_xcd * P.y_groups);
+  if (in_xcd >= per_xcd || tile >= n_tiles) return;
+  const long long row_first = tile * ROWS, b_first = row_first / P.y_rows;
+  const int s_first = (int)(row_first - b_first * P.y_rows);
+  auto decode = [&](int i, long long& b, int& s) {  // hop-block i of the tile; behind the last one: that one
+    if (row_first + i >= n_rows) i = (int)(n_rows - 1 - row_first);
+    const int u = s_first + i, w = u < P.y_rows ? 0 : u / P.y_rows;
+    b = b_first + w;
+    s = u - w * P.y_rows;
+  };
+  // this wave's row blocks: item, and block of its basis (behind the last: that one, not written)
+  const int blk0 = P.y_blocks * group / P.y_groups, blk1 = P.y_blocks * (group + 1) / P.y_groups;
+  int item_of[IB], ib_of[IB], stride[IB];
+  const uint4* up[IB];
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    int rb = blk0 + wave + 4 * i < blk1 ? blk0 + wave + 4 * i : blk1 - 1, it = 0;
+    while (rb >= P.basis.items[it].n_ib) rb -= P.basis.items[it++].n_ib;
+    item_of[i] = it;
+    ib_of[i] = rb;
+    stride[i] = P.basis.items[it].n_ib * 192;
+    up[i] = P.ub + P.basis.items[it].u0 / 2 * 3 + rb * 192 + lane;
+  }
+  // this thread's octets of a chunk: four columns and the four sixteen behind them
+  const float* xb[UNITS];
+  int pos[UNITS];
+  bool edge = false;
+#pragma unroll
+  for (int k = 0; k < UNITS; ++k) {
+    const int o = tid + 256 * k;
+    long long b;
+    int s;
+    decode(o >> 3, b, s);
+    const int first = (s + P.y_j0) * hop - g.pad;
+    xb[k] = g.x + b * g.L;
+    pos[k] = first + (o >> 2 & 1) * 32 + (o & 3) * 4;
+    edge = edge || first < 0 || first + hop > L;
+  }
+  const bool wave_edge = __builtin_amdgcn_ballot_w64(edge) != 0;
+  const bool second = (tid >> 2 & 1) != 0;  // the chunk's second 32 columns, which a hop's last one may lack
+  f32x4 v[UNITS][2];
+  auto request = [&](int c) {
+    if (second && c + 32 >= hop) return;
+    if (!wave_edge) {
+#pragma unroll
+      for (int k = 0; k < UNITS; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) v[k][h] = *reinterpret_cast<const f32x4_u*>(xb[k] + pos[k] + c + 16 * h);
+    } else {
+#pragma unroll
+      for (int k = 0; k < UNITS; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int s = pos[k] + c + 16 * h, src = s < 0 ? -s - 3 : s > L - 4 ? 2 * (L - 1) - s - 3 : s;
+          if ((unsigned)src <= (unsigned)(L - 4)) {
+            const f32x4 t = *reinterpret_cast<const f32x4_u*>(xb[k] + src);
+            v[k][h] = src != s ? (f32x4){t.w, t.z, t.y, t.x} : t;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[k][h][e] = xb[k][reflect_clamped(s + e, L)];
+          }
+        }
+    }
+  };
+  auto put = [&](int c, unsigned short* dst) {
+    if (second && c + 32 >= hop) return;
+#pragma unroll
+    for (int k = 0; k < UNITS; ++k) {
+      const int o = tid + 256 * k;
+      const Planes b = split8(v[k]);
+#pragma unroll
+      for (int l = 0; l < 3; ++l) *reinterpret_cast<u32x4*>(dst + l * PLANE + (o >> 3) * PJ_PITCH + (o & 7) * 8) = b.p[l];
+    }
+  };
+  f32x4 acc[NB][IB];
+#pragma unroll
+  for (int p = 0; p < NB; ++p)
+#pragma unroll
+    for (int i = 0; i < IB; ++i) acc[p][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  const int n_step = hop / 32;
+  u32x4 w[2][3];
+  auto fetch_w = [&](int i, int step, u32x4 (&to)[3]) {
+    const uint4* from = up[i] + (long long)(step < n_step ? step : n_step - 1) * stride[i];
+#pragma unroll
+    for (int l = 0; l < 3; ++l) to[l] = *reinterpret_cast<const u32x4*>(from + l * 64);
+  };
+  request(0);
+  fetch_w(0, 0, w[0]);
+  put(0, S);
+  for (int c = 0; c < hop; c += PJ_COLS) {
+    unsigned short* const tile_c = S + (c / PJ_COLS & 1) * 3 * PLANE;
+    __syncthreads();  // also: the other buffer has been read by every wave
+    if (c + PJ_COLS < hop) request(c + PJ_COLS);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (c + 32 * h >= hop) break;
+      Planes x[NB];
+#pragma unroll
+      for (int p = 0; p < NB; ++p)
+#pragma unroll
+        for (int l = 0; l < 3; ++l) x[p].p[l] = *reinterpret_cast<const u32x4*>(tile_c + l * PLANE + (16 * p + n) * PJ_PITCH + 32 * h + 8 * q);
+#pragma unroll
+      for (int i = 0; i < IB; ++i) {
+        constexpr int PARITY = IB & 1;
+        const int set = (i + h * PARITY) & 1;
+        fetch_w(i + 1 < IB ? i + 1 : 0, c / 32 + h + (i + 1 < IB ? 0 : 1), w[set ^ 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = 0; p < NB; ++p) acc[p][i] += multiply_octets(w[set], x[p], (f32x4){0.f, 0.f, 0.f, 0.f});
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (c + PJ_COLS < hop) put(c + PJ_COLS, S + (c / PJ_COLS + 1 & 1) * 3 * PLANE);
+  }
+  // lane (q, n), register e: row 4 q + e of a basis block, hop-block n.  Block 0's last n_lo rows go to its first.
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    if (blk0 + wave + 4 * i >= blk1) break;
+    const CqlItem& item = P.basis.items[item_of[i]];
+    const int n_lo = item.n_lo, ib = ib_of[i], r = item.r, rows = g.T + item.jspan - 1, f = ib ? 16 * ib - n_lo + 4 * q : 4 * q;
+    if (ib == 0) {
+#pragma unroll
+      for (int p = 0; p < NB; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float lo = __shfl(acc[p][i][e], lane + 64 - 4 * n_lo);  // (in every lane; used by those of the first n_lo rows)
+          if (4 * q < n_lo) acc[p][i][e] += lo;
+        }
+    }
+    if (f >= r || (!ib && f >= 16 - n_lo)) continue;
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+      long long b;
+      int s;
+      decode(16 * p + n, b, s);
+      s -= item.j0 - P.y_j0;
+      if (row_first + 16 * p + n < n_rows && s >= 0 && s < rows)
+        *reinterpret_cast<f32x4*>(P.y + b * P.y_wave + (long long)item.y_r * g.T + item.y_rj + (long long)s * r + f) = acc[p][i];
+    }
+  }
+}
+
+template <typename K>
+hipError_t allow(K kernel) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, CQL_LDS_ONE);
+}
+template <int FB, int FD, bool SHORT>
 hipError_t allow_lds() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(cqt_lowrank_kernel<FB, FD, SHORT>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             CQL_LDS_ONE);
+  return allow(cqt_lowrank_kernel<FB, FD, SHORT, false, false>);
+}
+template <int FB, int FD, bool SHARED>
+hipError_t allow_ready() {
+  return allow(cqt_lowrank_kernel<FB, FD, false, true, SHARED>);
+}
+template <int NB, int IB>
+hipError_t allow_project() {
+  const hipError_t e = allow(cqt_project_kernel<NB, IB, false>);
+  return e == hipSuccess ? allow(cqt_project_kernel<NB, IB, true>) : e;
 }
 
 template <int FB, int FD, bool SHORT = false>
 void launch(const CqlParams& p, unsigned blocks, hipStream_t stream) {
-  hipLaunchKernelGGL((cqt_lowrank_kernel<FB, FD, SHORT>), dim3(blocks), dim3(256), (size_t)p.lds_floats * 4, stream, p);
+  hipLaunchKernelGGL((cqt_lowrank_kernel<FB, FD, SHORT, false, false>), dim3(blocks), dim3(256), (size_t)p.lds_floats * 4, stream, p);
+}
+// stage 2 of the items with a basis (and direct items), their coordinates in memory
+template <int FB, int FD, bool SHARED>
+void launch_ready(const CqlParams& p, unsigned blocks, hipStream_t stream) {
+  hipLaunchKernelGGL((cqt_lowrank_kernel<FB, FD, false, true, SHARED>), dim3(blocks), dim3(256), (size_t)p.lds_floats * 4, stream, p);
+}
+
+template <int NB, int IB>
+void launch_project(const CqlParams& p, hipStream_t stream) {
+  const long long n_project = ((g_rows(p) + 16 * NB - 1) / (16 * NB) + 7) / 8 * 8 * p.y_groups;
+  if (p.shorts.n_items) {
+    const size_t lds = (size_t)p.shorts.plane * 6 + 16;
+    hipLaunchKernelGGL((cqt_project_kernel<NB, IB, true>), dim3((unsigned)(n_project + (p.shorts.n_ft + 7) / 8 * 8 * p.shorts.n_items)), dim3(256),
+                       lds < PJ_LDS(NB) ? PJ_LDS(NB) : lds, stream, p);
+  } else {
+    hipLaunchKernelGGL((cqt_project_kernel<NB, IB, false>), dim3((unsigned)n_project), dim3(256), PJ_LDS(NB), stream, p);
+  }
 }
 
 }  // namespace
 
 hipError_t cql_kernels_init() {
-  hipError_t e = allow_lds<1, 1>();
-  if (e == hipSuccess) e = allow_lds<2, 1>();
-  if (e == hipSuccess) e = allow_lds<4, 1>();
-  if (e == hipSuccess) e = allow_lds<2, 2>();
-  if (e == hipSuccess) e = allow_lds<4, 2>();
+  hipError_t e = allow_lds<1, 1, false>();
+  if (e == hipSuccess) e = allow_lds<2, 1, false>();
+  if (e == hipSuccess) e = allow_lds<4, 1, false>();
+  if (e == hipSuccess) e = allow_lds<2, 2, false>();
+  if (e == hipSuccess) e = allow_lds<4, 2, false>();
   if (e == hipSuccess) e = allow_lds<1, 4, true>();
   if (e == hipSuccess) e = allow_lds<2, 4, true>();
   if (e == hipSuccess) e = allow_lds<4, 4, true>();
+  if (e == hipSuccess) e = allow_ready<1, 1, false>();
+  if (e == hipSuccess) e = allow_ready<1, 1, true>();
+  if (e == hipSuccess) e = allow_ready<2, 1, false>();
+  if (e == hipSuccess) e = allow_ready<4, 1, false>();
+  if (e == hipSuccess) e = allow_ready<2, 2, false>();
+  if (e == hipSuccess) e = allow_ready<4, 2, false>();
+  if (e == hipSuccess) e = allow_project<2, 3>();
+  if (e == hipSuccess) e = allow_project<4, 3>();
+  if (e == hipSuccess) e = allow_project<2, 6>();
+  if (e == hipSuccess) e = allow_project<4, 6>();
   return e;
+}
+
+static bool short_fits(const CqlParams& p, size_t lds) {
+  const ShortParams& s = p.shorts;
+  constexpr int form = SHORT_COLUMNS_64;
+  return s.form == form && s.tile_frames >= 1 && s.tile_frames <= SHORT_FRAMES[form] && s.plane % 8 == 0 && s.plane >= SHORT_PLANE_MIN[form] &&
+         (size_t)s.plane * 6 + 16 <= lds && (s.columns_at_once == 32 || s.columns_at_once == 64 || s.columns_at_once == 128) && s.g.L >= 4;
+}
+
+// Stage 1 of p's items, to p.y, and the short kernels' tiles
+hipError_t launch_cqt_project(const CqlParams& p, hipStream_t stream) {
+  clear_stale_error();
+  if (!p.y || p.basis.n_items < 1 || p.g.hop % 32 || p.y_rows < 1 || p.y_groups < 1 || p.y_blocks < p.y_groups) return hipErrorInvalidValue;
+  const int each = (p.y_blocks + p.y_groups - 1) / p.y_groups;  // row blocks of a workgroup
+  if (each > 24 || (p.y_nb != 2 && p.y_nb != 4) || (p.shorts.n_items && !short_fits(p, CQL_LDS_ONE)) || (p.g.B * p.y_rows / (16 * p.y_nb) + 8) * p.y_groups > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (each <= 12)
+    p.y_nb == 2 ? launch_project<2, 3>(p, stream) : launch_project<4, 3>(p, stream);
+  else
+    p.y_nb == 2 ? launch_project<2, 6>(p, stream) : launch_project<4, 6>(p, stream);
+  return hipGetLastError();
 }
 
 hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream) {
   clear_stale_error();
-  const bool shorts = p.shorts.n_items > 0;
+  const bool shorts = p.shorts.n_items > 0 && !p.y;  // (coordinates in memory: the launch before this one took them)
   const long long blocks = (p.basis.n_ft + 7) / 8 * 8 * p.basis.n_items +
                            (shorts ? (p.shorts.n_ft + 7) / 8 * 8 * p.shorts.n_items : p.direct.n_ft * p.direct.n_items);
   if (blocks <= 0 || blocks > 0x7fffffffLL || p.g.hop % 32) return hipErrorInvalidValue;
@@ -714,12 +1011,16 @@ hipError_t launch_cqt_lowrank(const CqlParams& p, hipStream_t stream) {
   // (a batch large enough for two blocks per wave of the direct items is so for those with a basis)
   const int fb = p.basis.fb, fd = p.direct.fb;
   if ((fb != 1 && fb != 2 && fb != 4) || (fd != 1 && fd != 2) || fd > fb) return hipErrorInvalidValue;
-  if (shorts) {
-    const ShortParams& s = p.shorts;
-    constexpr int form = SHORT_COLUMNS_64;
-    if (s.form != form || s.tile_frames < 1 || s.tile_frames > SHORT_FRAMES[form] || s.plane % 8 != 0 || s.plane < SHORT_PLANE_MIN[form] ||
-        s.plane * 6 + 16 > p.lds_floats * 4 || (s.columns_at_once != 32 && s.columns_at_once != 64 && s.columns_at_once != 128) || s.g.L < 4)
-      return hipErrorInvalidValue;
+  if (p.y) {
+    const unsigned n = (unsigned)blocks;
+    if (fb == 1)
+      p.shared ? launch_ready<1, 1, true>(p, n, stream) : launch_ready<1, 1, false>(p, n, stream);
+    else if (fd == 1)
+      fb == 2 ? launch_ready<2, 1, false>(p, n, stream) : launch_ready<4, 1, false>(p, n, stream);
+    else
+      fb == 2 ? launch_ready<2, 2, false>(p, n, stream) : launch_ready<4, 2, false>(p, n, stream);
+  } else if (shorts) {
+    if (!short_fits(p, (size_t)p.lds_floats * 4)) return hipErrorInvalidValue;
     fb == 1 ? launch<1, 4, true>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 4, true>(p, (unsigned)blocks, stream) : launch<4, 4, true>(p, (unsigned)blocks, stream);
   } else if (fd == 1)
     fb == 1 ? launch<1, 1>(p, (unsigned)blocks, stream) : fb == 2 ? launch<2, 1>(p, (unsigned)blocks, stream) : launch<4, 1>(p, (unsigned)blocks, stream);

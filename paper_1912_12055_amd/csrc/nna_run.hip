@@ -453,8 +453,66 @@ bool shape_lowrank(const nna_plan* sub, long long n_frames, long long T, nna::Cq
   return cost <= 0.8 * 0.5 * (folds ? sub->exec_flops_cqf : sub->exec_flops) * CQ_FRAMES / M;
 }
 
+// The coordinates of a call's hop-blocks in memory: floats of a waveform; zero: no items with a basis
+long long coordinates_of(const nna_plan* sub, long long T, int& blocks, int& j0, int& j1) {
+  long long floats = 0;
+  blocks = j1 = 0;
+  j0 = INT_MAX;
+  for (const nna::CqlItem& it : sub->h_litems) {
+    if (!it.r) continue;
+    floats += (long long)it.r * (T + it.jspan - 1);
+    blocks += it.n_ib;
+    j0 = std::min(j0, it.j0);
+    j1 = std::max(j1, it.j0 + it.jspan);
+  }
+  return floats;
+}
+
+// What a call may use of a workspace, waveforms at a time, up to 256 MiB, what the last-level cache holds (1,770 x 176,400 samples, 168 bins: 64 MB
+// 5.12 ms, 128 4.87, 256 4.87, 1 GB 4.76); zero: it does as well without.  Two launches instead of one, where nothing runs beside the
+// items with a basis (time over the one launch's: 16 x 220,500 samples, 84 kernels of 16,384 taps 0.62, 2 x 60,000 0.70, 60 x 220,500 0.78), where
+// the first stage computes so much of one tile for its neighbours again that sharing it saves a sixth of all multiply-adds (20 x 176,400, 168
+// bins, a fifth: 0.92; 16 x 220,500, 84 bins, a seventh: 1.19), or where it is a good part of them in a large batch (168 bins, a third:
+// 20,700 frames 1.05, 55,200 0.95, 610,650 0.88; 72 bins at hop 256, a fifth, 112,060 frames: 1.14).
+size_t lowrank_workspace(const nna_plan* sub, long long B, long long L, long long T) {
+  nna::CqlParams P;
+  std::memset(&P, 0, sizeof(P));
+  if (!sub->runs_lowrank() || !shape_lowrank(sub, B * T, T, P)) return 0;
+  const double M = P.basis.tile_frames, nseg = 1 + (P.basis.tile_frames - 1 + T - 1) / T;
+  double first = 0, once = 0, second = 0;  // multiply-adds per frame
+  for (const nna::CqlItem& it : sub->h_litems) {
+    if (!it.r) continue;
+    const double each = 16.0 * it.n_ib * sub->hop;
+    first += each * (M + nseg * (it.jspan - 1)) / M;
+    once += each * (T + it.jspan - 1.0) / T;
+    second += 256.0 * (it.n_step + it.s_hi - it.s_lo) * 64 * P.basis.fb / M;
+  }
+  const double all = first + second + sub->lr_direct;
+  if (P.direct.n_items && first - once < all / 6 && (B * T < 50000 || first < 0.28 * all)) return 0;
+  int blocks, j0, j1;
+  const long long bytes = 4 * coordinates_of(sub, T, blocks, j0, j1);
+  constexpr long long most = 256LL << 20;
+  return bytes > most ? 0 : (size_t)(bytes * std::min(B, most / bytes));
+}
+
 nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
-                            long long out_wave_stride, int row_offset, nna::CqlParams& P, void* hip_stream) {
+                            long long out_wave_stride, int row_offset, nna::CqlParams& P, void* hip_stream, void* workspace = nullptr,
+                            size_t workspace_bytes = 0) {
+  int blocks, j0, j1;
+  const long long floats = coordinates_of(sub, T, blocks, j0, j1), at_once = workspace ? (long long)(workspace_bytes / 4) / floats : 0;
+  if (at_once > 0 && at_once < B) {
+    // as many waveforms at a time as the workspace holds the coordinates of, in parts of equal size
+    const long long parts = (B + at_once - 1) / at_once;
+    for (long long i = 0; i < parts; ++i) {
+      const long long b0 = B * i / parts, n = B * (i + 1) / parts - b0;
+      nna::CqlParams Q;
+      std::memset(&Q, 0, sizeof(Q));
+      if (!shape_lowrank(sub, n * T, T, Q)) return fail(NNA_ERR_UNSUPPORTED, "hop-block tiles");
+      const nna_status s = run_conv_lowrank(sub, x + b0 * L, n, L, T, out + b0 * out_wave_stride, out_wave_stride, row_offset, Q, hip_stream, workspace, workspace_bytes);
+      if (s != NNA_OK) return s;
+    }
+    return NNA_OK;
+  }
   P.g = make_geom(sub, x, B, L, T);
   P.u = reinterpret_cast<const float4*>(sub->d_lu);
   P.a = reinterpret_cast<const float4*>(sub->d_la);
@@ -474,6 +532,31 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
     s.fmt = sub->fmt;
     P.direct = nna::CqlPart{};
     P.direct.fb = 1;
+  }
+  if (at_once > 0) {
+    P.y = static_cast<float*>(workspace);
+    P.y_wave = floats;
+    P.y_j0 = j0;
+    P.y_rows = (int)T + j1 - j0 - 1;
+    P.y_blocks = blocks;
+    // 32 hop-blocks and twelve row blocks a workgroup fill the chip sooner (16 x 220,500 samples, 84 dense kernels: 33 us; 24 row blocks 41, 64
+    // hop-blocks 42, both 50); twice as many of both read the weights half as often
+    P.y_nb = B * P.y_rows >= 64 * 512 ? 4 : 2;
+    const int each = P.y_nb == 4 ? 24 : 12;
+    P.y_groups = (blocks + each - 1) / each;
+    // the coordinates' words, and the waves' sums where they keep the workgroup in half a CU's LDS, or all of it
+    int words = 0;
+    const long long nseg = 1 + (P.basis.tile_frames - 1 + T - 1) / T;
+    for (const nna::CqlItem& it : sub->h_litems)
+      if (it.r) words = std::max(words, (int)(P.basis.tile_frames + nseg * (it.jspan - 1)) * it.r + 32);
+    if (P.shorts.n_items) P.lds_floats = words;
+    const int with_sums = (words + 3) / 4 * 4 + 3 * 2 * 4 * 64 * 4;
+    if (P.basis.fb == 1 && (with_sums <= nna::CQL_LDS_TWO / 4 || (words > nna::CQL_LDS_TWO / 4 && with_sums <= nna::CQL_LDS_ONE / 4))) {
+      P.shared = (words + 3) / 4 * 4;
+      P.lds_floats = std::max(P.lds_floats, with_sums);
+    }
+    const hipError_t e = nna::launch_cqt_project(P, reinterpret_cast<hipStream_t>(hip_stream));
+    if (e != hipSuccess) return fail_hip(e, "kernel launch");
   }
   const hipError_t e = nna::launch_cqt_lowrank(P, reinterpret_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return fail_hip(e, "kernel launch");
@@ -538,11 +621,12 @@ hipError_t launch_conv(const nna_plan* sub, const nna::CqtParams& P, hipStream_t
 
 // one launch of the CQT kernel: `sub`'s bank over T frames of each of the B waveforms in x
 nna_status run_conv(const nna_plan* sub, const float* x, long long B, long long L, long long T, float* out,
-                    long long out_wave_stride, int row_offset, void* hip_stream, bool may_fold, float* keep) {
+                    long long out_wave_stride, int row_offset, void* hip_stream, bool may_fold, float* keep, void* workspace,
+                    size_t workspace_bytes) {
   if (sub->runs_lowrank()) {
     nna::CqlParams Q;
     std::memset(&Q, 0, sizeof(Q));
-    if (shape_lowrank(sub, B * T, T, Q)) return run_conv_lowrank(sub, x, B, L, T, out, out_wave_stride, row_offset, Q, hip_stream);
+    if (shape_lowrank(sub, B * T, T, Q)) return run_conv_lowrank(sub, x, B, L, T, out, out_wave_stride, row_offset, Q, hip_stream, workspace, workspace_bytes);
   }
   if (sub->runs_short()) {
     nna::ShortParams Q;
@@ -851,5 +935,37 @@ nna_status nna_cqt(const nna_plan* plan, const float* x_dev, long long B, long l
   hipError_t e = guard.enter(plan->device);
   if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
   return run_conv(plan, x_dev, B, L, T, out_dev, (long long)plan->out_rows() * T, 0, hip_stream, true);
+}
+
+// the plan whose kernels a call of nna_cqt or nna_cqt1992 applies at one rate, or NULL
+static const nna_plan* one_rate_plan(const nna_plan* plan) {
+  if (plan->kind == NNA_KIND_CQT) return plan;
+  return plan->kind == NNA_KIND_CQT1992 && plan->runs_composed() ? plan->composed : nullptr;
+}
+
+nna_status nna_cqt_workspace(const nna_plan* plan, long long B, long long L, size_t* bytes) {
+  if (!plan || !bytes) return fail(NNA_ERR_INVALID_ARG, "plan / bytes is NULL");
+  if (plan->kind != NNA_KIND_CQT && plan->kind != NNA_KIND_CQT1992) return fail(NNA_ERR_INVALID_ARG, "plan was built for a different transform");
+  const long long T = B < 1 ? 0 : frames_of(plan, L);
+  if (T < 1) return fail(NNA_ERR_SHAPE, "no frames");
+  const nna_plan* sub = one_rate_plan(plan);
+  *bytes = sub && plan->device >= 0 ? lowrank_workspace(sub, B, L, T) : 0;
+  return NNA_OK;
+}
+
+nna_status nna_cqt_in_workspace(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev, void* workspace_dev,
+                                size_t workspace_bytes, void* hip_stream) {
+  if (!plan) return fail(NNA_ERR_INVALID_ARG, "plan is NULL");
+  const nna_plan* sub = one_rate_plan(plan);
+  if (!sub || !workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 15))
+    return plan->kind == NNA_KIND_CQT1992 ? nna_cqt1992(plan, x_dev, B, L, out_dev, hip_stream) : nna_cqt(plan, x_dev, B, L, out_dev, hip_stream);
+  long long T = 0;
+  nna_status s = check_call(plan, plan->kind, x_dev, B, L, out_dev, &T);
+  if (s != NNA_OK) return s;
+  DeviceGuard guard;
+  hipError_t e = guard.enter(plan->device);
+  if (e != hipSuccess) return fail_hip(e, "hipSetDevice");
+  return run_conv(sub, x_dev, B, L, T, out_dev, (long long)plan->out_rows() * T, 0, hip_stream, plan->kind == NNA_KIND_CQT, nullptr, workspace_dev,
+                  workspace_bytes);
 }
 }  // extern "C"

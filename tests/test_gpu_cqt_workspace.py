@@ -1,0 +1,82 @@
+"""Constant-Q calls whose hop-blocks' coordinates go through the caller's memory, against the one launch that keeps them in LDS: every
+width of tile and kind of item beside them, waveforms in parts, hops that are no multiple of 64, samples that are not finite."""
+import sys
+
+import numpy as np
+import pytest
+
+from test_gpu_hopblocks import CASES, nb  # noqa: F401 (the fixture)
+
+pytestmark = pytest.mark.gpu
+# the same coordinates, products and blocks of 32 products; up to 108 block sums added in another order: 108 x 2^-24 of a bin's own sums at
+# most, 4e-7 of the peak measured
+TOL = 2e-6
+
+
+def _one_launch(nb, plan, x):
+    return nb._run(nb.lib().nna_cqt1992 if plan.info()["kind"] == nb.NNA_KIND_CQT1992 else nb.lib().nna_cqt, plan, x, None, None)
+
+
+def _both(nb, plan, x, floats):
+    import torch
+    ws = torch.full((floats,), float("nan"), device="cuda:0")
+    return nb.nna_cqt_in_workspace(plan, x, ws).cpu().numpy(), _one_launch(nb, plan, x).cpu().numpy()
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}x{c[3]}-{c[6]}x{c[7]}")
+def test_against_one_launch(nb, case):
+    import torch
+    n_bins, bpo, sr, hop, fmin, n_taps, B, L, center, tiles = case
+    print(f"[case] cqt workspace {case}", file=sys.stderr, flush=True)
+    x = torch.from_numpy((0.3 * np.random.default_rng([31, n_bins, hop]).standard_normal((B, L))).astype(np.float32)).to("cuda:0")
+    for fmt in (nb.NNA_OUT_MAGNITUDE, nb.NNA_OUT_COMPLEX):
+        plan = nb.nna_plan_cqt(sr=sr, hop=hop, fmin=fmin, n_bins=n_bins, bins_per_octave=bpo, n_taps=n_taps, center=center, fmt=fmt, device=0)
+        got, ref = _both(nb, plan, x, 1 << 24)
+        assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
+        if B > 2:  # in parts: what a third of the waveforms needs, at most 140 functions of every hop-block
+            got, ref = _both(nb, plan, x, (B // 3) * 140 * (L // hop + 200))
+            assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
+        got, ref = _both(nb, plan, x, 16)  # not one waveform's: not used
+        assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("B,L,n_bins,hop", [(1, 16390, 84, 512), (3, 40001, 84, 512), (70, 9000, 60, 256)])
+def test_dense_kernels(nb, B, L, n_bins, hop):
+    import torch
+    print(f"[case] cqt workspace dense {B} {L} {n_bins} {hop}", file=sys.stderr, flush=True)
+    plan = nb.nna_plan_cqt1992(sr=22050, hop=hop, n_bins=n_bins, fmin=32.7 if n_bins == 84 else 65.4, fmt=nb.NNA_OUT_COMPLEX, device=0)
+    x = torch.from_numpy((0.3 * np.random.default_rng([33, B]).standard_normal((B, L))).astype(np.float32)).to("cuda:0")
+    assert nb.nna_cqt_workspace(plan, B, L) > 0
+    got, ref = _both(nb, plan, x, nb.nna_cqt_workspace(plan, B, L) // 4)
+    assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
+    assert np.array_equal(nb.nna_cqt1992(plan, x).cpu().numpy(), got)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 3.3e38])
+def test_not_finite(nb, bad):
+    """The outputs that a bad sample reaches, and no others, whichever way the coordinates go."""
+    import torch
+    print(f"[case] cqt workspace {bad}", file=sys.stderr, flush=True)
+    x = torch.from_numpy((0.3 * np.random.default_rng(35).standard_normal((3, 60001))).astype(np.float32)).to("cuda:0")
+    x[1, 30011] = bad
+    for plan in (nb.nna_plan_cqt(n_bins=84, fmt=nb.NNA_OUT_COMPLEX, device=0), nb.nna_plan_cqt1992(n_bins=84, fmt=nb.NNA_OUT_COMPLEX, device=0)):
+        got, ref = _both(nb, plan, x, 1 << 24)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+        fine = np.isfinite(ref) & (np.abs(ref) < 1e10)
+        assert fine.any() and np.abs(got - ref)[fine].max() <= TOL * np.abs(ref[fine]).max()
+
+
+def test_memory_that_cannot_serve(nb):
+    import torch
+    plan = nb.nna_plan_cqt(n_bins=84, device=0)
+    x = torch.randn((2, 40000), generator=torch.Generator().manual_seed(1)).cuda()
+    ref = _one_launch(nb, plan, x)
+    ws = torch.empty(1 << 22, device="cuda:0")
+    assert torch.equal(nb.nna_cqt_in_workspace(plan, x, ws[1:]), ref)  # not aligned to 16 bytes
+    kept = nb.nna_plan_trainable(plan)  # trained kernels are contracted
+    assert nb.nna_cqt_workspace(kept, 2, 40000) == 0
+    assert torch.equal(nb.nna_cqt_in_workspace(kept, x, ws), _one_launch(nb, kept, x))
+    with pytest.raises(RuntimeError):
+        nb.nna_cqt_workspace(nb.nna_plan_stft(n_fft=256, hop=64, device=0), 2, 4000)
+    with pytest.raises(RuntimeError):
+        nb.nna_cqt_workspace(plan, 2, 100)
