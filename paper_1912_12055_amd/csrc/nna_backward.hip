@@ -539,11 +539,10 @@ static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, l
   Q.K = plan->K;
   Q.gw = gw_dev;
   Q.gx = gx_dev;
+  // (the buffers are the caller's, cleared here; one that the caller adds several gradients onto comes cleared)
+  const long long gw_clear = gw_dev && zero_gw ? 2LL * plan->stft_bins() * plan->K : 0;
+  if ((e = nna::launch_fill_two(gw_dev, gw_clear, gx_dev, gx_dev ? B * L : 0, stream)) != hipSuccess) return fail_hip(e, "kernel launch");
   if (gw_dev) {
-    if (zero_gw) {
-      e = nna::launch_fill_zero(gw_dev, 2LL * plan->stft_bins() * plan->K, stream);
-      if (e != hipSuccess) return fail_hip(e, "kernel launch");
-    }
     // split the contraction over the frames so that about 1,024 workgroups exist (two per compute
     // unit, twice over), each with at least 64 chunks to amortise its start-up
     const long long tiles = (long long)(plan->rows_pad / nna::BW_MT) * (plan->kp / nna::BW_NT);
@@ -553,15 +552,9 @@ static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, l
     if (split * tiles < 512) split = std::max(split, std::min((512 + tiles - 1) / tiles, chunks / 16));
     Q.chunks_per_split = (chunks + split - 1) / split;
     Q.n_split = (int)((chunks + Q.chunks_per_split - 1) / Q.chunks_per_split);
-    e = nna::launch_bw_bank(Q, stream);
-    if (e != hipSuccess) return fail_hip(e, "kernel launch");
   }
-  if (gx_dev) {
-    e = nna::launch_fill_zero(gx_dev, B * L, stream);
-    if (e != hipSuccess) return fail_hip(e, "kernel launch");
-    e = nna::launch_bw_wave(Q, stream);
-    if (e != hipSuccess) return fail_hip(e, "kernel launch");
-  }
+  e = gw_dev && gx_dev ? nna::launch_bw_both(Q, stream) : gw_dev ? nna::launch_bw_bank(Q, stream) : gx_dev ? nna::launch_bw_wave(Q, stream) : hipSuccess;
+  if (e != hipSuccess) return fail_hip(e, "kernel launch");
   return NNA_OK;
 }
 

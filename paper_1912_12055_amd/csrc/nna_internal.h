@@ -511,8 +511,11 @@ hipError_t launch_bank_to_logical(const BankPermuteParams& p, hipStream_t stream
 hipError_t launch_split_forward(StftParams p, int mode, const float* wrm, int kp, int K, hipStream_t stream);
 hipError_t launch_split_bank(const BwParams& p, hipStream_t stream);
 hipError_t launch_split_wave(BwParams p, hipStream_t stream);
+hipError_t launch_split_both(const BwParams& p, hipStream_t stream);
 hipError_t launch_bw_bank(const BwParams& p, hipStream_t stream);      // gw += G x frames
 hipError_t launch_bw_wave(const BwParams& p, hipStream_t stream);      // gx += transposed convolution
+hipError_t launch_bw_both(const BwParams& p, hipStream_t stream);      // both at once (dense banks)
+hipError_t launch_fill_two(float* p, long long n, float* q, long long m, hipStream_t stream);
 // decimation by two on the vector ALUs (fir_decimate_kernel)
 constexpr int FIR_T = 8;                // outputs per thread
 constexpr int FIR_TILE = 256 * FIR_T;   // outputs per workgroup

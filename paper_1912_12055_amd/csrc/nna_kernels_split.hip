@@ -230,14 +230,13 @@ __global__ __launch_bounds__(256, 2) void split_forward_kernel(const StftParams 
 // ---- bank gradient ------------------------------------------------------------------------------
 // SPARSE: the output tiles of P.tiles only, each with its count of 32-row blocks that hold taps.
 template <bool SPARSE>
-__global__ __launch_bounds__(256, 2) void split_bank_kernel(const BwParams P) {
-  __shared__ __attribute__((aligned(16))) unsigned lds[2 * 3 * SP_PLANE];
+__device__ __forceinline__ void bank_tile(const BwParams& P, long long bid, unsigned* __restrict__ lds) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, h = lane >> 5, r32 = lane & 31;
   const FrameGeom& g = P.g;
   const int n_nt = P.kp / BW_NT, n_mt = P.rows_pad / BW_MT;
   const long long tiles = SPARSE ? P.n_tiles : (long long)n_mt * n_nt;
-  const long long split = blockIdx.x / tiles;
-  int tile = (int)(blockIdx.x - split * tiles);
+  const long long split = bid / tiles;
+  int tile = (int)(bid - split * tiles);
   long long m0;
   int n0, alive_rt = 4;
   if constexpr (SPARSE) {
@@ -339,13 +338,12 @@ __global__ __launch_bounds__(256, 2) void split_bank_kernel(const BwParams P) {
 }
 
 // ---- waveform gradient --------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 2) void split_wave_kernel(const BwParams P) {
-  __shared__ __attribute__((aligned(16))) unsigned lds[2 * 3 * SP_PLANE];
+__device__ __forceinline__ void wave_tile(const BwParams& P, long long bid, unsigned* __restrict__ lds) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, h = lane >> 5, r32 = lane & 31;
   const FrameGeom& g = P.g;
   // the tap tiles of one frame tile are neighbours: they share its G columns in the L2
   const int n_nt = P.kp / BW_NT;
-  const long long tiles = P.gpitch / BW_MT * n_nt, split = blockIdx.x / tiles, tile = blockIdx.x - split * tiles;
+  const long long tiles = P.gpitch / BW_MT * n_nt, split = bid / tiles, tile = bid - split * tiles;
   const long long m0 = tile / n_nt * BW_MT;
   const int n0 = (int)(tile % n_nt) * BW_NT;
   const long long c_all = (2 * P.n_half + SP_KC - 1) / SP_KC;  // (the padding rows of G and W are zero)
@@ -397,6 +395,27 @@ __global__ __launch_bounds__(256, 2) void split_wave_kernel(const BwParams P) {
     }
 }
 
+template <bool SPARSE>
+__global__ __launch_bounds__(256, 2) void split_bank_kernel(const BwParams P) {
+  __shared__ __attribute__((aligned(16))) unsigned lds[2 * 3 * SP_PLANE];
+  bank_tile<SPARSE>(P, blockIdx.x, lds);
+}
+
+__global__ __launch_bounds__(256, 2) void split_wave_kernel(const BwParams P) {
+  __shared__ __attribute__((aligned(16))) unsigned lds[2 * 3 * SP_PLANE];
+  wave_tile(P, blockIdx.x, lds);
+}
+
+// Both gradients of a step in one launch: neither's tiles fill a short batch's chip.  A whole step, 16 x 44,217 samples, n_fft 2,048: 435 -> 417
+// us (432 workgroups, uncut, at once); 2 x 30,000: 280 -> 259; n_fft 512, 20 x 60,000: 177 -> 156; n_fft 4,096, 2 x 30,000: 586 -> 556.
+__global__ __launch_bounds__(256, 2) void split_both_kernel(const BwParams bank, const BwParams wave, unsigned n_wave) {
+  __shared__ __attribute__((aligned(16))) unsigned lds[2 * 3 * SP_PLANE];
+  if (blockIdx.x < n_wave)
+    wave_tile(wave, blockIdx.x, lds);
+  else
+    bank_tile<false>(bank, blockIdx.x - n_wave, lds);
+}
+
 }  // namespace
 
 hipError_t launch_split_forward(StftParams P, int mode, const float* wrm, int kp, int K, hipStream_t stream) {
@@ -428,17 +447,45 @@ hipError_t launch_split_bank(const BwParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_split_wave(BwParams p, hipStream_t stream) {
-  clear_stale_error();
+// blocks of a launch of the waveform gradient; sets p.chunks_per_split
+static long long shape_wave(BwParams& p) {
   // A short batch's contraction over the bank's rows is halved, or cut into pieces of sixteen chunks until there is a workgroup per compute
   // unit.  A whole step, n_fft 2,048, 176 tiles: 449 us whole, 427 halved, 456 in three (every piece adds onto the waveform by
   // itself); 48 tiles 311, 298, 290, 287 in four; 352 tiles the same either way; 496 tiles 830, 840; n_fft 512, sixteen chunks, 376 tiles: 249, 270.
   const long long tiles = p.gpitch / BW_MT * (p.kp / BW_NT), chunks = (2 * p.n_half + SP_KC - 1) / SP_KC;
   const long long split = tiles > 0 && tiles < 256 && chunks >= 32 ? std::min((256 + tiles - 1) / tiles, chunks / 16) : 1;
   p.chunks_per_split = std::max(1LL, (chunks + split - 1) / split);
-  const long long blocks = tiles * ((chunks + p.chunks_per_split - 1) / p.chunks_per_split);
+  return tiles * ((chunks + p.chunks_per_split - 1) / p.chunks_per_split);
+}
+
+hipError_t launch_split_wave(BwParams p, hipStream_t stream) {
+  clear_stale_error();
+  const long long blocks = shape_wave(p);
   if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL(split_wave_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_both(const BwParams& p, hipStream_t stream) {
+  clear_stale_error();
+  BwParams bank = p, wave = p;
+  const long long chunks = (2 * p.n_half + SP_KC - 1) / SP_KC, bank_tiles = (long long)(p.rows_pad / BW_MT) * (p.kp / BW_NT);
+  const long long wave_tiles = p.gpitch / BW_MT * (p.kp / BW_NT);
+  long long n_wave = shape_wave(wave), n_bank = bank_tiles * bank.n_split;
+  if (bank_tiles + wave_tiles >= 384 && bank_tiles + wave_tiles <= 512) {
+    // uncut they fill the chip once, two to a compute unit (256 and 176 of them: the step 417 us, bank halved 431, both halved 434)
+    bank.n_split = 1;
+    bank.chunks_per_split = p.gpitch / BW_KC;
+    wave.chunks_per_split = chunks;
+    n_wave = wave_tiles;
+    n_bank = bank_tiles;
+  }
+  if (p.tiles || n_wave <= 0 || n_bank <= 0 || n_wave + n_bank > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (n_wave + n_bank > 1536) {  // each fills the chip by itself (1,920 workgroups: the step 1,523 us in two launches, 1,531 in one)
+    const hipError_t e = launch_split_bank(p, stream);
+    return e == hipSuccess ? launch_split_wave(p, stream) : e;
+  }
+  hipLaunchKernelGGL(split_both_kernel, dim3((unsigned)(n_wave + n_bank)), dim3(256), 0, stream, bank, wave, (unsigned)n_wave);
   return hipGetLastError();
 }
 

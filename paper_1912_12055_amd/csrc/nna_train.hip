@@ -35,6 +35,11 @@ __global__ void fill_zero_kernel(float* __restrict__ p, long long n) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0.f;
 }
 
+__global__ void fill_two_kernel(float* __restrict__ p, long long n, float* __restrict__ q, long long m) {
+  const long long stride = (long long)gridDim.x * blockDim.x;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n + m; i += stride) (i < n ? p : q)[i < n ? i : i - n] = 0.f;
+}
+
 // Transposed decimation (Sec. III-C "Downsampling", backwards): the forward step is
 //     y[m] = sum_v he[v] x~[2 (m + ve0 + v)] + sum_v ho[v] x~[2 (m + vo0 + v) + 1],   x~ = x mirrored at both ends,
 // so sample p of the extended signal collects  u[p] = sum_v taps[v] g[i - v0 - v]  (p = 2 i even: he, ve0;
@@ -802,6 +807,14 @@ hipError_t launch_fill_zero(float* p, long long n, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// p[0 .. n) and q[0 .. m)
+hipError_t launch_fill_two(float* p, long long n, float* q, long long m, hipStream_t stream) {
+  clear_stale_error();
+  if (n + m < 1) return hipSuccess;
+  hipLaunchKernelGGL(fill_two_kernel, dim3(grid_for(n + m, 256 * 8)), dim3(256), 0, stream, p, n, q, m);
+  return hipGetLastError();
+}
+
 hipError_t launch_fir_transpose_add(const FirTParams& p, hipStream_t stream) {
   clear_stale_error();
   if (p.L < 1 || p.Ln != (p.L + 1) / 2 || p.B < 1 || p.B > 65535 || p.L > 0x3fffffffLL || p.ne < FT_T || p.no < FT_T ||
@@ -917,8 +930,7 @@ static bool bw_shapes_ok(const BwParams& p) {
          p.gpitch % BW_MT == 0 && p.gpitch >= p.g.n_frames && p.K <= p.kp && 2 * p.n_half <= p.rows_pad;
 }
 
-hipError_t launch_bw_bank(const BwParams& p, hipStream_t stream) {
-  clear_stale_error();
+static hipError_t check_bank(const BwParams& p) {
   if (!bw_shapes_ok(p) || p.n_split < 1 || p.chunks_per_split < 1) return hipErrorInvalidValue;
   if (p.chunks_per_split * p.n_split < p.gpitch / BW_KC) return hipErrorInvalidValue;
   const bool sparse = p.tiles != nullptr;
@@ -926,7 +938,13 @@ hipError_t launch_bw_bank(const BwParams& p, hipStream_t stream) {
   const long long tiles = sparse ? p.n_tiles : (long long)(p.rows_pad / BW_MT) * (p.kp / BW_NT);
   const long long blocks = tiles * p.n_split;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  return launch_split_bank(p, stream);
+  return hipSuccess;
+}
+
+hipError_t launch_bw_bank(const BwParams& p, hipStream_t stream) {
+  clear_stale_error();
+  const hipError_t e = check_bank(p);
+  return e == hipSuccess ? launch_split_bank(p, stream) : e;
 }
 
 hipError_t launch_bw_wave(const BwParams& p, hipStream_t stream) {
@@ -947,6 +965,13 @@ hipError_t launch_bw_wave(const BwParams& p, hipStream_t stream) {
   const long long blocks = (p.gpitch / BW_MT) * (p.kp / BW_NT);
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   return launch_split_wave(p, stream);
+}
+
+hipError_t launch_bw_both(const BwParams& p, hipStream_t stream) {
+  clear_stale_error();
+  if (p.tiles || p.shift_rng) return hipErrorInvalidValue;
+  const hipError_t e = check_bank(p);
+  return e == hipSuccess ? launch_split_both(p, stream) : e;
 }
 
 hipError_t launch_lin_from_logical(const LinLogicalParams& p, hipStream_t stream) {
