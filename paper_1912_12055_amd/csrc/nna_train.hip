@@ -520,14 +520,17 @@ __device__ __forceinline__ f32x4 load4_guarded(const float* row, int c, int lim)
 
 constexpr int MEL_BW_SPEC = 0, MEL_BW_WEIGHTS = 1;
 
-// 128 x 128 tiles, 2 x 2 waves of 64 x 64 (v_mfma_f32_32x32x2_f32); these two contractions are small
-// (2 n_mels F flop per frame each, 3 % of the STFT's) and bound by reading / writing the [B, F, T]
-// arrays, so the chunk loop is the plain one: load, barrier, write LDS, barrier, multiply.
+// 128 x 128 tiles, 2 x 2 waves of 64 x 64 (v_mfma_f32_32x32x2_f32); a chunk of 32 contraction indices is requested while the one before is
+// multiplied (asked for and waited for in turn, 13,824 frames of 1,025 bins: 128 bands from the spectrogram 128 us, the spectrogram's gradient
+// 62; now 50 and 47; the filters' gradient stays at 92).
 //   MEL_BW_SPEC:    C[k, f]                 A = W[m][k] (k-major: row = contraction index), B = g[b][m][t] (k-major)
 //   MEL_BW_WEIGHTS: C[m, k]                 A = g[b][m][t], B = P[b][k][t] (both: row = output index, contraction contiguous)
-template <int MODE>
+// NT: columns of a tile; 64 where those of 128 are fewer than the compute units (a step, 3 x 60,000, 229 bands: 294 -> 225 us).
+template <int MODE, int NT>
 __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
+  static_assert(NT == 128 || (NT == 64 && MODE == MEL_BW_SPEC), "columns of a tile");
   constexpr int TILE_FLOATS = MODE == MEL_BW_SPEC ? BW_KC * BW_PK : BW_MT * BW_PA_M;
+  constexpr int NI = NT / 64;  // 32-column blocks of a wave
   __shared__ __attribute__((aligned(16))) float ldsA[TILE_FLOATS];
   __shared__ __attribute__((aligned(16))) float ldsB[TILE_FLOATS];
 
@@ -536,25 +539,25 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
   const int wm = wave >> 1, wn = wave & 1;
   const int h = lane >> 5, r32 = lane & 31;
 
-  f32x16 acc[2][2];
+  f32x16 acc[2][NI];
 #pragma unroll
   for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
+    for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
 
   auto multiply = [&]() {
 #pragma unroll
     for (int kg = 0; kg < BW_KC / 8; ++kg) {
-      f32x4 a[2], b[2];
+      f32x4 a[2], b[NI];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         if constexpr (MODE == MEL_BW_SPEC) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             a[i][e] = ldsA[(8 * kg + 4 * h + e) * BW_PK + wm * 64 + i * 32 + r32];
-            b[i][e] = ldsB[(8 * kg + 4 * h + e) * BW_PK + wn * 64 + i * 32 + r32];
+            if (i < NI) b[i][e] = ldsB[(8 * kg + 4 * h + e) * BW_PK + wn * (NT / 2) + i * 32 + r32];
           }
         } else {
           a[i] = *reinterpret_cast<const f32x4*>(ldsA + (wm * 64 + i * 32 + r32) * BW_PA_M + 8 * kg + 4 * h);
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-          for (int ni = 0; ni < 2; ++ni)
+          for (int ni = 0; ni < NI; ++ni)
             acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mi][e], b[ni][e], acc[mi][ni], 0, 0, 0);
     }
   };
@@ -576,9 +579,11 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
     // have fewer than 64 frames: 4,000 x 10 frames, 128 bands, n_fft 512: 448 -> 183 us, contraction included)
     const int n_mt = P.fp / BW_MT;
     const int k0 = (int)(blockIdx.x % n_mt) * BW_MT;  // bins of this tile
-    const long long f0 = (long long)(blockIdx.x / n_mt) * BW_NT, n_frames = P.B * P.T;
-    // this thread's four columns
-    const long long fl = f0 + 4 * (tid & 31);
+    const long long f0 = (long long)(blockIdx.x / n_mt) * NT, n_frames = P.B * P.T;
+    // this thread's four columns of B, of every so many-th row
+    constexpr int LANES = NT / 4, ROWS = 256 / LANES, NB = BW_KC / ROWS;
+    const int cb = 4 * (tid % LANES), rowb = tid / LANES;
+    const long long fl = f0 + cb;
     long long off[4];
     int there = 0, t = (int)(fl % P.T);
     bool run = t + 3 < P.T && fl + 3 < n_frames;  // four consecutive samples
@@ -590,12 +595,13 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
         ++b;
       }
     }
-    for (int m0 = 0; m0 < P.mels_pad; m0 += BW_KC) {
-      f32x4 ra[4], rb[4];
+    f32x4 ra[4], rb[NB];
+    auto request = [&](int m0) {
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int m = m0 + (tid >> 5) + 8 * p;  // contraction index: the mel
-        ra[p] = *reinterpret_cast<const f32x4*>(P.wrm + (long long)m * P.fp + k0 + 4 * (tid & 31));
+      for (int p = 0; p < 4; ++p) ra[p] = *reinterpret_cast<const f32x4*>(P.wrm + (long long)(m0 + (tid >> 5) + 8 * p) * P.fp + k0 + 4 * (tid & 31));
+#pragma unroll
+      for (int p = 0; p < NB; ++p) {
+        const int m = m0 + rowb + ROWS * p;  // contraction index: the mel
         rb[p] = (f32x4){0.f, 0.f, 0.f, 0.f};
         if (m < P.n_mels) {
           const float* row = P.g + (long long)m * P.T;
@@ -608,18 +614,21 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
           }
         }
       }
+    };
+    request(0);
+    for (int m0 = 0; m0 < P.mels_pad; m0 += BW_KC) {
       __syncthreads();
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        *reinterpret_cast<f32x4*>(ldsA + ((tid >> 5) + 8 * p) * BW_PK + 4 * (tid & 31)) = ra[p];
-        *reinterpret_cast<f32x4*>(ldsB + ((tid >> 5) + 8 * p) * BW_PK + 4 * (tid & 31)) = rb[p];
-      }
+      for (int p = 0; p < 4; ++p) *reinterpret_cast<f32x4*>(ldsA + ((tid >> 5) + 8 * p) * BW_PK + 4 * (tid & 31)) = ra[p];
+#pragma unroll
+      for (int p = 0; p < NB; ++p) *reinterpret_cast<f32x4*>(ldsB + (rowb + ROWS * p) * BW_PK + cb) = rb[p];
       __syncthreads();
+      if (m0 + BW_KC < P.mels_pad) request(m0 + BW_KC);
       multiply();
     }
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-      const long long f = f0 + wn * 64 + ni * 32 + r32, b = f / P.T;
+    for (int ni = 0; ni < NI; ++ni) {
+      const long long f = f0 + wn * (NT / 2) + ni * 32 + r32, b = f / P.T;
       if (f >= n_frames) continue;
       float* __restrict__ ob = P.gP + b * (long long)P.F * P.T + (f - b * P.T);
 #pragma unroll
@@ -637,17 +646,20 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
     const int m0 = (tile / n_nt) * BW_MT, k0 = (tile % n_nt) * BW_NT;  // mels, bins of this tile
     const long long b_begin = split * P.b_per_split;
     const long long b_end = b_begin + P.b_per_split < P.B ? b_begin + P.b_per_split : P.B;
-    for (long long b = b_begin; b < b_end; ++b) {
+    f32x4 ra[4], rb[4];
+    auto request = [&](long long b, int t0) {
       const float* gb = P.g + b * (long long)P.n_mels * P.T;
       const float* pb = P.P + b * (long long)P.F * P.T;
-      for (int t0 = 0; t0 < P.T; t0 += BW_KC) {
-        f32x4 ra[4], rb[4];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const int row = (tid >> 3) + 32 * p;  // output index: mel (A), bin (B); contraction = frames
-          ra[p] = load4_guarded(m0 + row < P.n_mels ? gb + (long long)(m0 + row) * P.T : nullptr, t0 + 4 * (tid & 7), P.T);
-          rb[p] = load4_guarded(k0 + row < P.F ? pb + (long long)(k0 + row) * P.T : nullptr, t0 + 4 * (tid & 7), P.T);
-        }
+      for (int p = 0; p < 4; ++p) {
+        const int row = (tid >> 3) + 32 * p;  // output index: mel (A), bin (B); contraction = frames
+        ra[p] = load4_guarded(m0 + row < P.n_mels ? gb + (long long)(m0 + row) * P.T : nullptr, t0 + 4 * (tid & 7), P.T);
+        rb[p] = load4_guarded(k0 + row < P.F ? pb + (long long)(k0 + row) * P.T : nullptr, t0 + 4 * (tid & 7), P.T);
+      }
+    };
+    if (b_begin < b_end) request(b_begin, 0);
+    for (long long b = b_begin; b < b_end; ++b) {
+      for (int t0 = 0; t0 < P.T; t0 += BW_KC) {
         __syncthreads();
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -655,13 +667,15 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
           *reinterpret_cast<f32x4*>(ldsB + ((tid >> 3) + 32 * p) * BW_PA_M + 4 * (tid & 7)) = rb[p];
         }
         __syncthreads();
+        if (t0 + BW_KC < P.T) request(b, t0 + BW_KC);
+        else if (b + 1 < b_end) request(b + 1, 0);
         multiply();
       }
     }
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
+      for (int ni = 0; ni < NI; ++ni) {
         const int k = k0 + wn * 64 + ni * 32 + r32;
         if (k >= P.F) continue;
 #pragma unroll
@@ -1001,9 +1015,14 @@ hipError_t launch_lin_fold_gradient(const float* gylin, float* gysk, int n_bins,
 hipError_t launch_mel_bw_spec(const MelBwParams& p, hipStream_t stream) {
   clear_stale_error();
   if (p.fp <= 0 || p.fp % BW_MT || p.mels_pad % BW_KC || p.mels_pad < p.n_mels || p.F > p.fp || p.T < 1) return hipErrorInvalidValue;
-  const long long blocks = (p.fp / BW_MT) * ((p.B * p.T + BW_NT - 1) / BW_NT);
+  auto blocks_of = [&](int nt) { return (p.fp / BW_MT) * ((p.B * p.T + nt - 1) / nt); };
+  const bool half = blocks_of(128) < 256;
+  const long long blocks = blocks_of(half ? 64 : 128);
   if (blocks < 1 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((mel_bw_kernel<MEL_BW_SPEC>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  if (half)
+    hipLaunchKernelGGL((mel_bw_kernel<MEL_BW_SPEC, 64>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  else
+    hipLaunchKernelGGL((mel_bw_kernel<MEL_BW_SPEC, 128>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -1013,7 +1032,7 @@ hipError_t launch_mel_bw_weights(const MelBwParams& p, hipStream_t stream) {
   const long long splits = (p.B + p.b_per_split - 1) / p.b_per_split;
   const long long blocks = splits * ((p.n_mels + BW_MT - 1) / BW_MT) * (p.fp / BW_NT);
   if (blocks < 1 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((mel_bw_kernel<MEL_BW_WEIGHTS>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((mel_bw_kernel<MEL_BW_WEIGHTS, 128>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 
