@@ -436,6 +436,9 @@ __global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
         const int m = i0 + 2 * (lt + TPF * (i / R1) + (M / R1) * (i % R1));
         z[i] = (f32x2_u){xb[reflect(m, L)], xb[reflect(m + 1, L)]};
       }
+      // (left in flight, the compiler waits for them ahead of the requests above, and with them for every store before: N = 512, 300 x 176,400,
+      // hop 128, 232 -> 222 us)
+      __builtin_amdgcn_s_waitcnt(0x0f70);
     }
     t += advance;
     if (t >= T) {
