@@ -547,9 +547,10 @@ static nna_status stft_backward_core(const nna_plan* plan, const float* x_dev, l
     // unit, twice over), each with at least 64 chunks to amortise its start-up
     const long long tiles = (long long)(plan->rows_pad / nna::BW_MT) * (plan->kp / nna::BW_NT);
     const long long chunks = gpitch / nna::BW_KC;
-    // (a short batch: pieces of 16 chunks, if that is what it takes to have two workgroups per compute unit)
+    // (a short batch: pieces of eight chunks and more, if that is what it takes to have two workgroups per compute unit; a step of 6 x 44,217,
+    // n_fft 2,048: of sixteen 325 us, of eight 317; 3 x 60,000, n_fft 1,024, 80 bands: 176 -> 168)
     long long split = std::max(1LL, std::min((1024 + tiles - 1) / tiles, chunks / 64));
-    if (split * tiles < 512) split = std::max(split, std::min((512 + tiles - 1) / tiles, chunks / 16));
+    if (split * tiles < 512) split = std::max(split, std::min((512 + tiles - 1) / tiles, chunks / 8));
     Q.chunks_per_split = (chunks + split - 1) / split;
     Q.n_split = (int)((chunks + Q.chunks_per_split - 1) / Q.chunks_per_split);
   }
@@ -664,9 +665,10 @@ static nna_status cqt_backward_core(const nna_plan* plan, const float* x_dev, lo
     const long long chunks = gpitch / nna::BW_KC;
     // the tile count is whatever the supports give: aim at eight rounds of the 512 resident workgroups, so
     // that a partly filled last round costs little
-    // (a short batch: pieces of 16 chunks, if that is what it takes to have two workgroups per compute unit)
+    // (a short batch: pieces of four chunks and more, if that is what it takes to have two workgroups per compute unit: 16 x 88,200 samples, 84
+    // bins, 92 tiles of 88 chunks, in pieces of 18 78 us, of 15 72, of eleven 86; 4 x 60,000, 60 bins, sixteen chunks uncut 62, in pieces of four 42)
     long long split = std::max(1LL, std::min((4096 + (long long)Q.n_tiles - 1) / Q.n_tiles, chunks / 64));
-    if (split * Q.n_tiles < 512) split = std::max(split, std::min((512 + (long long)Q.n_tiles - 1) / Q.n_tiles, chunks / 16));
+    if (split * Q.n_tiles < 512) split = std::max(split, std::min((512 + (long long)Q.n_tiles - 1) / Q.n_tiles, chunks / 4));
     Q.chunks_per_split = (chunks + split - 1) / split;
     Q.n_split = (int)((chunks + Q.chunks_per_split - 1) / Q.chunks_per_split);
     e = nna::launch_bw_bank(Q, stream);
