@@ -299,8 +299,8 @@ __device__ __forceinline__ f32x4 load_g4(const float* __restrict__ gbuf, long lo
 //   out[q, c] = sum_r sum_j G[r, q - j] W[r, j hop + c],
 // a contraction over (row r, shift j) pairs whose A operand is G read j frames back.  Rows go in chunks
 // of CW_KC, the outer loop; for one chunk the frames q0 - j .. q0 - j + 127 of all its shifts form
-// one window of G that stays in LDS while only W tiles stream.  Each padded sample is written once
-// (the atomic add only folds the mirrored samples onto the waveform).
+// one window of G that stays in LDS while only W tiles stream.  Each padded sample is added once
+// by every part of a tile's pairs that the launch makes workgroups of (gridDim.y).
 constexpr int CW_SEG = BW_MT;             // shifts served by one window
 constexpr int CW_WIN = BW_MT + CW_SEG;    // frames in the window (128 tile rows + up to 127 shifts, rounded up)
 constexpr int CW_PA = CW_WIN + 4;         // its LDS pitch
@@ -416,9 +416,26 @@ __global__ __launch_bounds__(256, 2) void cq_wave_kernel(const BwParams P) {
   };
   using std::integral_constant;
 
+  // shifts on which rows k0 .. k0 + 15 hold taps, of this tile; this part's share of all of them, by fours
+  auto shifts_of = [&](int kc) {
+    const int2 rng = P.shift_rng[ct * P.n_kc + kc];
+    return make_int2(rng.x > j_lo ? rng.x : j_lo, rng.y < j_hi ? rng.y : j_hi);
+  };
+  int fours = 0, before = 0;
+  for (int kc = 0; kc < P.n_kc && gridDim.y > 1; ++kc) {
+    const int2 s = shifts_of(kc);
+    fours += s.y >= s.x ? (s.y - s.x + 4) / 4 : 0;
+  }
+  const int mine = fours * (int)blockIdx.y / (int)gridDim.y, mine_end = fours * ((int)blockIdx.y + 1) / (int)gridDim.y;
   for (int kc = 0; kc < P.n_kc; ++kc) {
-    const int2 rng = P.shift_rng[ct * P.n_kc + kc];  // shifts on which rows k0 .. k0 + 15 hold taps
-    const int ja = rng.x > j_lo ? rng.x : j_lo, jb = rng.y < j_hi ? rng.y : j_hi;
+    int2 rng = shifts_of(kc);
+    if (gridDim.y > 1 && rng.y >= rng.x) {
+      const int n = (rng.y - rng.x + 4) / 4, from = mine > before ? mine - before : 0, to = mine_end - before;
+      before += n;
+      if (to < n) rng.y = rng.x + 4 * to - 1;
+      rng.x += 4 * from;
+    }
+    const int ja = rng.x, jb = rng.y;
     const int k0 = kc * CW_KC;
     for (int js = ja; js <= jb; js += CW_SEG) {
       const int je = js + CW_SEG - 1 < jb ? js + CW_SEG - 1 : jb;
@@ -970,10 +987,15 @@ hipError_t launch_bw_wave(const BwParams& p, hipStream_t stream) {
       return hipErrorInvalidValue;
     const long long blocks = p.g.B * p.n_qt * p.n_ct;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    // A short batch: the (row, shift) pairs of a tile in as many parts as fill the chip, two workgroups per compute unit.  8 x 88,200 samples, 168
+    // bins, 96 tiles: 549 us whole, 244 in four, 176 in six, 190 in eight; 64 tiles 179, 60 in four, 63 in eight; 60 tiles of 252 bins 1,193, 403 in
+    // six, 322 in eight; 128 tiles 113, 66 in four, 83 in six; 8 tiles 100, 20 in twelve; 480 tiles 193, 196 in two.
+    const int parts = (int)std::max(1LL, std::min(16LL, 512 / blocks));
+    const dim3 grid((unsigned)blocks, (unsigned)parts);
     if (p.g.hop % BW_NT == 0 && (long long)p.n_shift * p.g.hop <= p.kp)
-      hipLaunchKernelGGL(cq_wave_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL(cq_wave_kernel<true>, grid, dim3(256), 0, stream, p);
     else
-      hipLaunchKernelGGL(cq_wave_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL(cq_wave_kernel<false>, grid, dim3(256), 0, stream, p);
     return hipGetLastError();
   }
   const long long blocks = (p.gpitch / BW_MT) * (p.kp / BW_NT);

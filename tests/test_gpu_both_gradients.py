@@ -20,3 +20,24 @@ def test_both_against_each(n_fft, hop, B, L):
     # the same products, summed onto the output piece by piece in any order: up to 44 pieces, half an ulp of the running sum each
     for got, ref in ((gw, nb.nna_stft_backward(plan, x, gout, want_gx=False)[0]), (gx, nb.nna_stft_backward(plan, x, gout, want_gw=False)[1])):
         assert (got - ref).abs().max() <= 44 * 2.0 ** -24 * ref.abs().max()
+
+
+# tiles of the waveform gradient in parts: 16 of one tile, of few, of kernels of many hops; hops that are no multiple of 128
+@pytest.mark.parametrize("sr,hop,fmin,n_bins,bpo,B,L", [(8000, 128, 300.0, 5, 12, 1, 4001), (22050, 512, 65.4, 60, 12, 2, 30001), (16000, 256, 60.0, 84, 24, 3, 20000),
+                                                        (16000, 96, 80.0, 30, 12, 2, 9000)])
+def test_waveform_gradient_in_parts(sr, hop, fmin, n_bins, bpo, B, L):
+    """A few waveforms' gradients, alone and in a batch whose tiles are taken whole: the same products, added in up to 16 parts."""
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] waveform gradient in parts {sr} {hop} {n_bins} {B}x{L}", file=sys.stderr, flush=True)
+    plan = nb.nna_plan_trainable(nb.nna_plan_cqt(sr=sr, hop=hop, fmin=fmin, n_bins=n_bins, bins_per_octave=bpo, fmt=nb.NNA_OUT_COMPLEX, device=0))
+    gen = torch.Generator().manual_seed(hop + L)
+    L = max(L, plan.info()["taps"] // 2 + 3)
+    x = torch.randn((B, L), generator=gen).cuda()
+    gout = torch.randn(tuple(nb.nna_cqt(plan, x).shape), generator=gen).cuda()
+    few = nb.nna_cqt_backward(plan, x, gout, want_gw=False)[1]
+    n = 520 // B + 1
+    many = nb.nna_cqt_backward(plan, x.repeat(n, 1), gout.repeat(n, 1, 1), want_gw=False)[1]
+    # sums of up to 2 n_bins x 100 shifts in chains: a chain of n roundings is off by sqrt(n) 2^-24 of its terms' norm
+    assert (few - many[:B]).abs().max() <= 2e-6 * many.abs().max()
+    assert (few - many[-B:]).abs().max() <= 2e-6 * many.abs().max()
