@@ -499,19 +499,25 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
                             long long out_wave_stride, int row_offset, nna::CqlParams& P, void* hip_stream, void* workspace = nullptr,
                             size_t workspace_bytes = 0) {
   int blocks, j0, j1;
-  const long long floats = coordinates_of(sub, T, blocks, j0, j1), at_once = workspace ? (long long)(workspace_bytes / 4) / floats : 0;
+  const long long floats = coordinates_of(sub, T, blocks, j0, j1);
+  long long at_once = workspace ? (long long)(workspace_bytes / 4) / floats : 0;
   if (at_once > 0 && at_once < B) {
-    // as many waveforms at a time as the workspace holds the coordinates of, in parts of equal size
+    // As many waveforms at a time as the workspace holds the coordinates of, in parts of equal size.  A part too short for this kernel's
+    // tiles: all of them in one launch, which needs no workspace.
     const long long parts = (B + at_once - 1) / at_once;
-    for (long long i = 0; i < parts; ++i) {
-      const long long b0 = B * i / parts, n = B * (i + 1) / parts - b0;
-      nna::CqlParams Q;
+    nna::CqlParams Q;
+    auto shape = [&](long long n) {
       std::memset(&Q, 0, sizeof(Q));
-      if (!shape_lowrank(sub, n * T, T, Q)) return fail(NNA_ERR_UNSUPPORTED, "hop-block tiles");
+      return shape_lowrank(sub, n * T, T, Q);
+    };
+    if (!shape(B / parts) || !shape((B + parts - 1) / parts)) at_once = 0;
+    for (long long i = 0; at_once && i < parts; ++i) {
+      const long long b0 = B * i / parts, n = B * (i + 1) / parts - b0;
+      shape(n);
       const nna_status s = run_conv_lowrank(sub, x + b0 * L, n, L, T, out + b0 * out_wave_stride, out_wave_stride, row_offset, Q, hip_stream, workspace, workspace_bytes);
       if (s != NNA_OK) return s;
     }
-    return NNA_OK;
+    if (at_once) return NNA_OK;
   }
   P.g = make_geom(sub, x, B, L, T);
   P.u = reinterpret_cast<const float4*>(sub->d_lu);
