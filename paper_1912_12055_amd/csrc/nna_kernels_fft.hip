@@ -489,6 +489,12 @@ __global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
   [[maybe_unused]] int step = 0;
   int n_done = 0;  // n_wave times the tiles this wave has computed
 
+  // What is in flight here counts as in flight at the head of every step, where the compiler then waits for all requests, and with them for
+  // the stores of the step before.  Waited for once, before the loop: 1 x 3,969,031 samples, N = 1,024, complex, 31.0 -> 29.6 us; Mel 64 x
+  // 110,250, N = 2,048, 38.4 -> 37.0; 1,770 x 80,000, N = 4,096, 512 bands, 1.59 -> 1.52 ms; magnitudes, N = 256, 500 x 176,400, 436 -> 397 us.
+  // Longer rows are the exception: waves that run ahead of their stores spread the halves of a line over more time, and rows that begin anywhere
+  // in a line take 1.51 ms for 1.35 (N = 2,048, 1,770 x 345 frames) and 1.27 for 0.91 (N = 4,096, 500 x 345); of 352 frames 1.19 for 1.33.
+  if constexpr (MODE == FFT_MODE_MEL || M < 1024) __builtin_amdgcn_s_waitcnt(0x0f70);
   float *cur = tile, *old = tile + P.buf_words;
   for (long long tile_i = lo; tile_i < hi; tile_i += stride) {
     if (FLAGS && n_done > n_wave) wait(written, n_done - n_wave);  // the buffer's last tile
