@@ -30,7 +30,7 @@ PEAK_F16_MFMA_TFLOPS = 2500.0  # MI355X dense fp16 / bf16 matrix peak
 PEAK_SPLIT_TFLOPS = PEAK_F16_MFMA_TFLOPS / 6  # ... of float32 products as six of bfloat16
 PEAK_HBM_GBS = 8000.0
 # the kernel each transform of the step launches (names as rocprofv3 prints them)
-KERNELS = {"stft": "fft_kernel<1024, ..., POWER>", "mel": "fft_kernel<1024, ..., MEL>", "cqt": "cqt_lowrank_kernel<4, 4, true>"}
+KERNELS = {"stft": "fft_kernel<1024, ..., POWER>", "mel": "fft_kernel<1024, ..., MEL>", "cqt": "cqt_project_kernel<4, 6, true>, cqt_lowrank_kernel<4, 1, false, true, false>"}
 
 
 def main() -> int:

@@ -28,12 +28,14 @@
 // blocks are off by 3e-7 at most.  Against 64 bits the bfloat16 form's errors are 0.5 .. 0.9 of the float32 instruction's, eight
 // configurations, six signals each.
 //
-// Bound by no one pipe at the batch below: the samples' splits keep the vector ALUs 52 % busy, the matrix pipe is at 39 %; a short batch
-// by latency, a workgroup or two per CU.  1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms
+// In one launch bound by no one pipe at the batch below: the samples' splits keep the vector ALUs 52 % busy, the matrix pipe is at 39 %; a
+// short batch by latency, a workgroup or two per CU.  With a workspace, where that pays, as two: coordinates first, the short kernels beside
+// them (pipe 48 % busy, vector ALUs 43 %), then the second stage (62, 59 %).  1,770 x 176,400 samples, 168 bins of 24 per octave (MI355X): 24.5 ms
 // folded about the centres, 8.25 here in float32, 6.59 in bfloat16 with every coordinate split by each frame that reads it, now 5.74;
 // 16 x 220,500, 84 bins of 12 per octave: 300 -> 67.8 -> 53.8 us; the dense composed kernels of the frequency-domain layer (16 x
 // 220,500, 16,384 taps): 566 -> 183 -> 138 us.  With the short kernels by tiles of nna_short.h (the direct items read four row blocks' weights for
-// every 16 frames, and the loads' issue bound them): 5.81 -> 5.12 ms, 58 -> 46 us.
+// every 16 frames, and the loads' issue bound them): 5.81 -> 5.12 ms, 58 -> 46 us.  In two
+// launches: the batch 5.2 -> 4.7 ms, the dense kernels 134 -> 81 us.
 #include <type_traits>
 
 #include "nna_short.h"

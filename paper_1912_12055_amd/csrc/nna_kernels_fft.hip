@@ -18,8 +18,8 @@
 // 1,770 x 176,400 samples, N = 2,048, hop 512 (MI355X): magnitudes 10.1 ms contracted, 2.20 with a tile computed, then stored
 // between two barriers and neighbouring tiles 29 us apart, 1.51 with samples requested word by word, now 1.35 (either way 3.66 GB are written for
 // 2.50: runs of half a line; writing them so, with nothing computed, takes 1.38 by itself, in runs that begin at 64 bytes 0.83);
-// N = 1,024, hop 256, complex: 4.02 -> 2.35.  Mel, 64 x 110,250, 128 bands: 808 us contracted, 48 -> 39 -> 38; 1,770 x 80,000,
-// N = 4,096, 512 bands: 34.9 ms, 2.02 -> 1.72 -> 1.58.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles read from the caches for
+// N = 1,024, hop 256, complex: 4.02 -> 2.35.  Mel, 64 x 110,250, 128 bands: 808 us contracted, 48 -> 39 -> 37; 1,770 x 80,000,
+// N = 4,096, 512 bands: 34.9 ms, 2.02 -> 1.72 -> 1.53.  4 x 22,050: 300 -> 10 us.  Tried: window and twiddles read from the caches for
 // every frame with four waves per SIMD (2.85 ms: the vector memory path saturates), from LDS with four waves per SIMD (spills,
 // 1.87 ms), three waves per SIMD (spills, 4.3 ms), the tile stored by two workgroups of four waves (runs of 32 bytes, 2.04 ms),
 // frames in a ring from which every row is written in segments that begin at 64 bytes (2.7 GB written, but waves that meet every step: 1.47 ms).
