@@ -432,6 +432,21 @@ def nna_cqt_in_workspace(plan: Plan, x, workspace, out=None, stream=None):
     return _run(fn, plan, x, out, stream)
 
 
+def _memory_on(stream, need: int, device):
+    """`need` bytes of the stream a call runs on (None: torch's current one), or None where they can't be that stream's alone: what its
+    allocator hands out again when the call has returned is used behind the call."""
+    import torch
+
+    if stream is None:
+        return torch.empty(need, dtype=torch.uint8, device=device)
+    if stream in (1, 2):  # HIP's names for the default stream and for every thread's own: no streams that torch has an allocator for
+        return None
+    # (ExternalStream takes 0, the default stream's handle, for "none given" and is then another stream, of torch's pool)
+    on = torch.cuda.ExternalStream(stream, device=device) if stream else torch.cuda.default_stream(device)
+    with torch.cuda.stream(on):
+        return torch.empty(need, dtype=torch.uint8, device=device)
+
+
 def _run_one_rate(cfn, plan, x, out, stream):
     """`cfn`, in a workspace where that is the faster way: memory of the stream the call runs on, back with its allocator
     when the call returns."""
@@ -442,12 +457,10 @@ def _run_one_rate(cfn, plan, x, out, stream):
         if not need:
             return cfn(handle, xp, B, L, op, st)
         try:
-            if stream is None:
-                workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-            else:
-                with torch.cuda.stream(torch.cuda.ExternalStream(st, device=x.device)):
-                    workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+            workspace = _memory_on(stream, need, x.device)
         except torch.OutOfMemoryError:
+            workspace = None
+        if workspace is None:
             return cfn(handle, xp, B, L, op, st)
         return lib().nna_cqt_in_workspace(handle, xp, B, L, op, workspace.data_ptr(), need, st)
 

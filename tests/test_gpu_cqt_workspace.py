@@ -80,3 +80,28 @@ def test_memory_that_cannot_serve(nb):
         nb.nna_cqt_workspace(nb.nna_plan_stft(n_fft=256, hop=64, device=0), 2, 4000)
     with pytest.raises(RuntimeError):
         nb.nna_cqt_workspace(plan, 2, 100)
+
+
+def test_memory_of_the_calls_stream(nb):
+    """No stream, the default stream's handle, a side stream's: the same outputs, and the same memory call after call."""
+    import torch
+    x = torch.randn((4, 60001), generator=torch.Generator().manual_seed(2)).cuda()
+    side = torch.cuda.Stream()
+    for make, call in ((nb.nna_plan_cqt, nb.nna_cqt), (nb.nna_plan_cqt1992, nb.nna_cqt1992)):
+        plan = make(sr=44100, n_bins=168, bins_per_octave=24, device=0) if call is nb.nna_cqt else make(n_bins=84, device=0)
+        xs = x if nb.nna_cqt_workspace(plan, *x.shape) else torch.randn((20, 176400), generator=torch.Generator().manual_seed(3)).cuda()
+        assert nb.nna_cqt_workspace(plan, *xs.shape) > 0
+        print(f"[case] cqt memory by stream {call.__name__} {tuple(xs.shape)}", file=sys.stderr, flush=True)
+        ref = call(plan, xs)
+        out = torch.empty_like(ref)
+        torch.cuda.synchronize()
+        for stream in (0, side.cuda_stream):
+            reserved = []
+            for _ in range(40):  # (more than torch's pool has streams)
+                out.fill_(float("nan"))
+                torch.cuda.current_stream().synchronize()
+                call(plan, xs, out=out, stream=stream)
+                torch.cuda.synchronize()
+                assert torch.equal(out, ref)
+                reserved.append(torch.cuda.memory_reserved())
+            assert len(set(reserved)) == 1, stream
