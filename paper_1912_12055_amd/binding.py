@@ -447,14 +447,14 @@ def _memory_on(stream, need: int, device):
         return torch.empty(need, dtype=torch.uint8, device=device)
 
 
-def _run_one_rate(cfn, plan, x, out, stream):
+def _run_one_rate(cfn, kind, plan, x, out, stream):
     """`cfn`, in a workspace where that is the faster way: memory of the stream the call runs on, back with its allocator
     when the call returns."""
     import torch
 
     def fn(handle, xp, B, L, op, st):
         need = nna_cqt_workspace(plan, B, L)
-        if not need:
+        if not need or plan.constants()[0] != kind:  # (nna_cqt_in_workspace takes either kind; `cfn` refuses the other's)
             return cfn(handle, xp, B, L, op, st)
         try:
             workspace = _memory_on(stream, need, x.device)
@@ -469,12 +469,12 @@ def _run_one_rate(cfn, plan, x, out, stream):
 
 def nna_cqt1992(plan: Plan, x, out=None, stream=None):
     """out[B, n_bins, T] = constant-Q spectrogram of x[B, L] with frequency-domain kernels."""
-    return _run_one_rate(lib().nna_cqt1992, plan, x, out, stream)
+    return _run_one_rate(lib().nna_cqt1992, NNA_KIND_CQT1992, plan, x, out, stream)
 
 
 def nna_cqt(plan: Plan, x, out=None, stream=None):
     """out[B, n_bins, T] = constant-Q spectrogram of x[B, L]."""
-    return _run_one_rate(lib().nna_cqt, plan, x, out, stream)
+    return _run_one_rate(lib().nna_cqt, NNA_KIND_CQT, plan, x, out, stream)
 
 
 # ---- trainable Fourier kernels -------------------------------------------------------------------

@@ -102,3 +102,10 @@ def test_no_memory_left(calls, monkeypatch):
     monkeypatch.setattr(torch, "empty", empty)
     nb.nna_cqt(calls["plan"], calls["x"])
     assert calls["calls"] == [("nna_cqt", 0x700, None)]
+
+
+def test_a_plan_of_the_other_kind_goes_to_the_entry_point_that_refuses_it(calls):
+    for kind, call in ((nb.NNA_KIND_CQT1992, nb.nna_cqt), (nb.NNA_KIND_CQT, nb.nna_cqt1992)):
+        calls["kind"] = kind
+        call(calls["plan"], calls["x"])
+    assert [c[0] for c in calls["calls"]] == ["nna_cqt", "nna_cqt1992"]

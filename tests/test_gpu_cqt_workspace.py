@@ -105,3 +105,12 @@ def test_memory_of_the_calls_stream(nb):
                 assert torch.equal(out, ref)
                 reserved.append(torch.cuda.memory_reserved())
             assert len(set(reserved)) == 1, stream
+
+
+def test_plans_of_the_other_kind_are_refused(nb):
+    import torch
+    x = torch.randn((16, 60001), generator=torch.Generator().manual_seed(4)).cuda()
+    for plan, call in ((nb.nna_plan_cqt1992(n_bins=84, device=0), nb.nna_cqt), (nb.nna_plan_cqt(sr=44100, n_bins=168, bins_per_octave=24, device=0), nb.nna_cqt1992)):
+        with pytest.raises(nb.NnaError) as e:
+            call(plan, x)
+        assert e.value.status == nb.NNA_ERR_INVALID_ARG
