@@ -437,14 +437,27 @@ def _memory_on(stream, need: int, device):
     allocator hands out again when the call has returned is used behind the call."""
     import torch
 
-    if stream is None:
-        return torch.empty(need, dtype=torch.uint8, device=device)
+    if stream is None and device.index == torch.cuda.current_device():
+        return _outlives_capture(torch.empty(need, dtype=torch.uint8, device=device))
     if stream in (1, 2):  # HIP's names for the default stream and for every thread's own: no streams that torch has an allocator for
         return None
     # (ExternalStream takes 0, the default stream's handle, for "none given" and is then another stream, of torch's pool)
-    on = torch.cuda.ExternalStream(stream, device=device) if stream else torch.cuda.default_stream(device)
+    on = (torch.cuda.current_stream(device) if stream is None else
+          torch.cuda.ExternalStream(stream, device=device) if stream else torch.cuda.default_stream(device))
     with torch.cuda.stream(on):
-        return torch.empty(need, dtype=torch.uint8, device=device)
+        return _outlives_capture(torch.empty(need, dtype=torch.uint8, device=device))
+
+
+def _outlives_capture(memory):
+    """`memory`, or None where the current stream is being captured and `memory` is not of a graph's own pool: a graph that torch knows
+    nothing of would be replayed when its allocator has long handed the memory to others."""
+    import torch
+
+    if not torch.cuda.is_current_stream_capturing():
+        return memory
+    at = memory.data_ptr()
+    pools = [s["segment_pool_id"] for s in torch.cuda.memory_snapshot() if s["address"] <= at < s["address"] + s["total_size"]]
+    return memory if pools and tuple(pools[0]) != (0, 0) else None
 
 
 def _run_one_rate(cfn, kind, plan, x, out, stream):

@@ -76,6 +76,9 @@ def calls(monkeypatch):
     monkeypatch.setattr(torch.cuda, "default_stream", lambda device=None: DefaultStream())
     monkeypatch.setattr(torch.cuda, "stream", on)
     monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: type("Current", (), dict(cuda_stream=seen["current"])))
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
     seen["plan"], seen["x"] = Plan(), X()
     return seen
 
@@ -109,3 +112,20 @@ def test_a_plan_of_the_other_kind_goes_to_the_entry_point_that_refuses_it(calls)
         calls["kind"] = kind
         call(calls["plan"], calls["x"])
     assert [c[0] for c in calls["calls"]] == ["nna_cqt", "nna_cqt1992"]
+
+
+# a graph that torch captures has a pool of its own, one captured by other means has not
+@pytest.mark.parametrize("pool,name", [((0, 3), "nna_cqt_in_workspace"), ((0, 0), "nna_cqt")])
+@pytest.mark.parametrize("stream", [None, 0x5550])
+def test_under_capture(calls, monkeypatch, stream, pool, name):
+    segments = [dict(address=1 << 12, total_size=1 << 12, segment_pool_id=(0, 9)), dict(address=1 << 19, total_size=1 << 20, segment_pool_id=pool)]
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", lambda: segments)
+    nb.nna_cqt(calls["plan"], calls["x"], stream=stream)
+    assert [c[0] for c in calls["calls"]] == [name]
+
+
+def test_current_stream_of_another_device(calls, monkeypatch):
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 1)
+    nb.nna_cqt(calls["plan"], calls["x"])
+    assert calls["calls"] == [("nna_cqt_in_workspace", 0x700, 0x700)]

@@ -114,3 +114,51 @@ def test_plans_of_the_other_kind_are_refused(nb):
         with pytest.raises(nb.NnaError) as e:
             call(plan, x)
         assert e.value.status == nb.NNA_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("by_torch", [True, False])
+def test_replays(nb, by_torch):
+    """A call in a graph, captured through torch or past it, replayed between eager work that takes and fills memory on every stream of the call."""
+    import ctypes
+
+    import torch
+    print(f"[case] cqt memory in a graph {by_torch}", file=sys.stderr, flush=True)
+    plan = nb.nna_plan_cqt1992(n_bins=84, device=0)
+    x = torch.randn((2, 60001), generator=torch.Generator().manual_seed(5)).cuda()
+    need = nb.nna_cqt_workspace(plan, *x.shape)
+    assert need > 0
+    out = nb.nna_cqt1992(plan, x)
+    side = torch.cuda.Stream()
+    nb.nna_cqt1992(plan, x, out=out, stream=side.cuda_stream)
+    torch.cuda.synchronize()
+    if by_torch:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            nb.nna_cqt1992(plan, x, out=out)
+        replay = graph.replay
+    else:
+        hip, handle = nb.lib(), ctypes.c_void_p(side.cuda_stream)  # (the library brings HIP's runtime along)
+        graph, run = ctypes.c_void_p(), ctypes.c_void_p()
+        assert hip.hipStreamBeginCapture(handle, 2) == 0
+        nb.nna_cqt1992(plan, x, out=out, stream=side.cuda_stream)
+        assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+        assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)) == 0
+
+        def replay():
+            assert hip.hipGraphLaunch(run, handle) == 0
+    for rep in range(3):
+        x.copy_(torch.randn(x.shape, generator=torch.Generator().manual_seed(6 + rep)))
+        for stream in (torch.cuda.current_stream(), side):
+            with torch.cuda.stream(stream):
+                taken = [torch.full((need // 4,), float("nan"), device="cuda:0") for _ in range(4)]
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        replay()
+        torch.cuda.synchronize()
+        # (a graph captured past torch runs in one launch, whose sums are added in another order)
+        ref = nb.nna_cqt1992(plan, x) if by_torch else _one_launch(nb, plan, x)
+        assert torch.equal(out, ref), rep
+        assert all(bool(t.isnan().all()) for t in taken)
+        del taken
+    if not by_torch:
+        assert hip.hipGraphExecDestroy(run) == 0 and hip.hipGraphDestroy(graph) == 0
