@@ -406,8 +406,10 @@ __global__ __launch_bounds__(256, 2) void split_wave_kernel(const BwParams P) {
   wave_tile(P, blockIdx.x, lds);
 }
 
-// Both gradients of a step in one launch: neither's tiles fill a short batch's chip.  A whole step, 16 x 44,217 samples, n_fft 2,048: 435 -> 417
-// us (432 workgroups, uncut, at once); 2 x 30,000: 280 -> 259; n_fft 512, 20 x 60,000: 177 -> 156; n_fft 4,096, 2 x 30,000: 586 -> 556.
+// Both gradients of a step in one launch: neither's tiles fill a short batch's chip.  The backward call, power, against two launches: 16 x
+// 44,217 samples, n_fft 2,048, 300 -> 293 us; 2 x 30,000 180 -> 163; n_fft 512, 20 x 60,000 166 -> 153; n_fft 4,096, 4 x 30,000 358 -> 347.  The
+// pieces are those of the launches by themselves: uncut where all tiles fill the chip once, a bank of few tiles is a few workgroups' chain over
+// all frames (n_fft 512, 30 x 60,000: 184 -> 791 us) and its sums are up to five times further from 64 bits.
 __global__ __launch_bounds__(256, 2) void split_both_kernel(const BwParams bank, const BwParams wave, unsigned n_wave) {
   __shared__ __attribute__((aligned(16))) unsigned lds[2 * 3 * SP_PLANE];
   if (blockIdx.x < n_wave)
@@ -468,24 +470,14 @@ hipError_t launch_split_wave(BwParams p, hipStream_t stream) {
 
 hipError_t launch_split_both(const BwParams& p, hipStream_t stream) {
   clear_stale_error();
-  BwParams bank = p, wave = p;
-  const long long chunks = (2 * p.n_half + SP_KC - 1) / SP_KC, bank_tiles = (long long)(p.rows_pad / BW_MT) * (p.kp / BW_NT);
-  const long long wave_tiles = p.gpitch / BW_MT * (p.kp / BW_NT);
-  long long n_wave = shape_wave(wave), n_bank = bank_tiles * bank.n_split;
-  if (bank_tiles + wave_tiles >= 384 && bank_tiles + wave_tiles <= 512) {
-    // uncut they fill the chip once, two to a compute unit (256 and 176 of them: the step 417 us, bank halved 431, both halved 434)
-    bank.n_split = 1;
-    bank.chunks_per_split = p.gpitch / BW_KC;
-    wave.chunks_per_split = chunks;
-    n_wave = wave_tiles;
-    n_bank = bank_tiles;
-  }
+  BwParams wave = p;
+  const long long n_wave = shape_wave(wave), n_bank = (long long)(p.rows_pad / BW_MT) * (p.kp / BW_NT) * p.n_split;
   if (p.tiles || n_wave <= 0 || n_bank <= 0 || n_wave + n_bank > 0x7fffffffLL) return hipErrorInvalidValue;
   if (n_wave + n_bank > 1536) {  // each fills the chip by itself (1,920 workgroups: the step 1,523 us in two launches, 1,531 in one)
     const hipError_t e = launch_split_bank(p, stream);
     return e == hipSuccess ? launch_split_wave(p, stream) : e;
   }
-  hipLaunchKernelGGL(split_both_kernel, dim3((unsigned)(n_wave + n_bank)), dim3(256), 0, stream, bank, wave, (unsigned)n_wave);
+  hipLaunchKernelGGL(split_both_kernel, dim3((unsigned)(n_wave + n_bank)), dim3(256), 0, stream, p, wave, (unsigned)n_wave);
   return hipGetLastError();
 }
 

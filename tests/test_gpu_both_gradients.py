@@ -1,4 +1,5 @@
-"""Training steps that want both gradients of an STFT stage at once, in one launch (uncut, in pieces) or two, against the calls that want one."""
+"""Training steps that want both gradients of an STFT stage at once, in one launch or two, against the calls that want one
+and against 64 bits."""
 import sys
 
 import pytest
@@ -6,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# n_fft, hop, B, L: 256 + 176 tiles uncut; a bank of few tiles in pieces beside a wave of few; more than one launch takes; one frame
+# n_fft, hop, B, L: 256 + 176 tiles; a bank of few tiles in pieces beside a wave of few; more than one launch takes; one frame
 @pytest.mark.parametrize("n_fft,hop,B,L", [(2048, 512, 16, 44217), (512, 160, 5, 9001), (1024, 256, 3, 5001), (512, 128, 120, 40001), (256, 256, 1, 129)])
 def test_both_against_each(n_fft, hop, B, L):
     import torch
@@ -41,3 +42,40 @@ def test_waveform_gradient_in_parts(sr, hop, fmin, n_bins, bpo, B, L):
     # sums of up to 2 n_bins x 100 shifts in chains: a chain of n roundings is off by sqrt(n) 2^-24 of its terms' norm
     assert (few - many[:B]).abs().max() <= 2e-6 * many.abs().max()
     assert (few - many[-B:]).abs().max() <= 2e-6 * many.abs().max()
+
+
+def _gradients_64(x, W, gout, hop):
+    """Of complex output: the bank's and the waveform's gradient, in 64 bits."""
+    import torch
+    (B, L), K, T = x.shape, W.shape[1], gout.shape[2]
+    at = torch.arange(T, device=x.device)[:, None] * hop + torch.arange(K, device=x.device) - K // 2
+    at = at.abs()
+    at = torch.where(at >= L, 2 * (L - 1) - at, at)
+    gw, gx = torch.zeros(W.shape, dtype=torch.float64, device=x.device), torch.zeros(x.shape, dtype=torch.float64, device=x.device)
+    for b in range(B):
+        g = gout[b].double()
+        gw += g @ x[b].double()[at]
+        gx[b].index_add_(0, at.reshape(-1), (g.T @ W.double()).reshape(-1))
+    gw[[1, -1]] = 0  # the imaginary kernels of bins 0 and n_fft / 2 are zero and no parameters
+    return gw, gx
+
+
+# 256 + 176 tiles of 44 and 64 chunks; 16 + 440 of 440 and 16; 64 + 448 of 192 and 32; 6 + 378 of 504 and 8
+@pytest.mark.parametrize("n_fft,hop,B,L", [(2048, 512, 16, 44217), (512, 128, 30, 60000), (1024, 256, 26, 60000), (256, 128, 52, 40001)])
+def test_sums_as_short_as_alone(n_fft, hop, B, L):
+    """Neither gradient's sums are longer than those of the call that wants it alone: no further from 64 bits."""
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] both gradients against 64 bits n_fft={n_fft} {B}x{L}", file=sys.stderr, flush=True)
+    gen = torch.Generator().manual_seed(n_fft + B)
+    plan = nb.nna_plan_trainable(nb.nna_plan_stft(n_fft=n_fft, hop=hop, fmt=nb.NNA_OUT_COMPLEX, device=0))
+    x = torch.randn((B, L), generator=gen).cuda()
+    gout = torch.randn(tuple(nb.nna_stft(plan, x).shape), generator=gen).cuda()
+    ref = _gradients_64(x, nb.nna_plan_get_bank(plan), gout, hop)
+    both = nb.nna_stft_backward(plan, x, gout)
+    alone = nb.nna_stft_backward(plan, x, gout, want_gx=False)[0], nb.nna_stft_backward(plan, x, gout, want_gw=False)[1]
+    for k in range(2):
+        far = [float((g.double() - ref[k]).norm() / ref[k].norm()) for g in (both[k], alone[k])]
+        print(f"[error] {'gw' if k == 0 else 'gx'} both {far[0]:.3e} alone {far[1]:.3e}", file=sys.stderr, flush=True)
+        # the same partial sums (of up to 176 x 2^-24 / sqrt(3) of their norm), added onto the output in any order: a tenth for that
+        assert far[0] <= 1.1 * far[1] and far[1] < 2e-6
