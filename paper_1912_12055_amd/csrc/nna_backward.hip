@@ -1272,9 +1272,9 @@ static nna_status mel_backward(const nna_plan* plan, const float* x_dev, long lo
   if (gmelw_dev) {
     e = nna::launch_fill_zero(gmelw_dev, (long long)plan->n_mels * F, stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
-    // about 512 workgroups share the output tiles, each of which they add to (1,024: 112 us for 92 at 64 x 110,250, 128 bands; 128: 135)
+    // about 1,024 workgroups share the output tiles
     const long long tiles = (long long)((plan->n_mels + nna::BW_MT - 1) / nna::BW_MT) * (plan->fp / nna::BW_NT);
-    const long long splits = std::max(1LL, std::min(B, (512 + tiles - 1) / tiles));
+    const long long splits = std::max(1LL, std::min(B, (1024 + tiles - 1) / tiles));
     Q.b_per_split = (int)((B + splits - 1) / splits);
     e = nna::launch_mel_bw_weights(Q, stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");

@@ -663,20 +663,17 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
     const int m0 = (tile / n_nt) * BW_MT, k0 = (tile % n_nt) * BW_NT;  // mels, bins of this tile
     const long long b_begin = split * P.b_per_split;
     const long long b_end = b_begin + P.b_per_split < P.B ? b_begin + P.b_per_split : P.B;
-    f32x4 ra[4], rb[4];
-    auto request = [&](long long b, int t0) {
+    for (long long b = b_begin; b < b_end; ++b) {
       const float* gb = P.g + b * (long long)P.n_mels * P.T;
       const float* pb = P.P + b * (long long)P.F * P.T;
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int row = (tid >> 3) + 32 * p;  // output index: mel (A), bin (B); contraction = frames
-        ra[p] = load4_guarded(m0 + row < P.n_mels ? gb + (long long)(m0 + row) * P.T : nullptr, t0 + 4 * (tid & 7), P.T);
-        rb[p] = load4_guarded(k0 + row < P.F ? pb + (long long)(k0 + row) * P.T : nullptr, t0 + 4 * (tid & 7), P.T);
-      }
-    };
-    if (b_begin < b_end) request(b_begin, 0);
-    for (long long b = b_begin; b < b_end; ++b) {
       for (int t0 = 0; t0 < P.T; t0 += BW_KC) {
+        f32x4 ra[4], rb[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const int row = (tid >> 3) + 32 * p;  // output index: mel (A), bin (B); contraction = frames
+          ra[p] = load4_guarded(m0 + row < P.n_mels ? gb + (long long)(m0 + row) * P.T : nullptr, t0 + 4 * (tid & 7), P.T);
+          rb[p] = load4_guarded(k0 + row < P.F ? pb + (long long)(k0 + row) * P.T : nullptr, t0 + 4 * (tid & 7), P.T);
+        }
         __syncthreads();
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -684,8 +681,6 @@ __global__ __launch_bounds__(256, 2) void mel_bw_kernel(const MelBwParams P) {
           *reinterpret_cast<f32x4*>(ldsB + ((tid >> 3) + 32 * p) * BW_PA_M + 4 * (tid & 7)) = rb[p];
         }
         __syncthreads();
-        if (t0 + BW_KC < P.T) request(b, t0 + BW_KC);
-        else if (b + 1 < b_end) request(b + 1, 0);
         multiply();
       }
     }

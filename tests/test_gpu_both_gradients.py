@@ -79,3 +79,26 @@ def test_sums_as_short_as_alone(n_fft, hop, B, L):
         print(f"[error] {'gw' if k == 0 else 'gx'} both {far[0]:.3e} alone {far[1]:.3e}", file=sys.stderr, flush=True)
         # the same partial sums (of up to 176 x 2^-24 / sqrt(3) of their norm), added onto the output in any order: a tenth for that
         assert far[0] <= 1.1 * far[1] and far[1] < 2e-6
+
+
+# 9 and 3 output tiles: a workgroup's share is one waveform
+@pytest.mark.parametrize("n_fft,hop,n_mels,B,L", [(2048, 512, 128, 64, 110250), (512, 128, 64, 200, 40000)])
+def test_filterbank_sums_of_one_waveform(n_fft, hop, n_mels, B, L):
+    """The filterbank's gradient of a batch: every waveform's frames summed by themselves, no further from 64 bits than those sums and their addition."""
+    import torch
+    from paper_1912_12055_amd import binding as nb
+    print(f"[case] filterbank gradient against 64 bits n_fft={n_fft} {B}x{L}", file=sys.stderr, flush=True)
+    plan = nb.nna_plan_trainable(nb.nna_plan_mel(n_fft=n_fft, hop=hop, n_mels=n_mels, device=0))
+    gen = torch.Generator().manual_seed(B)
+    x = torch.randn((B, L), generator=gen).cuda()
+    gout = torch.randn((B,) + tuple(nb.nna_out_shape(plan, B, L)), generator=gen).cuda()
+    window = torch.hann_window(n_fft, dtype=torch.float64, device="cuda")
+    ref, alone = 0, 0
+    for b in range(B):
+        padded = torch.nn.functional.pad(x[None, b:b + 1].double(), (n_fft // 2, n_fft // 2), mode="reflect")[0, 0]
+        ref = ref + gout[b].double() @ torch.fft.rfft(padded.unfold(0, n_fft, hop) * window).abs().square()
+        alone = alone + nb.nna_mel_backward(plan, x[b:b + 1], gout[b:b + 1], want_gw=False, want_gx=False)[0].double()
+    batch, alone = (float((g.double() - ref).norm() / ref.norm()) for g in (nb.nna_mel_backward(plan, x, gout, want_gx=False)[0], alone))
+    print(f"[error] batch {batch:.3e} one by one {alone:.3e}", file=sys.stderr, flush=True)
+    # adding B sums one after the other: a rounding of up to 2^-24 (a third of that squared on average) of what has been added, i / B of the whole squared
+    assert batch ** 2 <= alone ** 2 + 2.0 ** -48 * B / 6 and batch < 2e-6
