@@ -468,12 +468,26 @@ long long coordinates_of(const nna_plan* sub, long long T, int& blocks, int& j0,
   return floats;
 }
 
+// The launch of the first stage by itself: 16-hop-block parts of a tile, the parts that the row blocks of all bases are dealt to.  32
+// hop-blocks and twelve row blocks a workgroup fill the chip sooner (16 x 220,500 samples, 84 dense kernels: 33 us; 24 row blocks 41, 64
+// hop-blocks 42, both 50); twice as many of both read the weights half as often
+void shape_project(long long rows, int blocks, int& nb, int& groups) {
+  nb = rows >= 64 * 512 ? 4 : 2;
+  const int each = nb == 4 ? 24 : 12;
+  groups = (blocks + each - 1) / each;
+}
+
 // What a call may use of a workspace, waveforms at a time, up to 256 MiB, what the last-level cache holds (1,770 x 176,400 samples, 168 bins: 64 MB
-// 5.12 ms, 128 4.87, 256 4.87, 1 GB 4.76); zero: it does as well without.  Two launches instead of one, where nothing runs beside the
-// items with a basis (time over the one launch's: 16 x 220,500 samples, 84 kernels of 16,384 taps 0.62, 2 x 60,000 0.70, 60 x 220,500 0.78), where
-// the first stage computes so much of one tile for its neighbours again that sharing it saves a sixth of all multiply-adds (20 x 176,400, 168
-// bins, a fifth: 0.92; 16 x 220,500, 84 bins, a seventh: 1.19), or where it is a good part of them in a large batch (168 bins, a third:
-// 20,700 frames 1.05, 55,200 0.95, 610,650 0.88; 72 bins at hop 256, a fifth, 112,060 frames: 1.14).
+// 5.12 ms, 128 4.87, 256 4.87, 1 GB 4.76); zero: it does as well without.  Two launches instead of one (time over the one launch's, 624 calls of
+// 200 to 400,000 frames, hops of 128 to 1,024, 12 to 36 bins per octave) by what the first stage's multiply-adds come to, done once, its workgroups'
+// spare row blocks counted:
+// - nothing runs beside the items with a basis: where they get no more (0.52 .. 1.05; more: 0.89 .. 1.10), or bases are of five row blocks and
+//   more (0.52 .. 0.96: such tiles leave a compute unit one workgroup);
+// - the one launch's items are more than reside at once, what neighbouring tiles share is a sixth of all and a tenth is saved: 0.58 .. 1.04
+//   (fewer items 0.74 .. 1.45: the second launch waits for the first; less saved 0.9 .. 1.28);
+// - a large batch, the first stage 0.3 of all, a tenth of all more multiply-adds at most and four groups of bins or more that each read every
+//   sample: 0.80 .. 1.03 (a smaller stage up to 1.08, fewer groups 0.97 .. 1.14, more multiply-adds 0.75 .. 1.05); at hops of 1,024 and more
+//   either of the last two will do: 0.63 .. 0.95 (neither: 1.05, 1.06).
 size_t lowrank_workspace(const nna_plan* sub, long long B, long long L, long long T) {
   nna::CqlParams P;
   std::memset(&P, 0, sizeof(P));
@@ -487,10 +501,18 @@ size_t lowrank_workspace(const nna_plan* sub, long long B, long long L, long lon
     once += each * (T + it.jspan - 1.0) / T;
     second += 256.0 * (it.n_step + it.s_hi - it.s_lo) * 64 * P.basis.fb / M;
   }
-  const double all = first + second + sub->lr_direct;
-  if (P.direct.n_items && first - once < all / 6 && (B * T < 50000 || first < 0.28 * all)) return 0;
-  int blocks, j0, j1;
-  const long long bytes = 4 * coordinates_of(sub, T, blocks, j0, j1);
+  int blocks, j0, j1, nb, groups;
+  const long long floats = coordinates_of(sub, T, blocks, j0, j1);
+  shape_project(B * (T + j1 - j0 - 1), blocks, nb, groups);
+  const int slots = groups * (blocks <= 12 * groups ? 12 : 24);
+  const double all = first + second + sub->lr_direct, saved = first - once * slots / blocks;
+  const int items = P.basis.n_items;
+  const bool pays = !P.direct.n_items ? saved >= 0 || blocks >= 5 * items
+                    : (first - once >= all / 6 && saved >= all / 10 && P.basis.n_ft * items >= 512) ||
+                          (B * T >= 50000 && first >= 0.3 * all &&
+                           (sub->hop >= 1024 ? items >= 4 || saved >= -all / 10 : items >= 4 && saved >= -all / 10));
+  if (!pays) return 0;
+  const long long bytes = 4 * floats;
   constexpr long long most = 256LL << 20;
   return bytes > most ? 0 : (size_t)(bytes * std::min(B, most / bytes));
 }
@@ -545,11 +567,7 @@ nna_status run_conv_lowrank(const nna_plan* sub, const float* x, long long B, lo
     P.y_j0 = j0;
     P.y_rows = (int)T + j1 - j0 - 1;
     P.y_blocks = blocks;
-    // 32 hop-blocks and twelve row blocks a workgroup fill the chip sooner (16 x 220,500 samples, 84 dense kernels: 33 us; 24 row blocks 41, 64
-    // hop-blocks 42, both 50); twice as many of both read the weights half as often
-    P.y_nb = B * P.y_rows >= 64 * 512 ? 4 : 2;
-    const int each = P.y_nb == 4 ? 24 : 12;
-    P.y_groups = (blocks + each - 1) / each;
+    shape_project(B * P.y_rows, blocks, P.y_nb, P.y_groups);
     // the coordinates' words, and the waves' sums where they keep the workgroup in half a CU's LDS, or all of it
     int words = 0;
     const long long nseg = 1 + (P.basis.tile_frames - 1 + T - 1) / T;

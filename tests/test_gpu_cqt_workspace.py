@@ -162,3 +162,13 @@ def test_replays(nb, by_torch):
         del taken
     if not by_torch:
         assert hip.hipGraphExecDestroy(run) == 0 and hip.hipGraphDestroy(graph) == 0
+
+
+# calls where two launches took 0.60 .. 0.94 of one's time, and where they took 1.06 .. 1.45
+@pytest.mark.parametrize("sr,hop,fmin,n_bins,bpo,B,L,two", [
+    (44100, 512, 32.7, 168, 24, 1770, 176400, True), (44100, 256, 32.7, 216, 36, 4, 225000, True), (22050, 1024, 32.7, 119, 24, 304, 1048000, True),
+    (44100, 512, 32.7, 120, 24, 1, 794193, False), (22050, 256, 27.5, 119, 24, 1, 197033, False), (44100, 512, 32.7, 287, 36, 1, 249585, False),
+    (44100, 512, 32.7, 84, 12, 122, 512000, False), (22050, 1024, 32.7, 67, 12, 461, 245013, False), (44100, 256, 27.5, 59, 12, 656, 37448, False)])
+def test_two_launches_where_they_pay(nb, sr, hop, fmin, n_bins, bpo, B, L, two):
+    plan = nb.nna_plan_cqt(sr=sr, hop=hop, fmin=fmin, n_bins=n_bins, bins_per_octave=bpo, device=0)
+    assert (nb.nna_cqt_workspace(plan, B, L) > 0) == two
