@@ -23,6 +23,20 @@ def _both(nb, plan, x, floats):
     return nb.nna_cqt_in_workspace(plan, x, ws).cpu().numpy(), _one_launch(nb, plan, x).cpu().numpy()
 
 
+def _written(ws):
+    """Words of a workspace that was all NaN up to the last one that a call wrote."""
+    at = (~ws.isnan()).nonzero()
+    return int(at[-1]) + 1 if len(at) else 0
+
+
+def _floats_of_a_waveform(nb, plan, x):
+    import torch
+    ws = torch.full((1 << 24,), float("nan"), device="cuda:0")
+    nb.nna_cqt_in_workspace(plan, x[:1], ws)
+    assert 0 < _written(ws) < len(ws)
+    return _written(ws)
+
+
 @pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}x{c[3]}-{c[6]}x{c[7]}")
 def test_against_one_launch(nb, case):
     import torch
@@ -33,9 +47,15 @@ def test_against_one_launch(nb, case):
         plan = nb.nna_plan_cqt(sr=sr, hop=hop, fmin=fmin, n_bins=n_bins, bins_per_octave=bpo, n_taps=n_taps, center=center, fmt=fmt, device=0)
         got, ref = _both(nb, plan, x, 1 << 24)
         assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
-        if B > 2:  # in parts: what a third of the waveforms needs, at most 140 functions of every hop-block
-            got, ref = _both(nb, plan, x, (B // 3) * 140 * (L // hop + 200))
+        for share in {B // 3, 2 * B // 3} - {0}:  # in parts of unequal size where B is no multiple of them
+            parts = -(-B // share)
+            each = _floats_of_a_waveform(nb, plan, x)
+            assert share < B and parts > 1
+            ws = torch.full((share * each,), float("nan"), device="cuda:0")
+            got = nb.nna_cqt_in_workspace(plan, x, ws).cpu().numpy()
             assert np.abs(got - ref).max() <= TOL * np.abs(ref).max()
+            # the coordinates of the largest part, every word of them, and no more
+            assert _written(ws) == -(-B // parts) * each and not ws[:-(-B // parts) * each].isnan().any()
         got, ref = _both(nb, plan, x, 16)  # not one waveform's: not used
         assert np.array_equal(got, ref)
 
