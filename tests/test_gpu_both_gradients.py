@@ -7,6 +7,22 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+def _gradients_64(x, W, gout, hop):
+    """Of complex output: the bank's and the waveform's gradient, in 64 bits."""
+    import torch
+    (B, L), K, T = x.shape, W.shape[1], gout.shape[2]
+    at = torch.arange(T, device=x.device)[:, None] * hop + torch.arange(K, device=x.device) - K // 2
+    at = at.abs()
+    at = torch.where(at >= L, 2 * (L - 1) - at, at)
+    gw, gx = torch.zeros(W.shape, dtype=torch.float64, device=x.device), torch.zeros(x.shape, dtype=torch.float64, device=x.device)
+    for b in range(B):
+        g = gout[b].double()
+        gw += g @ x[b].double()[at]
+        gx[b].index_add_(0, at.reshape(-1), (g.T @ W.double()).reshape(-1))
+    gw[[1, -1]] = 0  # the imaginary kernels of bins 0 and n_fft / 2 are zero and no parameters
+    return gw, gx
+
+
 # n_fft, hop, B, L: 256 + 176 tiles; a bank of few tiles in pieces beside a wave of few; more than one launch takes; one frame
 @pytest.mark.parametrize("n_fft,hop,B,L", [(2048, 512, 16, 44217), (512, 160, 5, 9001), (1024, 256, 3, 5001), (512, 128, 120, 40001), (256, 256, 1, 129)])
 def test_both_against_each(n_fft, hop, B, L):
@@ -27,7 +43,7 @@ def test_both_against_each(n_fft, hop, B, L):
 @pytest.mark.parametrize("sr,hop,fmin,n_bins,bpo,B,L", [(8000, 128, 300.0, 5, 12, 1, 4001), (22050, 512, 65.4, 60, 12, 2, 30001), (16000, 256, 60.0, 84, 24, 3, 20000),
                                                         (16000, 96, 80.0, 30, 12, 2, 9000)])
 def test_waveform_gradient_in_parts(sr, hop, fmin, n_bins, bpo, B, L):
-    """A few waveforms' gradients, alone and in a batch whose tiles are taken whole: the same products, added in up to 16 parts."""
+    """A few waveforms' gradients against 64 bits and against a batch whose tiles are taken whole: the same products, added in up to 16 parts."""
     import torch
     from paper_1912_12055_amd import binding as nb
     print(f"[case] waveform gradient in parts {sr} {hop} {n_bins} {B}x{L}", file=sys.stderr, flush=True)
@@ -37,27 +53,13 @@ def test_waveform_gradient_in_parts(sr, hop, fmin, n_bins, bpo, B, L):
     x = torch.randn((B, L), generator=gen).cuda()
     gout = torch.randn(tuple(nb.nna_cqt(plan, x).shape), generator=gen).cuda()
     few = nb.nna_cqt_backward(plan, x, gout, want_gw=False)[1]
+    # sums of up to 2 n_bins x 100 shifts in chains: a chain of n roundings is off by sqrt(n) 2^-24 of its terms' norm
+    _, ref = _gradients_64(x, nb.nna_plan_get_bank(plan), gout, hop)
+    assert (few - ref).abs().max() <= 2e-6 * ref.abs().max()
     n = 520 // B + 1
     many = nb.nna_cqt_backward(plan, x.repeat(n, 1), gout.repeat(n, 1, 1), want_gw=False)[1]
-    # sums of up to 2 n_bins x 100 shifts in chains: a chain of n roundings is off by sqrt(n) 2^-24 of its terms' norm
     assert (few - many[:B]).abs().max() <= 2e-6 * many.abs().max()
     assert (few - many[-B:]).abs().max() <= 2e-6 * many.abs().max()
-
-
-def _gradients_64(x, W, gout, hop):
-    """Of complex output: the bank's and the waveform's gradient, in 64 bits."""
-    import torch
-    (B, L), K, T = x.shape, W.shape[1], gout.shape[2]
-    at = torch.arange(T, device=x.device)[:, None] * hop + torch.arange(K, device=x.device) - K // 2
-    at = at.abs()
-    at = torch.where(at >= L, 2 * (L - 1) - at, at)
-    gw, gx = torch.zeros(W.shape, dtype=torch.float64, device=x.device), torch.zeros(x.shape, dtype=torch.float64, device=x.device)
-    for b in range(B):
-        g = gout[b].double()
-        gw += g @ x[b].double()[at]
-        gx[b].index_add_(0, at.reshape(-1), (g.T @ W.double()).reshape(-1))
-    gw[[1, -1]] = 0  # the imaginary kernels of bins 0 and n_fft / 2 are zero and no parameters
-    return gw, gx
 
 
 # 256 + 176 tiles of 44 and 64 chunks; 16 + 440 of 440 and 16; 64 + 448 of 192 and 32; 6 + 378 of 504 and 8
