@@ -84,3 +84,25 @@ def test_mel_bands_and_their_spectrogram(nb, n_fft, hop, B, L, n_mels, power):
     assert _err(mel, ref) < TOL
     fmt = oracle.POWER if power == 2.0 else oracle.MAGNITUDE
     assert _err(spec, oracle.stft(x, n_fft=n_fft, hop=hop, fmt=fmt)) < TOL
+
+
+# one frame in twenty reaches past an end, and more: the same frames from either launch
+@pytest.mark.parametrize("n_fft", [64, 256, 1024, 2048, 4096])
+@pytest.mark.parametrize("kind", ["POWER", "COMPLEX", "MEL"])
+def test_frames_at_the_ends_few_or_many(nb, n_fft, kind):
+    import torch
+    print(f"[case] fft ends {n_fft} {kind}", file=sys.stderr, flush=True)
+    hop = n_fft // 4
+    L = {T: (T - 1) * hop for T in (79, 80)}  # four frames reach past an end
+    x = torch.from_numpy(_wave(n_fft, 3, L[80])).to("cuda:0")
+    if kind == "MEL":
+        plan = nb.nna_plan_mel(n_fft=n_fft, hop=hop, n_mels=12, device=0)
+    else:
+        plan = nb.nna_plan_stft(n_fft=n_fft, hop=hop, fmt=getattr(nb, "NNA_OUT_" + kind), device=0)
+    run = nb.nna_mel if kind == "MEL" else nb.nna_stft
+    few, many = run(plan, x), run(plan, x[:, :L[79]].contiguous())
+    assert few.shape[2] == 80 and many.shape[2] == 79
+    assert torch.equal(few[:, :, :77], many[:, :, :77])
+    if kind == "POWER":
+        ref = oracle.stft_complex(x[:, :L[79]].cpu().numpy(), n_fft=n_fft, hop=hop, window=oracle.WIN_HANN)
+        assert _err(many, ref[0] ** 2 + ref[1] ** 2) < TOL
