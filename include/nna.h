@@ -272,7 +272,7 @@ nna_status nna_cqt(const nna_plan* plan, const float* x_dev, long long B, long l
                    void* hip_stream);
 
 /* nna_cqt or nna_cqt1992, by the plan's kind, with device memory of the caller's in which the hop-blocks' coordinates are kept from a first
- * launch to a second: the same outputs, sooner.  nna_cqt_workspace: the bytes a call can use (at most 256 MiB; 0: it does as well without).
+ * launch to a second: the same outputs, but for the last bits of sums taken in another order, sooner.  nna_cqt_workspace: the bytes a call can use (at most 256 MiB; 0: it does as well without).
  * Less is used as far as it goes; a workspace that is NULL or not aligned to 16 bytes is not.  A workspace serves one call at a time. */
 nna_status nna_cqt_workspace(const nna_plan* plan, long long B, long long L, size_t* bytes);
 nna_status nna_cqt_in_workspace(const nna_plan* plan, const float* x_dev, long long B, long long L, float* out_dev, void* workspace_dev,
@@ -350,8 +350,8 @@ nna_status nna_cqt2010(const nna_plan* plan, const float* x_dev, long long B, lo
  *                     Both outputs are overwritten (zeroed, then accumulated with float atomic adds:
  *                     the last bits may differ between runs).  workspace_dev: caller-owned device
  *                     memory, 256-byte aligned, of nna_stft_backward_workspace bytes (G itself:
- *                     128-row-padded bank rows x frames x 4 bytes); nothing is allocated, four to
- *                     six kernels are enqueued on hip_stream.  The forward pass is recomputed inside,
+ *                     128-row-padded bank rows x frames x 4 bytes); nothing is allocated, three to
+ *                     five kernels are enqueued on hip_stream.  The forward pass is recomputed inside,
  *                     so nothing needs to be kept from nna_stft.
  * Errors: NNA_ERR_INVALID_ARG for a plan of another kind or one not made trainable, NULL pointers, a
  * small or misaligned workspace; NNA_ERR_UNSUPPORTED for float16 or host-only plans; NNA_ERR_SHAPE as

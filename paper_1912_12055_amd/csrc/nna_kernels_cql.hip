@@ -35,7 +35,7 @@
 // 16 x 220,500, 84 bins of 12 per octave: 300 -> 67.8 -> 53.8 us; the dense composed kernels of the frequency-domain layer (16 x
 // 220,500, 16,384 taps): 566 -> 183 -> 138 us.  With the short kernels by tiles of nna_short.h (the direct items read four row blocks' weights for
 // every 16 frames, and the loads' issue bound them): 5.81 -> 5.12 ms, 58 -> 46 us.  In two
-// launches: the batch 5.2 -> 4.7 ms, the dense kernels 134 -> 81 us.
+// launches: the batch 5.34 -> 4.75 ms, the dense kernels 134 -> 81 us.
 #include <type_traits>
 
 #include "nna_short.h"
@@ -750,8 +750,8 @@ __device__ __host__ inline long long g_rows(const CqlParams& P) { return P.g.B *
 // Stage 1 by itself: every hop-block's coordinates of all items, once.  A workgroup takes 16 NB hop-blocks and a part of the bases' row
 // blocks; the samples are split once, on the way into LDS, 64 columns at a time, and each wave multiplies every fourth row block with all
 // of them, so that a workgroup reads its weights once.  The sums are those of lowrank_item, in the same order.  lowrank_item itself reads and
-// splits every sample for each 16 bins, and for every tile whose frames reach it: 2.2 ms of 5.5 at 1,770 x 176,400 samples, 168 bins; here 1.5 ms
-// (41 % of the matrix pipe's peak; weights from the L2s at 31 bytes a cycle and CU), the call 5.5 -> 4.87.  16 x 220,500, 84 dense kernels of
+// splits every sample for each 16 bins, and for every tile whose frames reach it: 2.2 ms of 5.34 at 1,770 x 176,400 samples, 168 bins; here 1.5 ms
+// (41 % of the matrix pipe's peak; weights from the L2s at 31 bytes a cycle and CU), the call 4.75.  16 x 220,500, 84 dense kernels of
 // 16,384 taps: 137 -> 86 us, of which 33 here.
 constexpr int PJ_COLS = 64, PJ_PITCH = PJ_COLS + 8;  // (rows of 36 words: sixteen of them on different banks, four words each)
 constexpr int PJ_LDS(int nb) { return 2 * 3 * 16 * nb * PJ_PITCH * 2; }

@@ -492,7 +492,8 @@ __global__ __launch_bounds__(512, 2) void fft_kernel(FftParams P) {
   // the stores of the step before.  Waited for once, before the loop: 1 x 3,969,031 samples, N = 1,024, complex, 31.0 -> 29.6 us; Mel 64 x
   // 110,250, N = 2,048, 38.4 -> 37.0; 1,770 x 80,000, N = 4,096, 512 bands, 1.59 -> 1.52 ms; magnitudes, N = 256, 500 x 176,400, 436 -> 397 us.
   // Longer rows are the exception: waves that run ahead of their stores spread the halves of a line over more time, and rows that begin anywhere
-  // in a line take 1.51 ms for 1.35 (N = 2,048, 1,770 x 345 frames) and 1.27 for 0.91 (N = 4,096, 500 x 345); of 352 frames 1.19 for 1.33.
+  // in a line take 1.51 ms for 1.35 (N = 2,048, 1,770 x 345 frames) and 1.27 for 0.91 (N = 4,096, 500 x 345).  (Rows of whole lines gain: of 352 frames
+  // 1.19 for 1.33.  They run as the others of their window.)
   if constexpr (MODE == FFT_MODE_MEL || M < 1024) __builtin_amdgcn_s_waitcnt(0x0f70);
   float *cur = tile, *old = tile + P.buf_words;
   for (long long tile_i = lo; tile_i < hi; tile_i += stride) {

@@ -300,7 +300,8 @@ __device__ __forceinline__ f32x4 load_g4(const float* __restrict__ gbuf, long lo
 // a contraction over (row r, shift j) pairs whose A operand is G read j frames back.  Rows go in chunks
 // of CW_KC, the outer loop; for one chunk the frames q0 - j .. q0 - j + 127 of all its shifts form
 // one window of G that stays in LDS while only W tiles stream.  Each padded sample is added once
-// by every part of a tile's pairs that the launch makes workgroups of (gridDim.y).
+// by every part of a tile's pairs that the launch makes workgroups of (gridDim.y), in any order: the last
+// bits of a short batch's gradient differ from run to run, as those of the other gradients do.
 constexpr int CW_SEG = BW_MT;             // shifts served by one window
 constexpr int CW_WIN = BW_MT + CW_SEG;    // frames in the window (128 tile rows + up to 127 shifts, rounded up)
 constexpr int CW_PA = CW_WIN + 4;         // its LDS pitch
@@ -537,9 +538,9 @@ __device__ __forceinline__ f32x4 load4_guarded(const float* row, int c, int lim)
 
 constexpr int MEL_BW_SPEC = 0, MEL_BW_WEIGHTS = 1;
 
-// 128 x 128 tiles, 2 x 2 waves of 64 x 64 (v_mfma_f32_32x32x2_f32); a chunk of 32 contraction indices is requested while the one before is
-// multiplied (asked for and waited for in turn, 13,824 frames of 1,025 bins: 128 bands from the spectrogram 128 us, the spectrogram's gradient
-// 62; now 50 and 47; the filters' gradient stays at 92).
+// 128 x 128 tiles, 2 x 2 waves of 64 x 64 (v_mfma_f32_32x32x2_f32).  Of the first a chunk of 32 contraction indices is requested while the one
+// before is multiplied (asked for and waited for in turn, 13,824 frames of 1,025 bins: 128 bands from the spectrogram 128 us, the spectrogram's
+// gradient 62; now 50 and 47).  The filters' gradient asks and waits in turn: 91 us; ahead 112, or 93 in half the workgroups, whose sums are longer.
 //   MEL_BW_SPEC:    C[k, f]                 A = W[m][k] (k-major: row = contraction index), B = g[b][m][t] (k-major)
 //   MEL_BW_WEIGHTS: C[m, k]                 A = g[b][m][t], B = P[b][k][t] (both: row = output index, contraction contiguous)
 // NT: columns of a tile; 64 where those of 128 are fewer than the compute units (a step, 3 x 60,000, 229 bands: 294 -> 225 us).
