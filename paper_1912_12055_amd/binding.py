@@ -439,7 +439,9 @@ def _memory_on(stream, need: int, device):
 
     if stream is None and device.index == torch.cuda.current_device():
         return _outlives_capture(torch.empty(need, dtype=torch.uint8, device=device))
-    if stream in (1, 2):  # HIP's names for the default stream and for every thread's own: no streams that torch has an allocator for
+    # HIP's names for the default stream (1) and for every thread's own (2) are no streams that torch has an allocator for; a handle may also
+    # come as a ctypes pointer
+    if stream is not None and (not isinstance(stream, int) or stream in (1, 2)):
         return None
     # (ExternalStream takes 0, the default stream's handle, for "none given" and is then another stream, of torch's pool)
     on = (torch.cuda.current_stream(device) if stream is None else

@@ -1,6 +1,7 @@
 """Where the constant-Q calls of the binding take their workspace from, without a GPU: torch's streams and allocator and the library's calls
 are stand-ins that record what is asked of them."""
 import contextlib
+import ctypes
 
 import pytest
 import torch
@@ -42,6 +43,8 @@ def calls(monkeypatch):
         pool = 0x1000
 
         def __init__(self, stream_ptr, device=None):
+            if not isinstance(stream_ptr, int):
+                raise TypeError("an integer is required")
             # as torch's: no handle given, the next stream of the pool
             type(self).pool += 16
             self.cuda_stream = stream_ptr or type(self).pool
@@ -92,8 +95,8 @@ def test_memory_is_of_the_stream_the_call_runs_on(calls, stream):
     assert ran == taken == (0x700 if stream is None else stream)
 
 
-# HIP's handles for "the default stream" and "this thread's stream" are no streams of torch's
-@pytest.mark.parametrize("stream", [1, 2])
+# HIP's handles for "the default stream" and "this thread's stream" are no streams of torch's; a handle that is not a number
+@pytest.mark.parametrize("stream", [1, 2, ctypes.c_void_p(0x5550)], ids=str)
 def test_handles_that_name_no_one_stream_take_no_memory(calls, stream):
     nb.nna_cqt(calls["plan"], calls["x"], stream=stream)
     assert calls["calls"] == [("nna_cqt", stream, None)]
