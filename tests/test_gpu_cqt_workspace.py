@@ -192,3 +192,21 @@ def test_replays(nb, by_torch):
 def test_two_launches_where_they_pay(nb, sr, hop, fmin, n_bins, bpo, B, L, two):
     plan = nb.nna_plan_cqt(sr=sr, hop=hop, fmin=fmin, n_bins=n_bins, bins_per_octave=bpo, device=0)
     assert (nb.nna_cqt_workspace(plan, B, L) > 0) == two
+
+
+# a batch that the tiles take, in parts that they don't, and in parts short enough that they do again
+@pytest.mark.parametrize("share,in_parts", [(40, False), (16, True)])
+def test_parts_too_short_for_the_tiles(nb, share, in_parts):
+    import torch
+    plan = nb.nna_plan_cqt(sr=8000, hop=64, fmin=56.0, n_bins=60, bins_per_octave=24, device=0)
+    B, L = 80, 32768
+    print(f"[case] cqt workspace parts of {share}", file=sys.stderr, flush=True)
+    assert nb.nna_plan_applied_tiles(plan, B, L)[0][0] and bool(nb.nna_plan_applied_tiles(plan, share, L)[0][0]) == in_parts
+    x = torch.randn((B, L), generator=torch.Generator().manual_seed(9)).cuda()
+    each = _floats_of_a_waveform(nb, plan, x)
+    ws = torch.full((share * each,), float("nan"), device="cuda:0")
+    got, ref = nb.nna_cqt_in_workspace(plan, x, ws), _one_launch(nb, plan, x)
+    if in_parts:
+        assert _written(ws) == share * each and (got - ref).abs().max() <= TOL * ref.abs().max()
+    else:  # one launch, without the workspace
+        assert _written(ws) == 0 and torch.equal(got, ref)
